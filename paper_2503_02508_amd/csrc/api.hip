@@ -17,6 +17,8 @@ namespace qc {
 constexpr int MAX_LANES = 4;
 // rows of the conditioning tables: the conditioning of several sampler steps is prepared in one go
 constexpr int WINDOW_ROWS = 512;
+// token rows of one group of the un-quantised forward
+constexpr size_t CAL_ROWS = 1024;
 
 // a contiguous range of the (effective) batch handled by one stream; `lane` picks its private scratch
 struct Sub {
@@ -100,8 +102,9 @@ struct qc_ctx {
   int win_rows;               // row capacity of cond / fmod / mod / silu_q (per block for the last two)
   bool keep_qkv_f32 = false;
   bool stream_bf16 = false;   // the network-level calls keep the residual stream (tokens) as bfloat16
-  // calibration scratch (one sample)
-  float *cal_h, *cal_o, *cal_a, *cal_u, *cal_mod;
+  // scratch of the un-quantised forward (calibration, VC fit), which runs cal_group samples at a time
+  int cal_group;
+  float *cal_h, *cal_o, *cal_a, *cal_u, *cal_mod, *cal_cond;
   int *cal_slots, *cal_label;
   bool weights_loaded;
   // a denoiser call may run its batch as up to MAX_LANES independent sub-batches on internal streams
@@ -214,9 +217,12 @@ static size_t layout(const qc_model_desc &d, int max_batch, char *base, qc_ctx *
   const size_t hd = D / d.heads, DP = (hd + 15) / 16 * 16, Tp = (T + 63) / 64 * 64;
   const size_t part = B * d.heads * T * hd, vpart = B * d.heads * DP * Tp;
   float *qkv_hm = a.take<float>(2 * part + vpart);
-  float *cal_h = a.take<float>(T * D), *cal_o = a.take<float>(T * D), *cal_a = a.take<float>(T * D);
-  float *cal_u = a.take<float>(T * R), *cal_mod = a.take<float>(6 * D);
-  int *cal_slots = a.take<int>(L * QC_NUM_SITES * 2), *cal_label = a.take<int>(4);
+  // The un-quantised forward takes as many samples at once as make CAL_ROWS token rows (at least one): its products then
+  // read the float32 weights once per group
+  const size_t G = std::max<size_t>(1, std::min<size_t>(B, CAL_ROWS / T)), GT = G * T;
+  float *cal_h = a.take<float>(GT * D), *cal_o = a.take<float>(GT * D), *cal_a = a.take<float>(GT * D);
+  float *cal_u = a.take<float>(GT * R), *cal_mod = a.take<float>(G * 6 * D), *cal_cond = a.take<float>(G * D);
+  int *cal_slots = a.take<int>(L * QC_NUM_SITES * 2), *cal_label = a.take<int>(G);
   float *eps_ref = a.take<float>(B * C * d.latent_h * d.latent_w);
   double *vcfit_work = a.take<double>(B * C * 2);
   int *dev_flags = a.take<int>(64);
@@ -226,6 +232,7 @@ static size_t layout(const qc_model_desc &d, int max_batch, char *base, qc_ctx *
     c->dev_qp = dev_qp; c->cache = cache; c->emb = emb; c->h1 = h1; c->te = te; c->cond = cond; c->mod = mod; c->fmod = fmod;
     c->tokens = tokens; c->qkv = qkv; c->eps = eps; c->silu_q = silu_q; c->qa_ln = qa_ln; c->qa_attn = qa_attn;
     c->qa_mlp = qa_mlp; c->cal_h = cal_h; c->cal_o = cal_o; c->cal_a = cal_a; c->cal_u = cal_u; c->cal_mod = cal_mod;
+    c->cal_cond = cal_cond; c->cal_group = (int)G;
     c->cal_slots = cal_slots; c->cal_label = cal_label; c->eps_ref = eps_ref; c->vcfit_work = vcfit_work; c->dev_flags = dev_flags;
     c->qkv_hm = qkv_hm; c->qkv_part_stride = (long long)part;
     c->qkv_hm_bytes = (2 * part + vpart) * sizeof(float); c->DP = (int)DP; c->Tp = (int)Tp;
@@ -952,31 +959,31 @@ static inline float ord2f(int i) {
 
 }  // extern "C"
 
-// Un-quantised fp32 forward of one sample through all blocks (the network the quantiser parameters are
-// calibrated on and the reference the VC factors are fitted against): tokens must hold the embedded sample,
-// cond the sample's conditioning vector.  With slots != null the min / max of the five quantiser sites of
+// Un-quantised fp32 forward of g samples through all blocks (the network the quantiser parameters are
+// calibrated on and the reference the VC factors are fitted against): tokens must hold the embedded samples,
+// cond their conditioning vectors [g, D].  With slots != null the min / max of the five quantiser sites of
 // every block are folded into slots[l][site][2].
-static int fp32_blocks_one(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int *slots, hipStream_t st) {
-  const int D = ctx->D, R = ctx->R, T = ctx->T, L = ctx->L;
+static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int g, int *slots, hipStream_t st) {
+  const int D = ctx->D, R = ctx->R, T = ctx->T, L = ctx->L, M = g * T;
   for (int l = 0; l < L; ++l) {
     const qc_block_weights_f32 &b = w->blocks[l];
     int *slot = slots ? slots + (size_t)l * QC_NUM_SITES * 2 : nullptr;
     float *mod = ctx->cal_mod;
-    if (slot) QC_HIP(launch_minmax_silu(cond, D, slot + 2 * QC_SITE_ADA, st));
-    QC_HIP(launch_small_linear(cond, D, b.ada_w, b.ada_b, mod, 6 * D, 1, 6 * D, D, 1, 0, st));
-    QC_HIP(launch_ln_mod_quant(ctx->tokens, 0, mod, mod + D, 6 * D, T, D, T, nullptr, nullptr, ctx->cal_h, st));
-    if (slot) QC_HIP(launch_minmax(ctx->cal_h, (size_t)T * D, slot + 2 * QC_SITE_QKV, st));
-    QC_HIP(launch_linear_f32(ctx->cal_h, b.qkv_w, b.qkv_b, ctx->qkv, T, 3 * D, D, 0, st));
-    QC_HIP(launch_attention(ctx->qkv, 1, T, ctx->H, ctx->hd, nullptr, nullptr, ctx->cal_o, st));
-    if (slot) QC_HIP(launch_minmax(ctx->cal_o, (size_t)T * D, slot + 2 * QC_SITE_PROJ, st));
-    QC_HIP(launch_linear_f32(ctx->cal_o, b.proj_w, b.proj_b, ctx->cal_a, T, D, D, 0, st));
-    QC_HIP(launch_cache_reuse(ctx->tokens, 0, ctx->cal_a, mod + 2 * D, 6 * D, 1, T, D, false, st));
-    QC_HIP(launch_ln_mod_quant(ctx->tokens, 0, mod + 3 * D, mod + 4 * D, 6 * D, T, D, T, nullptr, nullptr, ctx->cal_h, st));
-    if (slot) QC_HIP(launch_minmax(ctx->cal_h, (size_t)T * D, slot + 2 * QC_SITE_FC1, st));
-    QC_HIP(launch_linear_f32(ctx->cal_h, b.fc1_w, b.fc1_b, ctx->cal_u, T, R, D, 2, st));
-    if (slot) QC_HIP(launch_minmax(ctx->cal_u, (size_t)T * R, slot + 2 * QC_SITE_FC2, st));
-    QC_HIP(launch_linear_f32(ctx->cal_u, b.fc2_w, b.fc2_b, ctx->cal_a, T, D, R, 0, st));
-    QC_HIP(launch_cache_reuse(ctx->tokens, 0, ctx->cal_a, mod + 5 * D, 6 * D, 1, T, D, false, st));
+    if (slot) QC_HIP(launch_minmax_silu(cond, (size_t)g * D, slot + 2 * QC_SITE_ADA, st));
+    QC_HIP(launch_small_linear(cond, D, b.ada_w, b.ada_b, mod, 6 * D, g, 6 * D, D, 1, 0, st));
+    QC_HIP(launch_ln_mod_quant(ctx->tokens, 0, mod, mod + D, 6 * D, M, D, T, nullptr, nullptr, ctx->cal_h, st));
+    if (slot) QC_HIP(launch_minmax(ctx->cal_h, (size_t)M * D, slot + 2 * QC_SITE_QKV, st));
+    QC_HIP(launch_linear_f32(ctx->cal_h, b.qkv_w, b.qkv_b, ctx->qkv, M, 3 * D, D, 0, st));
+    QC_HIP(launch_attention(ctx->qkv, g, T, ctx->H, ctx->hd, nullptr, nullptr, ctx->cal_o, st));
+    if (slot) QC_HIP(launch_minmax(ctx->cal_o, (size_t)M * D, slot + 2 * QC_SITE_PROJ, st));
+    QC_HIP(launch_linear_f32(ctx->cal_o, b.proj_w, b.proj_b, ctx->cal_a, M, D, D, 0, st));
+    QC_HIP(launch_cache_reuse(ctx->tokens, 0, ctx->cal_a, mod + 2 * D, 6 * D, g, T, D, false, st));
+    QC_HIP(launch_ln_mod_quant(ctx->tokens, 0, mod + 3 * D, mod + 4 * D, 6 * D, M, D, T, nullptr, nullptr, ctx->cal_h, st));
+    if (slot) QC_HIP(launch_minmax(ctx->cal_h, (size_t)M * D, slot + 2 * QC_SITE_FC1, st));
+    QC_HIP(launch_linear_f32(ctx->cal_h, b.fc1_w, b.fc1_b, ctx->cal_u, M, R, D, 1, st));
+    if (slot) QC_HIP(launch_minmax(ctx->cal_u, (size_t)M * R, slot + 2 * QC_SITE_FC2, st));
+    QC_HIP(launch_linear_f32(ctx->cal_u, b.fc2_w, b.fc2_b, ctx->cal_a, M, D, R, 0, st));
+    QC_HIP(launch_cache_reuse(ctx->tokens, 0, ctx->cal_a, mod + 5 * D, 6 * D, g, T, D, false, st));
   }
   return QC_OK;
 }
@@ -991,12 +998,13 @@ static int denoise_f32_impl(qc_ctx *ctx, const qc_weights_f32 *w, const float *x
   int rc = run_cond(ctx, &t32, 1, labels, n_labels, B, st);
   if (rc) return rc;
   QC_HIP(launch_small_linear(ctx->cond, D, ctx->fada_w, ctx->fada_b, ctx->fmod, 2 * D, B, 2 * D, D, 1, 0, st));
-  for (int b = 0; b < B; ++b) {
-    QC_HIP(launch_embed(x, ctx->patch_w, ctx->patch_b, ctx->pos, ctx->tokens, 0, 1, n_src, ctx->C, ctx->d.latent_h, ctx->d.latent_w,
+  for (int b = 0; b < B; b += ctx->cal_group) {
+    const int g = std::min(ctx->cal_group, B - b);
+    QC_HIP(launch_embed(x, ctx->patch_w, ctx->patch_b, ctx->pos, ctx->tokens, 0, g, n_src, ctx->C, ctx->d.latent_h, ctx->d.latent_w,
                         ctx->d.patch, D, b, st));
-    rc = fp32_blocks_one(ctx, w, ctx->cond + (size_t)b * D, nullptr, st);
+    rc = fp32_blocks(ctx, w, ctx->cond + (size_t)b * D, g, nullptr, st);
     if (rc) return rc;
-    QC_HIP(launch_final(ctx->tokens, 0, ctx->fmod + (size_t)b * 2 * D, ctx->flin_w, ctx->flin_b, eps_out + b * lat, 1, ctx->C,
+    QC_HIP(launch_final(ctx->tokens, 0, ctx->fmod + (size_t)b * 2 * D, ctx->flin_w, ctx->flin_b, eps_out + b * lat, g, ctx->C,
                         ctx->d.latent_h, ctx->d.latent_w, ctx->d.patch, D, st));
   }
   return QC_OK;
@@ -1027,15 +1035,19 @@ int qc_calibrate_minmax(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, co
   QC_HIP(hipMemcpyAsync(ctx->cal_slots, init.data(), init.size() * sizeof(int), hipMemcpyHostToDevice, st));
   QC_HIP(hipStreamSynchronize(st));
   const size_t lat = (size_t)ctx->C * ctx->d.latent_h * ctx->d.latent_w;
-  for (int i = 0; i < n; ++i) {
-    QC_HIP(hipMemcpyAsync(ctx->cal_label, &y[i], sizeof(int), hipMemcpyHostToDevice, st));
-    QC_HIP(hipStreamSynchronize(st));
-    rc = run_cond(ctx, &t[i], 1, ctx->cal_label, 1, 1, st);
-    if (rc) return rc;
-    QC_HIP(launch_embed(x + i * lat, ctx->patch_w, ctx->patch_b, ctx->pos, ctx->tokens, 0, 1, 1, ctx->C, ctx->d.latent_h,
+  for (int i = 0; i < n; i += ctx->cal_group) {
+    const int g = std::min(ctx->cal_group, n - i);
+    QC_HIP(hipMemcpyAsync(ctx->cal_label, y + i, (size_t)g * sizeof(int), hipMemcpyHostToDevice, st));
+    for (int j = 0; j < g; ++j) {            // every input has a timestep of its own
+      rc = run_cond(ctx, &t[i + j], 1, ctx->cal_label + j, 1, 1, st);
+      if (rc) return rc;
+      QC_HIP(hipMemcpyAsync(ctx->cal_cond + (size_t)j * D, ctx->cond, (size_t)D * sizeof(float), hipMemcpyDeviceToDevice, st));
+    }
+    QC_HIP(launch_embed(x + i * lat, ctx->patch_w, ctx->patch_b, ctx->pos, ctx->tokens, 0, g, g, ctx->C, ctx->d.latent_h,
                         ctx->d.latent_w, ctx->d.patch, D, 0, st));
-    rc = fp32_blocks_one(ctx, w, ctx->cond, ctx->cal_slots, st);
+    rc = fp32_blocks(ctx, w, ctx->cal_cond, g, ctx->cal_slots, st);
     if (rc) return rc;
+    QC_HIP(hipStreamSynchronize(st));        // the labels are the caller's host memory
   }
   std::vector<int> got(nslots * 2);
   QC_HIP(hipMemcpyAsync(got.data(), ctx->cal_slots, got.size() * sizeof(int), hipMemcpyDeviceToHost, st));
@@ -1050,9 +1062,12 @@ int qc_calibrate_minmax(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, co
       float zf = std::nearbyintf(-lo / s);
       z = (int)std::fmin(std::fmax(zf, 0.0f), 255.0f);
     }
-    rc = qc_set_act_qparams(ctx, (int)(i / QC_NUM_SITES), (int)(i % QC_NUM_SITES), s, z);
+    rc = check_qparam(s, z);
     if (rc) return rc;
+    ctx->host_qp[i] = QParam{s, z - 128};
+    ctx->qp_set[i] = 1;
   }
+  QC_HIP(hipMemcpy(ctx->dev_qp, ctx->host_qp.data(), nslots * sizeof(QParam), hipMemcpyHostToDevice));
   return QC_OK;
 }
 

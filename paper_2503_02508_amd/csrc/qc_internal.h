@@ -155,7 +155,7 @@ hipError_t launch_attention(const float *qkv, int B, int T, int H, int hd, const
 hipError_t launch_attention_f16(const float *q32, const float *k32, const float *vt32, int B, int T, int Tp, int H, int hd,
                                 int DPv, const QParam *qp, int8_t *q_out, hipStream_t st);
 // calibration helpers
-hipError_t launch_linear_f32(const float *x, const float *W, const float *b, float *y, int M, int N, int K, int act_out,
+hipError_t launch_linear_f32(const float *x, const float *W, const float *b, float *y, int M, int N, int K, int gelu,
                              hipStream_t st);
 hipError_t launch_minmax(const float *x, size_t n, int *slot, hipStream_t st);
 hipError_t launch_minmax_silu(const float *x, size_t n, int *slot, hipStream_t st);

@@ -22,10 +22,6 @@ __device__ __forceinline__ int wave_sum_i(int v) {
   return v;
 }
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x)); }
-__device__ __forceinline__ float gelu_f(float v) {
-  const float k0 = 0.7978845608028654f, k1 = 0.044715f;
-  return 0.5f * v * (1.0f + tanhf(k0 * (v + k1 * v * v * v)));
-}
 // Eq. 1 on signed codes: clip(round(v / s) + z, -128, 127), z already shifted.
 __device__ __forceinline__ int quant_code(float v, float s, int z) {
   float r = rintf(v / s) + (float)z;
@@ -928,57 +924,16 @@ hipError_t launch_vc_fit(const float *x_hat, const float *x_ref, int B, int C, i
 }
 
 // ------------------------------------------------------ calibration helpers
-// Plain fp32 tiled linear y = act(x W^T + b): 64x64 tile, 16-deep slabs, 4x4 per thread.
-__global__ __launch_bounds__(256) void linear_f32_kernel(const float *__restrict__ x, const float *__restrict__ W,
-                                                         const float *__restrict__ bias, float *__restrict__ y, int M, int N,
-                                                         int K, int act_out) {
-  __shared__ float sx[16][65], sw[16][65];
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = threadIdx.x; i < 64 * 16; i += 256) {
-      const int r = i / 16, k = i % 16;
-      sx[k][r] = (m0 + r < M && k0 + k < K) ? x[(size_t)(m0 + r) * K + k0 + k] : 0.0f;
-      sw[k][r] = (n0 + r < N && k0 + k < K) ? W[(size_t)(n0 + r) * K + k0 + k] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sx[k][ty * 4 + i], b[i] = sw[k][tx * 4 + i];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  for (int i = 0; i < 4; ++i)
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < N) {
-        float v = acc[i][j] + (bias ? bias[n] : 0.0f);
-        if (act_out == 2) v = gelu_f(v);
-        y[(size_t)m * N + n] = v;
-      }
-    }
-}
-
-hipError_t launch_linear_f32(const float *x, const float *W, const float *b, float *y, int M, int N, int K, int act_out,
-                             hipStream_t st) {
-  hipLaunchKernelGGL(linear_f32_kernel, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, x, W, b, y, M, N, K, act_out);
-  return hipGetLastError();
-}
-
 // Running min / max of a tensor kept as order-preserving integers:
 // slot[0] = min, slot[1] = max; act = 1 takes SiLU of the values first.
 __device__ __forceinline__ int f2ord(float f) {
   int i = __float_as_int(f);
   return i ^ ((i >> 31) & 0x7FFFFFFF);
 }
+// One pair of atomics per workgroup and at most 256 workgroups: atomics on one address are carried out one after the other
+// (8192 of them, one pair per wavefront of 1024 workgroups, took 77 us of a call's 77).
 __global__ __launch_bounds__(256) void minmax_kernel(const float *__restrict__ x, size_t n, int act, int *slot) {
+  __shared__ float red[2][4];
   float lo = INFINITY, hi = -INFINITY;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
@@ -989,26 +944,30 @@ __global__ __launch_bounds__(256) void minmax_kernel(const float *__restrict__ x
   }
   hi = wave_max(hi);
   lo = -wave_max(-lo);
-  if ((threadIdx.x & 63) == 0 && lo <= hi) {
-    atomicMin(slot, f2ord(lo));
-    atomicMax(slot + 1, f2ord(hi));
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = lo;
+    red[1][threadIdx.x >> 6] = hi;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    lo = fminf(fminf(red[0][0], red[0][1]), fminf(red[0][2], red[0][3]));
+    hi = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3]));
+    if (lo <= hi) {
+      atomicMin(slot, f2ord(lo));
+      atomicMax(slot + 1, f2ord(hi));
+    }
   }
 }
 
-hipError_t launch_minmax(const float *x, size_t n, int *slot, hipStream_t st) {
+static hipError_t launch_minmax_act(const float *x, size_t n, int act, int *slot, hipStream_t st) {
   size_t blocks = (n + 255) / 256;
-  if (blocks > 1024) blocks = 1024;
+  if (blocks > 256) blocks = 256;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(minmax_kernel, dim3((unsigned)blocks), dim3(256), 0, st, x, n, 0, slot);
+  hipLaunchKernelGGL(minmax_kernel, dim3((unsigned)blocks), dim3(256), 0, st, x, n, act, slot);
   return hipGetLastError();
 }
-hipError_t launch_minmax_silu(const float *x, size_t n, int *slot, hipStream_t st) {
-  size_t blocks = (n + 255) / 256;
-  if (blocks > 1024) blocks = 1024;
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(minmax_kernel, dim3((unsigned)blocks), dim3(256), 0, st, x, n, 1, slot);
-  return hipGetLastError();
-}
+hipError_t launch_minmax(const float *x, size_t n, int *slot, hipStream_t st) { return launch_minmax_act(x, n, 0, slot, st); }
+hipError_t launch_minmax_silu(const float *x, size_t n, int *slot, hipStream_t st) { return launch_minmax_act(x, n, 1, slot, st); }
 
 __global__ void fill_i32_kernel(int *p, size_t n, int v) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
