@@ -1,0 +1,556 @@
+// What the int8 GEMM kernels share: operand types, the XCD grid, and the epilogues (dequantise, GELU + requantise,
+// cache store + gated residual, QKV scatter) applied to a tile of integer accumulators.
+#pragma once
+#include <type_traits>
+
+#include "qc_internal.h"
+
+namespace qc {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+
+constexpr int NUM_XCD = 8;
+constexpr int GELU_FIX_CAP = 1024;      // queue of fc1 outputs decided again in float64, per tile
+
+__device__ __forceinline__ int map_col(int j, int sel_D) {
+  return sel_D ? (j < sel_D ? j + 2 * sel_D : j + 4 * sel_D) : j;
+}
+
+// 8 packed bytes (16 nibbles, element 2j low, 2j+1 high) -> 16 int8 codes.
+__device__ __forceinline__ v4i unpack_w4(v2i p) {
+  v4i o;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    unsigned w = (unsigned)(h ? p.y : p.x);
+    unsigned lo = w & 0x0F0F0F0Fu;
+    unsigned hi = (w >> 4) & 0x0F0F0F0Fu;
+    lo |= (lo & 0x08080808u) * 0x1Eu;   // sign-extend each nibble inside its byte
+    hi |= (hi & 0x08080808u) * 0x1Eu;
+    unsigned e0 = __builtin_amdgcn_perm(hi, lo, 0x05010400u);   // l0 h0 l1 h1
+    unsigned e1 = __builtin_amdgcn_perm(hi, lo, 0x07030602u);   // l2 h2 l3 h3
+    if (h == 0) { o.x = (int)e0; o.y = (int)e1; } else { o.z = (int)e0; o.w = (int)e1; }
+  }
+  return o;
+}
+
+// tanh-GELU written as v * sigmoid(2u), u = sqrt(2/pi) (v + 0.044715 v^3):
+// 0.5 v (1 + tanh u) = v / (1 + exp(-2u)); one exp2 and one reciprocal.
+__device__ __forceinline__ float gelu_tanh(float v) {
+  const float c1 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;   // -2 sqrt(2/pi) log2(e)
+  const float c2 = c1 * 0.044715f;
+  const float t = v * fmaf(c2, v * v, c1);
+  return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
+}
+// the same divided by the quantiser step s: v / (s + s exp(-2u)), the step folded into the denominator
+__device__ __forceinline__ float gelu_tanh_over(float v, float s) {
+  const float c1 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;
+  const float c2 = c1 * 0.044715f;
+  const float t = v * fmaf(c2, v * v, c1);
+  return v * __builtin_amdgcn_rcpf(fmaf(s, __builtin_amdgcn_exp2f(t), s));
+}
+
+// Dequantised output of a quantised linear as it is stored: the float32 rounding of the float64 value
+// (a_s * w_s[n]) * (acc - a_z * wsum[n]) + bias[n] (the product of the two scales is exact in float64; one float64
+// multiplication, one float64 addition, one rounding to float32).  Stored tensors then carry no rounding of their own
+// beyond the storage format, so the codes quantised from them further down do not depend on the order of operations here.
+__device__ __forceinline__ float dequant_f32(double sc, int corr, double bs) {
+  return (float)__dadd_rn(__dmul_rn(sc, (double)corr), bs);
+}
+
+// The fc1 epilogue's exact path for one output element: float64 from the integer accumulator to the GELU value, one
+// rounding to float32, Eq. 1 with an IEEE division.  x / (1 + exp(-2u)) = 0.5 x (1 + tanh u).
+__device__ __noinline__ int gelu_code_exact(int corr, float a_s, float w_s, float bias, float o_s, int o_z) {
+  const double u = __dadd_rn(__dmul_rn((double)a_s * (double)w_s, (double)corr), (double)bias);
+  const double k = 0.7978845608028654 * (u + 0.044715 * u * u * u);
+  const float g = (float)(u / (1.0 + exp(-2.0 * k)));
+  const float r = __builtin_rintf(g / o_s) + (float)o_z;
+  return (int)fminf(fmaxf(r, -128.0f), 127.0f);
+}
+
+// Eq. 1 on signed codes with the quotient v / s refined to the correctly rounded
+// value by one Newton step on the reciprocal estimate.
+__device__ __forceinline__ int quant_code(float v, float s, float inv_s, float z) {
+  float q = v * inv_s;
+  q = fmaf(fmaf(-q, s, v), inv_s, q);
+  float r = __builtin_rintf(q) + z;
+  r = fminf(fmaxf(r, -128.0f), 127.0f);
+  return (int)r;
+}
+
+// Epilogue of a tile: acc[i][j] is the 32 x 32 block (i along the rows m of the activations, j along the output
+// columns n) of wavefront (wave / WN, wave % WN); for EPI_GELU_Q the weights were the first MFMA operand (register
+// index runs along n), otherwise the activations were (register index runs along m).  smem: the workgroup's dynamic
+// LDS, free for reuse (every wavefront is past its last fragment read).
+// FAST: the launcher has checked that every tile is interior along m and lies in one batch element (and, for the QKV
+// scatter, the alignment its staged path needs); the general paths are then not compiled into the kernel.
+// RBF: the residual stream or the cache may be bfloat16 (read from the arguments); false: both are known to be float32.
+template <int BM, int BN, int WM, int WN, int EPI, bool FAST = false, bool RBF = true>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM / WM / 32][BN / WN / 32], unsigned char *smem,
+                                              const int m0, const int n0, const int z) {
+  constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NT = 64 * WM * WN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
+  const int ncover = p.sel_D ? 2 * p.sel_D : p.N;
+  float a_s = p.a_scale;
+  int a_z = p.a_zp;
+  if (p.a_qp) {
+    QParam q = p.a_qp[(long long)z * p.zs_qp];
+    a_s = q.s;
+    a_z = q.z;
+  }
+  const float *w_scale = p.w_scale + (long long)z * p.zs_vecN;
+  const int32_t *wsum = p.wsum + (long long)z * p.zs_vecN;
+  const float *bias = p.bias ? p.bias + (long long)z * p.zs_vecN : nullptr;
+
+  if (EPI == EPI_GELU_Q) {
+    // per-column constants into LDS: v = sc[n] * float(acc - zw[n]) + bs[n]
+    float *c_sc = (float *)smem;
+    int *c_zw = (int *)(smem + BN * 4);
+    float *c_bs = (float *)(smem + BN * 8);
+    unsigned char *stage = smem + BN * 12;             // [BM][BN + 16] codes
+    constexpr int SROW = BN + 16;
+    // Elements whose fast evaluation lands too close to a rounding boundary of Eq. 1 to be trusted are queued here and
+    // decided again in float64 (gelu_code_exact): the codes are then those of exact arithmetic on the accumulators.
+    int *fix_cnt = (int *)(stage + BM * SROW);
+    int *fix_ent = fix_cnt + 4;                        // [GELU_FIX_CAP][4]: accumulator minus zero-point term, column, row
+    if (tid == 0) *fix_cnt = 0;
+    if (tid < BN) {
+      const int n = n0 + tid;
+      const bool ok = n < p.N;
+      c_sc[tid] = ok ? a_s * w_scale[n] : 0.0f;
+      c_zw[tid] = ok ? a_z * wsum[n] : 0;
+      c_bs[tid] = (ok && bias) ? bias[n] : 0.0f;
+    }
+    __syncthreads();
+    const QParam oq = *p.o_qp;
+    // codes are formed as the paper's unsigned ones (zero point + 128, clamped to 0 .. 255, converted and packed by
+    // one instruction each); the sign bit of the four bytes is flipped back when the word is stored
+    const float o_s = oq.s, o_inv = 1.0f / oq.s, o_zu = (float)(oq.z + 128);
+    // Bound of the fast path's error in units of the output step, as a multiple of |v| / s (|GELU(v)| <= |v|):
+    // 1.5e-6 covers the float32 dequantisation (accumulators beyond 2^24 are rounded on conversion) and the exp2 /
+    // reciprocal estimates with a margin of 2, 2e-7 the unrefined quotient gv * (1 / s); 2e-6 absolute covers the bias
+    // rounding.  An element is in doubt when |q - rint(q)| + bound > 1/2.
+    const float tol_v = 1.7e-6f * o_inv;
+    const float doubt_at = 0.5f - 2e-6f;
+    const int g = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+#pragma unroll
+      for (int rg = 0; rg < 4; ++rg) {
+        const int nl = wn0 + j * 32 + rg * 8 + g * 4;       // 4 consecutive columns of this lane
+        const v4f sc = *(const v4f *)(c_sc + nl);
+        const v4i zw = *(const v4i *)(c_zw + nl);
+        const v4f bs = *(const v4f *)(c_bs + nl);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          unsigned w = 0;
+          float dist[4];                                      // distance from the rounding boundary plus the error bound
+          int corr[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            // the large-M kernel's accumulators already carry the zero-point term
+            corr[e] = FAST ? acc[i][j][rg * 4 + e] : acc[i][j][rg * 4 + e] - zw[e];
+            const float v = fmaf(sc[e], (float)corr[e], bs[e]);
+            const float q = gelu_tanh_over(v, o_s);
+            const float r = __builtin_rintf(q);
+            w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(r + o_zu, 0.0f, 255.0f), e, w);
+            dist[e] = fmaf(tol_v, fabsf(v), fabsf(q - r));
+          }
+          w ^= 0x80808080u;
+          // one comparison and one branch per four outputs; taken by a wavefront about once in a hundred times
+          if (fmaxf(fmaxf(dist[0], dist[1]), fmaxf(dist[2], dist[3])) > doubt_at) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (dist[e] > doubt_at) {
+                const int slot = atomicAdd(fix_cnt, 1);
+                if (slot < GELU_FIX_CAP) {
+                  fix_ent[slot * 4 + 0] = corr[e];
+                  fix_ent[slot * 4 + 1] = nl + e;
+                  fix_ent[slot * 4 + 2] = wm0 + i * 32 + (lane & 31);
+                }
+              }
+          }
+          *(unsigned *)(stage + (wm0 + i * 32 + (lane & 31)) * SROW + nl) = w;
+        }
+      }
+    }
+    __syncthreads();
+    {
+      const int nfix = min(*fix_cnt, GELU_FIX_CAP);
+      for (int f = tid; f < nfix; f += NT) {
+        const int corr = fix_ent[f * 4 + 0], nl = fix_ent[f * 4 + 1], row = fix_ent[f * 4 + 2];
+        const int n = n0 + nl;
+        if (n < p.N) stage[row * SROW + nl] = (unsigned char)gelu_code_exact(corr, a_s, w_scale[n], bias ? bias[n] : 0.0f, o_s, oq.z);
+      }
+      if (nfix) __syncthreads();
+    }
+    // coalesced write-out: 16-byte chunks, 8 lanes cover a 128-byte row segment
+    constexpr int CH = BN / 16;
+    for (int c = tid; c < BM * CH; c += NT) {
+      const int r = c / CH, cc = (c % CH) * 16;
+      const int m = m0 + r, n = n0 + cc;
+      if (m >= p.M || n >= p.N) continue;
+      int8_t *dst = p.q_out + (long long)m * p.ldq + n;
+      if (n + 16 <= p.N) {
+        // large launches: streaming stores (the tensor is far larger than the L2 and would only evict the operands)
+        if (FAST) __builtin_nontemporal_store(*(const v4i *)(stage + r * SROW + cc), (v4i *)dst);
+        else *(v4i *)dst = *(const v4i *)(stage + r * SROW + cc);
+      } else {
+        for (int e = 0; n + e < p.N; ++e) dst[e] = (int8_t)stage[r * SROW + cc + e];
+      }
+    }
+    return;
+  }
+
+  if (EPI == EPI_QKV) {
+    // float32 values scattered to the head-major layouts of the attention kernel: Q and K [B, H, T, hd], V transposed
+    // and key-permuted [B, H, DP, Tp]; p.y, when set, also receives them row-major ([M, 3 D], for inspection)
+    const int T = p.rows_per_batch, D = p.N / 3;
+    const bool fast_t = (T % 4) == 0;
+    const bool tile_one_batch = (T % BM) == 0;      // then every row of the tile belongs to batch element m0 / T
+    const int b_tile = m0 / T;
+    constexpr int HN = 128;                                   // the tile is handled in column halves of 128
+    if (FAST || (BM == 128 && BN % HN == 0 && (BN / WN) <= HN && tile_one_batch && fast_t && m0 + BM <= p.M && D % HN == 0 &&
+                 (p.hd & 3) == 0 && (p.Tp & 7) == 0)) {
+      // Tile inside one batch element, every 128 columns inside one of Q, K, V: the values go through LDS (free after
+      // the K loop) and leave as 16-byte stores along the contiguous direction of their layout (Q / K: features of a
+      // token and head; V^T: tokens of a feature).
+      const int tb = m0 - b_tile * T;                         // first token of the tile
+#pragma unroll
+      for (int hn = 0; hn < BN / HN; ++hn) {
+        const int n0h = n0 + hn * HN;                         // first column of this half
+        if (n0h >= p.N) break;
+        const bool mine = wn0 / HN == hn;                     // this wavefront's columns lie in the half
+        const int part = n0h / D;
+        if (hn) __syncthreads();                              // the previous half has left the staging area
+        float *stage = (float *)smem;
+        constexpr int SR = HN + 4;                            // Q / K: floats per staged token row
+        constexpr int VR = BM + 4;                            // V^T: floats per staged feature row
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          if (!mine) continue;
+          const int nl = wn0 - hn * HN + j * 32 + (lane & 31);
+          const double sc = (double)a_s * (double)w_scale[n0h + nl];
+          const int zw = a_z * wsum[n0h + nl];
+          const double bs = bias ? (double)bias[n0h + nl] : 0.0;
+          // the optional row-major copy is not compiled into the large-M kernel (its launcher declines such launches)
+          float *ycol = (!FAST && p.y) ? p.y + (long long)m0 * p.ldy + n0h + nl : nullptr;     // 32 lanes write 128 contiguous bytes
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+              const int ml = wm0 + i * 32 + rg * 8 + (lane >> 5) * 4;
+              v4f v;
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                v[q] = dequant_f32(sc, acc[i][j][rg * 4 + q] - zw, bs);
+                if (ycol) ycol[(unsigned)(ml + q) * (unsigned)p.ldy] = v[q];
+              }
+              if (part < 2) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) stage[(ml + q) * SR + nl] = v[q];
+              } else {
+                // four consecutive tokens stay together under the key permutation of the V^T rows
+                *(v4f *)(stage + nl * VR + vt_pos(ml)) = v;
+              }
+            }
+            if (TM * TN > 4) __builtin_amdgcn_sched_barrier(0);      // large register tiles: keep the live ranges of a block short
+          }
+        }
+        __syncthreads();
+        if (part < 2) {
+          // thread -> four features cc .. cc + 3 (inside one head: heads start at multiples of hd, a multiple of 4) of
+          // the rows cr, cr + NT / 32, ...
+          const int cr = tid >> 5, cc = (tid & 31) * 4;
+          const int nn = n0h - part * D + cc, h = nn / p.hd, e = nn - h * p.hd;
+          float *dst = (part == 0 ? p.q32 : p.k32) +
+                       ((unsigned)(b_tile * p.heads + h) * (unsigned)T + (unsigned)(tb + cr)) * (unsigned)p.hd + (unsigned)e;
+#pragma unroll
+          for (int q = 0; q < BM * 32 / NT; ++q) {
+            const v4f v = *(const v4f *)(stage + (cr + q * (NT / 32)) * SR + cc);
+            v4f *d = (v4f *)(dst + (unsigned)(q * (NT / 32)) * (unsigned)p.hd);
+            if (FAST) __builtin_nontemporal_store(v, d);      // large launches: streaming stores
+            else *d = v;
+          }
+        } else {
+          // thread -> 4 consecutive token positions ch of the features fc, fc + NT / 32, ...
+          const int fc = tid >> 5, ch = (tid & 31) * 4;
+#pragma unroll
+          for (int q = 0; q < HN * 32 / NT; ++q) {
+            const int col = fc + q * (NT / 32);
+            const int nn = n0h - 2 * D + col, h = nn / p.hd, e = nn - h * p.hd;
+            const unsigned o = ((unsigned)(b_tile * p.heads + h) * (unsigned)p.DP + (unsigned)e) * (unsigned)p.Tp + (unsigned)(tb + ch);
+            if (FAST) __builtin_nontemporal_store(*(const v4f *)(stage + col * VR + ch), (v4f *)(p.vt32 + o));
+            else *(v4f *)(p.vt32 + o) = *(const v4f *)(stage + col * VR + ch);
+          }
+        }
+      }
+      return;
+    }
+    if (FAST) return;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + wn0 + j * 32 + (lane & 31);
+      if (n >= p.N) continue;
+      const double sc = (double)a_s * (double)w_scale[n];
+      const int zw = a_z * wsum[n];
+      const double bs = bias ? (double)bias[n] : 0.0;
+      const int part = n / D, nn = n - part * D, h = nn / p.hd, e = nn - h * p.hd;
+      float *dqk = part == 0 ? p.q32 : p.k32;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+          const int mb = m0 + wm0 + i * 32 + rg * 8 + (lane >> 5) * 4;   // 4 consecutive rows mb .. mb+3
+          if (mb >= p.M) continue;
+          v4f v;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = dequant_f32(sc, acc[i][j][rg * 4 + q] - zw, bs);
+          const int b0 = tile_one_batch ? b_tile : mb / T, t0 = mb - b0 * T;
+          if (part == 2 && fast_t && mb + 3 < p.M) {
+            // T is a multiple of 4: the four rows are tokens t0 .. t0 + 3 of one batch element, contiguous in V^T
+            *(v4f *)(p.vt32 + ((long long)(b0 * p.heads + h) * p.DP + e) * p.Tp + vt_pos(t0)) = v;
+          } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              if (mb + q >= p.M) continue;
+              int b = b0, t = t0 + q;
+              while (t >= T) { t -= T; ++b; }
+              if (part == 2) p.vt32[((long long)(b * p.heads + h) * p.DP + e) * p.Tp + vt_pos(t)] = v[q];
+              else dqk[((long long)(b * p.heads + h) * T + t) * p.hd + e] = v[q];
+            }
+          }
+          if (p.y) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (mb + q < p.M) p.y[(long long)(mb + q) * p.ldy + n] = v[q];
+          }
+        }
+      }
+    }
+    return;
+  }
+
+  if (EPI == EPI_RESID) {
+    // read-modify-write of the residual stream: the loads of a batch of column blocks are all issued
+    // before the first use, so the epilogue pays one memory round trip per batch instead of one per
+    // register group; a batch is the whole tile when its values fit in registers beside the accumulators
+    constexpr int JB = TM * TN <= 4 ? TN : 1, IB = TM * TN <= 4 ? TM : 1;
+    const bool uniform_batch = (p.rows_per_batch % BM) == 0;
+    const int b_uniform = m0 / p.rows_per_batch;
+    const int x_bf16 = RBF ? p.x_bf16 : 0, cache_bf16 = RBF ? p.cache_bf16 : 0;
+    if (FAST && RBF && (x_bf16 || cache_bf16) && p.N % 128 == 0) {
+      // A bfloat16 stream or cache: 32 lanes of a wavefront cover only 64 bytes of a row, and 2-byte stores leave
+      // every cache line half written.  The dequantised values go through LDS in column halves of 128 instead, and
+      // every thread handles four adjacent columns of 16 rows: 8- or 16-byte loads and stores, whole lines per row.
+      constexpr int HN = 128, SR = HN + 4, RQ = BM * 32 / NT;
+      float *stage = (float *)smem;
+      const int cr = tid >> 5, cc = (tid & 31) * 4;     // thread -> rows cr + (NT / 32) q, columns cc .. cc + 3 of a half
+#pragma unroll
+      for (int hn = 0; hn < BN / HN; ++hn) {
+        const int n0h = n0 + hn * HN;
+        if (n0h >= p.N) break;
+        const bool mine = wn0 / HN == hn;               // this wavefront's columns lie in the half
+        if (hn) __syncthreads();                        // the previous half has left the staging area
+        const v4f gv = *(const v4f *)(p.gate + (long long)b_uniform * p.ld_gate + n0h + cc);
+        const size_t ob4 = ((size_t)m0 * p.N + n0h + cc) >> 2;      // in groups of four elements
+        const size_t row4 = (size_t)p.N >> 2;
+        // a bfloat16 stream: the thread's 16 pieces of x (8 bytes each) are requested before the staging, which hides
+        // their latency (a float32 stream would take twice the registers: its loads stay in the loop below)
+        uint2 xraw[RQ];
+        if (x_bf16) {
+#pragma unroll
+          for (int q = 0; q < RQ; ++q) xraw[q] = ((const uint2 *)p.x)[ob4 + (size_t)(cr + q * (NT / 32)) * row4];
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          if (!mine) continue;
+          const int nl = wn0 - hn * HN + j * 32 + (lane & 31);
+          const double sc = (double)a_s * (double)w_scale[n0h + nl];
+          const int zw = a_z * wsum[n0h + nl];
+          const double bs = bias ? (double)bias[n0h + nl] : 0.0;
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              stage[(wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * SR + nl] = dequant_f32(sc, acc[i][j][r] - zw, bs);
+            __builtin_amdgcn_sched_barrier(0);          // one block's values live at a time
+          }
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int q = 0; q < RQ; ++q) {
+          const int row = cr + q * (NT / 32);
+          const v4f v = *(const v4f *)(stage + row * SR + cc);
+          const size_t o4 = ob4 + (size_t)row * row4;
+          float4 xo;
+          if (x_bf16) {
+            xo = make_float4(__builtin_bit_cast(float, xraw[q].x << 16), __builtin_bit_cast(float, xraw[q].x & 0xFFFF0000u),
+                             __builtin_bit_cast(float, xraw[q].y << 16), __builtin_bit_cast(float, xraw[q].y & 0xFFFF0000u));
+          } else {
+            xo = stream_load4(p.x, o4, 0);
+          }
+          stream_store4(p.cache_out, o4, make_float4(v.x, v.y, v.z, v.w), cache_bf16);
+          stream_store4(p.x, o4, make_float4(fmaf(gv.x, v.x, xo.x), fmaf(gv.y, v.y, xo.y), fmaf(gv.z, v.z, xo.z), fmaf(gv.w, v.w, xo.w)),
+                        x_bf16);
+        }
+      }
+      return;
+    }
+    if (FAST) {
+      // every row of the tile exists and belongs to batch element b_uniform; N is a multiple of 32, so a wavefront's
+      // 32-column block lies inside the matrix or outside it as a whole.  Addresses are a wavefront-uniform row pointer
+      // (scalar arithmetic) plus one 32-bit lane offset, and the loads of x of XB blocks (16 values per lane each: the
+      // registers of the K loop's operand ring and fragments are free now) are issued before the first is used, so a
+      // tile's epilogue pays TM x TN / XB memory round trips instead of TM x TN.
+      constexpr int XB = (!RBF && TM % 2 == 0) ? 2 : 1;   // the bfloat16 variants have no registers to spare   // the bfloat16 variants have no registers to spare
+      const int wv = __builtin_amdgcn_readfirstlane(wave);
+      const int wm0u = (wv / WN) * (BM / WM), wn0u = (wv % WN) * (BN / WN);
+      const unsigned loff = (unsigned)((lane >> 5) * 4) * (unsigned)p.N + (unsigned)(lane & 31);
+      const size_t xsz = x_bf16 ? 2 : 4, csz = cache_bf16 ? 2 : 4;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int nb = n0 + wn0u + j * 32;
+        if (nb >= p.N) continue;
+        const int n = nb + (lane & 31);
+        const double sc = (double)a_s * (double)w_scale[n];
+        const int zw = a_z * wsum[n];
+        const double bs = bias ? (double)bias[n] : 0.0;
+        const float g = p.gate[(long long)b_uniform * p.ld_gate + n];
+        const size_t e0 = (size_t)(m0 + wm0u) * p.N + nb;           // first element of the wavefront's block column
+#pragma unroll
+        for (int i0 = 0; i0 < TM; i0 += XB) {
+          float xv[XB][16];
+#pragma unroll
+          for (int ii = 0; ii < XB; ++ii) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const size_t er = e0 + (size_t)((i0 + ii) * 32 + (r >> 2) * 8 + (r & 3)) * p.N;
+              xv[ii][r] = stream_load((const char *)p.x + er * xsz, loff, x_bf16);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int ii = 0; ii < XB; ++ii) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const size_t er = e0 + (size_t)((i0 + ii) * 32 + (r >> 2) * 8 + (r & 3)) * p.N;
+              const float v = dequant_f32(sc, acc[i0 + ii][j][r] - zw, bs);
+              // the cached tensor is written once and read a step later: a streaming store keeps it out of the L2's way
+              if (!RBF) __builtin_nontemporal_store(v, (float *)((char *)p.cache_out + er * csz) + loff);
+              else stream_store((char *)p.cache_out + er * csz, loff, v, cache_bf16);
+              stream_store((char *)p.x + er * xsz, loff, fmaf(g, v, xv[ii][r]), x_bf16);
+            }
+            __builtin_amdgcn_sched_barrier(0);                // one block's dequantised values live at a time
+          }
+        }
+      }
+      return;
+    }
+    const bool interior = uniform_batch && m0 + BM <= p.M && n0 + BN <= p.N;
+#pragma unroll
+    for (int j0 = 0; j0 < TN; j0 += JB)
+#pragma unroll
+      for (int i0 = 0; i0 < TM; i0 += IB) {
+        float xv[JB][IB][16], gv[JB];
+        double scv[JB], bsv[JB];
+        int zwv[JB];
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) {
+          const int n = min(n0 + wn0 + (j0 + jj) * 32 + (lane & 31), p.N - 1);
+#pragma unroll
+          for (int ii = 0; ii < IB; ++ii)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int m = min(m0 + wm0 + (i0 + ii) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), p.M - 1);
+              xv[jj][ii][r] = stream_load(p.x, (long long)m * p.N + n, x_bf16);
+            }
+          scv[jj] = (double)a_s * (double)w_scale[n];
+          zwv[jj] = a_z * wsum[n];
+          bsv[jj] = bias ? (double)bias[n] : 0.0;
+          gv[jj] = p.gate[(long long)b_uniform * p.ld_gate + n];
+        }
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) {
+          const int j = j0 + jj;
+          const int n = n0 + wn0 + j * 32 + (lane & 31);
+          if (interior) {
+            // interior tile inside one batch element: no bounds checks, one gate per column
+#pragma unroll
+            for (int ii = 0; ii < IB; ++ii)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                const int i = i0 + ii;
+                const float v = dequant_f32(scv[jj], acc[i][j][r] - zwv[jj], bsv[jj]);
+                // 32-bit offset inside the tile's rows from one 64-bit base per column
+                const long long ob = (long long)m0 * p.N + n;
+                const unsigned o = (unsigned)(wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * (unsigned)p.N;
+                if (cache_bf16) ((unsigned short *)p.cache_out + ob)[o] = bf16_bits(v);
+                else ((float *)p.cache_out + ob)[o] = v;
+                stream_store(p.x, ob + o, fmaf(gv[jj], v, xv[jj][ii][r]), x_bf16);
+              }
+          } else {
+            if (n >= p.N) continue;
+#pragma unroll
+            for (int ii = 0; ii < IB; ++ii)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                const int i = i0 + ii;
+                const int m = m0 + wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+                if (m >= p.M) continue;
+                const float v = dequant_f32(scv[jj], acc[i][j][r] - zwv[jj], bsv[jj]);
+                const long long o = (long long)m * p.N + n;
+                if (cache_bf16) ((unsigned short *)p.cache_out)[o] = bf16_bits(v);
+                else ((float *)p.cache_out)[o] = v;
+                const float g = p.gate[(long long)(m / p.rows_per_batch) * p.ld_gate + n];
+                stream_store(p.x, o, fmaf(g, v, xv[jj][ii][r]), x_bf16);
+              }
+          }
+        }
+        if (TM * TN > 4) __builtin_amdgcn_sched_barrier(0);      // large register tiles: one batch's values live at a time
+      }
+    return;
+  }
+
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int jl = n0 + wn0 + j * 32 + (lane & 31);
+    if (jl >= ncover) continue;
+    const int n = map_col(jl, p.sel_D);
+    const double sc = (double)a_s * (double)w_scale[n];
+    const int zw = a_z * wsum[n];
+    const double bs = bias ? (double)bias[n] : 0.0;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+        if (m >= p.M) continue;
+        const int a = acc[i][j][r];
+        float *y = p.y + (long long)z * p.zs_out;
+        y[(long long)m * p.ldy + n] = dequant_f32(sc, a - zw, bs);
+        if (p.acc_out) p.acc_out[(long long)m * p.N + n] = a;
+      }
+    }
+  }
+}
+
+// XCD grid rows that move the fewest bytes into the eight L2s, weighted by load imbalance
+inline int xcd_rows(int tiles_m, int tiles_n, double bytes_a, double bytes_w) {
+  int best_xm = 1;
+  double best = 1e300;
+  for (int xm = 1; xm <= NUM_XCD; xm *= 2) {
+    const int xn = NUM_XCD / xm;
+    const int cm = (tiles_m + xm - 1) / xm, cn = (tiles_n + xn - 1) / xn;
+    const double cost = (xn * bytes_a + xm * bytes_w) * ((double)cm * cn * NUM_XCD / ((double)tiles_m * tiles_n));
+    if (cost < best) { best = cost; best_xm = xm; }
+  }
+  return best_xm;
+}
+
+}  // namespace qc

@@ -118,6 +118,9 @@ __device__ __forceinline__ void stream_store4(void *x, size_t i4, float4 v, int 
 }
 
 hipError_t launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st, int site);
+// the split-K kernel of small launches (gemm_i8_split.hip): whether a launch is one of them, and the launch
+bool gemm_split_pays(const GemmArgs &a, int epi, int nz);
+hipError_t launch_gemm_split(const GemmArgs &a, int epi, hipStream_t st);
 // row-major codes [N, K] (or packed [N, K/2]) -> fragment order; N % 32 == 0, K % 32 == 0
 hipError_t launch_tile_weight(const void *q, void *qt, int N, int K, int bits, hipStream_t st);
 
