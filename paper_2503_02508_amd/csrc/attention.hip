@@ -200,17 +200,15 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
 // Two float32 values -> their hi halves (the values rounded to fp16, packed) and lo halves (what the rounding left,
-// again rounded to fp16): hi + lo carries about 22 significant bits.  One packed conversion per pair of halves.  The
-// hi halves that are stored and the ones that are subtracted must be the same bits, so the packed word is made opaque
-// to the compiler and converted back from there (otherwise it forms the subtracted halves with a second, scalar
-// conversion, and the two were observed to disagree on ties: the sum was then off by one unit of the hi half).
+// again rounded to fp16): hi + lo carries about 22 significant bits.  Three instructions per pair: one packed conversion,
+// then the mixed-precision multiply-add forms a - (float)hi (exact in float32) from the stored hi half and rounds it to
+// fp16 in one go, into either half of the lo word.
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void split_pair(float a, float b, unsigned &hi, unsigned &lo) {
   hi = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){a, b}, v2h));
-  asm volatile("" : "+v"(hi));
-  const v2h hh = __builtin_bit_cast(v2h, hi);
-  lo = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){a - (float)hh[0], b - (float)hh[1]}, v2h));
+  asm("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(hi), "v"(a));
+  asm("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(hi), "v"(b));
 }
 __device__ __forceinline__ void split_pairs(v4f v, v2u &hi, v2u &lo) {
   unsigned h0, l0, h1, l1;
@@ -224,18 +222,37 @@ __device__ __forceinline__ void split_pairs(v4f v, v2u &hi, v2u &lo) {
 // wavefront (a workgroup covers 64 * QB queries).  QB = 2 reads every K / V^T fragment once for two MFMAs; QB = 1 makes
 // twice as many workgroups with half the MFMA chain each, for launches that would leave compute units idle.  The
 // arithmetic per query is the same in both.
-template <int NCH, int NEB, int QB>
+//
+// TAIL: the last feature chunk holds at most 8 real features (d = 72: 64 + 8).  Its three products then share ONE
+// instruction: of the 32 k positions of the K operand, 0..7 are the features' hi halves, 8..15 their lo halves, 16..23 the
+// hi halves again, and the query operand has hi, hi, lo there (7 instructions per key block instead of 9 at d = 72).  In
+// that case the last V^T block has free rows as well: row d is set to ones, so that the sum of the probabilities falls out
+// of the P V product (row d of O^T) instead of costing an addition per probability.
+//
+// What bounds it: issue slots of the vector pipe, which an MFMA shares for about half of its 16 cycles.  Per tile of 64 keys
+// a wavefront issues 116 MFMAs (QB = 2, d = 72) and about 5 vector instructions per probability (exponential, subtraction,
+// half a maximum, one and a half for the split), so the vector work is what was cut: the running max is only raised when a
+// tile exceeds it by more than MAX_SLACK (a probability may reach 2^MAX_SLACK; hi + lo keep their relative precision), which
+// leaves one test per tile instead of two shuffles, an exponential and the rescaling of every output register.
+template <int NCH, int NEB, int QB, bool TAIL>
 __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__restrict__ Qp, const float *__restrict__ Kp,
                                                             const float *__restrict__ Vt, int BH, int T, int Tp, int H, int hd, int DPv,
                                                             float q_mul, const QParam *qp, int8_t *__restrict__ q_out) {
-  constexpr int DP = 32 * NCH;
-  constexpr int KROW = DP + 8;    // halves per K row in LDS (16 bytes of padding)
-  constexpr int VROW = 64 + 8;    // halves per V^T row in LDS
-  constexpr int KCH = 5;          // 16-byte chunks of K pairs per thread per tile: 64 keys * d/4 <= 256 * KCH for d <= 80
-  constexpr int VCH = (NEB * 16 * 8 + 255) / 256;
-  __shared__ __align__(16) _Float16 Ksh[2][64 * KROW];
+  constexpr int NM = TAIL ? NCH - 1 : NCH;        // feature chunks multiplied in three instructions
+  constexpr int NI = NM + (TAIL ? 1 : 0);         // fragment steps per key block
+  constexpr int KROW = 32 * NM + 8;               // halves per K row in LDS (16 bytes of padding)
+  constexpr int TROW = 32 + 8;                    // halves per row of the tail operand
+  constexpr int VROW = 64 + 8;                    // halves per V^T row in LDS
+  constexpr int NW = 4, NT = 64 * NW;            // wavefronts, threads
+  constexpr int KCH = (64 * 4 * NEB + NT - 1) / NT;       // 16-byte chunks of K per thread per tile (d <= 16 NEB)
+  constexpr int VCH = (NEB * 16 * 8 + NT - 1) / NT;       // 32-byte chunks of V^T
+  constexpr int NQ = 16 * QB * NW;                // queries of this workgroup
+  constexpr float MAX_SLACK = 8.0f;
+  __shared__ __align__(16) _Float16 Ksh[2 * 64 * KROW + (TAIL ? 64 * TROW : 0)];
   __shared__ __align__(16) _Float16 Vsh[2][NEB * 16 * VROW];
   __shared__ int fix_cnt_s;                       // outputs queued for the exact decision (epilogue)
+  __shared__ float m_s[NQ];                       // running max of every query (reference point of the exact decision)
+  _Float16 *const Khi = Ksh, *const Klo = Ksh + 64 * KROW, *const Kt = Ksh + 2 * 64 * KROW;
 
   const int D = H * hd;
   if (threadIdx.x == 0) fix_cnt_s = 0;            // published by the barriers of the key loop
@@ -254,8 +271,13 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   const long long vt_base = (long long)bh * DPv * Tp;
   const int kchunks = 64 * (hd / 4);            // 16-byte chunks of one K tile
 
-  // feature padding of the K tile is never written below: clear it once
-  for (int i = tid; i < 2 * 64 * KROW / 8; i += 256) ((v8h *)&Ksh[0][0])[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
+  // what no tile writes: the feature padding of the K rows, and the V^T rows beyond d (zeros; row d is ones with TAIL)
+  for (int i = tid; i < (int)(sizeof(Ksh) / 16); i += NT) ((v8h *)Ksh)[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
+  for (int i = tid; i < (16 * NEB - hd) * VROW / 8; i += NT) {
+    const _Float16 one = (TAIL && i < VROW / 8) ? (_Float16)1.0f : (_Float16)0.0f;
+    ((v8h *)(Vsh[0] + hd * VROW))[i] = (v8h){one, one, one, one, one, one, one, one};
+    ((v8h *)(Vsh[1] + hd * VROW))[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
+  }
 
   v4f o[QB][NEB];
 #pragma unroll
@@ -271,70 +293,84 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
 
   v4f kreg[KCH];
   v4f vreg[2][VCH];
-  // key row and feature offset of this thread's K chunks (the same for every tile: no divisions in the loop).
-  // Loads never branch: a chunk index beyond the tile is clamped to the last chunk and a key beyond T to key
-  // T-1 (finite values that the ragged-tile mask or the store predicate discards), so that all loads of a tile
-  // are issued back to back and nothing waits in between.
-  int kr[KCH], kc[KCH];
-  bool kvalid[KCH];
+  // Offsets of this thread's K and V^T chunks in memory and in LDS (the same for every tile: no address arithmetic in the
+  // loop).  Loads never branch: a chunk index beyond the tile is clamped to the last chunk, a key beyond T to key T - 1
+  // (finite values that the ragged-tile mask or the store predicate discards), so that all loads of a tile are issued back
+  // to back and nothing waits in between.
+  const int hd4 = hd >> 2;
+  unsigned koff[KCH], voff[VCH];
+  int k_hi[KCH], k_lo[KCH], v_at[VCH];            // positions in Ksh / Vsh[0], in halves; negative: no such chunk
 #pragma unroll
   for (int u = 0; u < KCH; ++u) {
-    const int i = tid + 256 * u;
-    kvalid[u] = i < kchunks;
-    const int ic = min(i, kchunks - 1);
-    kr[u] = ic / (hd / 4);
-    kc[u] = (ic % (hd / 4)) * 4;
+    const int i = tid + NT * u, ic = min(i, kchunks - 1);
+    const int r = ic / hd4, c = (ic - r * hd4) * 4;
+    const bool tail = TAIL && c >= 32 * NM;
+    koff[u] = (unsigned)(min(r, T - 1) * hd + c);
+    k_hi[u] = i >= kchunks ? -1 : tail ? 2 * 64 * KROW + r * TROW + c - 32 * NM : r * KROW + c;
+    k_lo[u] = tail ? k_hi[u] + 8 : k_hi[u] + 64 * KROW;
   }
-  auto load_tile = [&](int k0) {
 #pragma unroll
-    for (int u = 0; u < KCH; ++u)
-      kreg[u] = *(const v4f *)(Kp + tok_base + (long long)min(k0 + kr[u], T - 1) * hd + kc[u]);
+  for (int u = 0; u < VCH; ++u) {
+    const int i = tid + NT * u, ic = min(i, hd * 8 - 1);
+    voff[u] = (unsigned)((ic >> 3) * Tp + (ic & 7) * 8);
+    v_at[u] = i < hd * 8 ? (i >> 3) * VROW + (i & 7) * 8 : -1;
+  }
+  const float *const kbase = Kp + tok_base, *const vbase = Vt + vt_base;
+  auto load_tile = [&](int k0) {
+    const float *kb = kbase + (size_t)k0 * hd, *vb = vbase + k0;
+    if (k0 + 64 <= T || k0 == 0) {                // the first tile's offsets are clamped already
+#pragma unroll
+      for (int u = 0; u < KCH; ++u) kreg[u] = *(const v4f *)(kb + koff[u]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < KCH; ++u) {
+        const int ic = min(tid + NT * u, kchunks - 1), r = ic / hd4;
+        kreg[u] = *(const v4f *)(kb + (min(r, T - 1 - k0) * hd + (ic - r * hd4) * 4));
+      }
+    }
 #pragma unroll
     for (int u = 0; u < VCH; ++u) {
-      const int i = min(tid + 256 * u, NEB * 16 * 8 - 1);
-      const int e = i >> 3, c8 = (i & 7) * 8;
-      vreg[0][u] = *(const v4f *)(Vt + vt_base + (long long)e * Tp + k0 + c8);
-      vreg[1][u] = *(const v4f *)(Vt + vt_base + (long long)e * Tp + k0 + c8 + 4);
+      vreg[0][u] = *(const v4f *)(vb + voff[u]);
+      vreg[1][u] = *(const v4f *)(vb + voff[u] + 4);
     }
   };
   auto store_tile = [&]() {
 #pragma unroll
     for (int u = 0; u < KCH; ++u) {
-      if (kvalid[u]) {
+      if (k_hi[u] >= 0) {
         v2u hi, lo;
         split_pairs(kreg[u], hi, lo);
-        *(v2u *)(Ksh[0] + kr[u] * KROW + kc[u]) = hi;
-        *(v2u *)(Ksh[1] + kr[u] * KROW + kc[u]) = lo;
+        *(v2u *)(Ksh + k_hi[u]) = hi;
+        *(v2u *)(Ksh + k_lo[u]) = lo;
+        if (TAIL && k_lo[u] - k_hi[u] == 8) *(v2u *)(Ksh + k_hi[u] + 16) = hi;
       }
     }
 #pragma unroll
     for (int u = 0; u < VCH; ++u) {
-      const int i = tid + 256 * u;
-      if (i < NEB * 16 * 8) {
-        const int e = i >> 3, c8 = (i & 7) * 8;
+      if (v_at[u] >= 0) {
         v2u h0, l0, h1, l1;
         split_pairs(vreg[0][u], h0, l0);
         split_pairs(vreg[1][u], h1, l1);
-        *(v4u *)(Vsh[0] + e * VROW + c8) = (v4u){h0.x, h0.y, h1.x, h1.y};
-        *(v4u *)(Vsh[1] + e * VROW + c8) = (v4u){l0.x, l0.y, l1.x, l1.y};
+        *(v4u *)(Vsh[0] + v_at[u]) = (v4u){h0.x, h0.y, h1.x, h1.y};
+        *(v4u *)(Vsh[1] + v_at[u]) = (v4u){l0.x, l0.y, l1.x, l1.y};
       }
     }
   };
 
   load_tile(0);                            // first key tile and the queries are in flight together
   int q_row[QB];
-  v8h qh[QB][NCH], qlo[QB][NCH];
+  v8h qh[QB][NI], qlo[QB][NM > 0 ? NM : 1];       // with TAIL, qh[.][NM] is the packed tail operand
   {
     // all query loads are issued before any is used; rows beyond T read row T-1 (their results are never
     // stored), features beyond d read the last chunk and are zeroed below
     v4f qraw[QB][NCH][2];
 #pragma unroll
     for (int j = 0; j < QB; ++j) {
-      q_row[j] = qblk * (64 * QB) + wave * (16 * QB) + j * 16 + ql;
+      q_row[j] = qblk * NQ + wave * (16 * QB) + j * 16 + ql;
       const float *src = Qp + tok_base + (long long)min(q_row[j], T - 1) * hd;
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
-        const int f = 32 * c + 8 * g;
+        const int f = 32 * c + (c < NM ? 8 * g : 0);
         qraw[j][c][0] = *(const v4f *)(src + min(f, hd - 4));
         qraw[j][c][1] = *(const v4f *)(src + min(f + 4, hd - 4));
       }
@@ -343,15 +379,21 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
     for (int j = 0; j < QB; ++j)
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
-        const int f = 32 * c + 8 * g;
+        const int f = 32 * c + (c < NM ? 8 * g : 0);
         v2u h0, l0, h1, l1;
         split_pairs(qraw[j][c][0] * q_mul, h0, l0);     // queries pre-scaled by log2(e) / sqrt(d): the softmax runs in base 2
         split_pairs(qraw[j][c][1] * q_mul, h1, l1);
         if (f >= hd) { h0 = (v2u){0, 0}; l0 = h0; }
         if (f + 4 >= hd) { h1 = (v2u){0, 0}; l1 = h1; }
         v4u hh = {h0.x, h0.y, h1.x, h1.y}, ll = {l0.x, l0.y, l1.x, l1.y};
-        qh[j][c] = *(v8h *)&hh;
-        qlo[j][c] = *(v8h *)&ll;
+        if (c < NM) {
+          qh[j][c] = *(v8h *)&hh;
+          qlo[j][c] = *(v8h *)&ll;
+        } else {                                        // lane group g supplies k positions 8 g .. 8 g + 7
+          v4u t = g == 2 ? ll : hh;
+          if (g == 3) t = (v4u){0, 0, 0, 0};
+          qh[j][c] = *(v8h *)&t;
+        }
       }
   }
   for (int k0 = 0; k0 < T; k0 += 64) {
@@ -363,38 +405,43 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
     // S^T = K Q^T: the K fragments run two iterations ahead of the MFMAs that use them (LDS latency is
     // several MFMA groups long and a wavefront is alone on its SIMD)
     v4f s[QB][4];
-    constexpr int NS = 4 * NCH;
+    constexpr int NS = 4 * NI;
     v8h kfh[3], kfl[3];
     auto load_k = [&](int it, int slot) {
-      const int kt = it / NCH, c = it % NCH;
-      kfh[slot] = *(const v8h *)(Ksh[0] + (kt * 16 + ql) * KROW + 32 * c + 8 * g);
-      kfl[slot] = *(const v8h *)(Ksh[1] + (kt * 16 + ql) * KROW + 32 * c + 8 * g);
+      const int kt = it / NI, c = it % NI;
+      if (c < NM) {
+        kfh[slot] = *(const v8h *)(Khi + (kt * 16 + ql) * KROW + 32 * c + 8 * g);
+        kfl[slot] = *(const v8h *)(Klo + (kt * 16 + ql) * KROW + 32 * c + 8 * g);
+      } else {
+        kfh[slot] = *(const v8h *)(Kt + (kt * 16 + ql) * TROW + 8 * g);
+      }
     };
     load_k(0, 0);
     load_k(1, 1);
     v4f acc[QB];
 #pragma unroll
-    for (int j = 0; j < QB; ++j) acc[j] = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
     for (int it = 0; it < NS; ++it) {
-      const int kt = it / NCH, c = it % NCH, slot = it % 3;
+      const int kt = it / NI, c = it % NI, slot = it % 3;
       if (it + 2 < NS) load_k(it + 2, (it + 2) % 3);
       __builtin_amdgcn_sched_barrier(0);
       const v8h kh = kfh[slot], kl = kfl[slot];
+      if (c == 0) {
+#pragma unroll
+        for (int j = 0; j < QB; ++j) acc[j] = (v4f){0.f, 0.f, 0.f, 0.f};
+      }
       // the query blocks alternate so that consecutive MFMAs do not wait on each other's result
+      if (c < NM) {
 #pragma unroll
-      for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, qh[j][c], acc[j], 0, 0, 0);
+        for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, qh[j][c], acc[j], 0, 0, 0);
 #pragma unroll
-      for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qlo[j][c], acc[j], 0, 0, 0);
+        for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qlo[j][c < NM ? c : 0], acc[j], 0, 0, 0);
+      }
 #pragma unroll
       for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qh[j][c], acc[j], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
-      if (c == NCH - 1) {
+      if (c == NI - 1) {
 #pragma unroll
-        for (int j = 0; j < QB; ++j) {
-          s[j][kt] = acc[j];
-          acc[j] = (v4f){0.f, 0.f, 0.f, 0.f};
-        }
+        for (int j = 0; j < QB; ++j) s[j][kt] = acc[j];
       }
     }
     // the first V^T fragments are requested before the softmax arithmetic, which hides their latency
@@ -408,38 +455,54 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
     load_v(0, 0);
     load_v(1, 1);
     v8h ph[QB][2], pl[QB][2];
-    const bool ragged_tile = k0 + 64 > T;
+    if (k0 + 64 > T) {                      // wavefront-uniform: whole tiles skip the masking
+      asm volatile("");                     // (kept a branch: as selects it would cost every tile three instructions a key)
 #pragma unroll
-    for (int j = 0; j < QB; ++j) {
-      float mx = -INFINITY;
-      if (ragged_tile) {                    // wavefront-uniform: whole tiles skip the masking
+      for (int j = 0; j < QB; ++j)
 #pragma unroll
         for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             if (k0 + kt * 16 + 4 * g + r >= T) s[j][kt][r] = -INFINITY;
-      }
+    }
+    float mx[QB];
+    bool over = false;
+#pragma unroll
+    for (int j = 0; j < QB; ++j) {
+      mx[j] = s[j][0][0];
 #pragma unroll
       for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[j][kt][r]);
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m_run[j], mx);
-      const float alpha = __builtin_amdgcn_exp2f(m_run[j] - m_new);
-      m_run[j] = m_new;
-      l_run[j] *= alpha;
+        for (int r = 0; r < 4; ++r) mx[j] = fmaxf(mx[j], s[j][kt][r]);
+      over = over || mx[j] > m_run[j] + MAX_SLACK;      // true on the first tile: m_run starts at minus infinity
+    }
+    if (__builtin_amdgcn_ballot_w64(over) != 0ull) {
+      // raise the running max of every query of the wavefront to its true value so far and rescale what was summed
 #pragma unroll
-      for (int e = 0; e < NEB; ++e) o[j][e] *= alpha;
+      for (int j = 0; j < QB; ++j) {
+        mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 16, 64));
+        mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 32, 64));
+        const float m_new = fmaxf(m_run[j], mx[j]);
+        const float alpha = __builtin_amdgcn_exp2f(m_run[j] - m_new);
+        m_run[j] = m_new;
+        if (!TAIL) l_run[j] *= alpha;
+#pragma unroll
+        for (int e = 0; e < NEB; ++e) o[j][e] *= alpha;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < QB; ++j) {
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
         v4u hw, lw;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {         // word w of the operand: keys (kt = 2 a + w / 2, r = 2 (w % 2) .. + 1)
           const int kt = 2 * a + (w >> 1), r = 2 * (w & 1);
-          const float p0 = __builtin_amdgcn_exp2f(s[j][kt][r] - m_new), p1 = __builtin_amdgcn_exp2f(s[j][kt][r + 1] - m_new);
-          l_run[j] += p0;
-          l_run[j] += p1;
+          const float p0 = __builtin_amdgcn_exp2f(s[j][kt][r] - m_run[j]), p1 = __builtin_amdgcn_exp2f(s[j][kt][r + 1] - m_run[j]);
+          if (!TAIL) {
+            l_run[j] += p0;
+            l_run[j] += p1;
+          }
           unsigned h2, l2;
           split_pair(p0, p1, h2, l2);
           hw[w] = h2;
@@ -470,143 +533,157 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   // exponentials) to be trusted are decided again in float64 from the float32 Q | K | V, then the rows go out.
   const QParam t = *qp;
   const float qs = t.s, qz = (float)t.z;
-  constexpr int NQ = 64 * QB;                     // queries of this workgroup
-  constexpr int SRB = 16 * NEB + 16;              // staged row: the head's features, padded
+  constexpr int SRB = 16 * NEB;                   // staged row: the head's features, padded
   constexpr int FIX_CAP = 192;
   static_assert(NQ * SRB + FIX_CAP * 8 <= (int)sizeof(Ksh), "the epilogue's staging area must fit in the K tile buffers");
-  unsigned char *stage = (unsigned char *)&Ksh[0][0];
+  unsigned char *stage = (unsigned char *)Ksh;
   int *fix_cnt = &fix_cnt_s;
   int *fix_ent = (int *)(stage + NQ * SRB);       // [FIX_CAP][2]: query within the workgroup, feature
   __syncthreads();                                // every wavefront is past its last K / V^T fragment
   // |v / s - rint(v / s)| within tol of 1/2: 1.2e-5 steps + 4e-7 of the code's size at 256 keys is about ten times the
   // kernel's mean error there (its differing codes without this path, a few 1e-6 of all, put the mean error near 1e-6
-  // steps); the sums grow with the number of keys and the bound with them
+  // steps)
   // The quotient of Eq. 1 is formed as v * (1 / s) here: that is within 2.5e-7 |v / s| of the correctly rounded
   // quotient, so the two can only round to different integers inside the window below (whose relative part is widened
   // by that much), where the float64 path, which divides, decides.
-  const float tol_k = fmaxf(1.0f, (float)T * (1.0f / 256.0f));
+  // Growth of the bound with the number of keys: the measured largest error doubles from 256 to 1024 keys, a three-quarter
+  // power keeps the same margin at both.
+  const float tk = fmaxf(1.0f, (float)T * (1.0f / 256.0f)), tol_k = __builtin_sqrtf(tk * __builtin_sqrtf(tk));
   const float tol_0 = 1.2e-5f * tol_k, tol_q = 4e-7f * tol_k + 2.5e-7f;
-  const float inv_qs = 1.0f / qs;
+  const float doubt_at = 0.5f - tol_0;
+  const float inv_qs = 1.0f / qs, zu = qz + 128.0f;
 #pragma unroll
   for (int j = 0; j < QB; ++j) {
-    float l = l_run[j];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
-    const float inv = 1.0f / l;
+    float l;
+    if constexpr (TAIL) {
+      // row d of O^T: block d / 16, row d % 16 = 4 g + r with r = 0 (d is a multiple of 4)
+      l = __shfl(o[j][NEB - 1][0], ((hd & 15) >> 2) * 16 + ql, 64);
+    } else {
+      l = l_run[j];
+      l += __shfl_xor(l, 16, 64);
+      l += __shfl_xor(l, 32, 64);
+    }
+    const float k = (1.0f / l) * inv_qs;            // value and quotient of Eq. 1 in one multiplication per output
     const int qloc = wave * (16 * QB) + j * 16 + ql;
+    if (g == 0) m_s[qloc] = m_run[j];
 #pragma unroll
     for (int e = 0; e < NEB; ++e) {
       const int f = 16 * e + 4 * g;
-      const v4f v = o[j][e] * inv;
-      int c[4];
+      unsigned w = 0;
+      float dist[4];                                // distance from the rounding boundary plus the window's relative part
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float qv = v[r] * inv_qs, rr = rintf(qv);
-        c[r] = (int)fminf(fmaxf(rr + qz, -128.f), 127.f);
-        if (q_row[j] < T && f + r < hd && fabsf(fabsf(qv - rr) - 0.5f) < fmaf(tol_q, fabsf(qv), tol_0)) {
-          const int slot = atomicAdd(fix_cnt, 1);
-          if (slot < FIX_CAP) {
-            fix_ent[2 * slot] = qloc;
-            fix_ent[2 * slot + 1] = f + r;
-          }
-        }
+        const float qv = o[j][e][r] * k, rr = __builtin_rintf(qv);
+        w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(rr + zu, 0.0f, 255.0f), r, w);
+        dist[r] = fmaf(tol_q, fabsf(qv), fabsf(qv - rr));
       }
-      *(unsigned *)(stage + qloc * SRB + f) = (unsigned)(c[0] & 0xFF) | ((unsigned)(c[1] & 0xFF) << 8) |
-                                              ((unsigned)(c[2] & 0xFF) << 16) | ((unsigned)(c[3] & 0xFF) << 24);
+      // one comparison and one branch per four outputs
+      if (fmaxf(fmaxf(dist[0], dist[1]), fmaxf(dist[2], dist[3])) > doubt_at) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (dist[r] > doubt_at && q_row[j] < T && f + r < hd) {
+            const int slot = atomicAdd(fix_cnt, 1);
+            if (slot < FIX_CAP) {
+              fix_ent[2 * slot] = qloc;
+              fix_ent[2 * slot + 1] = f + r;
+            }
+          }
+      }
+      *(unsigned *)(stage + qloc * SRB + f) = w ^ 0x80808080u;
     }
   }
   __syncthreads();
   const int q_first = qblk * NQ;                  // first query of the workgroup
   {
-    // softmax(q K^T / sqrt(d)) V[:, feature] in float64 for every queued output
+    // softmax(q K^T / sqrt(d)) V[:, feature] in float64 for every queued output.  The reference point of the exponentials is
+    // the running max of the fast path (any point near the maximum gives the same quotient), so the parts of a sum need no
+    // common maximum: wavefront w takes the groups w, w + NW, ... of 64 keys of every output and the parts meet in LDS.  Four
+    // lanes share a key row (lane h: 16-byte chunks h, h + 4, ...) and take four keys of a group, 16 apart; a row of the
+    // next group is requested as soon as the current one is used, and after the exchange each lane has one key's score: one
+    // exponential per lane and group.  About 250 float64-rate instructions per 64 keys are what bounds it.
     const int nfix = min(*fix_cnt, FIX_CAP);
-    const int ld = hd;
-    const float *qbase = Qp + tok_base, *kbase = Kp + tok_base;
+    constexpr int FB = (int)sizeof(Vsh) / (NW * 16) < 64 ? (int)sizeof(Vsh) / (NW * 16) : 64;   // outputs per batch of parts in LDS
+    double *const parts = (double *)&Vsh[0][0];                   // [output][wavefront][2]
     const double rs = 1.0 / sqrt((double)hd);
-    // One wavefront per queued output.  A key row is shared by a pair of lanes (even lane: first half of its 16-byte
-    // chunks, odd lane: second half); a lane pair takes four keys per pass and all their loads are issued at once, so
-    // 128 keys cost one memory round trip; chunks beyond d are read from a clamped address and multiplied by zero.
-    // Running (max, sum, weighted sum) per lane; the lanes are merged by reducing the max first, so that the merge
-    // needs one exponential per lane.
-    constexpr int NCH2 = 2 * NEB;                 // chunks per lane
-    constexpr int KU = NEB >= 5 ? 2 : (NEB >= 4 ? 3 : 4);      // keys in flight per lane pair (as many as the register file holds)
-    const int half = lane & 1, kl = lane >> 1;    // 32 lane pairs
-    for (int fi = wave; fi < nfix; fi += 4) {
-      const int qloc = fix_ent[2 * fi], feat = fix_ent[2 * fi + 1];
-      const float *qr = qbase + (size_t)(q_first + qloc) * ld;
-      const float *vrow = Vt + vt_base + (size_t)feat * Tp;       // V^T row of the feature, keys in vt_pos order
-      v4f qf[NCH2];
+    const int h4 = lane & 3, kl = lane >> 2;
+    for (int base = 0; base < nfix; base += FB) {
+      const int nb = min(nfix - base, FB);
+      for (int fi = 0; fi < nb; ++fi) {
+        const int qloc = fix_ent[2 * (base + fi)], feat = fix_ent[2 * (base + fi) + 1];
+        const float *qr = Qp + tok_base + (size_t)(q_first + qloc) * hd;
+        const float *vrow = vbase + (size_t)feat * Tp;            // V^T row of the feature, keys in vt_pos order
+        v4f kv[4][NEB];
+        float va;
+        auto load_row = [&](int key, v4f (&dst)[NEB]) {
+          const float *r = kbase + (size_t)min(key, T - 1) * hd;
 #pragma unroll
-      for (int c = 0; c < NCH2; ++c) {
-        const int d0 = 4 * (half * NCH2 + c);
-        qf[c] = *(const v4f *)(qr + min(d0, hd - 4));
-        if (d0 >= hd) qf[c] = (v4f){0.f, 0.f, 0.f, 0.f};
-      }
-      double mx = -INFINITY, den = 0.0, num = 0.0;
-      for (int k0 = 0; k0 < T; k0 += 32 * KU) {
-        v4f kv[KU][NCH2];
-        float vv[KU];
+          for (int c = 0; c < NEB; ++c) dst[c] = *(const v4f *)(r + min(16 * c + 4 * h4, hd - 4));
+        };
+        int k0 = 64 * wave;
 #pragma unroll
-        for (int u = 0; u < KU; ++u) {
-          const int key = min(k0 + 32 * u + kl, T - 1);
-          const float *kr = kbase + (size_t)key * ld;
+        for (int u = 0; u < 4; ++u) load_row(k0 + 16 * u + kl, kv[u]);
+        va = vrow[vt_pos(min(k0 + 16 * h4 + kl, Tp - 1))];
+        double qd[NEB][4];
 #pragma unroll
-          for (int c = 0; c < NCH2; ++c) kv[u][c] = *(const v4f *)(kr + min(4 * (half * NCH2 + c), hd - 4));
-          vv[u] = vrow[vt_pos(key)];
+        for (int c = 0; c < NEB; ++c) {
+          const int f = 16 * c + 4 * h4;
+          const v4f t4 = *(const v4f *)(qr + min(f, hd - 4));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) qd[c][e] = f < hd ? (double)t4[e] : 0.0;
         }
-        double sv[KU];
-        double pm = -INFINITY;
+        const double mref = (double)m_s[qloc] * 0.6931471805599453;       // base 2 -> natural
+        double den = 0.0, num = 0.0;
+        for (; k0 < T; k0 += 64 * NW) {
+          const float v = va;
+          double sc = 0.0;
 #pragma unroll
-        for (int u = 0; u < KU; ++u) {
-          double acc = 0.0;
+          for (int u = 0; u < 4; ++u) {
+            double a0 = 0.0, a1 = 0.0;
 #pragma unroll
-          for (int c = 0; c < NCH2; ++c) {
-            acc = fma((double)qf[c][0], (double)kv[u][c][0], acc);
-            acc = fma((double)qf[c][1], (double)kv[u][c][1], acc);
-            acc = fma((double)qf[c][2], (double)kv[u][c][2], acc);
-            acc = fma((double)qf[c][3], (double)kv[u][c][3], acc);
+            for (int c = 0; c < NEB; ++c) {
+              a0 = fma(qd[c][0], (double)kv[u][c][0], a0);
+              a1 = fma(qd[c][1], (double)kv[u][c][1], a1);
+              a0 = fma(qd[c][2], (double)kv[u][c][2], a0);
+              a1 = fma(qd[c][3], (double)kv[u][c][3], a1);
+            }
+            load_row(k0 + 64 * NW + 16 * u + kl, kv[u]);          // beyond T: the last row again, never used
+            a0 += a1;
+            a0 += dpp_move_d<0xB1>(a0);                           // quad_perm [1, 0, 3, 2], then [2, 3, 0, 1]: the four lanes
+            a0 += dpp_move_d<0x4E>(a0);                           // hold the whole dot product
+            sc = h4 == u ? a0 : sc;
           }
-          acc += __shfl_xor(acc, 1, 64);          // both lanes of the pair now hold the whole dot product
-          sv[u] = (k0 + 32 * u + kl < T && half == 0) ? acc * rs : -INFINITY;      // the even lane carries the key
-          pm = fmax(pm, sv[u]);
+          va = vrow[vt_pos(min(k0 + 64 * NW + 16 * h4 + kl, Tp - 1))];
+          const double pj = k0 + 16 * h4 + kl < T ? exp(sc * rs - mref) : 0.0;
+          den += pj;
+          num = fma(pj, (double)v, num);
         }
-        if (pm > -INFINITY) {
-          const double mn = fmax(mx, pm);
-          const double a2 = exp(mx - mn);         // exp(-inf) = 0 on the first pass
-          den *= a2;
-          num *= a2;
-#pragma unroll
-          for (int u = 0; u < KU; ++u) {
-            const double pj = exp(sv[u] - mn);    // 0 for a key that is not this lane's
-            den += pj;
-            num = fma(pj, (double)vv[u], num);
-          }
-          mx = mn;
+        den = wave_sum_dpp(den);
+        num = wave_sum_dpp(num);
+        if (lane == 0) {
+          parts[(fi * NW + wave) * 2] = den;
+          parts[(fi * NW + wave) * 2 + 1] = num;
         }
       }
-      double gm = mx;
+      __syncthreads();
+      if (tid < nb) {
+        double den = 0.0, num = 0.0;
 #pragma unroll
-      for (int o2 = 32; o2 > 0; o2 >>= 1) gm = fmax(gm, __shfl_xor(gm, o2, 64));
-      const double sc2 = mx > -INFINITY ? exp(mx - gm) : 0.0;
-      den *= sc2;
-      num *= sc2;
-#pragma unroll
-      for (int o2 = 32; o2 > 0; o2 >>= 1) {
-        den += __shfl_xor(den, o2, 64);
-        num += __shfl_xor(num, o2, 64);
-      }
-      if (lane == 0) {
+        for (int w = 0; w < NW; ++w) {
+          den += parts[(tid * NW + w) * 2];
+          num += parts[(tid * NW + w) * 2 + 1];
+        }
         const float ov = (float)(num / den);
-        stage[qloc * SRB + feat] = (unsigned char)(int)fminf(fmaxf(rintf(ov / qs) + qz, -128.f), 127.f);
+        stage[fix_ent[2 * (base + tid)] * SRB + fix_ent[2 * (base + tid) + 1]] =
+            (unsigned char)(int)fminf(fmaxf(rintf(ov / qs) + qz, -128.f), 127.f);
       }
+      __syncthreads();
     }
-    if (nfix) __syncthreads();
   }
   // rows out: hd bytes per query (a multiple of 4), contiguous in the output row of the token
-  const int wpr = hd >> 2;                        // 32-bit words per row (<= 20): 32 lanes per row, 8 rows per pass
+  const int wpr = hd >> 2;                        // 32-bit words per row (<= 20): 32 lanes per row, 2 NW rows per pass
   const int wd = tid & 31;
 #pragma unroll
-  for (int r0 = 0; r0 < NQ; r0 += 8) {
+  for (int r0 = 0; r0 < NQ; r0 += 2 * NW) {
     const int qloc = r0 + (tid >> 5), qg = q_first + qloc;
     if (wd < wpr && qg < T)
       *(unsigned *)(q_out + ((size_t)b * T + qg) * D + (size_t)h * hd + 4 * wd) = *(const unsigned *)(stage + qloc * SRB + 4 * wd);
@@ -618,23 +695,29 @@ hipError_t launch_attention_f16(const float *q32, const float *k32, const float 
   const int neb = (hd + 15) / 16, nch = (hd + 31) / 32;
   if (hd > 80 || hd % 4) return hipErrorInvalidValue;      // K prefetch registers are sized for d <= 80
   const float q_mul = 1.4426950408889634f / std::sqrt((float)hd);     // log2(e) / sqrt(d)
-  // one query block per wavefront when two would leave compute units without a workgroup
-  const int qb = B * H * ((T + 127) / 128) < 256 ? 1 : 2;
+  // Two query blocks per wavefront (128 queries per workgroup) when that makes more workgroups than compute units, else one.
+  // Measured, one / two (16 heads of 72; us): 128 x 256 tokens 290 / 235 (281 before this form of the kernel), 16 x 1024:
+  // 422 / 328 (420), 16 x 256: 39.2 / 30.9, 8 x 256: 20.8 / 21.8 (26.2), 3 x 425: 29.5 / 31.2, 1 x 256: 14.4 / 18.8 (17.5);
+  // workgroups of eight wavefronts came out within 2 % at 1024 tokens and behind elsewhere.
+  const int qb = B * H * ((T + 127) / 128) <= 256 ? 1 : 2;
   dim3 grid((B * H + 7) / 8 * 8, (T + 64 * qb - 1) / (64 * qb));
-#define QC_ATT(NCH, NEB)                                                                                                    \
+#define QC_ATT(NCH, NEB, TAIL)                                                                                              \
   do {                                                                                                                      \
     if (qb == 1)                                                                                                            \
-      hipLaunchKernelGGL((attention_f16_kernel<NCH, NEB, 1>), grid, dim3(256), 0, st, q32, k32, vt32, B * H, T, Tp, H, hd, DPv,    \
-                         q_mul, qp, q_out);                                                                                 \
+      hipLaunchKernelGGL((attention_f16_kernel<NCH, NEB, 1, TAIL>), grid, dim3(256), 0, st, q32, k32, vt32, B * H, T, Tp, H, hd, \
+                         DPv, q_mul, qp, q_out);                                                                            \
     else                                                                                                                    \
-      hipLaunchKernelGGL((attention_f16_kernel<NCH, NEB, 2>), grid, dim3(256), 0, st, q32, k32, vt32, B * H, T, Tp, H, hd, DPv,    \
-                         q_mul, qp, q_out);                                                                                 \
+      hipLaunchKernelGGL((attention_f16_kernel<NCH, NEB, 2, TAIL>), grid, dim3(256), 0, st, q32, k32, vt32, B * H, T, Tp, H, hd, \
+                         DPv, q_mul, qp, q_out);                                                                            \
   } while (0)
-  if (nch == 1 && neb == 1) QC_ATT(1, 1);
-  else if (nch == 1) QC_ATT(1, 2);
-  else if (nch == 2 && neb == 3) QC_ATT(2, 3);
-  else if (nch == 2) QC_ATT(2, 4);
-  else if (nch == 3 && neb == 5) QC_ATT(3, 5);
+  const bool tail = nch > 1 && hd - 32 * (nch - 1) <= 8;      // at most 8 features in the last chunk
+  if (nch == 1 && neb == 1) QC_ATT(1, 1, false);
+  else if (nch == 1) QC_ATT(1, 2, false);
+  else if (nch == 2 && neb == 3 && tail) QC_ATT(2, 3, true);
+  else if (nch == 2 && neb == 3) QC_ATT(2, 3, false);
+  else if (nch == 2) QC_ATT(2, 4, false);
+  else if (nch == 3 && neb == 5 && tail) QC_ATT(3, 5, true);
+  else if (nch == 3 && neb == 5) QC_ATT(3, 5, false);
   else return hipErrorInvalidValue;
 #undef QC_ATT
   return hipGetLastError();

@@ -117,6 +117,29 @@ __device__ __forceinline__ void stream_store4(void *x, size_t i4, float4 v, int 
   }
 }
 
+// ---- cross-lane moves of a double on the data-parallel-primitive paths (no LDS)
+template <int CTRL>
+__device__ __forceinline__ double dpp_move_d(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned long long)(unsigned)lo);
+}
+__device__ __forceinline__ double readlane_d(double v, int l) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | (unsigned long long)lo);
+}
+// the same value in every lane (every lane adds the same pairs in the same order)
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+  v += dpp_move_d<0xB1>(v);     // quad_perm [1, 0, 3, 2]
+  v += dpp_move_d<0x4E>(v);     // quad_perm [2, 3, 0, 1]
+  v += dpp_move_d<0x141>(v);    // row_half_mirror: the other quad of the half row
+  v += dpp_move_d<0x140>(v);    // row_mirror: the other half of the row of 16
+  return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
+}
+
 hipError_t launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st, int site);
 // the split-K kernel of small launches (gemm_i8_split.hip): whether a launch is one of them, and the launch
 bool gemm_split_pays(const GemmArgs &a, int epi, int nz);

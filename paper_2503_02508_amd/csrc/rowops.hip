@@ -222,28 +222,6 @@ __global__ __launch_bounds__(512) void ln_mod_quant_kernel(const void *__restric
 // expression as above, rounded to float32 once.  Eq. 1 takes v * (1 / s) where that is certain to round to the same
 // integer as the IEEE quotient v / s and the quotient itself otherwise (decided for a float4 of the whole wavefront at
 // a time, so the common case is branch-free).
-template <int CTRL>
-__device__ __forceinline__ double dpp_move_d(double v) {
-  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
-  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned long long)(unsigned)lo);
-}
-__device__ __forceinline__ double readlane_d(double v, int l) {
-  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | (unsigned long long)lo);
-}
-// the same value in every lane (every lane adds the same pairs in the same order)
-__device__ __forceinline__ double wave_sum_dpp(double v) {
-  v += dpp_move_d<0xB1>(v);     // quad_perm [1, 0, 3, 2]
-  v += dpp_move_d<0x4E>(v);     // quad_perm [2, 3, 0, 1]
-  v += dpp_move_d<0x141>(v);    // row_half_mirror: the other quad of the half row
-  v += dpp_move_d<0x140>(v);    // row_mirror: the other half of the row of 16
-  return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
-}
-
 // Eq. 1 for four values at once, packed signed codes.  qf = v * inv_s differs from the correctly rounded quotient by
 // less than 2 units in its last place (inv_s carries half a unit of relative error, the product another half, the
 // quotient's own rounding a third), so when qf is farther than 4e-7 |qf| from a rounding boundary both round to the same

@@ -33,3 +33,21 @@ def test_reference_forward_does_not_depend_on_the_batch(hidden, heads, mlp, hw, 
         ctx.denoise_f32(x[b:b + 1], 345, lab[b:b + 1], 1, one[b:b + 1])
     assert torch.equal(eps, one)
     assert float(eps.abs().max()) > 0
+
+
+def _net(hidden, heads, mlp, h, w, patch=2):
+    return I.ModelDesc(depth=1, hidden=hidden, heads=heads, mlp_dim=mlp, patch=patch, latent_c=4, latent_h=h, latent_w=w)
+
+
+@pytest.mark.parametrize("name,model,B,wb", [
+    ("attention: 36 features a head (packed tail, two chunks), 70 tokens", _net(144, 4, 576, 20, 14), 3, 8),
+    ("attention: 72 features a head, 1 key past a tile", _net(288, 4, 512, 10, 26), 2, 8),
+    ("attention: two query blocks a wavefront, 575 tokens", _net(256, 4, 512, 46, 50), 33, 8),
+    ("attention: 16 features a head", _net(64, 4, 128, 16, 22), 2, 8),
+    ("split-K: one row past a 32-row tile, 4-bit", _net(128, 2, 512, 6, 22), 1, 4),
+    ("split-K: 64 x 64 tiles with remainders", _net(384, 6, 1536, 30, 26), 2, 8),
+    ("split-K: 64 x 96 tiles", _net(1152, 16, 4608, 32, 32), 4, 8),
+])
+def test_quantisers_of_small_and_ragged_launches(name, model, B, wb):
+    from test_gpu_quantisers import test_each_fused_quantiser_alone as check
+    check(name, model, B, wb, 0.05)
