@@ -329,7 +329,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN == 4 && BM * BN <= 128 * 128
 // all LDS writes of this wavefront done, then the workgroup barrier
 #define QC_LDS_DONE_BARRIER asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
 
-template <int EPI, int TAG, bool W4, bool RBF>
+template <int EPI, int TAG, bool W4, bool RBF, bool RAG>
 __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   constexpr int BM = 128, BN = 256, WM = 1, WN = 4, TM = 4, TN = 2, BK = 64;
   constexpr int RB = 4, NB = 3, NS = 2;           // ring depth (k-groups), LDS slab buffers, slabs in flight in registers
@@ -498,20 +498,24 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   QC_WAIT_VM(0);
   __builtin_amdgcn_sched_barrier(0);
   __syncthreads();
-  gemm_epilogue<BM, BN, WM, WN, EPI, true, RBF>(p, acc, smem, m0, n0, 0);
+  gemm_epilogue<BM, BN, WM, WN, EPI, true, RBF, RAG>(p, acc, smem, m0, n0, 0);
 }
 
 constexpr int BIG_SMEM_LOOP = 3 * 128 * 64;
 constexpr int BIG_SMEM_STAGE = 128 * (128 + 4) * 4;                      // one staged column half, float32 (QKV scatter, residual)
 constexpr int BIG_SMEM_GELU = 256 * 12 + 128 * (256 + 16) + 16 + GELU_FIX_CAP * 16;
 
-template <int EPI, int TAG, bool W4, bool RBF>
+template <int EPI, int TAG, bool W4, bool RBF, bool RAG = false>
 static hipError_t launch_big_fmt(const GemmArgs &a, hipStream_t st) {
+  // launches whose tiles are not all whole and inside one batch element take the variant that handles the others
+  if constexpr (!RAG && (EPI == EPI_RESID || EPI == EPI_QKV)) {
+    if (a.M % 128 || a.rows_per_batch % 128) return launch_big_fmt<EPI, TAG, W4, RBF, true>(a, st);
+  }
   constexpr int smem_epi = EPI == EPI_GELU_Q ? BIG_SMEM_GELU : BIG_SMEM_STAGE;
   constexpr int smem = smem_epi > BIG_SMEM_LOOP ? smem_epi : BIG_SMEM_LOOP;
   static_assert(2 * smem <= 160 * 1024, "two workgroups per compute unit");
   static bool attr_set = false;
-  auto kern = gemm_i8_big_kernel<EPI, TAG, W4, RBF>;
+  auto kern = gemm_i8_big_kernel<EPI, TAG, W4, RBF, RAG>;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
@@ -532,18 +536,20 @@ static hipError_t launch_big_fmt(const GemmArgs &a, hipStream_t st) {
 // the residual epilogue is compiled twice: for float32 stream and cache, and for the bfloat16 variants of either
 template <int EPI, int TAG, bool W4>
 static hipError_t launch_big(const GemmArgs &a, hipStream_t st) {
-  if (EPI == EPI_RESID && (a.x_bf16 || a.cache_bf16)) return launch_big_fmt<EPI, TAG, W4, true>(a, st);
+  if constexpr (EPI == EPI_RESID) {
+    if (a.x_bf16 || a.cache_bf16) return launch_big_fmt<EPI, TAG, W4, true>(a, st);
+  }
   return launch_big_fmt<EPI, TAG, W4, false>(a, st);
 }
 
 // The large-M kernel takes over when the weights exist in fragment order, the shape fits its loop (K a multiple of
-// 128, N of 32, 16-byte aligned rows), every 128-row tile is whole and inside one batch element (its epilogues are
+// 128, N of 32, 16-byte aligned rows), a 128-row tile holds rows of at most two batch elements (its epilogues are
 // compiled without the general paths) and the launch has enough 128 x 256 tiles for it to pay.
 static bool use_big(const GemmArgs &a, int epi, int nz) {
   if (!a.Wt || nz != 1 || a.sel_D || a.acc_out) return false;
-  if (a.K % 128 || a.N % 32 || a.lda % 16 || a.M % 128) return false;
-  if (epi == EPI_RESID && a.rows_per_batch % 128) return false;
-  if (epi == EPI_QKV && (a.y || a.rows_per_batch % 128 || (a.N / 3) % 128 || a.hd % 4 || a.Tp % 8)) return false;
+  if (a.K % 128 || a.N % 32 || a.lda % 16) return false;
+  if (epi == EPI_RESID && a.rows_per_batch < 128) return false;
+  if (epi == EPI_QKV && (a.y || a.rows_per_batch < 128 || (a.N / 3) % 128 || a.hd % 4 || a.Tp % 8)) return false;
   const long long tiles = (long long)((a.M + 127) / 128) * ((a.N + 255) / 256);
   // measured alone on the chip (DiT-XL/2 shapes): 160 tiles (proj / fc2 at M = 4096) run 20 % faster here than in the
   // tile kernel, 224 - 288 tiles (QKV / fc1 at M = 2048) 0 - 10 % faster, 112 - 144 tiles (M = 1024) 3 - 15 % slower,

@@ -89,7 +89,9 @@ __device__ __forceinline__ int quant_code(float v, float s, float inv_s, float z
 // FAST: the launcher has checked that every tile is interior along m and lies in one batch element (and, for the QKV
 // scatter, the alignment its staged path needs); the general paths are then not compiled into the kernel.
 // RBF: the residual stream or the cache may be bfloat16 (read from the arguments); false: both are known to be float32.
-template <int BM, int BN, int WM, int WN, int EPI, bool FAST = false, bool RBF = true>
+// RAG (with FAST): tiles may end beyond the last row and may span two batch elements (which have at least BM rows each); a
+// tile tests once which case it is, whole tiles inside one batch element keep the fast code.
+template <int BM, int BN, int WM, int WN, int EPI, bool FAST = false, bool RBF = true, bool RAG = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM / WM / 32][BN / WN / 32], unsigned char *smem,
                                               const int m0, const int n0, const int z) {
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NT = 64 * WM * WN;
@@ -221,6 +223,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
       // the K loop) and leave as 16-byte stores along the contiguous direction of their layout (Q / K: features of a
       // token and head; V^T: tokens of a feature).
       const int tb = m0 - b_tile * T;                         // first token of the tile
+      const int rows = RAG ? min(BM, p.M - m0) : BM;          // rows of the tile that exist
+      const int bnd = RAG ? min(rows, T - tb) : BM;           // rows of the first batch element (the others: of the next)
+      const bool edge = RAG && (bnd < BM || (tb & 31) != 0);
 #pragma unroll
       for (int hn = 0; hn < BN / HN; ++hn) {
         const int n0h = n0 + hn * HN;                         // first column of this half
@@ -256,7 +261,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
                 for (int q = 0; q < 4; ++q) stage[(ml + q) * SR + nl] = v[q];
               } else {
                 // four consecutive tokens stay together under the key permutation of the V^T rows
-                *(v4f *)(stage + nl * VR + vt_pos(ml)) = v;
+                *(v4f *)(stage + nl * VR + (edge ? ml : vt_pos(ml))) = v;
               }
             }
             if (TM * TN > 4) __builtin_amdgcn_sched_barrier(0);      // large register tiles: keep the live ranges of a block short
@@ -270,6 +275,16 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
           const int nn = n0h - part * D + cc, h = nn / p.hd, e = nn - h * p.hd;
           float *dst = (part == 0 ? p.q32 : p.k32) +
                        ((unsigned)(b_tile * p.heads + h) * (unsigned)T + (unsigned)(tb + cr)) * (unsigned)p.hd + (unsigned)e;
+          if (RAG && edge) {
+            // row beyond the first batch element: its token 0 lies (heads - 1) * T tokens further than the next row would
+#pragma unroll
+            for (int q = 0; q < BM * 32 / NT; ++q) {
+              const int ml = cr + q * (NT / 32);
+              const unsigned skip = ml >= bnd ? (unsigned)(p.heads - 1) * (unsigned)T : 0u;
+              if (ml < rows) *(v4f *)(dst + ((unsigned)(q * (NT / 32)) + skip) * (unsigned)p.hd) = *(const v4f *)(stage + ml * SR + cc);
+            }
+            continue;
+          }
 #pragma unroll
           for (int q = 0; q < BM * 32 / NT; ++q) {
             const v4f v = *(const v4f *)(stage + (cr + q * (NT / 32)) * SR + cc);
@@ -280,6 +295,29 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
         } else {
           // thread -> 4 consecutive token positions ch of the features fc, fc + NT / 32, ...
           const int fc = tid >> 5, ch = (tid & 31) * 4;
+          if (RAG && edge) {
+            // the tile's rows do not start at a group of 32 keys: natural order in LDS, permuted on the way out.  Units of
+            // four tokens stay whole when T is a multiple of 4 (then so is every tile's first token)
+            const bool second = ch >= bnd;
+            const int t0 = tb + ch - (second ? T : 0), b = b_tile + (second ? 1 : 0);
+#pragma unroll 4
+            for (int q = 0; q < HN * 32 / NT; ++q) {
+              const int col = fc + q * (NT / 32);
+              const int nn = n0h - 2 * D + col, h = nn / p.hd, e = nn - h * p.hd;
+              const float *src = stage + col * VR + ch;
+              if ((T & 3) == 0) {
+                float *row = p.vt32 + ((size_t)(b * p.heads + h) * p.DP + e) * p.Tp;
+                if (ch < rows) *(v4f *)(row + vt_pos(t0)) = *(const v4f *)src;
+              } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                  const int ml = ch + u, bu = b_tile + (ml >= bnd ? 1 : 0), t = tb + ml - (ml >= bnd ? T : 0);
+                  if (ml < rows) p.vt32[((size_t)(bu * p.heads + h) * p.DP + e) * p.Tp + vt_pos(t)] = src[u];
+                }
+              }
+            }
+            continue;
+          }
 #pragma unroll
           for (int q = 0; q < HN * 32 / NT; ++q) {
             const int col = fc + q * (NT / 32);
@@ -344,6 +382,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
     const bool uniform_batch = (p.rows_per_batch % BM) == 0;
     const int b_uniform = m0 / p.rows_per_batch;
     const int x_bf16 = RBF ? p.x_bf16 : 0, cache_bf16 = RBF ? p.cache_bf16 : 0;
+    const int rows = RAG ? min(BM, p.M - m0) : BM;                                  // rows of the tile that exist
+    const int bnd = RAG ? min(rows, (b_uniform + 1) * p.rows_per_batch - m0) : BM;  // rows of the first batch element
+    const size_t gate1 = RAG && bnd < rows ? (size_t)p.ld_gate : 0;                 // gate row of the others, relative
     if (FAST && RBF && (x_bf16 || cache_bf16) && p.N % 128 == 0) {
       // A bfloat16 stream or cache: 32 lanes of a wavefront cover only 64 bytes of a row, and 2-byte stores leave
       // every cache line half written.  The dequantised values go through LDS in column halves of 128 instead, and
@@ -357,7 +398,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
         if (n0h >= p.N) break;
         const bool mine = wn0 / HN == hn;               // this wavefront's columns lie in the half
         if (hn) __syncthreads();                        // the previous half has left the staging area
-        const v4f gv = *(const v4f *)(p.gate + (long long)b_uniform * p.ld_gate + n0h + cc);
+        const float *gp = p.gate + (long long)b_uniform * p.ld_gate + n0h + cc;
+        const v4f gv0 = *(const v4f *)gp, gv1 = RAG ? *(const v4f *)(gp + gate1) : gv0;
         const size_t ob4 = ((size_t)m0 * p.N + n0h + cc) >> 2;      // in groups of four elements
         const size_t row4 = (size_t)p.N >> 2;
         // a bfloat16 stream: the thread's 16 pieces of x (8 bytes each) are requested before the staging, which hides
@@ -365,7 +407,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
         uint2 xraw[RQ];
         if (x_bf16) {
 #pragma unroll
-          for (int q = 0; q < RQ; ++q) xraw[q] = ((const uint2 *)p.x)[ob4 + (size_t)(cr + q * (NT / 32)) * row4];
+          for (int q = 0; q < RQ; ++q) {
+            const int row = cr + q * (NT / 32);
+            xraw[q] = ((const uint2 *)p.x)[ob4 + (size_t)(RAG ? min(row, rows - 1) : row) * row4];
+          }
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
@@ -383,9 +428,11 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
           }
         }
         __syncthreads();
-#pragma unroll 4
-        for (int q = 0; q < RQ; ++q) {
+#pragma unroll
+        for (int q = 0; q < RQ; ++q) {      // (fully: xraw must stay in registers)
           const int row = cr + q * (NT / 32);
+          if (RAG && row >= rows) continue;
+          const v4f gv = RAG && row >= bnd ? gv1 : gv0;
           const v4f v = *(const v4f *)(stage + row * SR + cc);
           const size_t o4 = ob4 + (size_t)row * row4;
           float4 xo;
@@ -408,11 +455,45 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
       // (scalar arithmetic) plus one 32-bit lane offset, and the loads of x of XB blocks (16 values per lane each: the
       // registers of the K loop's operand ring and fragments are free now) are issued before the first is used, so a
       // tile's epilogue pays TM x TN / XB memory round trips instead of TM x TN.
-      constexpr int XB = (!RBF && TM % 2 == 0) ? 2 : 1;   // the bfloat16 variants have no registers to spare   // the bfloat16 variants have no registers to spare
+      constexpr int XB = (!RBF && TM % 2 == 0) ? 2 : 1;   // the bfloat16 variants have no registers to spare
       const int wv = __builtin_amdgcn_readfirstlane(wave);
       const int wm0u = (wv / WN) * (BM / WM), wn0u = (wv % WN) * (BN / WN);
       const unsigned loff = (unsigned)((lane >> 5) * 4) * (unsigned)p.N + (unsigned)(lane & 31);
       const size_t xsz = x_bf16 ? 2 : 4, csz = cache_bf16 ? 2 : 4;
+      if (RAG && bnd < BM) {
+        // a tile with rows of two batch elements or rows beyond the last one
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int nb = n0 + wn0u + j * 32;
+          if (nb >= p.N) continue;
+          const int n = nb + (lane & 31);
+          const double sc = (double)a_s * (double)w_scale[n];
+          const int zw = a_z * wsum[n];
+          const double bs = bias ? (double)bias[n] : 0.0;
+          const float g0 = p.gate[(long long)b_uniform * p.ld_gate + n], g1 = p.gate[(long long)b_uniform * p.ld_gate + gate1 + n];
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+            const int mb = wm0u + i * 32 + (lane >> 5) * 4;
+            float xv[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              xv[r] = stream_load(p.x, (size_t)(m0 + min(mb + (r >> 2) * 8 + (r & 3), rows - 1)) * p.N + n, x_bf16);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const int ml = mb + (r >> 2) * 8 + (r & 3);
+              const float v = dequant_f32(sc, acc[i][j][r] - zw, bs);
+              if (ml < rows) {
+                const size_t o = (size_t)(m0 + ml) * p.N + n;
+                stream_store(p.cache_out, o, v, cache_bf16);
+                stream_store(p.x, o, fmaf(ml >= bnd ? g1 : g0, v, xv[r]), x_bf16);
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        return;
+      }
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int nb = n0 + wn0u + j * 32;
