@@ -90,7 +90,7 @@ struct qc_ctx {
   std::vector<unsigned char> cache_mask;   // optional [steps][L][2] schedule (1 = recompute); empty = interval rule
   int mask_steps = 0;
   // workspace
-  float *emb, *h1, *te, *cond, *mod, *fmod, *tokens, *qkv, *eps;
+  float *h1, *te, *cond, *mod, *fmod, *tokens, *qkv, *eps;
   float *eps_ref;      // noise prediction of the un-quantised reference forward (VC fitting)
   double *vcfit_work;  // per-plane partial sums of the VC fit [max_batch * C][2]
   int8_t *silu_q, *qa_ln, *qa_attn, *qa_mlp;
@@ -209,7 +209,7 @@ static size_t layout(const qc_model_desc &d, int max_batch, char *base, qc_ctx *
   QParam *dev_qp = a.take<QParam>(L * QC_NUM_SITES);
   float *cache = a.take<float>(L * 2 * M * D);
   const size_t WR = B > (size_t)WINDOW_ROWS ? B : (size_t)WINDOW_ROWS;
-  float *emb = a.take<float>(WR * d.freq_dim), *h1 = a.take<float>(WR * D), *te = a.take<float>(WR * D);
+  float *h1 = a.take<float>(WR * D), *te = a.take<float>(WR * D);
   float *cond = a.take<float>(WR * D), *mod = a.take<float>(L * WR * 6 * D), *fmod = a.take<float>(WR * 2 * D);
   float *tokens = a.take<float>(M * D), *qkv = a.take<float>(M * 3 * D), *eps = a.take<float>(B * C * d.latent_h * d.latent_w);
   int8_t *silu_q = a.take<int8_t>(L * WR * D), *qa_ln = a.take<int8_t>(M * D), *qa_attn = a.take<int8_t>(M * D);
@@ -229,7 +229,7 @@ static size_t layout(const qc_model_desc &d, int max_batch, char *base, qc_ctx *
   if (c) {
     c->patch_w = patch_w; c->patch_b = patch_b; c->pos = pos; c->t_w1 = t_w1; c->t_b1 = t_b1; c->t_w2 = t_w2; c->t_b2 = t_b2;
     c->label_table = label_table; c->fada_w = fada_w; c->fada_b = fada_b; c->flin_w = flin_w; c->flin_b = flin_b;
-    c->dev_qp = dev_qp; c->cache = cache; c->emb = emb; c->h1 = h1; c->te = te; c->cond = cond; c->mod = mod; c->fmod = fmod;
+    c->dev_qp = dev_qp; c->cache = cache; c->h1 = h1; c->te = te; c->cond = cond; c->mod = mod; c->fmod = fmod;
     c->tokens = tokens; c->qkv = qkv; c->eps = eps; c->silu_q = silu_q; c->qa_ln = qa_ln; c->qa_attn = qa_attn;
     c->qa_mlp = qa_mlp; c->cal_h = cal_h; c->cal_o = cal_o; c->cal_a = cal_a; c->cal_u = cal_u; c->cal_mod = cal_mod;
     c->cal_cond = cal_cond; c->cal_group = (int)G;
@@ -561,8 +561,9 @@ int qc_dit_block(qc_ctx *ctx, int block, int mode, float *x, const float *c, int
     QC_FAIL(QC_ERR_STATE, "block %d has no cached outputs for batch %d", block, B);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const size_t D = ctx->D;
-  QC_HIP(launch_silu_quant(c, B, (int)D, 1, ctx->dev_qp + (size_t)block * QC_NUM_SITES + QC_SITE_ADA, QC_NUM_SITES,
-                           ctx->silu_q + (size_t)block * ctx->win_rows * D, (size_t)ctx->win_rows * D, st));
+  QC_HIP(launch_cond_silu(nullptr, nullptr, nullptr, 0, 0, B, B, (int)D, const_cast<float *>(c), nullptr, 1,
+                          ctx->dev_qp + (size_t)block * QC_NUM_SITES + QC_SITE_ADA, QC_NUM_SITES,
+                          ctx->silu_q + (size_t)block * ctx->win_rows * D, (size_t)ctx->win_rows * D, st));
   const Sub whole{0, B, 0, 0};
   rc = run_adaln(ctx, block, 1, 0, B, mode == QC_CACHED, st);
   if (rc) return rc;
@@ -696,19 +697,21 @@ int qc_keep_qkv_f32(qc_ctx *ctx, int on) {
 }
 
 // Conditioning vectors for nw timesteps and one set of labels: c[w * B + b, :] = tMLP(sinusoid(t[w])) + E[y_b]
-// (null label for b >= n_labels), rows 0 .. nw*B of the table.
-static int run_cond(qc_ctx *ctx, const int32_t *t, int nw, const int32_t *labels, int n_labels, int B, hipStream_t st) {
+// (null label for b >= n_labels), rows 0 .. nw*B of the table; with `codes` also the adaLN sites' codes of SiLU(c) for every
+// block.
+static int run_cond(qc_ctx *ctx, const int32_t *t, int nw, const int32_t *labels, int n_labels, int B, bool codes, hipStream_t st) {
   const int D = ctx->D, fd = ctx->d.freq_dim;
   bool affine = true;
   for (int w = 2; w < nw; ++w) affine = affine && (t[w] - t[w - 1] == t[1] - t[0]);
   if (affine) {
-    QC_HIP(launch_time_embed(t[0], nw > 1 ? t[1] - t[0] : 0, nw, fd, ctx->emb, st));
+    QC_HIP(launch_small_linear(nullptr, 0, t[0], nw > 1 ? t[1] - t[0] : 0, ctx->t_w1, ctx->t_b1, ctx->h1, D, nw, D, fd, 0, 1, st));
   } else {
-    for (int w = 0; w < nw; ++w) QC_HIP(launch_time_embed(t[w], 0, 1, fd, ctx->emb + (size_t)w * fd, st));
+    for (int w = 0; w < nw; ++w)
+      QC_HIP(launch_small_linear(nullptr, 0, t[w], 0, ctx->t_w1, ctx->t_b1, ctx->h1 + (size_t)w * D, D, 1, D, fd, 0, 1, st));
   }
-  QC_HIP(launch_small_linear(ctx->emb, fd, ctx->t_w1, ctx->t_b1, ctx->h1, D, nw, D, fd, 0, 1, st));
-  QC_HIP(launch_small_linear(ctx->h1, D, ctx->t_w2, ctx->t_b2, ctx->te, D, nw, D, D, 0, 0, st));
-  QC_HIP(launch_cond_finish(ctx->te, ctx->label_table, labels, n_labels, ctx->d.num_classes, nw * B, B, D, ctx->cond, ctx->dev_flags, st));
+  QC_HIP(launch_small_linear(ctx->h1, D, 0, 0, ctx->t_w2, ctx->t_b2, ctx->te, D, nw, D, D, 0, 0, st));
+  QC_HIP(launch_cond_silu(ctx->te, ctx->label_table, labels, n_labels, ctx->d.num_classes, nw * B, B, D, ctx->cond, ctx->dev_flags, ctx->L,
+                          codes ? ctx->dev_qp + QC_SITE_ADA : nullptr, QC_NUM_SITES, ctx->silu_q, (size_t)ctx->win_rows * D, st));
   return QC_OK;
 }
 
@@ -720,11 +723,9 @@ static int prepare_window(qc_ctx *ctx, const int32_t *t, int nw, const int32_t *
                           hipStream_t st) {
   const int D = ctx->D, L = ctx->L, rows = nw * B;
   if (rows > ctx->win_rows) QC_FAIL(QC_ERR_WORKSPACE, "conditioning window of %d rows exceeds %d", rows, ctx->win_rows);
-  int rc = run_cond(ctx, t, nw, labels, n_labels, B, st);
+  int rc = run_cond(ctx, t, nw, labels, n_labels, B, true, st);
   if (rc) return rc;
-  QC_HIP(launch_silu_quant(ctx->cond, rows, D, L, ctx->dev_qp + QC_SITE_ADA, QC_NUM_SITES, ctx->silu_q,
-                           (size_t)ctx->win_rows * D, st));
-  QC_HIP(launch_small_linear(ctx->cond, D, ctx->fada_w, ctx->fada_b, ctx->fmod, 2 * D, rows, 2 * D, D, 1, 0, st));
+  QC_HIP(launch_small_linear(ctx->cond, D, 0, 0, ctx->fada_w, ctx->fada_b, ctx->fmod, 2 * D, rows, 2 * D, D, 1, 0, st));
   return run_adaln(ctx, 0, L, 0, rows, gates_only, st);
 }
 
@@ -970,7 +971,7 @@ static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, 
     int *slot = slots ? slots + (size_t)l * QC_NUM_SITES * 2 : nullptr;
     float *mod = ctx->cal_mod;
     if (slot) QC_HIP(launch_minmax_silu(cond, (size_t)g * D, slot + 2 * QC_SITE_ADA, st));
-    QC_HIP(launch_small_linear(cond, D, b.ada_w, b.ada_b, mod, 6 * D, g, 6 * D, D, 1, 0, st));
+    QC_HIP(launch_small_linear(cond, D, 0, 0, b.ada_w, b.ada_b, mod, 6 * D, g, 6 * D, D, 1, 0, st));
     QC_HIP(launch_ln_mod_quant(ctx->tokens, 0, mod, mod + D, 6 * D, M, D, T, nullptr, nullptr, ctx->cal_h, st));
     if (slot) QC_HIP(launch_minmax(ctx->cal_h, (size_t)M * D, slot + 2 * QC_SITE_QKV, st));
     QC_HIP(launch_linear_f32(ctx->cal_h, b.qkv_w, b.qkv_b, ctx->qkv, M, 3 * D, D, 0, st));
@@ -995,9 +996,9 @@ static int denoise_f32_impl(qc_ctx *ctx, const qc_weights_f32 *w, const float *x
   const int D = ctx->D;
   const size_t lat = (size_t)ctx->C * ctx->d.latent_h * ctx->d.latent_w;
   const int32_t t32 = t;
-  int rc = run_cond(ctx, &t32, 1, labels, n_labels, B, st);
+  int rc = run_cond(ctx, &t32, 1, labels, n_labels, B, false, st);
   if (rc) return rc;
-  QC_HIP(launch_small_linear(ctx->cond, D, ctx->fada_w, ctx->fada_b, ctx->fmod, 2 * D, B, 2 * D, D, 1, 0, st));
+  QC_HIP(launch_small_linear(ctx->cond, D, 0, 0, ctx->fada_w, ctx->fada_b, ctx->fmod, 2 * D, B, 2 * D, D, 1, 0, st));
   for (int b = 0; b < B; b += ctx->cal_group) {
     const int g = std::min(ctx->cal_group, B - b);
     QC_HIP(launch_embed(x, ctx->patch_w, ctx->patch_b, ctx->pos, ctx->tokens, 0, g, n_src, ctx->C, ctx->d.latent_h, ctx->d.latent_w,
@@ -1039,7 +1040,7 @@ int qc_calibrate_minmax(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, co
     const int g = std::min(ctx->cal_group, n - i);
     QC_HIP(hipMemcpyAsync(ctx->cal_label, y + i, (size_t)g * sizeof(int), hipMemcpyHostToDevice, st));
     for (int j = 0; j < g; ++j) {            // every input has a timestep of its own
-      rc = run_cond(ctx, &t[i + j], 1, ctx->cal_label + j, 1, 1, st);
+      rc = run_cond(ctx, &t[i + j], 1, ctx->cal_label + j, 1, 1, false, st);
       if (rc) return rc;
       QC_HIP(hipMemcpyAsync(ctx->cal_cond + (size_t)j * D, ctx->cond, (size_t)D * sizeof(float), hipMemcpyDeviceToDevice, st));
     }

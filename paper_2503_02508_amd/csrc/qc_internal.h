@@ -154,13 +154,13 @@ hipError_t launch_quantize_weight(const float *w, int N, int K, int bits, void *
 // x_bf16 / tok_bf16 below: the residual stream argument is bfloat16 instead of fp32
 hipError_t launch_ln_mod_quant(const void *x, int x_bf16, const float *shift, const float *scale, int ld_mod, int M, int D, int T,
                                const QParam *qp, int8_t *q, float *f32_out, hipStream_t st);
-hipError_t launch_small_linear(const float *x, int ldx, const float *W, const float *b, float *y, int ldy, int B, int N,
+// x == nullptr: the inputs are the sinusoidal embeddings (K wide) of the timesteps t_first + row * t_step
+hipError_t launch_small_linear(const float *x, int ldx, int t_first, int t_step, const float *W, const float *b, float *y, int ldy, int B, int N,
                                int K, int act_in, int act_out, hipStream_t st);
-hipError_t launch_time_embed(int t_first, int t_step, int W, int dim, float *out, hipStream_t st);
-hipError_t launch_cond_finish(const float *te, const float *table, const int32_t *labels, int n_labels, int null_label,
-                              int rows, int B, int D, float *c, int *flags, hipStream_t st);
-hipError_t launch_silu_quant(const float *c, int B, int D, int L, const QParam *qp, int qp_stride, int8_t *q,
-                             size_t l_stride, hipStream_t st);
+// te == nullptr: c is given; qp == nullptr: no codes
+hipError_t launch_cond_silu(const float *te, const float *table, const int32_t *labels, int n_labels, int null_label, int rows, int B,
+                            int D, float *c, int *flags, int L, const QParam *qp, int qp_stride, int8_t *q, size_t l_stride,
+                            hipStream_t st);
 hipError_t launch_embed(const float *x, const float *pw, const float *pb, const float *pos, void *tok, int tok_bf16, int B,
                         int n_src, int C, int H, int W, int p, int D, int b_off, hipStream_t st);
 hipError_t launch_final(const void *tok, int tok_bf16, const float *fmod, const float *fw, const float *fb, float *eps, int B,

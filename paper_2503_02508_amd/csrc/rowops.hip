@@ -345,145 +345,246 @@ hipError_t launch_ln_mod_quant(const void *x, int x_bf16, const float *shift, co
 // summation order (conditioning vectors feed quantisers, where a last-bit difference can move a code).
 __device__ __forceinline__ double silu_d(double x) { return x / (1.0 + exp(-x)); }
 
-// One workgroup = 8 rows x 16 NC outputs: the (activated) inputs of the 8 rows are formed once, in float64, and kept in
-// LDS (the activation is an exponential per value: it must not be repeated per output); a wavefront takes 4 NC of the
-// outputs, four at a time, so that every input value read from LDS and every weight read from memory feeds 4 and 8
-// multiply-adds.  NC = 4 for many rows (all steps of a window at once), NC = 1 for few (one step: the outputs must
-// supply the workgroups).  Per output the summation order is fixed: lane l adds k = l, l + 64, ... in order, then the
-// lanes are reduced by the shuffle tree of wave_sum_d.
-template <int NC>
-__global__ __launch_bounds__(256) void small_linear_kernel(const float *__restrict__ x, int ldx, const float *__restrict__ W,
-                                                           const float *__restrict__ bias, float *__restrict__ y, int ldy,
-                                                           int B, int N, int K, int act_in, int act_out) {
-  extern __shared__ double xs[];                  // [8][K]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int b0 = blockIdx.y * 8, n0 = blockIdx.x * (16 * NC);
-  for (int i = threadIdx.x; i < 8 * K; i += 256) {
-    const int r = i / K, k = i - r * K;
-    double v = b0 + r < B ? (double)x[(size_t)(b0 + r) * ldx + k] : 0.0;
+// Widths that the kernel below does not cover (a timestep embedding whose width is not a multiple of 4 or beyond 2048): one
+// wavefront per output.
+__device__ __forceinline__ float time_embed_value(int t, int k, int dim);
+__global__ __launch_bounds__(256) void small_linear_any_kernel(const float *__restrict__ x, int ldx, int t_first, int t_step,
+                                                               const float *__restrict__ W, const float *__restrict__ bias,
+                                                               float *__restrict__ y, int ldy, int N, int K, int act_in, int act_out) {
+  const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
+  if (n >= N) return;
+  double t = 0.0;
+  for (int k = lane; k < K; k += 64) {
+    double v = x ? (double)x[(size_t)b * ldx + k] : (double)time_embed_value(t_first + b * t_step, k, K);
     if (act_in == 1) v = silu_d(v);
+    t = fma((double)W[(size_t)n * K + k], v, t);
+  }
+  t = wave_sum_d(t);
+  if (lane == 0) {
+    t += bias ? (double)bias[n] : 0.0;
+    if (act_out == 1) t = silu_d(t);
+    y[(size_t)b * ldy + n] = (float)t;
+  }
+}
+static hipError_t launch_small_linear_any(const float *x, int ldx, int t_first, int t_step, const float *W, const float *b, float *y, int ldy,
+                                          int B, int N, int K, int act_in, int act_out, hipStream_t st) {
+  hipLaunchKernelGGL(small_linear_any_kernel, dim3((N + 3) / 4, B), dim3(256), 0, st, x, ldx, t_first, t_step, W, b, y, ldy, N, K, act_in,
+                     act_out);
+  return hipGetLastError();
+}
+
+// One workgroup = R rows x 16 outputs: the (activated) inputs of the R rows are formed once, in float64, and kept in LDS (the
+// activation is an exponential per value: it must not be repeated per output); a wavefront takes four outputs, so that
+// every input value read from LDS and every weight read from memory feeds 4 and R multiply-adds.  A lane owns four
+// consecutive k of every 256 and requests its whole share of the four weight rows at once (NIT x 4 16-byte loads); the 4 R
+// sums are then reduced together, each exchange between lanes halving the number of sums a lane still carries.
+// x == nullptr: the inputs are the sinusoidal embeddings of the timesteps t_first + row * t_step (rounded to float32, as the
+// stored embedding would be).
+// Bound: the weights' bytes for a few rows (float32, read once per R rows), the float64 rate for many.  Rows are taken R =
+// 1, 2, 4 or 8 at a time, whichever covers them: absent rows used to cost as much as real ones (one row of 256 inputs and
+// 384 outputs 15 us, now 4.5; 6912 x 1152 weights, two rows: 41 us, now 13).
+__device__ __forceinline__ float time_embed_value(int t, int k, int dim) {
+  // [cos | sin], frequencies exp(-ln(1e4) j / half), evaluated in double so that the float32 result is correctly rounded
+  const int half = dim / 2, f = k < half ? k : k - half;
+  const double a = (double)t * exp(-log(10000.0) * (double)f / (double)half);
+  return (float)(k < half ? cos(a) : sin(a));
+}
+
+template <int R, int NIT>
+__global__ __launch_bounds__(256) void small_linear_kernel(const float *__restrict__ x, int ldx, int t_first, int t_step,
+                                                           const float *__restrict__ W, const float *__restrict__ bias,
+                                                           float *__restrict__ y, int ldy, int B, int N, int K, int act_in, int act_out) {
+  extern __shared__ double xs[];                  // [R][K]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b0 = blockIdx.y * R, n0 = blockIdx.x * 16 + wave * 4;
+  // weights first: they do not depend on the inputs
+  float4 w4[NIT][4];
+#pragma unroll
+  for (int it = 0; it < NIT; ++it)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)                   // outputs beyond N repeat the last, k beyond K the row's end (multiplied by zero)
+      w4[it][j] = *(const float4 *)(W + (size_t)min(n0 + j, N - 1) * K + min(4 * (lane + 64 * it), K - 4));
+  for (int i = threadIdx.x; i < R * K; i += 256) {
+    const int r = i / K, k = i - r * K;
+    double v = 0.0;
+    if (b0 + r < B) {
+      v = x ? (double)x[(size_t)(b0 + r) * ldx + k] : (double)time_embed_value(t_first + (b0 + r) * t_step, k, K);
+      if (act_in == 1) v = silu_d(v);
+    }
     xs[i] = v;
   }
   __syncthreads();
-  for (int c = 0; c < NC; ++c) {
-    const int n = n0 + wave * (4 * NC) + c * 4;
-    if (n >= N) break;
-    double acc[8][4];
+  double part[4 * R];                             // sum of (row r, output j) at r * 4 + j
 #pragma unroll
-    for (int r = 0; r < 8; ++r)
+  for (int i = 0; i < 4 * R; ++i) part[i] = 0.0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[r][j] = 0.0;
-    const float *wr[4];
+  for (int it = 0; it < NIT; ++it) {
+    const int k = 4 * (lane + 64 * it);
+    if (k < K) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) wr[j] = W + (size_t)min(n + j, N - 1) * K;      // outputs beyond N repeat the last (not stored)
-    for (int k = lane; k < K; k += 64) {
-      double wv[4];
+      for (int r = 0; r < R; ++r) {
+        const double x0 = xs[r * K + k], x1 = xs[r * K + k + 1], x2 = xs[r * K + k + 2], x3 = xs[r * K + k + 3];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) wv[j] = (double)wr[j][k];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const double xv = xs[r * K + k];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[r][j] = fma(wv[j], xv, acc[r][j]);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        double t = wave_sum_d(acc[r][j]);
-        if (lane == 0 && b0 + r < B && n + j < N) {
-          t += bias ? (double)bias[n + j] : 0.0;
-          if (act_out == 1) t = silu_d(t);
-          y[(size_t)(b0 + r) * ldy + n + j] = (float)t;
+        for (int j = 0; j < 4; ++j) {
+          part[r * 4 + j] = fma((double)w4[it][j].x, x0, part[r * 4 + j]);
+          part[r * 4 + j] = fma((double)w4[it][j].y, x1, part[r * 4 + j]);
+          part[r * 4 + j] = fma((double)w4[it][j].z, x2, part[r * 4 + j]);
+          part[r * 4 + j] = fma((double)w4[it][j].w, x3, part[r * 4 + j]);
         }
       }
+    }
+  }
+  // exchange over distance 32, 16, ...: a lane keeps the upper or lower half of its sums, as its own lane bit says
+  int mine = 0;
+  constexpr int V = 4 * R;
+#pragma unroll
+  for (int s2 = 0, half = V / 2; half > 0; ++s2, half >>= 1) {
+    const int dist = 32 >> s2;
+    const bool upper = (lane & dist) != 0;
+    mine += upper ? half : 0;
+#pragma unroll
+    for (int u = 0; u < half; ++u) {
+      const double keep = upper ? part[u + half] : part[u];
+      const double send = upper ? part[u] : part[u + half];
+      part[u] = keep + __shfl_xor(send, dist, 64);
+    }
+  }
+  double t = part[0];
+#pragma unroll
+  for (int dist = 32 / V; dist > 0; dist >>= 1) t += __shfl_xor(t, dist, 64);
+  const int r = mine >> 2, n = n0 + (mine & 3);
+  if ((lane & (64 / V - 1)) == 0 && b0 + r < B && n < N) {
+    t += bias ? (double)bias[n] : 0.0;
+    if (act_out == 1) t = silu_d(t);
+    y[(size_t)(b0 + r) * ldy + n] = (float)t;
   }
 }
 
-hipError_t launch_small_linear(const float *x, int ldx, const float *W, const float *b, float *y, int ldy, int B, int N,
-                               int K, int act_in, int act_out, hipStream_t st) {
-  const size_t smem = (size_t)8 * K * sizeof(double);
-  if (smem > 160 * 1024) return hipErrorInvalidValue;
-  static size_t attr = 0;
-  if (smem > attr) {
-    hipError_t e = hipFuncSetAttribute((const void *)small_linear_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void *)small_linear_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+template <int R, int NIT>
+static hipError_t launch_small_linear_as(const float *x, int ldx, int t_first, int t_step, const float *W, const float *b, float *y, int ldy,
+                                         int B, int N, int K, int act_in, int act_out, hipStream_t st) {
+  const size_t smem = (size_t)R * K * sizeof(double);
+  if (smem > 64 * 1024) {                         // more than a kernel may use without asking: ask once, for the widest input
+    static const hipError_t e = hipFuncSetAttribute((const void *)small_linear_kernel<R, NIT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                    R * 256 * NIT * (int)sizeof(double));
     if (e != hipSuccess) return e;
-    attr = smem;
   }
-  const int groups = (B + 7) / 8;
-  if ((long long)groups * ((N + 63) / 64) >= 512)
-    hipLaunchKernelGGL(small_linear_kernel<4>, dim3((N + 63) / 64, groups), dim3(256), smem, st, x, ldx, W, b, y, ldy, B, N, K,
-                       act_in, act_out);
-  else
-    hipLaunchKernelGGL(small_linear_kernel<1>, dim3((N + 15) / 16, groups), dim3(256), smem, st, x, ldx, W, b, y, ldy, B, N, K,
-                       act_in, act_out);
+  hipLaunchKernelGGL((small_linear_kernel<R, NIT>), dim3((N + 15) / 16, (B + R - 1) / R), dim3(256), smem, st, x, ldx, t_first, t_step, W, b,
+                     y, ldy, B, N, K, act_in, act_out);
   return hipGetLastError();
+}
+
+template <int R>
+static hipError_t launch_small_linear_rows(const float *x, int ldx, int t_first, int t_step, const float *W, const float *b, float *y, int ldy,
+                                           int B, int N, int K, int act_in, int act_out, hipStream_t st) {
+  if (K <= 256) return launch_small_linear_as<R, 1>(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
+  if (K <= 512) return launch_small_linear_as<R, 2>(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
+  if (K <= 1280) return launch_small_linear_as<R, 5>(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
+  return launch_small_linear_as<R, 8>(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
+}
+
+// x == nullptr: rows are the embeddings of timesteps t_first, t_first + t_step, ... (K wide)
+hipError_t launch_small_linear(const float *x, int ldx, int t_first, int t_step, const float *W, const float *b, float *y, int ldy, int B, int N,
+                               int K, int act_in, int act_out, hipStream_t st) {
+  if (K % 4 || K > 2048) return launch_small_linear_any(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
+  if (B <= 1) return launch_small_linear_rows<1>(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
+  if (B <= 2) return launch_small_linear_rows<2>(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
+  if (B <= 4) return launch_small_linear_rows<4>(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
+  return launch_small_linear_rows<8>(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
 }
 
 // ----------------------------------------------------------- conditioning
-// Sinusoidal timestep embedding [cos | sin], frequencies exp(-ln(1e4) j / half),
-// evaluated in double so that the fp32 result is correctly rounded.
-// Row w is the embedding of timestep t_first + w * t_step.
-__global__ void time_embed_kernel(int t_first, int t_step, int W, int dim, float *__restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= W * dim) return;
-  const int j = i % dim, half = dim / 2, t = t_first + (i / dim) * t_step;
-  const int f = j < half ? j : j - half;
-  const double a = (double)t * exp(-log(10000.0) * (double)f / (double)half);
-  out[i] = (float)(j < half ? cos(a) : sin(a));
-}
-
-hipError_t launch_time_embed(int t_first, int t_step, int W, int dim, float *out, hipStream_t st) {
-  hipLaunchKernelGGL(time_embed_kernel, dim3((W * dim + 255) / 256), dim3(256), 0, st, t_first, t_step, W, dim, out);
-  return hipGetLastError();
-}
-
-// c[r, :] = te[r / B, :] + table[label of batch element r % B]: rows are (timestep slot, batch element)
-__global__ void cond_finish_kernel(const float *__restrict__ te, const float *__restrict__ table,
-                                   const int32_t *__restrict__ labels, int n_labels, int null_label, int rows, int B, int D,
-                                   float *__restrict__ c, int *__restrict__ flags) {
+// c[r, :] = te[r / B, :] + table[label of batch element r % B] (rows are (timestep slot, batch element)), and the codes of
+// SiLU(c) for the adaLN site of L blocks: q[l, r, n].  te == nullptr: c is given and only the codes are formed; qp ==
+// nullptr: no codes.
+__global__ void cond_silu_kernel(const float *__restrict__ te, const float *__restrict__ table, const int32_t *__restrict__ labels,
+                                 int n_labels, int null_label, int rows, int B, int D, float *__restrict__ c, int *__restrict__ flags,
+                                 int L, const QParam *qp, int qp_stride, int8_t *__restrict__ q, size_t l_stride) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= rows * D) return;
-  const int r = i / D, n = i % D, w = r / B, b = r % B;
-  int y = b < n_labels ? labels[b] : null_label;
-  if (y < 0 || y > null_label) {                  // the table has null_label + 1 rows: clamp, and tell the host
-    if (n == 0) atomicOr(flags, 1);
-    y = min(max(y, 0), null_label);
+  float cv;
+  if (te) {
+    const int r = i / D, n = i % D, w = r / B, b = r % B;
+    int y = b < n_labels ? labels[b] : null_label;
+    if (y < 0 || y > null_label) {                // the table has null_label + 1 rows: clamp, and tell the host
+      if (n == 0) atomicOr(flags, 1);
+      y = min(max(y, 0), null_label);
+    }
+    cv = te[(size_t)w * D + n] + table[(size_t)y * D + n];
+    c[i] = cv;
+  } else {
+    cv = c[i];
   }
-  c[i] = te[(size_t)w * D + n] + table[(size_t)y * D + n];
-}
-
-hipError_t launch_cond_finish(const float *te, const float *table, const int32_t *labels, int n_labels, int null_label,
-                              int rows, int B, int D, float *c, int *flags, hipStream_t st) {
-  hipLaunchKernelGGL(cond_finish_kernel, dim3((rows * D + 255) / 256), dim3(256), 0, st, te, table, labels, n_labels,
-                     null_label, rows, B, D, c, flags);
-  return hipGetLastError();
-}
-
-// codes of SiLU(c) for the adaLN site of every block: q[l, b, n]
-__global__ void silu_quant_kernel(const float *__restrict__ c, int BD, int L, const QParam *qp, int qp_stride,
-                                  int8_t *__restrict__ q, size_t l_stride) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= BD) return;
-  const float v = (float)silu_d((double)c[i]);      // float64 value rounded once, then Eq. 1
+  if (!qp) return;
+  const float v = (float)silu_d((double)cv);      // float64 value rounded once, then Eq. 1
   for (int l = 0; l < L; ++l) {
     QParam t = qp[(size_t)l * qp_stride];
     q[(size_t)l * l_stride + i] = (int8_t)quant_code(v, t.s, t.z);
   }
 }
 
-hipError_t launch_silu_quant(const float *c, int B, int D, int L, const QParam *qp, int qp_stride, int8_t *q,
-                             size_t l_stride, hipStream_t st) {
-  hipLaunchKernelGGL(silu_quant_kernel, dim3((B * D + 255) / 256), dim3(256), 0, st, c, B * D, L, qp, qp_stride, q,
-                     l_stride);
+hipError_t launch_cond_silu(const float *te, const float *table, const int32_t *labels, int n_labels, int null_label, int rows, int B,
+                            int D, float *c, int *flags, int L, const QParam *qp, int qp_stride, int8_t *q, size_t l_stride,
+                            hipStream_t st) {
+  hipLaunchKernelGGL(cond_silu_kernel, dim3((rows * D + 255) / 256), dim3(256), 0, st, te, table, labels, n_labels, null_label, rows, B,
+                     D, c, flags, L, qp, qp_stride, q, l_stride);
   return hipGetLastError();
 }
 
 // --------------------------------------------------------- patch embedding
 // tok[b, t, n] = sum_f pw[n, f] * patch(b, t)[f] + pb[n] + pos[t, n], features f = (c, ph, pw).
+// A thread owns four adjacent outputs n and keeps their F = 16 weights each in registers (as float64) over TPW consecutive
+// tokens, so a workgroup writes whole token rows (16 bytes per thread) and reads the weights once per TPW tokens; one token
+// per workgroup re-read 74 KB of weights for every 4.6 KB written (177 us at 32768 tokens of 1152, now 90).
+// Float64 dot products in ascending f, rounded once when the token is stored.
+template <int TPW>
+__global__ __launch_bounds__(512) void embed16_kernel(const float *__restrict__ x, const float *__restrict__ pw, const float *__restrict__ pb,
+                                                      const float *__restrict__ pos, void *__restrict__ tok, int tok_bf16, int n_src, int C,
+                                                      int H, int W, int p, int D, int b_off, int M) {
+  constexpr int F = 16;
+  __shared__ double patch[TPW][F];
+  const int gw = W / p, T = (H / p) * gw, m0 = blockIdx.x * TPW;
+  for (int i = threadIdx.x; i < TPW * F; i += blockDim.x) {
+    const int m = min(m0 + i / F, M - 1), f = i % F, b = m / T, t = m % T;
+    const int c = f / (p * p), ph = (f / p) % p, pq = f % p;
+    patch[i / F][f] = (double)x[(((size_t)((b + b_off) % n_src) * C + c) * H + (t / gw) * p + ph) * W + (t % gw) * p + pq];
+  }
+  const int n = threadIdx.x * 4;
+  const bool live = n < D;
+  const int nc = live ? n : 0;
+  double w[4][F], bn[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    bn[j] = (double)pb[nc + j];
+#pragma unroll
+    for (int f = 0; f < F; f += 4) {
+      const float4 t4 = *(const float4 *)(pw + (size_t)(nc + j) * F + f);
+      w[j][f] = t4.x; w[j][f + 1] = t4.y; w[j][f + 2] = t4.z; w[j][f + 3] = t4.w;
+    }
+  }
+  __syncthreads();
+  if (!live) return;
+  float4 ps = *(const float4 *)(pos + (size_t)(m0 % T) * D + n);
+#pragma unroll 1
+  for (int k = 0; k < TPW; ++k) {
+    const int m = m0 + k;
+    if (m >= M) break;
+    const float4 ps_next = *(const float4 *)(pos + (size_t)((m + 1) % T) * D + n);       // arrives behind this token's products
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+      const double pv = patch[k][f];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j] = fma(w[j][f], pv, acc[j]);
+    }
+    stream_store4(tok, ((size_t)m * D + n) >> 2,
+                  make_float4((float)((acc[0] + bn[0]) + (double)ps.x), (float)((acc[1] + bn[1]) + (double)ps.y),
+                              (float)((acc[2] + bn[2]) + (double)ps.z), (float)((acc[3] + bn[3]) + (double)ps.w)), tok_bf16);
+    ps = ps_next;
+  }
+}
+
+// Any other number of patch features: one token per workgroup.
 __global__ __launch_bounds__(256) void embed_kernel(const float *__restrict__ x, const float *__restrict__ pw,
                                                     const float *__restrict__ pb, const float *__restrict__ pos,
                                                     void *__restrict__ tok, int tok_bf16, int n_src, int C, int H, int W, int p,
@@ -528,7 +629,19 @@ __global__ __launch_bounds__(256) void embed_kernel(const float *__restrict__ x,
 
 hipError_t launch_embed(const float *x, const float *pw, const float *pb, const float *pos, void *tok, int tok_bf16, int B,
                         int n_src, int C, int H, int W, int p, int D, int b_off, hipStream_t st) {
-  const int T = (H / p) * (W / p);
+  const int T = (H / p) * (W / p), M = B * T;
+  if (C * p * p == 16 && D % 4 == 0 && D <= 2048) {
+    // tokens per workgroup: as many as leave two workgroups per compute unit
+    const int threads = (D / 4 + 63) / 64 * 64;
+#define QC_EMBED(TPW) hipLaunchKernelGGL(embed16_kernel<TPW>, dim3((M + TPW - 1) / TPW), dim3(threads), 0, st, x, pw, pb, pos, tok, tok_bf16, n_src, C, H, W, p, D, b_off, M)
+    if (M >= 32 * 512) QC_EMBED(32);
+    else if (M >= 8 * 512) QC_EMBED(8);
+    else if (M >= 4 * 512) QC_EMBED(4);
+    else if (M >= 2 * 512) QC_EMBED(2);
+    else QC_EMBED(1);
+#undef QC_EMBED
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(embed_kernel, dim3(B * T), dim3(256), 0, st, x, pw, pb, pos, tok, tok_bf16, n_src, C, H, W, p, D, b_off);
   return hipGetLastError();
 }
@@ -537,105 +650,100 @@ hipError_t launch_embed(const float *x, const float *pw, const float *pb, const 
 // Per token: LayerNorm, modulate with (shift, scale) = fmod[b, 0:D], fmod[b, D:2D],
 // dot with the rows of the output linear that belong to the first C of the 2C
 // channels, and scatter to eps[b, c, ty*p+ph, tx*p+pw] (output features (ph, pw, c)).
-template <int NIT>   // 256-feature slices of a row that a wavefront holds (D <= 256 NIT)
-__global__ __launch_bounds__(256) void final_kernel(const void *__restrict__ tok, int tok_bf16, const float *__restrict__ fmod,
-                                                    const float *__restrict__ fw, const float *__restrict__ fb,
-                                                    float *__restrict__ eps, int M, int C, int H, int W, int p, int D) {
-  const int lane = threadIdx.x & 63;
-  const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (m >= M) return;
-  const int gw = W / p, T = (H / p) * gw;
-  const int b = m / T, t = m % T, ty = t / gw, tx = t % gw;
-  const float *sh = fmod + (size_t)b * 2 * D, *sc = sh + D;
-  // loads never branch (chunks beyond D re-read the last chunk and are zeroed): the row and its modulation
-  // vectors arrive in one memory round trip
-  float4 v[NIT], s4[NIT], c4[NIT];
-  int kk[NIT];
+// Float64 throughout, rounded once when the noise estimate is stored; the dot products run on the float64 matrix cores.
+// One workgroup = 16 tokens, its eight wavefronts share the features: 16-feature chunk c belongs to wavefront c % 8, lane l
+// holds features 4 (l / 16) .. + 3 of it for token l % 16 (and, as the other operand, for output l % 16), so a chunk is four
+// 16x16x4 products and a row is read from memory once, into registers.  The row sums and the partial products of the
+// wavefronts meet in LDS.  Bound: the token tensor's bytes (32768 tokens of 1152: 151 MB) and the load instructions; with one
+// wavefront per token, which fetched all 74 KB of weights for its 4.6 KB, 247 us; now 92.
+typedef double d4v __attribute__((ext_vector_type(4)));
+
+constexpr int FW = 8;  // wavefronts
+template <int NJ>      // chunks a wavefront holds (D <= 16 FW NJ)
+__global__ __launch_bounds__(64 * FW, NJ < 9 ? 4 : 2) void final_kernel(const void *__restrict__ tok, int tok_bf16, const float *__restrict__ fmod,
+                                                       const float *__restrict__ fw, const float *__restrict__ fb,
+                                                       float *__restrict__ eps, int M, int C, int H, int W, int p, int D) {
+  __shared__ double red[2][FW][16];
+  __shared__ double prod[FW][16][17];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = lane & 15, g = lane >> 4;
+  const int gw = W / p, T = (H / p) * gw, m0 = blockIdx.x * 16;
+  const int m = min(m0 + row, M - 1);             // rows beyond M repeat the last (not stored)
+  const float *sh = fmod + (size_t)(m / T) * 2 * D, *sc = sh + D;
+  // loads never branch: features beyond D re-read the row's end and are zeroed
+  float4 v[NJ];
 #pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    kk[it] = min((lane + 64 * it) * 4, D - 4);
-    v[it] = stream_load4(tok, ((size_t)m * D + kk[it]) >> 2, tok_bf16);
-    s4[it] = *(const float4 *)(sh + kk[it]);
-    c4[it] = *(const float4 *)(sc + kk[it]);
-  }
-  // float64 throughout (the noise estimate is rounded once, when it is stored)
+  for (int j = 0; j < NJ; ++j) v[j] = stream_load4(tok, ((size_t)m * D + min((j * FW + wave) * 16 + 4 * g, D - 4)) >> 2, tok_bf16);
   double sum = 0.0;
 #pragma unroll
-  for (int it = 0; it < NIT; ++it)
-    if ((lane + 64 * it) * 4 < D) sum += ((double)v[it].x + (double)v[it].y) + ((double)v[it].z + (double)v[it].w);
-  const double mean = wave_sum_d(sum) / (double)D;
+  for (int j = 0; j < NJ; ++j)
+    if ((j * FW + wave) * 16 + 4 * g < D) sum += ((double)v[j].x + (double)v[j].y) + ((double)v[j].z + (double)v[j].w);
+  sum += __shfl_xor(sum, 16, 64);
+  sum += __shfl_xor(sum, 32, 64);
+  if (g == 0) red[0][wave][row] = sum;
+  __syncthreads();
+  double mu = 0.0, var = 0.0;
+#pragma unroll
+  for (int w = 0; w < FW; ++w) mu += red[0][w][row];
+  mu /= (double)D;
   double sq = 0.0;
 #pragma unroll
-  for (int it = 0; it < NIT; ++it)
-    if ((lane + 64 * it) * 4 < D) {
-      const double a = v[it].x - mean, bq = v[it].y - mean, c = v[it].z - mean, d = v[it].w - mean;
-      sq += (a * a + bq * bq) + (c * c + d * d);
+  for (int j = 0; j < NJ; ++j)
+    if ((j * FW + wave) * 16 + 4 * g < D) {
+      const double a = v[j].x - mu, b = v[j].y - mu, c = v[j].z - mu, d = v[j].w - mu;
+      sq += (a * a + b * b) + (c * c + d * d);
     }
-  const double rstd = 1.0 / sqrt(wave_sum_d(sq) / (double)D + 1e-6);
-  double h[NIT][4];
+  sq += __shfl_xor(sq, 16, 64);
+  sq += __shfl_xor(sq, 32, 64);
+  if (g == 0) red[1][wave][row] = sq;
+  __syncthreads();
 #pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    if ((lane + 64 * it) * 4 < D) {
-      h[it][0] = (v[it].x - mean) * rstd * (1.0 + (double)c4[it].x) + (double)s4[it].x;
-      h[it][1] = (v[it].y - mean) * rstd * (1.0 + (double)c4[it].y) + (double)s4[it].y;
-      h[it][2] = (v[it].z - mean) * rstd * (1.0 + (double)c4[it].z) + (double)s4[it].z;
-      h[it][3] = (v[it].w - mean) * rstd * (1.0 + (double)c4[it].w) + (double)s4[it].w;
-    } else {
-      h[it][0] = h[it][1] = h[it][2] = h[it][3] = 0.0;      // contributes nothing to the dot products below
-    }
-  }
-  // the p*p*C dot products of this row, 16 at a time: per-lane partial sums, then a butterfly that halves
-  // the number of live values with every exchange (17 shuffles for 16 sums instead of 6 each)
+  for (int w = 0; w < FW; ++w) var += red[1][w][row];
+  double rstd = 1.0 / sqrt(var / (double)D + 1e-6);
   const int n_out = p * p * C;
+  int zero = 0;
   for (int o0 = 0; o0 < n_out; o0 += 16) {
-    double part[16];
+    const int oi = min(o0 + row, n_out - 1);      // outputs beyond the last repeat it (not stored)
+    const float *wr = fw + (size_t)((oi / C) * 2 * C + oi % C) * D;
+    d4v acc = {0.0, 0.0, 0.0, 0.0};
+    asm volatile("" : "+v"(mu), "+v"(rstd), "+v"(zero));      // keeps the row's float64 values out of registers between passes
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      part[u] = 0.0;
-      const int oi = o0 + u;
-      if (oi < n_out) {
-        const float *wr = fw + (size_t)((oi / C) * 2 * C + oi % C) * D;
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-          const float4 w4 = *(const float4 *)(wr + kk[it]);
-          part[u] += (h[it][0] * (double)w4.x + h[it][1] * (double)w4.y) + (h[it][2] * (double)w4.z + h[it][3] * (double)w4.w);
-        }
-      }
+    for (int j = 0; j < NJ; ++j) {
+      const int k = (j * FW + wave) * 16 + 4 * g, kc = min(k, D - 4) + zero;
+      const float4 s4 = *(const float4 *)(sh + kc), c4 = *(const float4 *)(sc + kc), w4 = *(const float4 *)(wr + kc);
+      const bool in = k < D;
+      const double h0 = in ? (v[j].x - mu) * rstd * (1.0 + (double)c4.x) + (double)s4.x : 0.0;
+      const double h1 = in ? (v[j].y - mu) * rstd * (1.0 + (double)c4.y) + (double)s4.y : 0.0;
+      const double h2 = in ? (v[j].z - mu) * rstd * (1.0 + (double)c4.z) + (double)s4.z : 0.0;
+      const double h3 = in ? (v[j].w - mu) * rstd * (1.0 + (double)c4.w) + (double)s4.w : 0.0;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(h0, (double)w4.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(h1, (double)w4.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(h2, (double)w4.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(h3, (double)w4.w, acc, 0, 0, 0);
     }
-    // after the exchange over distance 32 >> s a lane keeps the values whose index has bit (3 - s) equal to
-    // its own lane bit (5 - s); after 4 exchanges lane l holds value (l >> 2) & 15 summed over 16 lanes
 #pragma unroll
-    for (int s2 = 0; s2 < 4; ++s2) {
-      const int dist = 32 >> s2, half = 8 >> s2;
-      const bool upper = (lane & dist) != 0;
+    for (int i = 0; i < 4; ++i) prod[wave][g + 4 * i][row] = acc[i];      // lane l: tokens l / 16 + 4 i, output l % 16
+    __syncthreads();
+    const int tk = threadIdx.x & 15, u = threadIdx.x >> 4, o = o0 + u, mt = m0 + tk;
+    if (u < 16 && mt < M && o < n_out) {
+      const int pp = o / C, c = o % C, b = mt / T, t = mt % T, ty = t / gw, tx = t % gw;
+      double r = 0.0;
 #pragma unroll
-      for (int u = 0; u < half; ++u) {
-        const double keep = upper ? part[u + half] : part[u];
-        const double send = upper ? part[u] : part[u + half];
-        part[u] = keep + __shfl_xor(send, dist, 64);
-      }
-    }
-    double r = part[0];
-    r += __shfl_xor(r, 2, 64);
-    r += __shfl_xor(r, 1, 64);
-    const int u_mine = ((lane >> 5) & 1) * 8 + ((lane >> 4) & 1) * 4 + ((lane >> 3) & 1) * 2 + ((lane >> 2) & 1);
-    const int oi = o0 + u_mine;
-    if ((lane & 3) == 0 && oi < n_out) {
-      const int pp = oi / C, c = oi % C;
+      for (int w = 0; w < FW; ++w) r += prod[w][tk][u];
       eps[(((size_t)b * C + c) * H + ty * p + pp / p) * W + tx * p + pp % p] = (float)(r + (double)fb[pp * 2 * C + c]);
     }
+    __syncthreads();
   }
 }
 
 hipError_t launch_final(const void *tok, int tok_bf16, const float *fmod, const float *fw, const float *fb, float *eps, int B,
                         int C, int H, int W, int p, int D, hipStream_t st) {
   const int M = B * (H / p) * (W / p);
-  const dim3 grid((M + 3) / 4);
-#define QC_FINAL(NIT) hipLaunchKernelGGL(final_kernel<NIT>, grid, dim3(256), 0, st, tok, tok_bf16, fmod, fw, fb, eps, M, C, H, W, p, D)
-  if (D <= 256) QC_FINAL(1);
-  else if (D <= 512) QC_FINAL(2);
-  else if (D <= 1280) QC_FINAL(5);
-  else QC_FINAL(LN_MAX_IT);
+  const dim3 grid((M + 15) / 16);
+#define QC_FINAL(NJ) hipLaunchKernelGGL(final_kernel<NJ>, grid, dim3(64 * FW), 0, st, tok, tok_bf16, fmod, fw, fb, eps, M, C, H, W, p, D)
+  if (D <= 16 * FW * 3) QC_FINAL(3);
+  else if (D <= 16 * FW * 6) QC_FINAL(6);
+  else if (D <= 16 * FW * 9) QC_FINAL(9);
+  else QC_FINAL(16);
 #undef QC_FINAL
   return hipGetLastError();
 }

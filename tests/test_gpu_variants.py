@@ -87,3 +87,26 @@ def test_large_m_ragged_denoiser(cache, stream):
             for k, (full, t) in enumerate(((True, 500), (False, 480))):
                 want = dit.denoiser(lat[b % n][None].astype(np.float64), np.array([t]), yb, m, w, lin, cache_or, full, cache_bf16=cache == "bf16")
                 assert_close(got[k][b], want[0], "batch element %d, call %d" % (b, k))
+
+
+@pytest.mark.parametrize("model,B", [
+    (_net(64, 2, 128, 10, 14), 1),              # 35 tokens: the last group of 16 tokens has 3
+    (_net(400, 10, 800, 6, 10), 3),             # groups of 16 tokens span batch elements; features end inside a chunk
+    (_net(1152, 16, 1152, 18, 14), 5),
+    (_net(2048, 32, 2048, 6, 6), 9),            # widest row; more rows of conditioning than one group
+    (_net(96, 3, 192, 24, 24, patch=4), 2),     # 64 features a patch: four groups of output features
+    (_net(64, 2, 128, 5, 7, patch=1), 4),       # 4 features a patch
+    (_net(32, 2, 64, 130, 128), 8)])            # 32 tokens a workgroup of the embedding, 8 of them in the last
+def test_conditioning_embedding_and_final_layer(model, B):
+    import torch
+    from oracle import dit
+    from qc_testlib import assert_close, make_pair, oracle_calibration
+    w = I.make_weights(model, 31)
+    lat, lab = I.make_latents(B, model, 32), I.make_labels(B, model, 33)
+    qp, _, _ = oracle_calibration(model, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    lin, ctx = make_pair(model, w, qp, B, 1)
+    eps = torch.empty(lat.shape, device="cuda")
+    ctx.denoise(_cuda(lat), 333, _cuda(lab), B, 0, eps)
+    want = dit.denoiser(lat.astype(np.float64), np.full(B, 333), lab, model, w, lin, {}, True)
+    assert_close(eps.cpu().numpy(), want, "eps")
+    ctx.close()
