@@ -1,0 +1,558 @@
+// Large-M int8 GEMM: the quantised linears of a block at several thousand rows.
+//
+// Two things bound it.  A compute unit can pull 64 bytes a clock through its vector memory path and LDS writes run at a
+// quarter of the read rate; and the chip is held at its power limit throughout (the four linears at M = 32768 run at 1.5 -
+// 2.0 GHz), so that bytes moved and registers toggled cost time even where they hide behind the matrix cores.  Hence:
+//   * v_mfma_i32_16x16x64_i8, not 32x32x32: half the accumulator bytes per operation; with random operands and nothing else to do
+//     the chip sustains 4.1 against 3.4 Pop/s.  Consecutive products share one operand (the row blocks are walked forth and
+//     back), which is worth another 2 %;
+//   * tile 128 (M) x 256 (N), four wavefronts side by side along N, each 128 x 64 (8 x 4 blocks of 16 x 16), two workgroups
+//     per compute unit so that one tile's prologue and epilogue run under the other's main loop;
+//   * weights never touch LDS: they are stored a second time in MFMA fragment order (fragment (n / 32, k / 32) = 64 lanes x
+//     16 bytes, lane l = row n % 32 = l % 32, bytes 16 (l / 32) .. of the 32 k values; packed nibbles: 8 bytes per lane) and
+//     each wavefront streams the fragments of its own 64 columns straight into registers, 128 k ahead;
+//   * activations go global -> registers -> LDS in slabs of 128 bytes of K, so that a load instruction covers 8 whole
+//     128-byte lines (slabs of 64 bytes, half lines, were 2 % slower over all), one slab in flight in registers, two slab
+//     buffers in LDS.  The eight 16-byte chunks of a slab row are XOR-swizzled with bits 1..3 of the row: 16 rows of one
+//     chunk then lie in 16 different slots of 256 bytes, free of bank conflicts;
+//   * one barrier per slab; every memory instruction is issued behind an MFMA (pinned with scheduling barriers);
+//   * memory is written 256 contiguous bytes at a time: a lane's accumulators are four adjacent columns of one row, so that 16
+//     adjacent lanes cover 16 rows, and stores straight from them write every sector in four pieces (QKV / fc2 at M = 32768: 258
+//     / 262 us; 4-byte stores of 16 adjacent columns with the operands swapped 193 / 222).  Each wavefront turns its blocks
+//     through its own part of LDS instead, without barriers;
+//   * per-column constants are fetched before the K loop (an epilogue that starts with two dependent round trips to memory
+//     costs a tile about 2 of its 12 us) and the accumulators start at minus the zero-point term.
+// Every global load of the loop is an ordinary register load issued through inline assembly (the compiler neither sees nor
+// counts them); register loads complete in the order they were issued, so each wait on the vector memory counter below
+// is the number of loads issued after the one it is for.
+// (A variant that sent the activations straight to LDS (global_load_lds_dwordx4) was measured first: those loads and
+// register loads share the counter but complete out of order with respect to each other, so counted waits gave wrong
+// fragments on some boxes, and draining the counter before every barrier cost 8 % against this version.)
+#include <algorithm>
+
+#include "gemm_i8_epilogue.h"
+
+namespace qc {
+
+// a wait, tied to the registers that become valid with it: their uses cannot be moved above it
+#define QC_WAIT_VM_FOR4(n, r0, r1, r2, r3) asm volatile("s_waitcnt vmcnt(" #n ")" : "+v"(r0), "+v"(r1), "+v"(r2), "+v"(r3)::"memory")
+// all LDS writes of this wavefront done, then the workgroup barrier
+#define QC_LDS_DONE_BARRIER asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
+#define QC_SB __builtin_amdgcn_sched_barrier(0)
+
+constexpr int BIG_BM = 128, BIG_BN = 256, BIG_BK = 128;
+constexpr int BIG_TM = 8, BIG_TN = 4;                                    // 16 x 16 blocks of a wavefront
+constexpr int BIG_CST = 4 * BIG_BN;                                      // floats: per-column constants of the epilogue
+constexpr int BIG_SMEM_LOOP = 2 * BIG_BM * BIG_BK;                       // two activation slabs
+constexpr int BIG_VR = 64 + 4;                                           // floats per staged V^T row (64 tokens)
+constexpr int BIG_SMEM_QKV = 4 * 64 * BIG_VR * 4;                        // 64 features of each wavefront
+constexpr int BIG_SROW = BIG_BN + 16;                                    // bytes per staged row of codes
+constexpr int BIG_SMEM_RESID = 4 * 32 * (64 + 4) * 4;                    // 32 rows of each wavefront
+constexpr int BIG_FIX_CAP = 1024;                                        // groups of four fc1 outputs decided again in float64, per tile
+constexpr int BIG_SMEM_GELU = BIG_BM * BIG_SROW + 16 + BIG_FIX_CAP * 32;
+
+typedef v4i BigAcc[BIG_TM][BIG_TN];
+
+// Epilogues.  acc[i][j] is the 16 x 16 block of rows m0 + 16 i .. and columns n0 + wn0 + 16 j ..; the weights are the first
+// MFMA operand, so a lane holds row lane % 16 and the columns 4 (lane / 16) + e of a block.  cst: per-column constants in LDS,
+// BIG_BN each of w_scale, bias and, for the residual, the gates of the first and of the next batch element.  RAG: the tile may
+// end beyond the last row and may span two batch elements (which have at least BIG_BM rows each); otherwise it is whole and
+// inside one.
+
+// dequantised values of a lane's four columns
+struct BigCols {
+  double sc[4], bs[4];
+  __device__ __forceinline__ BigCols(const float *cst, int nl, float a_s) {
+    const v4f s = *(const v4f *)(cst + nl), b = *(const v4f *)(cst + BIG_BN + nl);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sc[e] = (double)a_s * (double)s[e];
+      bs[e] = (double)b[e];
+    }
+  }
+  __device__ __forceinline__ v4f value(const v4i &a) const {
+    v4f v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = dequant_f32(sc[e], a[e], bs[e]);
+    return v;
+  }
+};
+
+// 32 rows (row blocks ip, ip + 1) of a wavefront's 64 columns to its part of LDS, dequantised, rows of BIG_SR floats; afterwards
+// lane l reads columns 4 (l % 16) .. + 3 of the rows l / 16, l / 16 + 4, ...
+constexpr int BIG_SR = 64 + 4;
+__device__ __forceinline__ void big_stage_rows(const BigAcc &acc, float *stage, const float *cst, int wn0, float a_s, int ip) {
+  const int lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
+  int nl = wn0 + g * 4;
+  asm volatile("" : "+v"(nl));                                // the constants are read again by the next pass, not kept
+#pragma unroll
+  for (int j = 0; j < BIG_TN; ++j) {
+    const BigCols c(cst, nl + j * 16, a_s);
+#pragma unroll
+    for (int ii = 0; ii < 2; ++ii) {
+      *(v4f *)(stage + (ii * 16 + row) * BIG_SR + j * 16 + g * 4) = c.value(acc[ip + ii][j]);
+      QC_SB;                                                  // few dequantised values live at a time
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // (LDS operations of a wavefront are in order)
+}
+
+__device__ __forceinline__ void big_gelu(const GemmArgs &p, BigAcc &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+  const int tid = threadIdx.x, lane = tid & 63, wn0 = (tid >> 6) * 64, row = lane & 15, g = lane >> 4;
+  unsigned char *stage = smem;                         // [BIG_BM][BIG_SROW] codes
+  // Elements whose fast evaluation lands too close to a rounding boundary of Eq. 1 to be trusted are queued here and
+  // decided again in float64 (gelu_code_exact): the codes are then those of exact arithmetic on the accumulators.
+  int *fix_cnt = (int *)(stage + BIG_BM * BIG_SROW);
+  int *fix_ent = fix_cnt + 4;                          // [BIG_FIX_CAP][8]: a lane's four accumulators, row and first column
+  if (tid == 0) *fix_cnt = 0;
+  __syncthreads();
+  const QParam oq = *p.o_qp;
+  const GeluQuant gq(oq);
+#pragma unroll
+  for (int j = 0; j < BIG_TN; ++j) {
+    const int nl = wn0 + j * 16 + g * 4;
+    v4f sc = *(const v4f *)(cst + nl);
+    const v4f bs = *(const v4f *)(cst + BIG_BN + nl);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sc[e] *= a_s;
+#pragma unroll
+    for (int i = 0; i < BIG_TM; i += 2) {
+      float clear[2][4];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) *(unsigned *)(stage + ((i + u) * 16 + row) * BIG_SROW + nl) = gq.codes(acc[i + u][j], sc, bs, clear[u]);
+      // one comparison and one branch per eight outputs; the branch is short (this code is unrolled 16 times: with a queue entry
+      // per output it outgrew the instruction cache)
+      if (gq.doubt(clear[0]) || gq.doubt(clear[1])) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          if (gq.doubt(clear[u])) {
+            const int slot = atomicAdd(fix_cnt, 1);
+            if (slot < BIG_FIX_CAP) {
+              *(v4i *)(fix_ent + slot * 8) = acc[i + u][j];
+              fix_ent[slot * 8 + 4] = ((i + u) * 16 + row) * BIG_SROW + nl;
+            }
+          }
+      }
+    }
+  }
+  __syncthreads();
+  const int nfix = min(*fix_cnt, BIG_FIX_CAP) * 4;
+  for (int f = tid; f < nfix; f += 256) {
+    const int pos = fix_ent[(f >> 2) * 8 + 4] + (f & 3), nl = pos % BIG_SROW;
+    if (n0 + nl < p.N) stage[pos] = (unsigned char)gelu_code_exact(fix_ent[(f >> 2) * 8 + (f & 3)], a_s, cst[nl], cst[BIG_BN + nl], oq.s, oq.z);
+  }
+  if (nfix) __syncthreads();
+  // coalesced write-out: 16 lanes cover 256 bytes of a row; streaming stores (the tensor is far larger than the L2 and would
+  // only evict the operands)
+  const int cc = (tid & 15) * 16;
+  if (n0 + cc >= p.N) return;                          // N is a multiple of 32
+#pragma unroll
+  for (int q = 0; q < BIG_BM / 16; ++q) {
+    const int r = (tid >> 4) + q * 16;
+    if (m0 + r < p.M) __builtin_nontemporal_store(*(const v4i *)(stage + r * BIG_SROW + cc), (v4i *)(p.q_out + (size_t)(m0 + r) * p.ldq + n0 + cc));
+  }
+}
+
+template <bool RAG>
+__device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
+  if (n0 + wn0 >= p.N) return;
+  const int T = p.rows_per_batch, D = p.N / 3;
+  const int part = (n0 + wn0) / D, nn0 = n0 + wn0 - part * D;      // D is a multiple of 128: a wavefront's columns lie inside one of Q, K, V
+  const int b = m0 / T, tb = m0 - b * T;                      // batch element and token of the tile's first row
+  const int rows = RAG ? min(BIG_BM, p.M - m0) : BIG_BM;      // rows of the tile that exist
+  const int bnd = RAG ? min(rows, T - tb) : BIG_BM;           // rows of the first batch element (the others: of the next)
+  const float inv_hd = 1.0f / (float)p.hd;
+  const auto head_of = [&](int nn) { return (int)(((float)nn + 0.5f) * inv_hd); };      // nn / hd, exactly (nn < 2^16)
+  float *stage = (float *)smem + wave * (64 * BIG_VR);
+  if (part < 2) {
+    // a lane's four columns lie in one head (heads start at multiples of hd, a multiple of 4)
+    const auto buf = __builtin_amdgcn_make_buffer_rsrc((part == 0 ? p.q32 : p.k32) + (size_t)b * T * D, 0, -1, 0x00027000);
+    const int col = row * 4, nn = nn0 + col, h = head_of(nn), e = nn - h * p.hd;
+    const int off = ((h * T + tb + g) * p.hd + e) * 4;
+#pragma unroll
+    for (int ip = 0; ip < BIG_TM; ip += 2) {
+      big_stage_rows(acc, stage, cst, wn0, a_s, ip);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const v4u v = *(const v4u *)(stage + (q * 4 + g) * BIG_SR + col);
+        const int m = ip * 16 + q * 4;
+        if (!RAG) {
+          __builtin_amdgcn_raw_buffer_store_b128(v, buf, off, m * p.hd * 4, 2);
+        } else {
+          // row beyond the first batch element: its token 0 lies (heads - 1) * T tokens further than the next row would
+          const int o = off + (m + (m + g >= bnd ? (p.heads - 1) * T : 0)) * p.hd * 4;
+          if (m + g < rows) __builtin_amdgcn_raw_buffer_store_b128(v, buf, o, 0, 2);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    return;
+  }
+  // V^T: 64 tokens of the wavefront's 64 features at a time
+  const bool edge = RAG && (bnd < BIG_BM || (tb & 31) != 0);
+#pragma unroll
+  for (int rh = 0; rh < 2; ++rh) {
+    int nl = wn0 + g * 4;
+    asm volatile("" : "+v"(nl));                              // the constants are read again in the second pass, not kept
+#pragma unroll
+    for (int j = 0; j < BIG_TN; ++j) {
+      const BigCols c(cst, nl + j * 16, a_s);
+#pragma unroll
+      for (int ii = 0; ii < 4; ++ii) {
+        const int ml = ii * 16 + row, pos = edge ? ml : vt_pos(ml);
+        const v4f v = c.value(acc[rh * 4 + ii][j]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) stage[(j * 16 + g * 4 + e) * BIG_VR + pos] = v[e];
+        QC_SB;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // lane -> four consecutive token positions ch of the features fc, fc + 4, ...
+    const int fc = lane >> 4, ch = (lane & 15) * 4, r0 = rh * 64 + ch;
+    if (RAG && edge) {
+      // the tile's rows do not start at a group of 32 keys: natural order in LDS, permuted on the way out.  Units of
+      // four tokens stay whole when T is a multiple of 4 (then so is every tile's first token)
+#pragma unroll 4
+      for (int q = 0; q < 16; ++q) {
+        const int f = fc + q * 4, nn = nn0 + f, h = head_of(nn), e = nn - h * p.hd;
+        const float *src = stage + f * BIG_VR + ch;
+        if ((T & 3) == 0) {
+          const bool second = r0 >= bnd;
+          const int t0 = tb + r0 - (second ? T : 0), bb = b + (second ? 1 : 0);
+          if (r0 < rows) *(v4f *)(p.vt32 + ((size_t)(bb * p.heads + h) * p.DP + e) * p.Tp + vt_pos(t0)) = *(const v4f *)src;
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int ml = r0 + u, bb = b + (ml >= bnd ? 1 : 0), t = tb + ml - (ml >= bnd ? T : 0);
+            if (ml < rows) p.vt32[((size_t)(bb * p.heads + h) * p.DP + e) * p.Tp + vt_pos(t)] = src[u];
+          }
+        }
+      }
+    } else {
+      const auto buf = __builtin_amdgcn_make_buffer_rsrc(p.vt32 + (size_t)b * p.heads * p.DP * p.Tp, 0, -1, 0x00027000);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int f = fc + q * 4, nn = nn0 + f, h = head_of(nn), e = nn - h * p.hd;
+        __builtin_amdgcn_raw_buffer_store_b128(*(const v4u *)(stage + f * BIG_VR + ch), buf, ((h * p.DP + e) * p.Tp + tb + ch) * 4, rh * 64 * 4, 2);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+}
+
+template <bool RBF, bool RAG>
+__device__ __forceinline__ void big_resid(const GemmArgs &p, BigAcc &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
+  const int left = p.N - n0 - wn0;                            // columns from this wavefront's first to the matrix's end (a multiple of 32)
+  if (left <= 0) return;
+  const int b0 = m0 / p.rows_per_batch;
+  const int rows = RAG ? min(BIG_BM, p.M - m0) : BIG_BM;      // rows of the tile that exist
+  const int bnd = RAG ? min(rows, (b0 + 1) * p.rows_per_batch - m0) : BIG_BM;      // rows of the first batch element
+  // element sizes: float32, or (RBF) either tensor may be bfloat16
+  const int xb = RBF ? p.x_bf16 : 0, cb = RBF ? p.cache_bf16 : 0;
+  const size_t tile0 = (size_t)m0 * p.N + n0 + wn0;           // first element of this wavefront's columns
+  const auto xbuf = __builtin_amdgcn_make_buffer_rsrc((char *)p.x + tile0 * (xb ? 2 : 4), 0, -1, 0x00027000);
+  const auto cbuf = __builtin_amdgcn_make_buffer_rsrc((char *)p.cache_out + tile0 * (cb ? 2 : 4), 0, -1, 0x00027000);
+  float *stage = (float *)smem + wave * (32 * BIG_SR);
+  const int col = row * 4, lc = min(col, left - 4);
+  const auto pack = [](const v4f &v) {
+    return (v2u){(unsigned)bf16_bits(v[0]) | ((unsigned)bf16_bits(v[1]) << 16), (unsigned)bf16_bits(v[2]) | ((unsigned)bf16_bits(v[3]) << 16)};
+  };
+  // buffer instructions (tile base, scalar row offset, one lane offset) cost no address arithmetic
+  const auto lane_off = [&](int m) { return (RAG ? min(m + g, rows - 1) : g) * p.N + lc; };      // m: first row of a group of four
+  const auto row_off = [&](int m) { return RAG ? 0 : m * p.N; };
+  // x is requested XD passes ahead of its use
+  constexpr int XD = 2;
+  v4u xv[XD][8];
+  const auto load_x = [&](int ip) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int m = ip * 16 + q * 4;
+      v4u &x = xv[(ip >> 1) % XD][q];
+      if (RBF && xb) {
+        const auto t = __builtin_amdgcn_raw_buffer_load_b64(xbuf, lane_off(m) * 2, row_off(m) * 2, 0);
+        x = (v4u){t[0], t[1], 0u, 0u};                        // converted when it is used
+      } else {
+        x = __builtin_amdgcn_raw_buffer_load_b128(xbuf, lane_off(m) * 4, row_off(m) * 4, 0);
+      }
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < XD; ++k) load_x(2 * k);
+#pragma unroll
+  for (int ip = 0; ip < BIG_TM; ip += 2) {
+    QC_SB;
+    big_stage_rows(acc, stage, cst, wn0, a_s, ip);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int m = ip * 16 + q * 4;
+      const v4f v = *(const v4f *)(stage + (q * 4 + g) * BIG_SR + col);
+      const v4f gate = *(const v4f *)(cst + (RAG && m + g >= bnd ? 3 : 2) * BIG_BN + wn0 + col);
+      const v4u xr = xv[(ip >> 1) % XD][q];
+      const v4f xo = __builtin_bit_cast(v4f, RBF && xb ? (v4u){xr[0] << 16, xr[0] & 0xFFFF0000u, xr[1] << 16, xr[1] & 0xFFFF0000u} : xr);
+      v4f xn;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xn[e] = fmaf(gate[e], v[e], xo[e]);
+      if (col < left && (!RAG || m + g < rows)) {
+        // the cached tensor is written once and read a step later: a streaming store keeps it out of the L2's way
+        const int lo = lane_off(m), so = row_off(m);
+        if (RBF && cb) __builtin_amdgcn_raw_buffer_store_b64(pack(v), cbuf, lo * 2, so * 2, 2);
+        else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), cbuf, lo * 4, so * 4, 2);
+        if (RBF && xb) __builtin_amdgcn_raw_buffer_store_b64(pack(xn), xbuf, lo * 2, so * 2, 0);
+        else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, xn), xbuf, lo * 4, so * 4, 0);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    QC_SB;
+    if (ip + 2 * XD < BIG_TM) load_x(ip + 2 * XD);
+  }
+}
+
+template <int EPI, int TAG, bool W4, bool RBF, bool RAG>
+__global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
+  constexpr int BM = BIG_BM, BN = BIG_BN, BK = BIG_BK, TM = BIG_TM, TN = BIG_TN;
+  constexpr int PA = 4;                           // 16-byte activation chunks per thread per slab
+  constexpr int SLAB = BM * BK;
+  extern __shared__ __align__(16) unsigned char smem_base[];
+  float *cst = (float *)smem_base;
+  unsigned char *smem = smem_base + BIG_CST * 4;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Tile order: XCD x (= workgroup id mod 8) owns a contiguous range of the order "GM tile rows at a time, column by
+  // column", GM chosen by the launcher so that the column tiles of a group of rows are resident on the XCD at the same
+  // time, walk K in step and share the group's activation slabs through the XCD's L2.
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
+  const int per_xcd = (gridDim.x + 7) >> 3;
+  const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (t >= tiles_m * tiles_n) return;
+  const int GM = p.group_m;
+  const int grp = t / (GM * tiles_n), gm0 = grp * GM, gsz = min(GM, tiles_m - gm0), rr = t - grp * GM * tiles_n;
+  const int tn = rr / gsz, tm = gm0 + rr % gsz;
+  const int m0 = __builtin_amdgcn_readfirstlane(tm * BM), n0 = __builtin_amdgcn_readfirstlane(tn * BN);   // the divisions above run on the vector ALU
+  const int wn0 = wave * (TN * 16);
+  float a_s = p.a_scale;
+  int a_z = p.a_zp;
+  if (p.a_qp) {
+    a_s = p.a_qp[0].s;
+    a_z = p.a_qp[0].z;
+  }
+
+  // epilogue constants of column n0 + tid, in flight while the prologue's operand loads are issued
+  float c_sc = 0.0f, c_bs = 0.0f, c_g0 = 0.0f, c_g1 = 0.0f;
+  if (n0 + tid < p.N) {
+    const int n = n0 + tid;
+    c_sc = p.w_scale[n];
+    if (p.bias) c_bs = p.bias[n];
+    if (EPI == EPI_RESID) {
+      const int b = m0 / p.rows_per_batch;
+      c_g0 = p.gate[(size_t)b * p.ld_gate + n];
+      if (RAG && (b + 1) * p.rows_per_batch < min(m0 + BM, p.M)) c_g1 = p.gate[(size_t)(b + 1) * p.ld_gate + n];
+    }
+  }
+
+  // activations: load i of thread tid covers row 32 i + tid / 8, 16-byte chunk tid % 8 of a slab and is written to
+  // LDS at the swizzled position of that chunk.  Rows beyond M re-read row M - 1.
+  unsigned aoff[PA];
+  const int arow = tid >> 3, ac = tid & 7;
+#pragma unroll
+  for (int i = 0; i < PA; ++i) aoff[i] = (unsigned)(min(m0 + 32 * i + arow, p.M - 1) - m0) * (unsigned)p.lda + ac * 16;
+  const unsigned lpos = arow * BK + ((ac ^ ((arow >> 1) & 7)) * 16);          // + 32 i rows: the same swizzle
+  const int8_t *abase = p.A + (size_t)m0 * p.lda;
+  const int nk = p.K / BK, ng = p.K / 64;
+  v4i ra[PA];
+  auto load_a = [&](v4i &r, int kt, int i) {      // slabs past the end re-read the last one (never used)
+    asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(r) : "v"(aoff[i]), "s"(abase + min(kt, nk - 1) * BK) : "memory");
+  };
+  auto write_a = [&](const v4i &r, int buf, int i) { *(v4i *)(smem + buf * SLAB + lpos + i * 32 * BK) = r; };
+
+  // weight fragments of this wavefront: column block j (16 columns) is half j % 2 of the stored n-block (n0 + wn0) / 32 + j / 2
+  // (blocks past N re-read the last one), group g (64 k) the two stored fragments 2 g and 2 g + 1 of it: lane l takes chunk l / 16 of
+  // the 64 k, row l % 16 of the half
+  constexpr int FRAG = W4 ? 512 : 1024;           // bytes per stored fragment
+  typedef typename std::conditional<W4, v2i, v4i>::type wfrag_t;
+  const int nblocks = p.N / 32;
+  const int8_t *sb[TN / 2];
+#pragma unroll
+  for (int j = 0; j < TN / 2; ++j) sb[j] = (const int8_t *)p.Wt + (size_t)min((n0 + wn0) / 32 + j, nblocks - 1) * (2 * ng) * FRAG;
+  const unsigned woff = (lane >> 5) * FRAG + ((lane >> 4) & 1) * (FRAG / 2) + (lane & 15) * (FRAG / 64);
+  wfrag_t bq[2][TN];
+  auto load_w = [&](int g, int kg, int j) {       // groups past the end re-read the last one (never used)
+    const int8_t *src = sb[j >> 1] + (size_t)min(kg, ng - 1) * (2 * FRAG);
+    if constexpr (W4) {
+      if (j & 1) asm volatile("global_load_dwordx2 %0, %1, %2 offset:128" : "=v"(bq[g][j]) : "v"(woff), "s"(src) : "memory");
+      else asm volatile("global_load_dwordx2 %0, %1, %2" : "=v"(bq[g][j]) : "v"(woff), "s"(src) : "memory");
+    } else {
+      if (j & 1) asm volatile("global_load_dwordx4 %0, %1, %2 offset:256" : "=v"(bq[g][j]) : "v"(woff), "s"(src) : "memory");
+      else asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(bq[g][j]) : "v"(woff), "s"(src) : "memory");
+    }
+  };
+
+  // the accumulators start at minus the zero-point term a_z * wsum[n] of their column, so the epilogue finds acc - a_z *
+  // wsum[n] ready; the loads complete under the prologue's wait for the first slabs
+  BigAcc acc;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const v4i ws = *(const v4i *)(p.wsum + min(n0 + wn0 + j * 16 + (lane >> 4) * 4, p.N - 4));
+    v4i c0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c0[e] = -(a_z * ws[e]);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc[i][j] = c0;
+  }
+
+  unsigned fbase[2];                              // LDS position of this lane's chunk of group g in row block 0
+#pragma unroll
+  for (int g = 0; g < 2; ++g) fbase[g] = (lane & 15) * BK + (((g * 4 + (lane >> 4)) ^ ((lane >> 1) & 7)) * 16);
+  v4i fa[2][4];
+  auto read_frag = [&](int f, int buf, int g, int half, int i) {
+    fa[f][i] = *(const v4i *)(smem + buf * SLAB + fbase[g] + (half * 4 + i) * 16 * BK);
+  };
+
+  // prologue: slab 0 -> LDS (through registers of the fragments), slab 1 -> registers, the weights of slab 0
+#pragma unroll
+  for (int i = 0; i < PA; ++i) load_a(fa[1][i], 0, i);
+#pragma unroll
+  for (int i = 0; i < PA; ++i) load_a(ra[i], 1, i);
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) load_w(g, g, j);
+  QC_SB;
+  QC_WAIT_VM_FOR4(12, fa[1][0], fa[1][1], fa[1][2], fa[1][3]);
+#pragma unroll
+  for (int i = 0; i < PA; ++i) write_a(fa[1][i], 0, i);
+  cst[tid] = c_sc;
+  cst[BN + tid] = c_bs;
+  if (EPI == EPI_RESID) {
+    cst[2 * BN + tid] = c_g0;
+    if (RAG) cst[3 * BN + tid] = c_g1;
+  }
+  QC_LDS_DONE_BARRIER;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) read_frag(0, 0, 0, 0, i);
+  QC_SB;
+
+  // Slab kt = two groups of 64 k, each in two steps of 64 rows (four row blocks, 16 products): step s = 2 g + half.  On entry:
+  // slab kt is in LDS buffer kt % 2 and published; fa[0] holds (or awaits) the fragments of step 0; the weights of both groups and
+  // activation slab kt + 1 are requested.
+  //   step 0: activation slab kt + 1 registers -> LDS, slab kt + 2 requested (4 loads)
+  //   steps 1 and 3: the weights of the group are free column block by column block, the next slab's are requested (4 loads each)
+  //   every step reads the fragments of the next one; the barrier before step 3 publishes slab kt + 1, whose buffer was last
+  //   read in step 2 of slab kt - 1, before that slab's barrier.
+  // Loads issued after the one a wait is for:
+  //   step 0, for the weights of group 0 (step 1 of slab kt - 1) and, older, the activations: the weights of group 1    = 4
+  //   step 2, for the weights of group 1 (step 3 of slab kt - 1): the activations and weights of steps 0 and 1          = 8
+  v4i wf[TN];
+  auto step = [&](int kt, int s, int buf) {
+    const int g = s >> 1, half = s & 1, f = s & 1;
+    if constexpr (W4) {
+      if (half == 0) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) wf[j] = unpack_w4(bq[g][j]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      v4i w;
+      if constexpr (W4) w = wf[j];
+      else w = bq[g][j];
+#pragma unroll
+      for (int ii = 0; ii < 4; ++ii) {
+        const int i = (j & 1) ? 3 - ii : ii, k = j * 4 + ii;
+        QC_SB;
+        acc[half * 4 + i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, fa[f][i], acc[half * 4 + i][j], 0, 0, 0);
+        if (k < 4) read_frag(f ^ 1, s == 3 ? buf ^ 1 : buf, ((s + 1) >> 1) & 1, (s + 1) & 1, k);
+        if (s == 0 && k >= 4 && k < 8) write_a(ra[k - 4], buf ^ 1, k - 4);
+        if (s == 0 && k >= 12) load_a(ra[k - 12], kt + 2, k - 12);
+      }
+      if (half == 1) load_w(g, 2 * kt + g + 2, j);
+    }
+    QC_SB;
+  };
+  auto slab = [&](int kt, int buf) {
+    QC_WAIT_VM_FOR4(4, ra[0], ra[1], ra[2], ra[3]);
+    QC_WAIT_VM_FOR4(4, bq[0][0], bq[0][1], bq[0][2], bq[0][3]);
+    step(kt, 0, buf);
+    step(kt, 1, buf);
+    QC_WAIT_VM_FOR4(8, bq[1][0], bq[1][1], bq[1][2], bq[1][3]);
+    step(kt, 2, buf);
+    QC_LDS_DONE_BARRIER;
+    step(kt, 3, buf);
+  };
+  // K is a multiple of 128 (checked by the launcher)
+  int kt = 0;
+  for (; kt + 2 <= nk; kt += 2) {
+    slab(kt, 0);
+    slab(kt + 1, 1);
+  }
+  if (kt < nk) slab(kt, 0);
+  // the loads that ran past the end (clamped addresses) must have landed before registers are reused (the waits name their
+  // registers: a load whose result nobody uses would share its register with something live), and every wavefront must be past
+  // its last fragment read before the epilogue reuses LDS
+  QC_WAIT_VM_FOR4(0, ra[0], ra[1], ra[2], ra[3]);
+#pragma unroll
+  for (int g = 0; g < 2; ++g) QC_WAIT_VM_FOR4(0, bq[g][0], bq[g][1], bq[g][2], bq[g][3]);
+  QC_SB;
+  __syncthreads();
+  if constexpr (EPI == EPI_GELU_Q) big_gelu(p, acc, smem, cst, m0, n0, a_s);
+  else if constexpr (EPI == EPI_QKV) big_qkv<RAG>(p, acc, smem, cst, m0, n0, a_s);
+  else big_resid<RBF, RAG>(p, acc, smem, cst, m0, n0, a_s);
+}
+
+template <int EPI, int TAG, bool W4, bool RBF, bool RAG = false>
+static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
+  // launches whose tiles are not all whole and inside one batch element take the variant that handles the others
+  if constexpr (!RAG && EPI != EPI_GELU_Q) {
+    if (a.M % BIG_BM || a.rows_per_batch % BIG_BM) return launch_big_as<EPI, TAG, W4, RBF, true>(a, st);
+  }
+  constexpr int smem_epi = EPI == EPI_GELU_Q ? BIG_SMEM_GELU : (EPI == EPI_QKV ? BIG_SMEM_QKV : BIG_SMEM_RESID);
+  constexpr int smem = BIG_CST * 4 + (smem_epi > BIG_SMEM_LOOP ? smem_epi : BIG_SMEM_LOOP);
+  static_assert(2 * smem <= 160 * 1024, "two workgroups per compute unit");
+  auto kern = gemm_i8_big_kernel<EPI, TAG, W4, RBF, RAG>;
+  static const hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  if (attr != hipSuccess) return attr;
+  const int tiles_n = (a.N + BIG_BN - 1) / BIG_BN, tiles = ((a.M + BIG_BM - 1) / BIG_BM) * tiles_n;
+  GemmArgs b = a;
+  // tile rows per group: every column tile of a group resident on its XCD at once (64 workgroup slots), at most 4
+  // rows (measured on M = 32768: 4 rows beat 16 by 2 - 9 % on the four linears of DiT-XL/2, 1 - 2 rows lose again)
+  b.group_m = std::min(std::max(64 / tiles_n, 1), 4);
+  hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), smem, st, b);
+  return hipGetLastError();
+}
+
+// The large-M kernel takes over when the weights exist in fragment order, the shape fits its loop (K a multiple of
+// 128, N of 32, 16-byte aligned rows), a 128-row tile holds rows of at most two batch elements (its epilogues are
+// compiled without the general paths) and the launch has enough 128 x 256 tiles for it to pay.
+bool gemm_big_pays(const GemmArgs &a, int epi, int nz) {
+  if (epi == EPI_F32 || !a.Wt || nz != 1 || a.sel_D || a.acc_out) return false;
+  if (a.K % 128 || a.N % 32 || a.lda % 16) return false;
+  if (epi == EPI_RESID && a.rows_per_batch < 128) return false;
+  if (epi == EPI_QKV && (a.y || a.rows_per_batch < 128 || (a.N / 3) % 128 || a.hd % 4 || a.Tp % 8)) return false;
+  const long long tiles = (long long)((a.M + 127) / 128) * ((a.N + 255) / 256);
+  // measured alone on the chip (DiT-XL/2 shapes): 160 tiles (proj / fc2 at M = 4096) run 20 % faster here than in the
+  // tile kernel, 224 - 288 tiles (QKV / fc1 at M = 2048) 0 - 10 % faster, 112 - 144 tiles (M = 1024) 3 - 15 % slower,
+  // 80 tiles (proj / fc2 at M = 2048) 15 - 25 % slower
+  return tiles >= 150;
+}
+
+template <int EPI, int TAG, bool RBF>
+static hipError_t launch_big_w(const GemmArgs &a, hipStream_t st) {
+  return a.w4 ? launch_big_as<EPI, TAG, true, RBF>(a, st) : launch_big_as<EPI, TAG, false, RBF>(a, st);
+}
+
+// `site` only names the instantiation (so that profiles tell the linears apart); the residual epilogue is compiled twice,
+// for float32 stream and cache and for the bfloat16 variants of either
+hipError_t launch_gemm_big(const GemmArgs &a, int epi, hipStream_t st, int site) {
+  if (epi == EPI_GELU_Q) return launch_big_w<EPI_GELU_Q, QC_SITE_FC1, false>(a, st);
+  if (epi == EPI_QKV) return launch_big_w<EPI_QKV, QC_SITE_QKV, false>(a, st);
+  if (a.x_bf16 || a.cache_bf16)
+    return site == QC_SITE_FC2 ? launch_big_w<EPI_RESID, QC_SITE_FC2, true>(a, st) : launch_big_w<EPI_RESID, QC_SITE_PROJ, true>(a, st);
+  return site == QC_SITE_FC2 ? launch_big_w<EPI_RESID, QC_SITE_FC2, false>(a, st) : launch_big_w<EPI_RESID, QC_SITE_PROJ, false>(a, st);
+}
+
+#undef QC_WAIT_VM_FOR4
+#undef QC_LDS_DONE_BARRIER
+#undef QC_SB
+
+}  // namespace qc

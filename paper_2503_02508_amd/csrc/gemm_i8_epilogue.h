@@ -10,6 +10,7 @@ namespace qc {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
@@ -38,21 +39,36 @@ __device__ __forceinline__ v4i unpack_w4(v2i p) {
   return o;
 }
 
-// tanh-GELU written as v * sigmoid(2u), u = sqrt(2/pi) (v + 0.044715 v^3):
-// 0.5 v (1 + tanh u) = v / (1 + exp(-2u)); one exp2 and one reciprocal.
-__device__ __forceinline__ float gelu_tanh(float v) {
-  const float c1 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;   // -2 sqrt(2/pi) log2(e)
-  const float c2 = c1 * 0.044715f;
-  const float t = v * fmaf(c2, v * v, c1);
-  return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
-}
-// the same divided by the quantiser step s: v / (s + s exp(-2u)), the step folded into the denominator
-__device__ __forceinline__ float gelu_tanh_over(float v, float s) {
-  const float c1 = -2.0f * 0.7978845608028654f * 1.4426950408889634f;
-  const float c2 = c1 * 0.044715f;
-  const float t = v * fmaf(c2, v * v, c1);
-  return v * __builtin_amdgcn_rcpf(fmaf(s, __builtin_amdgcn_exp2f(t), s));
-}
+// Four codes of GELU(v) at once, v = sc * corr + bs.  The codes are formed as the paper's unsigned ones (zero point + 128): qz
+// = GELU(v) / s + z leaves one fused multiply-add, v times 1 / (s + s exp(-2u)) (the step folded into the denominator), and one
+// instruction rounds it to nearest even, clamps it to 0 .. 255 and places the byte; the sign bit of the four bytes is flipped
+// back in the result.
+// Bound of the fast path's error in units of the output step, as a multiple of |v| / s (|GELU(v)| <= |v|): 1.5e-6 covers the
+// float32 dequantisation (accumulators beyond 2^24 are rounded on conversion) and the exp2 / reciprocal estimates with a margin
+// of 2, 2e-7 the unrefined quotient; absolute, 2e-6 cover the bias rounding and 8e-6 = 2^-17 the rounding of qz (below 256;
+// beyond, every value clamps to the same code).  An element is in doubt when qz lies closer than the bound to a half:
+// | fract(qz) - 1/2 | - tol_v |v| < near_half.
+struct GeluQuant {
+  float o_s, o_zu, tol_v;
+  static constexpr float near_half = 1e-5f;
+  __device__ __forceinline__ explicit GeluQuant(const QParam &oq) : o_s(oq.s), o_zu((float)(oq.z + 128)), tol_v(1.7e-6f * (1.0f / oq.s)) {}
+  __device__ __forceinline__ unsigned codes(const v4i &corr, const v4f &sc, const v4f &bs, float (&clear)[4]) const {
+    const float c1 = -2.0f * 0.7978845608028654f * 1.4426950408889634f, c2 = c1 * 0.044715f;      // -2 sqrt(2/pi) log2(e)
+    unsigned w = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float v = fmaf(sc[e], (float)corr[e], bs[e]);
+      const float t = v * fmaf(c2, v * v, c1);
+      const float qz = fmaf(v, __builtin_amdgcn_rcpf(fmaf(o_s, __builtin_amdgcn_exp2f(t), o_s)), o_zu);
+      w = __builtin_amdgcn_cvt_pk_u8_f32(qz, e, w);
+      clear[e] = fmaf(-tol_v, fabsf(v), fabsf(__builtin_amdgcn_fractf(qz) - 0.5f));
+    }
+    return w ^ 0x80808080u;
+  }
+  __device__ __forceinline__ bool doubt(const float (&clear)[4]) const {
+    return fminf(fminf(clear[0], clear[1]), fminf(clear[2], clear[3])) < near_half;
+  }
+};
 
 // Dequantised output of a quantised linear as it is stored: the float32 rounding of the float64 value
 // (a_s * w_s[n]) * (acc - a_z * wsum[n]) + bias[n] (the product of the two scales is exact in float64; one float64
@@ -86,12 +102,8 @@ __device__ __forceinline__ int quant_code(float v, float s, float inv_s, float z
 // columns n) of wavefront (wave / WN, wave % WN); for EPI_GELU_Q the weights were the first MFMA operand (register
 // index runs along n), otherwise the activations were (register index runs along m).  smem: the workgroup's dynamic
 // LDS, free for reuse (every wavefront is past its last fragment read).
-// FAST: the launcher has checked that every tile is interior along m and lies in one batch element (and, for the QKV
-// scatter, the alignment its staged path needs); the general paths are then not compiled into the kernel.
 // RBF: the residual stream or the cache may be bfloat16 (read from the arguments); false: both are known to be float32.
-// RAG (with FAST): tiles may end beyond the last row and may span two batch elements (which have at least BM rows each); a
-// tile tests once which case it is, whole tiles inside one batch element keep the fast code.
-template <int BM, int BN, int WM, int WN, int EPI, bool FAST = false, bool RBF = true, bool RAG = false>
+template <int BM, int BN, int WM, int WN, int EPI, bool RBF = true>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM / WM / 32][BN / WN / 32], unsigned char *smem,
                                               const int m0, const int n0, const int z) {
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NT = 64 * WM * WN;
@@ -108,7 +120,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
   const float *w_scale = p.w_scale + (long long)z * p.zs_vecN;
   const int32_t *wsum = p.wsum + (long long)z * p.zs_vecN;
   const float *bias = p.bias ? p.bias + (long long)z * p.zs_vecN : nullptr;
-
   if (EPI == EPI_GELU_Q) {
     // per-column constants into LDS: v = sc[n] * float(acc - zw[n]) + bs[n]
     float *c_sc = (float *)smem;
@@ -130,15 +141,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
     }
     __syncthreads();
     const QParam oq = *p.o_qp;
-    // codes are formed as the paper's unsigned ones (zero point + 128, clamped to 0 .. 255, converted and packed by
-    // one instruction each); the sign bit of the four bytes is flipped back when the word is stored
-    const float o_s = oq.s, o_inv = 1.0f / oq.s, o_zu = (float)(oq.z + 128);
-    // Bound of the fast path's error in units of the output step, as a multiple of |v| / s (|GELU(v)| <= |v|):
-    // 1.5e-6 covers the float32 dequantisation (accumulators beyond 2^24 are rounded on conversion) and the exp2 /
-    // reciprocal estimates with a margin of 2, 2e-7 the unrefined quotient gv * (1 / s); 2e-6 absolute covers the bias
-    // rounding.  An element is in doubt when |q - rint(q)| + bound > 1/2.
-    const float tol_v = 1.7e-6f * o_inv;
-    const float doubt_at = 0.5f - 2e-6f;
+    const GeluQuant gq(oq);
     const int g = lane >> 5;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
@@ -150,25 +153,16 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
         const v4f bs = *(const v4f *)(c_bs + nl);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-          unsigned w = 0;
-          float dist[4];                                      // distance from the rounding boundary plus the error bound
-          int corr[4];
+          float clear[4];
+          v4i corr;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            // the large-M kernel's accumulators already carry the zero-point term
-            corr[e] = FAST ? acc[i][j][rg * 4 + e] : acc[i][j][rg * 4 + e] - zw[e];
-            const float v = fmaf(sc[e], (float)corr[e], bs[e]);
-            const float q = gelu_tanh_over(v, o_s);
-            const float r = __builtin_rintf(q);
-            w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(r + o_zu, 0.0f, 255.0f), e, w);
-            dist[e] = fmaf(tol_v, fabsf(v), fabsf(q - r));
-          }
-          w ^= 0x80808080u;
+          for (int e = 0; e < 4; ++e) corr[e] = acc[i][j][rg * 4 + e] - zw[e];
+          const unsigned w = gq.codes(corr, sc, bs, clear);
           // one comparison and one branch per four outputs; taken by a wavefront about once in a hundred times
-          if (fmaxf(fmaxf(dist[0], dist[1]), fmaxf(dist[2], dist[3])) > doubt_at) {
+          if (gq.doubt(clear)) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (dist[e] > doubt_at) {
+              if (clear[e] < gq.near_half) {
                 const int slot = atomicAdd(fix_cnt, 1);
                 if (slot < GELU_FIX_CAP) {
                   fix_ent[slot * 4 + 0] = corr[e];
@@ -187,7 +181,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
       for (int f = tid; f < nfix; f += NT) {
         const int corr = fix_ent[f * 4 + 0], nl = fix_ent[f * 4 + 1], row = fix_ent[f * 4 + 2];
         const int n = n0 + nl;
-        if (n < p.N) stage[row * SROW + nl] = (unsigned char)gelu_code_exact(corr, a_s, w_scale[n], bias ? bias[n] : 0.0f, o_s, oq.z);
+        if (n < p.N) stage[row * SROW + nl] = (unsigned char)gelu_code_exact(corr, a_s, w_scale[n], bias ? bias[n] : 0.0f, oq.s, oq.z);
       }
       if (nfix) __syncthreads();
     }
@@ -199,9 +193,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
       if (m >= p.M || n >= p.N) continue;
       int8_t *dst = p.q_out + (long long)m * p.ldq + n;
       if (n + 16 <= p.N) {
-        // large launches: streaming stores (the tensor is far larger than the L2 and would only evict the operands)
-        if (FAST) __builtin_nontemporal_store(*(const v4i *)(stage + r * SROW + cc), (v4i *)dst);
-        else *(v4i *)dst = *(const v4i *)(stage + r * SROW + cc);
+        *(v4i *)dst = *(const v4i *)(stage + r * SROW + cc);
       } else {
         for (int e = 0; n + e < p.N; ++e) dst[e] = (int8_t)stage[r * SROW + cc + e];
       }
@@ -216,121 +208,67 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
     const bool fast_t = (T % 4) == 0;
     const bool tile_one_batch = (T % BM) == 0;      // then every row of the tile belongs to batch element m0 / T
     const int b_tile = m0 / T;
-    constexpr int HN = 128;                                   // the tile is handled in column halves of 128
-    if (FAST || (BM == 128 && BN % HN == 0 && (BN / WN) <= HN && tile_one_batch && fast_t && m0 + BM <= p.M && D % HN == 0 &&
-                 (p.hd & 3) == 0 && (p.Tp & 7) == 0)) {
-      // Tile inside one batch element, every 128 columns inside one of Q, K, V: the values go through LDS (free after
+    if (BM == 128 && BN == 128 && tile_one_batch && fast_t && m0 + BM <= p.M && D % BN == 0 && (p.hd & 3) == 0 && (p.Tp & 7) == 0) {
+      // Tile inside one batch element and inside one of Q, K, V: the values go through LDS (free after
       // the K loop) and leave as 16-byte stores along the contiguous direction of their layout (Q / K: features of a
       // token and head; V^T: tokens of a feature).
       const int tb = m0 - b_tile * T;                         // first token of the tile
-      const int rows = RAG ? min(BM, p.M - m0) : BM;          // rows of the tile that exist
-      const int bnd = RAG ? min(rows, T - tb) : BM;           // rows of the first batch element (the others: of the next)
-      const bool edge = RAG && (bnd < BM || (tb & 31) != 0);
+      const int part = n0 / D;
+      float *stage = (float *)smem;
+      constexpr int SR = BN + 4, VR = BM + 4;                 // floats per staged token row (Q / K) and feature row (V^T)
 #pragma unroll
-      for (int hn = 0; hn < BN / HN; ++hn) {
-        const int n0h = n0 + hn * HN;                         // first column of this half
-        if (n0h >= p.N) break;
-        const bool mine = wn0 / HN == hn;                     // this wavefront's columns lie in the half
-        const int part = n0h / D;
-        if (hn) __syncthreads();                              // the previous half has left the staging area
-        float *stage = (float *)smem;
-        constexpr int SR = HN + 4;                            // Q / K: floats per staged token row
-        constexpr int VR = BM + 4;                            // V^T: floats per staged feature row
+      for (int j = 0; j < TN; ++j) {
+        const int nl = wn0 + j * 32 + (lane & 31);
+        const double sc = (double)a_s * (double)w_scale[n0 + nl];
+        const int zw = a_z * wsum[n0 + nl];
+        const double bs = bias ? (double)bias[n0 + nl] : 0.0;
+        float *ycol = p.y ? p.y + (long long)m0 * p.ldy + n0 + nl : nullptr;     // 32 lanes write 128 contiguous bytes
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          if (!mine) continue;
-          const int nl = wn0 - hn * HN + j * 32 + (lane & 31);
-          const double sc = (double)a_s * (double)w_scale[n0h + nl];
-          const int zw = a_z * wsum[n0h + nl];
-          const double bs = bias ? (double)bias[n0h + nl] : 0.0;
-          // the optional row-major copy is not compiled into the large-M kernel (its launcher declines such launches)
-          float *ycol = (!FAST && p.y) ? p.y + (long long)m0 * p.ldy + n0h + nl : nullptr;     // 32 lanes write 128 contiguous bytes
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
-          for (int i = 0; i < TM; ++i) {
+          for (int rg = 0; rg < 4; ++rg) {
+            const int ml = wm0 + i * 32 + rg * 8 + (lane >> 5) * 4;
+            v4f v;
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-              const int ml = wm0 + i * 32 + rg * 8 + (lane >> 5) * 4;
-              v4f v;
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                v[q] = dequant_f32(sc, acc[i][j][rg * 4 + q] - zw, bs);
-                if (ycol) ycol[(unsigned)(ml + q) * (unsigned)p.ldy] = v[q];
-              }
-              if (part < 2) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) stage[(ml + q) * SR + nl] = v[q];
-              } else {
-                // four consecutive tokens stay together under the key permutation of the V^T rows
-                *(v4f *)(stage + nl * VR + (edge ? ml : vt_pos(ml))) = v;
-              }
+            for (int q = 0; q < 4; ++q) {
+              v[q] = dequant_f32(sc, acc[i][j][rg * 4 + q] - zw, bs);
+              if (ycol) ycol[(unsigned)(ml + q) * (unsigned)p.ldy] = v[q];
             }
-            if (TM * TN > 4) __builtin_amdgcn_sched_barrier(0);      // large register tiles: keep the live ranges of a block short
+            if (part < 2) {
+#pragma unroll
+              for (int q = 0; q < 4; ++q) stage[(ml + q) * SR + nl] = v[q];
+            } else {
+              // four consecutive tokens stay together under the key permutation of the V^T rows
+              *(v4f *)(stage + nl * VR + vt_pos(ml)) = v;
+            }
           }
+          if (TM * TN > 4) __builtin_amdgcn_sched_barrier(0);      // large register tiles: keep the live ranges of a block short
         }
-        __syncthreads();
-        if (part < 2) {
-          // thread -> four features cc .. cc + 3 (inside one head: heads start at multiples of hd, a multiple of 4) of
-          // the rows cr, cr + NT / 32, ...
-          const int cr = tid >> 5, cc = (tid & 31) * 4;
-          const int nn = n0h - part * D + cc, h = nn / p.hd, e = nn - h * p.hd;
-          float *dst = (part == 0 ? p.q32 : p.k32) +
-                       ((unsigned)(b_tile * p.heads + h) * (unsigned)T + (unsigned)(tb + cr)) * (unsigned)p.hd + (unsigned)e;
-          if (RAG && edge) {
-            // row beyond the first batch element: its token 0 lies (heads - 1) * T tokens further than the next row would
+      }
+      __syncthreads();
+      if (part < 2) {
+        // thread -> four features cc .. cc + 3 (inside one head: heads start at multiples of hd, a multiple of 4) of
+        // the rows cr, cr + NT / 32, ...
+        const int cr = tid >> 5, cc = (tid & 31) * 4;
+        const int nn = n0 - part * D + cc, h = nn / p.hd, e = nn - h * p.hd;
+        float *dst = (part == 0 ? p.q32 : p.k32) +
+                     ((unsigned)(b_tile * p.heads + h) * (unsigned)T + (unsigned)(tb + cr)) * (unsigned)p.hd + (unsigned)e;
 #pragma unroll
-            for (int q = 0; q < BM * 32 / NT; ++q) {
-              const int ml = cr + q * (NT / 32);
-              const unsigned skip = ml >= bnd ? (unsigned)(p.heads - 1) * (unsigned)T : 0u;
-              if (ml < rows) *(v4f *)(dst + ((unsigned)(q * (NT / 32)) + skip) * (unsigned)p.hd) = *(const v4f *)(stage + ml * SR + cc);
-            }
-            continue;
-          }
+        for (int q = 0; q < BM * 32 / NT; ++q)
+          *(v4f *)(dst + (unsigned)(q * (NT / 32)) * (unsigned)p.hd) = *(const v4f *)(stage + (cr + q * (NT / 32)) * SR + cc);
+      } else {
+        // thread -> 4 consecutive token positions ch of the features fc, fc + NT / 32, ...
+        const int fc = tid >> 5, ch = (tid & 31) * 4;
 #pragma unroll
-          for (int q = 0; q < BM * 32 / NT; ++q) {
-            const v4f v = *(const v4f *)(stage + (cr + q * (NT / 32)) * SR + cc);
-            v4f *d = (v4f *)(dst + (unsigned)(q * (NT / 32)) * (unsigned)p.hd);
-            if (FAST) __builtin_nontemporal_store(v, d);      // large launches: streaming stores
-            else *d = v;
-          }
-        } else {
-          // thread -> 4 consecutive token positions ch of the features fc, fc + NT / 32, ...
-          const int fc = tid >> 5, ch = (tid & 31) * 4;
-          if (RAG && edge) {
-            // the tile's rows do not start at a group of 32 keys: natural order in LDS, permuted on the way out.  Units of
-            // four tokens stay whole when T is a multiple of 4 (then so is every tile's first token)
-            const bool second = ch >= bnd;
-            const int t0 = tb + ch - (second ? T : 0), b = b_tile + (second ? 1 : 0);
-#pragma unroll 4
-            for (int q = 0; q < HN * 32 / NT; ++q) {
-              const int col = fc + q * (NT / 32);
-              const int nn = n0h - 2 * D + col, h = nn / p.hd, e = nn - h * p.hd;
-              const float *src = stage + col * VR + ch;
-              if ((T & 3) == 0) {
-                float *row = p.vt32 + ((size_t)(b * p.heads + h) * p.DP + e) * p.Tp;
-                if (ch < rows) *(v4f *)(row + vt_pos(t0)) = *(const v4f *)src;
-              } else {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                  const int ml = ch + u, bu = b_tile + (ml >= bnd ? 1 : 0), t = tb + ml - (ml >= bnd ? T : 0);
-                  if (ml < rows) p.vt32[((size_t)(bu * p.heads + h) * p.DP + e) * p.Tp + vt_pos(t)] = src[u];
-                }
-              }
-            }
-            continue;
-          }
-#pragma unroll
-          for (int q = 0; q < HN * 32 / NT; ++q) {
-            const int col = fc + q * (NT / 32);
-            const int nn = n0h - 2 * D + col, h = nn / p.hd, e = nn - h * p.hd;
-            const unsigned o = ((unsigned)(b_tile * p.heads + h) * (unsigned)p.DP + (unsigned)e) * (unsigned)p.Tp + (unsigned)(tb + ch);
-            if (FAST) __builtin_nontemporal_store(*(const v4f *)(stage + col * VR + ch), (v4f *)(p.vt32 + o));
-            else *(v4f *)(p.vt32 + o) = *(const v4f *)(stage + col * VR + ch);
-          }
+        for (int q = 0; q < BN * 32 / NT; ++q) {
+          const int col = fc + q * (NT / 32);
+          const int nn = n0 - 2 * D + col, h = nn / p.hd, e = nn - h * p.hd;
+          const unsigned o = ((unsigned)(b_tile * p.heads + h) * (unsigned)p.DP + (unsigned)e) * (unsigned)p.Tp + (unsigned)(tb + ch);
+          *(v4f *)(p.vt32 + o) = *(const v4f *)(stage + col * VR + ch);
         }
       }
       return;
     }
-    if (FAST) return;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = n0 + wn0 + j * 32 + (lane & 31);
@@ -382,157 +320,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
     const bool uniform_batch = (p.rows_per_batch % BM) == 0;
     const int b_uniform = m0 / p.rows_per_batch;
     const int x_bf16 = RBF ? p.x_bf16 : 0, cache_bf16 = RBF ? p.cache_bf16 : 0;
-    const int rows = RAG ? min(BM, p.M - m0) : BM;                                  // rows of the tile that exist
-    const int bnd = RAG ? min(rows, (b_uniform + 1) * p.rows_per_batch - m0) : BM;  // rows of the first batch element
-    const size_t gate1 = RAG && bnd < rows ? (size_t)p.ld_gate : 0;                 // gate row of the others, relative
-    if (FAST && RBF && (x_bf16 || cache_bf16) && p.N % 128 == 0) {
-      // A bfloat16 stream or cache: 32 lanes of a wavefront cover only 64 bytes of a row, and 2-byte stores leave
-      // every cache line half written.  The dequantised values go through LDS in column halves of 128 instead, and
-      // every thread handles four adjacent columns of 16 rows: 8- or 16-byte loads and stores, whole lines per row.
-      constexpr int HN = 128, SR = HN + 4, RQ = BM * 32 / NT;
-      float *stage = (float *)smem;
-      const int cr = tid >> 5, cc = (tid & 31) * 4;     // thread -> rows cr + (NT / 32) q, columns cc .. cc + 3 of a half
-#pragma unroll
-      for (int hn = 0; hn < BN / HN; ++hn) {
-        const int n0h = n0 + hn * HN;
-        if (n0h >= p.N) break;
-        const bool mine = wn0 / HN == hn;               // this wavefront's columns lie in the half
-        if (hn) __syncthreads();                        // the previous half has left the staging area
-        const float *gp = p.gate + (long long)b_uniform * p.ld_gate + n0h + cc;
-        const v4f gv0 = *(const v4f *)gp, gv1 = RAG ? *(const v4f *)(gp + gate1) : gv0;
-        const size_t ob4 = ((size_t)m0 * p.N + n0h + cc) >> 2;      // in groups of four elements
-        const size_t row4 = (size_t)p.N >> 2;
-        // a bfloat16 stream: the thread's 16 pieces of x (8 bytes each) are requested before the staging, which hides
-        // their latency (a float32 stream would take twice the registers: its loads stay in the loop below)
-        uint2 xraw[RQ];
-        if (x_bf16) {
-#pragma unroll
-          for (int q = 0; q < RQ; ++q) {
-            const int row = cr + q * (NT / 32);
-            xraw[q] = ((const uint2 *)p.x)[ob4 + (size_t)(RAG ? min(row, rows - 1) : row) * row4];
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          if (!mine) continue;
-          const int nl = wn0 - hn * HN + j * 32 + (lane & 31);
-          const double sc = (double)a_s * (double)w_scale[n0h + nl];
-          const int zw = a_z * wsum[n0h + nl];
-          const double bs = bias ? (double)bias[n0h + nl] : 0.0;
-#pragma unroll
-          for (int i = 0; i < TM; ++i) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              stage[(wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * SR + nl] = dequant_f32(sc, acc[i][j][r] - zw, bs);
-            __builtin_amdgcn_sched_barrier(0);          // one block's values live at a time
-          }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < RQ; ++q) {      // (fully: xraw must stay in registers)
-          const int row = cr + q * (NT / 32);
-          if (RAG && row >= rows) continue;
-          const v4f gv = RAG && row >= bnd ? gv1 : gv0;
-          const v4f v = *(const v4f *)(stage + row * SR + cc);
-          const size_t o4 = ob4 + (size_t)row * row4;
-          float4 xo;
-          if (x_bf16) {
-            xo = make_float4(__builtin_bit_cast(float, xraw[q].x << 16), __builtin_bit_cast(float, xraw[q].x & 0xFFFF0000u),
-                             __builtin_bit_cast(float, xraw[q].y << 16), __builtin_bit_cast(float, xraw[q].y & 0xFFFF0000u));
-          } else {
-            xo = stream_load4(p.x, o4, 0);
-          }
-          stream_store4(p.cache_out, o4, make_float4(v.x, v.y, v.z, v.w), cache_bf16);
-          stream_store4(p.x, o4, make_float4(fmaf(gv.x, v.x, xo.x), fmaf(gv.y, v.y, xo.y), fmaf(gv.z, v.z, xo.z), fmaf(gv.w, v.w, xo.w)),
-                        x_bf16);
-        }
-      }
-      return;
-    }
-    if (FAST) {
-      // every row of the tile exists and belongs to batch element b_uniform; N is a multiple of 32, so a wavefront's
-      // 32-column block lies inside the matrix or outside it as a whole.  Addresses are a wavefront-uniform row pointer
-      // (scalar arithmetic) plus one 32-bit lane offset, and the loads of x of XB blocks (16 values per lane each: the
-      // registers of the K loop's operand ring and fragments are free now) are issued before the first is used, so a
-      // tile's epilogue pays TM x TN / XB memory round trips instead of TM x TN.
-      constexpr int XB = (!RBF && TM % 2 == 0) ? 2 : 1;   // the bfloat16 variants have no registers to spare
-      const int wv = __builtin_amdgcn_readfirstlane(wave);
-      const int wm0u = (wv / WN) * (BM / WM), wn0u = (wv % WN) * (BN / WN);
-      const unsigned loff = (unsigned)((lane >> 5) * 4) * (unsigned)p.N + (unsigned)(lane & 31);
-      const size_t xsz = x_bf16 ? 2 : 4, csz = cache_bf16 ? 2 : 4;
-      if (RAG && bnd < BM) {
-        // a tile with rows of two batch elements or rows beyond the last one
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int nb = n0 + wn0u + j * 32;
-          if (nb >= p.N) continue;
-          const int n = nb + (lane & 31);
-          const double sc = (double)a_s * (double)w_scale[n];
-          const int zw = a_z * wsum[n];
-          const double bs = bias ? (double)bias[n] : 0.0;
-          const float g0 = p.gate[(long long)b_uniform * p.ld_gate + n], g1 = p.gate[(long long)b_uniform * p.ld_gate + gate1 + n];
-#pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const int mb = wm0u + i * 32 + (lane >> 5) * 4;
-            float xv[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              xv[r] = stream_load(p.x, (size_t)(m0 + min(mb + (r >> 2) * 8 + (r & 3), rows - 1)) * p.N + n, x_bf16);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int ml = mb + (r >> 2) * 8 + (r & 3);
-              const float v = dequant_f32(sc, acc[i][j][r] - zw, bs);
-              if (ml < rows) {
-                const size_t o = (size_t)(m0 + ml) * p.N + n;
-                stream_store(p.cache_out, o, v, cache_bf16);
-                stream_store(p.x, o, fmaf(ml >= bnd ? g1 : g0, v, xv[r]), x_bf16);
-              }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-        return;
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int nb = n0 + wn0u + j * 32;
-        if (nb >= p.N) continue;
-        const int n = nb + (lane & 31);
-        const double sc = (double)a_s * (double)w_scale[n];
-        const int zw = a_z * wsum[n];
-        const double bs = bias ? (double)bias[n] : 0.0;
-        const float g = p.gate[(long long)b_uniform * p.ld_gate + n];
-        const size_t e0 = (size_t)(m0 + wm0u) * p.N + nb;           // first element of the wavefront's block column
-#pragma unroll
-        for (int i0 = 0; i0 < TM; i0 += XB) {
-          float xv[XB][16];
-#pragma unroll
-          for (int ii = 0; ii < XB; ++ii) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const size_t er = e0 + (size_t)((i0 + ii) * 32 + (r >> 2) * 8 + (r & 3)) * p.N;
-              xv[ii][r] = stream_load((const char *)p.x + er * xsz, loff, x_bf16);
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int ii = 0; ii < XB; ++ii) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const size_t er = e0 + (size_t)((i0 + ii) * 32 + (r >> 2) * 8 + (r & 3)) * p.N;
-              const float v = dequant_f32(sc, acc[i0 + ii][j][r] - zw, bs);
-              // the cached tensor is written once and read a step later: a streaming store keeps it out of the L2's way
-              if (!RBF) __builtin_nontemporal_store(v, (float *)((char *)p.cache_out + er * csz) + loff);
-              else stream_store((char *)p.cache_out + er * csz, loff, v, cache_bf16);
-              stream_store((char *)p.x + er * xsz, loff, fmaf(g, v, xv[ii][r]), x_bf16);
-            }
-            __builtin_amdgcn_sched_barrier(0);                // one block's dequantised values live at a time
-          }
-        }
-      }
-      return;
-    }
     const bool interior = uniform_batch && m0 + BM <= p.M && n0 + BN <= p.N;
 #pragma unroll
     for (int j0 = 0; j0 < TN; j0 += JB)

@@ -216,7 +216,7 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
   }
   __syncthreads();                                                 // the sums are read: LDS is free for the epilogue
   if (wave >= EM * EN) return;                                     // (ended wavefronts do not count at its barriers)
-  gemm_epilogue<BM, BN, EM, EN, EPI, false, RBF>(p, fin, smem, m0, n0, 0);
+  gemm_epilogue<BM, BN, EM, EN, EPI, RBF>(p, fin, smem, m0, n0, 0);
 }
 
 template <int TM, int TN, int NW, int EPI, bool W4, bool WROW, bool RBF = false>

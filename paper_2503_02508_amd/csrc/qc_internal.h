@@ -141,6 +141,9 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 }
 
 hipError_t launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st, int site);
+// the large-M kernel (gemm_i8_big.hip): whether a launch is one of its, and the launch
+bool gemm_big_pays(const GemmArgs &a, int epi, int nz);
+hipError_t launch_gemm_big(const GemmArgs &a, int epi, hipStream_t st, int site);
 // the split-K kernel of small launches (gemm_i8_split.hip): whether a launch is one of them, and the launch
 bool gemm_split_pays(const GemmArgs &a, int epi, int nz);
 hipError_t launch_gemm_split(const GemmArgs &a, int epi, hipStream_t st);
