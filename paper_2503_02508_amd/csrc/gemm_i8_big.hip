@@ -481,6 +481,25 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
     step(kt, 3, buf);
   };
   // K is a multiple of 128 (checked by the launcher)
+  if (EPI != EPI_GELU_Q && !W4 && n0 + wn0 >= p.N) {
+    // a wavefront whose columns all lie beyond N (half of a last tile when N = 1152) only moves its share of the activations: at
+    // the power limit the products it leaves out are time for the others (measured with M = 8192 and more: 0.3 - 0.7 % of a
+    // whole run; with packed weights, which fewer bytes and more vector work bound, it lost 1 %)
+#pragma unroll
+    for (int g = 0; g < 2; ++g) QC_WAIT_VM_FOR4(0, bq[g][0], bq[g][1], bq[g][2], bq[g][3]);
+    for (int kt = 0; kt < nk; ++kt) {
+      QC_WAIT_VM_FOR4(0, ra[0], ra[1], ra[2], ra[3]);
+#pragma unroll
+      for (int i = 0; i < PA; ++i) write_a(ra[i], (kt & 1) ^ 1, i);
+      QC_SB;
+#pragma unroll
+      for (int i = 0; i < PA; ++i) load_a(ra[i], kt + 2, i);
+      QC_LDS_DONE_BARRIER;
+    }
+    QC_WAIT_VM_FOR4(0, ra[0], ra[1], ra[2], ra[3]);
+    __syncthreads();
+    return;
+  }
   int kt = 0;
   for (; kt + 2 <= nk; kt += 2) {
     slab(kt, 0);
