@@ -333,7 +333,7 @@ int qc_load_weights_f32(qc_ctx *ctx, const qc_weights_f32 *w, void *stream) {
     for (int s = 0; s < QC_NUM_SITES; ++s) {
       LinearQ &q = ctx->blk[l].lin[s];
       QC_HIP(launch_quantize_weight(ws[s], q.N, q.K, ctx->d.weight_bits, q.q, q.scale, q.wsum, st));
-      if (q.qt) QC_HIP(launch_tile_weight(q.q, q.qt, q.N, q.K, ctx->d.weight_bits, st));
+      if (q.qt) QC_HIP(launch_tile_weight(q.q, q.qt, q.N, q.K, ctx->d.weight_bits, q.K, st));
       QC_HIP(hipMemcpyAsync(q.bias, bs[s], (size_t)q.N * sizeof(float), hipMemcpyDeviceToDevice, st));
     }
   }
@@ -414,7 +414,10 @@ int qc_w8a8_linear(const int8_t *qx, const void *qw, const int32_t *wsum, const 
   a.M = M; a.N = N; a.K = K; a.lda = K; a.w4 = weight_bits == 4;
   a.a_scale = x_scale; a.a_zp = x_zp - 128;
   a.y = y; a.ldy = N; a.acc_out = acc_or_null;
-  QC_HIP(launch_gemm(a, EPI_F32, 1, static_cast<hipStream_t>(stream), QC_SITE_QKV));
+  hipError_t err = hipSuccess;
+  if (!gemm_big_rows_pays(a) || !launch_gemm_big_rows(a, static_cast<hipStream_t>(stream), &err))
+    err = launch_gemm(a, EPI_F32, 1, static_cast<hipStream_t>(stream), QC_SITE_QKV);
+  QC_HIP(err);
   return QC_OK;
 }
 

@@ -29,6 +29,8 @@
 // register loads share the counter but complete out of order with respect to each other, so counted waits gave wrong
 // fragments on some boxes, and draining the counter before every barrier cost 8 % against this version.)
 #include <algorithm>
+#include <map>
+#include <mutex>
 
 #include "gemm_i8_epilogue.h"
 
@@ -309,6 +311,38 @@ __device__ __forceinline__ void big_resid(const GemmArgs &p, BigAcc &acc, unsign
   }
 }
 
+// float32 rows [M, ldy], any N and M
+__device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
+  const int left = p.N - n0 - wn0, rows = min(BIG_BM, p.M - m0);
+  if (left <= 0) return;
+  float *stage = (float *)smem + wave * (32 * BIG_SR);
+  const auto buf = __builtin_amdgcn_make_buffer_rsrc(p.y + (size_t)m0 * p.ldy + n0 + wn0, 0, -1, 0x00027000);
+  const int col = row * 4;
+#pragma unroll
+  for (int ip = 0; ip < BIG_TM; ip += 2) {
+    QC_SB;
+    big_stage_rows(acc, stage, cst, wn0, a_s, ip);
+    if ((p.N & 3) == 0) {                                     // whole groups of four columns
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int m = ip * 16 + q * 4;
+        const v4u v = *(const v4u *)(stage + (q * 4 + g) * BIG_SR + col);
+        if (col < left && m + g < rows) __builtin_amdgcn_raw_buffer_store_b128(v, buf, (g * p.ldy + col) * 4, m * p.ldy * 4, 2);
+      }
+    } else {                                                  // a row of 64 columns at a time
+#pragma unroll 8
+      for (int r = 0; r < 32; ++r) {
+        const int m = ip * 16 + r;
+        const unsigned v = *(const unsigned *)(stage + r * BIG_SR + lane);
+        if (lane < left && m < rows) __builtin_amdgcn_raw_buffer_store_b32(v, buf, lane * 4, m * p.ldy * 4, 2);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    QC_SB;
+  }
+}
+
 template <int EPI, int TAG, bool W4, bool RBF, bool RAG>
 __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   constexpr int BM = BIG_BM, BN = BIG_BN, BK = BIG_BK, TM = BIG_TM, TN = BIG_TN;
@@ -359,10 +393,19 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   for (int i = 0; i < PA; ++i) aoff[i] = (unsigned)(min(m0 + 32 * i + arow, p.M - 1) - m0) * (unsigned)p.lda + ac * 16;
   const unsigned lpos = arow * BK + ((ac ^ ((arow >> 1) & 7)) * 16);          // + 32 i rows: the same swizzle
   const int8_t *abase = p.A + (size_t)m0 * p.lda;
-  const int nk = p.K / BK, ng = p.K / 64;
+  // K: a multiple of 128, or (EPI_F32) of 16: the stored weights are zero from K to the end of the last slab, and chunks of it
+  // beyond K re-read the row's last one
+  const int nk = EPI == EPI_F32 ? (p.K + BK - 1) / BK : p.K / BK, ng = nk * (BK / 64);
+  const unsigned kback = EPI == EPI_F32 ? (unsigned)max((nk - 1) * BK + ac * 16 + 16 - p.K, 0) : 0u;
   v4i ra[PA];
   auto load_a = [&](v4i &r, int kt, int i) {      // slabs past the end re-read the last one (never used)
-    asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(r) : "v"(aoff[i]), "s"(abase + min(kt, nk - 1) * BK) : "memory");
+    // (kback of the last slab may exceed aoff of row 0: the sum of base and offset is what counts, so the base gives it up front)
+    if constexpr (EPI == EPI_F32) {
+      const int8_t *src = abase + min(kt, nk - 1) * BK - BK;
+      asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(r) : "v"(aoff[i] + (BK - (kt >= nk - 1 ? kback : 0u))), "s"(src) : "memory");
+    } else {
+      asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(r) : "v"(aoff[i]), "s"(abase + min(kt, nk - 1) * BK) : "memory");
+    }
   };
   auto write_a = [&](const v4i &r, int buf, int i) { *(v4i *)(smem + buf * SLAB + lpos + i * 32 * BK) = r; };
 
@@ -371,7 +414,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   // the 64 k, row l % 16 of the half
   constexpr int FRAG = W4 ? 512 : 1024;           // bytes per stored fragment
   typedef typename std::conditional<W4, v2i, v4i>::type wfrag_t;
-  const int nblocks = p.N / 32;
+  const int nblocks = (p.N + 31) / 32;
   const int8_t *sb[TN / 2];
 #pragma unroll
   for (int j = 0; j < TN / 2; ++j) sb[j] = (const int8_t *)p.Wt + (size_t)min((n0 + wn0) / 32 + j, nblocks - 1) * (2 * ng) * FRAG;
@@ -393,7 +436,14 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   BigAcc acc;
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
-    const v4i ws = *(const v4i *)(p.wsum + min(n0 + wn0 + j * 16 + (lane >> 4) * 4, p.N - 4));
+    const int n = n0 + wn0 + j * 16 + (lane >> 4) * 4;
+    v4i ws;
+    if constexpr (EPI == EPI_F32) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ws[e] = p.wsum[min(n + e, p.N - 1)];
+    } else {
+      ws = *(const v4i *)(p.wsum + min(n, p.N - 4));
+    }
     v4i c0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) c0[e] = -(a_z * ws[e]);
@@ -480,7 +530,6 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
     QC_LDS_DONE_BARRIER;
     step(kt, 3, buf);
   };
-  // K is a multiple of 128 (checked by the launcher)
   if (EPI != EPI_GELU_Q && !W4 && n0 + wn0 >= p.N) {
     // a wavefront whose columns all lie beyond N (half of a last tile when N = 1152) only moves its share of the activations: at
     // the power limit the products it leaves out are time for the others (measured with M = 8192 and more: 0.3 - 0.7 % of a
@@ -516,13 +565,14 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   __syncthreads();
   if constexpr (EPI == EPI_GELU_Q) big_gelu(p, acc, smem, cst, m0, n0, a_s);
   else if constexpr (EPI == EPI_QKV) big_qkv<RAG>(p, acc, smem, cst, m0, n0, a_s);
+  else if constexpr (EPI == EPI_F32) big_f32(p, acc, smem, cst, m0, n0, a_s);
   else big_resid<RBF, RAG>(p, acc, smem, cst, m0, n0, a_s);
 }
 
 template <int EPI, int TAG, bool W4, bool RBF, bool RAG = false>
 static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   // launches whose tiles are not all whole and inside one batch element take the variant that handles the others
-  if constexpr (!RAG && EPI != EPI_GELU_Q) {
+  if constexpr (!RAG && (EPI == EPI_RESID || EPI == EPI_QKV)) {
     if (a.M % BIG_BM || a.rows_per_batch % BIG_BM) return launch_big_as<EPI, TAG, W4, RBF, true>(a, st);
   }
   constexpr int smem_epi = EPI == EPI_GELU_Q ? BIG_SMEM_GELU : (EPI == EPI_QKV ? BIG_SMEM_QKV : BIG_SMEM_RESID);
@@ -568,6 +618,66 @@ hipError_t launch_gemm_big(const GemmArgs &a, int epi, hipStream_t st, int site)
   if (a.x_bf16 || a.cache_bf16)
     return site == QC_SITE_FC2 ? launch_big_w<EPI_RESID, QC_SITE_FC2, true>(a, st) : launch_big_w<EPI_RESID, QC_SITE_PROJ, true>(a, st);
   return site == QC_SITE_FC2 ? launch_big_w<EPI_RESID, QC_SITE_FC2, false>(a, st) : launch_big_w<EPI_RESID, QC_SITE_PROJ, false>(a, st);
+}
+
+// Row-major weights (qc_w8a8_linear): the launch first writes them in fragment order, rows padded with zeros to 32 and k to 128,
+// into memory of a stream-ordered pool: no wait on either side, safe with several streams and threads, and the pool keeps at
+// most BIG_POOL_KEEP bytes between calls.
+constexpr uint64_t BIG_POOL_KEEP = 64ull << 20;
+
+static hipMemPool_t big_pool() {
+  static std::mutex mu;
+  static std::map<int, hipMemPool_t> pools;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  std::lock_guard<std::mutex> lock(mu);
+  const auto it = pools.find(dev);
+  if (it != pools.end()) return it->second;
+  hipMemPoolProps props{};
+  props.allocType = hipMemAllocationTypePinned;
+  props.location.type = hipMemLocationTypeDevice;
+  props.location.id = dev;
+  hipMemPool_t pool = nullptr;
+  uint64_t keep = BIG_POOL_KEEP;
+  if (hipMemPoolCreate(&pool, &props) != hipSuccess) pool = nullptr;
+  else if (hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+    (void)hipMemPoolDestroy(pool);
+    pool = nullptr;
+  }
+  pools[dev] = pool;
+  return pool;
+}
+
+bool gemm_big_rows_pays(const GemmArgs &a) {
+  if (a.acc_out) return false;
+  const long long tiles = (long long)((a.M + 127) / 128) * ((a.N + 255) / 256);
+  // measured against the tile kernel (us, tile kernel / this one with its copy of the weights): 16384 x 4608 x 1152 204 / 136,
+  // 8192 x 3456 x 1152 71 / 54, 16384 x 1000 x 1168 48 / 40, 16384 x 2049 x 528 75 / 69, 3000 x 4608 x 1152 37 / 33; below 1.5e10
+  // products the copy and the pool's calls (24 us of host time) are not earned back (8192 x 2049 x 528 42 / 48), nor with half of
+  // the chip's tile slots idle (4096 x 1152 x 4608, 4-bit, 160 tiles: 50 / 51) or many columns of padding
+  return (double)a.M * a.N * a.K >= 1.55e10 && tiles >= 256 && (double)tiles * BIG_BM * BIG_BN <= 1.34 * a.M * a.N;
+}
+
+// false: not launched (no memory, or a stream that is being captured), nothing done
+bool launch_gemm_big_rows(const GemmArgs &a, hipStream_t st, hipError_t *err) {
+  *err = hipSuccess;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+  const hipMemPool_t pool = big_pool();
+  const int Kp = (a.K + BIG_BK - 1) / BIG_BK * BIG_BK;
+  const size_t bytes = (size_t)((a.N + 31) / 32 * 32) * (a.w4 ? Kp / 2 : Kp);
+  void *wt = nullptr;
+  if (!pool || hipMallocFromPoolAsync(&wt, bytes, pool, st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  GemmArgs b = a;
+  b.Wt = wt;
+  *err = launch_tile_weight(a.W, wt, a.N, a.K, a.w4 ? 4 : 8, Kp, st);
+  if (*err == hipSuccess) *err = a.w4 ? launch_big_as<EPI_F32, QC_SITE_QKV, true, false>(b, st) : launch_big_as<EPI_F32, QC_SITE_QKV, false, false>(b, st);
+  const hipError_t fe = hipFreeAsync(wt, st);
+  if (*err == hipSuccess) *err = fe;
+  return true;
 }
 
 #undef QC_WAIT_VM_FOR4

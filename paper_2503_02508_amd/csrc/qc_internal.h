@@ -144,11 +144,14 @@ hipError_t launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st, int s
 // the large-M kernel (gemm_i8_big.hip): whether a launch is one of its, and the launch
 bool gemm_big_pays(const GemmArgs &a, int epi, int nz);
 hipError_t launch_gemm_big(const GemmArgs &a, int epi, hipStream_t st, int site);
+// the same with float32 results and row-major weights: whether it pays, and the launch (false: nothing was launched)
+bool gemm_big_rows_pays(const GemmArgs &a);
+bool launch_gemm_big_rows(const GemmArgs &a, hipStream_t st, hipError_t *err);
 // the split-K kernel of small launches (gemm_i8_split.hip): whether a launch is one of them, and the launch
 bool gemm_split_pays(const GemmArgs &a, int epi, int nz);
 hipError_t launch_gemm_split(const GemmArgs &a, int epi, hipStream_t st);
-// row-major codes [N, K] (or packed [N, K/2]) -> fragment order; N % 32 == 0, K % 32 == 0
-hipError_t launch_tile_weight(const void *q, void *qt, int N, int K, int bits, hipStream_t st);
+// row-major codes [N, K] (or packed [N, K/2], K % 16 == 0) -> fragment order, zeros up to the next 32 rows and to Kp (% 32 == 0)
+hipError_t launch_tile_weight(const void *q, void *qt, int N, int K, int bits, int Kp, hipStream_t st);
 
 // ---- elementwise / row kernels
 hipError_t launch_quantize_act(const float *x, int8_t *q, size_t n, float s, int z_signed, hipStream_t st);

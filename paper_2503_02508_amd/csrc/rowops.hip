@@ -100,22 +100,23 @@ hipError_t launch_quantize_weight(const float *w, int N, int K, int bits, void *
 // (n / 32, k / 32) is 64 lanes x 16 bytes (8 bytes for packed nibbles), lane l holds row n % 32 = l % 32, k values
 // 16 (l / 32) .. 16 (l / 32) + 15 of the group.  One thread per (fragment, lane).
 __global__ __launch_bounds__(256) void tile_weight_kernel(const unsigned char *__restrict__ q, unsigned char *__restrict__ qt, int N,
-                                                          int K, int w4) {
+                                                          int K, int Kp, int w4) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int ng = K / 32;
-  if (i >= (size_t)(N / 32) * ng * 64) return;
+  const int ng = Kp / 32;
+  if (i >= (size_t)((N + 31) / 32) * ng * 64) return;
   const int l = (int)(i & 63), kg = (int)((i >> 6) % ng), nb = (int)((i >> 6) / ng);
   const size_t n = (size_t)nb * 32 + (l & 31);
   const int k = kg * 32 + (l >> 5) * 16;
-  if (w4) *(uint2 *)(qt + i * 8) = *(const uint2 *)(q + n * (K >> 1) + (k >> 1));
-  else *(uint4 *)(qt + i * 16) = *(const uint4 *)(q + n * K + k);
+  const bool in = n < (size_t)N && k < K;         // K is a multiple of 16
+  if (w4) *(uint2 *)(qt + i * 8) = in ? *(const uint2 *)(q + n * (K >> 1) + (k >> 1)) : make_uint2(0, 0);
+  else *(uint4 *)(qt + i * 16) = in ? *(const uint4 *)(q + n * K + k) : make_uint4(0, 0, 0, 0);
 }
 
-hipError_t launch_tile_weight(const void *q, void *qt, int N, int K, int bits, hipStream_t st) {
-  if (N % 32 || K % 32) return hipErrorInvalidValue;
-  const size_t n = (size_t)(N / 32) * (K / 32) * 64;
+hipError_t launch_tile_weight(const void *q, void *qt, int N, int K, int bits, int Kp, hipStream_t st) {
+  if (K % 16 || Kp % 32 || Kp < K) return hipErrorInvalidValue;
+  const size_t n = (size_t)((N + 31) / 32) * (Kp / 32) * 64;
   hipLaunchKernelGGL(tile_weight_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const unsigned char *)q,
-                     (unsigned char *)qt, N, K, bits == 4 ? 1 : 0);
+                     (unsigned char *)qt, N, K, Kp, bits == 4 ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -99,6 +99,25 @@ def test_w8a8_linear_accumulators_bit_exact(qc, bits, M, N, K):
     assert np.max(np.abs(got - want_y)) <= 1e-6 * np.max(np.abs(want_y)) + 1e-7
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K", [(16385, 1155, 848), (4001, 3460, 1168), (8192, 2048, 1024)])
+def test_w8a8_linear_large(qc, bits, M, N, K):
+    """The large-M kernel (taken when no accumulators are asked for): partial tiles in every direction, and whole ones, equal to
+    the tile kernel bit for bit and to exact sums of sampled rows."""
+    import torch
+    rng = np.random.default_rng(M + N + K + bits)
+    qx = rng.integers(-128, 128, size=(M, K), dtype=np.int8)
+    lin = OQ.QLinear((rng.standard_normal((N, K)) * 0.02).astype(np.float32), (rng.standard_normal(N) * 0.02).astype(np.float32), bits)
+    args = (_cuda(qx), _cuda(lin.packed()), _cuda(lin.wsum.astype(np.int32)), _cuda(lin.scale), _cuda(lin.bias), 0.0213, 117, bits)
+    y = [torch.full((M, N), float("nan"), device="cuda") for _ in range(2)]
+    acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    qc.qc_w8a8_linear(*args, y[0], None)
+    qc.qc_w8a8_linear(*args, y[1], acc)
+    assert torch.equal(y[0], y[1])
+    rows = [0, 1, M // 2, M - 2, M - 1]
+    assert np.array_equal(acc[rows].cpu().numpy().astype(np.int64), OQ.int_matmul(qx[rows], lin.q))
+
+
 def test_w8a8_linear_extreme_codes_and_no_bias(qc):
     import torch
     M, N, K = 40, 70, 4608
