@@ -37,6 +37,21 @@ def code_flip_stats(got_codes, want_codes):
     return float(np.mean(d != 0)), int(d.max()) if d.size else 0
 
 
+def qkv_difference(got, want, D, limit=12):
+    """What differs between two [M, 3 D] arrays of Q | K | V, in words: the rows, and for each of the first of them how many
+    columns of Q, K and V and which.  A row that differs in almost every column had other codes; one that differs in columns
+    of a few tiles only had the right codes and another product or another store."""
+    ne = np.asarray(got) != np.asarray(want)
+    rows = np.flatnonzero(ne.any(axis=1))
+    lines = ["%d of %d rows differ: %s" % (len(rows), len(ne), rows[:64].tolist())]
+    for r in rows[:limit]:
+        cols = np.flatnonzero(ne[r])
+        lines.append("row %d: Q %d, K %d, V %d of %d columns, from %d to %d, the first %s, got %s, want %s" % (
+            r, *(np.count_nonzero(ne[r, i * D:(i + 1) * D]) for i in range(3)), D, cols[0], cols[-1], cols[:8].tolist(),
+            np.asarray(got)[r, cols[:4]].tolist(), np.asarray(want)[r, cols[:4]].tolist()))
+    return "\n".join(lines)
+
+
 def qkv_rows_from_heads(ctx, model, max_batch, B):
     """The last QKV projection as a row-major [B * T, 3 D] device tensor, gathered from the head-major buffers the
     attention kernel reads (Q and K [max_batch, H, T, d], V transposed [max_batch, H, dp, Tp] with the keys of each group

@@ -1,0 +1,108 @@
+"""What the compiled kernels must keep that no run shows reliably."""
+import os
+import re
+import subprocess
+
+import pytest
+
+PKG = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2503_02508_amd")
+LLVM = "/opt/rocm/llvm/bin/"
+SLOTS = 2                  # issue slots after a wide store in which no vector instruction may write its data registers
+
+
+def _code_objects(lib, tmp):
+    """The gfx950 code objects inside a HIP shared library (one bundle per translation unit)."""
+    raw = os.path.join(tmp, "fatbin")
+    subprocess.run([LLVM + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + raw, lib, os.path.join(tmp, "copy")], check=True)
+    data = open(raw, "rb").read()
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    out = []
+    for m in re.finditer(magic, data):
+        p = m.start() + len(magic)
+        count = int.from_bytes(data[p:p + 8], "little")
+        p += 8
+        for _ in range(count):
+            off, size, n = (int.from_bytes(data[p + 8 * i:p + 8 * i + 8], "little") for i in range(3))
+            if b"gfx950" in data[p + 24:p + 24 + n]:
+                path = os.path.join(tmp, "code%d" % len(out))
+                with open(path, "wb") as f:
+                    f.write(data[m.start() + off:m.start() + off + size])
+                out.append(path)
+            p += 24 + n
+    return out
+
+
+def _vgprs(operand):
+    m = re.match(r"v\[(\d+):(\d+)\]$|v(\d+)$", operand.strip())
+    if not m:
+        return frozenset()
+    return frozenset([int(m.group(3))] if m.group(3) else range(int(m.group(1)), int(m.group(2)) + 1))
+
+
+def _overwritten_stores(lines):
+    """Stores of more than 64 bits whose data registers a vector instruction writes fewer than SLOTS slots later, along every
+    path.  lines: instructions and labels of a disassembly, in order."""
+    code, label = [], {}
+    for line in lines:
+        line = line.split("//")[0].strip()
+        if re.match(r"<?L\d+>?:$", line):
+            label[line.strip("<>:")] = len(code)
+        elif re.match(r"[a-z]\w+( |$)", line):
+            code.append(line)
+    found = []
+
+    def follow(at, data, left, store):
+        while left > 0 and at < len(code):
+            op, _, rest = code[at].partition(" ")
+            if op == "s_nop":
+                left -= int(rest, 0) + 1
+            elif op in ("s_endpgm", "s_setpc_b64", "s_swappc_b64"):
+                return
+            elif op.startswith(("s_branch", "s_cbranch")):
+                if rest.strip() in label:
+                    follow(label[rest.strip()], data, left - 1, store)
+                if op == "s_branch":
+                    return
+                left -= 1
+            else:
+                if op.startswith("v_") and _vgprs(rest.split(",")[0]) & data:
+                    found.append(store + "  ->  " + code[at])
+                    return
+                left -= 1
+            at += 1
+
+    for i, line in enumerate(code):
+        m = re.match(r"(buffer|global|flat|scratch)_store_(?:dwordx[34]|b96|b128)\s+(.*)", line)
+        if m:
+            args = re.split(r",\s*(?![^\[]*\])", m.group(2))
+            follow(i + 1, _vgprs(args[0] if m.group(1) == "buffer" else args[1]), SLOTS, line)
+    return found
+
+
+def test_a_data_register_of_a_store_written_too_early_is_found():
+    bad = "buffer_store_dwordx4 v[204:207], v88, s[4:7], s3 offen nt"
+    assert _overwritten_stores([bad, "v_cvt_f32_i32_e32 v204, v84"])
+    assert _overwritten_stores([bad, "s_mov_b32 s0, 0", "v_mad_u64_u32 v[206:207], s[8:9], s2, v88, v[84:85]"])
+    assert _overwritten_stores([bad, "s_branch L1", "v_mov_b32_e32 v1, 0", "<L1>:", "v_mov_b32_e32 v205, 0"])
+    assert not _overwritten_stores([bad, "s_nop 1", "v_cvt_f32_i32_e32 v204, v84"])
+    assert not _overwritten_stores([bad, "v_mov_b32_e32 v203, 0", "v_mov_b32_e32 v208, 0", "v_mov_b32_e32 v204, 0"])
+
+
+def test_no_store_loses_its_data_to_the_next_instruction(tmp_path):
+    """A store reads its data registers after it has issued; with a scalar offset the compiler does not keep vector writes away
+    from them (Q | K | V of a ragged large-M launch then had a few wrong words about once in 300 launches)."""
+    lib = os.path.join(PKG, "libqc.so")
+    if not os.path.exists(LLVM + "llvm-objdump"):
+        pytest.skip("no llvm-objdump")
+    objects = _code_objects(lib, str(tmp_path))
+    assert objects
+    kernels = 0
+    for obj in objects:
+        text = subprocess.run([LLVM + "llvm-objdump", "-d", "--mcpu=gfx950", "--symbolize-operands", "--no-show-raw-insn",
+                               "--no-leading-addr", obj], check=True, stdout=subprocess.PIPE, text=True).stdout
+        for part in re.split(r"^(?=<_Z\w+>:)", text, flags=re.M)[1:]:
+            name, _, body = part.partition("\n")
+            kernels += "s_endpgm" in body
+            found = _overwritten_stores(body.splitlines())
+            assert not found, "%s: %d stores, the first: %s" % (name, len(found), found[0])
+    assert kernels > 50

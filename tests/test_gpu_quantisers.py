@@ -19,7 +19,7 @@ import pytest
 
 from oracle import dit, quant, sampler
 from synthetic import dit_inputs as I
-from qc_testlib import make_pair, code_flip_stats, rel_rms, max_abs, qkv_rows_from_heads
+from qc_testlib import make_pair, code_flip_stats, rel_rms, max_abs, qkv_difference, qkv_rows_from_heads
 
 pytestmark = pytest.mark.gpu
 
@@ -101,7 +101,7 @@ def test_each_fused_quantiser_alone(name, model, B, wb, std):
     qkv_or = (np.float64(np.float32(s)) * L["qkv"].scale.astype(np.float64))[None] * corr + L["qkv"].bias.astype(np.float64)[None]
     rows_off = int(np.count_nonzero(np.any(qkv_dev.astype(np.float32) != f32(qkv_or), axis=1)))
     report["ln1 + qkv rows that differ"] = "%d of %d" % (rows_off, M)
-    assert rows_off == 0
+    assert rows_off == 0, qkv_difference(qkv_dev.astype(np.float32), f32(qkv_or), D)
 
     # ---- attention + quantise, from the device's own Q | K | V (the one approximate kernel: fp16-pair products)
     s, z = qp[(0, "proj")]

@@ -57,6 +57,40 @@ def test_quantisers_of_small_and_ragged_launches(name, model, B, wb):
     check(name, model, B, wb, 0.02 if model.hidden > 1000 else 0.05)
 
 
+@pytest.mark.parametrize("hw,B,wb", [((36, 28), 20, 4), ((36, 28), 20, 8), ((50, 34), 10, 4), ((50, 34), 10, 8)])
+def test_large_m_ragged_block_repeats_itself(hw, B, wb):
+    """Every run of a block whose large-M tiles span batch elements gives the same stored tensors from the same input, bit for bit."""
+    import torch
+    import paper_2503_02508_amd as qc
+    from oracle import sampler
+    from qc_testlib import make_pair, qkv_difference, qkv_rows_from_heads
+    model = replace(_net(1152, 16, 4608, *hw), weight_bits=wb)
+    w = I.make_weights(model, 77, std=0.02)
+    D, T = model.hidden, model.tokens
+    M = B * T
+    tok, cond = _cuda(I.make_tokens(B, model, 78)), _cuda(I.make_cond(B, model, 79, std=0.5))
+    qp, _ = sampler.calibrate_block(model, w, I.make_tokens(4, model, 80), I.make_cond(4, model, 81, std=0.5))
+    _, ctx = make_pair(model, w, qp, B)
+
+    def run():
+        x = tok.clone()
+        ctx.dit_block(0, qc.QC_FULL, x, cond)
+        torch.cuda.synchronize()
+        return dict(mod=ctx.workspace("mod", (512, 6 * D), torch.float32)[:B].clone(), qkv=qkv_rows_from_heads(ctx, model, B, B),
+                    c_attn=ctx.workspace("qact_attn", (M, D), torch.int8).clone(), c_ln2=ctx.workspace("qact_ln", (M, D), torch.int8).clone(),
+                    c_gelu=ctx.workspace("qact_mlp", (M, model.mlp_dim), torch.int8).clone(), x=x.reshape(M, D))
+
+    first = run()
+    for rep in range(7):
+        again = run()
+        for k in first:
+            if not torch.equal(first[k], again[k]):
+                where = qkv_difference(again[k].cpu().numpy(), first[k].cpu().numpy(), D) if k == "qkv" else "rows %s" % (
+                    torch.nonzero((first[k] != again[k]).any(dim=1)).flatten()[:64].tolist())
+                raise AssertionError("run %d: %s differs from the first run's: %s" % (rep + 2, k, where))
+    ctx.close()
+
+
 @pytest.mark.parametrize("cache,stream", [("fp32", "fp32"), ("bf16", "bf16")])
 def test_large_m_ragged_denoiser(cache, stream):
     """Full and cached denoiser calls whose large-M tiles span batch elements, against the oracle with the same storage."""
