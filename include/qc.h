@@ -154,7 +154,8 @@ int qc_quantize_weight(const float *w, int N, int K, int bits, void *qw, float *
  * qx: dev int8 [M, K]; qw: dev [N, K] int8 (weight_bits 8) or [N, K/2] packed
  * (weight_bits 4); wsum, w_scale, bias: dev [N] (bias may be NULL); y: dev fp32
  * [M, N]; acc_or_null: dev int32 [M, N] receiving the raw accumulators, or
- * NULL.  K % 16 == 0; pointers 16-byte aligned. */
+ * NULL.  K % 16 == 0; pointers 16-byte aligned.  Until the enqueued work has
+ * ended y may hold intermediate data (its last rows serve as workspace). */
 int qc_w8a8_linear(const int8_t *qx, const void *qw, const int32_t *wsum, const float *w_scale, const float *bias,
                    float x_scale, int x_zp, int M, int N, int K, int weight_bits,
                    float *y, int32_t *acc_or_null, void *stream);

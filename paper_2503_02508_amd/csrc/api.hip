@@ -414,10 +414,8 @@ int qc_w8a8_linear(const int8_t *qx, const void *qw, const int32_t *wsum, const 
   a.M = M; a.N = N; a.K = K; a.lda = K; a.w4 = weight_bits == 4;
   a.a_scale = x_scale; a.a_zp = x_zp - 128;
   a.y = y; a.ldy = N; a.acc_out = acc_or_null;
-  hipError_t err = hipSuccess;
-  if (!gemm_big_rows_pays(a) || !launch_gemm_big_rows(a, static_cast<hipStream_t>(stream), &err))
-    err = launch_gemm(a, EPI_F32, 1, static_cast<hipStream_t>(stream), QC_SITE_QKV);
-  QC_HIP(err);
+  QC_HIP(gemm_big_rows_pays(a) ? launch_gemm_big_rows(a, static_cast<hipStream_t>(stream))
+                               : launch_gemm(a, EPI_F32, 1, static_cast<hipStream_t>(stream), QC_SITE_QKV));
   return QC_OK;
 }
 

@@ -29,8 +29,6 @@
 // register loads share the counter but complete out of order with respect to each other, so counted waits gave wrong
 // fragments on some boxes, and draining the counter before every barrier cost 8 % against this version.)
 #include <algorithm>
-#include <map>
-#include <mutex>
 
 #include "gemm_i8_epilogue.h"
 
@@ -630,64 +628,42 @@ hipError_t launch_gemm_big(const GemmArgs &a, int epi, hipStream_t st, int site)
   return site == QC_SITE_FC2 ? launch_big_w<EPI_RESID, QC_SITE_FC2, false>(a, st) : launch_big_w<EPI_RESID, QC_SITE_PROJ, false>(a, st);
 }
 
-// Row-major weights (qc_w8a8_linear): the launch first writes them in fragment order, rows padded with zeros to 32 and k to 128,
-// into memory of a stream-ordered pool: no wait on either side, safe with several streams and threads, and the pool keeps at
-// most BIG_POOL_KEEP bytes between calls.
-constexpr uint64_t BIG_POOL_KEEP = 64ull << 20;
-
-static hipMemPool_t big_pool() {
-  static std::mutex mu;
-  static std::map<int, hipMemPool_t> pools;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
-  std::lock_guard<std::mutex> lock(mu);
-  const auto it = pools.find(dev);
-  if (it != pools.end()) return it->second;
-  hipMemPoolProps props{};
-  props.allocType = hipMemAllocationTypePinned;
-  props.location.type = hipMemLocationTypeDevice;
-  props.location.id = dev;
-  hipMemPool_t pool = nullptr;
-  uint64_t keep = BIG_POOL_KEEP;
-  if (hipMemPoolCreate(&pool, &props) != hipSuccess) pool = nullptr;
-  else if (hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
-    (void)hipMemPoolDestroy(pool);
-    pool = nullptr;
-  }
-  pools[dev] = pool;
-  return pool;
+// Row-major weights (qc_w8a8_linear).  The kernel wants them in fragment order and the library owns no memory for a second copy,
+// so the copy (columns padded with zeros to 32, k to 128) goes where the last rows of the result will lie; those rows
+// follow in a launch of their own from the row-major weights, which overwrites it.  (The kernel reading row-major weights
+// itself was measured: adjacent lanes of a fragment are different rows, the address unit merges only adjacent lanes, and
+// 32768 x 1152 x 4608 took 207 us instead of 151, more than the tile kernel at 8192 rows.)
+static int big_copy_rows(const GemmArgs &a) {     // rows of the result that hold the copy, plus those that make the rest whole tiles
+  const size_t bytes = (size_t)((a.N + 31) / 32 * 32) * ((a.K + BIG_BK - 1) / BIG_BK * BIG_BK) / (a.w4 ? 2 : 1) + 16;      // + alignment
+  const size_t row = (size_t)a.N * sizeof(float), n = (bytes + row - 1) / row;
+  return (size_t)a.M > n ? (int)(n + (a.M - n) % BIG_BM) : a.M;
 }
 
 bool gemm_big_rows_pays(const GemmArgs &a) {
   if (a.acc_out) return false;
-  const long long tiles = (long long)((a.M + 127) / 128) * ((a.N + 255) / 256);
-  // measured against the tile kernel (us, tile kernel / this one with its copy of the weights): 16384 x 4608 x 1152 204 / 136,
-  // 8192 x 3456 x 1152 71 / 54, 16384 x 1000 x 1168 48 / 40, 16384 x 2049 x 528 75 / 69, 3000 x 4608 x 1152 37 / 33; below 1.5e10
-  // products the copy and the pool's calls (24 us of host time) are not earned back (8192 x 2049 x 528 42 / 48), nor with half of
-  // the chip's tile slots idle (4096 x 1152 x 4608, 4-bit, 160 tiles: 50 / 51) or many columns of padding
-  return (double)a.M * a.N * a.K >= 1.55e10 && tiles >= 256 && (double)tiles * BIG_BM * BIG_BN <= 1.34 * a.M * a.N;
+  const double work = (double)a.M * a.N * a.K;
+  const double padded = (double)((a.M + BIG_BM - 1) / BIG_BM * BIG_BM) * ((a.N + BIG_BN - 1) / BIG_BN * BIG_BN) * ((a.K + BIG_BK - 1) / BIG_BK * BIG_BK);
+  // measured (us, tile kernel / copy, this kernel and the last rows): 16384 x 4608 x 1152 175 / 125, 32768 x 1152 x 4608 235 / 172,
+  // 8192 x 3456 x 1152 68 / 62, 16384 x 1152 x 1152 49 / 43, 16384 x 1000 x 1168 46 / 42.  Below 1.5e10 products the two more
+  // launches are not earned back (8192 x 2049 x 528 39 / 49), nor where the last rows are more than a sixteenth (8192 x 1152 x
+  // 4608 69 / 78, 4096 x 4608 x 1152 51 / 52, 3000 x 4608 x 1152 38 / 40) or a third of the products are padding
+  // (16384 x 2049 x 528 68 / 70)
+  return work >= 1.55e10 && padded <= 1.34 * work && big_copy_rows(a) <= a.M / 16;
 }
 
-// false: not launched (no memory, or a stream that is being captured), nothing done
-bool launch_gemm_big_rows(const GemmArgs &a, hipStream_t st, hipError_t *err) {
-  *err = hipSuccess;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
-  const hipMemPool_t pool = big_pool();
-  const int Kp = (a.K + BIG_BK - 1) / BIG_BK * BIG_BK;
-  const size_t bytes = (size_t)((a.N + 31) / 32 * 32) * (a.w4 ? Kp / 2 : Kp);
-  void *wt = nullptr;
-  if (!pool || hipMallocFromPoolAsync(&wt, bytes, pool, st) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  GemmArgs b = a;
+hipError_t launch_gemm_big_rows(const GemmArgs &a, hipStream_t st) {
+  const int m1 = a.M - big_copy_rows(a), Kp = (a.K + BIG_BK - 1) / BIG_BK * BIG_BK;
+  GemmArgs b = a, c = a;
+  float *const y1 = a.y + (size_t)m1 * a.ldy;
+  void *const wt = reinterpret_cast<void *>((reinterpret_cast<uintptr_t>(y1) + 15) & ~uintptr_t(15));
+  b.M = m1;
   b.Wt = wt;
-  *err = launch_tile_weight(a.W, wt, a.N, a.K, a.w4 ? 4 : 8, Kp, st);
-  if (*err == hipSuccess) *err = a.w4 ? launch_big_as<EPI_F32, QC_SITE_QKV, true, false>(b, st) : launch_big_as<EPI_F32, QC_SITE_QKV, false, false>(b, st);
-  const hipError_t fe = hipFreeAsync(wt, st);
-  if (*err == hipSuccess) *err = fe;
-  return true;
+  c.M = a.M - m1;
+  c.A = a.A + (size_t)m1 * a.lda;
+  c.y = y1;
+  hipError_t e = launch_tile_weight(a.W, wt, a.N, a.K, a.w4 ? 4 : 8, Kp, st);
+  if (e == hipSuccess) e = a.w4 ? launch_big_as<EPI_F32, QC_SITE_QKV, true, false>(b, st) : launch_big_as<EPI_F32, QC_SITE_QKV, false, false>(b, st);
+  return e == hipSuccess ? launch_gemm(c, EPI_F32, 1, st, QC_SITE_QKV) : e;
 }
 
 #undef QC_WAIT_VM_FOR4

@@ -144,9 +144,9 @@ hipError_t launch_gemm(const GemmArgs &a, int epi, int nz, hipStream_t st, int s
 // the large-M kernel (gemm_i8_big.hip): whether a launch is one of its, and the launch
 bool gemm_big_pays(const GemmArgs &a, int epi, int nz);
 hipError_t launch_gemm_big(const GemmArgs &a, int epi, hipStream_t st, int site);
-// the same with float32 results and row-major weights: whether it pays, and the launch (false: nothing was launched)
+// the same with float32 results (rows of N, nothing between them) and row-major weights: whether it pays, and the launches
 bool gemm_big_rows_pays(const GemmArgs &a);
-bool launch_gemm_big_rows(const GemmArgs &a, hipStream_t st, hipError_t *err);
+hipError_t launch_gemm_big_rows(const GemmArgs &a, hipStream_t st);
 // the split-K kernel of small launches (gemm_i8_split.hip): whether a launch is one of them, and the launch
 bool gemm_split_pays(const GemmArgs &a, int epi, int nz);
 hipError_t launch_gemm_split(const GemmArgs &a, int epi, hipStream_t st);

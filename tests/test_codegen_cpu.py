@@ -106,3 +106,10 @@ def test_no_store_loses_its_data_to_the_next_instruction(tmp_path):
             found = _overwritten_stores(body.splitlines())
             assert not found, "%s: %d stores, the first: %s" % (name, len(found), found[0])
     assert kernels > 50
+
+
+def test_the_library_imports_no_allocator():
+    """include/qc.h: the library never allocates device memory."""
+    names = subprocess.run(["nm", "-D", "--undefined-only", os.path.join(PKG, "libqc.so")], check=True, stdout=subprocess.PIPE, text=True).stdout
+    assert "hipLaunchKernel" in names
+    assert not re.findall(r"\bhip\w*(?:Malloc|MemPool|MemCreate|MemAlloc)\w*", names)

@@ -118,6 +118,25 @@ def test_w8a8_linear_large(qc, bits, M, N, K):
     assert np.array_equal(acc[rows].cpu().numpy().astype(np.int64), OQ.int_matmul(qx[rows], lin.q))
 
 
+@pytest.mark.parametrize("M,N,K,bits,shift", [
+    (16385, 1155, 848, 8, 1),       # the last rows hold the copy of the weights: one row past whole tiles, results 4 bytes off
+    (16512, 1000, 1168, 4, 3),      # whole tiles; columns and k of the copy padded
+    (131072, 256, 1536, 8, 0)])     # 512 rows hold the copy
+def test_w8a8_linear_large_leaves_what_is_around_the_result(qc, bits, M, N, K, shift):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    qx = torch.randint(-128, 128, (M, K), dtype=torch.int8, device="cuda", generator=g)
+    qw = torch.randint(-128, 128, (N, K * bits // 8), dtype=torch.int8, device="cuda", generator=g)
+    wsum = torch.randint(-500, 500, (N,), dtype=torch.int32, device="cuda", generator=g)
+    scale, bias = torch.rand(N, device="cuda", generator=g), torch.rand(N, device="cuda", generator=g)
+    room = torch.full((64 + M * N + 64,), 7.0, device="cuda")
+    y, want = room[60 + shift:60 + shift + M * N].view(M, N), torch.empty((M, N), device="cuda")
+    qc.qc_w8a8_linear(qx, qw, wsum, scale, bias, 0.0213, 117, bits, y)
+    qc.qc_w8a8_linear(qx, qw, wsum, scale, bias, 0.0213, 117, bits, want, torch.empty((M, N), dtype=torch.int32, device="cuda"))
+    assert torch.equal(y, want)
+    assert bool((room[:60 + shift] == 7.0).all()) and bool((room[60 + shift + M * N:] == 7.0).all())
+
+
 def test_w8a8_linear_extreme_codes_and_no_bias(qc):
     import torch
     M, N, K = 40, 70, 4608
