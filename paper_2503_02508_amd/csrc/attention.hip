@@ -225,15 +225,16 @@ __device__ __forceinline__ void split_pairs(v4f v, v2u &hi, v2u &lo) {
 //
 // TAIL: the last feature chunk holds at most 8 real features (d = 72: 64 + 8).  Its three products then share ONE
 // instruction: of the 32 k positions of the K operand, 0..7 are the features' hi halves, 8..15 their lo halves, 16..23 the
-// hi halves again, and the query operand has hi, hi, lo there (7 instructions per key block instead of 9 at d = 72).  In
-// that case the last V^T block has free rows as well: row d is set to ones, so that the sum of the probabilities falls out
-// of the P V product (row d of O^T) instead of costing an addition per probability.
+// hi halves again, and the query operand has hi, hi, lo there (7 instructions per key block instead of 9 at d = 72).
 //
 // What bounds it: issue slots of the vector pipe, which an MFMA shares for about half of its 16 cycles.  Per tile of 64 keys
-// a wavefront issues 116 MFMAs (QB = 2, d = 72) and about 5 vector instructions per probability (exponential, subtraction,
-// half a maximum, one and a half for the split), so the vector work is what was cut: the running max is only raised when a
-// tile exceeds it by more than MAX_SLACK (a probability may reach 2^MAX_SLACK; hi + lo keep their relative precision), which
-// leaves one test per tile instead of two shuffles, an exponential and the rescaling of every output register.
+// a wavefront issues 116 MFMAs (QB = 2, d = 72) and about 6 vector instructions per probability (exponential, subtraction,
+// half a maximum, one and a half for the split, the sum), so the vector work is what was cut: the running max is only raised
+// when a tile exceeds it by more than MAX_SLACK (a probability may reach 2^MAX_SLACK; hi + lo keep their relative precision),
+// which leaves one test per tile instead of two shuffles, an exponential and the rescaling of every output register.
+// The sum of the probabilities stays a float32 addition each: a row of ones in V^T gives it for free (2 - 4 % of a launch), but
+// from the 22 bits of the halves and with the matrix cores' accumulation, 1.2 (256 keys) to 1.6 (4096) times as far from
+// float64, and the outputs of a sharp softmax over 4096 keys 1.5 times.
 template <int NCH, int NEB, int QB, bool TAIL>
 __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__restrict__ Qp, const float *__restrict__ Kp,
                                                             const float *__restrict__ Vt, int BH, int T, int Tp, int H, int hd, int DPv,
@@ -271,11 +272,10 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   const long long vt_base = (long long)bh * DPv * Tp;
   const int kchunks = 64 * (hd / 4);            // 16-byte chunks of one K tile
 
-  // what no tile writes: the feature padding of the K rows, and the V^T rows beyond d (zeros; row d is ones with TAIL)
+  // what no tile writes: the feature padding of the K rows and the V^T rows beyond d (zeros)
   for (int i = tid; i < (int)(sizeof(Ksh) / 16); i += NT) ((v8h *)Ksh)[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
   for (int i = tid; i < (16 * NEB - hd) * VROW / 8; i += NT) {
-    const _Float16 one = (TAIL && i < VROW / 8) ? (_Float16)1.0f : (_Float16)0.0f;
-    ((v8h *)(Vsh[0] + hd * VROW))[i] = (v8h){one, one, one, one, one, one, one, one};
+    ((v8h *)(Vsh[0] + hd * VROW))[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
     ((v8h *)(Vsh[1] + hd * VROW))[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
   }
 
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
         const float m_new = fmaxf(m_run[j], mx[j]);
         const float alpha = __builtin_amdgcn_exp2f(m_run[j] - m_new);
         m_run[j] = m_new;
-        if (!TAIL) l_run[j] *= alpha;
+        l_run[j] *= alpha;
 #pragma unroll
         for (int e = 0; e < NEB; ++e) o[j][e] *= alpha;
       }
@@ -499,10 +499,8 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
         for (int w = 0; w < 4; ++w) {         // word w of the operand: keys (kt = 2 a + w / 2, r = 2 (w % 2) .. + 1)
           const int kt = 2 * a + (w >> 1), r = 2 * (w & 1);
           const float p0 = __builtin_amdgcn_exp2f(s[j][kt][r] - m_run[j]), p1 = __builtin_amdgcn_exp2f(s[j][kt][r + 1] - m_run[j]);
-          if (!TAIL) {
-            l_run[j] += p0;
-            l_run[j] += p1;
-          }
+          l_run[j] += p0;
+          l_run[j] += p1;
           unsigned h2, l2;
           split_pair(p0, p1, h2, l2);
           hw[w] = h2;
@@ -540,29 +538,23 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   int *fix_cnt = &fix_cnt_s;
   int *fix_ent = (int *)(stage + NQ * SRB);       // [FIX_CAP][2]: query within the workgroup, feature
   __syncthreads();                                // every wavefront is past its last K / V^T fragment
-  // |v / s - rint(v / s)| within tol of 1/2: 1.2e-5 steps + 4e-7 of the code's size at 256 keys is about ten times the
-  // kernel's mean error there (its differing codes without this path, a few 1e-6 of all, put the mean error near 1e-6
-  // steps)
+  // |v / s - rint(v / s)| within tol of 1/2: 1.2e-5 steps + 4e-7 of the code's size at 256 keys.  Against float64 on the Q | K | V of
+  // a DiT-XL/2 block (weights of standard deviation 0.02) the fast path is off by 3.9e-6 / 7.3e-6 / 1.4e-5 steps in the mean at
+  // 256 / 1024 / 4096 keys and by at most 1.02 / 0.59 / 0.34 of the window.  The window is no bound: an error beyond it turns a
+  // code only where the value lies between the two, and with weights of 0.05, whose scores are six times as large, the
+  // largest error at 256 keys was 7.6 windows (mean 0.3) and still no code of a million differed.
   // The quotient of Eq. 1 is formed as v * (1 / s) here: that is within 2.5e-7 |v / s| of the correctly rounded
   // quotient, so the two can only round to different integers inside the window below (whose relative part is widened
   // by that much), where the float64 path, which divides, decides.
-  // Growth of the bound with the number of keys: the measured largest error doubles from 256 to 1024 keys, a three-quarter
-  // power keeps the same margin at both.
-  const float tk = fmaxf(1.0f, (float)T * (1.0f / 256.0f)), tol_k = __builtin_sqrtf(tk * __builtin_sqrtf(tk));
+  const float tol_k = fmaxf(1.0f, (float)T * (1.0f / 256.0f));      // the sums grow with the number of keys and the bound with them
   const float tol_0 = 1.2e-5f * tol_k, tol_q = 4e-7f * tol_k + 2.5e-7f;
   const float doubt_at = 0.5f - tol_0;
   const float inv_qs = 1.0f / qs, zu = qz + 128.0f;
 #pragma unroll
   for (int j = 0; j < QB; ++j) {
-    float l;
-    if constexpr (TAIL) {
-      // row d of O^T: block d / 16, row d % 16 = 4 g + r with r = 0 (d is a multiple of 4)
-      l = __shfl(o[j][NEB - 1][0], ((hd & 15) >> 2) * 16 + ql, 64);
-    } else {
-      l = l_run[j];
-      l += __shfl_xor(l, 16, 64);
-      l += __shfl_xor(l, 32, 64);
-    }
+    float l = l_run[j];
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
     const float k = (1.0f / l) * inv_qs;            // value and quotient of Eq. 1 in one multiplication per output
     const int qloc = wave * (16 * QB) + j * 16 + ql;
     if (g == 0) m_s[qloc] = m_run[j];
@@ -696,9 +688,9 @@ hipError_t launch_attention_f16(const float *q32, const float *k32, const float 
   if (hd > 80 || hd % 4) return hipErrorInvalidValue;      // K prefetch registers are sized for d <= 80
   const float q_mul = 1.4426950408889634f / std::sqrt((float)hd);     // log2(e) / sqrt(d)
   // Two query blocks per wavefront (128 queries per workgroup) when that makes more workgroups than compute units, else one.
-  // Measured, one / two (16 heads of 72; us): 128 x 256 tokens 290 / 235 (281 before this form of the kernel), 16 x 1024:
-  // 422 / 328 (420), 16 x 256: 39.2 / 30.9, 8 x 256: 20.8 / 21.8 (26.2), 3 x 425: 29.5 / 31.2, 1 x 256: 14.4 / 18.8 (17.5);
-  // workgroups of eight wavefronts came out within 2 % at 1024 tokens and behind elsewhere.
+  // Measured, one / two (16 heads of 72; us): 128 x 256 tokens 240 / 185, 16 x 1024: 361 / 287, 2 x 4096: 854 / 731, 16 x 256:
+  // 34.5 / 27.5, 10 x 425: 57.8 / 55.7, 8 x 256: 18.8 / 19.0, 3 x 425: 28.5 / 32.0, 1 x 256: 13.3 / 17.0; workgroups of eight
+  // wavefronts came out within 2 % at 1024 tokens and behind elsewhere.
   const int qb = B * H * ((T + 127) / 128) <= 256 ? 1 : 2;
   dim3 grid((B * H + 7) / 8 * 8, (T + 64 * qb - 1) / (64 * qb));
 #define QC_ATT(NCH, NEB, TAIL)                                                                                              \
