@@ -305,13 +305,9 @@ static hipError_t launch_cfg(const GemmArgs &a, int nz, hipStream_t st) {
   constexpr int smem_loop = 2 * (BM + BN) * (BK + 16);
   constexpr int smem_epi = BN * 12 + BM * (BN + 16) + 16 + GELU_FIX_CAP * 16;
   constexpr int smem = smem_loop > smem_epi ? smem_loop : smem_epi;
-  static bool attr_set = false;
+  static std::atomic<unsigned long long> lds{0};
   auto kern = gemm_i8_kernel<BM, BN, WM, WN, EPI, TAG, W4, PF, BK, RBF>;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  if (const hipError_t e = allow_lds((const void *)kern, smem, lds)) return e;
   const int ncover = a.sel_D ? 2 * a.sel_D : a.N;
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (ncover + BN - 1) / BN;
   const int best_xm = xcd_rows(tiles_m, tiles_n, (double)a.M * a.K, (double)ncover * a.K * (W4 ? 0.5 : 1.0));

@@ -587,8 +587,8 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   constexpr int smem = BIG_CST * 4 + (smem_epi > BIG_SMEM_LOOP ? smem_epi : BIG_SMEM_LOOP);
   static_assert(2 * smem <= 160 * 1024, "two workgroups per compute unit");
   auto kern = gemm_i8_big_kernel<EPI, TAG, W4, RBF, RAG>;
-  static const hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-  if (attr != hipSuccess) return attr;
+  static std::atomic<unsigned long long> lds{0};
+  if (const hipError_t e = allow_lds((const void *)kern, smem, lds)) return e;
   const int tiles_n = (a.N + BIG_BN - 1) / BIG_BN, tiles = ((a.M + BIG_BM - 1) / BIG_BM) * tiles_n;
   GemmArgs b = a;
   // tile rows per group: every column tile of a group resident on its XCD at once (64 workgroup slots), at most 4

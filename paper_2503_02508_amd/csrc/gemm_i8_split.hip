@@ -229,13 +229,9 @@ static hipError_t launch_split(const GemmArgs &a, hipStream_t st) {
   constexpr int s_epi = EPI == EPI_GELU_Q ? BN * 12 + BM * (BN + 16) + 16 + GELU_FIX_CAP * 16 : 0;
   constexpr int smem = s_loop > s_red ? (s_loop > s_epi ? s_loop : s_epi) : (s_red > s_epi ? s_red : s_epi);
   static_assert(smem <= 160 * 1024, "LDS of a compute unit");
-  static bool attr_set = false;
+  static std::atomic<unsigned long long> lds{0};
   auto kern = gemm_i8_split_kernel<TM, TN, NW, EPI, W4, WROW, RBF>;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  if (const hipError_t e = allow_lds((const void *)kern, smem, lds)) return e;
   GemmArgs b = a;
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
   b.xcd_m = xcd_rows(tiles_m, tiles_n, (double)a.M * a.K, (double)a.N * a.K * (W4 ? 0.5 : 1.0));

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <atomic>
 #include <vector>
 #include "qc.h"
 
@@ -26,6 +27,19 @@ struct LinearQ {
 };
 
 void set_error(const char *fmt, ...);
+
+// Lets a kernel use `bytes` of dynamic LDS on the current device (the attribute is a device's own).  done: one per kernel, a bit
+// per device that was asked already.
+inline hipError_t allow_lds(const void *kern, int bytes, std::atomic<unsigned long long> &done) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const unsigned long long bit = dev < 64 ? 1ull << dev : 0ull;
+  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  return e;
+}
 
 // ---- epilogues of the int8 GEMM
 enum Epi { EPI_F32 = 0, EPI_GELU_Q = 1, EPI_RESID = 2, EPI_QKV = 3 };

@@ -466,9 +466,8 @@ static hipError_t launch_small_linear_as(const float *x, int ldx, int t_first, i
                                          int B, int N, int K, int act_in, int act_out, hipStream_t st) {
   const size_t smem = (size_t)R * K * sizeof(double);
   if (smem > 64 * 1024) {                         // more than a kernel may use without asking: ask once, for the widest input
-    static const hipError_t e = hipFuncSetAttribute((const void *)small_linear_kernel<R, NIT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                    R * 256 * NIT * (int)sizeof(double));
-    if (e != hipSuccess) return e;
+    static std::atomic<unsigned long long> lds{0};
+    if (const hipError_t e = allow_lds((const void *)small_linear_kernel<R, NIT>, R * 256 * NIT * (int)sizeof(double), lds)) return e;
   }
   hipLaunchKernelGGL((small_linear_kernel<R, NIT>), dim3((N + 15) / 16, (B + R - 1) / R), dim3(256), smem, st, x, ldx, t_first, t_step, W, b,
                      y, ldy, B, N, K, act_in, act_out);
