@@ -1054,6 +1054,7 @@ int qc_calibrate_minmax(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, co
   std::vector<int> got(nslots * 2);
   QC_HIP(hipMemcpyAsync(got.data(), ctx->cal_slots, got.size() * sizeof(int), hipMemcpyDeviceToHost, st));
   QC_HIP(hipStreamSynchronize(st));
+  std::vector<QParam> qp(nslots);            // installed together, or not at all
   for (size_t i = 0; i < nslots; ++i) {
     // Eq. 2-3 in fp32: range widened to contain 0, s = (u - l) / 255, z = round(-l / s)
     float lo = std::fmin(ord2f(got[2 * i]), 0.0f), hi = std::fmax(ord2f(got[2 * i + 1]), 0.0f);
@@ -1066,10 +1067,11 @@ int qc_calibrate_minmax(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, co
     }
     rc = check_qparam(s, z);
     if (rc) return rc;
-    ctx->host_qp[i] = QParam{s, z - 128};
-    ctx->qp_set[i] = 1;
+    qp[i] = QParam{s, z - 128};
   }
-  QC_HIP(hipMemcpy(ctx->dev_qp, ctx->host_qp.data(), nslots * sizeof(QParam), hipMemcpyHostToDevice));
+  QC_HIP(hipMemcpy(ctx->dev_qp, qp.data(), nslots * sizeof(QParam), hipMemcpyHostToDevice));
+  ctx->host_qp = qp;
+  ctx->qp_set.assign(nslots, 1);
   return QC_OK;
 }
 

@@ -468,6 +468,24 @@ def test_bf16_cache_store_and_reuse_calls():
     ctx.close()
 
 
+def test_a_refused_calibration_leaves_the_parameters_alone():
+    """The range of one site is infinite: none of the others is installed."""
+    import torch
+    import paper_2503_02508_amd as qc
+    model = I.shrink(TINY, 1)
+    w = I.make_weights(model, 5)
+    w["blocks"][0]["fc1_b"][0] = np.inf                       # the input of fc2
+    ctx = qc.Context(model, 1, 1)
+    ctx.load_weights(w, keep_fp32=True)
+    for site in range(5):
+        ctx.set_act_qparams(0, site, 0.5 + site, 100 + site)
+    with pytest.raises(qc.QCError) as e:
+        ctx.calibrate(_cuda(I.make_latents(1, model, 6)), [500], [3])
+    assert e.value.code == -4
+    assert [ctx.get_act_qparams(0, site) for site in range(5)] == [(0.5 + site, 100 + site) for site in range(5)]
+    ctx.close()
+
+
 def test_calibration_matches_oracle():
     """qc_calibrate_minmax (fp32 un-quantised forward on the device) against the oracle's calibration."""
     import torch
