@@ -242,7 +242,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
               *(v4f *)(stage + nl * VR + vt_pos(ml)) = v;
             }
           }
-          if (TM * TN > 4) __builtin_amdgcn_sched_barrier(0);      // large register tiles: keep the live ranges of a block short
         }
       }
       __syncthreads();
@@ -313,75 +312,64 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
   }
 
   if (EPI == EPI_RESID) {
-    // read-modify-write of the residual stream: the loads of a batch of column blocks are all issued
-    // before the first use, so the epilogue pays one memory round trip per batch instead of one per
-    // register group; a batch is the whole tile when its values fit in registers beside the accumulators
-    constexpr int JB = TM * TN <= 4 ? TN : 1, IB = TM * TN <= 4 ? TM : 1;
+    // read-modify-write of the residual stream: every load of the tile is issued before the first use, so the epilogue pays
+    // one memory round trip
     const bool uniform_batch = (p.rows_per_batch % BM) == 0;
     const int b_uniform = m0 / p.rows_per_batch;
     const int x_bf16 = RBF ? p.x_bf16 : 0, cache_bf16 = RBF ? p.cache_bf16 : 0;
     const bool interior = uniform_batch && m0 + BM <= p.M && n0 + BN <= p.N;
+    float xv[TN][TM][16], gv[TN];
+    double scv[TN], bsv[TN];
+    int zwv[TN];
 #pragma unroll
-    for (int j0 = 0; j0 < TN; j0 += JB)
+    for (int j = 0; j < TN; ++j) {
+      const int n = min(n0 + wn0 + j * 32 + (lane & 31), p.N - 1);
 #pragma unroll
-      for (int i0 = 0; i0 < TM; i0 += IB) {
-        float xv[JB][IB][16], gv[JB];
-        double scv[JB], bsv[JB];
-        int zwv[JB];
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-          const int n = min(n0 + wn0 + (j0 + jj) * 32 + (lane & 31), p.N - 1);
-#pragma unroll
-          for (int ii = 0; ii < IB; ++ii)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int m = min(m0 + wm0 + (i0 + ii) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), p.M - 1);
-              xv[jj][ii][r] = stream_load(p.x, (long long)m * p.N + n, x_bf16);
-            }
-          scv[jj] = (double)a_s * (double)w_scale[n];
-          zwv[jj] = a_z * wsum[n];
-          bsv[jj] = bias ? (double)bias[n] : 0.0;
-          gv[jj] = p.gate[(long long)b_uniform * p.ld_gate + n];
+        for (int r = 0; r < 16; ++r) {
+          const int m = min(m0 + wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), p.M - 1);
+          xv[j][i][r] = stream_load(p.x, (long long)m * p.N + n, x_bf16);
         }
+      scv[j] = (double)a_s * (double)w_scale[n];
+      zwv[j] = a_z * wsum[n];
+      bsv[j] = bias ? (double)bias[n] : 0.0;
+      gv[j] = p.gate[(long long)b_uniform * p.ld_gate + n];
+    }
 #pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-          const int j = j0 + jj;
-          const int n = n0 + wn0 + j * 32 + (lane & 31);
-          if (interior) {
-            // interior tile inside one batch element: no bounds checks, one gate per column
+    for (int j = 0; j < TN; ++j) {
+      const int n = n0 + wn0 + j * 32 + (lane & 31);
+      if (interior) {
+        // interior tile inside one batch element: no bounds checks, one gate per column
 #pragma unroll
-            for (int ii = 0; ii < IB; ++ii)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const int i = i0 + ii;
-                const float v = dequant_f32(scv[jj], acc[i][j][r] - zwv[jj], bsv[jj]);
-                // 32-bit offset inside the tile's rows from one 64-bit base per column
-                const long long ob = (long long)m0 * p.N + n;
-                const unsigned o = (unsigned)(wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * (unsigned)p.N;
-                if (cache_bf16) ((unsigned short *)p.cache_out + ob)[o] = bf16_bits(v);
-                else ((float *)p.cache_out + ob)[o] = v;
-                stream_store(p.x, ob + o, fmaf(gv[jj], v, xv[jj][ii][r]), x_bf16);
-              }
-          } else {
-            if (n >= p.N) continue;
-#pragma unroll
-            for (int ii = 0; ii < IB; ++ii)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const int i = i0 + ii;
-                const int m = m0 + wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-                if (m >= p.M) continue;
-                const float v = dequant_f32(scv[jj], acc[i][j][r] - zwv[jj], bsv[jj]);
-                const long long o = (long long)m * p.N + n;
-                if (cache_bf16) ((unsigned short *)p.cache_out)[o] = bf16_bits(v);
-                else ((float *)p.cache_out)[o] = v;
-                const float g = p.gate[(long long)(m / p.rows_per_batch) * p.ld_gate + n];
-                stream_store(p.x, o, fmaf(g, v, xv[jj][ii][r]), x_bf16);
-              }
+          for (int r = 0; r < 16; ++r) {
+            const float v = dequant_f32(scv[j], acc[i][j][r] - zwv[j], bsv[j]);
+            // 32-bit offset inside the tile's rows from one 64-bit base per column
+            const long long ob = (long long)m0 * p.N + n;
+            const unsigned o = (unsigned)(wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * (unsigned)p.N;
+            if (cache_bf16) ((unsigned short *)p.cache_out + ob)[o] = bf16_bits(v);
+            else ((float *)p.cache_out + ob)[o] = v;
+            stream_store(p.x, ob + o, fmaf(gv[j], v, xv[j][i][r]), x_bf16);
           }
-        }
-        if (TM * TN > 4) __builtin_amdgcn_sched_barrier(0);      // large register tiles: one batch's values live at a time
+      } else {
+        if (n >= p.N) continue;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int m = m0 + wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+            if (m >= p.M) continue;
+            const float v = dequant_f32(scv[j], acc[i][j][r] - zwv[j], bsv[j]);
+            const long long o = (long long)m * p.N + n;
+            if (cache_bf16) ((unsigned short *)p.cache_out)[o] = bf16_bits(v);
+            else ((float *)p.cache_out)[o] = v;
+            const float g = p.gate[(long long)(m / p.rows_per_batch) * p.ld_gate + n];
+            stream_store(p.x, o, fmaf(g, v, xv[j][i][r]), x_bf16);
+          }
       }
+    }
     return;
   }
 
