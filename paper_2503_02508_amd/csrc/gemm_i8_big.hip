@@ -380,16 +380,35 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
     a_z = p.a_qp[0].z;
   }
 
-  // epilogue constants of column n0 + tid, in flight while the prologue's operand loads are issued
-  float c_sc = 0.0f, c_bs = 0.0f, c_g0 = 0.0f, c_g1 = 0.0f;
-  if (n0 + tid < p.N) {
-    const int n = n0 + tid;
-    c_sc = p.w_scale[n];
-    if (p.bias) c_bs = p.bias[n];
-    if (EPI == EPI_RESID) {
-      const int b = m0 / p.rows_per_batch;
-      c_g0 = p.gate[(size_t)b * p.ld_gate + n];
-      if (RAG && (b + 1) * p.rows_per_batch < min(m0 + BM, p.M)) c_g1 = p.gate[(size_t)(b + 1) * p.ld_gate + n];
+  // Epilogue constants of column n0 + tid and the zero-point sums of this wavefront's columns (lane: 4 (lane / 16) .. + 3 of
+  // every block): requested first, so that the prologue's wait for the first slab covers them.  They are loads of inline assembly
+  // like all others: for loads that it sees the compiler places waits of its own, which count only those and so either stood in
+  // front of the first operand load (fc1, packed weights) or drained the operand loads behind the first barrier (the others).
+  // 16384 x 4608 x 1152 1.2 % faster, sampling runs 0.1 - 0.4 %.
+  // Columns past N re-read the last one (never stored).
+  const auto load_const = [](auto &r, const void *base, unsigned off) {
+    if constexpr (sizeof(r) == 16) asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(r) : "v"(off), "s"(base) : "memory");
+    else asm volatile("global_load_dword %0, %1, %2" : "=v"(r) : "v"(off), "s"(base) : "memory");
+  };
+  float c_sc, c_bs, c_g0 = 0.0f, c_g1 = 0.0f;
+  const unsigned ccol = (unsigned)min(n0 + tid, p.N - 1) * 4u;
+  load_const(c_sc, p.w_scale, ccol);
+  load_const(c_bs, p.bias ? p.bias : p.w_scale, ccol);        // without a bias it is zeroed below
+  if constexpr (EPI == EPI_RESID) {
+    const int b = m0 / p.rows_per_batch, b1 = RAG && (b + 1) * p.rows_per_batch < min(m0 + BM, p.M) ? b + 1 : b;
+    load_const(c_g0, p.gate + (size_t)b * p.ld_gate, ccol);
+    if constexpr (RAG) load_const(c_g1, p.gate + (size_t)b1 * p.ld_gate, ccol);
+  }
+  v4i ws[TN];
+  int w1[EPI == EPI_F32 ? TN * 4 : 1];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int n = n0 + wn0 + j * 16 + (lane >> 4) * 4;
+    if constexpr (EPI == EPI_F32) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) load_const(w1[j * 4 + e], p.wsum, (unsigned)min(n + e, p.N - 1) * 4u);
+    } else {
+      load_const(ws[j], p.wsum, (unsigned)min(n, p.N - 4) * 4u);
     }
   }
 
@@ -439,26 +458,6 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
     }
   };
 
-  // the accumulators start at minus the zero-point term a_z * wsum[n] of their column, so the epilogue finds acc - a_z *
-  // wsum[n] ready; the loads complete under the prologue's wait for the first slabs
-  BigAcc acc;
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = n0 + wn0 + j * 16 + (lane >> 4) * 4;
-    v4i ws;
-    if constexpr (EPI == EPI_F32) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) ws[e] = p.wsum[min(n + e, p.N - 1)];
-    } else {
-      ws = *(const v4i *)(p.wsum + min(n, p.N - 4));
-    }
-    v4i c0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c0[e] = -(a_z * ws[e]);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) acc[i][j] = c0;
-  }
-
   unsigned fbase[2];                              // LDS position of this lane's chunk of group g in row block 0
 #pragma unroll
   for (int g = 0; g < 2; ++g) fbase[g] = (lane & 15) * BK + (((g * 4 + (lane >> 4)) ^ ((lane >> 1) & 7)) * 16);
@@ -478,10 +477,32 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
     for (int j = 0; j < TN; ++j) load_w(g, g, j);
   QC_SB;
   QC_WAIT_VM_FOR4(12, fa[1][0], fa[1][1], fa[1][2], fa[1][3]);
+  asm volatile("" : "+v"(c_sc), "+v"(c_bs));                  // (valid with the same wait)
+  if constexpr (EPI == EPI_RESID) asm volatile("" : "+v"(c_g0));
+  if constexpr (EPI == EPI_RESID && RAG) asm volatile("" : "+v"(c_g1));
+  if constexpr (EPI == EPI_F32) {
+#pragma unroll
+    for (int i = 0; i < TN * 4; ++i) {
+      asm volatile("" : "+v"(w1[i]));
+      ws[i >> 2][i & 3] = w1[i];
+    }
+  } else {
+    asm volatile("" : "+v"(ws[0]), "+v"(ws[1]), "+v"(ws[2]), "+v"(ws[3]));
+  }
+  // the accumulators start at minus the zero-point term a_z * wsum[n] of their column, so the epilogue finds acc - a_z * wsum[n] ready
+  BigAcc acc;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    v4i c0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c0[e] = -(a_z * ws[j][e]);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc[i][j] = c0;
+  }
 #pragma unroll
   for (int i = 0; i < PA; ++i) write_a(fa[1][i], 0, i);
   cst[tid] = c_sc;
-  cst[BN + tid] = c_bs;
+  cst[BN + tid] = p.bias ? c_bs : 0.0f;
   if (EPI == EPI_RESID) {
     cst[2 * BN + tid] = c_g0;
     if (RAG) cst[3 * BN + tid] = c_g1;
