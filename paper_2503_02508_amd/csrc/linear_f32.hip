@@ -56,6 +56,7 @@ __global__ __launch_bounds__(256, 2) void linear_f32_kernel(const float *__restr
   const unsigned back = (unsigned)max((ns - 1) * BK + lc * 4 + 4 - K, 0) * 4;      // chunks of the last slab beyond K re-read its end
   const float *xb = x + (size_t)m0 * K, *wb = W + (size_t)n0 * K;
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) float *)&slabs[0][0][0] + wave * 1024;
+  // (m0 is a reserved register, which a clobber list cannot name: nothing else in this kernel uses it, tests/test_codegen_cpu.py)
   auto load = [&](int s, int b, int op, int i) {       // slabs past the end re-read the last one (never used)
     const unsigned off = (op ? wo[i] : xo[i]) - (s >= ns - 1 ? back : 0u);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds0 + ((b * 2 + op) * R + i * RP) * BK * 4), "v"(off),
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(256, 2) void linear_f32_kernel(const float *__restr
 }
 
 hipError_t launch_linear_f32(const float *x, const float *W, const float *b, float *y, int M, int N, int K, int gelu, hipStream_t st) {
-  if (K % 4 || K < 4) return hipErrorInvalidValue;
+  if (K % 4 || K < 4) return hipErrorInvalidValue;           // chunks of 16 bytes; the widths of a model are multiples of 16
   // Whole tiles per compute unit, in blocks of 16 x 16 per SIMD.  TB = 2 moves half the bytes per product, which is worth 16 % of a
   // block's time (K = 1152: 5.2 against 6.2 us); TB = 1 divides the work among the compute units more evenly.
   const long long t2 = (long long)((M + 63) / 64) * ((N + 63) / 64), t1 = (long long)((M + 31) / 32) * ((N + 31) / 32);

@@ -103,6 +103,8 @@ def test_no_store_loses_its_data_to_the_next_instruction(tmp_path):
         for part in re.split(r"^(?=<_Z\w+>:)", text, flags=re.M)[1:]:
             name, _, body = part.partition("\n")
             kernels += "s_endpgm" in body
+            if "linear_f32_kernel" in name:        # its loads to LDS write m0 in inline assembly, unknown to the compiler
+                assert all(l.strip().startswith("s_mov_b32 m0,") for l in body.splitlines() if re.search(r"\bm0\b", l))
             found = _overwritten_stores(body.splitlines())
             assert not found, "%s: %d stores, the first: %s" % (name, len(found), found[0])
     assert kernels > 50

@@ -102,8 +102,8 @@ def test_w8a8_linear_accumulators_bit_exact(qc, bits, M, N, K):
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(16385, 1155, 848), (4001, 3460, 1168), (8192, 2048, 1024)])
 def test_w8a8_linear_large(qc, bits, M, N, K):
-    """The large-M kernel (taken when no accumulators are asked for): partial tiles in every direction, and whole ones, equal to
-    the tile kernel bit for bit and to exact sums of sampled rows."""
+    """Large products, with the large-M kernel where its rule takes them (the first and the last, when no accumulators are asked
+    for): partial tiles in every direction, and whole ones, equal to the tile kernel bit for bit and to exact sums of sampled rows."""
     import torch
     rng = np.random.default_rng(M + N + K + bits)
     qx = rng.integers(-128, 128, size=(M, K), dtype=np.int8)

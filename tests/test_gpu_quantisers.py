@@ -153,8 +153,8 @@ def test_each_fused_quantiser_alone(name, model, B, wb, std):
 def test_large_m_linears_every_tile_at_32768_rows(wb):
     """The four linears of a DiT-XL/2 block at M = 32768 rows (128 latents, the launch shape of the guided workload):
     the large-M GEMM kernel streams activations and weights with hand-counted waits, so a wait that is one load short
-    shows up as a few wrong 32-row fragments somewhere in the 4608 tiles and not in a small product.  Four rows of
-    every 128-row tile (one per 32-row fragment) are recomputed by the oracle from the device's own upstream codes:
+    shows up as a few wrong 16-row fragments somewhere in the 4608 tiles and not in a small product.  Eight rows of
+    every 128-row tile (one per 16-row fragment) are recomputed by the oracle from the device's own upstream codes:
     Q | K | V, projection output, GELU codes and fc2 output must equal it exactly; and a second run from the same
     input must reproduce every stored tensor bit for bit."""
     import torch
@@ -169,7 +169,7 @@ def test_large_m_linears_every_tile_at_32768_rows(wb):
     qp, _ = sampler.calibrate_block(model, w, I.make_tokens(4, model, seed + 3), I.make_cond(4, model, seed + 4, std=0.5))
     lin, ctx = make_pair(model, w, qp, B)
     M = B * T
-    rows = (np.arange(M // 128)[:, None] * 128 + np.array([5, 44, 83, 122])[None]).reshape(-1)
+    rows = (np.arange(M // 128)[:, None] * 128 + np.array([5, 28, 44, 51, 67, 83, 106, 122])[None]).reshape(-1)
     rows_t = torch.from_numpy(rows).cuda()
     L = lin.lin[0]
     f32 = lambda a: np.asarray(a, dtype=np.float64).astype(np.float32)
