@@ -25,9 +25,9 @@
 // Every global load of the loop is an ordinary register load issued through inline assembly (the compiler neither sees nor
 // counts them); register loads complete in the order they were issued, so each wait on the vector memory counter below
 // is the number of loads issued after the one it is for.
-// (A variant that sent the activations straight to LDS (global_load_lds_dwordx4) was measured first: those loads and
-// register loads share the counter but complete out of order with respect to each other, so counted waits gave wrong
-// fragments on some boxes, and draining the counter before every barrier cost 8 % against this version.)
+// (A variant that sent the activations straight to LDS (global_load_lds_dwordx4) was measured first and gave wrong fragments on
+// some boxes with counted waits; draining the counter before every barrier cost 8 % against this version.  That the two kinds
+// of load complete out of order with respect to each other was taken for the cause and not shown.)
 #include <algorithm>
 
 #include "gemm_i8_epilogue.h"
