@@ -26,7 +26,7 @@
 // counts them); register loads complete in the order they were issued, so each wait on the vector memory counter below
 // is the number of loads issued after the one it is for.
 // (A variant that sent the activations straight to LDS (global_load_lds_dwordx4) was measured first and gave wrong fragments on
-// some boxes with counted waits; draining the counter before every barrier cost 8 % against this version.  That the two kinds
+// some machines with counted waits; draining the counter before every barrier cost 8 % against this version.  That the two kinds
 // of load complete out of order with respect to each other was taken for the cause and not shown.)
 #include <algorithm>
 
