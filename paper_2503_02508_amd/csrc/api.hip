@@ -24,6 +24,7 @@ constexpr size_t CAL_ROWS = 1024;
 struct Sub {
   int b0, nb, lane;
   int r0;   // first row of this range in the conditioning tables (cond, fmod, mod, silu_q): step slot * batch + b0
+  int lanes;   // ranges that run at the same time, this one included
 };
 
 static thread_local char g_err[512] = "";
@@ -517,7 +518,7 @@ static int run_block_full(qc_ctx *ctx, int l, void *x, int xb, const Sub &sb, hi
   }
   {
     QC_PROF(QC_K_ATTENTION);
-    QC_HIP(launch_attention_f16(q32, k32, vt32, B, T, ctx->Tp, ctx->H, ctx->hd, ctx->DP, qp + QC_SITE_PROJ, qa_attn, st));
+    QC_HIP(launch_attention_f16(q32, k32, vt32, B, T, ctx->Tp, ctx->H, ctx->hd, ctx->DP, qp + QC_SITE_PROJ, qa_attn, sb.lanes, st));
   }
   {
     GemmArgs a = base(bq.lin[QC_SITE_PROJ], qa_attn, D, QC_SITE_PROJ);
@@ -565,7 +566,7 @@ int qc_dit_block(qc_ctx *ctx, int block, int mode, float *x, const float *c, int
   QC_HIP(launch_cond_silu(nullptr, nullptr, nullptr, 0, 0, B, B, (int)D, const_cast<float *>(c), nullptr, 1,
                           ctx->dev_qp + (size_t)block * QC_NUM_SITES + QC_SITE_ADA, QC_NUM_SITES,
                           ctx->silu_q + (size_t)block * ctx->win_rows * D, (size_t)ctx->win_rows * D, st));
-  const Sub whole{0, B, 0, 0};
+  const Sub whole{0, B, 0, 0, 1};
   rc = run_adaln(ctx, block, 1, 0, B, mode == QC_CACHED, st);
   if (rc) return rc;
   if (mode == QC_FULL) {
@@ -792,7 +793,7 @@ static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mo
   Sub sub[MAX_LANES];
   hipStream_t ls[MAX_LANES];
   for (int i = 0, b0 = 0; i < lanes; ++i) {
-    sub[i] = Sub{b0, B / lanes + (i < B % lanes ? 1 : 0), i, w * B + b0};
+    sub[i] = Sub{b0, B / lanes + (i < B % lanes ? 1 : 0), i, w * B + b0, lanes};
     b0 += sub[i].nb;
   }
   ls[0] = st;

@@ -218,6 +218,135 @@ __device__ __forceinline__ void split_pairs(v4f v, v2u &hi, v2u &lo) {
   lo = (v2u){l0, l1};
 }
 
+// The same split of eight values into the two operands of a product that may follow at once.  v_fma_mixhi_f16 writes half a
+// register, and a product that reads that register as the first half of an operand less than two issue slots later (the
+// second half: one) gets its old upper half; the compiler does not see what the assembly holds, so the wait is part of it.
+__device__ __forceinline__ void split_operand(v4f a, v4f b, v8h &hi, v8h &lo) {
+  unsigned h0 = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){a[0], a[1]}, v2h));
+  unsigned h1 = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){a[2], a[3]}, v2h));
+  unsigned h2 = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){b[0], b[1]}, v2h));
+  unsigned h3 = __builtin_bit_cast(unsigned, __builtin_convertvector((v2f){b[2], b[3]}, v2h));
+  unsigned l0, l1, l2, l3;
+  asm("v_fma_mixlo_f16 %0, %4, -1.0, %8 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixlo_f16 %1, %5, -1.0, %10 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixlo_f16 %2, %6, -1.0, %12 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixlo_f16 %3, %7, -1.0, %14 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %0, %4, -1.0, %9 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %1, %5, -1.0, %11 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %2, %6, -1.0, %13 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %3, %7, -1.0, %15 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "s_nop 1"
+      : "=&v"(l0), "=&v"(l1), "=&v"(l2), "=&v"(l3)
+      : "v"(h0), "v"(h1), "v"(h2), "v"(h3), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]));
+  hi = __builtin_bit_cast(v8h, (v4u){h0, h1, h2, h3});
+  lo = __builtin_bit_cast(v8h, (v4u){l0, l1, l2, l3});
+}
+
+// Second half of both kernels' epilogue, run by the whole workgroup once the codes of its NQ queries (the first of them q_first)
+// are staged and the doubtful ones queued (FIX_CAP of them at most): the queued outputs are decided again in float64, then
+// the rows go out.  qbase, kbase, vbase: float32 Q, K and V^T of the (batch, head); m_s: reference point of the exponentials
+// per query; parts: FB * NW * 16 bytes of LDS, [output][wavefront][2]; q_out: the head's first byte in the batch element's
+// first output row.
+constexpr int FIX_CAP = 192;
+template <int NEB, int NQ, int NW, int FB>
+__device__ __forceinline__ void decide_again_and_store(unsigned char *stage, const int *fix_cnt, const int *fix_ent, double *parts,
+                                                       const float *m_s, const float *qbase, const float *kbase, const float *vbase,
+                                                       int q_first, int T, int Tp, int hd, int D, float qs, float qz,
+                                                       int8_t *__restrict__ q_out) {
+  constexpr int SRB = 16 * NEB;                   // staged row: the head's features, padded
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // softmax(q K^T / sqrt(d)) V[:, feature] in float64 for every queued output.  The reference point of the exponentials is
+  // the running max of the fast path (any point near the maximum gives the same quotient), so the parts of a sum need no
+  // common maximum: wavefront w takes the groups w, w + NW, ... of 64 keys of every output and the parts meet in LDS.  Four
+  // lanes share a key row (lane h: 16-byte chunks h, h + 4, ...) and take four keys of a group, 16 apart; a row of the
+  // next group is requested as soon as the current one is used, and after the exchange each lane has one key's score: one
+  // exponential per lane and group.  About 250 float64-rate instructions per 64 keys are what bounds it.
+  const int nfix = min(*fix_cnt, FIX_CAP);
+  const double rs = 1.0 / sqrt((double)hd);
+  const int h4 = lane & 3, kl = lane >> 2;
+  for (int base = 0; base < nfix; base += FB) {
+    const int nb = min(nfix - base, FB);
+    for (int fi = 0; fi < nb; ++fi) {
+      const int qloc = fix_ent[2 * (base + fi)], feat = fix_ent[2 * (base + fi) + 1];
+      const float *qr = qbase + (size_t)(q_first + qloc) * hd;
+      const float *vrow = vbase + (size_t)feat * Tp;            // V^T row of the feature, keys in vt_pos order
+      v4f kv[4][NEB];
+      float va;
+      auto load_row = [&](int key, v4f (&dst)[NEB]) {
+        const float *r = kbase + (size_t)min(key, T - 1) * hd;
+#pragma unroll
+        for (int c = 0; c < NEB; ++c) dst[c] = *(const v4f *)(r + min(16 * c + 4 * h4, hd - 4));
+      };
+      int k0 = 64 * wave;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) load_row(k0 + 16 * u + kl, kv[u]);
+      va = vrow[vt_pos(min(k0 + 16 * h4 + kl, Tp - 1))];
+      double qd[NEB][4];
+#pragma unroll
+      for (int c = 0; c < NEB; ++c) {
+        const int f = 16 * c + 4 * h4;
+        const v4f t4 = *(const v4f *)(qr + min(f, hd - 4));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qd[c][e] = f < hd ? (double)t4[e] : 0.0;
+      }
+      const double mref = (double)m_s[qloc] * 0.6931471805599453;       // base 2 -> natural
+      double den = 0.0, num = 0.0;
+      for (; k0 < T; k0 += 64 * NW) {
+        const float v = va;
+        double sc = 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+          for (int c = 0; c < NEB; ++c) {
+            a0 = fma(qd[c][0], (double)kv[u][c][0], a0);
+            a1 = fma(qd[c][1], (double)kv[u][c][1], a1);
+            a0 = fma(qd[c][2], (double)kv[u][c][2], a0);
+            a1 = fma(qd[c][3], (double)kv[u][c][3], a1);
+          }
+          load_row(k0 + 64 * NW + 16 * u + kl, kv[u]);          // beyond T: the last row again, never used
+          a0 += a1;
+          a0 += dpp_move_d<0xB1>(a0);                           // quad_perm [1, 0, 3, 2], then [2, 3, 0, 1]: the four lanes
+          a0 += dpp_move_d<0x4E>(a0);                           // hold the whole dot product
+          sc = h4 == u ? a0 : sc;
+        }
+        va = vrow[vt_pos(min(k0 + 64 * NW + 16 * h4 + kl, Tp - 1))];
+        const double pj = k0 + 16 * h4 + kl < T ? exp(sc * rs - mref) : 0.0;
+        den += pj;
+        num = fma(pj, (double)v, num);
+      }
+      den = wave_sum_dpp(den);
+      num = wave_sum_dpp(num);
+      if (lane == 0) {
+        parts[(fi * NW + wave) * 2] = den;
+        parts[(fi * NW + wave) * 2 + 1] = num;
+      }
+    }
+    __syncthreads();
+    if (tid < nb) {
+      double den = 0.0, num = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        den += parts[(tid * NW + w) * 2];
+        num += parts[(tid * NW + w) * 2 + 1];
+      }
+      const float ov = (float)(num / den);
+      stage[fix_ent[2 * (base + tid)] * SRB + fix_ent[2 * (base + tid) + 1]] =
+          (unsigned char)(int)fminf(fmaxf(rintf(ov / qs) + qz, -128.f), 127.f);
+    }
+    __syncthreads();
+  }
+  // rows out: hd bytes per query (a multiple of 4), contiguous in the output row of the token
+  const int wpr = hd >> 2;                        // 32-bit words per row (<= 20): 32 lanes per row, 2 NW rows per pass
+  const int wd = tid & 31;
+#pragma unroll
+  for (int r0 = 0; r0 < NQ; r0 += 2 * NW) {
+    const int qloc = r0 + (tid >> 5), qg = q_first + qloc;
+    if (wd < wpr && qg < T)
+      *(unsigned *)(q_out + (size_t)qg * D + 4 * wd) = *(const unsigned *)(stage + qloc * SRB + 4 * wd);
+  }
+}
+
 // NCH feature chunks of 32 (operand width), NEB feature blocks of 16 that hold real features, QB query blocks of 16 per
 // wavefront (a workgroup covers 64 * QB queries).  QB = 2 reads every K / V^T fragment once for two MFMAs; QB = 1 makes
 // twice as many workgroups with half the MFMA chain each, for launches that would leave compute units idle.  The
@@ -532,7 +661,6 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   const QParam t = *qp;
   const float qs = t.s, qz = (float)t.z;
   constexpr int SRB = 16 * NEB;                   // staged row: the head's features, padded
-  constexpr int FIX_CAP = 192;
   static_assert(NQ * SRB + FIX_CAP * 8 <= (int)sizeof(Ksh), "the epilogue's staging area must fit in the K tile buffers");
   unsigned char *stage = (unsigned char *)Ksh;
   int *fix_cnt = &fix_cnt_s;
@@ -585,122 +713,317 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
     }
   }
   __syncthreads();
-  const int q_first = qblk * NQ;                  // first query of the workgroup
-  {
-    // softmax(q K^T / sqrt(d)) V[:, feature] in float64 for every queued output.  The reference point of the exponentials is
-    // the running max of the fast path (any point near the maximum gives the same quotient), so the parts of a sum need no
-    // common maximum: wavefront w takes the groups w, w + NW, ... of 64 keys of every output and the parts meet in LDS.  Four
-    // lanes share a key row (lane h: 16-byte chunks h, h + 4, ...) and take four keys of a group, 16 apart; a row of the
-    // next group is requested as soon as the current one is used, and after the exchange each lane has one key's score: one
-    // exponential per lane and group.  About 250 float64-rate instructions per 64 keys are what bounds it.
-    const int nfix = min(*fix_cnt, FIX_CAP);
-    constexpr int FB = (int)sizeof(Vsh) / (NW * 16) < 64 ? (int)sizeof(Vsh) / (NW * 16) : 64;   // outputs per batch of parts in LDS
-    double *const parts = (double *)&Vsh[0][0];                   // [output][wavefront][2]
-    const double rs = 1.0 / sqrt((double)hd);
-    const int h4 = lane & 3, kl = lane >> 2;
-    for (int base = 0; base < nfix; base += FB) {
-      const int nb = min(nfix - base, FB);
-      for (int fi = 0; fi < nb; ++fi) {
-        const int qloc = fix_ent[2 * (base + fi)], feat = fix_ent[2 * (base + fi) + 1];
-        const float *qr = Qp + tok_base + (size_t)(q_first + qloc) * hd;
-        const float *vrow = vbase + (size_t)feat * Tp;            // V^T row of the feature, keys in vt_pos order
-        v4f kv[4][NEB];
-        float va;
-        auto load_row = [&](int key, v4f (&dst)[NEB]) {
-          const float *r = kbase + (size_t)min(key, T - 1) * hd;
+  constexpr int FB = (int)sizeof(Vsh) / (NW * 16) < 64 ? (int)sizeof(Vsh) / (NW * 16) : 64;   // outputs per batch of parts in LDS
+  decide_again_and_store<NEB, NQ, NW, FB>(stage, &fix_cnt_s, fix_ent, (double *)&Vsh[0][0], m_s, Qp + tok_base, kbase, vbase, qblk * NQ, T,
+                                          Tp, hd, D, qs, qz, q_out + (size_t)b * T * D + (size_t)h * hd);
+}
+
+// The same attention for launches that would leave the chip idle: one workgroup = 16 QB queries of one (batch, head), its four
+// wavefronts share the KEYS (wavefront w takes the tiles w, w + 4, ... of 64), so the chain of key tiles a query waits for is a
+// quarter as long and there are four times as many workgroups.  No K or V^T fragment is used by two wavefronts, so none
+// goes through LDS: each lane loads its fragments from memory in operand layout (32 bytes at a time) and splits them in
+// registers, all of a tile's loads in flight together, the next tile's K requested as soon as the scores are formed.  (Loads of
+// whole lines turned through LDS: 11.7 against 9.3 us at 1 x 256 tokens.)  Every workgroup splits its head's whole K and V, so the
+// kernel is for launches that fit the chip at once; what is left is memory latency, about 1100 vector instructions a wavefront
+// and the exact decisions (2 us).  The running sums meet in LDS at the end: with M the largest running max of a query, each wavefront's sums are scaled by
+// 2^(m - M) in float32, the arithmetic of the rescaling in the key loop.
+template <int NCH, int NEB, int QB, bool TAIL>
+__global__ __launch_bounds__(256, 1) void attention_f16_keys_kernel(const float *__restrict__ Qp, const float *__restrict__ Kp,
+                                                                    const float *__restrict__ Vt, int BH, int T, int Tp, int H, int hd,
+                                                                    int DPv, float q_mul, const QParam *qp, int8_t *__restrict__ q_out) {
+  constexpr int NM = TAIL ? NCH - 1 : NCH;        // feature chunks multiplied in three instructions
+  constexpr int NI = NM + (TAIL ? 1 : 0);
+  constexpr int NW = 4, NT = 64 * NW, NQ = 16 * QB;
+  constexpr int SRB = 16 * NEB;                   // staged row: the head's features, padded
+  constexpr int FB = 64;                          // doubtful outputs per batch of parts in LDS
+  constexpr float MAX_SLACK = 8.0f;
+  // sums of the wavefronts, [wavefront][query block, feature block][lane]; later the parts of the exact decisions
+  __shared__ __align__(16) v4f osum[NW * QB * NEB * 64];
+  __shared__ float msum[NW][NQ], lsum[NW][NQ], m_s[NQ];
+  __shared__ __align__(16) unsigned char stage[NQ * SRB];
+  __shared__ int fix_ent[2 * FIX_CAP], fix_cnt_s;
+  static_assert(FB * NW * 16 <= (int)sizeof(osum), "the parts of the exact decisions must fit in the sums' area");
+
+  const int D = H * hd;
+  if (threadIdx.x == 0) fix_cnt_s = 0;            // published by the barrier behind the sums
+  // query blocks of one (batch, head) on one XCD, as above
+  const int n_qblk = gridDim.y;
+  const int wg = blockIdx.y * gridDim.x + blockIdx.x;
+  const int pos = wg >> 3, qblk = pos % n_qblk;
+  const int bh = (pos / n_qblk) * 8 + (wg & 7);
+  if (bh >= BH) return;                           // the grid is rounded up to whole groups of 8 heads
+  const int b = bh / H, h = bh % H;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int ql = lane & 15, g = lane >> 4;
+  const float *const qbase = Qp + (long long)bh * T * hd, *const kbase = Kp + (long long)bh * T * hd;
+  const float *const vbase = Vt + (long long)bh * DPv * Tp;
+
+  // K fragment (key block kt, chunk c): features 32 c + 8 g .. + 7 of key 16 kt + ql; in the packed tail every lane group
+  // needs the last eight features (hi, lo, hi, unused).  Keys beyond T read key T - 1 (masked below), features beyond d the last
+  // chunk (their query operand is zero).
+  v4f kraw[4][NCH][2], vraw[2][NEB][2];
+  unsigned foff[NCH][2];                          // features of the fragment's halves
 #pragma unroll
-          for (int c = 0; c < NEB; ++c) dst[c] = *(const v4f *)(r + min(16 * c + 4 * h4, hd - 4));
-        };
-        int k0 = 64 * wave;
+  for (int c = 0; c < NCH; ++c) {
+    const int f = 32 * c + (c < NM ? 8 * g : 0);
+    foff[c][0] = (unsigned)min(f, hd - 4);
+    foff[c][1] = (unsigned)min(f + 4, hd - 4);
+  }
+  auto load_k = [&](int k0) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) load_row(k0 + 16 * u + kl, kv[u]);
-        va = vrow[vt_pos(min(k0 + 16 * h4 + kl, Tp - 1))];
-        double qd[NEB][4];
+    for (int kt = 0; kt < 4; ++kt) {
+      const unsigned row = (unsigned)(min(k0 + 16 * kt + ql, T - 1) * hd);
 #pragma unroll
-        for (int c = 0; c < NEB; ++c) {
-          const int f = 16 * c + 4 * h4;
-          const v4f t4 = *(const v4f *)(qr + min(f, hd - 4));
+      for (int c = 0; c < NCH; ++c)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) qd[c][e] = f < hd ? (double)t4[e] : 0.0;
-        }
-        const double mref = (double)m_s[qloc] * 0.6931471805599453;       // base 2 -> natural
-        double den = 0.0, num = 0.0;
-        for (; k0 < T; k0 += 64 * NW) {
-          const float v = va;
-          double sc = 0.0;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-            for (int c = 0; c < NEB; ++c) {
-              a0 = fma(qd[c][0], (double)kv[u][c][0], a0);
-              a1 = fma(qd[c][1], (double)kv[u][c][1], a1);
-              a0 = fma(qd[c][2], (double)kv[u][c][2], a0);
-              a1 = fma(qd[c][3], (double)kv[u][c][3], a1);
-            }
-            load_row(k0 + 64 * NW + 16 * u + kl, kv[u]);          // beyond T: the last row again, never used
-            a0 += a1;
-            a0 += dpp_move_d<0xB1>(a0);                           // quad_perm [1, 0, 3, 2], then [2, 3, 0, 1]: the four lanes
-            a0 += dpp_move_d<0x4E>(a0);                           // hold the whole dot product
-            sc = h4 == u ? a0 : sc;
-          }
-          va = vrow[vt_pos(min(k0 + 64 * NW + 16 * h4 + kl, Tp - 1))];
-          const double pj = k0 + 16 * h4 + kl < T ? exp(sc * rs - mref) : 0.0;
-          den += pj;
-          num = fma(pj, (double)v, num);
-        }
-        den = wave_sum_dpp(den);
-        num = wave_sum_dpp(num);
-        if (lane == 0) {
-          parts[(fi * NW + wave) * 2] = den;
-          parts[(fi * NW + wave) * 2 + 1] = num;
-        }
-      }
-      __syncthreads();
-      if (tid < nb) {
-        double den = 0.0, num = 0.0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-          den += parts[(tid * NW + w) * 2];
-          num += parts[(tid * NW + w) * 2 + 1];
-        }
-        const float ov = (float)(num / den);
-        stage[fix_ent[2 * (base + tid)] * SRB + fix_ent[2 * (base + tid) + 1]] =
-            (unsigned char)(int)fminf(fmaxf(rintf(ov / qs) + qz, -128.f), 127.f);
-      }
-      __syncthreads();
+        for (int i = 0; i < 2; ++i) kraw[kt][c][i] = *(const v4f *)(kbase + (row + foff[c][i]));
     }
-  }
-  // rows out: hd bytes per query (a multiple of 4), contiguous in the output row of the token
-  const int wpr = hd >> 2;                        // 32-bit words per row (<= 20): 32 lanes per row, 2 NW rows per pass
-  const int wd = tid & 31;
+  };
+  // V^T fragment (32 keys a, feature block e): keys 8 g .. + 7 (in stored order) of row 16 e + ql; the rows and keys of the
+  // padding are zeros in memory
+  auto load_v = [&](int k0) {
 #pragma unroll
-  for (int r0 = 0; r0 < NQ; r0 += 2 * NW) {
-    const int qloc = r0 + (tid >> 5), qg = q_first + qloc;
-    if (wd < wpr && qg < T)
-      *(unsigned *)(q_out + ((size_t)b * T + qg) * D + (size_t)h * hd + 4 * wd) = *(const unsigned *)(stage + qloc * SRB + 4 * wd);
+    for (int e = 0; e < NEB; ++e) {
+      const unsigned at = (unsigned)((16 * e + ql) * Tp + k0 + 8 * g);
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) vraw[a][e][i] = *(const v4f *)(vbase + (at + 32 * a + 4 * i));
+    }
+  };
+
+  const int k_first = 64 * wave;                  // wavefronts beyond the last tile load a valid one and use nothing of it
+  load_k(min(k_first, Tp - 64));
+  int q_row[QB];
+  v8h qh[QB][NI], qlo[QB][NM > 0 ? NM : 1];       // with TAIL, qh[.][NM] is the packed tail operand
+  {
+    v4f qraw[QB][NCH][2];
+#pragma unroll
+    for (int j = 0; j < QB; ++j) {
+      q_row[j] = qblk * NQ + j * 16 + ql;
+      const unsigned row = (unsigned)(min(q_row[j], T - 1) * hd);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) qraw[j][c][i] = *(const v4f *)(qbase + (row + foff[c][i]));
+    }
+    load_v(min(k_first, Tp - 64));
+#pragma unroll
+    for (int j = 0; j < QB; ++j)
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        const int f = 32 * c + (c < NM ? 8 * g : 0);
+        v2u h0, l0, h1, l1;
+        split_pairs(qraw[j][c][0] * q_mul, h0, l0);     // queries pre-scaled by log2(e) / sqrt(d): the softmax runs in base 2
+        split_pairs(qraw[j][c][1] * q_mul, h1, l1);
+        if (f >= hd) { h0 = (v2u){0, 0}; l0 = h0; }
+        if (f + 4 >= hd) { h1 = (v2u){0, 0}; l1 = h1; }
+        const v4u hh = {h0.x, h0.y, h1.x, h1.y}, ll = {l0.x, l0.y, l1.x, l1.y};
+        if (c < NM) {
+          qh[j][c] = __builtin_bit_cast(v8h, hh);
+          qlo[j][c] = __builtin_bit_cast(v8h, ll);
+        } else {                                        // lane group g supplies k positions 8 g .. 8 g + 7: hi, hi, lo, nothing
+          v4u t = g == 2 ? ll : hh;
+          if (g == 3) t = (v4u){0, 0, 0, 0};
+          qh[j][c] = __builtin_bit_cast(v8h, t);
+        }
+      }
   }
+  v4f o[QB][NEB];
+  float m_run[QB], l_run[QB];
+#pragma unroll
+  for (int j = 0; j < QB; ++j) {
+    m_run[j] = -INFINITY;
+    l_run[j] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < NEB; ++e) o[j][e] = (v4f){0.f, 0.f, 0.f, 0.f};
+  }
+
+  for (int k0 = k_first; k0 < T; k0 += 64 * NW) {
+    const int k_next = k0 + 64 * NW;
+    v4f s[QB][4];
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+#pragma unroll
+      for (int j = 0; j < QB; ++j) s[j][kt] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NI; ++c) {
+        v8h kh, kl;
+        split_operand(kraw[kt][c][0], kraw[kt][c][1], kh, kl);
+        if (c < NM) {
+#pragma unroll
+          for (int j = 0; j < QB; ++j) s[j][kt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, qh[j][c], s[j][kt], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < QB; ++j) s[j][kt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qlo[j][c < NM ? c : 0], s[j][kt], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < QB; ++j) s[j][kt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qh[j][c], s[j][kt], 0, 0, 0);
+        } else {
+          const v8h kt8 = g == 1 ? kl : kh;
+#pragma unroll
+          for (int j = 0; j < QB; ++j) s[j][kt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kt8, qh[j][c], s[j][kt], 0, 0, 0);
+        }
+      }
+    }
+    if (k_next < T) load_k(k_next);
+    if (k0 + 64 > T) {
+#pragma unroll
+      for (int j = 0; j < QB; ++j)
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (k0 + kt * 16 + 4 * g + r >= T) s[j][kt][r] = -INFINITY;
+    }
+    float mx[QB];
+    bool over = false;
+#pragma unroll
+    for (int j = 0; j < QB; ++j) {
+      mx[j] = s[j][0][0];
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx[j] = fmaxf(mx[j], s[j][kt][r]);
+      over = over || mx[j] > m_run[j] + MAX_SLACK;      // true on the first tile: m_run starts at minus infinity
+    }
+    if (__builtin_amdgcn_ballot_w64(over) != 0ull) {
+#pragma unroll
+      for (int j = 0; j < QB; ++j) {
+        mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 16, 64));
+        mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 32, 64));
+        const float m_new = fmaxf(m_run[j], mx[j]);
+        const float alpha = __builtin_amdgcn_exp2f(m_run[j] - m_new);
+        m_run[j] = m_new;
+        l_run[j] *= alpha;
+#pragma unroll
+        for (int e = 0; e < NEB; ++e) o[j][e] *= alpha;
+      }
+    }
+    v8h ph[QB][2], pl[QB][2];
+#pragma unroll
+    for (int j = 0; j < QB; ++j)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        v4f p[2];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {         // word w of the operand: keys (kt = 2 a + w / 2, r = 2 (w % 2) .. + 1)
+          const int kt = 2 * a + (w >> 1), r = 2 * (w & 1);
+          const float p0 = __builtin_amdgcn_exp2f(s[j][kt][r] - m_run[j]), p1 = __builtin_amdgcn_exp2f(s[j][kt][r + 1] - m_run[j]);
+          l_run[j] += p0;
+          l_run[j] += p1;
+          p[w >> 1][r] = p0;
+          p[w >> 1][r + 1] = p1;
+        }
+        split_operand(p[0], p[1], ph[j][a], pl[j][a]);
+      }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int e = 0; e < NEB; ++e) {
+        v8h vh, vl;
+        split_operand(vraw[a][e][0], vraw[a][e][1], vh, vl);
+#pragma unroll
+        for (int j = 0; j < QB; ++j) o[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vl, ph[j][a], o[j][e], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < QB; ++j) o[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh, pl[j][a], o[j][e], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < QB; ++j) o[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh, ph[j][a], o[j][e], 0, 0, 0);
+      }
+    if (k_next < T) load_v(k_next);
+  }
+
+  // the wavefronts' sums meet
+#pragma unroll
+  for (int j = 0; j < QB; ++j) {
+    float l = l_run[j];
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    if (g == 0) {
+      msum[wave][16 * j + ql] = m_run[j];
+      lsum[wave][16 * j + ql] = l;
+    }
+#pragma unroll
+    for (int e = 0; e < NEB; ++e) osum[((wave * QB + j) * NEB + e) * 64 + lane] = o[j][e];
+  }
+  __syncthreads();
+  const QParam t = *qp;
+  const float qs = t.s, qz = (float)t.z;
+  // the window of the exact decisions, as in the kernel above
+  const float tol_k = fmaxf(1.0f, (float)T * (1.0f / 256.0f));
+  const float tol_0 = 1.2e-5f * tol_k, tol_q = 4e-7f * tol_k + 2.5e-7f;
+  const float doubt_at = 0.5f - tol_0;
+  const float inv_qs = 1.0f / qs, zu = qz + 128.0f;
+#pragma unroll
+  for (int i0 = 0; i0 < QB * NEB * 64; i0 += NT) {
+    const int i = i0 + tid;
+    if (i >= QB * NEB * 64) break;                // whole wavefronts
+    const int je = i >> 6, j = je / NEB, e = je - j * NEB;
+    const int qloc = 16 * j + ql, f = 16 * e + 4 * g;
+    float M = msum[0][qloc];                      // finite: wavefront 0 has a tile
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, msum[w][qloc]);
+    float l = 0.0f;
+    v4f ov = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {                // a wavefront without a tile: 2^(-inf) = 0 times sums that are zero
+      const float a = __builtin_amdgcn_exp2f(msum[w][qloc] - M);
+      l += lsum[w][qloc] * a;
+      ov += osum[(w * QB * NEB + je) * 64 + lane] * a;
+    }
+    if (e == 0 && g == 0) m_s[qloc] = M;
+    const float k = (1.0f / l) * inv_qs;          // value and quotient of Eq. 1 in one multiplication per output
+    unsigned w4 = 0;
+    float dist[4];                                // distance from the rounding boundary plus the window's relative part
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float qv = ov[r] * k, rr = __builtin_rintf(qv);
+      w4 = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(rr + zu, 0.0f, 255.0f), r, w4);
+      dist[r] = fmaf(tol_q, fabsf(qv), fabsf(qv - rr));
+    }
+    if (fmaxf(fmaxf(dist[0], dist[1]), fmaxf(dist[2], dist[3])) > doubt_at) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (dist[r] > doubt_at && qblk * NQ + qloc < T && f + r < hd) {
+          const int slot = atomicAdd(&fix_cnt_s, 1);
+          if (slot < FIX_CAP) {
+            fix_ent[2 * slot] = qloc;
+            fix_ent[2 * slot + 1] = f + r;
+          }
+        }
+    }
+    *(unsigned *)(stage + qloc * SRB + f) = w4 ^ 0x80808080u;
+  }
+  __syncthreads();
+  decide_again_and_store<NEB, NQ, NW, FB>(stage, &fix_cnt_s, fix_ent, (double *)osum, m_s, qbase, kbase, vbase, qblk * NQ, T, Tp, hd, D,
+                                          qs, qz, q_out + (size_t)b * T * D + (size_t)h * hd);
 }
 
 hipError_t launch_attention_f16(const float *q32, const float *k32, const float *vt32, int B, int T, int Tp, int H, int hd,
-                                int DPv, const QParam *qp, int8_t *q_out, hipStream_t st) {
+                                int DPv, const QParam *qp, int8_t *q_out, int beside, hipStream_t st) {
   const int neb = (hd + 15) / 16, nch = (hd + 31) / 32;
   if (hd > 80 || hd % 4) return hipErrorInvalidValue;      // K prefetch registers are sized for d <= 80
   const float q_mul = 1.4426950408889634f / std::sqrt((float)hd);     // log2(e) / sqrt(d)
-  // Two query blocks per wavefront (128 queries per workgroup) when that makes more workgroups than compute units, else one.
-  // Measured, one / two (16 heads of 72; us): 128 x 256 tokens 240 / 185, 16 x 1024: 361 / 287, 2 x 4096: 854 / 731, 16 x 256:
-  // 34.5 / 27.5, 10 x 425: 57.8 / 55.7, 8 x 256: 18.8 / 19.0, 3 x 425: 28.5 / 32.0, 1 x 256: 13.3 / 17.0; workgroups of eight
-  // wavefronts came out within 2 % at 1024 tokens and behind elsewhere.
+  // Keys shared by the wavefronts, 16 (else 32) queries a workgroup, while that makes no more workgroups than this launch's share of
+  // the compute units (`beside` launches of its kind run at the same time).  Measured, keys shared with 16 / with 32 queries / not
+  // shared (16 heads of 72; us back to back, 4.5 of them the launch): 1 x 256 tokens 9.3 / 10.7 / 14.5, 2 x 256 18.3 / 11.9 / 15.0,
+  // 1 x 425 21.8 / 17.1 / 22.5, 3 x 256 23.5 / 17.8 / 15.3, 2 x 425 38.6 / 26.5 / 23.6, 1 x 1024 78 / 52.5 / 44.9, 1 x 64 6.8 / 8.7 /
+  // 7.6; 6 heads of 64: 1 x 256 8.4 / 10.1 / 11.0, 4 x 256 12.9 / 10.5 / 11.7.
+  // Otherwise two query blocks per wavefront (128 queries per workgroup) when that makes more workgroups than compute units, else
+  // one.  Measured, one / two (16 heads of 72; us): 128 x 256 tokens 240 / 185, 16 x 1024: 361 / 287, 2 x 4096: 854 / 731, 16 x 256:
+  // 34.5 / 27.5, 10 x 425: 57.8 / 55.7, 8 x 256: 18.8 / 19.0, 3 x 425: 28.5 / 32.0; workgroups of eight wavefronts came out
+  // within 2 % at 1024 tokens and behind elsewhere.
+  const long long share = 256 / (beside > 1 ? beside : 1), heads = (long long)B * H;
+  const int kq = heads * ((T + 15) / 16) <= share ? 1 : heads * ((T + 31) / 32) <= share ? 2 : 0;
   const int qb = B * H * ((T + 127) / 128) <= 256 ? 1 : 2;
-  dim3 grid((B * H + 7) / 8 * 8, (T + 64 * qb - 1) / (64 * qb));
-#define QC_ATT(NCH, NEB, TAIL)                                                                                              \
-  do {                                                                                                                      \
-    if (qb == 1)                                                                                                            \
-      hipLaunchKernelGGL((attention_f16_kernel<NCH, NEB, 1, TAIL>), grid, dim3(256), 0, st, q32, k32, vt32, B * H, T, Tp, H, hd, \
-                         DPv, q_mul, qp, q_out);                                                                            \
-    else                                                                                                                    \
-      hipLaunchKernelGGL((attention_f16_kernel<NCH, NEB, 2, TAIL>), grid, dim3(256), 0, st, q32, k32, vt32, B * H, T, Tp, H, hd, \
-                         DPv, q_mul, qp, q_out);                                                                            \
+  const int per_wg = kq ? 16 * kq : 64 * qb;
+  dim3 grid((B * H + 7) / 8 * 8, (T + per_wg - 1) / per_wg);
+#define QC_ATT_LAUNCH(...) \
+  hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), 0, st, q32, k32, vt32, B * H, T, Tp, H, hd, DPv, q_mul, qp, q_out)
+#define QC_ATT(NCH, NEB, TAIL)                                                \
+  do {                                                                        \
+    if (kq == 1) QC_ATT_LAUNCH(attention_f16_keys_kernel<NCH, NEB, 1, TAIL>); \
+    else if (kq == 2) QC_ATT_LAUNCH(attention_f16_keys_kernel<NCH, NEB, 2, TAIL>); \
+    else if (qb == 1) QC_ATT_LAUNCH(attention_f16_kernel<NCH, NEB, 1, TAIL>); \
+    else QC_ATT_LAUNCH(attention_f16_kernel<NCH, NEB, 2, TAIL>);              \
   } while (0)
   const bool tail = nch > 1 && hd - 32 * (nch - 1) <= 8;      // at most 8 features in the last chunk
   if (nch == 1 && neb == 1) QC_ATT(1, 1, false);
@@ -712,6 +1035,7 @@ hipError_t launch_attention_f16(const float *q32, const float *k32, const float 
   else if (nch == 3 && neb == 5) QC_ATT(3, 5, false);
   else return hipErrorInvalidValue;
 #undef QC_ATT
+#undef QC_ATT_LAUNCH
   return hipGetLastError();
 }
 

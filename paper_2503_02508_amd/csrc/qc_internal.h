@@ -198,8 +198,9 @@ hipError_t launch_vc_fit(const float *x_hat, const float *x_ref, int B, int C, i
                          hipStream_t st);
 hipError_t launch_attention(const float *qkv, int B, int T, int H, int hd, const QParam *qp, int8_t *q_out, float *f32_out,
                             hipStream_t st);
+// `beside`: launches of its kind that run at the same time (sub-batches of a denoiser call), this one included
 hipError_t launch_attention_f16(const float *q32, const float *k32, const float *vt32, int B, int T, int Tp, int H, int hd,
-                                int DPv, const QParam *qp, int8_t *q_out, hipStream_t st);
+                                int DPv, const QParam *qp, int8_t *q_out, int beside, hipStream_t st);
 // calibration helpers
 hipError_t launch_linear_f32(const float *x, const float *W, const float *b, float *y, int M, int N, int K, int gelu,
                              hipStream_t st);

@@ -79,6 +79,34 @@ def _overwritten_stores(lines):
     return found
 
 
+def _half_written_operands(lines):
+    """v_fma_mixlo/hi_f16 (half a register) fewer than two issue slots in front of a matrix product that reads the register, in
+    straight-line code."""
+    code = [l.split("//")[0].strip() for l in lines]
+    code = [l for l in code if re.match(r"[a-z]\w+( |$)", l)]
+    found = []
+    for i, line in enumerate(code):
+        if not line.startswith(("v_fma_mixlo_f16", "v_fma_mixhi_f16")):
+            continue
+        dst, slots = _vgprs(line.partition(" ")[2].split(",")[0]), 0
+        for nxt in code[i + 1:]:
+            op, _, rest = nxt.partition(" ")
+            if slots >= 2 or op.startswith(("s_branch", "s_cbranch", "s_endpgm")):
+                break
+            args = re.split(r",\s*(?![^\[]*\])", rest)
+            if op.startswith("v_mfma") and dst & (_vgprs(args[1]) | _vgprs(args[2])):
+                found.append(line + "  ->  " + nxt)
+            slots += int(rest, 0) + 1 if op == "s_nop" else 1
+    return found
+
+
+def test_a_half_written_operand_read_too_early_is_found():
+    half, use = "v_fma_mixhi_f16 v115, v111, -1.0, v55 op_sel:[1,0,0] op_sel_hi:[1,0,0]", "v_mfma_f32_16x16x32_f16 a[4:7], v[114:117], v[20:23], 0"
+    assert _half_written_operands([half, "v_mov_b32_e32 v109, v3", use])
+    assert not _half_written_operands([half, "s_nop 1", use])
+    assert not _half_written_operands([half, "v_mov_b32_e32 v109, v3", use.replace("114:117", "116:119")])
+
+
 def test_a_data_register_of_a_store_written_too_early_is_found():
     bad = "buffer_store_dwordx4 v[204:207], v88, s[4:7], s3 offen nt"
     assert _overwritten_stores([bad, "v_cvt_f32_i32_e32 v204, v84"])
@@ -105,6 +133,9 @@ def test_no_store_loses_its_data_to_the_next_instruction(tmp_path):
             kernels += "s_endpgm" in body
             if "linear_f32_kernel" in name:        # its loads to LDS write m0 in inline assembly, unknown to the compiler
                 assert all(l.strip().startswith("s_mov_b32 m0,") for l in body.splitlines() if re.search(r"\bm0\b", l))
+            # a product that follows too closely reads the old half (27 % of the codes of 1 x 256 tokens, 6 heads of 64, were wrong)
+            early = _half_written_operands(body.splitlines())
+            assert not early, "%s: %d products, the first: %s" % (name, len(early), early[0])
             found = _overwritten_stores(body.splitlines())
             assert not found, "%s: %d stores, the first: %s" % (name, len(found), found[0])
     assert kernels > 50

@@ -44,6 +44,13 @@ def _net(hidden, heads, mlp, h, w, patch=2):
     ("attention: 72 features a head, 1 key past a tile", _net(288, 4, 512, 10, 26), 2, 8),
     ("attention: two query blocks a wavefront, 575 tokens", _net(256, 4, 512, 46, 50), 33, 8),
     ("attention: 16 features a head", _net(64, 4, 128, 16, 22), 2, 8),
+    # keys shared by the wavefronts: two rounds of tiles, the second of three wavefronts (the last one's ragged); one tile for three
+    # wavefronts and a half of queries; fewer keys than a tile, padded feature chunk; 80 features a head
+    ("attention, shared keys: 425 tokens, 32 queries a workgroup", _net(1152, 16, 1152, 50, 34), 1, 8),
+    ("attention, shared keys: 133 tokens, 64 features", _net(384, 6, 512, 14, 38), 1, 8),
+    ("attention, shared keys: 35 tokens, 48 features", _net(192, 4, 512, 10, 14), 2, 8),
+    ("attention, shared keys: 100 tokens, 80 features", _net(320, 4, 512, 20, 20), 3, 8),
+    ("attention, shared keys: 260 tokens, 40 features", _net(160, 4, 512, 20, 52), 2, 8),
     ("split-K: one row past a 32-row tile, 4-bit", _net(128, 2, 512, 6, 22), 1, 4),
     ("split-K: 64 x 64 tiles with remainders", _net(384, 6, 1536, 30, 26), 2, 8),
     # more than 150 tiles of 128 x 256 that do not all lie inside one batch element: 425 tokens (no unit of four tokens is
