@@ -37,6 +37,13 @@ constexpr int NUM_XCD = 8;
 constexpr int KB_MAX = 128;
 constexpr int M_MAX = 8;
 
+// Every kernel of the chain works on one subsample per grid layer z: the subsamples of a group lie the same number of bytes
+// apart in the workspace (0 for what they share), so one launch serves them all.
+template <class T>
+__device__ __forceinline__ T *in_slot(T *p, long long bytes) {
+  return reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(p) + blockIdx.z * (uintptr_t)bytes);
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -75,6 +82,8 @@ struct SgemmArgs {
   // symmetric product (SE_PLAIN, B = A with the same strides, M = N): only the tiles on and below the diagonal are
   // computed; the kernel that adds the partial products also writes the mirror image
   int sym;
+  // bytes from one subsample to the next (grid z): the operands, the result, the partial products, the epilogue's factors
+  long long za, zb, zc, zpart, zrs, zcs, ztr, ztc;
 };
 
 // One operand's share of a slab for this thread: four units of four consecutive elements.
@@ -172,6 +181,15 @@ __device__ __forceinline__ void tri_decode(int t, int &row, int &col) {
 template <bool AKC, bool BKC, int EPI, bool VEC>
 __global__ __launch_bounds__(256, 2) void sgemm_kernel(SgemmArgs p) {
   constexpr int LDA = ldt<AKC>(), LDB = ldt<BKC>();
+  p.A = in_slot(p.A, p.za);
+  p.B = in_slot(p.B, p.zb);
+  p.C = in_slot(p.C, gridDim.y > 1 ? p.zpart : p.zc);
+  if (EPI != SE_PLAIN) p.cs = in_slot(p.cs, p.zcs);
+  if (EPI == SE_SIM) {
+    p.rs = in_slot(p.rs, p.zrs);
+    p.tr = in_slot(p.tr, p.ztr);
+    p.tc = in_slot(p.tc, p.ztc);
+  }
   __shared__ __align__(16) float As[2][TK * LDA];
   __shared__ __align__(16) float Bs[2][TK * LDB];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -288,7 +306,9 @@ __global__ __launch_bounds__(256, 2) void sgemm_kernel(SgemmArgs p) {
 }
 
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *part, int splits, long long stride,
-                                                            long long count, float *out) {
+                                                            long long count, float *out, long long zpart, long long zout) {
+  part = in_slot(part, zpart);
+  out = in_slot(out, zout);
   const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
   if (i >= count) return;
   float s = 0.f;
@@ -300,7 +320,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *part, i
 // workgroup per 32 x 32 block on or below the diagonal adds the partial products, writes the block and, through LDS,
 // its transpose (`out` may be `part` when there is a single partial product)
 __global__ __launch_bounds__(256) void splitk_reduce_sym_kernel(const float *part, int splits, long long stride, int n,
-                                                                long long ldc, float *out) {
+                                                                long long ldc, float *out, long long zpart, long long zout) {
+  part = in_slot(part, zpart);
+  out = in_slot(out, zout);
   __shared__ float tile[32][33];
   int bm, bn;
   tri_decode(blockIdx.x, bm, bn);
@@ -324,7 +346,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_sym_kernel(const float *par
 }
 
 // `part` (part_elems floats) allows a plain product with few tiles and a long K to be split along K
-hipError_t sgemm(SgemmArgs a, int epi, hipStream_t st, float *part = nullptr, size_t part_elems = 0) {
+hipError_t sgemm(SgemmArgs a, int epi, int nz, hipStream_t st, float *part = nullptr, size_t part_elems = 0) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   a.a_kc = a.sak == 1;
   a.b_kc = a.sbk == 1;
@@ -357,8 +379,8 @@ hipError_t sgemm(SgemmArgs a, int epi, hipStream_t st, float *part = nullptr, si
   const bool vec = a.a_vec && a.b_vec;
 #define SG_LAUNCH(AK, BK, E)                                                                                   \
   do {                                                                                                         \
-    if (vec) hipLaunchKernelGGL((sgemm_kernel<AK, BK, E, true>), dim3(grid, splits), dim3(256), 0, st, a);     \
-    else hipLaunchKernelGGL((sgemm_kernel<AK, BK, E, false>), dim3(grid, splits), dim3(256), 0, st, a);        \
+    if (vec) hipLaunchKernelGGL((sgemm_kernel<AK, BK, E, true>), dim3(grid, splits, nz), dim3(256), 0, st, a); \
+    else hipLaunchKernelGGL((sgemm_kernel<AK, BK, E, false>), dim3(grid, splits, nz), dim3(256), 0, st, a);    \
   } while (0)
   if (epi == SE_SIM) {
     if (a.a_kc && a.b_kc) SG_LAUNCH(true, true, SE_SIM);
@@ -375,11 +397,12 @@ hipError_t sgemm(SgemmArgs a, int epi, hipStream_t st, float *part = nullptr, si
 #undef SG_LAUNCH
   if (a.sym) {
     const int nb = (a.M + 31) / 32;
-    hipLaunchKernelGGL(splitk_reduce_sym_kernel, dim3(nb * (nb + 1) / 2), dim3(256), 0, st,
-                       splits > 1 ? (const float *)part : (const float *)out, splits, out_elems, a.M, a.ldc, out);
+    hipLaunchKernelGGL(splitk_reduce_sym_kernel, dim3(nb * (nb + 1) / 2, 1, nz), dim3(256), 0, st,
+                       splits > 1 ? (const float *)part : (const float *)out, splits, out_elems, a.M, a.ldc, out,
+                       splits > 1 ? a.zpart : a.zc, a.zc);
   } else if (splits > 1) {
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((out_elems + 255) / 256)), dim3(256), 0, st, part, splits,
-                       out_elems, out_elems, out);
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((out_elems + 255) / 256), 1, nz), dim3(256), 0, st, part,
+                       splits, out_elems, out_elems, out, a.zpart, a.zc);
   }
   return hipGetLastError();
 }
@@ -402,8 +425,14 @@ __global__ __launch_bounds__(256) void rownorm_kernel(const float *X, int N, int
 // rows, inverse norms and timestamps of one subsample gathered into dense arrays; an index outside [0, N) raises
 // the flag and is replaced by 0
 __global__ __launch_bounds__(256) void gather_kernel(const float *X, const float *rinv, const float *t, const int *idx,
-                                                     int N, int F, float *Xs, float *cs, float *tc, int *flag) {
+                                                     int N, int F, float *Xs, float *cs, float *tc, int *flag,
+                                                     long long zidx, long long zw, long long zflag) {
   const int h = blockIdx.x;
+  idx = in_slot(idx, zidx);
+  Xs = in_slot(Xs, zw);
+  cs = in_slot(cs, zw);
+  tc = in_slot(tc, zw);
+  flag = in_slot(flag, zflag);
   int s = idx[h];
   if (s < 0 || s >= N) {
     if (threadIdx.x == 0) atomicOr(flag, 1);
@@ -419,10 +448,12 @@ __global__ __launch_bounds__(256) void gather_kernel(const float *X, const float
 }
 
 // d_r: one wavefront per row, fp64 sum
-__global__ __launch_bounds__(256) void rowsum_kernel(const float *A, int N, int n, float *dr) {
+__global__ __launch_bounds__(256) void rowsum_kernel(const float *A, int N, int n, int lda, float *dr, long long zw) {
+  A = in_slot(A, zw);
+  dr = in_slot(dr, zw);
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= N) return;
-  const float *a = A + (long long)row * n;
+  const float *a = A + (long long)row * lda;
   double s = 0.0;
   for (int j = lane; j < n; j += 64) s += (double)a[j];
   s = wave_sum(s);
@@ -431,7 +462,10 @@ __global__ __launch_bounds__(256) void rowsum_kernel(const float *A, int N, int 
 
 // d_c in two deterministic stages: partial sums of COL_CHUNKS row ranges, then their sum in order
 constexpr int COL_CHUNKS = 64;
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const float *A, int N, int n, double *part) {
+__global__ __launch_bounds__(256) void colsum_partial_kernel(const float *A, int N, int n, int lda, double *part,
+                                                             long long zw) {
+  A = in_slot(A, zw);
+  part = in_slot(part, zw);
   __shared__ double red[4][64];
   const int c = threadIdx.x & 63, ph = threadIdx.x >> 6;
   const int col = blockIdx.x * 64 + c;
@@ -439,13 +473,15 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float *A, int
   const int r0 = blockIdx.y * rows_per, r1 = min(N, r0 + rows_per);
   double s = 0.0;
   if (col < n)
-    for (int r = r0 + ph; r < r1; r += 4) s += (double)A[(long long)r * n + col];
+    for (int r = r0 + ph; r < r1; r += 4) s += (double)A[(long long)r * lda + col];
   red[ph][c] = s;
   __syncthreads();
   if (ph == 0 && col < n) part[(long long)blockIdx.y * n + col] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }
 
-__global__ __launch_bounds__(256) void colsum_final_kernel(const double *part, int n, float *dc) {
+__global__ __launch_bounds__(256) void colsum_final_kernel(const double *part, int n, float *dc, long long zw) {
+  part = in_slot(part, zw);
+  dc = in_slot(dc, zw);
   const int col = blockIdx.x * 256 + threadIdx.x;
   if (col >= n) return;
   double s = 0.0;
@@ -453,29 +489,45 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(const double *part, i
   dc[col] = (float)s;
 }
 
-__global__ __launch_bounds__(256) void fill_int_kernel(int *p, int count, int v) {
+__global__ __launch_bounds__(256) void fill_int_kernel(int *p, int count, int v, long long zp) {
+  p = in_slot(p, zp);
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < count) p[i] = v;
 }
 
-__global__ __launch_bounds__(256) void degree_check_kernel(const float *d, int count, int *flag) {
+__global__ __launch_bounds__(256) void degree_check_kernel(const float *dr, int N, const float *dc, int n, int *flag,
+                                                           long long zw, long long zflag) {
+  dr = in_slot(dr, zw);
+  dc = in_slot(dc, zw);
+  flag = in_slot(flag, zflag);
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < count) {
-    const float v = d[i];
+  if (i < N + n) {
+    const float v = i < N ? dr[i] : dc[i - N];
     if (!(v > 0.f) || !isfinite(v)) atomicOr(flag, 1);
   }
 }
 
-// `guard` (may be null): a device flag raised by the degree check; the matrix is left alone when it is set
-__global__ __launch_bounds__(256) void normalise_kernel(float *A, const float *dr, const float *dc, int N, int n,
-                                                        const int *guard) {
-  if (guard && *guard) return;
-  const int nblk = (n + 255) / 256;
+// `guard` (may be null): a device flag raised by the degree check; the matrix is left alone when it is set.  Rows lie lda
+// floats apart; what lies between (a workspace matrix with padded rows) becomes zero.
+__global__ __launch_bounds__(256) void normalise_kernel(float *A, const float *dr, const float *dc, int N, int n, int lda,
+                                                        const int *guard, long long zw, long long zflag) {
+  if (guard && *in_slot(guard, zflag)) return;
+  A = in_slot(A, zw);
+  dr = in_slot(dr, zw);
+  dc = in_slot(dc, zw);
+  const int nblk = (lda + 255) / 256;
   const int r = blockIdx.x / nblk;
   const int h = (blockIdx.x % nblk) * 256 + threadIdx.x;
-  if (h >= n) return;
-  const float s = (1.f / sqrtf(dr[r])) * (1.f / sqrtf(dc[h]));
-  A[(long long)r * n + h] *= s;
+  if (h >= lda) return;
+  float *a = A + (long long)r * lda + h;
+  if (h >= n) *a = 0.f;
+  else *a *= (1.f / sqrtf(dr[r])) * (1.f / sqrtf(dc[h]));
+}
+
+// rows of n floats copied to rows of ld floats, zeros behind them
+__global__ __launch_bounds__(256) void pad_rows_kernel(const float *src, int n, float *dst, int ld, long long zdst) {
+  dst = in_slot(dst, zdst);
+  for (int j = threadIdx.x; j < ld; j += 256) dst[(long long)blockIdx.x * ld + j] = j < n ? src[(long long)blockIdx.x * n + j] : 0.f;
 }
 
 // -------------------------------------------------------------------------- orthonormalisation (Cholesky QR)
@@ -483,7 +535,9 @@ __global__ __launch_bounds__(256) void normalise_kernel(float *A, const float *d
 // y_c[j], vector a's element j at Y[a * sv + j * sj] (rows of a [kb, n] matrix: sv = n, sj = 1; columns of an
 // [n, kb] matrix: sv = 1, sj = kb)
 __global__ __launch_bounds__(256) void gram_partial_kernel(const float *Y, int kb, int n, long long sv, long long sj,
-                                                           int jchunk, double *part) {
+                                                           int jchunk, double *part, long long zy, long long zw) {
+  Y = in_slot(Y, zy);
+  part = in_slot(part, zw);
   __shared__ float ys[KB_MAX][33];
   const int tid = threadIdx.x, ta = tid >> 4, tb = tid & 15;
   double acc[8][8];
@@ -525,7 +579,9 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(const float *Y, int k
     }
 }
 
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const double *part, int nparts, int kk, double *W) {
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const double *part, int nparts, int kk, double *W, long long zw) {
+  part = in_slot(part, zw);
+  W = in_slot(W, zw);
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= kk) return;
   double s = 0.0;
@@ -559,7 +615,10 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double *part, in
 // identity at once when W is the identity to 1e-5, and a pivot below 1/4 raises the flag: the block has no full
 // rank.  A non-positive pivot always raises it.
 __global__ __launch_bounds__(1024) void chol_inv_kernel(const double *W, int kb, double shift_rel, int check,
-                                                         float *Rinv, int *flag) {
+                                                         float *Rinv, int *flag, long long zw, long long zflag) {
+  W = in_slot(W, zw);
+  Rinv = in_slot(Rinv, zw);
+  flag = in_slot(flag, zflag);
   __shared__ double colbuf[2][KB_MAX];
   __shared__ double pivbuf[2];
   __shared__ double pivs[KB_MAX];
@@ -721,7 +780,11 @@ __device__ __forceinline__ double nr_rsq(double x) {
 // the k eigenvectors of largest eigenvalue as rows of Wk[k, kb], sigma[k] = lambda^1/2 (descending) and inv_sigma[k] =
 // lambda^-1/2 (0 where lambda = 0).
 __global__ __launch_bounds__(1024) void jacobi_kernel(const double *T, int kb, int k, int max_sweeps, float *Wk,
-                                                       float *inv_sigma, float *sigma) {
+                                                       float *inv_sigma, float *sigma, long long zw, long long zsigma) {
+  T = in_slot(T, zw);
+  Wk = in_slot(Wk, zw);
+  inv_sigma = in_slot(inv_sigma, zw);
+  sigma = in_slot(sigma, zsigma);
   extern __shared__ double Ms[];
   __shared__ int rotated;
   __shared__ double nrm2[KB_MAX];
@@ -828,7 +891,12 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const double *T, int kb, i
 __device__ __forceinline__ int clamp_label(int v, int k) { return v < 0 ? 0 : (v >= k ? k - 1 : v); }
 
 __global__ __launch_bounds__(256) void kmeans_init_kernel(const float *U, int N, int d, int k, const int *init_idx,
-                                                          float *centres, int *flag) {
+                                                          float *centres, int *flag, long long zu, long long zinit,
+                                                          long long zflag) {
+  U = in_slot(U, zu);
+  init_idx = in_slot(init_idx, zinit);
+  centres = in_slot(centres, zu);
+  flag = in_slot(flag, zflag);
   const int c = blockIdx.x;
   int r = init_idx[c];
   if (r < 0 || r >= N) {
@@ -843,175 +911,287 @@ __global__ __launch_bounds__(256) void kmeans_init_kernel(const float *U, int N,
 // when ctl[2] is up, so the host may enqueue passes ahead of knowing whether they are needed.
 constexpr int KM_DONE = 2, KM_PASSES = 3;
 
-// assignment pass `it`: 64 rows per workgroup staged in LDS beside the centres (rows padded with zeros to whole
-// float4s, which leaves every sum as it is); thread (row, g) scans the centres c = g, g + 4, ... four at a time (one
-// 16-byte broadcast read per centre and four dimensions), each sum running over the dimensions in ascending order; the
-// four candidates of a row are merged with ties to the lowest centre
-__global__ __launch_bounds__(256) void kmeans_assign_kernel(const float *U, int N, int d, const float *centres, int k,
-                                                            int *labels, int *ctl, int it) {
+// Pass `it`: assignment, and the sums of the clusters it touched.  One workgroup = one range of rows (rows_per of them, taken in
+// batches of KM_ROWS), the centres in LDS (rows of 16 NC + 4 floats, zeros behind the d-th).
+//
+// Assignment.  The label of a row u is the centre c with the least s(c) = sum (u_j - c_j)^2, a chain of float32 multiply-adds
+// over ascending j, ties to the lowest centre.  The products u . c of 16 rows and 16 centres at a time come from the float32 matrix
+// cores (fragments 16 c + 4 g + u of both operands, so 16-byte reads), which gives D(c) = |c|^2 - 2 u . c.  With
+// K = (5 d + 16) 2^-24, D(c) and s(c) - |u|^2 are within K (|u|^2 + |c|^2) of each other: 2^-23 d (|u|^2 + |c|^2) for the products
+// (half a unit more than round to nearest per step), (d + 4) 2^-24 (..) for |c|^2 and the last addition, (d + 3) 2^-24 |u - c|^2 for
+// the chain.  So the least D(c) names the label when every other D(c) (1 - K) lies above it by 2 K (|u|^2 + |c|^2) and more; the other
+// rows (ties, NaN and infinities among them) are queued and a wavefront evaluates s(c) itself for each, a centre a lane.  On the
+// embedding of a pool of 32768 samples in 100 dimensions fewer than one row in a thousand is queued.
+//
+// Sums.  A range whose labels stay as they were keeps its sums from the last pass; so do the clusters of a changed range that no
+// row entered or left.  Wavefront w takes the clusters w, w + 8, ...: the rows of a cluster come out of a ballot in ascending
+// order, lane l adds dimensions l and l + 64 in float64 in that order.  pcnt = 0 stands for sums that were never written.
+//
+// Three subsamples of 32768 rows, 100 centres in 100 dimensions: 83 us in the first pass, 42 in the late ones, where one
+// subsample took 48 for an assignment on the vector units and 32 for sums by LDS atomics.  The products are what is left:
+// 392 instructions of 32 cycles a wavefront, on 384 workgroups, so half the compute units have two.
+constexpr int KM_ROWS = 256;
+typedef float kmv4 __attribute__((ext_vector_type(4)));
+
+template <int NC, bool V4>
+__global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N, int d, const float *centres, int k, int rows_per,
+                                                          int *labels, double *psum, int *pcnt, int *dirty, int *ctl, int it,
+                                                          long long zu, long long zlab, long long zw, long long zctl) {
+  ctl = in_slot(ctl, zctl);
   if (ctl[KM_DONE]) return;
+  U = in_slot(U, zu);
+  centres = in_slot(centres, zu);
+  labels = in_slot(labels, zlab);
+  psum = in_slot(psum, zw);
+  pcnt = in_slot(pcnt, zw);
+  dirty = in_slot(dirty, zw);
+  constexpr int DP = 16 * NC, S = DP + 4, NW = 8;
   extern __shared__ float sm[];
-  const int dp = (d + 3) & ~3;
-  float *cs = sm;                       // [k][dp]
-  float *us = sm + k * dp;              // [64][dp + 1]
-  __shared__ float bd[4][64];
-  __shared__ int bi[4][64];
-  const int tid = threadIdx.x, row = tid & 63, g = tid >> 6;
-  const int r0 = blockIdx.x * 64;
+  const int k16 = (k + 15) & ~15;
+  float *const cs = sm, *const cn = sm + k16 * S;
+  __shared__ int lab_s[KM_ROWS], queue[KM_ROWS], queued, changed, touched[KB_MAX];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ql = lane & 15, g = lane >> 4;
+  const float kappa = (float)(5 * d + 16) * 5.9604645e-8f;
   if (blockIdx.x == 0 && tid == 0) atomicAdd(&ctl[KM_PASSES], 1);
-  for (int u = tid; u < k * dp; u += 256) {
-    const int c = u / dp, j = u - c * dp;
-    const float v = centres[j < d ? c * d + j : 0];
-    cs[u] = j < d ? v : 0.f;
+  if (tid == 0) {
+    queued = 0;
+    changed = 0;
   }
-  for (int u = tid; u < 64 * dp; u += 256) {
-    const int rr = u / dp, j = u - rr * dp;
-    const bool ok = r0 + rr < N && j < d;
-    const float v = U[ok ? (long long)(r0 + rr) * d + j : 0];
-    us[rr * (dp + 1) + j] = ok ? v : 0.f;
+  if (tid < KB_MAX) touched[tid] = it == 0;       // the first pass writes every count
+  for (int u = tid; u < k16 * DP; u += 512) {
+    const int c = u / DP, j = u - c * DP;
+    const bool in = c < k && j < d;
+    const float v = centres[in ? c * d + j : 0];
+    cs[c * S + j] = in ? v : 0.f;
   }
   __syncthreads();
-  float best = INFINITY;
-  int besti = 0x7fffffff;
-  const float *u = us + row * (dp + 1);
-  for (int c0 = g; c0 < k; c0 += 16) {
-    const float *p0 = cs + c0 * dp;
-    const float *p1 = cs + (c0 + 4 < k ? c0 + 4 : c0) * dp;
-    const float *p2 = cs + (c0 + 8 < k ? c0 + 8 : c0) * dp;
-    const float *p3 = cs + (c0 + 12 < k ? c0 + 12 : c0) * dp;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    for (int j = 0; j < dp; j += 4) {
-      const float4 a0 = *(const float4 *)(p0 + j), a1 = *(const float4 *)(p1 + j);
-      const float4 a2 = *(const float4 *)(p2 + j), a3 = *(const float4 *)(p3 + j);
-      const float u0 = u[j], u1 = u[j + 1], u2 = u[j + 2], u3 = u[j + 3];
-      float t;
-      t = u0 - a0.x; s0 = fmaf(t, t, s0); t = u1 - a0.y; s0 = fmaf(t, t, s0);
-      t = u2 - a0.z; s0 = fmaf(t, t, s0); t = u3 - a0.w; s0 = fmaf(t, t, s0);
-      t = u0 - a1.x; s1 = fmaf(t, t, s1); t = u1 - a1.y; s1 = fmaf(t, t, s1);
-      t = u2 - a1.z; s1 = fmaf(t, t, s1); t = u3 - a1.w; s1 = fmaf(t, t, s1);
-      t = u0 - a2.x; s2 = fmaf(t, t, s2); t = u1 - a2.y; s2 = fmaf(t, t, s2);
-      t = u2 - a2.z; s2 = fmaf(t, t, s2); t = u3 - a2.w; s2 = fmaf(t, t, s2);
-      t = u0 - a3.x; s3 = fmaf(t, t, s3); t = u1 - a3.y; s3 = fmaf(t, t, s3);
-      t = u2 - a3.z; s3 = fmaf(t, t, s3); t = u3 - a3.w; s3 = fmaf(t, t, s3);
-    }
-    if (s0 < best) { best = s0; besti = c0; }
-    if (c0 + 4 < k && s1 < best) { best = s1; besti = c0 + 4; }
-    if (c0 + 8 < k && s2 < best) { best = s2; besti = c0 + 8; }
-    if (c0 + 12 < k && s3 < best) { best = s3; besti = c0 + 12; }
+  {
+    const int c = tid >> 2, q = tid & 3;          // four lanes a centre
+    float s = 0.f;
+    if (c < k16)
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const kmv4 v = *(const kmv4 *)(cs + c * S + 16 * i + 4 * q);
+        s = fmaf(v[0], v[0], s);
+        s = fmaf(v[1], v[1], s);
+        s = fmaf(v[2], v[2], s);
+        s = fmaf(v[3], v[3], s);
+      }
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    if (c < k16 && q == 0) cn[c] = c < k ? s * (1.f - kappa) : INFINITY;
   }
-  bd[g][row] = best;
-  bi[g][row] = besti;
   __syncthreads();
-  if (g == 0 && r0 + row < N) {
-    for (int q = 1; q < 4; ++q) {
-      const float s = bd[q][row];
-      const int c = bi[q][row];
-      if (s < best || (s == best && c < besti)) {
-        best = s;
-        besti = c;
+
+  const int r0 = blockIdx.x * rows_per, r1 = min(N, r0 + rows_per);
+  for (int b0 = r0; b0 < r1; b0 += KM_ROWS) {
+    kmv4 uf[2][NC];
+    float un[2], v1[2], v2[2];
+    int i1[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float *u = U + (long long)min(b0 + wave * 32 + 16 * j + ql, N - 1) * d;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int f = 16 * c + 4 * g;
+        if (V4) {
+          const kmv4 v = *(const kmv4 *)(u + min(f, d - 4));
+          uf[j][c] = f < d ? v : (kmv4){0.f, 0.f, 0.f, 0.f};
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v = u[min(f + e, d - 1)];
+            uf[j][c][e] = f + e < d ? v : 0.f;
+          }
+        }
       }
     }
-    if (labels[r0 + row] != besti) {
-      labels[r0 + row] = besti;
-      atomicAdd(&ctl[it & 1], 1);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      float s = 0.f;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = fmaf(uf[j][c][e], uf[j][c][e], s);
+      s += __shfl_xor(s, 16, 64);
+      s += __shfl_xor(s, 32, 64);
+      un[j] = s;
+      v1[j] = v2[j] = INFINITY;
+      i1[j] = 0x7fffffff;
+    }
+    for (int kt = 0; kt < k16; kt += 16) {
+      kmv4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const kmv4 kf = *(const kmv4 *)(cs + (kt + ql) * S + 16 * c + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], uf[j][c][e], acc[j], 0, 0, 0);
+      }
+      const kmv4 c4 = *(const kmv4 *)(cn + kt + 4 * g);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float v = fmaf(-2.f, acc[j][r], c4[r]);
+          const bool less = v < v1[j];
+          v2[j] = less ? v1[j] : fminf(v2[j], v);
+          i1[j] = less ? kt + 4 * g + r : i1[j];
+          v1[j] = less ? v : v1[j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+      for (int o = 16; o <= 32; o <<= 1) {
+        const float a1 = __shfl_xor(v1[j], o, 64), a2 = __shfl_xor(v2[j], o, 64);
+        const int ai = __shfl_xor(i1[j], o, 64);
+        const bool other = a1 < v1[j] || (a1 == v1[j] && ai < i1[j]);
+        v2[j] = fminf(other ? v1[j] : v2[j], other ? a2 : a1);
+        v1[j] = other ? a1 : v1[j];
+        i1[j] = other ? ai : i1[j];
+      }
+      const int rr = wave * 32 + 16 * j + ql;
+      if (g == 0 && b0 + rr < r1) {
+        const float cb = i1[j] < k ? cn[i1[j]] : INFINITY;
+        if (v2[j] - v1[j] > 2.2f * kappa * (cb + un[j]) + 1e-34f) lab_s[rr] = i1[j];
+        else queue[atomicAdd(&queued, 1)] = rr;
+      }
+    }
+    __syncthreads();
+    for (int q = wave; q < queued; q += NW) {
+      const int rr = queue[q];
+      const float *u = U + (long long)(b0 + rr) * d;
+      const float *ca = cs + (lane < k ? lane : 0) * S, *cb = cs + (lane + 64 < k ? lane + 64 : 0) * S;
+      float sa = 0.f, sb = 0.f;
+      for (int j = 0; j < d; ++j) {
+        const float v = u[j], ta = v - ca[j], tb = v - cb[j];
+        sa = fmaf(ta, ta, sa);
+        sb = fmaf(tb, tb, sb);
+      }
+      float best = INFINITY;
+      int besti = 0x7fffffff;
+      if (lane < k && sa < best) { best = sa; besti = lane; }
+      if (lane + 64 < k && sb < best) { best = sb; besti = lane + 64; }
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const float s = __shfl_xor(best, o, 64);
+        const int c = __shfl_xor(besti, o, 64);
+        if (s < best || (s == best && c < besti)) { best = s; besti = c; }
+      }
+      if (lane == 0) lab_s[rr] = besti;
+    }
+    __syncthreads();
+    bool moved = false;
+    if (tid < KM_ROWS && b0 + tid < r1) {
+      const int was = labels[b0 + tid], is = lab_s[tid];
+      moved = was != is;
+      if (moved) {
+        labels[b0 + tid] = is;
+        touched[clamp_label(is, k)] = 1;
+        if (was >= 0) touched[clamp_label(was, k)] = 1;
+      }
+    }
+    const int n = (int)__popcll(__builtin_amdgcn_ballot_w64(moved));
+    if (n && lane == 0) {
+      atomicAdd(&ctl[it & 1], n);
+      changed = 1;
+    }
+    if (tid == 0) queued = 0;
+    __syncthreads();                              // before the next batch queues rows and writes labels
+  }
+  if (!changed) return;                           // the same value in every thread
+
+  double *const ps = psum + (long long)blockIdx.x * k * d;
+  for (int c = wave; c < k; c += NW) {
+    if (!touched[c]) continue;
+    double s0 = 0.0, s1 = 0.0;
+    int count = 0;
+    const int ja = min(lane, d - 1), jb = min(lane + 64, d - 1);
+    for (int b0 = r0; b0 < r1; b0 += KM_ROWS) {
+#pragma unroll
+      for (int q = 0; q < KM_ROWS / 64; ++q) {
+        const int row = b0 + 64 * q + lane;
+        const int l = b0 == r0 && r1 - r0 <= KM_ROWS ? lab_s[64 * q + lane] : labels[min(row, N - 1)];
+        unsigned long long rows = __builtin_amdgcn_ballot_w64(row < r1 && clamp_label(l, k) == c);
+        count += (int)__popcll(rows);
+        const float *base = U + (long long)(b0 + 64 * q) * d;
+        while (rows) {                            // eight rows at a time (the last one repeated), added in ascending order
+          float a[8], b[8];
+          int have = 0;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const int r = (int)__builtin_ctzll(rows);
+            a[i] = base[(long long)r * d + ja];
+            b[i] = base[(long long)r * d + jb];
+            have = i + 1;
+            const unsigned long long rest = rows & (rows - 1);
+            if (!rest) { rows = 0; break; }
+            rows = rest;
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (i < have) {
+              s0 += (double)a[i];
+              s1 += (double)b[i];
+            }
+        }
+      }
+    }
+    if (count) {
+      if (lane < d) ps[c * d + lane] = s0;
+      if (lane + 64 < d) ps[c * d + lane + 64] = s1;
+    }
+    if (lane == 0) {
+      pcnt[blockIdx.x * k + c] = count;
+      dirty[c] = 1;
     }
   }
 }
 
-// update pass, stage 1: workgroup b walks its range of rows in ascending order, thread j owning dimension j, and adds
-// each row to its cluster's fp64 sums in LDS (LDS adds without return value: the adds of one thread to one address
-// are carried out in program order, so the sums are those of the rows in ascending order; 32 rows are loaded ahead);
-// stage 2 adds the workgroups' sums in order.  An empty cluster keeps its centre.  Nothing happens when the pass
-// changed no label.
-__global__ __launch_bounds__(128) void kmeans_partial_kernel(const float *U, int N, int d, const int *labels, int k,
-                                                             int rows_per, double *psum, int *pcnt, const int *ctl,
-                                                             int it) {
-  if (ctl[KM_DONE] || ctl[it & 1] == 0) return;
-  extern __shared__ double accs[];      // [k][d]
-  __shared__ int cnt[KB_MAX];
-  const int j = threadIdx.x;
-  for (int u = j; u < k * d; u += 128) accs[u] = 0.0;
-  for (int u = j; u < k; u += 128) cnt[u] = 0;
-  __syncthreads();
-  const int r0 = blockIdx.x * rows_per, r1 = min(N, r0 + rows_per);
-  const int jj = j < d ? j : 0;
-  int r = r0;
-  constexpr int RB = 32;                  // rows per batch; two batches are in flight
-  int c[RB], cn[RB];
-  float v[RB], vn[RB];
-  if (r + RB <= r1) {
-#pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      c[i] = labels[r + i];
-      v[i] = U[(long long)(r + i) * d + jj];
-    }
-  }
-  for (; r + RB <= r1; r += RB) {
-    // the next batch is requested before this one is added (clamped to the range: the last request repeats rows)
-    const int rn = r + 2 * RB <= r1 ? r + RB : r;
-#pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      cn[i] = labels[rn + i];
-      vn[i] = U[(long long)(rn + i) * d + jj];
-    }
-#pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      const int ci = clamp_label(c[i], k);
-      if (j < d) atomicAdd(&accs[ci * d + j], (double)v[i]);
-      if (j == 0) atomicAdd(&cnt[ci], 1);
-    }
-#pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      c[i] = cn[i];
-      v[i] = vn[i];
-    }
-  }
-  for (; r < r1; ++r) {
-    const int c = clamp_label(labels[r], k);
-    if (j < d) atomicAdd(&accs[c * d + j], (double)U[(long long)r * d + j]);
-    if (j == 0) atomicAdd(&cnt[c], 1);
-  }
-  __syncthreads();
-  double *ps = psum + (long long)blockIdx.x * k * d;
-  for (int u = j; u < k * d; u += 128) ps[u] = accs[u];
-  for (int u = j; u < k; u += 128) pcnt[blockIdx.x * k + u] = cnt[u];
-}
-
-// stage 2, and the bookkeeping of pass `it`: a pass that changed nothing raises ctl[2]; otherwise the other pass
-// parity's counter is cleared for the next pass (nothing reads it during this kernel)
-__global__ __launch_bounds__(64) void kmeans_finish_kernel(const double *psum, const int *pcnt, int nb, int k, int d,
-                                                           float *centres, int *ctl, int it) {
+// New centres of the clusters the pass touched, one workgroup each: the ranges' sums added in order (an empty cluster keeps its
+// centre); and the bookkeeping of pass `it`: a pass that changed nothing raises ctl[2], otherwise the other pass parity's
+// counter is cleared for the next pass (nothing reads it during this kernel).
+__global__ __launch_bounds__(128) void kmeans_finish_kernel(const double *psum, const int *pcnt, int nb, int k, int d,
+                                                           float *centres, int *dirty, int *ctl, int it, long long zu, long long zw,
+                                                           long long zctl) {
+  ctl = in_slot(ctl, zctl);
   if (ctl[KM_DONE]) return;
+  psum = in_slot(psum, zw);
+  pcnt = in_slot(pcnt, zw);
+  dirty = in_slot(dirty, zw);
+  centres = in_slot(centres, zu);
   if (ctl[it & 1] == 0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) ctl[KM_DONE] = 1;
     return;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) ctl[(it + 1) & 1] = 0;
-  const int u = blockIdx.x * 64 + threadIdx.x;
-  if (u >= k * d) return;
-  const int c = u / d;
+  const int c = blockIdx.x, j = threadIdx.x;
+  if (!dirty[c]) return;
+  __syncthreads();
+  if (j == 0) dirty[c] = 0;
+  if (j >= d) return;
   double tot = 0.0;
   int m = 0;
-  int b = 0;
-  for (; b + 16 <= nb; b += 16) {
-    double t[16];
-    int q[16];
+  constexpr int AHEAD = 32;
+  for (int b = 0; b < nb; b += AHEAD) {
+    double t[AHEAD];
+    int q[AHEAD];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      t[i] = psum[(long long)(b + i) * k * d + u];
-      q[i] = pcnt[(b + i) * k + c];
+    for (int i = 0; i < AHEAD; ++i) {
+      const int bb = min(b + i, nb - 1);
+      q[i] = pcnt[bb * k + c];
+      t[i] = psum[((long long)bb * k + c) * d + j];
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      tot += t[i];
-      m += q[i];
-    }
+    for (int i = 0; i < AHEAD; ++i)
+      if (b + i < nb && q[i] > 0) {               // a count of 0: sums of an earlier pass, or none
+        tot += t[i];
+        m += q[i];
+      }
   }
-  for (; b < nb; ++b) {
-    tot += psum[(long long)b * k * d + u];
-    m += pcnt[b * k + c];
-  }
-  if (m > 0) centres[u] = (float)(tot / (double)m);
+  if (m > 0) centres[c * d + j] = (float)(tot / (double)m);
 }
 
 // ---------------------------------------------------------------------------------------------- aggregation
@@ -1158,29 +1338,32 @@ struct EmbedWork {
 };
 
 struct SmallWork {      // k-means (N rows of d dimensions), aggregation, normalisation
-  int *flag, *changed, *T, *perm, *pcnt;
+  int *flag, *T, *perm, *pcnt, *dirty;
   double *psum;
   size_t bytes;
   SmallWork(void *w, int N, int d, int k) {
     Carve c(w);
     flag = c.take<int>(64);
-    changed = c.take<int>(64);
     T = c.take<int>((size_t)k * k);
     perm = c.take<int>((size_t)M_MAX * k);
     pcnt = c.take<int>((size_t)kmeans_blocks(N) * k);
+    dirty = c.take<int>(k);
     psum = c.take<double>((size_t)kmeans_blocks(N) * k * d);
     bytes = c.off + 256;
   }
 };
 
+// rows of the matrices with n columns in the workspace are padded to whole 16-byte loads
+int padded(int n) { return (n + 3) & ~3; }
+
 struct ClusterWork {
   float *A, *dr, *dc, *U, *sigma, *centres;
-  int *flags;           // [4]: index, degree, rank, initial-centre checks of a deferred run
+  int *flags;           // [MAX_SLOTS][SLOT_WORDS], those of the group in its first subsample's workspace
   void *sub;            // region handed to the calls above
   size_t sub_bytes, bytes;
   ClusterWork(void *w, int N, int F, int n, int k, int kb) {
     Carve c(w);
-    A = c.take<float>((size_t)N * n);
+    A = c.take<float>((size_t)N * padded(n));
     dr = c.take<float>(N);
     dc = c.take<float>(n);
     U = c.take<float>((size_t)N * k);
@@ -1189,7 +1372,7 @@ struct ClusterWork {
     flags = c.take<int>(64);
     // the k-means region is sized for rows of up to kb dimensions, so that the one size also covers qc_tap_kmeans
     // on an embedding of the whole iteration block
-    size_t s1 = SimWork(nullptr, N, F, n).bytes, s2 = EmbedWork(nullptr, N, n, k, kb).bytes, s3 = SmallWork(nullptr, N, kb, kb).bytes;
+    size_t s1 = SimWork(nullptr, N, F, n).bytes, s2 = EmbedWork(nullptr, N, padded(n), k, kb).bytes, s3 = SmallWork(nullptr, N, kb, kb).bytes;
     sub_bytes = s1 > s2 ? s1 : s2;
     if (s3 > sub_bytes) sub_bytes = s3;
     sub = c.take<char>(sub_bytes);
@@ -1219,47 +1402,40 @@ struct SimProfile {
   bool on = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev;
   size_t used = 0;
+  int products = 0;
 };
 SimProfile g_prof;
 
-// Each stage below takes `ext`: null = use the flag word in its own workspace and report the error before returning
-// (the stage waits for the stream); non-null = raise that device flag instead and only enqueue (the caller reads the
-// flags of several stages, possibly of several streams, later).
-// Internal streams and events of one qc_tap_cluster call (default priority).  They belong to the call, not to the
-// process: calls from several host threads, or on several devices, share nothing.
+// Each stage below works on a group of nz subsamples in one launch per kernel (grid z), whose workspaces lie `zw` bytes apart
+// (0 with a single one), and takes `ext`: null = use the flag word in its own workspace and report the error before
+// returning (the stage waits for the stream); non-null = raise that device flag instead (SLOT_WORDS words from one subsample's to
+// the next) and only enqueue: the caller reads the flags of all stages later.
 constexpr int MAX_SLOTS = 3;
-struct CallStreams {
-  hipStream_t streams[MAX_SLOTS] = {nullptr, nullptr, nullptr};
-  hipEvent_t fork = nullptr;
-  hipEvent_t chain[MAX_SLOTS] = {nullptr, nullptr, nullptr};
-  ~CallStreams() {
-    for (int j = 0; j < MAX_SLOTS; ++j) {
-      if (streams[j]) { (void)hipStreamSynchronize(streams[j]); (void)hipStreamDestroy(streams[j]); }
-      if (chain[j]) (void)hipEventDestroy(chain[j]);
-    }
-    if (fork) (void)hipEventDestroy(fork);
-  }
+constexpr int SLOT_WORDS = 16;          // a subsample's flags (index, degree, rank, initial centres), then its k-means control words
+constexpr int SLOT_CTL = 4;
+constexpr long long ZF = SLOT_WORDS * sizeof(int);
+struct Group {
+  int nz;
+  long long zw;
 };
 
-// `gemm_after` (may be null): the contraction starts after this event.  A caller that runs several subsamples on
-// several streams chains them (embed_impl records the matching event after its own large product), so that the
-// chip-filling products run one after the other and only the small, latency-bound kernels overlap.
-int similarity_impl(const float *X, const float *t, int N, int F, const int *idx, int n, float alpha, float *A,
-                    float *d_r, float *d_c, void *work, hipStream_t st, int *ext = nullptr,
-                    hipEvent_t gemm_after = nullptr) {
+// idx of the group's subsamples lie one behind the other; A has rows of lda floats
+int similarity_impl(const float *X, const float *t, int N, int F, const int *idx, int n, float alpha, float *A, int lda,
+                    float *d_r, float *d_c, void *work, Group gr, hipStream_t st, int *ext = nullptr) {
   SimWork w(work, N, F, n);
   int *fl = ext ? ext : w.flag;
-  if (!ext) hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, st, w.flag, 64, 0);
-  hipLaunchKernelGGL(rownorm_kernel, dim3((N + 3) / 4), dim3(256), 0, st, X, N, F, w.rinv);
-  hipLaunchKernelGGL(gather_kernel, dim3(n), dim3(256), 0, st, X, w.rinv, t, idx, N, F, w.Xs, w.cs, w.tc, fl);
+  const unsigned nz = (unsigned)gr.nz;
+  if (!ext) hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, st, w.flag, 64, 0, 0ll);
+  hipLaunchKernelGGL(rownorm_kernel, dim3((N + 3) / 4), dim3(256), 0, st, X, N, F, w.rinv);      // once for the whole group
+  hipLaunchKernelGGL(gather_kernel, dim3(n, 1, nz), dim3(256), 0, st, X, w.rinv, t, idx, N, F, w.Xs, w.cs, w.tc, fl,
+                     (long long)n * sizeof(int), gr.zw, ZF);
   TAP_HIP(hipGetLastError());
   SgemmArgs g{};
   g.A = X; g.sam = F; g.sak = 1;
-  g.B = w.Xs; g.sbn = F; g.sbk = 1;
-  g.C = A; g.ldc = n;
+  g.B = w.Xs; g.sbn = F; g.sbk = 1; g.zb = gr.zw;
+  g.C = A; g.ldc = lda; g.zc = gr.zw;
   g.M = N; g.N = n; g.K = F;
-  g.rs = w.rinv; g.cs = w.cs; g.tr = t; g.tc = w.tc; g.alpha = alpha;
-  if (gemm_after) TAP_HIP(hipStreamWaitEvent(st, gemm_after, 0));
+  g.rs = w.rinv; g.cs = w.cs; g.tr = t; g.tc = w.tc; g.alpha = alpha; g.zcs = gr.zw; g.ztc = gr.zw;
   if (g_prof.on) {
     if (g_prof.used == g_prof.ev.size()) {
       hipEvent_t a, b;
@@ -1269,11 +1445,14 @@ int similarity_impl(const float *X, const float *t, int N, int F, const int *idx
     }
     TAP_HIP(hipEventRecord(g_prof.ev[g_prof.used].first, st));
   }
-  TAP_HIP(sgemm(g, SE_SIM, st));
-  if (g_prof.on) TAP_HIP(hipEventRecord(g_prof.ev[g_prof.used++].second, st));
-  hipLaunchKernelGGL(rowsum_kernel, dim3((N + 3) / 4), dim3(256), 0, st, A, N, n, d_r);
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3((n + 63) / 64, COL_CHUNKS), dim3(256), 0, st, A, N, n, w.colpart);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((n + 255) / 256), dim3(256), 0, st, w.colpart, n, d_c);
+  TAP_HIP(sgemm(g, SE_SIM, gr.nz, st));
+  if (g_prof.on) {
+    TAP_HIP(hipEventRecord(g_prof.ev[g_prof.used++].second, st));
+    g_prof.products += gr.nz;
+  }
+  hipLaunchKernelGGL(rowsum_kernel, dim3((N + 3) / 4, 1, nz), dim3(256), 0, st, A, N, n, lda, d_r, gr.zw);
+  hipLaunchKernelGGL(colsum_partial_kernel, dim3((n + 63) / 64, COL_CHUNKS, nz), dim3(256), 0, st, A, N, n, lda, w.colpart, gr.zw);
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((n + 255) / 256, 1, nz), dim3(256), 0, st, w.colpart, n, d_c, gr.zw);
   TAP_HIP(hipGetLastError());
   if (ext) return QC_OK;
   int flag = 0;
@@ -1282,13 +1461,13 @@ int similarity_impl(const float *X, const float *t, int N, int F, const int *idx
   return QC_OK;
 }
 
-int normalise_impl(float *A, const float *d_r, const float *d_c, int N, int n, void *work, hipStream_t st,
+int normalise_impl(float *A, const float *d_r, const float *d_c, int N, int n, int lda, void *work, Group gr, hipStream_t st,
                    int *ext = nullptr) {
   SmallWork w(work, 1, 1, 1);
   int *fl = ext ? ext : w.flag;
-  if (!ext) hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, st, w.flag, 64, 0);
-  hipLaunchKernelGGL(degree_check_kernel, dim3((N + 255) / 256), dim3(256), 0, st, d_r, N, fl);
-  hipLaunchKernelGGL(degree_check_kernel, dim3((n + 255) / 256), dim3(256), 0, st, d_c, n, fl);
+  const unsigned nz = (unsigned)gr.nz;
+  if (!ext) hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, st, w.flag, 64, 0, 0ll);
+  hipLaunchKernelGGL(degree_check_kernel, dim3((N + n + 255) / 256, 1, nz), dim3(256), 0, st, d_r, N, d_c, n, fl, gr.zw, ZF);
   TAP_HIP(hipGetLastError());
   if (!ext) {
     int flag = 0;
@@ -1296,8 +1475,8 @@ int normalise_impl(float *A, const float *d_r, const float *d_c, int N, int n, v
     if (flag) TAP_FAIL(QC_ERR_RANGE, "a degree of the similarity matrix is not positive and finite");
   }
   // with a deferred check the kernel itself leaves the matrix alone when the flag is up
-  hipLaunchKernelGGL(normalise_kernel, dim3(((n + 255) / 256) * N), dim3(256), 0, st, A, d_r, d_c, N, n,
-                     ext ? (const int *)ext : (const int *)nullptr);
+  hipLaunchKernelGGL(normalise_kernel, dim3(((lda + 255) / 256) * N, 1, nz), dim3(256), 0, st, A, d_r, d_c, N, n, lda,
+                     ext ? (const int *)ext : (const int *)nullptr, gr.zw, ZF);
   TAP_HIP(hipGetLastError());
   if (!ext) TAP_HIP(hipStreamSynchronize(st));
   return QC_OK;
@@ -1307,91 +1486,100 @@ hipError_t set_lds(const void *kern, size_t bytes) {
   return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// one pass of shifted Cholesky QR on the rows of `in` [kb, n] into `out` (`in` and `out` must differ)
-int cholqr_pass(const float *in, float *out, int kb, int n, int check, EmbedWork &w, int *fl, hipStream_t st) {
+// one pass of shifted Cholesky QR on the rows of `in` [kb, n] into `out` (`in` and `out` must differ); zin: bytes from one
+// subsample's rows to the next
+int cholqr_pass(const float *in, long long zin, float *out, int kb, int n, int check, EmbedWork &w, Group gr, int *fl, hipStream_t st) {
   const int parts = gram_parts(n);
-  hipLaunchKernelGGL(gram_partial_kernel, dim3(parts), dim3(256), 0, st, in, kb, n, (long long)n, 1ll, gram_chunk(n),
-                     w.part);
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((kb * kb + 255) / 256), dim3(256), 0, st, w.part, parts, kb * kb, w.W);
-  hipLaunchKernelGGL(chol_inv_kernel, dim3(1), dim3(1024), 0, st, w.W, kb, 1e-12, check, w.Rinv, fl);
+  const unsigned nz = (unsigned)gr.nz;
+  hipLaunchKernelGGL(gram_partial_kernel, dim3(parts, 1, nz), dim3(256), 0, st, in, kb, n, (long long)n, 1ll, gram_chunk(n),
+                     w.part, zin, gr.zw);
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((kb * kb + 255) / 256, 1, nz), dim3(256), 0, st, w.part, parts, kb * kb, w.W, gr.zw);
+  hipLaunchKernelGGL(chol_inv_kernel, dim3(1, 1, nz), dim3(1024), 0, st, w.W, kb, 1e-12, check, w.Rinv, fl, gr.zw, ZF);
   TAP_HIP(hipGetLastError());
   SgemmArgs g{};
-  g.A = w.Rinv; g.sam = kb; g.sak = 1;
-  g.B = in; g.sbn = 1; g.sbk = n;
-  g.C = out; g.ldc = n;
+  g.A = w.Rinv; g.sam = kb; g.sak = 1; g.za = gr.zw;
+  g.B = in; g.sbn = 1; g.sbk = n; g.zb = zin;
+  g.C = out; g.ldc = n; g.zc = gr.zw;
   g.M = kb; g.N = n; g.K = kb;
-  TAP_HIP(sgemm(g, SE_PLAIN, st));
+  TAP_HIP(sgemm(g, SE_PLAIN, gr.nz, st));
   return QC_OK;
 }
 
 // rows of `in` made orthonormal into w.Q: three passes, which is enough for a block whose condition number is as
 // large as 10^12 (the power iteration multiplies by L^T L, whose small eigenvalues are rounding noise in fp32); uses
 // w.Z and w.Y as intermediates (`in` may be w.Y)
-int orthonormalise(const float *in, EmbedWork &w, int kb, int n, int *fl, hipStream_t st) {
-  TAP_RC(cholqr_pass(in, w.Z, kb, n, 0, w, fl, st));
-  TAP_RC(cholqr_pass(w.Z, w.Y, kb, n, 0, w, fl, st));
-  TAP_RC(cholqr_pass(w.Y, w.Q, kb, n, 1, w, fl, st));
+int orthonormalise(const float *in, long long zin, EmbedWork &w, int kb, int n, Group gr, int *fl, hipStream_t st) {
+  TAP_RC(cholqr_pass(in, zin, w.Z, kb, n, 0, w, gr, fl, st));
+  TAP_RC(cholqr_pass(w.Z, gr.zw, w.Y, kb, n, 0, w, gr, fl, st));
+  TAP_RC(cholqr_pass(w.Y, gr.zw, w.Q, kb, n, 1, w, gr, fl, st));
   return QC_OK;
 }
 
 // Between two multiplications of the power iteration one pass is enough: the next product only needs rows that span
 // the same space and are well conditioned (a single shifted pass leaves them orthonormal to about the square of the
 // block's condition number times the fp64 rounding, far from dependent); `in` must not be w.Q
-int recondition(const float *in, EmbedWork &w, int kb, int n, int *fl, hipStream_t st) {
-  return cholqr_pass(in, w.Q, kb, n, 0, w, fl, st);
+int recondition(const float *in, long long zin, EmbedWork &w, int kb, int n, Group gr, int *fl, hipStream_t st) {
+  return cholqr_pass(in, zin, w.Q, kb, n, 0, w, gr, fl, st);
 }
 
-// `big_done` (may be null) is recorded after the one chip-filling product of this stage (L^T L)
-int embed_impl(const float *L, int N, int n, int k, int kb, int iters, const float *q0, float *U, float *sigma,
-               void *work, hipStream_t st, int *ext = nullptr, hipEvent_t big_done = nullptr) {
+// L has rows of n floats and q0 rows of n0 <= n; the columns of L beyond n0 are zero.  The results U, sigma lie zout bytes apart.
+int embed_impl(const float *L, int N, int n, int n0, int k, int kb, int iters, const float *q0, float *U, float *sigma, long long zout,
+               void *work, Group gr, hipStream_t st, int *ext = nullptr) {
   EmbedWork w(work, N, n, k, kb);
   int *fl = ext ? ext : w.flag;
-  if (!ext) hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, st, w.flag, 64, 0);
+  const unsigned nz = (unsigned)gr.nz;
+  if (!ext) hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, st, w.flag, 64, 0, 0ll);
   TAP_HIP(hipGetLastError());
   // G = L^T L drives the power iteration (its fp32 rounding only slows the convergence of directions whose singular
   // values are below about 3e-4 of the largest; the Rayleigh-Ritz step below works on L itself)
   SgemmArgs g{};
-  g.A = L; g.sam = 1; g.sak = n;
-  g.B = L; g.sbn = 1; g.sbk = n;
-  g.C = w.G; g.ldc = n;
+  g.A = L; g.sam = 1; g.sak = n; g.za = gr.zw;
+  g.B = L; g.sbn = 1; g.sbk = n; g.zb = gr.zw;
+  g.C = w.G; g.ldc = n; g.zc = gr.zw; g.zpart = gr.zw;
   g.M = n; g.N = n; g.K = N;
   g.sym = 1;
-  TAP_HIP(sgemm(g, SE_PLAIN, st, w.spart, w.spart_elems));
-  if (big_done) TAP_HIP(hipEventRecord(big_done, st));
-  if (iters > 0) TAP_RC(recondition(q0, w, kb, n, fl, st));
-  else TAP_RC(orthonormalise(q0, w, kb, n, fl, st));
+  TAP_HIP(sgemm(g, SE_PLAIN, gr.nz, st, w.spart, w.spart_elems));
+  const float *start = q0;
+  long long zstart = 0;
+  if (n != n0) {
+    hipLaunchKernelGGL(pad_rows_kernel, dim3(kb, 1, nz), dim3(256), 0, st, q0, n0, w.Y, n, gr.zw);
+    start = w.Y;
+    zstart = gr.zw;
+  }
+  if (iters > 0) TAP_RC(recondition(start, zstart, w, kb, n, gr, fl, st));
+  else TAP_RC(orthonormalise(start, zstart, w, kb, n, gr, fl, st));
   SgemmArgs mul{};
-  mul.A = w.Q; mul.sam = n; mul.sak = 1;
-  mul.B = w.G; mul.sbn = n; mul.sbk = 1;      // G is symmetric
-  mul.C = w.Y; mul.ldc = n;
+  mul.A = w.Q; mul.sam = n; mul.sak = 1; mul.za = gr.zw;
+  mul.B = w.G; mul.sbn = n; mul.sbk = 1; mul.zb = gr.zw;      // G is symmetric
+  mul.C = w.Y; mul.ldc = n; mul.zc = gr.zw; mul.zpart = gr.zw;
   mul.M = kb; mul.N = n; mul.K = n;
   for (int it = 0; it < iters; ++it) {
-    TAP_HIP(sgemm(mul, SE_PLAIN, st, w.spart, w.spart_elems));
-    if (it + 1 < iters) TAP_RC(recondition(w.Y, w, kb, n, fl, st));
-    else TAP_RC(orthonormalise(w.Y, w, kb, n, fl, st));      // the final basis: orthonormal to fp32 level
+    TAP_HIP(sgemm(mul, SE_PLAIN, gr.nz, st, w.spart, w.spart_elems));
+    if (it + 1 < iters) TAP_RC(recondition(w.Y, gr.zw, w, kb, n, gr, fl, st));
+    else TAP_RC(orthonormalise(w.Y, gr.zw, w, kb, n, gr, fl, st));      // the final basis: orthonormal to fp32 level
   }
   // Rayleigh-Ritz on B = L Q^T [N, kb]: T = B^T B (fp64), its k leading eigenvectors W, U = B W^T diag(1 / sigma)
   SgemmArgs bm{};
-  bm.A = L; bm.sam = n; bm.sak = 1;
-  bm.B = w.Q; bm.sbn = n; bm.sbk = 1;
-  bm.C = w.Bm; bm.ldc = kb;
+  bm.A = L; bm.sam = n; bm.sak = 1; bm.za = gr.zw;
+  bm.B = w.Q; bm.sbn = n; bm.sbk = 1; bm.zb = gr.zw;
+  bm.C = w.Bm; bm.ldc = kb; bm.zc = gr.zw;
   bm.M = N; bm.N = kb; bm.K = n;
-  TAP_HIP(sgemm(bm, SE_PLAIN, st));
+  TAP_HIP(sgemm(bm, SE_PLAIN, gr.nz, st));
   const int parts = gram_parts(N);
-  hipLaunchKernelGGL(gram_partial_kernel, dim3(parts), dim3(256), 0, st, w.Bm, kb, N, 1ll, (long long)kb, gram_chunk(N),
-                     w.part);
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((kb * kb + 255) / 256), dim3(256), 0, st, w.part, parts, kb * kb, w.W);
+  hipLaunchKernelGGL(gram_partial_kernel, dim3(parts, 1, nz), dim3(256), 0, st, w.Bm, kb, N, 1ll, (long long)kb, gram_chunk(N),
+                     w.part, gr.zw, gr.zw);
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((kb * kb + 255) / 256, 1, nz), dim3(256), 0, st, w.part, parts, kb * kb, w.W, gr.zw);
   const size_t lds = (size_t)kb * (kb + 2) * sizeof(double);
   TAP_HIP(set_lds((const void *)jacobi_kernel, lds));
-  hipLaunchKernelGGL(jacobi_kernel, dim3(1), dim3(1024), lds, st, w.W, kb, k, 30, w.Wk, w.isig, sigma);
+  hipLaunchKernelGGL(jacobi_kernel, dim3(1, 1, nz), dim3(1024), lds, st, w.W, kb, k, 30, w.Wk, w.isig, sigma, gr.zw, zout);
   TAP_HIP(hipGetLastError());
   SgemmArgs u{};
-  u.A = w.Bm; u.sam = kb; u.sak = 1;
-  u.B = w.Wk; u.sbn = kb; u.sbk = 1;
-  u.C = U; u.ldc = k;
+  u.A = w.Bm; u.sam = kb; u.sak = 1; u.za = gr.zw;
+  u.B = w.Wk; u.sbn = kb; u.sbk = 1; u.zb = gr.zw;
+  u.C = U; u.ldc = k; u.zc = zout;
   u.M = N; u.N = k; u.K = kb;
-  u.cs = w.isig;
-  TAP_HIP(sgemm(u, SE_COLSCALE, st));
+  u.cs = w.isig; u.zcs = gr.zw;
+  TAP_HIP(sgemm(u, SE_COLSCALE, gr.nz, st));
   if (ext) return QC_OK;
   int flag = 0;
   TAP_RC(read_flag(w.flag, st, &flag));
@@ -1399,90 +1587,82 @@ int embed_impl(const float *L, int N, int n, int k, int kb, int iters, const flo
   return QC_OK;
 }
 
-// One k-means problem of a group that advances in lockstep, each on its own stream
-struct KmSlot {
-  const float *U;
-  const int *init_idx;
-  int *labels;
-  float *centres;
-  void *work;
-  hipStream_t st;
-  int *ext;            // null, or a device flag for the index check (read by the caller)
-  int passes;
-  bool active;
-};
+hipError_t launch_kmeans_pass(const float *U, int N, int d, const float *centres, int k, int *labels, const SmallWork &w, int *ctl, int it,
+                              long long zu, long long zlab, Group gr, hipStream_t st) {
+  const int nc = (d + 15) / 16, k16 = (k + 15) / 16 * 16;
+  const size_t lds = (size_t)k16 * (16 * nc + 4 + 1) * sizeof(float);
+  const bool v4 = d % 4 == 0 && aligned16(U);
+#define KM_CASE(NC)                                                                                                          \
+  case NC: {                                                                                                                 \
+    const auto kern = v4 ? kmeans_pass_kernel<NC, true> : kmeans_pass_kernel<NC, false>;                                     \
+    const hipError_t e = it == 0 ? set_lds((const void *)kern, lds) : hipSuccess;                                            \
+    if (e != hipSuccess) return e;                                                                                           \
+    hipLaunchKernelGGL(kern, dim3(kmeans_blocks(N), 1, (unsigned)gr.nz), dim3(512), lds, st, U, N, d, centres, k, kmeans_rows_per(N), \
+                       labels, w.psum, w.pcnt, w.dirty, ctl, it, zu, zlab, gr.zw, ZF);                                       \
+    break;                                                                                                                   \
+  }
+  switch (nc) {
+    KM_CASE(1)
+    KM_CASE(2)
+    KM_CASE(3)
+    KM_CASE(4)
+    KM_CASE(5)
+    KM_CASE(6)
+    KM_CASE(7)
+    KM_CASE(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef KM_CASE
+  return hipGetLastError();
+}
 
-// Lloyd's iteration on `ns` problems of the same shape, each on its own stream.  The passes decide on the device
-// whether they still have work (see the control words above), so the host enqueues KM_BATCH passes on every stream and
-// only then reads the control words; a problem leaves the loop when a pass has changed nothing.  With a null `ext` the
-// initial-centre indices are checked (and the error reported) before the first pass.
+// Lloyd's iteration on the group's problems.  The passes decide on the device whether they still have work (see the control
+// words above), so the host enqueues KM_BATCH passes and only then reads the control words; a problem is over when a pass
+// has changed nothing, and the loop when all are.  U and the centres of the group lie zu bytes apart; `ext` holds the index
+// check's flag of each problem (word 3) and its control words; null: a single problem whose index check is reported before
+// the first pass, words in the workspace.  `words` (host, SLOT_WORDS a problem): all of them after the last pass.
 constexpr int KM_BATCH = 8;
 
-int kmeans_multi(KmSlot *slots, int ns, int N, int d, int k, int max_iter) {
-  const int dp = (d + 3) & ~3;
-  const size_t lds = ((size_t)k * dp + (size_t)64 * (dp + 1)) * sizeof(float);
-  TAP_HIP(set_lds((const void *)kmeans_assign_kernel, lds));
-  const size_t lds_acc = (size_t)k * d * sizeof(double);
-  TAP_HIP(set_lds((const void *)kmeans_partial_kernel, lds_acc));
+int kmeans_group(const float *U, long long zu, int N, int d, int k, const int *init_idx, int max_iter, int *labels, float *centres,
+                 void *work, Group gr, hipStream_t st, int *ext, int *words) {
   const int nb = kmeans_blocks(N);
-  for (int i = 0; i < ns; ++i) {
-    KmSlot &q = slots[i];
-    SmallWork w(q.work, N, d, k);
-    if (!q.ext) hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, q.st, w.flag, 64, 0);
-    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, q.st, w.changed, 64, 0);
-    hipLaunchKernelGGL(fill_int_kernel, dim3((N + 255) / 256), dim3(256), 0, q.st, q.labels, N, -1);
-    hipLaunchKernelGGL(kmeans_init_kernel, dim3(k), dim3(256), 0, q.st, q.U, N, d, k, q.init_idx, q.centres,
-                       q.ext ? q.ext : w.flag);
-    TAP_HIP(hipGetLastError());
-    q.passes = 0;
-    q.active = max_iter > 0;
-  }
-  for (int i = 0; i < ns; ++i) {
-    if (slots[i].ext) continue;
-    SmallWork w(slots[i].work, N, d, k);
+  const unsigned nz = (unsigned)gr.nz;
+  SmallWork w(work, N, d, k);
+  int *all = ext ? ext : w.flag, *ctl = all + SLOT_CTL;
+  const long long zlab = (long long)N * sizeof(int);
+  if (!ext) hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, st, all, 64, 0, 0ll);
+  hipLaunchKernelGGL(fill_int_kernel, dim3((N * nz + 255) / 256), dim3(256), 0, st, labels, (int)(N * nz), -1, 0ll);
+  hipLaunchKernelGGL(fill_int_kernel, dim3(1, 1, nz), dim3(256), 0, st, w.dirty, k, 0, gr.zw);
+  hipLaunchKernelGGL(kmeans_init_kernel, dim3(k, 1, nz), dim3(256), 0, st, U, N, d, k, init_idx, centres, all + 3, zu,
+                     (long long)k * sizeof(int), ZF);
+  TAP_HIP(hipGetLastError());
+  if (!ext) {
     int flag = 0;
-    TAP_RC(read_flag(w.flag, slots[i].st, &flag));
+    TAP_RC(read_flag(all + 3, st, &flag));
     if (flag) TAP_FAIL(QC_ERR_RANGE, "an initial-centre index lies outside [0, %d)", N);
   }
   for (int it0 = 0; it0 < max_iter; it0 += KM_BATCH) {
     const int it1 = it0 + KM_BATCH < max_iter ? it0 + KM_BATCH : max_iter;
-    bool any = false;
     for (int it = it0; it < it1; ++it) {
-      for (int i = 0; i < ns; ++i) {
-        KmSlot &q = slots[i];
-        if (!q.active) continue;
-        any = true;
-        SmallWork w(q.work, N, d, k);
-        hipLaunchKernelGGL(kmeans_assign_kernel, dim3((N + 63) / 64), dim3(256), lds, q.st, q.U, N, d, q.centres, k,
-                           q.labels, w.changed, it);
-        hipLaunchKernelGGL(kmeans_partial_kernel, dim3(nb), dim3(128), lds_acc, q.st, q.U, N, d, q.labels, k,
-                           kmeans_rows_per(N), w.psum, w.pcnt, w.changed, it);
-        hipLaunchKernelGGL(kmeans_finish_kernel, dim3((k * d + 63) / 64), dim3(64), 0, q.st, w.psum, w.pcnt, nb, k, d,
-                           q.centres, w.changed, it);
-        TAP_HIP(hipGetLastError());
-      }
+      TAP_HIP(launch_kmeans_pass(U, N, d, centres, k, labels, w, ctl, it, zu, zlab, gr, st));
+      hipLaunchKernelGGL(kmeans_finish_kernel, dim3(k, 1, nz), dim3(128), 0, st, w.psum, w.pcnt, nb, k, d, centres, w.dirty, ctl, it,
+                         zu, gr.zw, ZF);
+      TAP_HIP(hipGetLastError());
     }
+    TAP_HIP(hipMemcpyAsync(words, all, (size_t)gr.nz * ZF, hipMemcpyDeviceToHost, st));
+    TAP_HIP(hipStreamSynchronize(st));
+    bool any = false;
+    for (int z = 0; z < gr.nz; ++z) any = any || !words[z * SLOT_WORDS + SLOT_CTL + KM_DONE];
     if (!any) break;
-    for (int i = 0; i < ns; ++i) {
-      KmSlot &q = slots[i];
-      if (!q.active) continue;
-      SmallWork w(q.work, N, d, k);
-      int ctl[4] = {0, 0, 0, 0};
-      TAP_HIP(hipMemcpyAsync(ctl, w.changed, sizeof(ctl), hipMemcpyDeviceToHost, q.st));
-      TAP_HIP(hipStreamSynchronize(q.st));
-      q.passes = ctl[KM_PASSES];
-      if (ctl[KM_DONE]) q.active = false;
-    }
   }
-  for (int i = 0; i < ns; ++i) TAP_HIP(hipStreamSynchronize(slots[i].st));
   return QC_OK;
 }
 
 int kmeans_impl(const float *U, int N, int d, int k, const int *init_idx, int max_iter, int *labels, float *centres,
                 int *passes_out, void *work, hipStream_t st) {
-  KmSlot q{U, init_idx, labels, centres, work, st, nullptr, 0, false};
-  TAP_RC(kmeans_multi(&q, 1, N, d, k, max_iter));
-  if (passes_out) *passes_out = q.passes;
+  int words[SLOT_WORDS];
+  TAP_RC(kmeans_group(U, 0, N, d, k, init_idx, max_iter, labels, centres, work, Group{1, 0}, st, nullptr, words));
+  if (passes_out) *passes_out = words[SLOT_CTL + KM_PASSES];
   return QC_OK;
 }
 
@@ -1490,7 +1670,7 @@ int aggregate_impl(const int *labels, int m, int N, int k, int *out, int *perm_o
   SmallWork w(work, 1, 1, k);
   hipLaunchKernelGGL(identity_perm_kernel, dim3((k + 255) / 256), dim3(256), 0, st, w.perm, k);
   for (int i = 1; i < m; ++i) {
-    hipLaunchKernelGGL(fill_int_kernel, dim3((k * k + 255) / 256), dim3(256), 0, st, w.T, k * k, 0);
+    hipLaunchKernelGGL(fill_int_kernel, dim3((k * k + 255) / 256), dim3(256), 0, st, w.T, k * k, 0, 0ll);
     hipLaunchKernelGGL(contingency_kernel, dim3((N + 255) / 256), dim3(256), 0, st, labels, labels + (size_t)i * N, N, k, w.T);
     hipLaunchKernelGGL(greedy_match_kernel, dim3(1), dim3(1024), 0, st, w.T, k, w.perm + (size_t)i * k);
   }
@@ -1521,6 +1701,7 @@ int qc_tap_workspace_bytes(int N, int F, int n, int k, int kb, size_t *bytes_out
 int qc_tap_profile_begin(void) {
   g_prof.on = true;
   g_prof.used = 0;
+  g_prof.products = 0;
   return QC_OK;
 }
 
@@ -1536,7 +1717,7 @@ int qc_tap_profile_end(float *sim_ms_out, int *launches_out) {
     total += ms;
   }
   *sim_ms_out = total;
-  *launches_out = (int)g_prof.used;
+  *launches_out = g_prof.products;
   return QC_OK;
 }
 
@@ -1549,7 +1730,7 @@ int qc_tap_similarity(const float *X, const float *t, int N, int F, const int *i
   if (!(alpha >= 0.f && alpha <= 1.f)) TAP_FAIL(QC_ERR_RANGE, "alpha must lie in [0, 1]");
   if (!aligned16(X) || !aligned16(A)) TAP_FAIL(QC_ERR_ALIGN, "X and A must be 16-byte aligned");
   TAP_RC(check_work(work, work_bytes, SimWork(nullptr, N, F, n).bytes));
-  return similarity_impl(X, t, N, F, idx, n, alpha, A, d_r, d_c, work, static_cast<hipStream_t>(stream));
+  return similarity_impl(X, t, N, F, idx, n, alpha, A, n, d_r, d_c, work, Group{1, 0}, static_cast<hipStream_t>(stream));
 }
 
 int qc_tap_normalise(float *A, const float *d_r, const float *d_c, int N, int n, void *work, size_t work_bytes,
@@ -1558,7 +1739,7 @@ int qc_tap_normalise(float *A, const float *d_r, const float *d_c, int N, int n,
   if (N < 1 || n < 1) TAP_FAIL(QC_ERR_SHAPE, "N and n must be positive");
   if ((long long)N * n >= (1ll << 31)) TAP_FAIL(QC_ERR_UNSUPPORTED, "N * n must be below 2^31");
   TAP_RC(check_work(work, work_bytes, SmallWork(nullptr, 1, 1, 1).bytes));
-  return normalise_impl(A, d_r, d_c, N, n, work, static_cast<hipStream_t>(stream));
+  return normalise_impl(A, d_r, d_c, N, n, n, work, Group{1, 0}, static_cast<hipStream_t>(stream));
 }
 
 int qc_tap_embed(const float *L, int N, int n, int k, int kb, int iters, const float *q0, float *U, float *sigma,
@@ -1568,7 +1749,7 @@ int qc_tap_embed(const float *L, int N, int n, int k, int kb, int iters, const f
   if (iters < 0 || iters > 1000) TAP_FAIL(QC_ERR_RANGE, "iters must lie in [0, 1000]");
   if (!aligned16(L) || !aligned16(q0) || !aligned16(U)) TAP_FAIL(QC_ERR_ALIGN, "L, q0 and U must be 16-byte aligned");
   TAP_RC(check_work(work, work_bytes, EmbedWork(nullptr, N, n, k, kb).bytes));
-  return embed_impl(L, N, n, k, kb, iters, q0, U, sigma, work, static_cast<hipStream_t>(stream));
+  return embed_impl(L, N, n, n, k, kb, iters, q0, U, sigma, 0, work, Group{1, 0}, static_cast<hipStream_t>(stream));
 }
 
 int qc_tap_kmeans(const float *U, int N, int d, int k, const int *init_idx, int max_iter, int *labels, float *centres,
@@ -1607,56 +1788,33 @@ int qc_tap_cluster(const float *X, const float *t, int N, int F, const int *subs
   const size_t per = (ClusterWork(nullptr, N, F, n, k, kb).bytes + 255) & ~size_t(255);
   TAP_RC(check_work(work, work_bytes, per));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // as many subsamples at a time as the workspace holds (at most MAX_SLOTS): the first on the caller's stream, the
-  // others on internal streams that start after the work already enqueued on the caller's stream
+  // As many subsamples at a time as the workspace holds (at most MAX_SLOTS), one launch a kernel for all of them.  (Three streams whose
+  // large products were chained by events, so that one subsample's small kernels ran beside another's products: the same time at
+  // 32768 samples, where they slowed each other down, and three times the launches, which bound small pools.)
   int slots = (int)(work_bytes / per);
   if (slots > MAX_SLOTS) slots = MAX_SLOTS;
   if (slots > m) slots = m;
-  hipStream_t ss[MAX_SLOTS] = {st, nullptr, nullptr};
-  CallStreams cs;                                 // destroyed (after a wait on each stream) on every way out
-  if (slots > 1) {
-    TAP_HIP(hipEventCreateWithFlags(&cs.fork, hipEventDisableTiming));
-    TAP_HIP(hipEventRecord(cs.fork, st));
-    for (int j = 1; j < slots; ++j) {
-      TAP_HIP(hipStreamCreateWithFlags(&cs.streams[j], hipStreamNonBlocking));
-      TAP_HIP(hipStreamWaitEvent(cs.streams[j], cs.fork, 0));
-      ss[j] = cs.streams[j];
-    }
-    for (int j = 0; j < slots; ++j) TAP_HIP(hipEventCreateWithFlags(&cs.chain[j], hipEventDisableTiming));
-  }
   for (int i0 = 0; i0 < m; i0 += slots) {
-    const int ns = m - i0 < slots ? m - i0 : slots;
-    KmSlot km[MAX_SLOTS];
-    for (int j = 0; j < ns; ++j) {
-      ClusterWork w(static_cast<char *>(work) + (size_t)j * per, N, F, n, k, kb);
-      const int i = i0 + j;
-      hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, ss[j], w.flags, 64, 0);
-      TAP_RC(similarity_impl(X, t, N, F, subsamples + (size_t)i * n, n, alpha, w.A, w.dr, w.dc, w.sub, ss[j], w.flags + 0,
-                             j > 0 ? cs.chain[j - 1] : nullptr));
-      TAP_RC(normalise_impl(w.A, w.dr, w.dc, N, n, w.sub, ss[j], w.flags + 1));
-      TAP_RC(embed_impl(w.A, N, n, k, kb, iters, q0, w.U, w.sigma, w.sub, ss[j], w.flags + 2,
-                        slots > 1 ? cs.chain[j] : nullptr));
-      km[j] = KmSlot{w.U, init_idx + (size_t)i * k, per_labels + (size_t)i * N, w.centres, w.sub, ss[j], w.flags + 3, 0, false};
-    }
+    const Group gr{m - i0 < slots ? m - i0 : slots, (long long)per};
+    ClusterWork w(work, N, F, n, k, kb);
+    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(256), 0, st, w.flags, 64, 0, 0ll);
+    const int ld = padded(n);
+    TAP_RC(similarity_impl(X, t, N, F, subsamples + (size_t)i0 * n, n, alpha, w.A, ld, w.dr, w.dc, w.sub, gr, st, w.flags + 0));
+    TAP_RC(normalise_impl(w.A, w.dr, w.dc, N, n, ld, w.sub, gr, st, w.flags + 1));
+    TAP_RC(embed_impl(w.A, N, ld, n, k, kb, iters, q0, w.U, w.sigma, gr.zw, w.sub, gr, st, w.flags + 2));
     // the first pass of the k-means below runs on whatever the earlier stages left; the flags tell afterwards
     // whether that was meaningful (every kernel stays inside its buffers on any input)
-    int rc = kmeans_multi(km, ns, N, k, k, max_iter);
-    for (int j = 0; j < ns && rc == QC_OK; ++j) {
-      ClusterWork w(static_cast<char *>(work) + (size_t)j * per, N, F, n, k, kb);
-      int fl[4] = {0, 0, 0, 0};
-      TAP_HIP(hipMemcpyAsync(fl, w.flags, sizeof(fl), hipMemcpyDeviceToHost, ss[j]));
-      TAP_HIP(hipStreamSynchronize(ss[j]));
-      if (fl[0]) { qc::set_error("a subsample index lies outside [0, %d)", N); rc = QC_ERR_RANGE; }
-      else if (fl[1]) { qc::set_error("a degree of the similarity matrix is not positive and finite"); rc = QC_ERR_RANGE; }
-      else if (fl[2]) { qc::set_error("the iteration block has no full rank (a zero start vector, or fewer than kb independent directions)"); rc = QC_ERR_RANGE; }
-      else if (fl[3]) { qc::set_error("an initial-centre index lies outside [0, %d)", N); rc = QC_ERR_RANGE; }
-    }
-    if (rc != QC_OK) {
-      for (int j = 0; j < slots; ++j) (void)hipStreamSynchronize(ss[j]);
-      return rc;
+    int words[MAX_SLOTS * SLOT_WORDS];
+    TAP_RC(kmeans_group(w.U, gr.zw, N, k, k, init_idx + (size_t)i0 * k, max_iter, per_labels + (size_t)i0 * N, w.centres, w.sub, gr, st,
+                        w.flags, words));
+    for (int z = 0; z < gr.nz; ++z) {
+      const int *fl = words + z * SLOT_WORDS;
+      if (fl[0]) TAP_FAIL(QC_ERR_RANGE, "a subsample index lies outside [0, %d)", N);
+      if (fl[1]) TAP_FAIL(QC_ERR_RANGE, "a degree of the similarity matrix is not positive and finite");
+      if (fl[2]) TAP_FAIL(QC_ERR_RANGE, "the iteration block has no full rank (a zero start vector, or fewer than kb independent directions)");
+      if (fl[3]) TAP_FAIL(QC_ERR_RANGE, "an initial-centre index lies outside [0, %d)", N);
     }
   }
-  // every stream has drained (the k-means loop ends with a wait on each): the merge runs on the caller's stream
   TAP_RC(aggregate_impl(per_labels, m, N, k, labels_out, nullptr, work, st));
   TAP_HIP(hipStreamSynchronize(st));
   return QC_OK;
