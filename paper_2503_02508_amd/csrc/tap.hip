@@ -8,6 +8,7 @@
 #include <vector>
 #include "qc_tap.h"
 #include "qc_internal.h"
+#include "gemm_f32_tile.h"
 
 namespace {
 
@@ -305,6 +306,64 @@ __global__ __launch_bounds__(256, 2) void sgemm_kernel(SgemmArgs p) {
   }
 }
 
+// The same product for operands that are both contiguous along k and take 16-byte loads, K a multiple of 4 (split K: whole slabs),
+// on tiles of 64 WT x 64 WT whose slabs go straight to LDS (gemm_f32_tile.h).  Same chains, same bits.  What bounds it: the matrix
+// rate at the clock the chip holds (2.1 - 2.3 GHz), 93 % of the cycles multiplying.  32768 x 1638 x 4096: 4.2 ms on sgemm_kernel
+// (105 TFLOP/s, slabs through registers, two workgroups a compute unit), 3.2 here (138; four buffers 3.3, eight 3.2, ten 3.25, slabs of
+// 32 k 3.3, wavefronts of 128 x 64 3.5, tiles of 128 x 256 3.25); the library's product takes 2.96.  The order of the tiles made
+// no difference.
+constexpr int NT_BK = 16;
+template <int WT, int EPI>
+__global__ __launch_bounds__(256, WT == 2 ? 1 : 2) void sgemm_nt_kernel(SgemmArgs p) {
+  using Tile = qc::F32Tile<2, 2, WT, WT, NT_BK, 6>;
+  __shared__ __align__(16) float slabs[6 * Tile::SLAB];
+  const int tiles_m = (p.M + Tile::RM - 1) / Tile::RM, tiles_n = (p.N + Tile::RN - 1) / Tile::RN;
+  const int total = tiles_m * tiles_n, per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
+  const int t = (blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
+  if (blockIdx.x / NUM_XCD >= per_xcd || t >= total) return;
+  const int m0 = __builtin_amdgcn_readfirstlane(t / tiles_n * Tile::RM), n0 = __builtin_amdgcn_readfirstlane(t % tiles_n * Tile::RN);
+  const float *A = in_slot(p.A, p.za), *B = in_slot(p.B, p.zb);
+  float *C = in_slot(p.C, gridDim.y > 1 ? p.zpart : p.zc) + (EPI == SE_PLAIN ? (long long)blockIdx.y * p.part_stride : 0);
+  const int kbeg = EPI == SE_PLAIN ? blockIdx.y * p.kchunk : 0, kend = EPI == SE_PLAIN ? min(p.K, kbeg + p.kchunk) : p.K;
+  Tile tile;
+  tile.run(A + kbeg, (size_t)p.sam, B + kbeg, (size_t)p.sbn, p.M, p.N, kend - kbeg, m0, n0, slabs);
+  // register r of a 32 x 32 block is row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32
+  const int lane = threadIdx.x & 63;
+  const float *rs = nullptr, *tr = nullptr, *tc = nullptr, *cs = nullptr;
+  if (EPI != SE_PLAIN) cs = in_slot(p.cs, p.zcs);
+  if (EPI == SE_SIM) {
+    rs = in_slot(p.rs, p.zrs);
+    tr = in_slot(p.tr, p.ztr);
+    tc = in_slot(p.tc, p.ztc);
+  }
+#pragma unroll
+  for (int i = 0; i < WT; ++i) {
+    float rsv[16], trv[16];
+    if (EPI == SE_SIM) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {        // the row factors of this lane in one batch (clamped, branch-free)
+        const int m = min(m0 + tile.wm + 32 * i + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), p.M - 1);
+        rsv[r] = rs[m];
+        trv[r] = tr[m];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < WT; ++j) {
+      const int n = n0 + tile.wn + 32 * j + (lane & 31);
+      const bool nok = n < p.N;
+      const float csn = EPI != SE_PLAIN ? cs[nok ? n : 0] : 1.f, tcn = EPI == SE_SIM ? tc[nok ? n : 0] : 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = m0 + tile.wm + 32 * i + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+        float v = tile.acc[i][j][r];
+        if (EPI == SE_SIM) v = p.alpha * (v * rsv[r] * csn) + (1.f - p.alpha) * expf(-fabsf(trv[r] - tcn));
+        if (EPI == SE_COLSCALE) v *= csn;
+        if (nok && m < p.M) C[(long long)m * p.ldc + n] = v;
+      }
+    }
+  }
+}
+
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *part, int splits, long long stride,
                                                             long long count, float *out, long long zpart, long long zout) {
   part = in_slot(part, zpart);
@@ -377,6 +436,24 @@ hipError_t sgemm(SgemmArgs a, int epi, int nz, hipStream_t st, float *part = nul
     }
   }
   const bool vec = a.a_vec && a.b_vec;
+  // both operands contiguous along k, whole 16-byte chunks: the kernel whose slabs go straight to LDS.  Tiles of 128 x 128 while they
+  // fill the chip, of 64 x 64 below (1536 x 160 x 256, three subsamples: 38 us on sgemm_kernel, 21 on 128 x 128, 12 on 64 x 64)
+  // (its offsets inside a tile are 32-bit bytes: rows shorter than 2^22 floats)
+  if (vec && a.a_kc && a.b_kc && a.K >= 4 && a.sam < (1 << 22) && a.sbn < (1 << 22)) {
+    const long long t2 = (long long)tiles * splits * nz;
+    const int wt = t2 >= 256 ? 2 : 1;
+    const int nt_tiles = wt == 2 ? tiles : ((a.M + 63) / 64) * ((a.N + 63) / 64);
+    const dim3 nt_grid((unsigned)((nt_tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD), (unsigned)splits, (unsigned)nz);
+#define NT_LAUNCH(E)                                                                                       \
+  do {                                                                                                     \
+    if (wt == 2) hipLaunchKernelGGL((sgemm_nt_kernel<2, E>), nt_grid, dim3(256), 0, st, a);                \
+    else hipLaunchKernelGGL((sgemm_nt_kernel<1, E>), nt_grid, dim3(256), 0, st, a);                        \
+  } while (0)
+    if (epi == SE_SIM) NT_LAUNCH(SE_SIM);
+    else if (epi == SE_COLSCALE) NT_LAUNCH(SE_COLSCALE);
+    else NT_LAUNCH(SE_PLAIN);
+#undef NT_LAUNCH
+  } else {
 #define SG_LAUNCH(AK, BK, E)                                                                                   \
   do {                                                                                                         \
     if (vec) hipLaunchKernelGGL((sgemm_kernel<AK, BK, E, true>), dim3(grid, splits, nz), dim3(256), 0, st, a); \
@@ -395,6 +472,7 @@ hipError_t sgemm(SgemmArgs a, int epi, int nz, hipStream_t st, float *part = nul
     else return hipErrorInvalidValue;
   }
 #undef SG_LAUNCH
+  }
   if (a.sym) {
     const int nb = (a.M + 31) / 32;
     hipLaunchKernelGGL(splitk_reduce_sym_kernel, dim3(nb * (nb + 1) / 2, 1, nz), dim3(256), 0, st,
