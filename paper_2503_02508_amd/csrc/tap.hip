@@ -609,213 +609,310 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const float *src, int n, 
 }
 
 // -------------------------------------------------------------------------- orthonormalisation (Cholesky QR)
-// partial Gram matrices of kb vectors of length n over ranges of their elements, fp64: part[b][a][c] = sum_j y_a[j]
-// y_c[j], vector a's element j at Y[a * sv + j * sj] (rows of a [kb, n] matrix: sv = n, sj = 1; columns of an
-// [n, kb] matrix: sv = 1, sj = kb)
-__global__ __launch_bounds__(256) void gram_partial_kernel(const float *Y, int kb, int n, long long sv, long long sj,
-                                                           int jchunk, double *part, long long zy, long long zw) {
-  Y = in_slot(Y, zy);
-  part = in_slot(part, zw);
-  __shared__ float ys[KB_MAX][33];
-  const int tid = threadIdx.x, ta = tid >> 4, tb = tid & 15;
-  double acc[8][8];
+// v_mfma_f64_16x16x4_f64: lane l supplies row l % 16, k = l / 16 of either operand; result i of lane l is row l / 16 + 4 i,
+// column l % 16.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// One wavefront's share of a partial Gram matrix (below): the blocks of parity H, groups of 16 elements number wave, wave + 4, ...
+template <int NB, bool KC, bool V4, int H>
+__device__ __forceinline__ void gram_half(const float *Y, int kb, int n, long long sv, int j0, int j1, int wave, double *out) {
+  constexpr int BLK = NB * (NB + 1) / 2, MINE = (BLK + 1 - H) / 2;
+  extern __shared__ double gs[];                  // [2][BLK][64][4]
+  const int lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
+  f64x4 acc[MINE > 0 ? MINE : 1];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int b = 0; b < MINE; ++b) acc[b] = (f64x4){0.0, 0.0, 0.0, 0.0};
+  for (int jb = j0 + 16 * wave; jb < j1; jb += 64) {
+    float v[NB][4];
+    const int j = jb + 4 * g;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[i][c] = 0.0;
-  const int j0 = blockIdx.x * jchunk, j1 = min(n, j0 + jchunk);
-  for (int jb = j0; jb < j1; jb += 32) {
-    __syncthreads();
-    for (int u = tid; u < KB_MAX * 32; u += 256) {
-      // consecutive lanes along the contiguous direction
-      const int a = sj == 1 ? u >> 5 : u & (KB_MAX - 1), j = sj == 1 ? u & 31 : u >> 7;
-      const bool ok = a < kb && jb + j < j1;
-      const float v = Y[ok ? (long long)a * sv + (long long)(jb + j) * sj : 0];
-      ys[a][j] = ok ? v : 0.f;
-    }
-    __syncthreads();
-    for (int j = 0; j < 32; ++j) {
-      double av[8], bv[8];
+    for (int b = 0; b < NB; ++b) {
+      const int a = 16 * b + row, ac = min(a, kb - 1);
+      if (V4) {                                   // n a multiple of 4
+        const float4 t = *(const float4 *)(Y + (long long)ac * sv + min(j, n - 4));
+        const bool in = a < kb && j < j1;
+        v[b][0] = in ? t.x : 0.f;
+        v[b][1] = in ? t.y : 0.f;
+        v[b][2] = in ? t.z : 0.f;
+        v[b][3] = in ? t.w : 0.f;
+      } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        av[i] = (double)ys[ta * 8 + i][j];
-        bv[i] = (double)ys[tb * 8 + i][j];
+        for (int e = 0; e < 4; ++e) {
+          const int je = min(j + e, n - 1);
+          const float t = KC ? Y[(long long)ac * sv + je] : Y[(long long)je * sv + ac];
+          v[b][e] = a < kb && j + e < j1 ? t : 0.f;
+        }
       }
+    }
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+    for (int e = 0; e < 4; ++e) {
+      double d[NB];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[i][c] = fma(av[i], bv[c], acc[i][c]);
+      for (int b = 0; b < NB; ++b) d[b] = (double)v[b][e];
+#pragma unroll
+      for (int p = 0; p < NB; ++p)
+#pragma unroll
+        for (int q = 0; q <= p; ++q) {
+          const int b = p * (p + 1) / 2 + q;
+          if (b % 2 == H) acc[b / 2] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[p], d[q], acc[b / 2], 0, 0, 0);
+        }
     }
   }
-  double *out = part + (long long)blockIdx.x * kb * kb;
+  // the four wavefronts of a parity: 2 + 0, 3 + 1, then the two
+  f64x4 *const half = (f64x4 *)gs;
+  if (wave >= 2) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+    for (int b = 0; b < MINE; ++b) half[((wave - 2) * BLK + 2 * b + H) * 64 + lane] = acc[b];
+  }
+  __syncthreads();
+  if (wave < 2) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int a = ta * 8 + i, b = tb * 8 + c;
-      if (a < kb && b < kb) out[a * kb + b] = acc[i][c];
+    for (int b = 0; b < MINE; ++b) acc[b] += half[(wave * BLK + 2 * b + H) * 64 + lane];
+  }
+  __syncthreads();
+  if (wave == 1) {
+#pragma unroll
+    for (int b = 0; b < MINE; ++b) half[(2 * b + H) * 64 + lane] = acc[b];
+  }
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int p = 0; p < NB; ++p)
+#pragma unroll
+    for (int q = 0; q <= p; ++q) {
+      const int b = p * (p + 1) / 2 + q;
+      if (b % 2 != H) continue;
+      const f64x4 s = acc[b / 2] + half[b * 64 + lane];
+      const int c = 16 * q + row;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 16 * p + g + 4 * i;
+        if (r < kb && c < kb) out[r * kb + c] = s[i];
+      }
     }
 }
 
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const double *part, int nparts, int kk, double *W, long long zw) {
+// Partial Gram matrices of kb vectors of length n over ranges of their elements, fp64: part[b][a][c] = sum_j y_a[j] y_c[j] for the
+// blocks of 16 x 16 on and below the diagonal (the others are not written).  Vector a's element j is Y[a * sv + j] (KC) or
+// Y[j * sv + a].  Both operands of a product are the same 16 vectors' values, so a wavefront loads each value once, in operand layout
+// (lane l: vector l % 16, elements 4 (l / 16) .. + 3 of a group of 16), and multiplies all pairs of blocks of it on the
+// float64 matrix cores; four pairs of wavefronts (every other block each, so that the sums fit the registers) take every fourth group
+// and their sums meet in LDS.  Bound: the
+// float64 matrix rate (NB = 8: 144 products of 64 cycles per group), then the latency of the loads.
+// Three subsamples, 128 vectors of 1640 elements: 42 us on the vector units (operands from LDS), 13 here; 32 vectors of 160: 13 and 3.7.
+template <int NB, bool KC, bool V4>
+__global__ __launch_bounds__(512) void gram_partial_kernel(const float *Y, int kb, int n, long long sv, int jchunk, double *part,
+                                                           long long zy, long long zw) {
+  Y = in_slot(Y, zy);
+  part = in_slot(part, zw);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j0 = blockIdx.x * jchunk, j1 = min(n, j0 + jchunk);
+  double *const out = part + (long long)blockIdx.x * kb * kb;
+  if (wave & 1) gram_half<NB, KC, V4, 1>(Y, kb, n, sv, j0, j1, wave >> 1, out);
+  else gram_half<NB, KC, V4, 0>(Y, kb, n, sv, j0, j1, wave >> 1, out);
+}
+
+// the ranges' partial matrices added in order, the lower triangle written to both sides of the diagonal
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const double *part, int nparts, int kb, double *W, long long zw) {
   part = in_slot(part, zw);
   W = in_slot(W, zw);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= kk) return;
+  const int i = blockIdx.x * 256 + threadIdx.x, kk = kb * kb, r = i / kb, c = i - r * kb;
+  if (i >= kk || c > r) return;
   double s = 0.0;
   int b = 0;
-  for (; b + 8 <= nparts; b += 8) {        // eight loads in flight, added in order
-    double t[8];
+  for (; b + 16 <= nparts; b += 16) {        // sixteen loads in flight, added in order
+    double t[16];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) t[q] = part[(long long)(b + q) * kk + i];
+    for (int q = 0; q < 16; ++q) t[q] = part[(long long)(b + q) * kk + i];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) s += t[q];
+    for (int q = 0; q < 16; ++q) s += t[q];
   }
   for (; b < nparts; ++b) s += part[(long long)b * kk + i];
   W[i] = s;
+  W[c * kb + r] = s;
+}
+
+// 1 / x and x^-1/2 to fp64 rounding level: hardware estimate, two Newton steps
+__device__ __forceinline__ double nr_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = r * (2.0 - x * r);
+  return r * (2.0 - x * r);
+}
+__device__ __forceinline__ double nr_rsq(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = r * (1.5 - 0.5 * x * r * r);
+  return r * (1.5 - 0.5 * x * r * r);
+}
+
+// A block of 16 x 16: B[i][j] += or = sum_k X[i][k] Z[j][k], X and Z rows of ldx, ldz doubles
+__device__ __forceinline__ f64x4 block_nt(const double *X, int ldx, const double *Z, int ldz, int row, int g) {
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[row * ldx + g + 4 * e], Z[row * ldz + g + 4 * e], acc, 0, 0, 0);
+  return acc;
+}
+
+// lane N's value of a row of 16 lanes to all of the row
+template <int N>
+__device__ __forceinline__ double row_bcast(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + N, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + N, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+// a[c] -= t * (lane c's col), c = C .. 15: the broadcast is part of the multiply-add (col was written long before: t depends on it)
+template <int C>
+__device__ __forceinline__ void eliminate_columns(double (&a)[16], double col, double minus_t) {
+  if constexpr (C < 16) {
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(a[C]) : "v"(col), "v"(minus_t), "n"(C));
+    eliminate_columns<C + 1>(a, col, minus_t);
+  }
+}
+// columns J .. 15 of the elimination of a 16 x 16 block, lane R (of each 16) its row R; rs[j] = pivot_j^-1/2
+template <int J>
+__device__ __forceinline__ void eliminate(double (&a)[16], double (&rs)[16], int row, int check, bool &bad) {
+  if constexpr (J < 16) {
+    double piv = row_bcast<J>(a[J]);
+    const bool no = !(piv > 0.0) || !(piv < INFINITY);
+    bad = bad || no || (check && piv < 0.25);
+    piv = no ? 1.0 : piv;
+    rs[J] = nr_rsq(piv);
+    const bool own = row == J;
+    const double col = a[J], minus_t = -(own ? 1.0 : col) * nr_rcp(piv);
+#pragma unroll
+    for (int c = J + 1; c < 16; ++c) a[c] = own ? 0.0 : a[c];
+    eliminate_columns<J + 1>(a, col, minus_t);
+    eliminate<J + 1>(a, rs, row, check, bad);
+  }
 }
 
 // Inverse Cholesky factor of W + shift I (= Lc Lc^T, Lc lower), one workgroup.  The shift, shift_rel times the largest
 // diagonal entry, keeps the factorisation alive when the rows are numerically dependent (shifted Cholesky QR: the
 // rows come out better conditioned, not yet orthonormal, and the next pass finishes).
-// The sweep is the square-root-free form on one kb x kb array S.  After column j, rows R > j of the columns C > j
-// hold the trailing matrix w (kept whole: the copies above the diagonal are updated too and never read, which saves
-// every per-lane condition), rows R <= j of the columns C > j hold the inverse being built, r_CR at S[R][C], r's unit
-// diagonal implicit.  At column j, with pivot p_j = S[j][j], every element of the columns C > j takes
-//   S[R][C] -= g(R) g(C) / p_j,   g(x) = S[x][j] for x != j, g(j) = 1,
-// where row j starts from zero (r_Cj = -w_Cj / p_j), which reads only column j.  Wavefront w of the 16 keeps the
-// columns w, w + 16, ..., lane l the rows l and l + 64 of each: finished columns are skipped by a test that is
-// uniform over the wavefront, and the work stays balanced until the last columns.  The owner of column j publishes it
-// through LDS (two buffers in turn, so one barrier per column suffices), with 1 in place of the pivot.
-// Then Lc^-1 = diag(p)^-1/2 r.
+//
+// Blocks of 16 on one kb x kb array S in LDS (padded with the identity).  After block column p, the blocks R > p of the columns C > p
+// hold the trailing matrix (kept whole), the blocks R <= p of the columns C > p the inverse being built, r_CR^T at S[R][C], and
+// S[p][p] the inverse D_p of its own factor.  At column p, with G(R) = S[R][p] (the identity for R = p) and M(R) = G(R) D_p^T,
+//   S[R][C] -= M(R) M(C)^T for C > p (block row p starts from zero),
+// and at the end block row C of the result is D_C [r_C0 .. r_C,C-1, I].  D_p comes out of one wavefront: lane R keeps row R of
+// S[p][p] and eliminates column after column in the square-root-free form of the same scheme on single elements, the column's values
+// broadcast within the multiply-adds.  The products run on the float64 matrix cores, a block a wavefront; the wavefront that
+// factorises takes S[p+1][p+1] first and goes on with D_p+1 while the others update the rest, two barriers a block column.
+// Three at a time, kb = 128: 114 us with one column and one barrier at a time, 47 so; kb = 32: 25 and 9.6.  The chain of 16 pivots a block
+// (reciprocal, broadcast, multiply-add) is what is left.
 // Out: Rinv[kb, kb] fp32 = Lc^-1 (lower triangular), so that Rinv Y has orthonormal rows when the shift is
 // negligible.  With `check` set (the last pass, whose input should already be near orthonormal) the kernel returns the
 // identity at once when W is the identity to 1e-5, and a pivot below 1/4 raises the flag: the block has no full
 // rank.  A non-positive pivot always raises it.
+constexpr int CHOL_LDM = 20;
 __global__ __launch_bounds__(1024) void chol_inv_kernel(const double *W, int kb, double shift_rel, int check,
                                                          float *Rinv, int *flag, long long zw, long long zflag) {
   W = in_slot(W, zw);
   Rinv = in_slot(Rinv, zw);
   flag = in_slot(flag, zflag);
-  __shared__ double colbuf[2][KB_MAX];
-  __shared__ double pivbuf[2];
-  __shared__ double pivs[KB_MAX];
-  __shared__ double red[16];
-  __shared__ double dmax;
-  const int tid = threadIdx.x, lane = tid & 63;
+  extern __shared__ double cs_[];
+  const int nb = (kb + 15) / 16, kp = 16 * nb, ld = kp + 4;
+  double *const S = cs_, *const M = cs_ + kp * ld;
+  __shared__ double redm[16], redd[16];
+  const int tid = threadIdx.x, lane = tid & 63, row = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  constexpr int NC = KB_MAX / 16;
-  double S[NC][2];
+  double dmax = 0.0, dev = 0.0;
+  for (int u = tid; u < kp * kp; u += 1024) {
+    const int R = u / kp, C = u - R * kp;
+    const bool in = R < kb && C < kb;
+    const int hi = R < C ? C : R, lo = R < C ? R : C;
+    const double v = W[in ? hi * kb + lo : 0];
+    const double one = R == C ? 1.0 : 0.0, x = in ? v : one;
+    S[R * ld + C] = x;
+    if (in && R == C) dmax = fmax(dmax, v);
+    dev = fmax(dev, fabs(x - one));
+    if (!(x == x)) dev = INFINITY;
+  }
 #pragma unroll
-  for (int i = 0; i < NC; ++i)
+  for (int o = 32; o > 0; o >>= 1) {
+    dmax = fmax(dmax, __shfl_xor(dmax, o, 64));
+    dev = fmax(dev, __shfl_xor(dev, o, 64));
+  }
+  if (lane == 0) {
+    redm[w] = dmax;
+    redd[w] = dev;
+  }
+  __syncthreads();
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int R = lane + 64 * h, C = w + 16 * i;
-      const bool in = R < kb && C < kb;
-      const int lo = R < C ? R : C, hi = R < C ? C : R;
-      const double v = W[in ? hi * kb + lo : 0];        // the Gram matrix is read from its lower triangle
-      S[i][h] = in ? v : 0.0;
-      if (in && R == C) pivs[R] = v;
-    }
+  for (int q = 0; q < 16; ++q) {
+    dmax = fmax(dmax, redm[q]);
+    dev = fmax(dev, redd[q]);
+  }
   // last pass only: rows that are already orthonormal to fp32 level (|W - I| <= 1e-5 everywhere) are left as they are
-  if (check) {
-    double dev = 0.0;
-#pragma unroll
-    for (int i = 0; i < NC; ++i)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int R = lane + 64 * h, C = w + 16 * i;
-        const double d = fabs(S[i][h] - (R == C ? 1.0 : 0.0));
-        dev = (R < kb && C < kb) ? fmax(dev, d) : dev;
-      }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) dev = fmax(dev, __shfl_xor(dev, o, 64));
-    if (lane == 0) red[w] = dev;
+  if (check && dev <= 1e-5) {                     // the same value in every thread: the whole workgroup leaves together
+    for (int u = tid; u < kb * kb; u += 1024) Rinv[u] = u / kb == u % kb ? 1.f : 0.f;
+    return;
   }
-  __syncthreads();
-  if (tid == 0) {
-    double m = 0.0;
-    for (int i = 0; i < kb; ++i) m = fmax(m, pivs[i]);
-    dmax = m;
-  }
-  if (check) {
-    double dev = 0.0;
-    for (int q = 0; q < 16; ++q) dev = fmax(dev, red[q]);
-    if (dev <= 1e-5) {                    // the same value in every thread: the whole workgroup leaves together
-#pragma unroll
-      for (int i = 0; i < NC; ++i)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int R = lane + 64 * h, C = w + 16 * i;
-          if (R < kb && C < kb) Rinv[C * kb + R] = R == C ? 1.f : 0.f;
-        }
-      return;
-    }
-  }
-  __syncthreads();
   const double shift = shift_rel * dmax;
+  if (tid < kb) S[tid * ld + tid] += shift;
+  __syncthreads();
+
+  // D_p in place of S[p][p] (one wavefront; its four groups of 16 lanes do the same)
+  auto factor = [&](int p) {
+    double *const P = S + 16 * p * ld + 16 * p;
+    double a[16], rs[16];
 #pragma unroll
-  for (int i = 0; i < NC; ++i)
+    for (int c = 0; c < 16; ++c) a[c] = P[row * ld + c];
+    bool bad = false;
+    eliminate<0>(a, rs, row, check, bad);
+    if (bad && lane == 0) atomicOr(flag, 2);
+    // lane R holds r_CR in a[C] for C > R: column R of D_p
+    if (g == 0) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (lane + 64 * h == w + 16 * i) S[i][h] += shift;
-  for (int j = 0; j < kb; ++j) {
-    double *buf = colbuf[j & 1];
-    const bool z0 = lane == j, z1 = lane + 64 == j;       // this lane's copy of row j
-    if (w == (j & 15)) {
-      double v0 = 0.0, v1 = 0.0;
+      for (int c = 0; c < 16; ++c) P[c * ld + row] = c > row ? a[c] * rs[c] : c == row ? rs[c] : 0.0;
+    }
+  };
+  if (w == 0) factor(0);
+  __syncthreads();
+  for (int p = 0; p + 1 < nb; ++p) {
+    const double *const D = S + 16 * p * ld + 16 * p;
+    if (w < nb) {                                 // M(R), R = w
+      if (w == p) {                               // the identity times D_p^T
 #pragma unroll
-      for (int i = 0; i < NC; ++i)
-        if (i == (j >> 4)) {
-          v0 = S[i][0];
-          v1 = S[i][1];
-        }
-      if (z0) pivbuf[j & 1] = v0;
-      if (z1) pivbuf[j & 1] = v1;
-      buf[lane] = z0 ? 1.0 : v0;
-      buf[lane + 64] = z1 ? 1.0 : v1;
+        for (int i = 0; i < 4; ++i) M[(16 * w + g + 4 * i) * CHOL_LDM + row] = D[row * ld + g + 4 * i];
+      } else {
+        const f64x4 m = block_nt(S + 16 * w * ld + 16 * p, ld, D, ld, row, g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) M[(16 * w + g + 4 * i) * CHOL_LDM + row] = m[i];
+      }
     }
     __syncthreads();
-    double piv = pivbuf[j & 1];
-    if (!(piv > 0.0) || !isfinite(piv)) {
-      if (tid == 0) atomicOr(flag, 2);
-      piv = 1.0;
-    } else if (check && piv < 0.25) {
-      if (tid == 0) atomicOr(flag, 2);
-    }
-    if (tid == 0) pivs[j] = piv;
-    if (w + 16 * (NC - 1) > j) {          // this wavefront still has a column beyond j
-      // 1 / p: hardware estimate refined by two Newton steps
-      double inv_p = __builtin_amdgcn_rcp(piv);
-      inv_p = inv_p * (2.0 - piv * inv_p);
-      inv_p = inv_p * (2.0 - piv * inv_p);
-      const double g0 = buf[lane], g1 = buf[lane + 64];
+    // blocks (R, C), C > p: the first, (p + 1, p + 1), is wavefront 0's, which then factorises it; the others share the rest
+    const int cols = nb - 1 - p, blocks = nb * cols;
+    for (int u = w == 0 ? 0 : w; u < blocks; u += w == 0 ? blocks : 15) {
+      const int uu = u == 0 ? (p + 1) * cols : u <= (p + 1) * cols ? u - 1 : u;      // block (p + 1, p + 1) in front
+      const int R = uu / cols, C = p + 1 + uu % cols;
+      const f64x4 m = block_nt(M + 16 * R * CHOL_LDM, CHOL_LDM, M + 16 * C * CHOL_LDM, CHOL_LDM, row, g);
+      double *const B = S + 16 * R * ld + 16 * C;
 #pragma unroll
-      for (int i = 0; i < NC; ++i) {
-        const int C = w + 16 * i;
-        if (C > j && C < kb) {
-          const double gc = buf[C] * inv_p;
-          const double s0 = z0 ? 0.0 : S[i][0], s1 = z1 ? 0.0 : S[i][1];
-          S[i][0] = fma(-g0, gc, s0);
-          S[i][1] = fma(-g1, gc, s1);
-        }
+      for (int i = 0; i < 4; ++i) {
+        double *const b = B + (g + 4 * i) * ld + row;
+        *b = (R == p ? 0.0 : *b) - m[i];
       }
     }
-    // the buffer that column j + 1 is published to was last read at column j - 1, before this column's barrier
+    if (w == 0) factor(p + 1);
+    __syncthreads();
   }
-  __syncthreads();
+  // block row C of the result
+  for (int u = w; u < nb * nb; u += 16) {
+    const int C = u / nb, R = u - C * nb;
+    const double *const D = S + 16 * C * ld + 16 * C;
+    f64x4 m = {0.0, 0.0, 0.0, 0.0};
+    if (R < C) m = block_nt(D, ld, S + 16 * R * ld + 16 * C, ld, row, g);
+    if (R == C) {
 #pragma unroll
-  for (int i = 0; i < NC; ++i)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int R = lane + 64 * h, C = w + 16 * i;
-      if (R >= kb || C >= kb) continue;
-      // S[R][C] with R < C is r_{C, R}: row C of the inverse; everything above the diagonal of Rinv is zero
-      float v = 0.f;
-      if (R == C) v = (float)(1.0 / sqrt(pivs[R]));
-      else if (R < C) v = (float)(S[i][h] / sqrt(pivs[C]));
-      Rinv[C * kb + R] = v;
+      for (int i = 0; i < 4; ++i) m[i] = D[(g + 4 * i) * ld + row];
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 16 * C + g + 4 * i, c = 16 * R + row;
+      if (r < kb && c < kb) Rinv[r * kb + c] = (float)m[i];
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------- Rayleigh-Ritz (Jacobi)
@@ -835,18 +932,6 @@ __device__ __forceinline__ double row16_sum(double v) {
   v += dpp_move<0x141>(v);   // row_half_mirror
   v += dpp_move<0x140>(v);   // row_mirror
   return v;
-}
-
-// 1 / x and x^-1/2 to fp64 rounding level: hardware estimate, two Newton steps
-__device__ __forceinline__ double nr_rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = r * (2.0 - x * r);
-  return r * (2.0 - x * r);
-}
-__device__ __forceinline__ double nr_rsq(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  r = r * (1.5 - 0.5 * x * r * r);
-  return r * (1.5 - 0.5 * x * r * r);
 }
 
 // Eigenvectors of the symmetric positive semi-definite T[kb, kb] (fp64) by one-sided Jacobi rotations on the rows of
@@ -1360,9 +1445,9 @@ struct Carve {
   }
 };
 
-// element ranges of the partial Gram matrices: at most 128 of them, whole multiples of the 32 elements the kernel
-// stages at a time
-int gram_chunk(int len) { return (((len + 127) / 128) + 31) / 32 * 32; }
+// element ranges of the partial Gram matrices: at most 128 of them, whole multiples of the 64 elements that a workgroup's
+// wavefronts take at a time
+int gram_chunk(int len) { return (((len + 127) / 128) + 63) / 64 * 64; }
 int gram_parts(int len) { return (len + gram_chunk(len) - 1) / gram_chunk(len); }
 
 // row ranges of the k-means partial sums: at most 256 of them, at least 256 rows each
@@ -1564,15 +1649,50 @@ hipError_t set_lds(const void *kern, size_t bytes) {
   return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// Gram matrix W of kb vectors of n elements: vector a's element j at Y[a * sv + j] (kc) or Y[j * sv + a]; zy: bytes from one
+// subsample's vectors to the next
+int gram(const float *Y, long long zy, bool kc, int kb, int n, long long sv, EmbedWork &w, Group gr, hipStream_t st) {
+  const int nb = (kb + 15) / 16, parts = gram_parts(n);
+  const size_t lds = (size_t)2 * (nb * (nb + 1) / 2) * 256 * sizeof(double);
+  const bool v4 = kc && aligned16(Y) && sv % 4 == 0 && n % 4 == 0;
+  const dim3 grid((unsigned)parts, 1, (unsigned)gr.nz);
+#define GRAM_ONE(NB, K, V)                                                                                             \
+  do {                                                                                                                 \
+    TAP_HIP(set_lds((const void *)gram_partial_kernel<NB, K, V>, lds));                                                \
+    hipLaunchKernelGGL((gram_partial_kernel<NB, K, V>), grid, dim3(512), lds, st, Y, kb, n, sv, gram_chunk(n), w.part, zy, gr.zw); \
+  } while (0)
+#define GRAM_CASE(NB)                       \
+  case NB:                                  \
+    if (!kc) GRAM_ONE(NB, false, false);    \
+    else if (v4) GRAM_ONE(NB, true, true);  \
+    else GRAM_ONE(NB, true, false);         \
+    break;
+  switch (nb) {
+    GRAM_CASE(1)
+    GRAM_CASE(2)
+    GRAM_CASE(3)
+    GRAM_CASE(4)
+    GRAM_CASE(5)
+    GRAM_CASE(6)
+    GRAM_CASE(7)
+    GRAM_CASE(8)
+    default: TAP_FAIL(QC_ERR_UNSUPPORTED, "at most %d vectors", KB_MAX);
+  }
+#undef GRAM_CASE
+#undef GRAM_ONE
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((kb * kb + 255) / 256, 1, (unsigned)gr.nz), dim3(256), 0, st, w.part, parts, kb, w.W, gr.zw);
+  TAP_HIP(hipGetLastError());
+  return QC_OK;
+}
+
 // one pass of shifted Cholesky QR on the rows of `in` [kb, n] into `out` (`in` and `out` must differ); zin: bytes from one
 // subsample's rows to the next
 int cholqr_pass(const float *in, long long zin, float *out, int kb, int n, int check, EmbedWork &w, Group gr, int *fl, hipStream_t st) {
-  const int parts = gram_parts(n);
-  const unsigned nz = (unsigned)gr.nz;
-  hipLaunchKernelGGL(gram_partial_kernel, dim3(parts, 1, nz), dim3(256), 0, st, in, kb, n, (long long)n, 1ll, gram_chunk(n),
-                     w.part, zin, gr.zw);
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((kb * kb + 255) / 256, 1, nz), dim3(256), 0, st, w.part, parts, kb * kb, w.W, gr.zw);
-  hipLaunchKernelGGL(chol_inv_kernel, dim3(1, 1, nz), dim3(1024), 0, st, w.W, kb, 1e-12, check, w.Rinv, fl, gr.zw, ZF);
+  TAP_RC(gram(in, zin, true, kb, n, n, w, gr, st));
+  const int kp = (kb + 15) / 16 * 16;
+  const size_t lds = ((size_t)kp * (kp + 4) + (size_t)kp * CHOL_LDM) * sizeof(double);
+  TAP_HIP(set_lds((const void *)chol_inv_kernel, lds));
+  hipLaunchKernelGGL(chol_inv_kernel, dim3(1, 1, (unsigned)gr.nz), dim3(1024), lds, st, w.W, kb, 1e-12, check, w.Rinv, fl, gr.zw, ZF);
   TAP_HIP(hipGetLastError());
   SgemmArgs g{};
   g.A = w.Rinv; g.sam = kb; g.sak = 1; g.za = gr.zw;
@@ -1643,10 +1763,7 @@ int embed_impl(const float *L, int N, int n, int n0, int k, int kb, int iters, c
   bm.C = w.Bm; bm.ldc = kb; bm.zc = gr.zw;
   bm.M = N; bm.N = kb; bm.K = n;
   TAP_HIP(sgemm(bm, SE_PLAIN, gr.nz, st));
-  const int parts = gram_parts(N);
-  hipLaunchKernelGGL(gram_partial_kernel, dim3(parts, 1, nz), dim3(256), 0, st, w.Bm, kb, N, 1ll, (long long)kb, gram_chunk(N),
-                     w.part, gr.zw, gr.zw);
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((kb * kb + 255) / 256, 1, nz), dim3(256), 0, st, w.part, parts, kb * kb, w.W, gr.zw);
+  TAP_RC(gram(w.Bm, gr.zw, false, kb, N, kb, w, gr, st));
   const size_t lds = (size_t)kb * (kb + 2) * sizeof(double);
   TAP_HIP(set_lds((const void *)jacobi_kernel, lds));
   hipLaunchKernelGGL(jacobi_kernel, dim3(1, 1, nz), dim3(1024), lds, st, w.W, kb, k, 30, w.Wk, w.isig, sigma, gr.zw, zout);
