@@ -1,5 +1,5 @@
-// A tile of a float32 product on the matrix cores, C(m, n) = sum_k A[m, k] B[n, k], both operands contiguous along k: every
-// output one chain of float32 fused multiply-adds in ascending k.
+// A tile of a float32 product on the matrix cores, C(m, n) = sum_k A(m, k) B(n, k), both operands contiguous along k (run) or both
+// along their own index (run_tn): every output one chain of float32 fused multiply-adds in ascending k.
 //
 // v_mfma_f32_32x32x2_f32 adds its two products one after the other, each with the rounding of a fused multiply-add, in
 // ascending k (checked bit by bit against fmaf), so the result is that of a plain loop over k, whatever the tile; K is never split.
@@ -43,15 +43,13 @@ struct F32Tile {
     // c of row r lies at chunk c ^ swz(r) (so that the rows of a fragment read spread over the banks): the thread of a place
     // fetches the chunk that belongs there.
     const auto swz = [](int r) { return (BK == 64 ? r : BK == 32 ? r >> 1 : r >> 2) & (CH - 1); };
-    const int lr = tid / CH, lc = (tid % CH) ^ swz(lr);
-    static_assert(RP % 32 == 0 || 32 % RP == 0, "");
+    const int lr = tid / CH;
     const int ns = (K + BK - 1) / BK;
     unsigned ao[LM], bo[LN];                             // byte offsets of this thread's chunk in slab 0
 #pragma unroll
     for (int i = 0; i < LM; ++i) ao[i] = ((unsigned)(min(m0 + lr + RP * i, M - 1) - m0) * (unsigned)lda + ((tid % CH) ^ swz(lr + RP * i)) * 4) * 4;
 #pragma unroll
     for (int i = 0; i < LN; ++i) bo[i] = ((unsigned)(min(n0 + lr + RP * i, N - 1) - n0) * (unsigned)ldb + ((tid % CH) ^ swz(lr + RP * i)) * 4) * 4;
-    (void)lc;
     const float *ab = A + (size_t)m0 * lda, *bb = B + (size_t)n0 * ldb;
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) float *)slabs + wave * 1024;
     // (m0 is a reserved register, which a clobber list cannot name: nothing else in these kernels uses it, tests/test_codegen_cpu.py)
@@ -143,16 +141,101 @@ struct F32Tile {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // nothing lands in LDS after the workgroup's end
   }
 
-  // f(row in the tile, column in the tile, value) for the outputs of this lane
-  template <class F>
-  __device__ __forceinline__ void each(F f) const {
-    const int lane = threadIdx.x & 63;
+  // The same with A(m, k) = A[k * lda + m], B(n, k) = B[k * ldb + n]; M, N, lda, ldb multiples of 4.  A slab keeps k rows of RM (RN)
+  // floats; the 32-float halves of every odd row change places, so that the two k of a fragment read lie in different banks.
+  __device__ __forceinline__ void run_tn(const float *__restrict__ A, size_t lda, const float *__restrict__ B, size_t ldb, int M, int N,
+                                         int K, int m0, int n0, float *slabs) {
+    static_assert(RM % 64 == 0 && RN % 64 == 0 && NT % (RM / 4) == 0 && NT % (RN / 4) == 0, "");
+    constexpr int PA = NT / (RM / 4), PB = NT / (RN / 4);              // k rows per pass
+    constexpr int XA = BK / PA, XB = BK / PB, XL = XA + XB, XSLAB = BK * (RM + RN);
+    static_assert(XA * PA == BK && XB * PB == BK && XSLAB <= SLAB && PA % 2 == 0 && PB % 2 == 0, "");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ka = tid / (RM / 4), ca = ((tid % (RM / 4)) ^ ((ka & 1) << 3)) * 4, kb = tid / (RN / 4), cb = ((tid % (RN / 4)) ^ ((kb & 1) << 3)) * 4;
+    const int ns = (K + BK - 1) / BK, nk = K - (ns - 1) * BK;          // k of the last slab
+    const unsigned am = (unsigned)min(m0 + ca, M - 4) * 4, bn = (unsigned)min(n0 + cb, N - 4) * 4;
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) float *)slabs + wave * 1024;
+    auto load = [&](int s, int b, int i) {               // slabs past the end re-read the last one, rows past K the last row
+      const bool of_a = i < XA;
+      const int k = of_a ? ka + PA * i : kb + PB * (i - XA);
+      const int kc = s >= ns - 1 ? min(k, nk - 1) : k;
+      const unsigned off = (unsigned)kc * (unsigned)((of_a ? lda : ldb) * 4) + (of_a ? am : bn);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds0 + (b * XSLAB + (of_a ? i * PA * RM : BK * RM + (i - XA) * PB * RN)) * 4),
+                   "v"(off), "s"((of_a ? A : B) + (size_t)min(s, ns - 1) * BK * (of_a ? lda : ldb))
+                   : "memory");
+    };
+    wm = (wave / WN) * 32 * TM;
+    wn = (wave % WN) * 32 * TN;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) f(wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), wn + 32 * j + (lane & 31), acc[i][j][r]);
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    const int row = lane & 31, h = lane >> 5;
+    float fa[2][BK / 2][TM], fb[2][BK / 2][TN];
+    auto read = [&](int f, int b, int n) {
+      const int e = n / (TM + TN), i = n % (TM + TN);
+      if (i < TM) {
+        const int x = wm + 32 * i + row;
+        fa[f][e][i < TM ? i : 0] = slabs[b * XSLAB + (2 * e + h) * RM + (((x >> 2) ^ (h << 3)) << 2) + (x & 3)];
+      } else {
+        const int x = wn + 32 * (i - TM) + row;
+        fb[f][e][i < TM ? 0 : i - TM] = slabs[b * XSLAB + BK * RM + (2 * e + h) * RN + (((x >> 2) ^ (h << 3)) << 2) + (x & 3)];
+      }
+    };
+    auto mul = [&](int f, int n) {
+      const int e = n / (TM * TN), i = n / TN % TM, j = n % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[f][e][i], fb[f][e][j], acc[i][j], 0, 0, 0);
+    };
+    constexpr int NM = BK / 2 * TM * TN, NR = BK / 2 * (TM + TN);
+    constexpr int RB = (NR + NM - 3) / (NM - 2), LB = (XL + NM - 3) / (NM - 2);
+    auto step = [&](int s, int u) {                      // as in run
+      const int f = u & 1;
+#pragma unroll
+      for (int n = 0; n < NM; ++n) {
+        __builtin_amdgcn_sched_barrier(0);
+        mul(f, n);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = n * RB; r < min(n * RB + RB, NR); ++r) read(f ^ 1, (u + 1) % NS, r);
+#pragma unroll
+        for (int l = n * LB; l < min(n * LB + LB, XL); ++l) load(s + NS, u, l);
+        if (n == NM - 2) slab_barrier<(NS - 2) * XL>();
+      }
+    };
+#pragma unroll
+    for (int b = 0; b < NS; ++b)
+#pragma unroll
+      for (int i = 0; i < XL; ++i) load(b, b, i);
+    slab_barrier<(NS - 2) * XL>();
+#pragma unroll
+    for (int r = 0; r < NR; ++r) read(0, 0, r);
+    slab_barrier<(NS - 2) * XL>();
+    int s = 0;
+    for (; s + NS < ns; s += NS) {
+#pragma unroll
+      for (int u = 0; u < NS; ++u) step(s + u, u);
+    }
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      if (s + u + 1 < ns) {
+        step(s + u, u);
+      } else if (s + u < ns) {                           // no slab follows; an odd K leaves half a pair
+        const int f = u & 1;
+#pragma unroll
+        for (int e = 0; e < BK / 2; ++e) {
+          if (2 * e >= nk) break;
+          const bool in = 2 * e + h < nk;
+#pragma unroll
+          for (int i = 0; i < TM; ++i) fa[f][e][i] = in ? fa[f][e][i] : 0.f;
+#pragma unroll
+          for (int j = 0; j < TN; ++j) fb[f][e][j] = in ? fb[f][e][j] : 0.f;
+#pragma unroll
+          for (int n = 0; n < TM * TN; ++n) mul(f, e * TM * TN + n);
+        }
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
 };
 

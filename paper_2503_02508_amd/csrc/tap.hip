@@ -306,27 +306,30 @@ __global__ __launch_bounds__(256, 2) void sgemm_kernel(SgemmArgs p) {
   }
 }
 
-// The same product for operands that are both contiguous along k and take 16-byte loads, K a multiple of 4 (split K: whole slabs),
-// on tiles of 64 WT x 64 WT whose slabs go straight to LDS (gemm_f32_tile.h).  Same chains, same bits.  What bounds it: the matrix
+// The same product for operands that are both contiguous along k, K a multiple of 4 (split K: whole slabs), or both along their own
+// index, and take 16-byte loads, on tiles of 64 WT x 64 WT whose slabs go straight to LDS (gemm_f32_tile.h).  Same chains, same bits.  What bounds it: the matrix
 // rate at the clock the chip holds (2.1 - 2.3 GHz), 93 % of the cycles multiplying.  32768 x 1638 x 4096: 4.2 ms on sgemm_kernel
 // (105 TFLOP/s, slabs through registers, two workgroups a compute unit), 3.2 here (138; four buffers 3.3, eight 3.2, ten 3.25, slabs of
 // 32 k 3.3, wavefronts of 128 x 64 3.5, tiles of 128 x 256 3.25); the library's product takes 2.96.  The order of the tiles made
-// no difference.
+// no difference.  L^T L of 32768 x 1640 (three): 3.0 ms there, 2.6 here.
 constexpr int NT_BK = 16;
-template <int WT, int EPI>
-__global__ __launch_bounds__(256, WT == 2 ? 1 : 2) void sgemm_nt_kernel(SgemmArgs p) {
+template <int WT, int EPI, bool TN>      // TN: both operands contiguous along their own index (plain products)
+__global__ __launch_bounds__(256, WT == 2 ? 1 : 2) void sgemm_slab_kernel(SgemmArgs p) {
   using Tile = qc::F32Tile<2, 2, WT, WT, NT_BK, 6>;
   __shared__ __align__(16) float slabs[6 * Tile::SLAB];
   const int tiles_m = (p.M + Tile::RM - 1) / Tile::RM, tiles_n = (p.N + Tile::RN - 1) / Tile::RN;
-  const int total = tiles_m * tiles_n, per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
+  const int total = TN && p.sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n, per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
   const int t = (blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
   if (blockIdx.x / NUM_XCD >= per_xcd || t >= total) return;
-  const int m0 = __builtin_amdgcn_readfirstlane(t / tiles_n * Tile::RM), n0 = __builtin_amdgcn_readfirstlane(t % tiles_n * Tile::RN);
+  int tm = t / tiles_n, tn = t % tiles_n;
+  if (TN && p.sym) tri_decode(t, tm, tn);
+  const int m0 = __builtin_amdgcn_readfirstlane(tm * Tile::RM), n0 = __builtin_amdgcn_readfirstlane(tn * Tile::RN);
   const float *A = in_slot(p.A, p.za), *B = in_slot(p.B, p.zb);
   float *C = in_slot(p.C, gridDim.y > 1 ? p.zpart : p.zc) + (EPI == SE_PLAIN ? (long long)blockIdx.y * p.part_stride : 0);
   const int kbeg = EPI == SE_PLAIN ? blockIdx.y * p.kchunk : 0, kend = EPI == SE_PLAIN ? min(p.K, kbeg + p.kchunk) : p.K;
   Tile tile;
-  tile.run(A + kbeg, (size_t)p.sam, B + kbeg, (size_t)p.sbn, p.M, p.N, kend - kbeg, m0, n0, slabs);
+  if (TN) tile.run_tn(A + (size_t)kbeg * p.sak, (size_t)p.sak, B + (size_t)kbeg * p.sbk, (size_t)p.sbk, p.M, p.N, kend - kbeg, m0, n0, slabs);
+  else tile.run(A + kbeg, (size_t)p.sam, B + kbeg, (size_t)p.sbn, p.M, p.N, kend - kbeg, m0, n0, slabs);
   // register r of a 32 x 32 block is row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32
   const int lane = threadIdx.x & 63;
   const float *rs = nullptr, *tr = nullptr, *tc = nullptr, *cs = nullptr;
@@ -436,23 +439,26 @@ hipError_t sgemm(SgemmArgs a, int epi, int nz, hipStream_t st, float *part = nul
     }
   }
   const bool vec = a.a_vec && a.b_vec;
-  // both operands contiguous along k, whole 16-byte chunks: the kernel whose slabs go straight to LDS.  Tiles of 128 x 128 while they
-  // fill the chip, of 64 x 64 below (1536 x 160 x 256, three subsamples: 38 us on sgemm_kernel, 21 on 128 x 128, 12 on 64 x 64)
-  // (its offsets inside a tile are 32-bit bytes: rows shorter than 2^22 floats)
-  if (vec && a.a_kc && a.b_kc && a.K >= 4 && a.sam < (1 << 22) && a.sbn < (1 << 22)) {
-    const long long t2 = (long long)tiles * splits * nz;
-    const int wt = t2 >= 256 ? 2 : 1;
-    const int nt_tiles = wt == 2 ? tiles : ((a.M + 63) / 64) * ((a.N + 63) / 64);
-    const dim3 nt_grid((unsigned)((nt_tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD), (unsigned)splits, (unsigned)nz);
-#define NT_LAUNCH(E)                                                                                       \
+  // Both operands contiguous along k or both along their own index, whole 16-byte chunks: the kernel whose slabs go straight to LDS
+  // (its offsets inside a tile are 32-bit bytes: rows shorter than 2^22 floats).  Tiles of 128 x 128 while they fill the chip, of
+  // 64 x 64 below (1536 x 160 x 256, three subsamples: 38 us on sgemm_kernel, 21 on 128 x 128, 16 on 64 x 64).
+  const bool nt = a.a_kc && a.b_kc && a.sam < (1 << 22) && a.sbn < (1 << 22);
+  const bool tn = !a.a_kc && !a.b_kc && epi == SE_PLAIN && a.sak < (1 << 22) && a.sbk < (1 << 22);
+  if (vec && a.K >= 4 && a.M >= 4 && a.N >= 4 && (nt || tn)) {
+    const int wt = (long long)tiles * splits * nz >= 256 ? 2 : 1;
+    const int side = (a.M + 63) / 64;
+    const int slab_tiles = wt == 2 ? tiles : a.sym ? side * (side + 1) / 2 : side * ((a.N + 63) / 64);
+    const dim3 slab_grid((unsigned)((slab_tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD), (unsigned)splits, (unsigned)nz);
+#define SLAB_LAUNCH(E, T)                                                                                  \
   do {                                                                                                     \
-    if (wt == 2) hipLaunchKernelGGL((sgemm_nt_kernel<2, E>), nt_grid, dim3(256), 0, st, a);                \
-    else hipLaunchKernelGGL((sgemm_nt_kernel<1, E>), nt_grid, dim3(256), 0, st, a);                        \
+    if (wt == 2) hipLaunchKernelGGL((sgemm_slab_kernel<2, E, T>), slab_grid, dim3(256), 0, st, a);         \
+    else hipLaunchKernelGGL((sgemm_slab_kernel<1, E, T>), slab_grid, dim3(256), 0, st, a);                 \
   } while (0)
-    if (epi == SE_SIM) NT_LAUNCH(SE_SIM);
-    else if (epi == SE_COLSCALE) NT_LAUNCH(SE_COLSCALE);
-    else NT_LAUNCH(SE_PLAIN);
-#undef NT_LAUNCH
+    if (tn) SLAB_LAUNCH(SE_PLAIN, true);
+    else if (epi == SE_SIM) SLAB_LAUNCH(SE_SIM, false);
+    else if (epi == SE_COLSCALE) SLAB_LAUNCH(SE_COLSCALE, false);
+    else SLAB_LAUNCH(SE_PLAIN, false);
+#undef SLAB_LAUNCH
   } else {
 #define SG_LAUNCH(AK, BK, E)                                                                                   \
   do {                                                                                                         \
@@ -557,6 +563,44 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float *A, int
   if (ph == 0 && col < n) part[(long long)blockIdx.y * n + col] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }
 
+// Both sums in one pass over A for up to 64 NC columns: the same row ranges and phases, a wavefront's lanes across a row, the
+// column sums of its phase in registers.  What bounds it: the pass over A (three of 215 MB: 390 us as two kernels, 182 here).
+template <int NC>
+__global__ __launch_bounds__(256) void degree_sums_kernel(const float *A, int N, int n, int lda, float *dr, double *part, long long zw) {
+  A = in_slot(A, zw);
+  dr = in_slot(dr, zw);
+  part = in_slot(part, zw);
+  __shared__ double red[4][64];
+  const int lane = threadIdx.x & 63, ph = threadIdx.x >> 6;
+  const int rows_per = (N + COL_CHUNKS - 1) / COL_CHUNKS;
+  const int r0 = blockIdx.x * rows_per, r1 = min(N, r0 + rows_per);
+  double cs[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) cs[c] = 0.0;
+  for (int r = r0 + ph; r < r1; r += 4) {
+    const float *a = A + (long long)r * lda;
+    float v[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) v[c] = a[min(lane + 64 * c, n - 1)];
+    double s = 0.0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const double d = lane + 64 * c < n ? (double)v[c] : 0.0;
+      s += d;
+      cs[c] += d;
+    }
+    s = wave_sum(s);
+    if (lane == 0) dr[r] = (float)s;
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    __syncthreads();
+    red[ph][lane] = cs[c];
+    __syncthreads();
+    if (ph == 0 && lane + 64 * c < n) part[(long long)blockIdx.x * n + lane + 64 * c] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+  }
+}
+
 __global__ __launch_bounds__(256) void colsum_final_kernel(const double *part, int n, float *dc, long long zw) {
   part = in_slot(part, zw);
   dc = in_slot(dc, zw);
@@ -586,20 +630,41 @@ __global__ __launch_bounds__(256) void degree_check_kernel(const float *dr, int 
 }
 
 // `guard` (may be null): a device flag raised by the degree check; the matrix is left alone when it is set.  Rows lie lda
-// floats apart; what lies between (a workspace matrix with padded rows) becomes zero.
+// floats apart; what lies between (a workspace matrix with padded rows) becomes zero.  A workgroup takes NORM_ROWS rows of 256 VEC
+// columns: the reciprocal roots of its rows and columns are formed once, so that the pass is bound by its bytes (three matrices of
+// 215 MB: 656 us with both roots per element, 250 here).
+constexpr int NORM_ROWS = 8;
+template <int VEC>
 __global__ __launch_bounds__(256) void normalise_kernel(float *A, const float *dr, const float *dc, int N, int n, int lda,
                                                         const int *guard, long long zw, long long zflag) {
   if (guard && *in_slot(guard, zflag)) return;
   A = in_slot(A, zw);
   dr = in_slot(dr, zw);
   dc = in_slot(dc, zw);
-  const int nblk = (lda + 255) / 256;
-  const int r = blockIdx.x / nblk;
-  const int h = (blockIdx.x % nblk) * 256 + threadIdx.x;
+  __shared__ float ir[NORM_ROWS];
+  const int nblk = (lda + 256 * VEC - 1) / (256 * VEC);
+  const int r0 = blockIdx.x / nblk * NORM_ROWS, h = (blockIdx.x % nblk * 256 + threadIdx.x) * VEC;
+  if (threadIdx.x < NORM_ROWS && r0 + (int)threadIdx.x < N) ir[threadIdx.x] = 1.f / sqrtf(dr[r0 + threadIdx.x]);
+  __syncthreads();
   if (h >= lda) return;
-  float *a = A + (long long)r * lda + h;
-  if (h >= n) *a = 0.f;
-  else *a *= (1.f / sqrtf(dr[r])) * (1.f / sqrtf(dc[h]));
+  float ic[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) ic[e] = h + e < n ? 1.f / sqrtf(dc[h + e]) : 0.f;
+  const int rows = min(NORM_ROWS, N - r0);
+  float *a = A + (long long)r0 * lda + h;
+#pragma unroll 4
+  for (int r = 0; r < rows; ++r, a += lda) {
+    if constexpr (VEC == 4) {
+      float4 v = *(const float4 *)a;
+      v.x = h < n ? v.x * (ir[r] * ic[0]) : 0.f;
+      v.y = h + 1 < n ? v.y * (ir[r] * ic[1]) : 0.f;
+      v.z = h + 2 < n ? v.z * (ir[r] * ic[2]) : 0.f;
+      v.w = h + 3 < n ? v.w * (ir[r] * ic[3]) : 0.f;
+      *(float4 *)a = v;
+    } else {
+      *a = h < n ? *a * (ir[r] * ic[0]) : 0.f;
+    }
+  }
 }
 
 // rows of n floats copied to rows of ld floats, zeros behind them
@@ -1613,8 +1678,16 @@ int similarity_impl(const float *X, const float *t, int N, int F, const int *idx
     TAP_HIP(hipEventRecord(g_prof.ev[g_prof.used++].second, st));
     g_prof.products += gr.nz;
   }
-  hipLaunchKernelGGL(rowsum_kernel, dim3((N + 3) / 4, 1, nz), dim3(256), 0, st, A, N, n, lda, d_r, gr.zw);
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3((n + 63) / 64, COL_CHUNKS, nz), dim3(256), 0, st, A, N, n, lda, w.colpart, gr.zw);
+#define DEGREE_SUMS(NC) hipLaunchKernelGGL(degree_sums_kernel<NC>, dim3(COL_CHUNKS, 1, nz), dim3(256), 0, st, A, N, n, lda, d_r, w.colpart, gr.zw)
+  if (n <= 64 * 3) DEGREE_SUMS(3);
+  else if (n <= 64 * 8) DEGREE_SUMS(8);
+  else if (n <= 64 * 16) DEGREE_SUMS(16);
+  else if (n <= 64 * 26) DEGREE_SUMS(26);
+  else {      // more columns than a wavefront keeps sums of
+    hipLaunchKernelGGL(rowsum_kernel, dim3((N + 3) / 4, 1, nz), dim3(256), 0, st, A, N, n, lda, d_r, gr.zw);
+    hipLaunchKernelGGL(colsum_partial_kernel, dim3((n + 63) / 64, COL_CHUNKS, nz), dim3(256), 0, st, A, N, n, lda, w.colpart, gr.zw);
+  }
+#undef DEGREE_SUMS
   hipLaunchKernelGGL(colsum_final_kernel, dim3((n + 255) / 256, 1, nz), dim3(256), 0, st, w.colpart, n, d_c, gr.zw);
   TAP_HIP(hipGetLastError());
   if (ext) return QC_OK;
@@ -1638,8 +1711,13 @@ int normalise_impl(float *A, const float *d_r, const float *d_c, int N, int n, i
     if (flag) TAP_FAIL(QC_ERR_RANGE, "a degree of the similarity matrix is not positive and finite");
   }
   // with a deferred check the kernel itself leaves the matrix alone when the flag is up
-  hipLaunchKernelGGL(normalise_kernel, dim3(((lda + 255) / 256) * N, 1, nz), dim3(256), 0, st, A, d_r, d_c, N, n, lda,
-                     ext ? (const int *)ext : (const int *)nullptr, gr.zw, ZF);
+  const unsigned row_blocks = (unsigned)((N + NORM_ROWS - 1) / NORM_ROWS);
+  if (lda % 4 == 0 && aligned16(A))
+    hipLaunchKernelGGL(normalise_kernel<4>, dim3((unsigned)((lda + 1023) / 1024) * row_blocks, 1, nz), dim3(256), 0, st, A, d_r, d_c, N, n,
+                       lda, ext ? (const int *)ext : (const int *)nullptr, gr.zw, ZF);
+  else
+    hipLaunchKernelGGL(normalise_kernel<1>, dim3((unsigned)((lda + 255) / 256) * row_blocks, 1, nz), dim3(256), 0, st, A, d_r, d_c, N, n,
+                       lda, ext ? (const int *)ext : (const int *)nullptr, gr.zw, ZF);
   TAP_HIP(hipGetLastError());
   if (!ext) TAP_HIP(hipStreamSynchronize(st));
   return QC_OK;

@@ -131,7 +131,7 @@ def test_no_store_loses_its_data_to_the_next_instruction(tmp_path):
         for part in re.split(r"^(?=<_Z\w+>:)", text, flags=re.M)[1:]:
             name, _, body = part.partition("\n")
             kernels += "s_endpgm" in body
-            if "linear_f32_kernel" in name or "sgemm_nt_kernel" in name:        # its loads to LDS write m0 in inline assembly, unknown to the compiler
+            if "linear_f32_kernel" in name or "sgemm_slab_kernel" in name:        # its loads to LDS write m0 in inline assembly, unknown to the compiler
                 assert all(l.strip().startswith("s_mov_b32 m0,") for l in body.splitlines() if re.search(r"\bm0\b", l))
             # a product that follows too closely reads the old half (27 % of the codes of 1 x 256 tokens, 6 heads of 64, were wrong)
             early = _half_written_operands(body.splitlines())
