@@ -7,7 +7,9 @@
 //     the chip sustains 4.1 against 3.4 Pop/s.  Consecutive products share one operand (the row blocks are walked forth and
 //     back), which is worth another 2 %;
 //   * tile 128 (M) x 256 (N), four wavefronts side by side along N, each 128 x 64 (8 x 4 blocks of 16 x 16), two workgroups
-//     per compute unit so that one tile's prologue and epilogue run under the other's main loop;
+//     per compute unit so that one tile's prologue and epilogue run under the other's main loop.  A launch with too few of those
+//     for the chip takes tiles of 64 rows (4 x 4 blocks a wavefront), which ask for their operands a slab earlier since a slab
+//     lasts half as long (the rule and both sides' times stand at big_rows);
 //   * weights never touch LDS: they are stored a second time in MFMA fragment order (fragment (n / 32, k / 32) = 64 lanes x
 //     16 bytes, lane l = row n % 32 = l % 32, bytes 16 (l / 32) .. of the 32 k values; packed nibbles: 8 bytes per lane) and
 //     each wavefront streams the fragments of its own 64 columns straight into registers, 128 k ahead;
@@ -35,28 +37,32 @@
 namespace qc {
 
 // a wait, tied to the registers that become valid with it: their uses cannot be moved above it
+#define QC_WAIT_VM_FOR2(n, r0, r1) asm volatile("s_waitcnt vmcnt(" #n ")" : "+v"(r0), "+v"(r1)::"memory")
 #define QC_WAIT_VM_FOR4(n, r0, r1, r2, r3) asm volatile("s_waitcnt vmcnt(" #n ")" : "+v"(r0), "+v"(r1), "+v"(r2), "+v"(r3)::"memory")
 // all LDS writes of this wavefront done, then the workgroup barrier
 #define QC_LDS_DONE_BARRIER asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
 #define QC_SB __builtin_amdgcn_sched_barrier(0)
 
-constexpr int BIG_BM = 128, BIG_BN = 256, BIG_BK = 128;
-constexpr int BIG_TM = 8, BIG_TN = 4;                                    // 16 x 16 blocks of a wavefront
+constexpr int BIG_BN = 256, BIG_BK = 128;
+constexpr int BIG_TN = 4;                                                // 16 x 16 blocks of a wavefront: TM (8 or 4) x BIG_TN
 constexpr int BIG_CST = 4 * BIG_BN;                                      // floats: per-column constants of the epilogue
-constexpr int BIG_SMEM_LOOP = 2 * BIG_BM * BIG_BK;                       // two activation slabs
+template <int TM>
+constexpr int big_smem_loop = 2 * 16 * TM * BIG_BK;                      // two activation slabs
 constexpr int BIG_VR = 64 + 4;                                           // floats per staged V^T row (64 tokens)
 constexpr int BIG_SMEM_QKV = 4 * 64 * BIG_VR * 4;                        // 64 features of each wavefront
 constexpr int BIG_SROW = BIG_BN + 16;                                    // bytes per staged row of codes
 constexpr int BIG_SMEM_RESID = 4 * 32 * (64 + 4) * 4;                    // 32 rows of each wavefront
 constexpr int BIG_FIX_CAP = 1024;                                        // groups of four fc1 outputs decided again in float64, per tile
-constexpr int BIG_SMEM_GELU = BIG_BM * BIG_SROW + 16 + BIG_FIX_CAP * 32;
+template <int TM>
+constexpr int big_smem_gelu = 16 * TM * BIG_SROW + 16 + BIG_FIX_CAP * 32;
 
-typedef v4i BigAcc[BIG_TM][BIG_TN];
+template <int TM>
+using BigAcc = v4i[TM][BIG_TN];
 
 // Epilogues.  acc[i][j] is the 16 x 16 block of rows m0 + 16 i .. and columns n0 + wn0 + 16 j ..; the weights are the first
 // MFMA operand, so a lane holds row lane % 16 and the columns 4 (lane / 16) + e of a block.  cst: per-column constants in LDS,
 // BIG_BN each of w_scale, bias and, for the residual, the gates of the first and of the next batch element.  RAG: the tile may
-// end beyond the last row and may span two batch elements (which have at least BIG_BM rows each); otherwise it is whole and
+// end beyond the last row and may span two batch elements (which have at least as many rows as a tile); otherwise it is whole and
 // inside one.
 
 // Stores 16 bytes a lane at `off` bytes (a vector register) from the buffer's start.  The whole offset goes through the vector
@@ -91,7 +97,8 @@ struct BigCols {
 // 32 rows (row blocks ip, ip + 1) of a wavefront's 64 columns to its part of LDS, dequantised, rows of BIG_SR floats; afterwards
 // lane l reads columns 4 (l % 16) .. + 3 of the rows l / 16, l / 16 + 4, ...
 constexpr int BIG_SR = 64 + 4;
-__device__ __forceinline__ void big_stage_rows(const BigAcc &acc, float *stage, const float *cst, int wn0, float a_s, int ip) {
+template <int TM>
+__device__ __forceinline__ void big_stage_rows(const BigAcc<TM> &acc, float *stage, const float *cst, int wn0, float a_s, int ip) {
   const int lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
   int nl = wn0 + g * 4;
   asm volatile("" : "+v"(nl));                                // the constants are read again by the next pass, not kept
@@ -107,12 +114,13 @@ __device__ __forceinline__ void big_stage_rows(const BigAcc &acc, float *stage, 
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // (LDS operations of a wavefront are in order)
 }
 
-__device__ __forceinline__ void big_gelu(const GemmArgs &p, BigAcc &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+template <int TM>
+__device__ __forceinline__ void big_gelu(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
   const int tid = threadIdx.x, lane = tid & 63, wn0 = (tid >> 6) * 64, row = lane & 15, g = lane >> 4;
-  unsigned char *stage = smem;                         // [BIG_BM][BIG_SROW] codes
+  unsigned char *stage = smem;                         // [16 TM][BIG_SROW] codes
   // Elements whose fast evaluation lands too close to a rounding boundary of Eq. 1 to be trusted are queued here and
   // decided again in float64 (gelu_code_exact): the codes are then those of exact arithmetic on the accumulators.
-  int *fix_cnt = (int *)(stage + BIG_BM * BIG_SROW);
+  int *fix_cnt = (int *)(stage + 16 * TM * BIG_SROW);
   int *fix_ent = fix_cnt + 4;                          // [BIG_FIX_CAP][8]: a lane's four accumulators, row and first column
   if (tid == 0) *fix_cnt = 0;
   __syncthreads();
@@ -126,7 +134,7 @@ __device__ __forceinline__ void big_gelu(const GemmArgs &p, BigAcc &acc, unsigne
 #pragma unroll
     for (int e = 0; e < 4; ++e) sc[e] *= a_s;
 #pragma unroll
-    for (int i = 0; i < BIG_TM; i += 2) {
+    for (int i = 0; i < TM; i += 2) {
       float clear[2][4];
 #pragma unroll
       for (int u = 0; u < 2; ++u) *(unsigned *)(stage + ((i + u) * 16 + row) * BIG_SROW + nl) = gq.codes(acc[i + u][j], sc, bs, clear[u]);
@@ -157,21 +165,22 @@ __device__ __forceinline__ void big_gelu(const GemmArgs &p, BigAcc &acc, unsigne
   const int cc = (tid & 15) * 16;
   if (n0 + cc >= p.N) return;                          // N is a multiple of 32
 #pragma unroll
-  for (int q = 0; q < BIG_BM / 16; ++q) {
+  for (int q = 0; q < TM; ++q) {
     const int r = (tid >> 4) + q * 16;
     if (m0 + r < p.M) __builtin_nontemporal_store(*(const v4i *)(stage + r * BIG_SROW + cc), (v4i *)(p.q_out + (size_t)(m0 + r) * p.ldq + n0 + cc));
   }
 }
 
-template <bool RAG>
-__device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+template <int TM, bool RAG>
+__device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
   if (n0 + wn0 >= p.N) return;
+  constexpr int BM = 16 * TM;
   const int T = p.rows_per_batch, D = p.N / 3;
   const int part = (n0 + wn0) / D, nn0 = n0 + wn0 - part * D;      // D is a multiple of 128: a wavefront's columns lie inside one of Q, K, V
   const int b = m0 / T, tb = m0 - b * T;                      // batch element and token of the tile's first row
-  const int rows = RAG ? min(BIG_BM, p.M - m0) : BIG_BM;      // rows of the tile that exist
-  const int bnd = RAG ? min(rows, T - tb) : BIG_BM;           // rows of the first batch element (the others: of the next)
+  const int rows = RAG ? min(BM, p.M - m0) : BM;      // rows of the tile that exist
+  const int bnd = RAG ? min(rows, T - tb) : BM;           // rows of the first batch element (the others: of the next)
   const float inv_hd = 1.0f / (float)p.hd;
   const auto head_of = [&](int nn) { return (int)(((float)nn + 0.5f) * inv_hd); };      // nn / hd, exactly (nn < 2^16)
   float *stage = (float *)smem + wave * (64 * BIG_VR);
@@ -181,8 +190,8 @@ __device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc &acc, unsigned
     const int col = row * 4, nn = nn0 + col, h = head_of(nn), e = nn - h * p.hd;
     const int off = ((h * T + tb + g) * p.hd + e) * 4;
 #pragma unroll
-    for (int ip = 0; ip < BIG_TM; ip += 2) {
-      big_stage_rows(acc, stage, cst, wn0, a_s, ip);
+    for (int ip = 0; ip < TM; ip += 2) {
+      big_stage_rows<TM>(acc, stage, cst, wn0, a_s, ip);
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const v4u v = *(const v4u *)(stage + (q * 4 + g) * BIG_SR + col);
@@ -200,11 +209,11 @@ __device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc &acc, unsigned
     return;
   }
   // V^T: 64 tokens of the wavefront's 64 features at a time
-  const bool edge = RAG && (bnd < BIG_BM || (tb & 31) != 0);
+  const bool edge = RAG && (bnd < BM || (tb & 31) != 0);
 #pragma unroll
-  for (int rh = 0; rh < 2; ++rh) {
+  for (int rh = 0; rh < TM / 4; ++rh) {
     int nl = wn0 + g * 4;
-    asm volatile("" : "+v"(nl));                              // the constants are read again in the second pass, not kept
+    asm volatile("" : "+v"(nl));                              // the constants are read again in the next pass, not kept
 #pragma unroll
     for (int j = 0; j < BIG_TN; ++j) {
       const BigCols c(cst, nl + j * 16, a_s);
@@ -251,14 +260,15 @@ __device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc &acc, unsigned
   }
 }
 
-template <bool RBF, bool RAG>
-__device__ __forceinline__ void big_resid(const GemmArgs &p, BigAcc &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+template <int TM, bool RBF, bool RAG>
+__device__ __forceinline__ void big_resid(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
   const int left = p.N - n0 - wn0;                            // columns from this wavefront's first to the matrix's end (a multiple of 32)
   if (left <= 0) return;
+  constexpr int BM = 16 * TM;
   const int b0 = m0 / p.rows_per_batch;
-  const int rows = RAG ? min(BIG_BM, p.M - m0) : BIG_BM;      // rows of the tile that exist
-  const int bnd = RAG ? min(rows, (b0 + 1) * p.rows_per_batch - m0) : BIG_BM;      // rows of the first batch element
+  const int rows = RAG ? min(BM, p.M - m0) : BM;      // rows of the tile that exist
+  const int bnd = RAG ? min(rows, (b0 + 1) * p.rows_per_batch - m0) : BM;      // rows of the first batch element
   // element sizes: float32, or (RBF) either tensor may be bfloat16
   const int xb = RBF ? p.x_bf16 : 0, cb = RBF ? p.cache_bf16 : 0;
   const size_t tile0 = (size_t)m0 * p.N + n0 + wn0;           // first element of this wavefront's columns
@@ -291,9 +301,9 @@ __device__ __forceinline__ void big_resid(const GemmArgs &p, BigAcc &acc, unsign
 #pragma unroll
   for (int k = 0; k < XD; ++k) load_x(2 * k);
 #pragma unroll
-  for (int ip = 0; ip < BIG_TM; ip += 2) {
+  for (int ip = 0; ip < TM; ip += 2) {
     QC_SB;
-    big_stage_rows(acc, stage, cst, wn0, a_s, ip);
+    big_stage_rows<TM>(acc, stage, cst, wn0, a_s, ip);
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int m = ip * 16 + q * 4;
@@ -315,22 +325,23 @@ __device__ __forceinline__ void big_resid(const GemmArgs &p, BigAcc &acc, unsign
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     QC_SB;
-    if (ip + 2 * XD < BIG_TM) load_x(ip + 2 * XD);
+    if (ip + 2 * XD < TM) load_x(ip + 2 * XD);
   }
 }
 
 // float32 rows [M, ldy], any N and M
-__device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+template <int TM>
+__device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
-  const int left = p.N - n0 - wn0, rows = min(BIG_BM, p.M - m0);
+  const int left = p.N - n0 - wn0, rows = min(16 * TM, p.M - m0);
   if (left <= 0) return;
   float *stage = (float *)smem + wave * (32 * BIG_SR);
   const auto buf = __builtin_amdgcn_make_buffer_rsrc(p.y + (size_t)m0 * p.ldy + n0 + wn0, 0, -1, 0x00027000);
   const int col = row * 4;
 #pragma unroll
-  for (int ip = 0; ip < BIG_TM; ip += 2) {
+  for (int ip = 0; ip < TM; ip += 2) {
     QC_SB;
-    big_stage_rows(acc, stage, cst, wn0, a_s, ip);
+    big_stage_rows<TM>(acc, stage, cst, wn0, a_s, ip);
     if ((p.N & 3) == 0) {                                     // whole groups of four columns
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
@@ -351,10 +362,12 @@ __device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc &acc, unsigned
   }
 }
 
-template <int EPI, int TAG, bool W4, bool RBF, bool RAG>
+template <int TM, int EPI, int TAG, bool W4, bool RBF, bool RAG>
 __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
-  constexpr int BM = BIG_BM, BN = BIG_BN, BK = BIG_BK, TM = BIG_TM, TN = BIG_TN;
-  constexpr int PA = 4;                           // 16-byte activation chunks per thread per slab
+  static_assert(TM == 8 || TM == 4, "");
+  constexpr int BM = 16 * TM, BN = BIG_BN, BK = BIG_BK, TN = BIG_TN;
+  constexpr int PA = BM / 32;                     // 16-byte activation chunks per thread per slab
+  constexpr int AHEAD = TM == 8 ? 1 : 2;          // slabs that the operands are requested ahead of the one multiplied
   constexpr int SLAB = BM * BK;
   extern __shared__ __align__(16) unsigned char smem_base[];
   float *cst = (float *)smem_base;
@@ -424,7 +437,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   // beyond K re-read the row's last one
   const int nk = EPI == EPI_F32 ? (p.K + BK - 1) / BK : p.K / BK, ng = nk * (BK / 64);
   const unsigned kback = EPI == EPI_F32 ? (unsigned)max((nk - 1) * BK + ac * 16 + 16 - p.K, 0) : 0u;
-  v4i ra[PA];
+  v4i ra[AHEAD][PA];                              // slab kt in set kt % AHEAD
   auto load_a = [&](v4i &r, int kt, int i) {      // slabs past the end re-read the last one (never used)
     // (kback of the last slab may exceed aoff of row 0: the sum of base and offset is what counts, so the base gives it up front)
     if constexpr (EPI == EPI_F32) {
@@ -436,6 +449,42 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   };
   auto write_a = [&](const v4i &r, int buf, int i) { *(v4i *)(smem + buf * SLAB + lpos + i * 32 * BK) = r; };
 
+  if (EPI != EPI_GELU_Q && !W4 && n0 + wn0 >= p.N) {
+    // A wavefront whose columns all lie beyond N (half of a last tile when N = 1152) only moves its share of the activations: at
+    // the power limit the products it leaves out are time for the others (measured with M = 8192 and more: 0.3 - 0.7 % of a
+    // whole run; with packed weights, which fewer bytes and more vector work bound, it lost 1 %).  It has registers and loads of its
+    // own from the start: where it shared them with the loop below, the compiler copied registers that loads were on their way to.
+    v4i sa[2][PA];                                // slab kt in set kt % 2
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < PA; ++i) load_a(sa[u][i], u, i);
+    auto move = [&](int kt, int u) {              // slab kt (set u = kt % 2) to LDS, slab kt + 2 requested
+      if constexpr (PA == 4) QC_WAIT_VM_FOR4(4, sa[u][0], sa[u][1], sa[u][2], sa[u][3]);
+      else QC_WAIT_VM_FOR2(2, sa[u][0], sa[u][1]);
+#pragma unroll
+      for (int i = 0; i < PA; ++i) write_a(sa[u][i], u, i);
+      QC_SB;
+#pragma unroll
+      for (int i = 0; i < PA; ++i) load_a(sa[u][i], kt + 2, i);
+      QC_LDS_DONE_BARRIER;
+    };
+    // the barriers of the other wavefronts: one behind slab 0, one per slab of the loop (behind slab kt + 1), one at its end
+    int kt = 0;
+    for (; kt + 2 <= nk + 1; kt += 2) {
+      move(kt, 0);
+      move(kt + 1, 1);
+    }
+    if (kt < nk + 1) move(kt, 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < PA; ++i) asm volatile("" : "+v"(sa[u][i]));
+    __syncthreads();
+    return;
+  }
+
   // weight fragments of this wavefront: column block j (16 columns) is half j % 2 of the stored n-block (n0 + wn0) / 32 + j / 2
   // (blocks past N re-read the last one), group g (64 k) the two stored fragments 2 g and 2 g + 1 of it: lane l takes chunk l / 16 of
   // the 64 k, row l % 16 of the half
@@ -446,7 +495,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
 #pragma unroll
   for (int j = 0; j < TN / 2; ++j) sb[j] = (const int8_t *)p.Wt + (size_t)min((n0 + wn0) / 32 + j, nblocks - 1) * (2 * ng) * FRAG;
   const unsigned woff = (lane >> 5) * FRAG + ((lane >> 4) & 1) * (FRAG / 2) + (lane & 15) * (FRAG / 64);
-  wfrag_t bq[2][TN];
+  wfrag_t bq[2 * AHEAD][TN];                      // group g (64 k, of all of K) in set g % (2 AHEAD)
   auto load_w = [&](int g, int kg, int j) {       // groups past the end re-read the last one (never used)
     const int8_t *src = sb[j >> 1] + (size_t)min(kg, ng - 1) * (2 * FRAG);
     if constexpr (W4) {
@@ -466,17 +515,21 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
     fa[f][i] = *(const v4i *)(smem + buf * SLAB + fbase[g] + (half * 4 + i) * 16 * BK);
   };
 
-  // prologue: slab 0 -> LDS (through registers of the fragments), slab 1 -> registers, the weights of slab 0
+  // prologue: slab 0 -> LDS (through registers of the fragments), slabs 1 .. AHEAD -> registers, the weights of slabs 0 .. AHEAD - 1
 #pragma unroll
   for (int i = 0; i < PA; ++i) load_a(fa[1][i], 0, i);
 #pragma unroll
-  for (int i = 0; i < PA; ++i) load_a(ra[i], 1, i);
+  for (int u = 0; u < AHEAD; ++u) {
 #pragma unroll
-  for (int g = 0; g < 2; ++g)
+    for (int i = 0; i < PA; ++i) load_a(ra[(u + 1) % AHEAD][i], u + 1, i);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) load_w(g, g, j);
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) load_w(2 * u + g, 2 * u + g, j);
+  }
   QC_SB;
-  QC_WAIT_VM_FOR4(12, fa[1][0], fa[1][1], fa[1][2], fa[1][3]);
+  if constexpr (TM == 8) QC_WAIT_VM_FOR4(12, fa[1][0], fa[1][1], fa[1][2], fa[1][3]);
+  else QC_WAIT_VM_FOR2(20, fa[1][0], fa[1][1]);
   asm volatile("" : "+v"(c_sc), "+v"(c_bs));                  // (valid with the same wait)
   if constexpr (EPI == EPI_RESID) asm volatile("" : "+v"(c_g0));
   if constexpr (EPI == EPI_RESID && RAG) asm volatile("" : "+v"(c_g1));
@@ -490,7 +543,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
     asm volatile("" : "+v"(ws[0]), "+v"(ws[1]), "+v"(ws[2]), "+v"(ws[3]));
   }
   // the accumulators start at minus the zero-point term a_z * wsum[n] of their column, so the epilogue finds acc - a_z * wsum[n] ready
-  BigAcc acc;
+  BigAcc<TM> acc;
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     v4i c0;
@@ -522,121 +575,181 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   // Loads issued after the one a wait is for:
   //   step 0, for the weights of group 0 (step 1 of slab kt - 1) and, older, the activations: the weights of group 1    = 4
   //   step 2, for the weights of group 1 (step 3 of slab kt - 1): the activations and weights of steps 0 and 1          = 8
-  v4i wf[TN];
-  auto step = [&](int kt, int s, int buf) {
-    const int g = s >> 1, half = s & 1, f = s & 1;
-    if constexpr (W4) {
-      if (half == 0) {
+  if constexpr (TM == 8) {
+    v4i wf[TN];
+    auto step = [&](int kt, int s, int buf) {
+      const int g = s >> 1, half = s & 1, f = s & 1;
+      if constexpr (W4) {
+        if (half == 0) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) wf[j] = unpack_w4(bq[g][j]);
+          for (int j = 0; j < TN; ++j) wf[j] = unpack_w4(bq[g][j]);
+        }
       }
-    }
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      v4i w;
-      if constexpr (W4) w = wf[j];
-      else w = bq[g][j];
+      for (int j = 0; j < TN; ++j) {
+        v4i w;
+        if constexpr (W4) w = wf[j];
+        else w = bq[g][j];
 #pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int i = (j & 1) ? 3 - ii : ii, k = j * 4 + ii;
-        QC_SB;
-        acc[half * 4 + i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, fa[f][i], acc[half * 4 + i][j], 0, 0, 0);
-        if (k < 4) read_frag(f ^ 1, s == 3 ? buf ^ 1 : buf, ((s + 1) >> 1) & 1, (s + 1) & 1, k);
-        if (s == 0 && k >= 4 && k < 8) write_a(ra[k - 4], buf ^ 1, k - 4);
-        if (s == 0 && k >= 12) load_a(ra[k - 12], kt + 2, k - 12);
+        for (int ii = 0; ii < 4; ++ii) {
+          const int i = (j & 1) ? 3 - ii : ii, k = j * 4 + ii;
+          QC_SB;
+          acc[half * 4 + i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, fa[f][i], acc[half * 4 + i][j], 0, 0, 0);
+          if (k < 4) read_frag(f ^ 1, s == 3 ? buf ^ 1 : buf, ((s + 1) >> 1) & 1, (s + 1) & 1, k);
+          if (s == 0 && k >= 4 && k < 8) write_a(ra[0][k - 4], buf ^ 1, k - 4);
+          if (s == 0 && k >= 12) load_a(ra[0][k - 12], kt + 2, k - 12);
+        }
+        if (half == 1) load_w(g, 2 * kt + g + 2, j);
       }
-      if (half == 1) load_w(g, 2 * kt + g + 2, j);
+      QC_SB;
+    };
+    auto slab = [&](int kt, int buf) {
+      QC_WAIT_VM_FOR4(4, ra[0][0], ra[0][1], ra[0][2], ra[0][3]);
+      QC_WAIT_VM_FOR4(4, bq[0][0], bq[0][1], bq[0][2], bq[0][3]);
+      step(kt, 0, buf);
+      step(kt, 1, buf);
+      QC_WAIT_VM_FOR4(8, bq[1][0], bq[1][1], bq[1][2], bq[1][3]);
+      step(kt, 2, buf);
+      QC_LDS_DONE_BARRIER;
+      step(kt, 3, buf);
+    };
+    int kt = 0;
+    for (; kt + 2 <= nk; kt += 2) {
+      slab(kt, 0);
+      slab(kt + 1, 1);
     }
-    QC_SB;
-  };
-  auto slab = [&](int kt, int buf) {
-    QC_WAIT_VM_FOR4(4, ra[0], ra[1], ra[2], ra[3]);
-    QC_WAIT_VM_FOR4(4, bq[0][0], bq[0][1], bq[0][2], bq[0][3]);
-    step(kt, 0, buf);
-    step(kt, 1, buf);
-    QC_WAIT_VM_FOR4(8, bq[1][0], bq[1][1], bq[1][2], bq[1][3]);
-    step(kt, 2, buf);
-    QC_LDS_DONE_BARRIER;
-    step(kt, 3, buf);
-  };
-  if (EPI != EPI_GELU_Q && !W4 && n0 + wn0 >= p.N) {
-    // a wavefront whose columns all lie beyond N (half of a last tile when N = 1152) only moves its share of the activations: at
-    // the power limit the products it leaves out are time for the others (measured with M = 8192 and more: 0.3 - 0.7 % of a
-    // whole run; with packed weights, which fewer bytes and more vector work bound, it lost 1 %)
+    if (kt < nk) slab(kt, 0);
+    // the loads that ran past the end (clamped addresses) must have landed before registers are reused (the waits name their
+    // registers: a load whose result nobody uses would share its register with something live), and every wavefront must be past
+    // its last fragment read before the epilogue reuses LDS
+    QC_WAIT_VM_FOR4(0, ra[0][0], ra[0][1], ra[0][2], ra[0][3]);
 #pragma unroll
     for (int g = 0; g < 2; ++g) QC_WAIT_VM_FOR4(0, bq[g][0], bq[g][1], bq[g][2], bq[g][3]);
-    for (int kt = 0; kt < nk; ++kt) {
-      QC_WAIT_VM_FOR4(0, ra[0], ra[1], ra[2], ra[3]);
+  } else {
+    // 64 rows: slab kt = two groups of 64 k, one step each (16 products).  A slab takes half as long, so its operands are requested
+    // two slabs ahead: on entry slab kt is in LDS buffer kt % 2 and published; fa[0] holds (or awaits) the fragments of its group 0;
+    // the weights of slabs kt, kt + 1 and the activations of slabs kt + 1, kt + 2 are requested.
+    //   step 0: activation slab kt + 1 registers -> LDS, slab kt + 3 requested into the same registers (2 loads, in front of the
+    //           weights of the last column block)
+    //   both steps: the group's weights are free column block by column block, those of slab kt + 2 are requested (4 loads)
+    //   the barrier before step 1 publishes slab kt + 1, whose buffer was last read in step 0 of slab kt - 1
+    // Loads issued after the one a wait is for:
+    //   step 0, for the weights of group 0 (step 0 of slab kt - 2) and, older, the activations: step 1 of slab kt - 2 (4), slab kt - 1 (10) = 14
+    //   step 1, for the weights of group 1 (step 1 of slab kt - 2): slab kt - 1 (10), step 0 of this slab (6)                            = 16
+    auto step = [&](int kt, int g, int u) {       // u = kt % 2
+      constexpr bool w4 = W4;
+      v4i wf[TN];
+      if constexpr (w4) {
 #pragma unroll
-      for (int i = 0; i < PA; ++i) write_a(ra[i], (kt & 1) ^ 1, i);
+        for (int j = 0; j < TN; ++j) wf[j] = unpack_w4(bq[2 * u + g][j]);
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        v4i w;
+        if constexpr (w4) w = wf[j];
+        else w = bq[2 * u + g][j];
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii) {
+          const int i = (j & 1) ? 3 - ii : ii, k = j * 4 + ii;
+          QC_SB;
+          acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, fa[g][i], acc[i][j], 0, 0, 0);
+          if (k < 4) read_frag(g ^ 1, g == 1 ? u ^ 1 : u, g ^ 1, 0, k);
+          if (g == 0 && k >= 4 && k < 6) write_a(ra[u ^ 1][k - 4], u ^ 1, k - 4);
+          if (g == 0 && k >= 12 && k < 14) load_a(ra[u ^ 1][k - 12], kt + 3, k - 12);
+        }
+        load_w(2 * u + g, 2 * (kt + 2) + g, j);
+      }
       QC_SB;
-#pragma unroll
-      for (int i = 0; i < PA; ++i) load_a(ra[i], kt + 2, i);
+    };
+    auto slab = [&](int kt, int u) {
+      QC_WAIT_VM_FOR2(14, ra[u ^ 1][0], ra[u ^ 1][1]);
+      QC_WAIT_VM_FOR4(14, bq[2 * u][0], bq[2 * u][1], bq[2 * u][2], bq[2 * u][3]);
+      step(kt, 0, u);
       QC_LDS_DONE_BARRIER;
-    }
-    QC_WAIT_VM_FOR4(0, ra[0], ra[1], ra[2], ra[3]);
-    __syncthreads();
-    return;
-  }
-  int kt = 0;
-  for (; kt + 2 <= nk; kt += 2) {
-    slab(kt, 0);
-    slab(kt + 1, 1);
-  }
-  if (kt < nk) slab(kt, 0);
-  // the loads that ran past the end (clamped addresses) must have landed before registers are reused (the waits name their
-  // registers: a load whose result nobody uses would share its register with something live), and every wavefront must be past
-  // its last fragment read before the epilogue reuses LDS
-  QC_WAIT_VM_FOR4(0, ra[0], ra[1], ra[2], ra[3]);
+      QC_WAIT_VM_FOR4(16, bq[2 * u + 1][0], bq[2 * u + 1][1], bq[2 * u + 1][2], bq[2 * u + 1][3]);
+      step(kt, 1, u);
+    };
+    auto drain = [&]() {
 #pragma unroll
-  for (int g = 0; g < 2; ++g) QC_WAIT_VM_FOR4(0, bq[g][0], bq[g][1], bq[g][2], bq[g][3]);
+      for (int u = 0; u < AHEAD; ++u) {
+        QC_WAIT_VM_FOR2(0, ra[u][0], ra[u][1]);
+        QC_WAIT_VM_FOR4(0, bq[2 * u][0], bq[2 * u][1], bq[2 * u][2], bq[2 * u][3]);
+        QC_WAIT_VM_FOR4(0, bq[2 * u + 1][0], bq[2 * u + 1][1], bq[2 * u + 1][2], bq[2 * u + 1][3]);
+      }
+    };
+    int kt = 0;
+    for (; kt + 2 <= nk; kt += 2) {
+      slab(kt, 0);
+      slab(kt + 1, 1);
+    }
+    if (kt < nk) slab(kt, 0);
+    drain();
+  }
   QC_SB;
   __syncthreads();
-  if constexpr (EPI == EPI_GELU_Q) big_gelu(p, acc, smem, cst, m0, n0, a_s);
-  else if constexpr (EPI == EPI_QKV) big_qkv<RAG>(p, acc, smem, cst, m0, n0, a_s);
-  else if constexpr (EPI == EPI_F32) big_f32(p, acc, smem, cst, m0, n0, a_s);
-  else big_resid<RBF, RAG>(p, acc, smem, cst, m0, n0, a_s);
+  if constexpr (EPI == EPI_GELU_Q) big_gelu<TM>(p, acc, smem, cst, m0, n0, a_s);
+  else if constexpr (EPI == EPI_QKV) big_qkv<TM, RAG>(p, acc, smem, cst, m0, n0, a_s);
+  else if constexpr (EPI == EPI_F32) big_f32<TM>(p, acc, smem, cst, m0, n0, a_s);
+  else big_resid<TM, RBF, RAG>(p, acc, smem, cst, m0, n0, a_s);
 }
 
-template <int EPI, int TAG, bool W4, bool RBF, bool RAG = false>
+template <int TM, int EPI, int TAG, bool W4, bool RBF, bool RAG = false>
 static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
+  constexpr int BM = 16 * TM;
   // launches whose tiles are not all whole and inside one batch element take the variant that handles the others
   if constexpr (!RAG && (EPI == EPI_RESID || EPI == EPI_QKV)) {
-    if (a.M % BIG_BM || a.rows_per_batch % BIG_BM) return launch_big_as<EPI, TAG, W4, RBF, true>(a, st);
+    if (a.M % BM || a.rows_per_batch % BM) return launch_big_as<TM, EPI, TAG, W4, RBF, true>(a, st);
   }
-  constexpr int smem_epi = EPI == EPI_GELU_Q ? BIG_SMEM_GELU : (EPI == EPI_QKV ? BIG_SMEM_QKV : BIG_SMEM_RESID);
-  constexpr int smem = BIG_CST * 4 + (smem_epi > BIG_SMEM_LOOP ? smem_epi : BIG_SMEM_LOOP);
+  constexpr int smem_epi = EPI == EPI_GELU_Q ? big_smem_gelu<TM> : (EPI == EPI_QKV ? BIG_SMEM_QKV : BIG_SMEM_RESID);
+  constexpr int smem = BIG_CST * 4 + (smem_epi > big_smem_loop<TM> ? smem_epi : big_smem_loop<TM>);
   static_assert(2 * smem <= 160 * 1024, "two workgroups per compute unit");
-  auto kern = gemm_i8_big_kernel<EPI, TAG, W4, RBF, RAG>;
+  auto kern = gemm_i8_big_kernel<TM, EPI, TAG, W4, RBF, RAG>;
   static std::atomic<unsigned long long> lds{0};
   if (const hipError_t e = allow_lds((const void *)kern, smem, lds)) return e;
-  const int tiles_n = (a.N + BIG_BN - 1) / BIG_BN, tiles = ((a.M + BIG_BM - 1) / BIG_BM) * tiles_n;
+  const int tiles_n = (a.N + BIG_BN - 1) / BIG_BN, tiles = ((a.M + BM - 1) / BM) * tiles_n;
   GemmArgs b = a;
   // tile rows per group: every column tile of a group resident on its XCD at once (64 workgroup slots), at most 4
-  // rows (measured on M = 32768: 4 rows beat 16 by 2 - 9 % on the four linears of DiT-XL/2, 1 - 2 rows lose again)
-  b.group_m = std::min(std::max(64 / tiles_n, 1), 4);
+  // rows of 128 (measured on M = 32768: 4 rows beat 16 by 2 - 9 % on the four linears of DiT-XL/2, 1 - 2 rows lose again)
+  b.group_m = std::min(std::max(64 / tiles_n, 1), 32 / TM);
   hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), smem, st, b);
   return hipGetLastError();
 }
 
+// Rows of a tile for this launch; 0: the launch has too few tiles, the other kernels take it.  Measured alone on the chip
+// (us; other kernels | 64 rows | 128 rows), by the number of 64-row tiles, at K = 1152 unless said otherwise:
+//    48 - 80 tiles    11.6 | 12.9 | 17.0 (N = 1152, M = 1024), 10.4 | 11.2 | 15.1 (N = 3456, M = 256), K = 4608: 20.4 | 24.2 | 38.8
+//   112 - 144 tiles   13.2 | 11.6 | 15.2 (N = 3456, M = 512), 14.2 | 13.3 | 17.3 (N = 1152, M = 1536), K = 4608: 27.1 | 24.0 | 39.7
+//   160 - 252 tiles   18.4 | 12.6 | 15.5 (N = 3456, M = 1024), 24.6 | 14.5 | 18.4 (N = 4608, M = 850), K = 4608: 30.8 | 25.1 | 39.8
+//   288 tiles         21.1 | 17.9 | 18.8 (N = 4608, M = 1024)
+//   320 - 384 tiles   16.9 | 16.4 (64 | 128 rows; N = 3456, M = 1536), 21.8 | 20.0 (N = 1152, M = 4096), K = 4608: 42.2 | 43.0
+//   from 576 tiles    the 128-row tile reads each weight for twice the rows and is 0 - 25 % faster
+// One 64-row tile on each of the 256 compute units is what such a launch can use; two on a unit take as long as one of
+// 128 rows.  The 4-bit codes lie the same way (288 tiles 22.7 | 20.1 | 20.7, 80 tiles 12.9 | 14.7 | 20.4).
+// Refresh and cached steps of an eight-block network of width 1152, before and after: 6 latents of 256 tokens 2804 -> 2607 us,
+// 8: 3116 -> 3061, 16: 4749 -> 4620, 5 of 425 tokens 4453 -> 3854; 1 and 24 latents unchanged.  (From 60 tiles on: 6 latents 2910.)
+static int big_rows(const GemmArgs &a) {
+  const long long tiles_n = (a.N + BIG_BN - 1) / BIG_BN;
+  const long long t64 = (a.M + 63) / 64 * tiles_n, t128 = (a.M + 127) / 128 * tiles_n;
+  if (t64 >= 100 && t64 < 300) return 64;
+  return t128 >= 150 ? 128 : 0;
+}
+
 // The large-M kernel takes over when the weights exist in fragment order, the shape fits its loop (K a multiple of
-// 128, N of 32, 16-byte aligned rows), a 128-row tile holds rows of at most two batch elements (its epilogues are
-// compiled without the general paths) and the launch has enough 128 x 256 tiles for it to pay.
+// 128, N of 32, 16-byte aligned rows), a tile holds rows of at most two batch elements (its epilogues are compiled
+// without the general paths) and the launch has enough tiles for it to pay.
 bool gemm_big_pays(const GemmArgs &a, int epi, int nz) {
   if (epi == EPI_F32 || !a.Wt || nz != 1 || a.sel_D || a.acc_out) return false;
   if (a.K % 128 || a.N % 32 || a.lda % 16) return false;
-  if (epi == EPI_RESID && a.rows_per_batch < 128) return false;
-  if (epi == EPI_QKV && (a.y || a.rows_per_batch < 128 || (a.N / 3) % 128 || a.hd % 4 || a.Tp % 8)) return false;
-  const long long tiles = (long long)((a.M + 127) / 128) * ((a.N + 255) / 256);
-  // measured alone on the chip (DiT-XL/2 shapes): 160 tiles (proj / fc2 at M = 4096) run 20 % faster here than in the
-  // tile kernel, 224 - 288 tiles (QKV / fc1 at M = 2048) 0 - 10 % faster, 112 - 144 tiles (M = 1024) 3 - 15 % slower,
-  // 80 tiles (proj / fc2 at M = 2048) 15 - 25 % slower
-  return tiles >= 150;
+  const int rows = big_rows(a);
+  if (epi == EPI_RESID && a.rows_per_batch < rows) return false;
+  if (epi == EPI_QKV && (a.y || a.rows_per_batch < rows || (a.N / 3) % 128 || a.hd % 4 || a.Tp % 8)) return false;
+  return rows > 0;
 }
 
 template <int EPI, int TAG, bool RBF>
 static hipError_t launch_big_w(const GemmArgs &a, hipStream_t st) {
-  return a.w4 ? launch_big_as<EPI, TAG, true, RBF>(a, st) : launch_big_as<EPI, TAG, false, RBF>(a, st);
+  if (big_rows(a) == 64) return a.w4 ? launch_big_as<4, EPI, TAG, true, RBF>(a, st) : launch_big_as<4, EPI, TAG, false, RBF>(a, st);
+  return a.w4 ? launch_big_as<8, EPI, TAG, true, RBF>(a, st) : launch_big_as<8, EPI, TAG, false, RBF>(a, st);
 }
 
 // `site` only names the instantiation (so that profiles tell the linears apart); the residual epilogue is compiled twice,
@@ -657,13 +770,13 @@ hipError_t launch_gemm_big(const GemmArgs &a, int epi, hipStream_t st, int site)
 static int big_copy_rows(const GemmArgs &a) {     // rows of the result that hold the copy, plus those that make the rest whole tiles
   const size_t bytes = (size_t)((a.N + 31) / 32 * 32) * ((a.K + BIG_BK - 1) / BIG_BK * BIG_BK) / (a.w4 ? 2 : 1) + 16;      // + alignment
   const size_t row = (size_t)a.N * sizeof(float), n = (bytes + row - 1) / row;
-  return (size_t)a.M > n ? (int)(n + (a.M - n) % BIG_BM) : a.M;
+  return (size_t)a.M > n ? (int)(n + (a.M - n) % 128) : a.M;
 }
 
 bool gemm_big_rows_pays(const GemmArgs &a) {
   if (a.acc_out) return false;
   const double work = (double)a.M * a.N * a.K;
-  const double padded = (double)((a.M + BIG_BM - 1) / BIG_BM * BIG_BM) * ((a.N + BIG_BN - 1) / BIG_BN * BIG_BN) * ((a.K + BIG_BK - 1) / BIG_BK * BIG_BK);
+  const double padded = (double)((a.M + 127) / 128 * 128) * ((a.N + BIG_BN - 1) / BIG_BN * BIG_BN) * ((a.K + BIG_BK - 1) / BIG_BK * BIG_BK);
   // measured (us, tile kernel / copy, this kernel and the last rows): 16384 x 4608 x 1152 175 / 125, 32768 x 1152 x 4608 235 / 172,
   // 8192 x 3456 x 1152 68 / 62, 16384 x 1152 x 1152 49 / 43, 16384 x 1000 x 1168 46 / 42.  Below 1.5e10 products the two more
   // launches are not earned back (8192 x 2049 x 528 39 / 49), nor where the last rows are more than a sixteenth (8192 x 1152 x
@@ -683,10 +796,11 @@ hipError_t launch_gemm_big_rows(const GemmArgs &a, hipStream_t st) {
   c.A = a.A + (size_t)m1 * a.lda;
   c.y = y1;
   hipError_t e = launch_tile_weight(a.W, wt, a.N, a.K, a.w4 ? 4 : 8, Kp, st);
-  if (e == hipSuccess) e = a.w4 ? launch_big_as<EPI_F32, QC_SITE_QKV, true, false>(b, st) : launch_big_as<EPI_F32, QC_SITE_QKV, false, false>(b, st);
+  if (e == hipSuccess) e = a.w4 ? launch_big_as<8, EPI_F32, QC_SITE_QKV, true, false>(b, st) : launch_big_as<8, EPI_F32, QC_SITE_QKV, false, false>(b, st);
   return e == hipSuccess ? launch_gemm(c, EPI_F32, 1, st, QC_SITE_QKV) : e;
 }
 
+#undef QC_WAIT_VM_FOR2
 #undef QC_WAIT_VM_FOR4
 #undef QC_LDS_DONE_BARRIER
 #undef QC_SB

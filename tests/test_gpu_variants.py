@@ -57,6 +57,13 @@ def _net(hidden, heads, mlp, h, w, patch=2):
     # whole), 252 tokens (units of four are), the last tile has 2 or 48 rows
     ("large-M, 425 tokens", _net(1152, 16, 4608, 50, 34), 10, 8),
     ("large-M, 252 tokens, 4-bit", _net(1152, 16, 4608, 36, 28), 20, 4),
+    # 100 - 300 tiles of 64 x 256: 100 and 77 tokens (tiles that span batch elements, with and without whole units of four tokens; the
+    # last tile has 52 and 31 rows), 64 tokens (one batch element a tile), residuals of 425 tokens (the last tile has 13 rows)
+    ("64-row tiles, 100 tokens", _net(384, 6, 1536, 20, 20), 21, 8),
+    ("64-row tiles, 77 tokens, 4-bit", _net(384, 6, 1536, 14, 22), 27, 4),
+    ("64-row tiles, 64 tokens", _net(384, 6, 1536, 16, 16), 40, 8),
+    ("64-row tiles, residuals, 425 tokens", _net(1152, 16, 4608, 50, 34), 5, 8),
+    ("64-row tiles, residuals, 256 tokens, 4-bit", _net(1152, 16, 4608, 32, 32), 9, 4),
     ("split-K: 64 x 96 tiles", _net(1152, 16, 4608, 32, 32), 4, 8),
 ])
 def test_quantisers_of_small_and_ragged_launches(name, model, B, wb):
@@ -128,6 +135,32 @@ def test_large_m_ragged_denoiser(cache, stream):
             for k, (full, t) in enumerate(((True, 500), (False, 480))):
                 want = dit.denoiser(lat[b % n][None].astype(np.float64), np.array([t]), yb, m, w, lin, cache_or, full, cache_bf16=cache == "bf16")
                 assert_close(got[k][b], want[0], "batch element %d, call %d" % (b, k))
+
+
+@pytest.mark.parametrize("cache,stream", [("fp32", "bf16"), ("bf16", "fp32"), ("bf16", "bf16")])
+@pytest.mark.parametrize("hw,B", [((50, 34), 5), ((32, 32), 8)])
+def test_64_row_tiles_equal_the_small_launches(hw, B, cache, stream):
+    """Residual linears on 64-row tiles (a batch) against the small tiles of each latent alone, bit for bit, in every storage format."""
+    import torch
+    import paper_2503_02508_amd as qc
+    from qc_testlib import make_pair, oracle_calibration
+    m = _net(1152, 16, 4608, *hw)
+    w = I.make_weights(m, 21)
+    lat, lab = I.make_latents(B, m, 22), I.make_labels(B, m, 23)
+    qp, _, _ = oracle_calibration(m, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    _, ctx = make_pair(m, w, qp, B, 2)
+    ctx.set_cache_format(cache)
+    ctx.set_stream_format(stream)
+    xd, ld = _cuda(lat), _cuda(lab)
+    got = [torch.empty(lat.shape, device="cuda") for _ in range(2)]
+    for eps, mode, t in zip(got, (qc.QC_FULL, qc.QC_CACHED), (500, 480)):
+        ctx.denoise(xd, t, ld, B, mode, eps)
+    for b in range(B):
+        one = torch.empty_like(xd[:1])
+        for eps, mode, t in zip(got, (qc.QC_FULL, qc.QC_CACHED), (500, 480)):
+            ctx.denoise(xd[b:b + 1], t, ld[b:b + 1], 1, mode, one)
+            assert torch.equal(one, eps[b:b + 1]), (b, mode)
+    ctx.close()
 
 
 @pytest.mark.parametrize("model,B", [
