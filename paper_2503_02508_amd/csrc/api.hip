@@ -14,7 +14,7 @@
 
 namespace qc {
 
-constexpr int MAX_LANES = 4;
+constexpr int MAX_LANES = 2;
 // rows of the conditioning tables: the conditioning of several sampler steps is prepared in one go
 constexpr int WINDOW_ROWS = 512;
 // token rows of one group of the un-quantised forward
@@ -109,8 +109,8 @@ struct qc_ctx {
   int *cal_slots, *cal_label;
   bool weights_loaded;
   // a denoiser call may run its batch as up to MAX_LANES independent sub-batches on internal streams
-  hipStream_t lane_stream[4] = {nullptr, nullptr, nullptr, nullptr};
-  hipEvent_t ev_fork = nullptr, ev_join[4] = {nullptr, nullptr, nullptr, nullptr};
+  hipStream_t lane_stream[MAX_LANES] = {};
+  hipEvent_t ev_fork = nullptr, ev_join[MAX_LANES] = {};
   // optional per-kernel-class timing with HIP events (qc_profile_begin / qc_profile_end)
   bool prof_on = false;
   std::vector<hipEvent_t> prof_pool;
@@ -763,16 +763,15 @@ static int denoise_tail(qc_ctx *ctx, const Sub &sb, int mode, float *eps_out, hi
   return QC_OK;
 }
 
-// Small batches leave most of the chip idle inside every kernel (a launch has fewer workgroups than
-// compute units, and every dependent kernel pays a few microseconds of dispatch latency), and latents
-// are independent, so the batch may be cut into sub-batches that run the network concurrently: the first
-// on the caller's stream, the others on internal streams, their launches interleaved block by block.
-static int choose_lanes(qc_ctx *ctx, int B) {
-  int n = (long long)B * ctx->T <= 4096 ? 2 : 1;
-  if (n > MAX_LANES) n = MAX_LANES;
-  if (n > B) n = B;
-  return n < 1 ? 1 : n;
-}
+// Latents are independent, so a batch is cut into two halves that run the network concurrently: the first on the caller's
+// stream, the other on an internal stream, their launches interleaved block by block.  Small batches leave most of the chip idle
+// inside every kernel (a launch has fewer workgroups than compute units, and every dependent kernel pays a few microseconds
+// of dispatch latency).  Large ones gain too: the last, partly empty round of tiles of one half, its memory-bound kernels and the
+// dispatch of its next kernel run beside the other half's.  A network of eight blocks of width 1152, two of six steps
+// refreshed, one part -> two (us): 20 x 256 tokens 5600 -> 5150, 32: 7920 -> 7220, 64: 13680 -> 13330, 128: 26140 -> 25990; 8 x 1024
+// tokens 10440 -> 9530, 16: 18510 -> 18140; 10 x 425 tokens 5980 -> 5300; width 384, 128 x 256 tokens 7210 -> 6690.  Three parts
+// are 1 - 5 % slower than two up to 16384 rows and within 2 % of them beyond; four are slower throughout.
+static int choose_lanes(int B) { return B < MAX_LANES ? B : MAX_LANES; }
 
 // One denoiser evaluation whose conditioning sits in slot `w` of the prepared window.  sched (optional,
 // [L][2], 1 = recompute) decides per (block, module) instead of `mode`.
@@ -789,7 +788,7 @@ static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mo
     else if (n_full == 0) mode = QC_CACHED;
     else mixed = true;
   }
-  const int lanes = choose_lanes(ctx, B);
+  const int lanes = choose_lanes(B);
   Sub sub[MAX_LANES];
   hipStream_t ls[MAX_LANES];
   for (int i = 0, b0 = 0; i < lanes; ++i) {

@@ -163,6 +163,48 @@ def test_64_row_tiles_equal_the_small_launches(hw, B, cache, stream):
     ctx.close()
 
 
+@pytest.mark.parametrize("model,B", [(_net(1152, 16, 4608, 32, 32), 2 * 16 + 1),        # halves of 17 and 16 latents
+                                     (_net(384, 6, 1536, 64, 64), 5), (_net(384, 6, 1536, 50, 34), 41)])
+def test_halves_of_a_large_batch(model, B):
+    """More than 4096 rows in two concurrent halves: each latent as it comes out alone, eager and in a replayed graph."""
+    import torch
+    import paper_2503_02508_amd as qc
+    from qc_testlib import make_pair, oracle_calibration
+    m = replace(model, depth=2)
+    w = I.make_weights(m, 21)
+    lat, lab = I.make_latents(B, m, 22), I.make_labels(B, m, 23)
+    qp, _, _ = oracle_calibration(m, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    _, ctx = make_pair(m, w, qp, B, 2)
+    xd, ld = _cuda(lat), _cuda(lab)
+    calls = list(zip((qc.QC_FULL, qc.QC_CACHED), (500, 480)))
+
+    def run(x, l, outs):
+        for eps, (mode, t) in zip(outs, calls):
+            ctx.denoise(x, t, l, x.shape[0], mode, eps)
+
+    want = [torch.empty_like(xd) for _ in calls]
+    for b in range(B):
+        one = [torch.empty_like(xd[:1]) for _ in calls]
+        run(xd[b:b + 1], ld[b:b + 1], one)
+        for k in range(2):
+            want[k][b:b + 1] = one[k]
+    got = [torch.empty_like(xd) for _ in calls]
+    run(xd, ld, got)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run(xd, ld, got)
+    for _ in range(3):
+        for g in got:
+            g.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        run(xd, ld, got)
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    ctx.close()
+
+
 @pytest.mark.parametrize("model,B", [
     (_net(64, 2, 128, 10, 14), 1),              # 35 tokens: the last group of 16 tokens has 3
     (_net(400, 10, 800, 6, 10), 3),             # groups of 16 tokens span batch elements; features end inside a chunk
