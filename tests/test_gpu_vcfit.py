@@ -130,3 +130,29 @@ def test_vc_fit_along_a_trajectory(name, model, B, steps, interval, cfg):
     torch.cuda.synchronize()
     assert torch.equal(x2, xh)
     ctx.close()
+
+
+@pytest.mark.parametrize("model,B,steps,cfg", [(TINY, 3, 5, 1.5), (RAGGED, 2, 4, 0.0),
+                                               (TINY, 90, 7, 1.5)])       # windows of two steps, several groups of samples
+def test_networks_beside_each_other_or_in_turn(model, B, steps, cfg):
+    """The two networks of a fit on streams of their own against one after the other (which keeping Q | K | V asks for): the
+    same bits, which the quantised run gives again when it is handed the factors."""
+    import torch
+    _, _, ctx, _ = _setup(model, 41, B, steps, 2, cfg)
+    lat, lab = _cuda(I.make_latents(B, model, 42)), _cuda(I.make_labels(B, model, 43).astype(np.int32))
+
+    def fit():
+        xh, xr = lat.clone(), lat.clone()
+        K = torch.zeros((steps, model.latent_c), device="cuda")
+        ctx.vc_fit_sampler(xh, xr, lab, steps, cfg, 1e-2, K)
+        return xh, xr, K
+
+    ctx.keep_qkv_f32(True)
+    want = fit()
+    ctx.keep_qkv_f32(False)
+    for _ in range(4):
+        assert all(torch.equal(a, b) for a, b in zip(fit(), want))
+    xh = lat.clone()
+    ctx.sample(xh, lab, steps, cfg, want[2])
+    assert torch.equal(xh, want[0])
+    ctx.close()
