@@ -16,6 +16,13 @@
 // enumerates keys as 4g + r; the V^T operand is read with the same enumeration.
 // The running max / sum of a query are per-lane scalars, shared across the four
 // g groups with two shuffles.
+//
+// What bounds it: the float32 matrix rate of a wavefront that is alone on its SIMD (42 of 32 clocks a product) and, at a few
+// hundred tokens, the first round trips.  So nothing stands in front of the products: the next tile of keys comes into registers
+// while one is multiplied, the four blocks of keys alternate (a chain on one accumulator waits for itself), and the fragments
+// are read from LDS a step ahead.  Us (16 heads of 72): 1 x 256 tokens 26.5 -> 18.1, 4 x 256 29.2 -> 22.1, 2 x 425 45.2 -> 31.8, 1 x 1024
+// 98.6 -> 66.0, 1 x 4096 992 -> 874.  (Workgroups of 32 queries, twice as many: 1 x 256 21.2, 4 x 256 27.7, 1 x 4096 1200, against 20.1, 23.9
+// and 926 without the fragments read ahead.)
 #include "qc_internal.h"
 
 namespace qc {
@@ -53,35 +60,62 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
   for (int c = 0; c < NC; ++c) o[c] = (v4f){0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.0f;
 
-  for (int k0 = 0; k0 < T; k0 += 64) {
-    __syncthreads();
-    // stage K and V tiles (zero padded in features and keys)
-    for (int i = tid; i < 64 * (DP / 4); i += 256) {
-      const int r = i / (DP / 4), e = (i % (DP / 4)) * 4;
-      v4f kv = {0.f, 0.f, 0.f, 0.f}, vv = {0.f, 0.f, 0.f, 0.f};
+  // K and V tiles, zero padded in features and keys; the next tile's loads are in flight while a tile is multiplied
+  constexpr int NL = NC;             // 64 rows x 4 NC chunks, 256 threads
+  v4f kreg[NL], vreg[NL];
+  auto load_tile = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int i = tid + 256 * u, r = i / (DP / 4), e = (i % (DP / 4)) * 4;
+      kreg[u] = vreg[u] = (v4f){0.f, 0.f, 0.f, 0.f};
       if (k0 + r < T && e < hd) {
         const float *src = base + (size_t)(k0 + r) * 3 * D + e;
-        kv = *(const v4f *)(src + D);
-        vv = *(const v4f *)(src + 2 * D);
+        kreg[u] = *(const v4f *)(src + D);
+        vreg[u] = *(const v4f *)(src + 2 * D);
       }
-      *(v4f *)(Ks + r * S + e) = kv;
-      *(v4f *)(Vs + r * S + e) = vv;
+    }
+  };
+  load_tile(0);
+  for (int k0 = 0; k0 < T; k0 += 64) {
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int i = tid + 256 * u, r = i / (DP / 4), e = (i % (DP / 4)) * 4;
+      *(v4f *)(Ks + r * S + e) = kreg[u];
+      *(v4f *)(Vs + r * S + e) = vreg[u];
     }
     __syncthreads();
+    if (k0 + 64 < T) load_tile(k0 + 64);
 
-    // S^T tile: 4 blocks of 16 keys
+    // S^T tile: 4 blocks of 16 keys, whose chains of products alternate
     v4f s[4];
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt) {
-      v4f acc = {0.f, 0.f, 0.f, 0.f};
+    for (int kt = 0; kt < 4; ++kt) s[kt] = (v4f){0.f, 0.f, 0.f, 0.f};
+    v4f kf[2][4];
+    auto load_k = [&](int c) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const v4f kf = *(const v4f *)(Ks + (kt * 16 + ql) * S + 16 * c + 4 * g);
+      for (int kt = 0; kt < 4; ++kt) kf[c & 1][kt] = *(const v4f *)(Ks + (kt * 16 + ql) * S + 16 * c + 4 * g);
+    };
+    load_k(0);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u], qf[c][u], acc, 0, 0, 0);
-      }
-      s[kt] = acc;
+    for (int c = 0; c < NC; ++c) {
+      if (c + 1 < NC) load_k(c + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) s[kt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c & 1][kt][u], qf[c][u], s[kt], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    // the first V fragments are requested before the softmax arithmetic
+    float vf[2][4][NC];
+    auto load_v = [&](int kt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) vf[kt & 1][r][c] = Vs[(kt * 16 + 4 * g + r) * S + ql + 16 * c];
+    };
+    load_v(0);
     // mask keys past the end, running max
     float mx = -INFINITY;
 #pragma unroll
@@ -109,13 +143,15 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
       }
     // O^T += V^T P^T
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
+    for (int kt = 0; kt < 4; ++kt) {
+      if (kt < 3) load_v(kt + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float *vrow = Vs + (kt * 16 + 4 * g + r) * S + ql;
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int c = 0; c < NC; ++c) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vrow[16 * c], s[kt][r], o[c], 0, 0, 0);
-      }
+        for (int c = 0; c < NC; ++c) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[kt & 1][r][c], s[kt][r], o[c], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 
   l_run += __shfl_xor(l_run, 16, 64);
@@ -149,21 +185,24 @@ __global__ __launch_bounds__(256) void attention_kernel(const float *__restrict_
   }
 }
 
+template <int DP>
+static hipError_t launch_attention_dp(const float *qkv, int B, int T, int H, int hd, const QParam *qp, int8_t *q_out, float *f32_out, hipStream_t st) {
+  const float sl2 = 1.4426950408889634f / sqrtf((float)hd);
+  hipLaunchKernelGGL(attention_kernel<DP>, dim3((T + 63) / 64, B * H), dim3(256), 0, st, qkv, T, H, hd, qp, q_out, f32_out, sl2);
+  return hipGetLastError();
+}
+
 hipError_t launch_attention(const float *qkv, int B, int T, int H, int hd, const QParam *qp, int8_t *q_out, float *f32_out,
                             hipStream_t st) {
-  const float sl2 = 1.4426950408889634f / sqrtf((float)hd);
-  dim3 grid((T + 63) / 64, B * H);
-  const int dp = (hd + 15) / 16 * 16;
-  switch (dp) {
-    case 16: hipLaunchKernelGGL(attention_kernel<16>, grid, dim3(256), 0, st, qkv, T, H, hd, qp, q_out, f32_out, sl2); break;
-    case 32: hipLaunchKernelGGL(attention_kernel<32>, grid, dim3(256), 0, st, qkv, T, H, hd, qp, q_out, f32_out, sl2); break;
-    case 48: hipLaunchKernelGGL(attention_kernel<48>, grid, dim3(256), 0, st, qkv, T, H, hd, qp, q_out, f32_out, sl2); break;
-    case 64: hipLaunchKernelGGL(attention_kernel<64>, grid, dim3(256), 0, st, qkv, T, H, hd, qp, q_out, f32_out, sl2); break;
-    case 80: hipLaunchKernelGGL(attention_kernel<80>, grid, dim3(256), 0, st, qkv, T, H, hd, qp, q_out, f32_out, sl2); break;
-    case 96: hipLaunchKernelGGL(attention_kernel<96>, grid, dim3(256), 0, st, qkv, T, H, hd, qp, q_out, f32_out, sl2); break;
+  switch ((hd + 15) / 16) {
+    case 1: return launch_attention_dp<16>(qkv, B, T, H, hd, qp, q_out, f32_out, st);
+    case 2: return launch_attention_dp<32>(qkv, B, T, H, hd, qp, q_out, f32_out, st);
+    case 3: return launch_attention_dp<48>(qkv, B, T, H, hd, qp, q_out, f32_out, st);
+    case 4: return launch_attention_dp<64>(qkv, B, T, H, hd, qp, q_out, f32_out, st);
+    case 5: return launch_attention_dp<80>(qkv, B, T, H, hd, qp, q_out, f32_out, st);
+    case 6: return launch_attention_dp<96>(qkv, B, T, H, hd, qp, q_out, f32_out, st);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace qc
