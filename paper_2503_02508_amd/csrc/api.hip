@@ -15,6 +15,8 @@
 namespace qc {
 
 constexpr int MAX_LANES = 2;
+// internal streams of a device
+constexpr int NUM_SIDE = 3;
 // rows of the conditioning tables: the conditioning of several sampler steps is prepared in one go
 constexpr int WINDOW_ROWS = 512;
 // token rows of one group of the un-quantised forward
@@ -109,10 +111,11 @@ struct qc_ctx {
   int *cal_slots, *cal_label;
   bool weights_loaded;
   // a denoiser call may run its batch as up to MAX_LANES independent sub-batches on internal streams
-  hipStream_t lane_stream[MAX_LANES] = {};
+  int side_dev = -1;                              // device whose shared internal streams this context holds, see side_streams
+  hipStream_t own_side[NUM_SIDE] = {};            // internal streams of calls that are captured
   hipEvent_t ev_fork = nullptr, ev_join[MAX_LANES] = {};
-  // the factor fit runs its un-quantised network beside the quantised one, on a stream of its own
-  hipStream_t ref_stream = nullptr;
+  hipEvent_t ev_f32_fork = nullptr, ev_f32_join[2] = {};
+  // the factor fit runs its un-quantised network beside the quantised one
   hipEvent_t ev_ready = nullptr, ev_ref = nullptr, ev_fit = nullptr;
   // optional per-kernel-class timing with HIP events (qc_profile_begin / qc_profile_end)
   bool prof_on = false;
@@ -286,16 +289,69 @@ int qc_create(const qc_model_desc *desc, void *arena, size_t arena_bytes, int ma
   return QC_OK;
 }
 
+// Internal streams.  HIP puts the streams of a process on four hardware queues, each new one on the queue with the fewest users, and
+// a queue runs its work in order: two streams that share one run one after the other.  Streams of every context would
+// share sooner or later (with one for each, every fourth context ran the halves of its batches in turn: 8 latents through eight blocks
+// 4840 instead of 3180 us, 20 latents 7600 instead of 5400).  So the contexts of a device share three streams, made
+// one after the other when the first context needs one and given back with the last that does; and work that is to run beside
+// other work goes to these only, unless it is short, since the caller's stream may lie on any queue.  Each context orders its own work with
+// events; work of contexts that run at the same time queues up.  A call that is being captured takes streams of its context, so that
+// no other context's work can get into its graph.
+struct SidePool {
+  std::mutex m;
+  int users[64] = {};
+  hipStream_t s[64][NUM_SIDE] = {};
+};
+static SidePool side_pool;
+
+static void release_side(qc_ctx *ctx) {
+  if (ctx->side_dev < 0) return;
+  std::lock_guard<std::mutex> lock(side_pool.m);
+  if (--side_pool.users[ctx->side_dev] == 0)
+    for (hipStream_t &s : side_pool.s[ctx->side_dev]) {
+      (void)hipStreamDestroy(s);
+      s = nullptr;
+    }
+  ctx->side_dev = -1;
+}
+
+// The internal streams of a call on `st`, and the given events, made when they are first needed.
+static int side_streams(qc_ctx *ctx, hipStream_t st, hipStream_t (&side)[NUM_SIDE], std::initializer_list<hipEvent_t *> events) {
+  for (hipEvent_t *e : events)
+    if (!*e) QC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (st) QC_HIP(hipStreamIsCapturing(st, &cap));      // the null stream cannot be captured
+  if (cap != hipStreamCaptureStatusNone) {
+    for (int i = 0; i < NUM_SIDE; ++i) {
+      if (!ctx->own_side[i]) QC_HIP(hipStreamCreateWithFlags(&ctx->own_side[i], hipStreamNonBlocking));
+      side[i] = ctx->own_side[i];
+    }
+    return QC_OK;
+  }
+  if (ctx->side_dev < 0) {
+    int dev = 0;
+    QC_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64) QC_FAIL(QC_ERR_RANGE, "device %d", dev);
+    std::lock_guard<std::mutex> lock(side_pool.m);
+    if (side_pool.users[dev] == 0)
+      for (hipStream_t &s : side_pool.s[dev])
+        if (!s) QC_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));      // (those made stay if one fails)
+    ++side_pool.users[dev];
+    ctx->side_dev = dev;
+  }
+  for (int i = 0; i < NUM_SIDE; ++i) side[i] = side_pool.s[ctx->side_dev][i];
+  return QC_OK;
+}
+
 int qc_destroy(qc_ctx *ctx) {
   if (!ctx) QC_FAIL(QC_ERR_NULL, "ctx is NULL");
   for (hipEvent_t e : ctx->prof_pool) (void)hipEventDestroy(e);
-  for (int i = 0; i < MAX_LANES; ++i) {
-    if (ctx->lane_stream[i]) (void)hipStreamDestroy(ctx->lane_stream[i]);
-    if (ctx->ev_join[i]) (void)hipEventDestroy(ctx->ev_join[i]);
-  }
-  if (ctx->ref_stream) (void)hipStreamDestroy(ctx->ref_stream);
-  for (hipEvent_t e : {ctx->ev_fork, ctx->ev_ready, ctx->ev_ref, ctx->ev_fit})
+  for (hipEvent_t e : {ctx->ev_fork, ctx->ev_join[0], ctx->ev_join[1], ctx->ev_f32_fork, ctx->ev_f32_join[0], ctx->ev_f32_join[1],
+                       ctx->ev_ready, ctx->ev_ref, ctx->ev_fit})
     if (e) (void)hipEventDestroy(e);
+  for (hipStream_t s : ctx->own_side)
+    if (s) (void)hipStreamDestroy(s);
+  release_side(ctx);
   delete ctx;
   return QC_OK;
 }
@@ -768,8 +824,8 @@ static int denoise_tail(qc_ctx *ctx, const Sub &sb, int mode, float *eps_out, hi
   return QC_OK;
 }
 
-// Latents are independent, so a batch is cut into two halves that run the network concurrently: the first on the caller's
-// stream, the other on an internal stream, their launches interleaved block by block.  Small batches leave most of the chip idle
+// Latents are independent, so a batch is cut into two halves that run the network concurrently, on an internal stream
+// each (or on the caller's and one internal stream), their launches interleaved block by block.  Small batches leave most of the chip idle
 // inside every kernel (a launch has fewer workgroups than compute units, and every dependent kernel pays a few microseconds
 // of dispatch latency).  Large ones gain too: the last, partly empty round of tiles of one half, its memory-bound kernels and the
 // dispatch of its next kernel run beside the other half's.  A network of eight blocks of width 1152, two of six steps
@@ -781,7 +837,7 @@ static int choose_lanes(int B) { return B < MAX_LANES ? B : MAX_LANES; }
 // One denoiser evaluation whose conditioning sits in slot `w` of the prepared window.  sched (optional,
 // [L][2], 1 = recompute) decides per (block, module) instead of `mode`.
 static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mode, int w, float *eps_out, hipStream_t st,
-                        const unsigned char *sched = nullptr) {
+                        const unsigned char *sched = nullptr, int max_lanes = MAX_LANES) {
   bool mixed = false;
   if (sched) {
     int n_full = 0;
@@ -793,7 +849,7 @@ static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mo
     else if (n_full == 0) mode = QC_CACHED;
     else mixed = true;
   }
-  const int lanes = choose_lanes(B);
+  const int lanes = std::min(choose_lanes(B), max_lanes);
   Sub sub[MAX_LANES];
   hipStream_t ls[MAX_LANES];
   for (int i = 0, b0 = 0; i < lanes; ++i) {
@@ -801,17 +857,21 @@ static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mo
     b0 += sub[i].nb;
   }
   ls[0] = st;
+  int rc = QC_OK;
   if (lanes > 1) {
-    if (!ctx->ev_fork) QC_HIP(hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
+    static_assert(MAX_LANES == 2, "");
+    hipStream_t side[NUM_SIDE];
+    rc = side_streams(ctx, st, side, {&ctx->ev_fork, &ctx->ev_join[0], &ctx->ev_join[1]});
+    if (rc) return rc;
+    // Up to 4096 rows the first half stays on the caller's stream: another two events cost 25 - 35 us a step there (8 latents, eight
+    // blocks, 16 steps 8160 us, 8720 with both halves on internal streams; 20 latents, 6 steps 5320 and 5460).
+    const int first = (long long)B * ctx->T <= 4096 ? 1 : 0;
     QC_HIP(hipEventRecord(ctx->ev_fork, st));
-    for (int i = 1; i < lanes; ++i) {
-      if (!ctx->lane_stream[i]) QC_HIP(hipStreamCreateWithFlags(&ctx->lane_stream[i], hipStreamNonBlocking));
-      if (!ctx->ev_join[i]) QC_HIP(hipEventCreateWithFlags(&ctx->ev_join[i], hipEventDisableTiming));
-      ls[i] = ctx->lane_stream[i];
+    for (int i = first; i < lanes; ++i) {
+      ls[i] = side[i];
       QC_HIP(hipStreamWaitEvent(ls[i], ctx->ev_fork, 0));
     }
   }
-  int rc = QC_OK;
   for (int i = 0; i < lanes && !rc; ++i) rc = denoise_head(ctx, x, n_labels, sub[i], ls[i]);
   if (mode == QC_FULL || mixed)
     for (int l = 0; l < ctx->L && !rc; ++l)
@@ -820,7 +880,8 @@ static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mo
                             mixed ? sched[2 * l] != 0 : true, mixed ? sched[2 * l + 1] != 0 : true);
   for (int i = 0; i < lanes && !rc; ++i) rc = denoise_tail(ctx, sub[i], mixed ? QC_FULL : mode, eps_out, ls[i]);
   // join even after an error so that the internal streams never run past the caller's stream unobserved
-  for (int i = 1; i < lanes; ++i) {
+  for (int i = 0; i < lanes && lanes > 1; ++i) {
+    if (ls[i] == st) continue;
     QC_HIP(hipEventRecord(ctx->ev_join[i], ls[i]));
     QC_HIP(hipStreamWaitEvent(st, ctx->ev_join[i], 0));
   }
@@ -966,34 +1027,60 @@ static inline float ord2f(int i) {
 
 }  // extern "C"
 
+// Block l of the un-quantised fp32 forward on g samples, the first of them b0 of the group that the scratch holds (cond, tokens and o
+// point at the group's first).  With slot != null the min / max of the five quantiser sites are folded into slot[site][2].
+static int fp32_block(qc_ctx *ctx, const qc_block_weights_f32 &b, const float *cond, int b0, int g, int *slot, float *tokens, float *o,
+                      hipStream_t st) {
+  const int D = ctx->D, R = ctx->R, T = ctx->T, M = g * T;
+  const size_t row0 = (size_t)b0 * T;
+  float *mod = ctx->cal_mod + (size_t)b0 * 6 * D, *x = tokens + row0 * D, *h = ctx->cal_h + row0 * D, *a = ctx->cal_a + row0 * D;
+  float *u = ctx->cal_u + row0 * R, *qkv = ctx->qkv + row0 * 3 * D;
+  cond += (size_t)b0 * D;
+  o += row0 * D;
+  if (slot) QC_HIP(launch_minmax_silu(cond, (size_t)g * D, slot + 2 * QC_SITE_ADA, st));
+  QC_HIP(launch_small_linear(cond, D, 0, 0, b.ada_w, b.ada_b, mod, 6 * D, g, 6 * D, D, 1, 0, st));
+  QC_HIP(launch_ln_mod_quant(x, 0, mod, mod + D, 6 * D, M, D, T, nullptr, nullptr, h, st));
+  if (slot) QC_HIP(launch_minmax(h, (size_t)M * D, slot + 2 * QC_SITE_QKV, st));
+  QC_HIP(launch_linear_f32(h, b.qkv_w, b.qkv_b, qkv, M, 3 * D, D, 0, st));
+  QC_HIP(launch_attention(qkv, g, T, ctx->H, ctx->hd, nullptr, nullptr, o, st));
+  if (slot) QC_HIP(launch_minmax(o, (size_t)M * D, slot + 2 * QC_SITE_PROJ, st));
+  QC_HIP(launch_linear_f32(o, b.proj_w, b.proj_b, a, M, D, D, 0, st));
+  QC_HIP(launch_cache_reuse(x, 0, a, mod + 2 * D, 6 * D, g, T, D, false, st));
+  QC_HIP(launch_ln_mod_quant(x, 0, mod + 3 * D, mod + 4 * D, 6 * D, M, D, T, nullptr, nullptr, h, st));
+  if (slot) QC_HIP(launch_minmax(h, (size_t)M * D, slot + 2 * QC_SITE_FC1, st));
+  QC_HIP(launch_linear_f32(h, b.fc1_w, b.fc1_b, u, M, R, D, 1, st));
+  if (slot) QC_HIP(launch_minmax(u, (size_t)M * R, slot + 2 * QC_SITE_FC2, st));
+  QC_HIP(launch_linear_f32(u, b.fc2_w, b.fc2_b, a, M, D, R, 0, st));
+  QC_HIP(launch_cache_reuse(x, 0, a, mod + 5 * D, 6 * D, g, T, D, false, st));
+  return QC_OK;
+}
+
 // Un-quantised fp32 forward of g samples through all blocks (the network the quantiser parameters are
 // calibrated on and the reference the VC factors are fitted against): tokens must hold the embedded samples,
 // cond their conditioning vectors [g, D].  With slots != null the min / max of the five quantiser sites of
 // every block are folded into slots[l][site][2].  o: where the attention's output goes; cal_h will do (its last reader, the
-// QKV product, is then done) unless the tokens lie in cal_o already.
+// QKV product, is then done) unless the tokens lie in cal_o already.  Two halves of the samples run beside each other, for
+// the same reasons as in choose_lanes.
 static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int g, int *slots, float *tokens, float *o, hipStream_t st) {
-  const int D = ctx->D, R = ctx->R, T = ctx->T, L = ctx->L, M = g * T;
-  for (int l = 0; l < L; ++l) {
-    const qc_block_weights_f32 &b = w->blocks[l];
-    int *slot = slots ? slots + (size_t)l * QC_NUM_SITES * 2 : nullptr;
-    float *mod = ctx->cal_mod;
-    if (slot) QC_HIP(launch_minmax_silu(cond, (size_t)g * D, slot + 2 * QC_SITE_ADA, st));
-    QC_HIP(launch_small_linear(cond, D, 0, 0, b.ada_w, b.ada_b, mod, 6 * D, g, 6 * D, D, 1, 0, st));
-    QC_HIP(launch_ln_mod_quant(tokens, 0, mod, mod + D, 6 * D, M, D, T, nullptr, nullptr, ctx->cal_h, st));
-    if (slot) QC_HIP(launch_minmax(ctx->cal_h, (size_t)M * D, slot + 2 * QC_SITE_QKV, st));
-    QC_HIP(launch_linear_f32(ctx->cal_h, b.qkv_w, b.qkv_b, ctx->qkv, M, 3 * D, D, 0, st));
-    QC_HIP(launch_attention(ctx->qkv, g, T, ctx->H, ctx->hd, nullptr, nullptr, o, st));
-    if (slot) QC_HIP(launch_minmax(o, (size_t)M * D, slot + 2 * QC_SITE_PROJ, st));
-    QC_HIP(launch_linear_f32(o, b.proj_w, b.proj_b, ctx->cal_a, M, D, D, 0, st));
-    QC_HIP(launch_cache_reuse(tokens, 0, ctx->cal_a, mod + 2 * D, 6 * D, g, T, D, false, st));
-    QC_HIP(launch_ln_mod_quant(tokens, 0, mod + 3 * D, mod + 4 * D, 6 * D, M, D, T, nullptr, nullptr, ctx->cal_h, st));
-    if (slot) QC_HIP(launch_minmax(ctx->cal_h, (size_t)M * D, slot + 2 * QC_SITE_FC1, st));
-    QC_HIP(launch_linear_f32(ctx->cal_h, b.fc1_w, b.fc1_b, ctx->cal_u, M, R, D, 1, st));
-    if (slot) QC_HIP(launch_minmax(ctx->cal_u, (size_t)M * R, slot + 2 * QC_SITE_FC2, st));
-    QC_HIP(launch_linear_f32(ctx->cal_u, b.fc2_w, b.fc2_b, ctx->cal_a, M, D, R, 0, st));
-    QC_HIP(launch_cache_reuse(tokens, 0, ctx->cal_a, mod + 5 * D, 6 * D, g, T, D, false, st));
+  const int g0 = (g + 1) / 2;
+  int rc = QC_OK;
+  hipStream_t side[NUM_SIDE] = {st, st, st};
+  if (g > g0) {
+    rc = side_streams(ctx, st, side, {&ctx->ev_f32_fork, &ctx->ev_f32_join[0], &ctx->ev_f32_join[1]});
+    if (rc) return rc;
+    QC_HIP(hipEventRecord(ctx->ev_f32_fork, st));
+    for (int i = 0; i < 2; ++i) QC_HIP(hipStreamWaitEvent(side[i], ctx->ev_f32_fork, 0));
   }
-  return QC_OK;
+  for (int l = 0; l < ctx->L && !rc; ++l) {
+    int *slot = slots ? slots + (size_t)l * QC_NUM_SITES * 2 : nullptr;
+    rc = fp32_block(ctx, w->blocks[l], cond, 0, g0, slot, tokens, o, side[0]);
+    if (!rc && g > g0) rc = fp32_block(ctx, w->blocks[l], cond, g0, g - g0, slot, tokens, o, side[1]);
+  }
+  for (int i = 0; i < 2 && g > g0; ++i) {           // also after an error
+    QC_HIP(hipEventRecord(ctx->ev_f32_join[i], side[i]));
+    QC_HIP(hipStreamWaitEvent(st, ctx->ev_f32_join[i], 0));
+  }
+  return rc;
 }
 
 // eps[B] of the un-quantised network with the conditioning vectors in rows r0 .. of cond and fmod; x holds n_src latents, batch
@@ -1170,17 +1257,22 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
   if (!ctx->cache_mask.empty() && steps > ctx->mask_steps)
     QC_FAIL(QC_ERR_RANGE, "%d steps requested but the installed cache schedule has %d", steps, ctx->mask_steps);
   const int HW = ctx->d.latent_h * ctx->d.latent_w, C = ctx->C;
-  // The un-quantised network never reads anything of the quantised one: it runs on a stream of its own, its tokens in cal_o, and
-  // fills what the many short launches of the other leave of the chip.  Only its step's update of x_ref waits for the previous
-  // fit.  (The optional row-major copy of Q | K | V lies where the un-quantised network keeps its own: then one after the other.)
-  // 2 latents, depth 28, 3 steps: 24.9 -> 22.2 ms.
+  // The un-quantised network never reads anything of the quantised one, which is much shorter and a chain of small launches:
+  // the first runs in two halves on two internal streams, its tokens in cal_o, the second in one part on a third, and only the
+  // update of x_ref waits for the previous fit.  (The optional row-major copy of Q | K | V lies where the un-quantised network
+  // keeps its own: then one network after the other.)  2 latents, depth 28, 3 steps: 24.9 -> 19.5 ms
+  // (22.2 with the un-quantised network in one part).
   const bool beside = !ctx->keep_qkv_f32;
-  hipStream_t rs = st;
+  hipStream_t rs = st, qs = st;
   if (beside) {
-    if (!ctx->ref_stream) QC_HIP(hipStreamCreateWithFlags(&ctx->ref_stream, hipStreamNonBlocking));
-    for (hipEvent_t *e : {&ctx->ev_ready, &ctx->ev_ref, &ctx->ev_fit})
-      if (!*e) QC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
-    rs = ctx->ref_stream;
+    hipStream_t side[NUM_SIDE];
+    rc = side_streams(ctx, st, side, {&ctx->ev_ready, &ctx->ev_ref, &ctx->ev_fit});
+    if (rc) return rc;
+    rs = side[0];                         // the halves fork from there to side[0] and side[1]
+    qs = side[2];
+    QC_HIP(hipEventRecord(ctx->ev_ready, st));
+    QC_HIP(hipStreamWaitEvent(qs, ctx->ev_ready, 0));
+    QC_HIP(hipStreamWaitEvent(rs, ctx->ev_ready, 0));
   }
   float *tokens = beside ? ctx->cal_o : ctx->tokens, *o = beside ? ctx->cal_h : ctx->cal_o;
   const auto step = [&](int i, int w_slot) -> int {
@@ -1193,31 +1285,33 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
     QC_HIP(launch_ddim_vc(x_ref, ctx->eps_ref, B, C, HW, cx, ce, cfg_scale, nullptr, rs));
     if (beside) QC_HIP(hipEventRecord(ctx->ev_ref, rs));
     // accelerated: quantised network under the cache rule, VC with the factor fitted at this very step
-    r = denoise_impl(ctx, x_hat, B, Beff, step_mode(ctx, i, -1), w_slot, ctx->eps, st, step_sched(ctx, i, -1));
+    r = denoise_impl(ctx, x_hat, B, Beff, step_mode(ctx, i, -1), w_slot, ctx->eps, qs, step_sched(ctx, i, -1), beside ? 1 : MAX_LANES);
     if (r) return r;
-    QC_HIP(launch_ddim_vc(x_hat, ctx->eps, B, C, HW, cx, ce, cfg_scale, nullptr, st));
-    if (beside) QC_HIP(hipStreamWaitEvent(st, ctx->ev_ref, 0));
+    QC_HIP(launch_ddim_vc(x_hat, ctx->eps, B, C, HW, cx, ce, cfg_scale, nullptr, qs));
+    if (beside) QC_HIP(hipStreamWaitEvent(qs, ctx->ev_ref, 0));
     float *K_i = K_out + (size_t)i * C;
-    QC_HIP(launch_vc_fit(x_hat, x_ref, B, C, HW, vc_eps, ctx->vcfit_work, K_i, st));
-    if (beside) QC_HIP(hipEventRecord(ctx->ev_fit, st));
-    QC_HIP(launch_vc(x_hat, K_i, nullptr, B, C, HW, st));
+    QC_HIP(launch_vc_fit(x_hat, x_ref, B, C, HW, vc_eps, ctx->vcfit_work, K_i, qs));
+    if (beside) QC_HIP(hipEventRecord(ctx->ev_fit, qs));
+    QC_HIP(launch_vc(x_hat, K_i, nullptr, B, C, HW, qs));
     return QC_OK;
   };
-  // conditioning, adaLN and final modulation of a window of steps, as in qc_sample, for both networks
+  // Conditioning, adaLN and final modulation of a window of steps, as in qc_sample, for both networks (the previous window's are no
+  // longer read: its last fit waited for both).
   const int W = std::max(1, std::min(steps, ctx->win_rows / Beff));
   for (int i0 = 0; i0 < steps && !rc; i0 += W) {
     const int nw = std::min(W, steps - i0);
-    rc = prepare_window(ctx, t.data() + i0, nw, labels, B, Beff, false, st);
-    if (rc) break;
-    if (beside) {
-      QC_HIP(hipEventRecord(ctx->ev_ready, st));
+    rc = prepare_window(ctx, t.data() + i0, nw, labels, B, Beff, false, qs);
+    if (!rc && beside) {
+      QC_HIP(hipEventRecord(ctx->ev_ready, qs));
       QC_HIP(hipStreamWaitEvent(rs, ctx->ev_ready, 0));
     }
     for (int i = i0; i < i0 + nw && !rc; ++i) rc = step(i, i - i0);
   }
-  if (rc && beside) {                   // the caller's stream is never past work that still runs
+  if (beside) {                           // also after an error: the caller's stream is never past work that still runs
     QC_HIP(hipEventRecord(ctx->ev_ref, rs));
     QC_HIP(hipStreamWaitEvent(st, ctx->ev_ref, 0));
+    QC_HIP(hipEventRecord(ctx->ev_ready, qs));
+    QC_HIP(hipStreamWaitEvent(st, ctx->ev_ready, 0));
   }
   return rc;
 }

@@ -205,6 +205,62 @@ def test_halves_of_a_large_batch(model, B):
     ctx.close()
 
 
+def test_contexts_share_the_internal_streams():
+    """Three contexts of one device in threads and on streams of their own, one captured while the others run, and contexts made after
+    all earlier ones were closed: every result as it comes out alone."""
+    import threading
+    import torch
+    import paper_2503_02508_amd as qc
+    from qc_testlib import make_pair, oracle_calibration
+    m = replace(_net(128, 4, 256, 16, 16), depth=3)
+    w, B, n = I.make_weights(m, 51), 5, 3
+    lat, lab = I.make_latents(B, m, 52), I.make_labels(B, m, 53)
+    qp, _, _ = oracle_calibration(m, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    xd, ld = _cuda(lat), _cuda(lab)
+
+    def make():
+        return make_pair(m, w, qp, B, 2)[1]
+
+    ctx = make()
+    want = xd.clone()
+    ctx.sample(want, ld, 4)
+    torch.cuda.synchronize()
+    ctx.close()
+    for _ in range(2):                                   # the second time the streams are made anew
+        ctxs, outs, bad = [make() for _ in range(n)], [[] for _ in range(n)], []
+
+        def run(i):
+            try:
+                s = torch.cuda.Stream()
+                with torch.cuda.stream(s):
+                    for k in range(8):
+                        x = xd.clone()
+                        if i == 0 and k == 4:
+                            g = torch.cuda.CUDAGraph()
+                            with torch.cuda.graph(g, stream=s, capture_error_mode="thread_local"):
+                                ctxs[i].sample(x, ld, 4)
+                            x.copy_(xd)
+                            g.replay()
+                        else:
+                            ctxs[i].sample(x, ld, 4)
+                        outs[i].append(x)
+                    s.synchronize()
+            except Exception as e:                       # seen by the main thread
+                bad.append(e)
+
+        torch.cuda.synchronize()
+        threads = [threading.Thread(target=run, args=(i,)) for i in range(n)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+        assert not bad, bad
+        assert all(torch.equal(x, want) for o in outs for x in o) and all(len(o) == 8 for o in outs)
+        for c in ctxs:
+            c.close()
+
+
 @pytest.mark.parametrize("model,B", [
     (_net(64, 2, 128, 10, 14), 1),              # 35 tokens: the last group of 16 tokens has 3
     (_net(400, 10, 800, 6, 10), 3),             # groups of 16 tokens span batch elements; features end inside a chunk
