@@ -832,12 +832,58 @@ static int denoise_tail(qc_ctx *ctx, const Sub &sb, int mode, float *eps_out, hi
 // refreshed, one part -> two (us): 20 x 256 tokens 5600 -> 5150, 32: 7920 -> 7220, 64: 13680 -> 13330, 128: 26140 -> 25990; 8 x 1024
 // tokens 10440 -> 9530, 16: 18510 -> 18140; 10 x 425 tokens 5980 -> 5300; width 384, 128 x 256 tokens 7210 -> 6690.  Three parts
 // are 1 - 5 % slower than two up to 16384 rows and within 2 % of them beyond; four are slower throughout.
-static int choose_lanes(int B) { return B < MAX_LANES ? B : MAX_LANES; }
+// Below some 1000 rows of width 1152 the launches are as short as launches get and two of each only cost (one | two parts: 3 x 256 tokens of
+// width 1152 1918 | 2106, 4 x 256 2195 | 2297, 2 x 425 2704 | 2810, 4 x 256 of width 768 1606 | 1787, 8 x 256 of 384 1477 | 1568; 6 x 256 of 1152
+// 2817 | 2598, 8 x 256 3169 | 3037, of 768 2099 | 2057).
+static int choose_lanes(const qc_ctx *ctx, int B) {
+  if (B < 2 || (long long)B * ctx->T * ctx->D <= 1024 * 1152) return 1;
+  return MAX_LANES;
+}
 
-// One denoiser evaluation whose conditioning sits in slot `w` of the prepared window.  sched (optional,
+// The streams that the parts of a batch run on: n of them, which wait for what `st` holds so far (fork_lanes) and which it
+// waits for in the end (join_lanes).
+struct Lanes {
+  int n;
+  hipStream_t s[MAX_LANES];
+};
+
+static int fork_lanes(qc_ctx *ctx, int n, int B, hipStream_t st, Lanes *out) {
+  *out = Lanes{n, {st, st}};
+  if (n == 1) return QC_OK;
+  hipStream_t side[NUM_SIDE];
+  static_assert(MAX_LANES == 2, "");
+  const int rc = side_streams(ctx, st, side, {&ctx->ev_fork, &ctx->ev_join[0], &ctx->ev_join[1]});
+  if (rc) return rc;
+  // Up to 4096 rows the first half stays on the caller's stream: a fork and a join of another two events cost 25 - 35 us (a call of
+  // eight blocks, 8 latents, refreshed or cached, 510 against 545).
+  const int first = (long long)B * ctx->T <= 4096 ? 1 : 0;
+  QC_HIP(hipEventRecord(ctx->ev_fork, st));
+  for (int i = first; i < n; ++i) {
+    out->s[i] = side[i];
+    QC_HIP(hipStreamWaitEvent(out->s[i], ctx->ev_fork, 0));
+  }
+  return QC_OK;
+}
+
+static int join_lanes(qc_ctx *ctx, const Lanes &l, hipStream_t st) {
+  for (int i = 0; i < l.n; ++i) {
+    if (l.s[i] == st) continue;
+    QC_HIP(hipEventRecord(ctx->ev_join[i], l.s[i]));
+    QC_HIP(hipStreamWaitEvent(st, ctx->ev_join[i], 0));
+  }
+  return QC_OK;
+}
+
+// the part of the effective batch that lane i of n takes; its conditioning sits in slot `w` of the prepared window
+static Sub lane_part(int B, int w, int i, int n) {
+  const int b0 = i * (B / n) + std::min(i, B % n);
+  return Sub{b0, B / n + (i < B % n ? 1 : 0), i, w * B + b0, n};
+}
+
+// One denoiser evaluation on forked lanes whose conditioning sits in slot `w` of the prepared window.  sched (optional,
 // [L][2], 1 = recompute) decides per (block, module) instead of `mode`.
-static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mode, int w, float *eps_out, hipStream_t st,
-                        const unsigned char *sched = nullptr, int max_lanes = MAX_LANES) {
+static int denoise_on_lanes(qc_ctx *ctx, const float *x, int n_labels, int B, int mode, int w, float *eps_out, const Lanes &on,
+                            const unsigned char *sched) {
   bool mixed = false;
   if (sched) {
     int n_full = 0;
@@ -849,42 +895,16 @@ static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mo
     else if (n_full == 0) mode = QC_CACHED;
     else mixed = true;
   }
-  const int lanes = std::min(choose_lanes(B), max_lanes);
   Sub sub[MAX_LANES];
-  hipStream_t ls[MAX_LANES];
-  for (int i = 0, b0 = 0; i < lanes; ++i) {
-    sub[i] = Sub{b0, B / lanes + (i < B % lanes ? 1 : 0), i, w * B + b0, lanes};
-    b0 += sub[i].nb;
-  }
-  ls[0] = st;
+  for (int i = 0; i < on.n; ++i) sub[i] = lane_part(B, w, i, on.n);
   int rc = QC_OK;
-  if (lanes > 1) {
-    static_assert(MAX_LANES == 2, "");
-    hipStream_t side[NUM_SIDE];
-    rc = side_streams(ctx, st, side, {&ctx->ev_fork, &ctx->ev_join[0], &ctx->ev_join[1]});
-    if (rc) return rc;
-    // Up to 4096 rows the first half stays on the caller's stream: another two events cost 25 - 35 us a step there (8 latents, eight
-    // blocks, 16 steps 8160 us, 8720 with both halves on internal streams; 20 latents, 6 steps 5320 and 5460).
-    const int first = (long long)B * ctx->T <= 4096 ? 1 : 0;
-    QC_HIP(hipEventRecord(ctx->ev_fork, st));
-    for (int i = first; i < lanes; ++i) {
-      ls[i] = side[i];
-      QC_HIP(hipStreamWaitEvent(ls[i], ctx->ev_fork, 0));
-    }
-  }
-  for (int i = 0; i < lanes && !rc; ++i) rc = denoise_head(ctx, x, n_labels, sub[i], ls[i]);
+  for (int i = 0; i < on.n && !rc; ++i) rc = denoise_head(ctx, x, n_labels, sub[i], on.s[i]);
   if (mode == QC_FULL || mixed)
     for (int l = 0; l < ctx->L && !rc; ++l)
-      for (int i = 0; i < lanes && !rc; ++i)
-        rc = run_block_full(ctx, l, tokens_at(ctx, (size_t)sub[i].b0 * ctx->T * ctx->D), ctx->stream_bf16, sub[i], ls[i],
+      for (int i = 0; i < on.n && !rc; ++i)
+        rc = run_block_full(ctx, l, tokens_at(ctx, (size_t)sub[i].b0 * ctx->T * ctx->D), ctx->stream_bf16, sub[i], on.s[i],
                             mixed ? sched[2 * l] != 0 : true, mixed ? sched[2 * l + 1] != 0 : true);
-  for (int i = 0; i < lanes && !rc; ++i) rc = denoise_tail(ctx, sub[i], mixed ? QC_FULL : mode, eps_out, ls[i]);
-  // join even after an error so that the internal streams never run past the caller's stream unobserved
-  for (int i = 0; i < lanes && lanes > 1; ++i) {
-    if (ls[i] == st) continue;
-    QC_HIP(hipEventRecord(ctx->ev_join[i], ls[i]));
-    QC_HIP(hipStreamWaitEvent(st, ctx->ev_join[i], 0));
-  }
+  for (int i = 0; i < on.n && !rc; ++i) rc = denoise_tail(ctx, sub[i], mixed ? QC_FULL : mode, eps_out, on.s[i]);
   if (rc == QC_OK && mixed) {
     for (int i = 0; i < 2 * ctx->L; ++i)
       if (sched[i]) ctx->cache_batch[i] = B;
@@ -892,6 +912,17 @@ static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mo
     for (int &v : ctx->cache_batch) v = B;
   }
   return rc;
+}
+
+// the same between a fork and a join
+static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mode, int w, float *eps_out, hipStream_t st,
+                        const unsigned char *sched = nullptr, int max_lanes = MAX_LANES) {
+  Lanes on;
+  int rc = fork_lanes(ctx, std::min(choose_lanes(ctx, B), max_lanes), B, st, &on);
+  if (rc) return rc;
+  rc = denoise_on_lanes(ctx, x, n_labels, B, mode, w, eps_out, on, sched);
+  const int rj = join_lanes(ctx, on, st);      // also after an error: the internal streams never run past the caller's unobserved
+  return rc ? rc : rj;
 }
 
 static int check_denoise(qc_ctx *ctx, const float *x, const int32_t *labels, int n_labels, int B, int mode) {
@@ -931,17 +962,22 @@ static const unsigned char *step_sched(const qc_ctx *ctx, int step_index, int fo
   return ctx->cache_mask.data() + (size_t)step_index * ctx->L * 2;
 }
 
+// Solver update and variance compensation of latents b0 .. b0 + nb.
+static int solver_update(qc_ctx *ctx, float *x, int b0, int nb, double abar_t, double abar_prev, float cfg_scale, const float *K_t, hipStream_t st) {
+  const double cx = std::sqrt(abar_prev / abar_t);
+  const double ce = std::sqrt(1.0 - abar_prev) - cx * std::sqrt(1.0 - abar_t);
+  const size_t at = (size_t)b0 * ctx->C * ctx->d.latent_h * ctx->d.latent_w;
+  QC_PROF(QC_K_DDIM_VC);
+  QC_HIP(launch_ddim_vc(x + at, ctx->eps + at, nb, ctx->C, ctx->d.latent_h * ctx->d.latent_w, cx, ce, cfg_scale, K_t, st));
+  return QC_OK;
+}
+
 // One sampler step whose conditioning sits in slot w of the prepared window: denoiser, CFG, DDIM update, VC.
 static int sample_step_prepared(qc_ctx *ctx, float *x, int B, int mode, int w, double abar_t, double abar_prev, float cfg_scale,
                                 const float *K_t, hipStream_t st, const unsigned char *sched = nullptr) {
   const int Beff = cfg_scale > 0.0f ? 2 * B : B;
-  int rc = denoise_impl(ctx, x, B, Beff, mode, w, ctx->eps, st, sched);
-  if (rc) return rc;
-  const double cx = std::sqrt(abar_prev / abar_t);
-  const double ce = std::sqrt(1.0 - abar_prev) - cx * std::sqrt(1.0 - abar_t);
-  QC_PROF(QC_K_DDIM_VC);
-  QC_HIP(launch_ddim_vc(x, ctx->eps, B, ctx->C, ctx->d.latent_h * ctx->d.latent_w, cx, ce, cfg_scale, K_t, st));
-  return QC_OK;
+  const int rc = denoise_impl(ctx, x, B, Beff, mode, w, ctx->eps, st, sched);
+  return rc ? rc : solver_update(ctx, x, 0, B, abar_t, abar_prev, cfg_scale, K_t, st);
 }
 
 int qc_sample_step(qc_ctx *ctx, float *x, const int32_t *labels, int B, int step_index, int t, double abar_t,
@@ -982,6 +1018,24 @@ int qc_sample(qc_ctx *ctx, float *x, const int32_t *labels, int B, int steps, fl
     const int nw = std::min(W, steps - i0);
     rc = prepare_window(ctx, t.data() + i0, nw, labels, B, Beff, false, st);
     if (rc) return rc;
+    // Without guidance the two halves of the batch never meet: each runs the steps of the window on its stream, without a join at every
+    // step, and one's cached steps and solver updates lie beside the other's blocks.  Eight blocks, 6 steps,
+    // joined at every step -> once (us): 8 latents 3045 -> 2945, 20: 5240 -> 5100, 32: 7320 -> 7170, 8 of 1024 tokens 9690 -> 9510.
+    if (Beff == B && choose_lanes(ctx, B) > 1) {
+      Lanes on;
+      rc = fork_lanes(ctx, choose_lanes(ctx, B), B, st, &on);
+      if (rc) return rc;
+      for (int i = i0; i < i0 + nw && !rc; ++i) {
+        rc = denoise_on_lanes(ctx, x, B, B, step_mode(ctx, i, -1), i - i0, ctx->eps, on, step_sched(ctx, i, -1));
+        for (int l = 0; l < on.n && !rc; ++l) {
+          const Sub p = lane_part(B, 0, l, on.n);
+          rc = solver_update(ctx, x, p.b0, p.nb, at[i], ap[i], cfg_scale, K ? K + (size_t)i * ctx->C : nullptr, on.s[l]);
+        }
+      }
+      const int rj = join_lanes(ctx, on, st);
+      if (rc || rj) return rc ? rc : rj;
+      continue;
+    }
     for (int i = i0; i < i0 + nw; ++i) {
       rc = sample_step_prepared(ctx, x, B, step_mode(ctx, i, -1), i - i0, at[i], ap[i], cfg_scale,
                                 K ? K + (size_t)i * ctx->C : nullptr, st, step_sched(ctx, i, -1));

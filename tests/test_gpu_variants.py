@@ -205,6 +205,44 @@ def test_halves_of_a_large_batch(model, B):
     ctx.close()
 
 
+@pytest.mark.parametrize("hw,B,steps,cfg,mask", [
+    ((20, 20), 13, 45, 0.0, False),             # two windows of steps, halves of 7 and 6 latents on the caller's and one internal stream
+    ((20, 20), 13, 7, 0.0, True),               # a schedule per block and module
+    ((36, 28), 17, 5, 0.0, False),              # both halves on internal streams
+    ((20, 20), 7, 5, 1.5, False)])              # guidance: the halves meet at every step
+def test_halves_of_a_sampling_run(hw, B, steps, cfg, mask):
+    """A run whose halves go through a window of steps on their own equals the same steps called one by one, and latents run alone."""
+    import torch
+    from oracle import sampler
+    from qc_testlib import make_pair, oracle_calibration
+    m = replace(_net(1152, 16, 1152, *hw), depth=2)
+    w = I.make_weights(m, 61)
+    lat, lab = I.make_latents(B, m, 62), I.make_labels(B, m, 63)
+    qp, _, _ = oracle_calibration(m, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    _, ctx = make_pair(m, w, qp, 2 * B if cfg else B, 3)
+    xd, ld = _cuda(lat), _cuda(lab)
+    K = _cuda(np.linspace(0.9, 1.1, steps * 4, dtype=np.float32).reshape(steps, 4))
+    if mask:
+        rng = np.random.default_rng(5)
+        sched = (rng.random((steps, 2, 2)) < 0.5).astype(np.uint8)
+        sched[0] = 1
+        sched[2] = 1
+        sched[3] = 0
+        ctx.set_cache_mask(sched)
+    want = xd.clone()
+    for i, (t, at, ap) in enumerate(zip(*sampler.ddim_schedule(steps))):
+        ctx.sample_step(want, ld, i, int(t), float(at), float(ap), cfg, K[i])
+    for _ in range(3):
+        got = xd.clone()
+        ctx.sample(got, ld, steps, cfg, K)
+        assert torch.equal(got, want)
+    for b in (0, B // 2, B // 2 + 1, B - 1):
+        one = xd[b:b + 1].clone()
+        ctx.sample(one, ld[b:b + 1], steps, cfg, K)
+        assert torch.equal(one, want[b:b + 1]), b
+    ctx.close()
+
+
 def test_contexts_share_the_internal_streams():
     """Three contexts of one device in threads and on streams of their own, one captured while the others run, and contexts made after
     all earlier ones were closed: every result as it comes out alone."""
@@ -212,8 +250,8 @@ def test_contexts_share_the_internal_streams():
     import torch
     import paper_2503_02508_amd as qc
     from qc_testlib import make_pair, oracle_calibration
-    m = replace(_net(128, 4, 256, 16, 16), depth=3)
-    w, B, n = I.make_weights(m, 51), 5, 3
+    m = replace(_net(768, 12, 768, 20, 20), depth=2)            # 1700 rows: two halves
+    w, B, n = I.make_weights(m, 51), 17, 3
     lat, lab = I.make_latents(B, m, 52), I.make_labels(B, m, 53)
     qp, _, _ = oracle_calibration(m, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
     xd, ld = _cuda(lat), _cuda(lab)
