@@ -463,3 +463,40 @@ def test_edge_shapes(qc):
     want = tap.similarity(X, t, idx, 0.7)
     assert np.abs(A.cpu().numpy() - want).max() <= 2e-6
     assert np.allclose(dr.cpu().numpy(), want.sum(1), rtol=2e-6) and np.allclose(dc.cpu().numpy(), want.sum(0), rtol=2e-6)
+
+
+# --------------------------------------------------------------------- forms that the sizes pick
+@pytest.mark.parametrize("N,d,k", [
+    (70000, 8, 4),            # ranges of 274 rows, two batches each; centres formed by the passes themselves (256 x 32 sums)
+    (70000, 7, 6),            # the same ranges, element loads, centres by a kernel of their own
+    (2600, 31, 10),           # element loads, two chunks of 16 dimensions
+    (1537, 24, 40),           # 6720 sums
+    (1537, 24, 72),           # 12096: beyond the rule
+    (600, 128, 128), (300, 5, 1), (257, 16, 16)])
+def test_kmeans_forms(qc, N, d, k):
+    import torch
+    rng = np.random.default_rng(N + d + k)
+    means = rng.standard_normal((k, d)) * 2
+    U = (means[rng.integers(0, k, size=N)] + 0.8 * rng.standard_normal((N, d))).astype(np.float32)
+    init = rng.choice(N, k, replace=False).astype(np.int32)
+    if k > 2:
+        U[init[1]] = U[init[0]]                    # equal centres: the second has no rows in the first pass
+    labels, centres = torch.empty(N, dtype=torch.int32, device="cuda"), torch.empty((k, d), device="cuda")
+    for limit in (1, 2, 10):
+        wl, wc, wp = tap.kmeans(U, init, limit)
+        passes = qc.qc_tap_kmeans(_cuda(U), _cuda(init), limit, labels, centres, _work(qc, max(N, 256), 8, 128, k, 128))
+        if _check_labels(U, labels.cpu().numpy(), wl, wc) == 0:
+            assert passes == wp
+            assert np.allclose(centres.cpu().numpy(), wc, rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("N,F,n", [(211, 24, 191), (211, 24, 192), (211, 24, 193), (1701, 16, 1664), (1701, 16, 1665), (900, 20, 260)])
+def test_degree_sums_of_every_width(qc, N, F, n):
+    test_similarity_and_degrees(qc, N, F, n, 0.5, False)
+
+
+@pytest.mark.parametrize("N,n,k,kb,iters", [
+    (501, 64, 4, 8, 6), (601, 129, 5, 40, 4), (901, 300, 6, 72, 3),     # 1, 3 and 5 ranges: 64, 4800 and 25920 partial sums
+    (1203, 520, 8, 112, 3), (655, 192, 5, 56, 3), (655, 193, 5, 32, 3)])
+def test_embedding_of_every_block_size(qc, N, n, k, kb, iters):
+    test_embedding_matches_singular_vectors(qc, N, n, k, kb, iters)
