@@ -984,6 +984,11 @@ __global__ __launch_bounds__(1024) void chol_inv_kernel(const double *W, int par
 }
 
 // ------------------------------------------------------------------------------- Rayleigh-Ritz (Jacobi)
+// x^-1/2 to fp64 rounding level in four dependent steps: hardware estimate (2^-24 and better), one step of third order
+__device__ __forceinline__ double rsq3(double x) {
+  const double r = __builtin_amdgcn_rsq(x), e = fma(-(x * r), r, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
+}
 // sum over each row of 16 lanes, every lane receiving it: four butterfly steps on the data-parallel-primitive paths
 // (quad permutes, mirror within 8, mirror within 16), no LDS traffic.  All lanes of a row add the same pairs in the
 // same tree, so they hold bitwise the same result.
@@ -1004,13 +1009,19 @@ __device__ __forceinline__ double row16_sum(double v) {
 
 // Eigenvectors of the symmetric positive semi-definite T[kb, kb] (fp64) by one-sided Jacobi rotations on the rows of
 // a copy M of T (LDS): rotations from the left make the rows mutually orthogonal; then row j = lambda_j v_j^T.  The
-// kb / 2 pairs of a round are disjoint (round-robin schedule) and rotate concurrently, one pair per row of 16 lanes
-// (64 rows in the workgroup), lane e holding elements e, e + 16, ....  The squared row norms are carried along (a
+// kb / 2 pairs of a round are disjoint (round-robin schedule) and rotate concurrently, one pair per row of 16 lanes (as many
+// as there are pairs, in whole wavefronts), lane e holding elements e, e + 16, ....  The squared row norms are carried along (a
 // rotation by tangent t moves t * <x, y> from one to the other) and recomputed at the start of every sweep, so a pair
 // costs one reduction.  Rows whose norm is below 10^-11 of the largest are rounding noise and are left alone.  Out:
 // the k eigenvectors of largest eigenvalue as rows of Wk[k, kb], sigma[k] = lambda^1/2 (descending) and inv_sigma[k] =
 // lambda^-1/2 (0 where lambda = 0).
-__global__ __launch_bounds__(1024) void jacobi_kernel(const double *T, int kb, int k, int max_sweeps, float *Wk,
+//
+// What bounds it: the length of a round (read, reduce, rotation, write, barrier), kb - 1 of them in each of about nine sweeps; at kb = 128 also
+// the vector instructions of sixteen wavefronts.  So there are no wavefronts without a pair, no chunks beyond kb, no remainder by
+// kb - 1 (its division was a third of the chain), no square root in the test and no division in the rotation.  kb = 32: 181 -> 98 us, 128:
+// 1664 -> 1428.  (Eight lanes a pair instead of sixteen, half the scalar part: a third slower at 64 and at 128.)
+template <int NC>      // chunks of 16 elements a row
+__global__ __launch_bounds__(NC <= 2 ? 256 : NC <= 4 ? 512 : 1024) void jacobi_kernel(const double *T, int kb, int k, int max_sweeps, float *Wk,
                                                        float *inv_sigma, float *sigma, long long zw, long long zsigma) {
   T = in_slot(T, zw);
   Wk = in_slot(Wk, zw);
@@ -1020,9 +1031,9 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const double *T, int kb, i
   __shared__ int rotated;
   __shared__ double nrm2[KB_MAX];
   __shared__ double amax;
-  const int tid = threadIdx.x, e = tid & 15, grp = tid >> 4;   // grp: 0..63
+  const int tid = threadIdx.x, e = tid & 15, grp = tid >> 4, threads = blockDim.x, groups = threads >> 4;
   const int ldm = kb + 2;
-  for (int u = tid; u < kb * kb; u += 1024) {
+  for (int u = tid; u < kb * kb; u += threads) {
     const int i = u / kb, j = u % kb;
     Ms[i * ldm + j] = 0.5 * (T[i * kb + j] + T[j * kb + i]);
   }
@@ -1030,7 +1041,7 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const double *T, int kb, i
   __syncthreads();
   const int half = kb / 2, ring = kb - 1;
   for (int sweep = 0; sweep <= max_sweeps; ++sweep) {
-    for (int j = grp; j < kb; j += 64) {
+    for (int j = grp; j < kb; j += groups) {
       double s = 0.0;
       for (int c = e; c < kb; c += 16) {
         const double x = Ms[j * ldm + c];
@@ -1041,10 +1052,12 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const double *T, int kb, i
     }
     __syncthreads();
     if (sweep == max_sweeps) break;       // the norms are exact again: ready for the ranking below
-    if (tid == 0) {
-      double m = 0.0;
-      for (int i = 0; i < kb; ++i) m = fmax(m, nrm2[i]);
-      amax = m;
+    if (tid < 64) {
+      double m = tid < kb ? nrm2[tid] : 0.0;
+      if (tid + 64 < kb) m = fmax(m, nrm2[tid + 64]);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+      if (tid == 0) amax = fmax(m, 0.0);
     }
     __syncthreads();
     const double floor2 = 1e-22 * amax;
@@ -1052,13 +1065,13 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const double *T, int kb, i
       // all 64 lanes of a wavefront run the reduction (the 16-lane groups without a pair add zeros)
       const bool live = grp < half;
       const int pr = live ? grp : 0;
-      const int a = pr == 0 ? round : (round + pr) % ring;
-      const int b = pr == 0 ? ring : (round - pr + ring) % ring;
+      const int up = round + pr, down = round - pr;             // modulo ring
+      const int a = up >= ring ? up - ring : up, b = pr == 0 ? ring : down < 0 ? down + ring : down;
       double *ra = Ms + a * ldm, *rb = Ms + b * ldm;
-      double x[8], y[8];
+      double x[NC], y[NC];
       double ga = 0.0;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < NC; ++i) {
         const int c = e + 16 * i;
         const bool ok = live && c < kb;
         x[i] = ok ? ra[c] : 0.0;
@@ -1067,16 +1080,17 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const double *T, int kb, i
       }
       ga = row16_sum(ga);
       const double al = nrm2[a], be = nrm2[b];
-      if (live && fmin(al, be) > floor2 && fabs(ga) > 1e-11 * sqrt(al * be)) {
-        // the rotation from hardware reciprocal / reciprocal-square-root estimates refined by Newton steps: a
-        // correctly rounded division and square root cost several times the rest of the round, and any (c, s) with
-        // c^2 + s^2 = 1 to rounding keeps the rows' span; the sweeps converge on the same vectors
-        const double zeta = (be - al) * nr_rcp(2.0 * ga);
-        const double h2 = fma(zeta, zeta, 1.0);
-        const double tt = copysign(1.0, zeta) * nr_rcp(fabs(zeta) + h2 * nr_rsq(h2));
-        const double c_ = nr_rsq(fma(tt, tt, 1.0)), s_ = c_ * tt;
+      if (live && fmin(al, be) > floor2 && ga * ga > 1e-22 * (al * be)) {
+        // With d = |y|^2 - |x|^2, p = 2 <x, y> and r = sqrt(d^2 + p^2): c^2 = (1 + |d| / r) / 2, s = sign(d) p / (2 r c), t = s / c,
+        // two reciprocal square roots in a row (hardware estimates refined by Newton steps: a correctly rounded division and
+        // square root cost several times the rest of the round, and any (c, s) with c^2 + s^2 = 1 to rounding keeps the rows' span;
+        // the sweeps converge on the same vectors)
+        const double d = be - al, p = 2.0 * ga;
+        const double ir = rsq3(fma(d, d, p * p));
+        const double c2 = fma(0.5 * fabs(d), ir, 0.5), ic = rsq3(c2);
+        const double c_ = c2 * ic, s_ = copysign(0.5, d) * (p * ir) * ic, tt = s_ * ic;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < NC; ++i) {
           const int c = e + 16 * i;
           if (c < kb) {
             ra[c] = c_ * x[i] - s_ * y[i];
@@ -1099,7 +1113,7 @@ __global__ __launch_bounds__(1024) void jacobi_kernel(const double *T, int kb, i
   }
   __syncthreads();
   // eigenvalues = row norms; rank them (descending, ties to the lower row)
-  for (int j = grp; j < kb; j += 64) {
+  for (int j = grp; j < kb; j += groups) {
     int rank = 0;
     const double mine = nrm2[j] > 0.0 ? nrm2[j] : 0.0;
     for (int i = 0; i < kb; ++i) {
@@ -1883,8 +1897,24 @@ int embed_impl(const float *L, int N, int n, int n0, int k, int kb, int iters, c
   TAP_HIP(sgemm(bm, SE_PLAIN, gr.nz, st));
   TAP_RC(gram(w.Bm, gr.zw, false, kb, N, kb, w, gr, st));
   const size_t lds = (size_t)kb * (kb + 2) * sizeof(double);
-  TAP_HIP(set_lds((const void *)jacobi_kernel, lds));
-  hipLaunchKernelGGL(jacobi_kernel, dim3(1, 1, nz), dim3(1024), lds, st, w.W, kb, k, 30, w.Wk, w.isig, sigma, gr.zw, zout);
+#define JACOBI_CASE(NC)                                                                                                          \
+  case NC:                                                                                                                       \
+    TAP_HIP(set_lds((const void *)jacobi_kernel<NC>, lds));                                                                      \
+    hipLaunchKernelGGL(jacobi_kernel<NC>, dim3(1, 1, nz), dim3((unsigned)((kb * 8 + 63) / 64 * 64)), lds, st, w.W, kb, k, 30, w.Wk, w.isig, \
+                       sigma, gr.zw, zout);                                                                                      \
+    break;
+  switch ((kb + 15) / 16) {
+    JACOBI_CASE(1)
+    JACOBI_CASE(2)
+    JACOBI_CASE(3)
+    JACOBI_CASE(4)
+    JACOBI_CASE(5)
+    JACOBI_CASE(6)
+    JACOBI_CASE(7)
+    JACOBI_CASE(8)
+    default: TAP_FAIL(QC_ERR_UNSUPPORTED, "at most %d vectors", KB_MAX);
+  }
+#undef JACOBI_CASE
   TAP_HIP(hipGetLastError());
   SgemmArgs u{};
   u.A = w.Bm; u.sam = kb; u.sak = 1; u.za = gr.zw;
