@@ -223,6 +223,10 @@ __global__ __launch_bounds__(512) void ln_mod_quant_kernel(const void *__restric
 // expression as above, rounded to float32 once.  Eq. 1 takes v * (1 / s) where that is certain to round to the same
 // integer as the IEEE quotient v / s and the quotient itself otherwise (decided for a float4 of the whole wavefront at
 // a time, so the common case is branch-free).
+// What bounds it: about 24 vector instructions an element, most of them float64, against 5 bytes; 32768 rows of 1152 move 3.6 TB/s.
+// So 1 + scale is formed once a batch element and the test of a float4 is one comparison of its largest values: 57 -> 53 us there,
+// 17.1 -> 15.0 at 8192 rows.  (The shifts as float64 as well: a wavefront less on a SIMD, 56; two register sets that change places instead of
+// the copies: 56 - 60.)
 // Eq. 1 for four values at once, packed signed codes.  qf = v * inv_s differs from the correctly rounded quotient by
 // less than 2 units in its last place (inv_s carries half a unit of relative error, the product another half, the
 // quotient's own rounding a third), so when qf is farther than 4e-7 |qf| from a rounding boundary both round to the same
@@ -230,15 +234,17 @@ __global__ __launch_bounds__(512) void ln_mod_quant_kernel(const void *__restric
 // converted exactly; the sign bit of each byte is flipped back at the end.
 __device__ __forceinline__ unsigned quant4_packed(float h0, float h1, float h2, float h3, float s, float inv_s, float zu) {
   const float h[4] = {h0, h1, h2, h3};
-  float r[4];
-  bool doubt = false;
+  float r[4], d[4], q[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const float qf = h[e] * inv_s;
-    r[e] = __builtin_rintf(qf);
-    doubt |= (0.5f - fabsf(qf - r[e])) <= 4e-7f * fabsf(qf);
+    q[e] = h[e] * inv_s;
+    r[e] = __builtin_rintf(q[e]);
+    d[e] = q[e] - r[e];
   }
-  if (__builtin_amdgcn_ballot_w64(doubt) != 0ull) {
+  // the largest distance from an integer and the largest quotient of the four: one comparison
+  const float far = fmaxf(fmaxf(fabsf(d[0]), fabsf(d[1])), fmaxf(fabsf(d[2]), fabsf(d[3])));
+  const float big = fmaxf(fmaxf(fabsf(q[0]), fabsf(q[1])), fmaxf(fabsf(q[2]), fabsf(q[3])));
+  if (__builtin_amdgcn_ballot_w64(!(fmaf(4e-7f, big, far) < 0.5f)) != 0ull) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) r[e] = __builtin_rintf(h[e] / s);
   }
@@ -267,7 +273,8 @@ __global__ __launch_bounds__(256) void ln_mod_quant_wave_kernel(const void *__re
   }
   const QParam t = *qp;
   const float qs = t.s, inv_s = 1.0f / t.s, zu = (float)(t.z + 128);
-  float4 xa[NV], xn[NV], s4[NV], c4[NV];
+  float4 xa[NV], xn[NV], s4[NV];
+  double cd[NV][4];                                // 1 + scale
 #pragma unroll
   for (int it = 0; it < NV; ++it) xa[it] = stream_load4(x, (((size_t)m_begin * D) >> 2) + kc[it], x_bf16);
   int b_cur = -1;
@@ -280,7 +287,11 @@ __global__ __launch_bounds__(256) void ln_mod_quant_wave_kernel(const void *__re
 #pragma unroll
       for (int it = 0; it < NV; ++it) {
         s4[it] = *(const float4 *)(shift + (size_t)b * ld_mod + 4 * kc[it]);
-        c4[it] = *(const float4 *)(scale + (size_t)b * ld_mod + 4 * kc[it]);
+        const float4 c4 = *(const float4 *)(scale + (size_t)b * ld_mod + 4 * kc[it]);
+        cd[it][0] = 1.0 + (double)c4.x;
+        cd[it][1] = 1.0 + (double)c4.y;
+        cd[it][2] = 1.0 + (double)c4.z;
+        cd[it][3] = 1.0 + (double)c4.w;
       }
       b_cur = b;
     }
@@ -301,10 +312,10 @@ __global__ __launch_bounds__(256) void ln_mod_quant_wave_kernel(const void *__re
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
       if (live[it]) {
-        const float h0 = (float)((xa[it].x - mean) * rstd * (1.0 + (double)c4[it].x) + (double)s4[it].x);
-        const float h1 = (float)((xa[it].y - mean) * rstd * (1.0 + (double)c4[it].y) + (double)s4[it].y);
-        const float h2 = (float)((xa[it].z - mean) * rstd * (1.0 + (double)c4[it].z) + (double)s4[it].z);
-        const float h3 = (float)((xa[it].w - mean) * rstd * (1.0 + (double)c4[it].w) + (double)s4[it].w);
+        const float h0 = (float)((xa[it].x - mean) * rstd * cd[it][0] + (double)s4[it].x);
+        const float h1 = (float)((xa[it].y - mean) * rstd * cd[it][1] + (double)s4[it].y);
+        const float h2 = (float)((xa[it].z - mean) * rstd * cd[it][2] + (double)s4[it].z);
+        const float h3 = (float)((xa[it].w - mean) * rstd * cd[it][3] + (double)s4[it].w);
         *(unsigned *)(q + (size_t)m * D + 4 * kc[it]) = quant4_packed(h0, h1, h2, h3, qs, inv_s, zu);
       }
     }
@@ -320,7 +331,7 @@ hipError_t launch_ln_mod_quant(const void *x, int x_bf16, const float *shift, co
   const int nv = (D / 4 + 63) / 64;
   if (q && !f32_out && M >= 1024 && nv <= 5) {
     // wavefront per row; with thousands of rows four consecutive rows per wavefront (they share the batch element's
-    // modulation vectors; 2 / 4 / 8 / 16 rows measured at M = 32768: 53.3 / 51.8 / 55.3 / 57.7 us)
+    // modulation vectors; 2 / 4 / 8 / 16 rows measured at M = 32768, before the last changes: 53.3 / 51.8 / 55.3 / 57.7 us)
     const int rpw = M >= 8192 ? 4 : 1;
     const int waves = (M + rpw - 1) / rpw;
     const dim3 grid((waves + 3) / 4);
