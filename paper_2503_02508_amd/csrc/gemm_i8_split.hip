@@ -265,9 +265,11 @@ static hipError_t launch_tile(const GemmArgs &a, hipStream_t st) {
     // M = 1024: 16.4 against 19.1 us)
     const long long t96 = (long long)((a.M + 63) / 64) * ((a.N + 95) / 96);
     if (t64 > 256 && t96 <= 256 && a.K >= 2048) return launch_split<2, 3, 4, EPI, W4, WROW>(a, st);
-    // a short K: the fixed costs count, two or three small workgroups share a compute unit
-    if (t64 > 256) return launch_split<1, 2, 4, EPI, W4, WROW>(a, st);
   }
+  // about as many 64 x 64 tiles as compute units and more: some unit gets two, one after the other, where several 32 x 64 tiles share it
+  // (64 x 64 | 32 x 64, us between events: 252 tiles, M = 850: proj 14.5 | 12.6, fc2 23.7 | 20.9; 288: fc1 at M = 256 12.2 | 11.5, 4-bit 13.2 |
+  // 12.8, QKV of width 384 at M = 1024 10.8 | 10.2; 384: fc1 there 10.5 | 10.0; but 216: fc2 at M = 768 16.3 | 18.0, QKV at M = 256 10.8 | 11.2)
+  if (EPI != EPI_F32 && t64 > 232) return launch_split<1, 2, 4, EPI, W4, WROW>(a, st);
   return launch_split<2, 2, 4, EPI, W4, WROW>(a, st);
 }
 

@@ -64,6 +64,8 @@ def _net(hidden, heads, mlp, h, w, patch=2):
     ("64-row tiles, 64 tokens", _net(384, 6, 1536, 16, 16), 40, 8),
     ("64-row tiles, residuals, 425 tokens", _net(1152, 16, 4608, 50, 34), 5, 8),
     ("64-row tiles, residuals, 256 tokens, 4-bit", _net(1152, 16, 4608, 32, 32), 9, 4),
+    ("split-K: 32 x 64 tiles in place of 252 of 64 x 64, 425 tokens", _net(1152, 16, 4608, 50, 34), 2, 8),
+    ("split-K: 32 x 64 tiles in place of 288 of 64 x 64, 4-bit", _net(1152, 16, 4608, 32, 32), 1, 4),
     ("split-K: 64 x 96 tiles", _net(1152, 16, 4608, 32, 32), 4, 8),
 ])
 def test_quantisers_of_small_and_ragged_launches(name, model, B, wb):
