@@ -500,3 +500,30 @@ def test_degree_sums_of_every_width(qc, N, F, n):
     (1203, 520, 8, 112, 3), (655, 192, 5, 56, 3), (655, 193, 5, 32, 3)])
 def test_embedding_of_every_block_size(qc, N, n, k, kb, iters):
     test_embedding_matches_singular_vectors(qc, N, n, k, kb, iters)
+
+
+@pytest.mark.parametrize("k,kind", [(1, "chain"), (2, "chain"), (7, "chain"), (100, "chain"), (128, "chain"), (128, "ties"), (33, "ties"), (64, "empty")])
+def test_renaming_in_rounds(qc, k, kind):
+    """Tables that need as many rounds as labels (every entry but the last is larger than the one that waits for it), equal counts
+    (the lowest row and column first) and empty rows and columns."""
+    import torch
+    if kind == "chain":
+        T = np.zeros((k, k), dtype=np.int64)
+        for i in range(k):
+            T[i, i] = 2 * (k - i)
+            if i + 1 < k:
+                T[i, i + 1] = 2 * (k - i) - 1
+    elif kind == "ties":
+        T = np.random.default_rng(k).integers(0, 3, size=(k, k))
+    else:
+        T = np.zeros((k, k), dtype=np.int64)
+        T[3, 5] = T[5, 3] = T[9, 9] = 4
+    perm_rows, perm_cols = np.random.default_rng(k + 1).permutation(k), np.random.default_rng(k + 2).permutation(k)
+    T = T[perm_rows][:, perm_cols]
+    a, b = np.repeat(np.arange(k * k) // k, T.ravel()), np.repeat(np.arange(k * k) % k, T.ravel())
+    labels = np.stack([a, b]).astype(np.int32)
+    N = labels.shape[1]
+    out, perm = torch.empty(N, dtype=torch.int32, device="cuda"), torch.empty((2, k), dtype=torch.int32, device="cuda")
+    qc.qc_tap_aggregate(_cuda(labels), k, out, _work(qc, 256, 8, 128, k, 128), perm)
+    assert np.array_equal(perm.cpu().numpy()[1], tap.greedy_match(T))
+    assert np.array_equal(out.cpu().numpy(), tap.aggregate(labels, k))
