@@ -22,9 +22,12 @@
  *   - a context is not thread-safe: calls on one context must not overlap, and
  *     work enqueued through one context on different streams must be ordered by
  *     the caller (the context owns one workspace).  The denoiser entry points
- *     may run parts of a call on internal streams of the context; these fork
- *     from and join back into `stream`, so the caller only ever orders against
- *     `stream`.  Different contexts are independent.
+ *     may run parts of a call on internal streams; these fork from and join
+ *     back into `stream`, so the caller only ever orders against `stream`.
+ *     Different contexts are independent and may be used from different
+ *     threads; the contexts of a device share the internal streams, so calls
+ *     of two contexts that run at the same time may wait for each other there
+ *     (a call that is being captured takes internal streams of its context).
  */
 #ifndef QC_H_
 #define QC_H_
