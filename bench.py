@@ -34,25 +34,25 @@ TAP_ITERS, TAP_MAX_PASSES = 8, 100   # power-iteration rounds and k-means pass l
 # under profiles/, keyed by (workload, kernel class).  None where no counter run covers the pair.
 TRAFFIC = {
     # profiles/sampler_cfg1_dit_xl2_b8_hbm_traffic.txt: (FETCH_SIZE * 2.0 + WRITE_SIZE * 1.0) KiB per dispatch
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc2"): (16870.1 * 2.0 + 9216.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_qkv"): (6387.9 * 2.0 + 13824.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc1"): (7739.5 * 2.0 + 4608.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_proj"): (6150.1 * 2.0 + 9216.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "attention"): (7048.2 * 2.0 + 1536.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc2"): (16870.0 * 2.0 + 9216.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_qkv"): (9093.3 * 2.0 + 15182.6) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc1"): (16082.6 * 2.0 + 4608.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_proj"): (6150.0 * 2.0 + 9216.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "attention"): (7048.0 * 2.0 + 1536.0) * 1024,
     # profiles/sampler_cfg2_dit_xl2_b64_cfg_hbm_traffic.txt
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc2"): (343707.4 * 2.0 + 294912.7) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_qkv"): (130344.3 * 2.0 + 487122.2) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc1"): (214332.0 * 2.0 + 147465.9) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_proj"): (121007.1 * 2.0 + 294930.0) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "attention"): (252733.8 * 2.0 + 49152.0) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc2"): (145813.8 * 2.0 + 147461.4) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_qkv"): (65825.1 * 2.0 + 243508.2) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc1"): (110695.8 * 2.0 + 73728.8) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_proj"): (60129.9 * 2.0 + 147467.1) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "attention"): (124324.0 * 2.0 + 24576.0) * 1024,
     # profiles/sampler_cfg3_dit_xl2_512_b16_hbm_traffic.txt
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc2"): (145343.9 * 2.0 + 147464.0) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_qkv"): (63769.5 * 2.0 + 244564.8) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc1"): (108765.2 * 2.0 + 73744.2) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_proj"): (60118.6 * 2.0 + 147457.4) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "attention"): (131955.4 * 2.0 + 24576.0) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc2"): (67727.1 * 2.0 + 73751.1) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_qkv"): (32505.2 * 2.0 + 123222.5) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc1"): (56542.4 * 2.0 + 36864.9) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_proj"): (29814.2 * 2.0 + 73735.9) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "attention"): (64642.1 * 2.0 + 12288.0) * 1024,
     # profiles/clustering_tap1_counters.txt
-    ("tap1", "similarity"): (1706447.7 * 2.0 + 279718.4) * 1024,
+    ("tap1", "similarity"): (1724525.8 * 2.0 + 211461.5) * 1024,
 }
 
 
@@ -229,7 +229,7 @@ def bench_tap(args):
                    "clusters": wl.k, "alpha": wl.alpha, "iteration_block": kb, "power_iterations": TAP_ITERS,
                    "concurrent_subsamples": slots,
                    "kmeans_pass_limit": TAP_MAX_PASSES},
-        "roofline": {"bound": "mfma", "kernel": "similarity (sgemm_kernel, cosine + temporal epilogue)", "achieved": ach,
+        "roofline": {"bound": "mfma", "kernel": "similarity (sgemm_slab_kernel, cosine + temporal epilogue)", "achieved": ach,
                      "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": ach / FP32_MFMA_PEAK_TFLOPS,
                      "traffic": TRAFFIC.get((wl.name, "similarity")), "avg_launch_us": sim_ms / launches * 1e3,
                      "launches": launches},
