@@ -394,9 +394,12 @@ __device__ __forceinline__ void decide_again_and_store(unsigned char *stage, con
 // TAIL: the last feature chunk holds at most 8 real features (d = 72: 64 + 8).  Its three products then share ONE
 // instruction: of the 32 k positions of the K operand, 0..7 are the features' hi halves, 8..15 their lo halves, 16..23 the
 // hi halves again, and the query operand has hi, hi, lo there (7 instructions per key block instead of 9 at d = 72).
+// The last block of V^T then has at most 8 real features as well, and its other 8 rows hold their lo halves: one fragment, two
+// products instead of three (the lo x lo terms come with them), and one addition across lanes at the end.
+// (16 heads of 72, 16 x 1024 tokens: 301.6 -> 298 us, and 0.1 - 1 % closer to float64 in the mean.)
 //
 // What bounds it: issue slots of the vector pipe, which an MFMA shares for about half of its 16 cycles.  Per tile of 64 keys
-// a wavefront issues 116 MFMAs (QB = 2, d = 72) and about 6 vector instructions per probability (exponential, subtraction,
+// a wavefront issues 112 MFMAs (QB = 2, d = 72) and about 6 vector instructions per probability (exponential, subtraction,
 // half a maximum, one and a half for the split, the sum), so the vector work is what was cut: the running max is only raised
 // when a tile exceeds it by more than MAX_SLACK (a probability may reach 2^MAX_SLACK; hi + lo keep their relative precision),
 // which leaves one test per tile instead of two shuffles, an exponential and the rescaling of every output register.
@@ -467,7 +470,7 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   // to back and nothing waits in between.
   const int hd4 = hd >> 2;
   unsigned koff[KCH], voff[VCH];
-  int k_hi[KCH], k_lo[KCH], v_at[VCH];            // positions in Ksh / Vsh[0], in halves; negative: no such chunk
+  int k_hi[KCH], k_lo[KCH], v_at[VCH], v_lo[VCH]; // positions in Ksh / Vsh[0], in halves; negative: no such chunk
 #pragma unroll
   for (int u = 0; u < KCH; ++u) {
     const int i = tid + NT * u, ic = min(i, kchunks - 1);
@@ -482,6 +485,7 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
     const int i = tid + NT * u, ic = min(i, hd * 8 - 1);
     voff[u] = (unsigned)((ic >> 3) * Tp + (ic & 7) * 8);
     v_at[u] = i < hd * 8 ? (i >> 3) * VROW + (i & 7) * 8 : -1;
+    v_lo[u] = v_at[u] + (TAIL && (i >> 3) >= 16 * (NEB - 1) ? 8 : 16 * NEB) * VROW;
   }
   const float *const kbase = Kp + tok_base, *const vbase = Vt + vt_base;
   auto load_tile = [&](int k0) {
@@ -520,7 +524,7 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
         split_pairs(vreg[0][u], h0, l0);
         split_pairs(vreg[1][u], h1, l1);
         *(v4u *)(Vsh[0] + v_at[u]) = (v4u){h0.x, h0.y, h1.x, h1.y};
-        *(v4u *)(Vsh[1] + v_at[u]) = (v4u){l0.x, l0.y, l1.x, l1.y};
+        *(v4u *)(Vsh[0] + v_lo[u]) = (v4u){l0.x, l0.y, l1.x, l1.y};
       }
     }
   };
@@ -618,7 +622,7 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
     auto load_v = [&](int it, int slot) {
       const int a = it / NEB, e = it % NEB;
       vfh[slot] = *(const v8h *)(Vsh[0] + (e * 16 + ql) * VROW + 32 * a + 8 * g);
-      vfl[slot] = *(const v8h *)(Vsh[1] + (e * 16 + ql) * VROW + 32 * a + 8 * g);
+      if (!TAIL || e < NEB - 1) vfl[slot] = *(const v8h *)(Vsh[1] + (e * 16 + ql) * VROW + 32 * a + 8 * g);
     };
     load_v(0, 0);
     load_v(1, 1);
@@ -684,14 +688,22 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
       if (it + 2 < NP) load_v(it + 2, (it + 2) % 3);
       __builtin_amdgcn_sched_barrier(0);
       const v8h vh = vfh[slot], vl = vfl[slot];
+      if (!TAIL || e < NEB - 1) {
 #pragma unroll
-      for (int j = 0; j < QB; ++j) o[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vl, ph[j][a], o[j][e], 0, 0, 0);
+        for (int j = 0; j < QB; ++j) o[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vl, ph[j][a], o[j][e], 0, 0, 0);
+      }
 #pragma unroll
       for (int j = 0; j < QB; ++j) o[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh, pl[j][a], o[j][e], 0, 0, 0);
 #pragma unroll
       for (int j = 0; j < QB; ++j) o[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh, ph[j][a], o[j][e], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  if constexpr (TAIL) {                           // the lo halves' rows to those of their features: 8 rows = 2 lane groups further
+#pragma unroll
+    for (int j = 0; j < QB; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[j][NEB - 1][r] += __shfl_xor(o[j][NEB - 1][r], 32, 64);
   }
 
   // ---- epilogue.  The codes of the workgroup's queries are staged in LDS (the K tiles are no longer needed), the ones
