@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <math.h>
+#include <algorithm>
 #include <utility>
 #include <vector>
 #include "qc_tap.h"
@@ -1182,9 +1183,17 @@ typedef float kmv4 __attribute__((ext_vector_type(4)));
 // `own` (it > 0, no kmeans_finish_kernel in between): every workgroup starts from the sums of the pass before and forms the centres
 // itself, with the arithmetic of that kernel.  A cluster that has become empty keeps the centre that workgroup 0 has put to memory in an
 // earlier pass (it writes those that are not empty, the others are only read).
+//
+// Nothing orders the workgroups of a launch: beside other work one may start after another has ended.  So, where passes are `own`,
+// no location that a workgroup of the launch reads is written by another one in it: a pass reads the sums and counts of the pass before
+// (psum_in, pcnt_in) and writes all of its range's to the other of two copies (psum, pcnt), the ones that it keeps copied over; a centre is
+// either read by all (its cluster is empty) or written by workgroup 0 (it is not), and which of the two follows from the counts
+// of the pass before; labels are each range's own; the control words are read as said above, `dirty` is only set.  Without `own` the
+// two copies are one (psum_in == psum), which a workgroup reads and writes in its own range alone.
 template <int NC, bool V4>
 __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N, int d, float *centres, int k, int rows_per,
-                                                          int *labels, double *psum, int *pcnt, int *dirty, int *ctl, int it, int own,
+                                                          int *labels, const double *psum_in, const int *pcnt_in, double *psum, int *pcnt,
+                                                          int *dirty, int *ctl, int it, int own,
                                                           long long zu, long long zlab, long long zw, long long zctl) {
   ctl = in_slot(ctl, zctl);
   if (ctl[KM_DONE]) return;
@@ -1196,6 +1205,9 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
   U = in_slot(U, zu);
   centres = in_slot(centres, zu);
   labels = in_slot(labels, zlab);
+  const bool copies = psum_in != psum && it > 0;            // (the first pass keeps nothing)
+  psum_in = in_slot(psum_in, zw);
+  pcnt_in = in_slot(pcnt_in, zw);
   psum = in_slot(psum, zw);
   pcnt = in_slot(pcnt, zw);
   dirty = in_slot(dirty, zw);
@@ -1212,10 +1224,16 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
     changed = 0;
   }
   if (tid < KB_MAX) touched[tid] = it == 0;       // the first pass writes every count
+  // The sums and counts of before go to this pass's copy at once; the clusters that turn out to be touched are written again below, barriers
+  // later (so that their loads lie beside the others: at the end, for the kept ones alone, a clustering of 1536 samples is 2 % slower).
+  double *const ps = psum + (long long)blockIdx.x * k * d;
+  if (copies && tid < k) pcnt[blockIdx.x * k + tid] = pcnt_in[blockIdx.x * k + tid];
   for (int u = tid; u < k16 * DP; u += 512) {
     const int c = u / DP, j = u - c * DP;
     const bool in = c < k && j < d;
-    float v = centres[in ? c * d + j : 0];
+    const double kept = copies && in ? psum_in[((long long)blockIdx.x * k + c) * d + j] : 0.0;
+    float v = 0.f;
+    bool stored = in;                             // the centre is the one in memory
     if (own && in) {
       double tot = 0.0;
       int m = 0;
@@ -1226,8 +1244,8 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
           const int bb = min(b + i, (int)gridDim.x - 1);
-          q[i] = pcnt[bb * k + c];
-          t[i] = psum[((long long)bb * k + c) * d + j];
+          q[i] = pcnt_in[bb * k + c];
+          t[i] = psum_in[((long long)bb * k + c) * d + j];
         }
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i)
@@ -1236,12 +1254,15 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
             m += q[i];
           }
       }
-      if (m > 0) {
+      stored = m <= 0;
+      if (!stored) {
         v = (float)(tot / (double)m);
         if (blockIdx.x == 0) centres[c * d + j] = v;
       }
     }
-    cs[c * S + j] = in ? v : 0.f;
+    if (stored) v = centres[c * d + j];
+    if (copies && in) ps[c * d + j] = kept;
+    cs[c * S + j] = v;
   }
   __syncthreads();
   {
@@ -1382,7 +1403,6 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
   }
   if (!changed) return;                           // the same value in every thread
 
-  double *const ps = psum + (long long)blockIdx.x * k * d;
   for (int c = wave; c < k; c += NW) {
     if (!touched[c]) continue;
     double s0 = 0.0, s1 = 0.0;
@@ -1392,7 +1412,7 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
 #pragma unroll
       for (int q = 0; q < KM_ROWS / 64; ++q) {
         const int row = b0 + 64 * q + lane;
-        const int l = b0 == r0 && r1 - r0 <= KM_ROWS ? lab_s[64 * q + lane] : labels[min(row, N - 1)];
+        const int l = b0 == r0 && r1 - r0 <= KM_ROWS ? lab_s[64 * q + lane] : labels[min(row, r1 - 1)];
         unsigned long long rows = __builtin_amdgcn_ballot_w64(row < r1 && clamp_label(l, k) == c);
         count += (int)__popcll(rows);
         const float *base = U + (long long)(b0 + 64 * q) * d;
@@ -1608,6 +1628,11 @@ int kmeans_rows_per(int N) {
   return r < 256 ? 256 : r;
 }
 int kmeans_blocks(int N) { return (N + kmeans_rows_per(N) - 1) / kmeans_rows_per(N); }
+// A pass forms its centres itself, a launch less, where every workgroup can read all sums in a few round trips: the whole clustering is
+// 3 - 6 % faster up to 9216 sums (1536 samples, 8 clusters 842 -> 815 us; 4000, 16: 1355 -> 1276; 4000, 24: 1780 -> 1731), 4 - 5 % slower at
+// 13800 and 18400.
+constexpr long long KM_OWN = 10240;
+bool kmeans_own(int N, int d, int k) { return (long long)kmeans_blocks(N) * k * d <= KM_OWN; }
 
 struct SimWork {
   float *rinv, *Xs, *cs, *tc;
@@ -1655,15 +1680,19 @@ struct EmbedWork {
 struct SmallWork {      // k-means (N rows of d dimensions), aggregation, normalisation
   int *flag, *T, *perm, *pcnt, *dirty;
   double *psum;
+  size_t count;         // of one copy
   size_t bytes;
   SmallWork(void *w, int N, int d, int k) {
     Carve c(w);
     flag = c.take<int>(64);
     T = c.take<int>((size_t)k * k);
     perm = c.take<int>((size_t)M_MAX * k);
-    pcnt = c.take<int>((size_t)kmeans_blocks(N) * k);
+    // two copies of the k-means sums and counts where the passes form the centres (sums: at most 2 KM_OWN then, reserved for larger
+    // problems as well, so that a workspace for d dimensions and k clusters also does for fewer)
+    count = (size_t)kmeans_blocks(N) * k;
+    pcnt = c.take<int>(2 * count);
     dirty = c.take<int>(k);
-    psum = c.take<double>((size_t)kmeans_blocks(N) * k * d);
+    psum = c.take<double>(std::max(count * d, std::min(2 * count * d, (size_t)(2 * KM_OWN))));
     bytes = c.off + 256;
   }
 };
@@ -1973,13 +2002,15 @@ hipError_t launch_kmeans_pass(const float *U, int N, int d, float *centres, int 
   const int nc = (d + 15) / 16, k16 = (k + 15) / 16 * 16;
   const size_t lds = (size_t)k16 * (16 * nc + 4 + 1) * sizeof(float);
   const bool v4 = d % 4 == 0 && aligned16(U);
+  const size_t out = kmeans_own(N, d, k) ? it & 1 : 0, in = kmeans_own(N, d, k) ? out ^ 1 : 0;
 #define KM_CASE(NC)                                                                                                          \
   case NC: {                                                                                                                 \
     const auto kern = v4 ? kmeans_pass_kernel<NC, true> : kmeans_pass_kernel<NC, false>;                                     \
     const hipError_t e = it == 0 ? set_lds((const void *)kern, lds) : hipSuccess;                                            \
     if (e != hipSuccess) return e;                                                                                           \
     hipLaunchKernelGGL(kern, dim3(kmeans_blocks(N), 1, (unsigned)gr.nz), dim3(512), lds, st, U, N, d, centres, k, kmeans_rows_per(N), \
-                       labels, w.psum, w.pcnt, w.dirty, ctl, it, own ? 1 : 0, zu, zlab, gr.zw, ZF);                                       \
+                       labels, w.psum + in * w.count * d, w.pcnt + in * w.count, w.psum + out * w.count * d, w.pcnt + out * w.count, \
+                       w.dirty, ctl, it, own ? 1 : 0, zu, zlab, gr.zw, ZF);                                                  \
     break;                                                                                                                   \
   }
   switch (nc) {
@@ -2022,16 +2053,14 @@ int kmeans_group(const float *U, long long zu, int N, int d, int k, const int *i
     TAP_RC(read_flag(all + 3, st, &flag));
     if (flag) TAP_FAIL(QC_ERR_RANGE, "an initial-centre index lies outside [0, %d)", N);
   }
-  // A pass forms its centres itself, a launch less, where every workgroup can read all sums in a few round trips: the whole clustering is 3 - 6 %
-  // faster up to 9216 sums (1536 samples, 8 clusters 842 -> 815 us; 4000, 16: 1355 -> 1276; 4000, 24: 1780 -> 1731), 4 - 5 % slower at
-  // 13800 and 18400.
-  const bool own = (long long)nb * k * d <= 10240;
+  const bool own = kmeans_own(N, d, k);
   for (int it0 = 0; it0 < max_iter; it0 += KM_BATCH) {
     const int it1 = it0 + KM_BATCH < max_iter ? it0 + KM_BATCH : max_iter;
     for (int it = it0; it < it1; ++it) {
       TAP_HIP(launch_kmeans_pass(U, N, d, centres, k, labels, w, ctl, it, own && it > it0, zu, zlab, gr, st));
       if (own && it + 1 < it1) continue;
-      hipLaunchKernelGGL(kmeans_finish_kernel, dim3(k, 1, nz), dim3(128), 0, st, w.psum, w.pcnt, nb, k, d, centres, w.dirty, ctl, it,
+      hipLaunchKernelGGL(kmeans_finish_kernel, dim3(k, 1, nz), dim3(128), 0, st, w.psum + (own ? it & 1 : 0) * w.count * d,
+                         w.pcnt + (own ? it & 1 : 0) * w.count, nb, k, d, centres, w.dirty, ctl, it,
                          zu, gr.zw, ZF);
       TAP_HIP(hipGetLastError());
     }

@@ -527,3 +527,57 @@ def test_renaming_in_rounds(qc, k, kind):
     qc.qc_tap_aggregate(_cuda(labels), k, out, _work(qc, 256, 8, 128, k, 128), perm)
     assert np.array_equal(perm.cpu().numpy()[1], tap.greedy_match(T))
     assert np.array_equal(out.cpu().numpy(), tap.aggregate(labels, k))
+
+
+def test_small_clusterings_beside_a_sampler(qc):
+    """Clusterings whose passes form the centres themselves (few sums), on one stream while a sampling run fills the chip from another, so
+    that workgroups of a launch start late: the labels, centres and number of passes that they give alone."""
+    import torch
+    from synthetic import dit_inputs as I
+    from qc_testlib import make_pair, oracle_calibration
+    m = I.ModelDesc(depth=4, hidden=1152, heads=16, mlp_dim=4608, patch=2, latent_c=4, latent_h=32, latent_w=32)
+    w, B = I.make_weights(m, 61), 24
+    lat, lab = I.make_latents(B, m, 62), I.make_labels(B, m, 63)
+    qp, _, _ = oracle_calibration(m, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    _, ctx = make_pair(m, w, qp, B, 1)
+    x, ld = _cuda(lat), _cuda(lab)
+
+    problems = []
+    for N, d, k, seed in ((70000, 8, 4, 1), (3000, 8, 12, 2), (1537, 24, 40, 3), (12345, 4, 40, 4)):
+        rng = np.random.default_rng(seed)
+        U = (rng.standard_normal((k, d))[rng.integers(0, k, size=N)] + 1.2 * rng.standard_normal((N, d))).astype(np.float32)
+        init = rng.choice(N, k, replace=False).astype(np.int32)
+        problems.append((_cuda(U), _cuda(init), k, _work(qc, max(N, 256), 8, 128, k, 128)))
+    wl = TI.TAP_WORKLOADS["tap0"]
+    kb = 32
+    X, t, _, _ = TI.make_pool(wl.N, wl.F, wl.steps, wl.classes, wl.seed)
+    pool = [_cuda(v) for v in (X, t, TI.make_subsamples(wl.N, wl.n, wl.m, wl.seed + 1), TI.make_start_block(kb, wl.n, wl.seed + 3),
+                               TI.make_init(wl.N, wl.k, wl.m, wl.seed + 2))]
+    base = (qc.qc_tap_workspace_bytes(wl.N, wl.F, wl.n, wl.k, kb) + 255) // 256 * 256
+    work = torch.empty(3 * base, dtype=torch.uint8, device="cuda")
+
+    def once():
+        out = []
+        for U, init, k, wk in problems:
+            labels, centres = torch.empty(U.shape[0], dtype=torch.int32, device="cuda"), torch.empty((k, U.shape[1]), device="cuda")
+            out += [qc.qc_tap_kmeans(U, init, 60, labels, centres, wk), labels, centres]
+        final, per = torch.empty(wl.N, dtype=torch.int32, device="cuda"), torch.empty((wl.m, wl.N), dtype=torch.int32, device="cuda")
+        qc.qc_tap_cluster(pool[0], pool[1], pool[2], wl.alpha, wl.k, 8, pool[3], pool[4], 100, final, per, work)
+        return out + [final, per]
+
+    want = once()
+    torch.cuda.synchronize()
+    side, done, beside = torch.cuda.Stream(), torch.cuda.Event(), 0
+    for _ in range(3):
+        with torch.cuda.stream(side):
+            ctx.sample(x, ld, 20)
+            done.record()
+        for _ in range(40):
+            got = once()
+            assert all(a == b if isinstance(a, int) else torch.equal(a, b) for a, b in zip(got, want))
+            if done.query():
+                break
+            beside += 1
+        side.synchronize()
+    assert beside >= 3
+    ctx.close()
