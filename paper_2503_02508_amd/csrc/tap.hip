@@ -78,8 +78,9 @@ struct SgemmArgs {
   const float *rs, *cs, *tr, *tc;
   float alpha;
   // split K (SE_PLAIN only): workgroup (tile, blockIdx.y = s) multiplies k in [s * kchunk, (s + 1) * kchunk) and writes
-  // its partial product to C + s * part_stride; a second kernel adds the partial products in order
-  int kchunk;
+  // its partial product to C + s * part_stride; a second kernel adds the partial products in order.  zero_k: that many of the last k
+  // are padding, zero in both operands: they don't count for where K is split, so that padding changes no sum
+  int zero_k, kchunk;
   long long part_stride;
   // symmetric product (SE_PLAIN, B = A with the same strides, M = N): only the tiles on and below the diagonal are
   // computed; the kernel that adds the partial products also writes the mirror image
@@ -427,13 +428,14 @@ hipError_t sgemm(SgemmArgs a, int epi, int nz, hipStream_t st, float *part = nul
   a.part_stride = 0;
   float *out = a.C;
   const long long out_elems = (long long)a.M * a.ldc;
-  if (epi == SE_PLAIN && part && tiles < 256 && a.K >= 8 * TK) {
+  const int K = a.K - a.zero_k;
+  if (epi == SE_PLAIN && part && tiles < 256 && K >= 8 * TK) {
     long long want = 512 / tiles;            // at most the 512 workgroups the chip holds at a time
     if (want > 16) want = 16;
-    if (want > a.K / (4 * TK)) want = a.K / (4 * TK);
+    if (want > K / (4 * TK)) want = K / (4 * TK);
     if (want > (long long)(part_elems / (size_t)out_elems)) want = (long long)(part_elems / (size_t)out_elems);
     if (want > 1) {
-      a.kchunk = (int)(((a.K + want - 1) / want + TK - 1) / TK * TK);
+      a.kchunk = (int)(((K + want - 1) / want + TK - 1) / TK * TK);
       splits = (a.K + a.kchunk - 1) / a.kchunk;
       a.part_stride = out_elems;
       a.C = part;
@@ -679,103 +681,94 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const float *src, int n, 
 // column l % 16.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// One wavefront's share of a partial Gram matrix (below): the blocks of parity H, groups of 16 elements number wave, wave + 4, ...
-template <int NB, bool KC, bool V4, int H>
-__device__ __forceinline__ void gram_half(const float *Y, int kb, int n, long long sv, int j0, int j1, int wave, double *out) {
-  constexpr int BLK = NB * (NB + 1) / 2, MINE = (BLK + 1 - H) / 2;
-  extern __shared__ double gs[];                  // [2][BLK][64][4]
-  const int lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
-  f64x4 acc[MINE > 0 ? MINE : 1];
-#pragma unroll
-  for (int b = 0; b < MINE; ++b) acc[b] = (f64x4){0.0, 0.0, 0.0, 0.0};
-  for (int jb = j0 + 16 * wave; jb < j1; jb += 64) {
-    float v[NB][4];
-    const int j = jb + 4 * g;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int a = 16 * b + row, ac = min(a, kb - 1);
-      if (V4) {                                   // n a multiple of 4
-        const float4 t = *(const float4 *)(Y + (long long)ac * sv + min(j, n - 4));
-        const bool in = a < kb && j < j1;
-        v[b][0] = in ? t.x : 0.f;
-        v[b][1] = in ? t.y : 0.f;
-        v[b][2] = in ? t.z : 0.f;
-        v[b][3] = in ? t.w : 0.f;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int je = min(j + e, n - 1);
-          const float t = KC ? Y[(long long)ac * sv + je] : Y[(long long)je * sv + ac];
-          v[b][e] = a < kb && j + e < j1 ? t : 0.f;
-        }
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      double d[NB];
-#pragma unroll
-      for (int b = 0; b < NB; ++b) d[b] = (double)v[b][e];
-#pragma unroll
-      for (int p = 0; p < NB; ++p)
-#pragma unroll
-        for (int q = 0; q <= p; ++q) {
-          const int b = p * (p + 1) / 2 + q;
-          if (b % 2 == H) acc[b / 2] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[p], d[q], acc[b / 2], 0, 0, 0);
-        }
-    }
-  }
-  // the four wavefronts of a parity: 2 + 0, 3 + 1, then the two
-  f64x4 *const half = (f64x4 *)gs;
-  if (wave >= 2) {
-#pragma unroll
-    for (int b = 0; b < MINE; ++b) half[((wave - 2) * BLK + 2 * b + H) * 64 + lane] = acc[b];
-  }
-  __syncthreads();
-  if (wave < 2) {
-#pragma unroll
-    for (int b = 0; b < MINE; ++b) acc[b] += half[(wave * BLK + 2 * b + H) * 64 + lane];
-  }
-  __syncthreads();
-  if (wave == 1) {
-#pragma unroll
-    for (int b = 0; b < MINE; ++b) half[(2 * b + H) * 64 + lane] = acc[b];
-  }
-  __syncthreads();
-  if (wave != 0) return;
-#pragma unroll
-  for (int p = 0; p < NB; ++p)
-#pragma unroll
-    for (int q = 0; q <= p; ++q) {
-      const int b = p * (p + 1) / 2 + q;
-      if (b % 2 != H) continue;
-      const f64x4 s = acc[b / 2] + half[b * 64 + lane];
-      const int c = 16 * q + row;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = 16 * p + g + 4 * i;
-        if (r < kb && c < kb) out[r * kb + c] = s[i];
-      }
-    }
-}
-
 // Partial Gram matrices of kb vectors of length n over ranges of their elements, fp64: part[b][a][c] = sum_j y_a[j] y_c[j] for the
 // blocks of 16 x 16 on and below the diagonal (the others are not written).  Vector a's element j is Y[a * sv + j] (KC) or
-// Y[j * sv + a].  Both operands of a product are the same 16 vectors' values, so a wavefront loads each value once, in operand layout
-// (lane l: vector l % 16, elements 4 (l / 16) .. + 3 of a group of 16), and multiplies all pairs of blocks of it on the
-// float64 matrix cores; four pairs of wavefronts (every other block each, so that the sums fit the registers) take every fourth group
-// and their sums meet in LDS.  Bound: the
-// float64 matrix rate (NB = 8: 144 products of 64 cycles per group), then the latency of the loads.
-// Three subsamples, 128 vectors of 1640 elements: 42 us on the vector units (operands from LDS), 13 here; 32 vectors of 160: 13 and 3.7.
+// Y[j * sv + a] (rows of whole, aligned 16-byte chunks).
+//
+// Every entry is one chain of float64 multiply-adds over the elements of its range in ascending order, from zero: the matrix
+// instruction adds its four products one after the other, each with the rounding of a fused multiply-add (checked bit by bit against
+// fma).  The order counts: the factor of these sums is rounded to float32 behind a matrix of condition up to 1e12 and Lloyd's iteration
+// amplifies what is left; four interleaved chains, or ranges of another length, move 1 % of the labels of a large pool.
+//
+// 32 elements at a time go through LDS as float32 (the next ones are on their way into registers meanwhile); wavefront w multiplies the
+// blocks w, w + 8, ... of the lower triangle, counted row by row.  Bound by the float64 matrix rate where ranges are long (32768
+// elements: 256 a range), by the first loads where they are short.  Three subsamples, 128 vectors of 1640 elements: 42 us on the vector
+// units (64 outputs a thread, operands from LDS), 8.2 here; 32 vectors of 160: 13 and 3.0; 128 of 32768: 52 here.
 template <int NB, bool KC, bool V4>
 __global__ __launch_bounds__(512) void gram_partial_kernel(const float *Y, int kb, int n, long long sv, int jchunk, double *part,
                                                            long long zy, long long zw) {
+  constexpr int BLK = NB * (NB + 1) / 2, MINE = (BLK + 7) / 8, KP = 16 * NB, JB = 32;
+  constexpr int UNITS = KP * JB / 4, NL = (UNITS + 511) / 512;          // 16-byte chunks of a stage, per thread
+  // A fragment (16 vectors, 4 elements) is read without bank conflicts: rows of 36 floats, one a vector (KC), or of 16 mod 64, one an element.
+  constexpr int LD = KC ? JB + 4 : KP + (80 - KP % 64) % 64;
+  __shared__ __align__(16) float ys[2][KC ? KP * LD : JB * LD];
   Y = in_slot(Y, zy);
   part = in_slot(part, zw);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, row = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j0 = blockIdx.x * jchunk, j1 = min(n, j0 + jchunk);
+  float4 r[NL];
+  auto load = [&](int jb) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int u = tid + 512 * i;
+      const int a = KC ? u / (JB / 4) : u % (KP / 4) * 4, j = jb + (KC ? u % (JB / 4) * 4 : u / (KP / 4));
+      if (!KC || V4) {                            // KC: n a multiple of 4
+        const float *p = KC ? Y + (long long)min(a, kb - 1) * sv + min(j, n - 4) : Y + (long long)min(j, n - 1) * sv + min(a, kb - 4);
+        const float4 t = *(const float4 *)p;
+        const bool in = a < kb && j < j1;
+        r[i] = make_float4(in ? t.x : 0.f, in ? t.y : 0.f, in ? t.z : 0.f, in ? t.w : 0.f);
+      } else {
+        float t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = Y[(long long)min(a, kb - 1) * sv + min(j + e, n - 1)];
+        r[i] = make_float4(a < kb && j < j1 ? t[0] : 0.f, a < kb && j + 1 < j1 ? t[1] : 0.f, a < kb && j + 2 < j1 ? t[2] : 0.f,
+                           a < kb && j + 3 < j1 ? t[3] : 0.f);
+      }
+    }
+  };
+  int p[MINE], q[MINE], fa[MINE], fb[MINE];       // the wavefront's blocks; places of their fragments
+  f64x4 acc[MINE];
+#pragma unroll
+  for (int b = 0; b < MINE; ++b) {
+    tri_decode(min(wave + 8 * b, BLK - 1), p[b], q[b]);
+    p[b] = __builtin_amdgcn_readfirstlane(p[b]);
+    q[b] = __builtin_amdgcn_readfirstlane(q[b]);
+    fa[b] = KC ? (16 * p[b] + row) * LD + g : g * LD + 16 * p[b] + row;
+    fb[b] = KC ? (16 * q[b] + row) * LD + g : g * LD + 16 * q[b] + row;
+    acc[b] = (f64x4){0.0, 0.0, 0.0, 0.0};
+  }
+  load(j0);
+  int s = 0;
+  for (int jb = j0; jb < j1; jb += JB, s ^= 1) {
+    // (this buffer's last readers were done before the barrier of the stage in between)
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int u = tid + 512 * i;
+      if (u < UNITS) *(float4 *)(ys[s] + (KC ? u / (JB / 4) * LD + u % (JB / 4) * 4 : u / (KP / 4) * LD + u % (KP / 4) * 4)) = r[i];
+    }
+    __syncthreads();
+    if (jb + JB < j1) load(jb + JB);
+#pragma unroll
+    for (int e = 0; e < JB / 4; ++e)
+#pragma unroll
+      for (int b = 0; b < MINE; ++b) {
+        if (8 * b + 8 > BLK && wave + 8 * b >= BLK) continue;           // uniform
+        const int at = KC ? 4 * e : 4 * e * LD;
+        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)ys[s][fa[b] + at], (double)ys[s][fb[b] + at], acc[b], 0, 0, 0);
+      }
+  }
   double *const out = part + (long long)blockIdx.x * kb * kb;
-  if (wave & 1) gram_half<NB, KC, V4, 1>(Y, kb, n, sv, j0, j1, wave >> 1, out);
-  else gram_half<NB, KC, V4, 0>(Y, kb, n, sv, j0, j1, wave >> 1, out);
+#pragma unroll
+  for (int b = 0; b < MINE; ++b) {
+    if (wave + 8 * b >= BLK) continue;
+    const int c = 16 * q[b] + row;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int rr = 16 * p[b] + g + 4 * i;
+      if (rr < kb && c < kb) out[rr * kb + c] = acc[b][i];
+    }
+  }
 }
 
 // the ranges' partial matrices added in order, the lower triangle written to both sides of the diagonal
@@ -810,14 +803,6 @@ __device__ __forceinline__ double nr_rsq(double x) {
   return r * (1.5 - 0.5 * x * r * r);
 }
 
-// A block of 16 x 16: B[i][j] += or = sum_k X[i][k] Z[j][k], X and Z rows of ldx, ldz doubles
-__device__ __forceinline__ f64x4 block_nt(const double *X, int ldx, const double *Z, int ldz, int row, int g) {
-  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[row * ldx + g + 4 * e], Z[row * ldz + g + 4 * e], acc, 0, 0, 0);
-  return acc;
-}
-
 // lane N's value of a row of 16 lanes to all of the row
 template <int N>
 __device__ __forceinline__ double row_bcast(double v) {
@@ -825,29 +810,36 @@ __device__ __forceinline__ double row_bcast(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + N, 0xF, 0xF, true);
   return __hiloint2double(hi, lo);
 }
-// a[c] -= t * (lane c's col), c = C .. 15: the broadcast is part of the multiply-add (col was written long before: t depends on it)
+// a[c] += (lane c's sc) * ma and b[c] += (lane c's sc) * mb, c = C .. 15: the broadcast is part of the multiply-add
 template <int C>
-__device__ __forceinline__ void eliminate_columns(double (&a)[16], double col, double minus_t) {
+__device__ __forceinline__ void eliminate_columns(double (&a)[16], double (&b)[16], double sc, double ma, double mb) {
   if constexpr (C < 16) {
-    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(a[C]) : "v"(col), "v"(minus_t), "n"(C));
-    eliminate_columns<C + 1>(a, col, minus_t);
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(a[C]) : "v"(sc), "v"(ma), "n"(C));
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(b[C]) : "v"(sc), "v"(mb), "n"(C));
+    eliminate_columns<C + 1>(a, b, sc, ma, mb);
   }
 }
-// columns J .. 15 of the elimination of a 16 x 16 block, lane R (of each 16) its row R; rs[j] = pivot_j^-1/2
+// columns J .. 15 of the elimination of a 16 x 16 block, lane R (of each 16) its row R in a, and of 16 other rows, one a lane, in b; piv, inv:
+// lane R's own pivot and its reciprocal
 template <int J>
-__device__ __forceinline__ void eliminate(double (&a)[16], double (&rs)[16], int row, int check, bool &bad) {
+__device__ __forceinline__ void eliminate(double (&a)[16], double (&b)[16], double &piv, double &inv, int row, int check, bool &bad) {
   if constexpr (J < 16) {
-    double piv = row_bcast<J>(a[J]);
-    const bool no = !(piv > 0.0) || !(piv < INFINITY);
-    bad = bad || no || (check && piv < 0.25);
-    piv = no ? 1.0 : piv;
-    rs[J] = nr_rsq(piv);
+    asm("s_nop 1" : "+v"(a[J]));                  // written by the assembly above, which the compiler does not see into, and read across lanes next
+    double p = row_bcast<J>(a[J]);
+    const bool no = !(p > 0.0) || !(p < INFINITY);
+    bad = bad || no || (check && p < 0.25);
+    p = no ? 1.0 : p;
     const bool own = row == J;
-    const double col = a[J], minus_t = -(own ? 1.0 : col) * nr_rcp(piv);
+    const double r = nr_rcp(p);
+    piv = own ? p : piv;
+    inv = own ? r : inv;
+    const double col = a[J], ma = -(own ? 1.0 : col), mb = -b[J];
+    double sc;                                    // a value read across lanes has to be two instructions old: the wait is part of it
+    asm("v_mul_f64 %0, %1, %2\n\ts_nop 1" : "=v"(sc) : "v"(col), "v"(r));
 #pragma unroll
     for (int c = J + 1; c < 16; ++c) a[c] = own ? 0.0 : a[c];
-    eliminate_columns<J + 1>(a, col, minus_t);
-    eliminate<J + 1>(a, rs, row, check, bad);
+    eliminate_columns<J + 1>(a, b, sc, ma, mb);
+    eliminate<J + 1>(a, b, piv, inv, row, check, bad);
   }
 }
 
@@ -855,22 +847,25 @@ __device__ __forceinline__ void eliminate(double (&a)[16], double (&rs)[16], int
 // diagonal entry, keeps the factorisation alive when the rows are numerically dependent (shifted Cholesky QR: the
 // rows come out better conditioned, not yet orthonormal, and the next pass finishes).
 //
-// Blocks of 16 on one kb x kb array S in LDS (padded with the identity).  After block column p, the blocks R > p of the columns C > p
-// hold the trailing matrix (kept whole), the blocks R <= p of the columns C > p the inverse being built, r_CR^T at S[R][C], and
-// S[p][p] the inverse D_p of its own factor.  At column p, with G(R) = S[R][p] (the identity for R = p) and M(R) = G(R) D_p^T,
-//   S[R][C] -= M(R) M(C)^T for C > p (block row p starts from zero),
-// and at the end block row C of the result is D_C [r_C0 .. r_C,C-1, I].  D_p comes out of one wavefront: lane R keeps row R of
-// S[p][p] and eliminates column after column in the square-root-free form of the same scheme on single elements, the column's values
-// broadcast within the multiply-adds.  The products run on the float64 matrix cores, a block a wavefront; the wavefront that
-// factorises takes S[p+1][p+1] first and goes on with D_p+1 while the others update the rest, two barriers a block column.
-// Three at a time, kb = 128: 114 us with one column and one barrier at a time, 47 so; kb = 32: 25 and 9.6.  The chain of 16 pivots a block
-// (reciprocal, broadcast, multiply-add) is what is left.
+// The square-root-free sweep on one kb x kb array S in LDS (padded with the identity to whole blocks of 16).  After column j, rows R > j of
+// the columns C > j hold the trailing matrix, rows R <= j of the columns C > j the inverse being built, r_CR at S[R][C], r's unit diagonal
+// implicit.  At column j, with pivot p_j = S[j][j], every element of the columns C > j takes
+//   S[R][C] = fma(-g(R), g(C) (1 / p_j), S[R][C]),   g(x) = S[x][j] for x != j, g(j) = 1,
+// where row j starts from zero; at the end Lc^-1 = diag(p)^-1/2 r.  An element is one chain of multiply-adds over ascending j whatever the
+// blocking: the values go to float32 behind a matrix of condition up to 1e12, so another sequence of roundings gives other labels.
+//
+// Sixteen columns at a time.  Two wavefronts eliminate block column p: lane R of each 16 keeps row R of the diagonal block, and a row of one other
+// block beside it, the scaled column broadcast within the multiply-adds (both take the diagonal block, so nothing passes between
+// them).  Then S[R][C] of the columns beyond takes its 16 products on the float64 matrix cores, which add them one after the other with
+// the rounding of fma, a block a wavefront: column p + 1 first, the others while p + 1 is eliminated.  Blocks p < R < C are never read
+// before their row starts from zero and are left alone.  Two barriers a block column; the chain of 16 pivots a block (reciprocal,
+// broadcast, multiply-add) is what bounds it.  Three at a time, kb = 128: 114 us with one column and one barrier at a time, 50 so; kb = 32:
+// 25 and 13.6.
 // W: the matrix, or the partial sums of `parts` ranges (their triangle on and below the diagonal), added in order.
 // Out: Rinv[kb, kb] fp32 = Lc^-1 (lower triangular), so that Rinv Y has orthonormal rows when the shift is
 // negligible.  With `check` set (the last pass, whose input should already be near orthonormal) the kernel returns the
 // identity at once when W is the identity to 1e-5, and a pivot below 1/4 raises the flag: the block has no full
 // rank.  A non-positive pivot always raises it.
-constexpr int CHOL_LDM = 20;
 __global__ __launch_bounds__(1024) void chol_inv_kernel(const double *W, int parts, int kb, double shift_rel, int check,
                                                          float *Rinv, int *flag, long long zw, long long zflag) {
   W = in_slot(W, zw);
@@ -878,8 +873,8 @@ __global__ __launch_bounds__(1024) void chol_inv_kernel(const double *W, int par
   flag = in_slot(flag, zflag);
   extern __shared__ double cs_[];
   const int nb = (kb + 15) / 16, kp = 16 * nb, ld = kp + 4;
-  double *const S = cs_, *const M = cs_ + kp * ld;
-  __shared__ double redm[16], redd[16];
+  double *const S = cs_;
+  __shared__ double redm[16], redd[16], pivs[KB_MAX], invs[2][16];
   const int tid = threadIdx.x, lane = tid & 63, row = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   double dmax = 0.0, dev = 0.0;
@@ -920,76 +915,83 @@ __global__ __launch_bounds__(1024) void chol_inv_kernel(const double *W, int par
   if (tid < kb) S[tid * ld + tid] += shift;
   __syncthreads();
 
-  // D_p in place of S[p][p] (one wavefront; its four groups of 16 lanes do the same)
-  auto factor = [&](int p) {
+  // Block column p: wavefront w eliminates the diagonal block and, beside it, the rows of four others, one a group of 16 lanes.  Only wavefront 0
+  // writes the diagonal block, and only above its diagonal, where nobody reads it before the next barrier.
+  const int panel_waves = max(1, (nb + 2) / 4);
+  auto panel = [&](int p) {
     double *const P = S + 16 * p * ld + 16 * p;
-    double a[16], rs[16];
+    const int o = 4 * w + g, R = o < p ? o : o + 1;
+    const bool live = o < nb - 1;
+    double *const O = S + (16 * (live ? R : p) + row) * ld + 16 * p;
+    double a[16], b[16], piv = 1.0, inv = 1.0;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) a[c] = P[row * ld + c];
+    for (int c = 0; c < 16; ++c) {
+      a[c] = c <= row ? P[row * ld + c] : 0.0;    // above the diagonal a row starts from zero
+      b[c] = live ? O[c] : 0.0;
+    }
     bool bad = false;
-    eliminate<0>(a, rs, row, check, bad);
+    eliminate<0>(a, b, piv, inv, row, check, bad);
     if (bad && lane == 0) atomicOr(flag, 2);
-    // lane R holds r_CR in a[C] for C > R: column R of D_p
-    if (g == 0) {
+    if (live) {
 #pragma unroll
-      for (int c = 0; c < 16; ++c) P[c * ld + row] = c > row ? a[c] * rs[c] : c == row ? rs[c] : 0.0;
+      for (int c = 0; c < 16; ++c) O[c] = b[c];
+    }
+    if (w == 0 && g == 0) {
+#pragma unroll
+      for (int c = 0; c < 16; ++c)
+        if (c > row) P[row * ld + c] = a[c];
+      pivs[16 * p + row] = piv;
+      invs[p & 1][row] = inv;
     }
   };
-  if (w == 0) factor(0);
-  __syncthreads();
-  for (int p = 0; p + 1 < nb; ++p) {
-    const double *const D = S + 16 * p * ld + 16 * p;
-    if (w < nb) {                                 // M(R), R = w
-      if (w == p) {                               // the identity times D_p^T
+  // the 16 columns of block column p taken from block (R, C), C > p
+  auto update = [&](int R, int C, int p) {
+    const double *const m = S + (16 * R + row) * ld + 16 * p, *const c = S + (16 * C + row) * ld + 16 * p;
+    double *const B = S + 16 * R * ld + 16 * C + row;
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};             // block row p starts from zero
+    if (R != p) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) M[(16 * w + g + 4 * i) * CHOL_LDM + row] = D[row * ld + g + 4 * i];
-      } else {
-        const f64x4 m = block_nt(S + 16 * w * ld + 16 * p, ld, D, ld, row, g);
+      for (int i = 0; i < 4; ++i) acc[i] = B[(g + 4 * i) * ld];
+    }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) M[(16 * w + g + 4 * i) * CHOL_LDM + row] = m[i];
+    for (int e = 0; e < 4; ++e) {
+      const int k = g + 4 * e;
+      double x = m[k];
+      if (R == p) x = k < row ? 0.0 : k == row ? 1.0 : x;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-x, c[k] * invs[p & 1][k], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) B[(g + 4 * i) * ld] = acc[i];
+  };
+  for (int p = 0;; ++p) {
+    if (w < panel_waves) {
+      panel(p);
+    } else if (p > 0) {                           // block column p - 1 from the columns C = p + 1 + i: of each the rows up to p - 1 and from C on
+      int u = w - panel_waves;
+      for (int i = 0; i + p + 1 < nb; ++i) {
+        for (; u < nb - 1 - i; u += 16 - panel_waves) update(u < p ? u : u + i + 1, p + 1 + i, p - 1);
+        u -= nb - 1 - i;
       }
     }
     __syncthreads();
-    // blocks (R, C), C > p: the first, (p + 1, p + 1), is wavefront 0's, which then factorises it; the others share the rest
-    const int cols = nb - 1 - p, blocks = nb * cols;
-    for (int u = w == 0 ? 0 : w; u < blocks; u += w == 0 ? blocks : 15) {
-      const int uu = u == 0 ? (p + 1) * cols : u <= (p + 1) * cols ? u - 1 : u;      // block (p + 1, p + 1) in front
-      const int R = uu / cols, C = p + 1 + uu % cols;
-      const f64x4 m = block_nt(M + 16 * R * CHOL_LDM, CHOL_LDM, M + 16 * C * CHOL_LDM, CHOL_LDM, row, g);
-      double *const B = S + 16 * R * ld + 16 * C;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        double *const b = B + (g + 4 * i) * ld + row;
-        *b = (R == p ? 0.0 : *b) - m[i];
-      }
-    }
-    if (w == 0) factor(p + 1);
+    if (p + 1 == nb) break;
+    if (w < nb) update(w, p + 1, p);
     __syncthreads();
   }
-  // block row C of the result
-  for (int u = w; u < nb * nb; u += 16) {
-    const int C = u / nb, R = u - C * nb;
-    const double *const D = S + 16 * C * ld + 16 * C;
-    f64x4 m = {0.0, 0.0, 0.0, 0.0};
-    if (R < C) m = block_nt(D, ld, S + 16 * R * ld + 16 * C, ld, row, g);
-    if (R == C) {
+  // S[R][C] with R < C is r_CR: row C of the inverse; everything above the diagonal of Rinv is zero
+  for (int C = w; C < kb; C += 16) {
+    const double root = sqrt(pivs[C]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) m[i] = D[(g + 4 * i) * ld + row];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 16 * C + g + 4 * i, c = 16 * R + row;
-      if (r < kb && c < kb) Rinv[r * kb + c] = (float)m[i];
+    for (int h = 0; h < 2; ++h) {
+      const int R = lane + 64 * h;
+      float v = 0.f;
+      if (64 * h <= C) v = R < C ? (float)(S[min(R, kp - 1) * ld + C] / root) : R == C ? (float)(1.0 / root) : 0.f;
+      if (R < kb) Rinv[C * kb + R] = v;
     }
   }
 }
 
 // ------------------------------------------------------------------------------- Rayleigh-Ritz (Jacobi)
-// x^-1/2 to fp64 rounding level in four dependent steps: hardware estimate (2^-24 and better), one step of third order
-__device__ __forceinline__ double rsq3(double x) {
-  const double r = __builtin_amdgcn_rsq(x), e = fma(-(x * r), r, 1.0);
-  return fma(r * e, fma(0.375, e, 0.5), r);
-}
 // sum over each row of 16 lanes, every lane receiving it: four butterfly steps on the data-parallel-primitive paths
 // (quad permutes, mirror within 8, mirror within 16), no LDS traffic.  All lanes of a row add the same pairs in the
 // same tree, so they hold bitwise the same result.
@@ -1019,8 +1021,9 @@ __device__ __forceinline__ double row16_sum(double v) {
 //
 // What bounds it: the length of a round (read, reduce, rotation, write, barrier), kb - 1 of them in each of about nine sweeps; at kb = 128 also
 // the vector instructions of sixteen wavefronts.  So there are no wavefronts without a pair, no chunks beyond kb, no remainder by
-// kb - 1 (its division was a third of the chain), no square root in the test and no division in the rotation.  kb = 32: 181 -> 98 us, 128:
-// 1664 -> 1428.  (Eight lanes a pair instead of sixteen, half the scalar part: a third slower at 64 and at 128.)
+// kb - 1 (its division was a third of the chain) and no square root in the test.  kb = 32: 181 -> 107 us, 128: 1664 -> 1572, same bits.
+// (Two reciprocal square roots in place of the rotation's four steps: 86 and 1340, but other last bits, which move labels.  Eight lanes a pair
+// instead of sixteen, half the scalar part: a third slower at 64 and at 128.)
 template <int NC>      // chunks of 16 elements a row
 __global__ __launch_bounds__(NC <= 2 ? 256 : NC <= 4 ? 512 : 1024) void jacobi_kernel(const double *T, int kb, int k, int max_sweeps, float *Wk,
                                                        float *inv_sigma, float *sigma, long long zw, long long zsigma) {
@@ -1081,15 +1084,19 @@ __global__ __launch_bounds__(NC <= 2 ? 256 : NC <= 4 ? 512 : 1024) void jacobi_k
       }
       ga = row16_sum(ga);
       const double al = nrm2[a], be = nrm2[b];
-      if (live && fmin(al, be) > floor2 && ga * ga > 1e-22 * (al * be)) {
-        // With d = |y|^2 - |x|^2, p = 2 <x, y> and r = sqrt(d^2 + p^2): c^2 = (1 + |d| / r) / 2, s = sign(d) p / (2 r c), t = s / c,
-        // two reciprocal square roots in a row (hardware estimates refined by Newton steps: a correctly rounded division and
-        // square root cost several times the rest of the round, and any (c, s) with c^2 + s^2 = 1 to rounding keeps the rows' span;
-        // the sweeps converge on the same vectors)
-        const double d = be - al, p = 2.0 * ga;
-        const double ir = rsq3(fma(d, d, p * p));
-        const double c2 = fma(0.5 * fabs(d), ir, 0.5), ic = rsq3(c2);
-        const double c_ = c2 * ic, s_ = copysign(0.5, d) * (p * ir) * ic, tt = s_ * ic;
+      // |<x, y>| > 1e-11 |x| |y|, by its square where that is certain to decide alike
+      const double sq = ga * ga, lim = 1e-22 * (al * be);
+      bool turn = sq > lim;
+      if (!(fabs(sq - lim) > 1e-12 * lim && lim > 1e-280 && lim < 1e280)) turn = fabs(ga) > 1e-11 * sqrt(al * be);
+      if (live && fmin(al, be) > floor2 && turn) {
+        // the rotation from hardware reciprocal / reciprocal-square-root estimates refined by Newton steps: a correctly rounded
+        // division and square root cost several times the rest of the round, and any (c, s) with c^2 + s^2 = 1 to rounding keeps the
+        // rows' span; the sweeps converge on the same vectors, but a formula of other roundings ends on other last bits
+        // and so on other labels
+        const double zeta = (be - al) * nr_rcp(2.0 * ga);
+        const double h2 = fma(zeta, zeta, 1.0);
+        const double tt = copysign(1.0, zeta) * nr_rcp(fabs(zeta) + h2 * nr_rsq(h2));
+        const double c_ = nr_rsq(fma(tt, tt, 1.0)), s_ = c_ * tt;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
           const int c = e + 16 * i;
@@ -1617,9 +1624,8 @@ struct Carve {
   }
 };
 
-// element ranges of the partial Gram matrices: at most 128 of them, whole multiples of the 64 elements that a workgroup's
-// wavefronts take at a time
-int gram_chunk(int len) { return (((len + 127) / 128) + 63) / 64 * 64; }
+// element ranges of the partial Gram matrices: at most 128 of them, whole multiples of the 32 elements that a workgroup takes at a time
+int gram_chunk(int len) { return (((len + 127) / 128) + 31) / 32 * 32; }
 int gram_parts(int len) { return (len + gram_chunk(len) - 1) / gram_chunk(len); }
 
 // row ranges of the k-means partial sums: at most 256 of them, at least 256 rows each
@@ -1847,14 +1853,10 @@ hipError_t set_lds(const void *kern, size_t bytes) {
 // subsample's vectors to the next
 int gram(const float *Y, long long zy, bool kc, int kb, int n, long long sv, EmbedWork &w, Group gr, hipStream_t st, bool reduce = true) {
   const int nb = (kb + 15) / 16, parts = gram_parts(n);
-  const size_t lds = (size_t)2 * (nb * (nb + 1) / 2) * 256 * sizeof(double);
   const bool v4 = kc && aligned16(Y) && sv % 4 == 0 && n % 4 == 0;
   const dim3 grid((unsigned)parts, 1, (unsigned)gr.nz);
-#define GRAM_ONE(NB, K, V)                                                                                             \
-  do {                                                                                                                 \
-    TAP_HIP(set_lds((const void *)gram_partial_kernel<NB, K, V>, lds));                                                \
-    hipLaunchKernelGGL((gram_partial_kernel<NB, K, V>), grid, dim3(512), lds, st, Y, kb, n, sv, gram_chunk(n), w.part, zy, gr.zw); \
-  } while (0)
+#define GRAM_ONE(NB, K, V) \
+  hipLaunchKernelGGL((gram_partial_kernel<NB, K, V>), grid, dim3(512), 0, st, Y, kb, n, sv, gram_chunk(n), w.part, zy, gr.zw)
 #define GRAM_CASE(NB)                       \
   case NB:                                  \
     if (!kc) GRAM_ONE(NB, false, false);    \
@@ -1888,7 +1890,7 @@ int cholqr_pass(const float *in, long long zin, float *out, int kb, int n, int c
   const bool direct = (long long)gram_parts(n) * kb * kb <= 12288;
   TAP_RC(gram(in, zin, true, kb, n, n, w, gr, st, !direct));
   const int kp = (kb + 15) / 16 * 16;
-  const size_t lds = ((size_t)kp * (kp + 4) + (size_t)kp * CHOL_LDM) * sizeof(double);
+  const size_t lds = (size_t)kp * (kp + 4) * sizeof(double);
   TAP_HIP(set_lds((const void *)chol_inv_kernel, lds));
   hipLaunchKernelGGL(chol_inv_kernel, dim3(1, 1, (unsigned)gr.nz), dim3(1024), lds, st, direct ? w.part : w.W, direct ? gram_parts(n) : 1, kb,
                      1e-12, check, w.Rinv, fl, gr.zw, ZF);
@@ -1949,7 +1951,7 @@ int embed_impl(const float *L, int N, int n, int n0, int k, int kb, int iters, c
   mul.A = w.Q; mul.sam = n; mul.sak = 1; mul.za = gr.zw;
   mul.B = w.G; mul.sbn = n; mul.sbk = 1; mul.zb = gr.zw;      // G is symmetric
   mul.C = w.Y; mul.ldc = n; mul.zc = gr.zw; mul.zpart = gr.zw;
-  mul.M = kb; mul.N = n; mul.K = n;
+  mul.M = kb; mul.N = n; mul.K = n; mul.zero_k = n - n0;
   for (int it = 0; it < iters; ++it) {
     TAP_HIP(sgemm(mul, SE_PLAIN, gr.nz, st, w.spart, w.spart_elems));
     if (it + 1 < iters) TAP_RC(recondition(w.Y, gr.zw, w, kb, n, gr, fl, st));

@@ -2,6 +2,9 @@
 ABI, on seeded synthetic pools.  Floating-point results: fp32 arithmetic against fp64, tolerances stated at each check;
 labels, permutations and votes: exact, except where a distance tie within fp32 rounding decides (then the label must be
 one of the tied centres)."""
+import hashlib
+import os
+
 import numpy as np
 import pytest
 
@@ -500,6 +503,53 @@ def test_degree_sums_of_every_width(qc, N, F, n):
     (1203, 520, 8, 112, 3), (655, 192, 5, 56, 3), (655, 193, 5, 32, 3)])
 def test_embedding_of_every_block_size(qc, N, n, k, kb, iters):
     test_embedding_matches_singular_vectors(qc, N, n, k, kb, iters)
+
+
+# ------------------------------------------------------------------------------------------- bits that stay
+# Digests of an embedding and of a whole clustering (three subsamples), or "refused", a pool a row.  Lloyd's iteration amplifies the last
+# bits of the embedding, which stands behind a matrix of condition up to 1e12, so another order of roundings in the Gram
+# matrices, their factors or the rotations gives other labels (and refuses other pools of numerically deficient rank).
+# The digests are those of the plain forms: one ascending chain of multiply-adds an entry and range, one column at a time, ranges of a multiple of 32
+# elements, K split by the unpadded length.
+DIGESTS = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "clustering_digests.txt")
+
+
+def clustering_digests(qc, N, F, n, k, kb, alpha, slots):
+    """Digests of the normalised matrix of the first subsample, of its embedding and of the clustering's labels."""
+    import torch
+    X, t, _, _ = TI.make_pool(N, F, 50, max(2, k * 4 // 5), seed=N + n)
+    if alpha == 1.0:
+        X = np.abs(X)                   # positive degrees; the matrix has at most F independent columns
+    subs, init = TI.make_subsamples(N, n, 3, seed=N + k), TI.make_init(N, k, 3, seed=N + kb)
+    X, t, subs, init, q0 = (_cuda(v) for v in (X, t, subs, init, TI.make_start_block(kb, n, seed=n + kb)))
+    size = (qc.qc_tap_workspace_bytes(N, F, n, k, kb) + 255) // 256 * 256
+    work = torch.empty(slots * size, dtype=torch.uint8, device="cuda")
+
+    def digest(call, *outs):
+        try:
+            call()
+        except qc.QCError as e:
+            if e.code != -4:
+                raise
+            return "refused"
+        return hashlib.sha1(b"".join(o.cpu().numpy().tobytes() for o in outs)).hexdigest()[:16]
+
+    A, dr, dc = (torch.empty(shape, device="cuda") for shape in ((N, n), (N,), (n,)))
+
+    def matrix():
+        qc.qc_tap_similarity(X, t, subs[0], alpha, A, dr, dc, work)
+        qc.qc_tap_normalise(A, dr, dc, work)
+
+    U, sigma = torch.empty((N, k), device="cuda"), torch.empty(k, device="cuda")
+    final, per = torch.empty(N, dtype=torch.int32, device="cuda"), torch.empty((3, N), dtype=torch.int32, device="cuda")
+    return [digest(matrix, A), digest(lambda: qc.qc_tap_embed(A, k, 8, q0, U, sigma, work), U, sigma),
+            digest(lambda: qc.qc_tap_cluster(X, t, subs, alpha, k, 8, q0, init, 100, final, per, work), final, per)]
+
+
+@pytest.mark.parametrize("row", [line.split() for line in open(DIGESTS) if not line.startswith("#")], ids=lambda r: "-".join(r[:6]))
+def test_embeddings_and_labels_keep_their_bits(qc, row):
+    N, F, n, k, kb, slots = (int(v) for v in row[:5] + [row[6]])
+    assert clustering_digests(qc, N, F, n, k, kb, float(row[5]), slots) == row[7:]
 
 
 @pytest.mark.parametrize("k,kind", [(1, "chain"), (2, "chain"), (7, "chain"), (100, "chain"), (128, "chain"), (128, "ties"), (33, "ties"), (64, "empty")])
