@@ -25,9 +25,12 @@
  *     may run parts of a call on internal streams; these fork from and join
  *     back into `stream`, so the caller only ever orders against `stream`.
  *     Different contexts are independent and may be used from different
- *     threads; the contexts of a device share the internal streams, so calls
- *     of two contexts that run at the same time may wait for each other there
- *     (a call that is being captured takes internal streams of its context).
+ *     threads: no stream orders work of one behind work of another that the
+ *     callers' streams do not order so.  (The contexts of a device share
+ *     internal streams; a call that finds them busy with work of another
+ *     caller's stream, or that is being captured, takes internal streams of its
+ *     context.  Which streams the runtime runs one after the other because they
+ *     lie on the same hardware queue is not the library's.)
  */
 #ifndef QC_H_
 #define QC_H_

@@ -111,8 +111,11 @@ struct qc_ctx {
   int *cal_slots, *cal_label;
   bool weights_loaded;
   // a denoiser call may run its batch as up to MAX_LANES independent sub-batches on internal streams
-  int side_dev = -1;                              // device whose shared internal streams this context holds, see side_streams
-  hipStream_t own_side[NUM_SIDE] = {};            // internal streams of calls that are captured
+  int side_dev = -1;                              // device whose shared internal streams this context has a part in, see SideCall
+  hipStream_t own_side[2][NUM_SIDE] = {};         // internal streams of its own, of calls that are captured [1] or find the shared ones busy [0]
+  hipStream_t call_st = nullptr;                  // the present call: the caller's stream, its internal streams (null: none so far) and
+  hipStream_t *call_side = nullptr;               // whether they are the shared ones
+  bool call_shared = false;
   hipEvent_t ev_fork = nullptr, ev_join[MAX_LANES] = {};
   hipEvent_t ev_f32_fork = nullptr, ev_f32_join[2] = {};
   // the factor fit runs its un-quantised network beside the quantised one
@@ -295,51 +298,116 @@ int qc_create(const qc_model_desc *desc, void *arena, size_t arena_bytes, int ma
 // 4840 instead of 3180 us, 20 latents 7600 instead of 5400).  So the contexts of a device share three streams, made
 // one after the other when the first context needs one and given back with the last that does; and work that is to run beside
 // other work goes to these only, unless it is short, since the caller's stream may lie on any queue.  Each context orders its own work with
-// events; work of contexts that run at the same time queues up.  A call that is being captured takes streams of its context, so that
-// no other context's work can get into its graph.
+// events.
+//
+// A stream runs in order, so work of two contexts on the shared ones must not be ordered otherwise by their callers' streams: a call
+// whose caller's stream is held up would hold up a call on another one.  So the shared streams belong to one caller's stream at a time.
+// A call on another one takes them if all their work is done and no call is enqueuing to them, else streams of its context.  A call that is
+// being captured always takes streams of its context, so that no other context's work can get into its graph.
 struct SidePool {
   std::mutex m;
-  int users[64] = {};
-  hipStream_t s[64][NUM_SIDE] = {};
+  struct Device {
+    int users, calls;                             // contexts; calls that are enqueuing
+    bool held;
+    hipStream_t holder;                           // the caller's stream whose calls take them
+    hipStream_t s[NUM_SIDE];
+  } d[64] = {};
 };
 static SidePool side_pool;
 
 static void release_side(qc_ctx *ctx) {
   if (ctx->side_dev < 0) return;
   std::lock_guard<std::mutex> lock(side_pool.m);
-  if (--side_pool.users[ctx->side_dev] == 0)
-    for (hipStream_t &s : side_pool.s[ctx->side_dev]) {
+  SidePool::Device &d = side_pool.d[ctx->side_dev];
+  if (--d.users == 0) {
+    for (hipStream_t &s : d.s) {
       (void)hipStreamDestroy(s);
       s = nullptr;
     }
+    d.held = false;
+  }
   ctx->side_dev = -1;
 }
 
-// The internal streams of a call on `st`, and the given events, made when they are first needed.
-static int side_streams(qc_ctx *ctx, hipStream_t st, hipStream_t (&side)[NUM_SIDE], std::initializer_list<hipEvent_t *> events) {
-  for (hipEvent_t *e : events)
-    if (!*e) QC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
+// All work on the shared streams is done.  (A query is allowed while another thread captures.)
+static bool side_idle(const SidePool::Device &d) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+  bool idle = true;
+  for (hipStream_t s : d.s)
+    if (idle && hipStreamQuery(s) != hipSuccess) {
+      (void)hipGetLastError();                    // "not ready" is no error of the caller's
+      idle = false;
+    }
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return idle;
+}
+
+// A call of the interface that may use internal streams: which ones is decided when it first asks for them, and they are its until it
+// returns.
+struct SideCall {
+  qc_ctx *c;
+  SideCall(qc_ctx *ctx, hipStream_t st) : c(ctx) { c->call_st = st; }
+  ~SideCall() {
+    if (c->call_shared) {
+      std::lock_guard<std::mutex> lock(side_pool.m);
+      --side_pool.d[c->side_dev].calls;
+    }
+    c->call_side = nullptr;
+    c->call_shared = false;
+  }
+  SideCall(const SideCall &) = delete;
+  SideCall &operator=(const SideCall &) = delete;
+};
+
+static int take_side(qc_ctx *ctx) {
+  const hipStream_t st = ctx->call_st;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (st) QC_HIP(hipStreamIsCapturing(st, &cap));      // the null stream cannot be captured
-  if (cap != hipStreamCaptureStatusNone) {
-    for (int i = 0; i < NUM_SIDE; ++i) {
-      if (!ctx->own_side[i]) QC_HIP(hipStreamCreateWithFlags(&ctx->own_side[i], hipStreamNonBlocking));
-      side[i] = ctx->own_side[i];
-    }
-    return QC_OK;
-  }
-  if (ctx->side_dev < 0) {
+  const bool capturing = cap != hipStreamCaptureStatusNone;
+  if (!capturing) {
     int dev = 0;
-    QC_HIP(hipGetDevice(&dev));
+    if (ctx->side_dev < 0) QC_HIP(hipGetDevice(&dev));
+    else dev = ctx->side_dev;
     if (dev < 0 || dev >= 64) QC_FAIL(QC_ERR_RANGE, "device %d", dev);
     std::lock_guard<std::mutex> lock(side_pool.m);
-    if (side_pool.users[dev] == 0)
-      for (hipStream_t &s : side_pool.s[dev])
+    SidePool::Device &d = side_pool.d[dev];
+    if (ctx->side_dev < 0) {
+      for (hipStream_t &s : d.s)
         if (!s) QC_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));      // (those made stay if one fails)
-    ++side_pool.users[dev];
-    ctx->side_dev = dev;
+      ++d.users;
+      ctx->side_dev = dev;
+    }
+    // the handle of the per-thread stream stands for a stream a thread
+    const bool same = d.held && d.holder == st && st != hipStreamPerThread;
+    if (same || (d.calls == 0 && (!d.held || side_idle(d)))) {
+      d.held = true;
+      d.holder = st;
+      ++d.calls;
+      ctx->call_shared = true;
+      ctx->call_side = d.s;
+      return QC_OK;
+    }
   }
-  for (int i = 0; i < NUM_SIDE; ++i) side[i] = side_pool.s[ctx->side_dev][i];
+  ctx->call_side = ctx->own_side[capturing];
+  return QC_OK;
+}
+
+// Internal stream i of the present call.  (Streams of the context are made one by one, when they are first asked for: the fewer
+// there are, the fewer share a hardware queue.)
+static int side_stream(qc_ctx *ctx, int i, hipStream_t *out) {
+  if (!ctx->call_side) {
+    const int rc = take_side(ctx);
+    if (rc) return rc;
+  }
+  if (!ctx->call_shared && !ctx->call_side[i]) QC_HIP(hipStreamCreateWithFlags(&ctx->call_side[i], hipStreamNonBlocking));
+  *out = ctx->call_side[i];
+  return QC_OK;
+}
+
+static int make_events(std::initializer_list<hipEvent_t *> events) {
+  for (hipEvent_t *e : events)
+    if (!*e) QC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
   return QC_OK;
 }
 
@@ -349,8 +417,9 @@ int qc_destroy(qc_ctx *ctx) {
   for (hipEvent_t e : {ctx->ev_fork, ctx->ev_join[0], ctx->ev_join[1], ctx->ev_f32_fork, ctx->ev_f32_join[0], ctx->ev_f32_join[1],
                        ctx->ev_ready, ctx->ev_ref, ctx->ev_fit})
     if (e) (void)hipEventDestroy(e);
-  for (hipStream_t s : ctx->own_side)
-    if (s) (void)hipStreamDestroy(s);
+  for (const auto &own : ctx->own_side)
+    for (hipStream_t s : own)
+      if (s) (void)hipStreamDestroy(s);
   release_side(ctx);
   delete ctx;
   return QC_OK;
@@ -850,18 +919,15 @@ struct Lanes {
 static int fork_lanes(qc_ctx *ctx, int n, int B, hipStream_t st, Lanes *out) {
   *out = Lanes{n, {st, st}};
   if (n == 1) return QC_OK;
-  hipStream_t side[NUM_SIDE];
   static_assert(MAX_LANES == 2, "");
-  const int rc = side_streams(ctx, st, side, {&ctx->ev_fork, &ctx->ev_join[0], &ctx->ev_join[1]});
-  if (rc) return rc;
+  int rc = make_events({&ctx->ev_fork, &ctx->ev_join[0], &ctx->ev_join[1]});
   // Up to 4096 rows the first half stays on the caller's stream: a fork and a join of another two events cost 25 - 35 us (a call of
   // eight blocks, 8 latents, refreshed or cached, 510 against 545).
   const int first = (long long)B * ctx->T <= 4096 ? 1 : 0;
+  for (int i = first; i < n && !rc; ++i) rc = side_stream(ctx, i, &out->s[i]);
+  if (rc) return rc;
   QC_HIP(hipEventRecord(ctx->ev_fork, st));
-  for (int i = first; i < n; ++i) {
-    out->s[i] = side[i];
-    QC_HIP(hipStreamWaitEvent(out->s[i], ctx->ev_fork, 0));
-  }
+  for (int i = first; i < n; ++i) QC_HIP(hipStreamWaitEvent(out->s[i], ctx->ev_fork, 0));
   return QC_OK;
 }
 
@@ -945,6 +1011,7 @@ int qc_denoise(qc_ctx *ctx, const float *x, int t, const int32_t *labels, int n_
   if (!eps_out) QC_FAIL(QC_ERR_NULL, "eps_out is NULL");
   if (t < 0) QC_FAIL(QC_ERR_RANGE, "timestep must be non-negative");
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const SideCall call(ctx, st);
   const int32_t t32 = t;
   rc = prepare_window(ctx, &t32, 1, labels, n_labels, B, mode == QC_CACHED, st);
   if (rc) return rc;
@@ -987,6 +1054,7 @@ int qc_sample_step(qc_ctx *ctx, float *x, const int32_t *labels, int B, int step
   if (!(abar_t > 0.0 && abar_t <= 1.0) || !(abar_prev > 0.0 && abar_prev <= 1.0)) QC_FAIL(QC_ERR_RANGE, "abar values must be in (0, 1]");
   if (force_mode != -1 && force_mode != QC_FULL && force_mode != QC_CACHED) QC_FAIL(QC_ERR_RANGE, "force_mode must be -1, QC_FULL or QC_CACHED");
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const SideCall call(ctx, st);
   const int Beff = cfg_scale > 0.0f ? 2 * B : B;
   if (force_mode < 0 && !ctx->cache_mask.empty() && step_index >= ctx->mask_steps)
     QC_FAIL(QC_ERR_RANGE, "step %d is outside the installed cache schedule of %d steps", step_index, ctx->mask_steps);
@@ -1007,6 +1075,7 @@ int qc_sample(qc_ctx *ctx, float *x, const int32_t *labels, int B, int steps, fl
   int rc = qc_ddim_schedule(steps, t.data(), at.data(), ap.data());
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const SideCall call(ctx, st);
   const int Beff = cfg_scale > 0.0f ? 2 * B : B;
   rc = check_denoise(ctx, x, labels, B, Beff, QC_FULL);
   if (rc) return rc;
@@ -1118,9 +1187,10 @@ static int fp32_block(qc_ctx *ctx, const qc_block_weights_f32 &b, const float *c
 static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int g, int *slots, float *tokens, float *o, hipStream_t st) {
   const int g0 = (g + 1) / 2;
   int rc = QC_OK;
-  hipStream_t side[NUM_SIDE] = {st, st, st};
+  hipStream_t side[2] = {st, st};
   if (g > g0) {
-    rc = side_streams(ctx, st, side, {&ctx->ev_f32_fork, &ctx->ev_f32_join[0], &ctx->ev_f32_join[1]});
+    rc = make_events({&ctx->ev_f32_fork, &ctx->ev_f32_join[0], &ctx->ev_f32_join[1]});
+    for (int i = 0; i < 2 && !rc; ++i) rc = side_stream(ctx, i, &side[i]);
     if (rc) return rc;
     QC_HIP(hipEventRecord(ctx->ev_f32_fork, st));
     for (int i = 0; i < 2; ++i) QC_HIP(hipStreamWaitEvent(side[i], ctx->ev_f32_fork, 0));
@@ -1181,6 +1251,7 @@ int qc_calibrate_minmax(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, co
     if (y[i] < 0 || y[i] > ctx->d.num_classes) QC_FAIL(QC_ERR_RANGE, "label %d outside 0..%d", y[i], ctx->d.num_classes);
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const SideCall call(ctx, st);
   const int D = ctx->D, L = ctx->L;
   const size_t nslots = (size_t)L * QC_NUM_SITES;
   std::vector<int> init(nslots * 2);
@@ -1289,7 +1360,9 @@ int qc_denoise_f32(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, int t, 
   if (n_labels < 1 || (B != n_labels && B != 2 * n_labels))
     QC_FAIL(QC_ERR_SHAPE, "effective batch %d must be n_labels (%d) or twice that", B, n_labels);
   if (t < 0) QC_FAIL(QC_ERR_RANGE, "timestep must be non-negative");
-  return denoise_f32_impl(ctx, w, x, n_labels, t, labels, n_labels, B, eps_out, static_cast<hipStream_t>(stream));
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const SideCall call(ctx, st);
+  return denoise_f32_impl(ctx, w, x, n_labels, t, labels, n_labels, B, eps_out, st);
 }
 
 int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float *x_ref, const int32_t *labels, int B, int steps,
@@ -1305,6 +1378,7 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
   rc = qc_ddim_schedule(steps, t.data(), at.data(), ap.data());
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const SideCall call(ctx, st);
   const int Beff = cfg_scale > 0.0f ? 2 * B : B;
   rc = check_denoise(ctx, x_hat, labels, B, Beff, QC_FULL);
   if (rc) return rc;
@@ -1319,11 +1393,10 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
   const bool beside = !ctx->keep_qkv_f32;
   hipStream_t rs = st, qs = st;
   if (beside) {
-    hipStream_t side[NUM_SIDE];
-    rc = side_streams(ctx, st, side, {&ctx->ev_ready, &ctx->ev_ref, &ctx->ev_fit});
+    rc = make_events({&ctx->ev_ready, &ctx->ev_ref, &ctx->ev_fit});
+    if (!rc) rc = side_stream(ctx, 0, &rs);      // the halves fork from there to streams 0 and 1
+    if (!rc) rc = side_stream(ctx, 2, &qs);
     if (rc) return rc;
-    rs = side[0];                         // the halves fork from there to side[0] and side[1]
-    qs = side[2];
     QC_HIP(hipEventRecord(ctx->ev_ready, st));
     QC_HIP(hipStreamWaitEvent(qs, ctx->ev_ready, 0));
     QC_HIP(hipStreamWaitEvent(rs, ctx->ev_ready, 0));

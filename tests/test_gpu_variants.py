@@ -301,6 +301,54 @@ def test_contexts_share_the_internal_streams():
             c.close()
 
 
+def test_a_stream_that_is_held_up_holds_up_no_other_context():
+    """A call on a stream behind a kernel of half a second, then calls of other contexts on other streams: one of theirs is done long before
+    it.  (Not all: a stream that shares its hardware queue, one of four, with one that waits does wait, and in some rounds all do.
+    Every round has contexts and streams that lie on other queues.)"""
+    import time
+    import torch
+    from qc_testlib import make_pair, oracle_calibration
+    m = replace(_net(768, 12, 768, 20, 20), depth=2)            # 1700 rows: two halves
+    w, B = I.make_weights(m, 51), 17
+    lat, lab = I.make_latents(B, m, 52), I.make_labels(B, m, 53)
+    qp, _, _ = oracle_calibration(m, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    xd, ld = _cuda(lat), _cuda(lab)
+    begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda._sleep(1000)                              # (the kernel is loaded when it is first used)
+    begin.record()
+    torch.cuda._sleep(1000000)
+    end.record()
+    torch.cuda.synchronize()
+    cycles = int(1000000 * 500 / begin.elapsed_time(end))
+    want, keep, early = None, [], 0
+    for _ in range(16):
+        ctxs, streams = [make_pair(m, w, qp, B, 2)[1] for _ in range(5)], [torch.cuda.Stream() for _ in range(5)]
+        keep.append(torch.cuda.Stream())
+        outs, done = [xd.clone() for _ in ctxs], [torch.cuda.Event() for _ in ctxs]
+        if want is None:
+            want = xd.clone()
+            ctxs[0].sample(want, ld, 4)
+        torch.cuda.synchronize()
+        for i, (ctx, s) in enumerate(zip(ctxs, streams)):
+            with torch.cuda.stream(s):
+                if i == 0:
+                    torch.cuda._sleep(cycles)
+                ctx.sample(outs[i], ld, 4)
+                done[i].record()
+        stop = time.monotonic() + 0.2
+        while time.monotonic() < stop and not all(e.query() for e in done[1:]):
+            time.sleep(0.005)
+        finished = [e.query() for e in done]
+        torch.cuda.synchronize()
+        early += 0 if finished[0] else sum(finished[1:])
+        assert all(torch.equal(x, want) for x in outs)
+        for c in ctxs:
+            c.close()
+        if early:
+            break
+    assert early >= 1
+
+
 @pytest.mark.parametrize("model,B", [
     (_net(64, 2, 128, 10, 14), 1),              # 35 tokens: the last group of 16 tokens has 3
     (_net(400, 10, 800, 6, 10), 3),             # groups of 16 tokens span batch elements; features end inside a chunk
