@@ -52,7 +52,7 @@ TRAFFIC = {
     ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_proj"): (29814.2 * 2.0 + 73735.9) * 1024,
     ("dit_xl2_512_w8a8_b16_ddim50_n2", "attention"): (64642.1 * 2.0 + 12288.0) * 1024,
     # profiles/clustering_tap1_counters.txt
-    ("tap1", "similarity"): (1724525.8 * 2.0 + 211461.5) * 1024,
+    ("tap1", "similarity"): (1724819.0 * 2.0 + 210910.1) * 1024,
 }
 
 

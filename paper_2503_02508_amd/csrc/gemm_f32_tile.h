@@ -25,6 +25,7 @@ __device__ __forceinline__ void slab_barrier() {
 
 template <int WM, int WN, int TM, int TN, int BK, int NS>
 struct F32Tile {
+  static_assert(BK == 16, "the swizzle is that of rows of four chunks");
   static constexpr int NT = 64 * WM * WN, RM = 32 * WM * TM, RN = 32 * WN * TN;      // threads, rows of either operand
   static constexpr int CH = BK / 4, RP = NT / CH;                                     // 16-byte chunks of a slab row, rows per pass
   static constexpr int LM = (RM + RP - 1) / RP, LN = (RN + RP - 1) / RP, NL = LM + LN;      // passes
@@ -42,7 +43,7 @@ struct F32Tile {
     // Pass i of the loads covers rows RP i .. of a slab, 16 bytes per thread, and goes straight to LDS, thread after thread.  Chunk
     // c of row r lies at chunk c ^ swz(r) (so that the rows of a fragment read spread over the banks): the thread of a place
     // fetches the chunk that belongs there.
-    const auto swz = [](int r) { return (BK == 64 ? r : BK == 32 ? r >> 1 : r >> 2) & (CH - 1); };
+    const auto swz = [](int r) { return (r >> 2) & (CH - 1); };
     const int lr = tid / CH;
     const int ns = (K + BK - 1) / BK;
     unsigned ao[LM], bo[LN];                             // byte offsets of this thread's chunk in slab 0

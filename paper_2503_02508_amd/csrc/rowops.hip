@@ -223,7 +223,8 @@ __global__ __launch_bounds__(512) void ln_mod_quant_kernel(const void *__restric
 // expression as above, rounded to float32 once.  Eq. 1 takes v * (1 / s) where that is certain to round to the same
 // integer as the IEEE quotient v / s and the quotient itself otherwise (decided for a float4 of the whole wavefront at
 // a time, so the common case is branch-free).
-// What bounds it: about 24 vector instructions an element, most of them float64, against 5 bytes; 32768 rows of 1152 move 3.6 TB/s.
+// What bounds it: vector issue, about 34 instructions an element in the compiled loop (21 of them modulation and quantiser, the others the
+// two sums and the loads; a third float64), against 5 bytes; 32768 rows of 1152 move 3.6 TB/s.
 // So 1 + scale is formed once a batch element and the test of a float4 is one comparison of its largest values: 57 -> 53 us there,
 // 17.1 -> 15.0 at 8192 rows.  (The shifts as float64 as well: a wavefront less on a SIMD, 56; two register sets that change places instead of
 // the copies: 56 - 60.)

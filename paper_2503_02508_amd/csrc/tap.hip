@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256, 2) void sgemm_kernel(SgemmArgs p) {
 
 // The same product for operands that are both contiguous along k, K a multiple of 4 (split K: whole slabs), or both along their own
 // index, and take 16-byte loads, on tiles of 64 WT x 64 WT whose slabs go straight to LDS (gemm_f32_tile.h).  Same chains, same bits.  What bounds it: the matrix
-// rate at the clock the chip holds (2.1 - 2.3 GHz), 93 % of the cycles multiplying.  32768 x 1638 x 4096: 4.2 ms on sgemm_kernel
+// rate at the clock the chip holds (2.1 - 2.3 GHz): of a launch's cycles the matrix cores are busy 85 % (similarity, epilogue included).  32768 x 1638 x 4096: 4.2 ms on sgemm_kernel
 // (105 TFLOP/s, slabs through registers, two workgroups a compute unit), 3.2 here (138; four buffers 3.3, eight 3.2, ten 3.25, slabs of
 // 32 k 3.3, wavefronts of 128 x 64 3.5, tiles of 128 x 256 3.25); the library's product takes 2.96.  The order of the tiles made
 // no difference.  L^T L of 32768 x 1640 (three): 3.0 ms there, 2.6 here.
@@ -1511,7 +1511,8 @@ __global__ __launch_bounds__(256) void contingency_kernel(const int *a, const in
 // largest of the table is one of them, so there are at most k rounds: a handful for counts that differ, nearly k where most are equal and
 // small), and only rows and columns whose partner has retired look again.  Table in LDS, eight lanes a row, then eight lanes a column.
 // A round is bound by its LDS round trips and barriers, 1 us.  One entry a round, all keys in registers, one barrier: 16 us at 8 labels,
-// 170 at 100; 5 and 103 here, with the tables of 1536 and of 32768 samples.
+// 170 at 100, whatever the table.  Here 5 at 8; at 100 it depends on the table: 92 - 118 for pools whose subsamples agree for the most part, 180
+// for one without such classes, where the counts are small and most of them equal.
 __device__ __forceinline__ long long max8(long long m) {          // over eight adjacent lanes
 #pragma unroll
   for (int o = 1; o < 8; o <<= 1) {
@@ -1800,6 +1801,7 @@ int similarity_impl(const float *X, const float *t, int N, int F, const int *idx
     TAP_HIP(hipEventRecord(g_prof.ev[g_prof.used++].second, st));
     g_prof.products += gr.nz;
   }
+  // (26 blocks of columns, 175 registers, cover a twentieth of a pool of 33000; wider ones were not measured against the two passes)
 #define DEGREE_SUMS(NC) hipLaunchKernelGGL(degree_sums_kernel<NC>, dim3(COL_CHUNKS, 1, nz), dim3(256), 0, st, A, N, n, lda, d_r, w.colpart, gr.zw)
   if (n <= 64 * 3) DEGREE_SUMS(3);
   else if (n <= 64 * 8) DEGREE_SUMS(8);

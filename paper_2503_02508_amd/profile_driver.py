@@ -13,8 +13,8 @@ byte is fetched from and written to HBM once).
     rocprofv3 --pmc FETCH_SIZE --kernel-trace -d <out> -- python3 paper_2503_02508_amd/profile_driver.py
     rocprofv3 --pmc WRITE_SIZE --kernel-trace -d <out> -- python3 paper_2503_02508_amd/profile_driver.py
 
-With `--workload tap1` the run is one subsample of the calibration-set clustering instead (similarity, degree
-normalisation, embedding, k-means at the benchmark's sizes and settings), followed by the same copies.
+With `--workload tap1` the run is the calibration-set clustering instead, with one subsample at the benchmark's sizes and
+settings, followed by the same copies.
 """
 from __future__ import annotations
 
@@ -76,19 +76,13 @@ def run_tap(args, qc, np, torch):
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
     X, t, _, _ = TI.make_pool(wl.N, wl.F, wl.steps, wl.classes, wl.seed)
     Xd, td = dev(X), dev(t)
-    idx = dev(TI.make_subsamples(wl.N, wl.n, wl.m, wl.seed + 1)[0])
-    init = dev(TI.make_init(wl.N, wl.k, wl.m, wl.seed + 2)[0])
+    subs = dev(TI.make_subsamples(wl.N, wl.n, wl.m, wl.seed + 1)[:1])
+    init = dev(TI.make_init(wl.N, wl.k, wl.m, wl.seed + 2)[:1])
     q0 = dev(TI.make_start_block(kb, wl.n, wl.seed + 3))
-    work = torch.empty(qc.qc_tap_workspace_bytes(wl.N, wl.F, wl.n, wl.k, kb), dtype=torch.uint8, device="cuda")
-    A = torch.empty((wl.N, wl.n), device="cuda")
-    dr, dc = torch.empty(wl.N, device="cuda"), torch.empty(wl.n, device="cuda")
-    U, sig = torch.empty((wl.N, wl.k), device="cuda"), torch.empty(wl.k, device="cuda")
-    lab, cen = torch.empty(wl.N, dtype=torch.int32, device="cuda"), torch.empty((wl.k, wl.k), device="cuda")
+    work = torch.empty((qc.qc_tap_workspace_bytes(wl.N, wl.F, wl.n, wl.k, kb) + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+    lab, per = torch.empty(wl.N, dtype=torch.int32, device="cuda"), torch.empty((1, wl.N), dtype=torch.int32, device="cuda")
     print("profile_driver: %s, one subsample" % wl.name, flush=True)
-    qc.qc_tap_similarity(Xd, td, idx, wl.alpha, A, dr, dc, work)
-    qc.qc_tap_normalise(A, dr, dc, work)
-    qc.qc_tap_embed(A, wl.k, 8, q0, U, sig, work)
-    qc.qc_tap_kmeans(U, init, 100, lab, cen, work)
+    qc.qc_tap_cluster(Xd, td, subs, wl.alpha, wl.k, 8, q0, init, 100, lab, per, work)
     torch.cuda.synchronize()
 
 

@@ -546,6 +546,24 @@ def clustering_digests(qc, N, F, n, k, kb, alpha, slots):
             digest(lambda: qc.qc_tap_cluster(X, t, subs, alpha, k, 8, q0, init, 100, final, per, work), final, per)]
 
 
+@pytest.mark.parametrize("N,F,n,k,kb", [
+    (70001, 8, 130, 4, 32),             # 256 ranges, two batches of rows each, centres formed by the passes: 768 workgroups for three
+    (66000, 12, 129, 9, 40)])           # centres by a kernel of their own
+def test_subsamples_of_a_group_equal_single_ones(qc, N, F, n, k, kb):
+    """Per-subsample labels, one, two and three subsamples a launch."""
+    import torch
+    X, t, _, _ = TI.make_pool(N, F, 50, 6, seed=N)
+    args = [_cuda(v) for v in (X, t, TI.make_subsamples(N, n, 3, seed=1))], _cuda(TI.make_start_block(kb, n, seed=2)), _cuda(TI.make_init(N, k, 3, seed=3))
+    size = (qc.qc_tap_workspace_bytes(N, F, n, k, kb) + 255) // 256 * 256
+    want = None
+    for slots in (1, 2, 3, 3):
+        work = torch.empty(slots * size, dtype=torch.uint8, device="cuda")
+        final, per = torch.empty(N, dtype=torch.int32, device="cuda"), torch.empty((3, N), dtype=torch.int32, device="cuda")
+        qc.qc_tap_cluster(*args[0], 0.5, k, 6, args[1], args[2], 60, final, per, work)
+        want = want or (final, per)
+        assert torch.equal(final, want[0]) and torch.equal(per, want[1]), slots
+
+
 @pytest.mark.parametrize("row", [line.split() for line in open(DIGESTS) if not line.startswith("#")], ids=lambda r: "-".join(r[:6]))
 def test_embeddings_and_labels_keep_their_bits(qc, row):
     N, F, n, k, kb, slots = (int(v) for v in row[:5] + [row[6]])
