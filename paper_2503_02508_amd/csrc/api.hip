@@ -595,7 +595,7 @@ static void *cache_at(const qc_ctx *ctx, int block, int which, size_t elem = 0) 
 
 // adaLN projection of blocks [l0, l0+nl) for `rows` rows of the conditioning tables starting at row r0:
 // mod[l, r, :] = Lin_q(codes of SiLU(c[r])); gates only on request.
-static int run_adaln(qc_ctx *ctx, int l0, int nl, int r0, int rows, bool gates_only, hipStream_t st) {
+static GemmArgs adaln_args(const qc_ctx *ctx, int l0, int r0, int rows, bool gates_only) {
   const size_t D = ctx->D, WR = ctx->win_rows;
   GemmArgs a{};
   const LinearQ &q = ctx->blk[l0].lin[QC_SITE_ADA];
@@ -607,8 +607,12 @@ static int run_adaln(qc_ctx *ctx, int l0, int nl, int r0, int rows, bool gates_o
   a.zs_out = (long long)(WR * 6 * D); a.zs_qp = QC_NUM_SITES;
   a.sel_D = (gates_only && D % 128 == 0) ? (int)D : 0;
   a.y = ctx->mod + ((size_t)l0 * WR + r0) * 6 * D; a.ldy = (int)(6 * D);
+  return a;
+}
+
+static int run_adaln(qc_ctx *ctx, int l0, int nl, int r0, int rows, bool gates_only, hipStream_t st) {
   QC_PROF(QC_K_ADALN);
-  QC_HIP(launch_gemm(a, EPI_F32, nl, st, QC_SITE_ADA));
+  QC_HIP(launch_gemm(adaln_args(ctx, l0, r0, rows, gates_only), EPI_F32, nl, st, QC_SITE_ADA));
   return QC_OK;
 }
 
@@ -861,14 +865,32 @@ static int prepare_window(qc_ctx *ctx, const int32_t *t, int nw, const int32_t *
   return run_adaln(ctx, 0, L, 0, rows, gates_only, st);
 }
 
-// The x-dependent part of the network on one sub-batch (rows b0 .. b0+nb of the effective batch) in three
-// pieces, so that the caller can interleave the launches of several sub-batches: the patch embedding ...
 // The token tensor of the network-level calls: float32, or bfloat16 in the reduced-precision variant (the same
 // buffer, half used); element offset -> address.
 static void *tokens_at(qc_ctx *ctx, size_t elem) {
   return reinterpret_cast<char *>(ctx->tokens) + elem * (ctx->stream_bf16 ? 2 : 4);
 }
 
+static int choose_lanes(const qc_ctx *ctx, int B);
+
+// The same for one step of the latents x; *embedded: whether their tokens are formed already (denoise_head is not called then).
+static int prepare_step(qc_ctx *ctx, const float *x, int32_t t, const int32_t *labels, int n_labels, int B, bool gates_only, bool *embedded,
+                        hipStream_t st) {
+  const int D = ctx->D, M = B * ctx->T;
+  // (the halves of a larger batch embed their own tokens, on their own streams)
+  *embedded = choose_lanes(ctx, B) == 1 && step_cond_covers(B, ctx->d.freq_dim, ctx->C, ctx->d.patch, D, M);
+  if (!*embedded) return prepare_window(ctx, &t, 1, labels, n_labels, B, gates_only, st);
+  const EmbedSrc e{x, ctx->patch_w, ctx->patch_b, ctx->pos, n_labels, ctx->C, ctx->d.latent_h, ctx->d.latent_w, ctx->d.patch};
+  QC_HIP(launch_step_time(t, ctx->t_w1, ctx->t_b1, ctx->h1, ctx->d.freq_dim, e, ctx->tokens, ctx->stream_bf16, B, D, st));
+  QC_HIP(launch_step_cond(ctx->h1, ctx->t_w2, ctx->t_b2, ctx->label_table, labels, n_labels, ctx->d.num_classes, B, D, ctx->cond, ctx->dev_flags,
+                          ctx->L, ctx->dev_qp + QC_SITE_ADA, QC_NUM_SITES, ctx->silu_q, (size_t)ctx->win_rows * D, st));
+  QC_PROF(QC_K_ADALN);
+  QC_HIP(launch_step_mod(ctx->cond, ctx->fada_w, ctx->fada_b, ctx->fmod, B, D, adaln_args(ctx, 0, 0, B, gates_only), ctx->L, st));
+  return QC_OK;
+}
+
+// The x-dependent part of the network on one sub-batch (rows b0 .. b0+nb of the effective batch) in three
+// pieces, so that the caller can interleave the launches of several sub-batches: the patch embedding ...
 static int denoise_head(qc_ctx *ctx, const float *x, int n_labels, const Sub &sb, hipStream_t st) {
   const int D = ctx->D;
   QC_HIP(launch_embed(x, ctx->patch_w, ctx->patch_b, ctx->pos, tokens_at(ctx, (size_t)sb.b0 * ctx->T * D), ctx->stream_bf16,
@@ -949,7 +971,7 @@ static Sub lane_part(int B, int w, int i, int n) {
 // One denoiser evaluation on forked lanes whose conditioning sits in slot `w` of the prepared window.  sched (optional,
 // [L][2], 1 = recompute) decides per (block, module) instead of `mode`.
 static int denoise_on_lanes(qc_ctx *ctx, const float *x, int n_labels, int B, int mode, int w, float *eps_out, const Lanes &on,
-                            const unsigned char *sched) {
+                            const unsigned char *sched, bool embedded = false) {
   bool mixed = false;
   if (sched) {
     int n_full = 0;
@@ -964,7 +986,7 @@ static int denoise_on_lanes(qc_ctx *ctx, const float *x, int n_labels, int B, in
   Sub sub[MAX_LANES];
   for (int i = 0; i < on.n; ++i) sub[i] = lane_part(B, w, i, on.n);
   int rc = QC_OK;
-  for (int i = 0; i < on.n && !rc; ++i) rc = denoise_head(ctx, x, n_labels, sub[i], on.s[i]);
+  for (int i = 0; i < on.n && !rc && !embedded; ++i) rc = denoise_head(ctx, x, n_labels, sub[i], on.s[i]);
   if (mode == QC_FULL || mixed)
     for (int l = 0; l < ctx->L && !rc; ++l)
       for (int i = 0; i < on.n && !rc; ++i)
@@ -982,11 +1004,11 @@ static int denoise_on_lanes(qc_ctx *ctx, const float *x, int n_labels, int B, in
 
 // the same between a fork and a join
 static int denoise_impl(qc_ctx *ctx, const float *x, int n_labels, int B, int mode, int w, float *eps_out, hipStream_t st,
-                        const unsigned char *sched = nullptr, int max_lanes = MAX_LANES) {
+                        const unsigned char *sched = nullptr, int max_lanes = MAX_LANES, bool embedded = false) {
   Lanes on;
   int rc = fork_lanes(ctx, std::min(choose_lanes(ctx, B), max_lanes), B, st, &on);
   if (rc) return rc;
-  rc = denoise_on_lanes(ctx, x, n_labels, B, mode, w, eps_out, on, sched);
+  rc = denoise_on_lanes(ctx, x, n_labels, B, mode, w, eps_out, on, sched, embedded);
   const int rj = join_lanes(ctx, on, st);      // also after an error: the internal streams never run past the caller's unobserved
   return rc ? rc : rj;
 }
@@ -1012,10 +1034,10 @@ int qc_denoise(qc_ctx *ctx, const float *x, int t, const int32_t *labels, int n_
   if (t < 0) QC_FAIL(QC_ERR_RANGE, "timestep must be non-negative");
   hipStream_t st = static_cast<hipStream_t>(stream);
   const SideCall call(ctx, st);
-  const int32_t t32 = t;
-  rc = prepare_window(ctx, &t32, 1, labels, n_labels, B, mode == QC_CACHED, st);
+  bool embedded;
+  rc = prepare_step(ctx, x, t, labels, n_labels, B, mode == QC_CACHED, &embedded, st);
   if (rc) return rc;
-  return denoise_impl(ctx, x, n_labels, B, mode, 0, eps_out, st);
+  return denoise_impl(ctx, x, n_labels, B, mode, 0, eps_out, st, nullptr, MAX_LANES, embedded);
 }
 
 static int step_mode(const qc_ctx *ctx, int step_index, int force_mode) {
@@ -1041,9 +1063,9 @@ static int solver_update(qc_ctx *ctx, float *x, int b0, int nb, double abar_t, d
 
 // One sampler step whose conditioning sits in slot w of the prepared window: denoiser, CFG, DDIM update, VC.
 static int sample_step_prepared(qc_ctx *ctx, float *x, int B, int mode, int w, double abar_t, double abar_prev, float cfg_scale,
-                                const float *K_t, hipStream_t st, const unsigned char *sched = nullptr) {
+                                const float *K_t, hipStream_t st, const unsigned char *sched = nullptr, bool embedded = false) {
   const int Beff = cfg_scale > 0.0f ? 2 * B : B;
-  const int rc = denoise_impl(ctx, x, B, Beff, mode, w, ctx->eps, st, sched);
+  const int rc = denoise_impl(ctx, x, B, Beff, mode, w, ctx->eps, st, sched, MAX_LANES, embedded);
   return rc ? rc : solver_update(ctx, x, 0, B, abar_t, abar_prev, cfg_scale, K_t, st);
 }
 
@@ -1062,10 +1084,10 @@ int qc_sample_step(qc_ctx *ctx, float *x, const int32_t *labels, int B, int step
   const int mode = sched ? QC_FULL : step_mode(ctx, step_index, force_mode);   // with a schedule the per-module check is in the denoiser
   int rc = check_denoise(ctx, x, labels, B, Beff, mode);
   if (rc) return rc;
-  const int32_t t32 = t;
-  rc = prepare_window(ctx, &t32, 1, labels, B, Beff, !sched && mode == QC_CACHED, st);
+  bool embedded;
+  rc = prepare_step(ctx, x, t, labels, B, Beff, !sched && mode == QC_CACHED, &embedded, st);
   if (rc) return rc;
-  return sample_step_prepared(ctx, x, B, mode, 0, abar_t, abar_prev, cfg_scale, K_t, st, sched);
+  return sample_step_prepared(ctx, x, B, mode, 0, abar_t, abar_prev, cfg_scale, K_t, st, sched, embedded);
 }
 
 int qc_sample(qc_ctx *ctx, float *x, const int32_t *labels, int B, int steps, float cfg_scale, const float *K, void *stream) {

@@ -183,6 +183,22 @@ hipError_t launch_cond_silu(const float *te, const float *table, const int32_t *
                             hipStream_t st);
 hipError_t launch_embed(const float *x, const float *pw, const float *pb, const float *pos, void *tok, int tok_bf16, int B,
                         int n_src, int C, int H, int W, int p, int D, int b_off, hipStream_t st);
+// The latents that tokens are embedded from: batch element b reads latent b % n_src of x, [C, H, W] each, in patches of p x p
+struct EmbedSrc {
+  const float *x, *pw, *pb, *pos;
+  int n_src, C, H, W, p;
+};
+// Conditioning of one timestep and a few rows in three launches: whether they cover a call of B rows and M tokens; the hidden layer of
+// the timestep MLP beside the patch embedding; its output, c and the codes of SiLU(c); the adaLN projections of nz blocks (a: as for
+// launch_gemm) beside the final layer's modulation
+bool step_cond_covers(int B, int freq_dim, int C, int p, int D, int M);
+hipError_t launch_step_time(int t, const float *w1, const float *b1, float *h1, int freq_dim, const EmbedSrc &e, void *tok, int tok_bf16, int B,
+                            int D, hipStream_t st);
+hipError_t launch_step_cond(const float *h1, const float *w2, const float *b2, const float *table, const int32_t *labels, int n_labels,
+                            int null_label, int B, int D, float *c, int *flags, int L, const QParam *qp, int qp_stride, int8_t *q,
+                            size_t l_stride, hipStream_t st);
+hipError_t launch_step_mod(const float *cond, const float *fw, const float *fb, float *fmod, int B, int D, const GemmArgs &a, int nz,
+                           hipStream_t st);
 hipError_t launch_final(const void *tok, int tok_bf16, const float *fmod, const float *fw, const float *fb, float *eps, int B,
                         int C, int H, int W, int p, int D, hipStream_t st);
 hipError_t launch_cache_store(const float *src, void *dst, size_t n, bool bf16, hipStream_t st);

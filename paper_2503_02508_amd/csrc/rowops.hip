@@ -2,7 +2,7 @@
 // LayerNorm + adaLN modulation + quantise, conditioning, patch embedding, final
 // layer, cache store / reuse, DDIM update + variance compensation.
 // One wavefront is 64 lanes; row reductions use cross-lane shuffles only.
-#include "qc_internal.h"
+#include "gemm_i8_epilogue.h"
 
 namespace qc {
 
@@ -403,13 +403,13 @@ __device__ __forceinline__ float time_embed_value(int t, int k, int dim) {
   return (float)(k < half ? cos(a) : sin(a));
 }
 
-template <int R, int NIT>
-__global__ __launch_bounds__(256) void small_linear_kernel(const float *__restrict__ x, int ldx, int t_first, int t_step,
-                                                           const float *__restrict__ W, const float *__restrict__ bias,
-                                                           float *__restrict__ y, int ldy, int B, int N, int K, int act_in, int act_out) {
-  extern __shared__ double xs[];                  // [R][K]
+// 256 threads; xs: [R][K] of LDS; out(row, n, value) takes a result (in one lane)
+template <int R, int NIT, typename Out>
+__device__ __forceinline__ void small_linear_tile(double *xs, int bx, int by, const float *__restrict__ x, int ldx, int t_first, int t_step,
+                                                  const float *__restrict__ W, const float *__restrict__ bias, int B, int N, int K,
+                                                  int act_in, int act_out, const Out &out) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int b0 = blockIdx.y * R, n0 = blockIdx.x * 16 + wave * 4;
+  const int b0 = by * R, n0 = bx * 16 + wave * 4;
   // weights first: they do not depend on the inputs
   float4 w4[NIT][4];
 #pragma unroll
@@ -469,9 +469,19 @@ __global__ __launch_bounds__(256) void small_linear_kernel(const float *__restri
   if ((lane & (64 / V - 1)) == 0 && b0 + r < B && n < N) {
     t += bias ? (double)bias[n] : 0.0;
     if (act_out == 1) t = silu_d(t);
-    y[(size_t)(b0 + r) * ldy + n] = (float)t;
+    out(b0 + r, n, (float)t);
   }
 }
+
+template <int R, int NIT>
+__global__ __launch_bounds__(256) void small_linear_kernel(const float *__restrict__ x, int ldx, int t_first, int t_step,
+                                                           const float *__restrict__ W, const float *__restrict__ bias,
+                                                           float *__restrict__ y, int ldy, int B, int N, int K, int act_in, int act_out) {
+  extern __shared__ double xs[];                  // [R][K]
+  small_linear_tile<R, NIT>(xs, blockIdx.x, blockIdx.y, x, ldx, t_first, t_step, W, bias, B, N, K, act_in, act_out,
+                            [&](int b, int n, float v) { y[(size_t)b * ldy + n] = v; });
+}
+
 
 template <int R, int NIT>
 static hipError_t launch_small_linear_as(const float *x, int ldx, int t_first, int t_step, const float *W, const float *b, float *y, int ldy,
@@ -550,12 +560,11 @@ hipError_t launch_cond_silu(const float *te, const float *table, const int32_t *
 // per workgroup re-read 74 KB of weights for every 4.6 KB written (177 us at 32768 tokens of 1152, now 90).
 // Float64 dot products in ascending f, rounded once when the token is stored.
 template <int TPW>
-__global__ __launch_bounds__(512) void embed16_kernel(const float *__restrict__ x, const float *__restrict__ pw, const float *__restrict__ pb,
-                                                      const float *__restrict__ pos, void *__restrict__ tok, int tok_bf16, int n_src, int C,
-                                                      int H, int W, int p, int D, int b_off, int M) {
+__device__ __forceinline__ void embed16_tile(double (*patch)[16], int block, const float *__restrict__ x, const float *__restrict__ pw,
+                                             const float *__restrict__ pb, const float *__restrict__ pos, void *__restrict__ tok, int tok_bf16,
+                                             int n_src, int C, int H, int W, int p, int D, int b_off, int M) {
   constexpr int F = 16;
-  __shared__ double patch[TPW][F];
-  const int gw = W / p, T = (H / p) * gw, m0 = blockIdx.x * TPW;
+  const int gw = W / p, T = (H / p) * gw, m0 = block * TPW;
   for (int i = threadIdx.x; i < TPW * F; i += blockDim.x) {
     const int m = min(m0 + i / F, M - 1), f = i % F, b = m / T, t = m % T;
     const int c = f / (p * p), ph = (f / p) % p, pq = f % p;
@@ -594,6 +603,14 @@ __global__ __launch_bounds__(512) void embed16_kernel(const float *__restrict__ 
                               (float)((acc[2] + bn[2]) + (double)ps.z), (float)((acc[3] + bn[3]) + (double)ps.w)), tok_bf16);
     ps = ps_next;
   }
+}
+
+template <int TPW>
+__global__ __launch_bounds__(512) void embed16_kernel(const float *__restrict__ x, const float *__restrict__ pw, const float *__restrict__ pb,
+                                                      const float *__restrict__ pos, void *__restrict__ tok, int tok_bf16, int n_src, int C,
+                                                      int H, int W, int p, int D, int b_off, int M) {
+  __shared__ double patch[TPW][16];
+  embed16_tile<TPW>(patch, blockIdx.x, x, pw, pb, pos, tok, tok_bf16, n_src, C, H, W, p, D, b_off, M);
 }
 
 // Any other number of patch features: one token per workgroup.
@@ -656,6 +673,189 @@ hipError_t launch_embed(const float *x, const float *pw, const float *pb, const 
   }
   hipLaunchKernelGGL(embed_kernel, dim3(B * T), dim3(256), 0, st, x, pw, pb, pos, tok, tok_bf16, n_src, C, H, W, p, D, b_off);
   return hipGetLastError();
+}
+
+// ------------------------------------------------- conditioning of one step, few rows
+// A caller that drives the sampler step by step has one timestep and a few latents a call, and every launch in front of the
+// first block is as short as launches get (4.4 us, one after the other).  So what does not depend on each other shares a launch:
+//   step_time_kernel   hidden layer of the timestep MLP | patch embedding of all tokens
+//   step_cond_kernel   its output layer, with the label's row added, and the codes of SiLU(c) for every block
+//   step_mod_kernel    adaLN projections of all blocks | modulation of the final layer
+// instead of six.  DiT-S/2 block, 1 latent, a refreshed and a cached step: 24 launches, 104 us -> 18, 86 us.  Each part's
+// arithmetic is that of its kernel of many rows.
+constexpr int STEP_ROWS = 8;                      // rows of conditioning at most
+
+template <int TPW>
+__global__ __launch_bounds__(512) void step_time_kernel(int nb_time, int t, const float *__restrict__ w1, const float *__restrict__ b1, float *__restrict__ h1,
+                                                        int K, const float *__restrict__ x, const float *__restrict__ pw,
+                                                        const float *__restrict__ pb, const float *__restrict__ pos, void *__restrict__ tok,
+                                                        int tok_bf16, int n_src, int C, int H, int W, int p, int D, int M) {
+  __shared__ double xs[256];
+  __shared__ double patch[TPW][16];
+  if ((int)blockIdx.x < nb_time) {
+    if (threadIdx.x >= 256) return;               // whole wavefronts
+    small_linear_tile<1, 1>(xs, blockIdx.x, 0, nullptr, 0, t, 0, w1, b1, 1, D, K, 0, 1, [&](int, int n, float v) { h1[n] = v; });
+  } else {
+    embed16_tile<TPW>(patch, blockIdx.x - nb_time, x, pw, pb, pos, tok, tok_bf16, n_src, C, H, W, p, D, 0, M);
+  }
+}
+
+// one workgroup = 16 features of every row
+template <int NIT>
+__global__ __launch_bounds__(256) void step_cond_kernel(const float *__restrict__ h1, const float *__restrict__ w2, const float *__restrict__ b2,
+                                                        const float *__restrict__ table, const int32_t *__restrict__ labels, int n_labels,
+                                                        int null_label, int B, int D, float *__restrict__ c, int *__restrict__ flags, int L,
+                                                        const QParam *qp, int qp_stride, int8_t *__restrict__ q, size_t l_stride) {
+  extern __shared__ double xs[];                  // [D]
+  __shared__ float te[16], vs[STEP_ROWS][16];
+  const int n0 = blockIdx.x * 16;
+  small_linear_tile<1, NIT>(xs, blockIdx.x, 0, h1, D, 0, 0, w2, b2, 1, D, D, 0, 0, [&](int, int n, float v) { te[n - n0] = v; });
+  __syncthreads();
+  if ((int)threadIdx.x < 16 * B) {
+    const int b = threadIdx.x >> 4, j = threadIdx.x & 15;
+    int y = b < n_labels ? labels[b] : null_label;
+    if (y < 0 || y > null_label) {                // as in cond_silu_kernel
+      if (n0 + j == 0) atomicOr(flags, 1);
+      y = min(max(y, 0), null_label);
+    }
+    const float cv = te[j] + table[(size_t)y * D + n0 + j];
+    c[(size_t)b * D + n0 + j] = cv;
+    vs[b][j] = (float)silu_d((double)cv);
+  }
+  __syncthreads();
+  // four codes at a time: thread = (block and row, quarter of the 16 features)
+  const int f = (threadIdx.x & 3) * 4;
+  for (int i = threadIdx.x >> 2; i < L * B; i += 64) {
+    const int l = i / B, b = i - l * B;
+    const QParam t = qp[(size_t)l * qp_stride];
+    const float *v = vs[b] + f;
+    *(unsigned *)(q + (size_t)l * l_stride + (size_t)b * D + n0 + f) =
+        pack4(quant_code(v[0], t.s, t.z), quant_code(v[1], t.s, t.z), quant_code(v[2], t.s, t.z), quant_code(v[3], t.s, t.z));
+  }
+}
+
+// The adaLN part: a wavefront takes eight output columns at a time, eight lanes each, 16 bytes of codes per lane and load (whole
+// cache lines of a weight row), four-product integer dot instructions, and the eight lanes' sums meet in DPP moves.  One pass over
+// the weights whatever the number of rows, bound by their bytes (223 MB for the 28 blocks of DiT-XL/2, a third of that in a cached step):
+// with all three kernels a refreshed step of 1 latent of 256 tokens takes 1643 -> 1620 us, a cached one 79 -> 59; 8 latents of 16
+// tokens cached 91 -> 72.  R rows at once there, RF at once in the final layer's part (whose inputs lie in LDS as
+// float64); NI: loads of 128 bytes a weight row.
+template <int R, int RF, int NIT, int NI, bool W4>
+__global__ __launch_bounds__(256) void step_mod_kernel(int nb_final, const float *__restrict__ cond, const float *__restrict__ fw,
+                                                       const float *__restrict__ fb, float *__restrict__ fmod, int B, int D, int nb_ada, GemmArgs p) {
+  extern __shared__ double xs[];                  // [RF][D]
+  if ((int)blockIdx.x < nb_final) {
+    const int tiles = (2 * D + 15) / 16, by = blockIdx.x / tiles;
+    small_linear_tile<RF, NIT>(xs, blockIdx.x - by * tiles, by, cond, D, 0, 0, fw, fb, B, 2 * D, D, 1, 0,
+                              [&](int b, int n, float v) { fmod[(size_t)b * 2 * D + n] = v; });
+    return;
+  }
+  const int bi = blockIdx.x - nb_final, z = bi / nb_ada, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ncover = p.sel_D ? 2 * p.sel_D : p.N;
+  const int j = (bi - z * nb_ada) * 32 + wave * 8 + (lane >> 3), c = lane & 7;
+  const int n = map_col(min(j, ncover - 1), p.sel_D);
+  const unsigned char *w = (const unsigned char *)p.W + (size_t)z * p.zs_W + (size_t)n * (W4 ? p.K >> 1 : p.K);
+  const int8_t *act = p.A + (size_t)z * p.zs_A;
+  typedef typename std::conditional<W4, v2i, v4i>::type wload_t;
+  wload_t wv[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int k = min((8 * i + c) * 16, p.K - 16);
+    wv[i] = *(const wload_t *)(w + (W4 ? k >> 1 : k));
+  }
+  int acc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] = 0;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    v4i v;
+    if constexpr (W4) v = unpack_w4(wv[i]);
+    else v = wv[i];
+    const int k = (8 * i + c) * 16;
+    if (k >= p.K) v = (v4i){0, 0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const v4i x = *(const v4i *)(act + (size_t)min(r, B - 1) * p.lda + min(k, p.K - 16));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[r] = __builtin_amdgcn_sdot4(x[e], v[e], acc[r], false);
+    }
+  }
+  // the eight lanes of a column: neighbours, the other pair, the other quad of the half row
+  int sum = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    int a = acc[r];
+    a += __builtin_amdgcn_update_dpp(0, a, 0xB1, 0xF, 0xF, false);
+    a += __builtin_amdgcn_update_dpp(0, a, 0x4E, 0xF, 0xF, false);
+    a += __builtin_amdgcn_update_dpp(0, a, 0x141, 0xF, 0xF, false);
+    if (c == r) sum = a;
+  }
+  if (c >= B || j >= ncover) return;              // lane c finishes row c
+  const QParam q = p.a_qp[(size_t)z * p.zs_qp];
+  const size_t at = (size_t)z * p.zs_vecN + n;
+  const double sc = (double)q.s * (double)p.w_scale[at];
+  p.y[(size_t)z * p.zs_out + (size_t)c * p.ldy + n] = dequant_f32(sc, sum - q.z * p.wsum[at], p.bias ? (double)p.bias[at] : 0.0);
+}
+
+// Whether the three kernels cover a call: one timestep, a few rows, and few enough tokens that embedding them takes no longer than the
+// linear beside it.
+bool step_cond_covers(int B, int freq_dim, int C, int p, int D, int M) {
+  return B <= STEP_ROWS && freq_dim <= 256 && freq_dim % 4 == 0 && C * p * p == 16 && D <= 2048 && M <= 2048;
+}
+
+hipError_t launch_step_time(int t, const float *w1, const float *b1, float *h1, int freq_dim, const EmbedSrc &e, void *tok, int tok_bf16, int B,
+                            int D, hipStream_t st) {
+  const int M = B * (e.H / e.p) * (e.W / e.p), nb_time = (D + 15) / 16;
+  const int threads = std::max(256, (D / 4 + 63) / 64 * 64);
+#define QC_STEP_TIME(TPW)                                                                                                                  \
+  hipLaunchKernelGGL(step_time_kernel<TPW>, dim3(nb_time + (M + TPW - 1) / TPW), dim3(threads), 0, st, nb_time, t, w1, b1, h1, freq_dim, e.x, \
+                     e.pw, e.pb, e.pos, tok, tok_bf16, e.n_src, e.C, e.H, e.W, e.p, D, M)
+  if (M >= 2 * 512) QC_STEP_TIME(2);
+  else QC_STEP_TIME(1);
+#undef QC_STEP_TIME
+  return hipGetLastError();
+}
+
+hipError_t launch_step_cond(const float *h1, const float *w2, const float *b2, const float *table, const int32_t *labels, int n_labels,
+                            int null_label, int B, int D, float *c, int *flags, int L, const QParam *qp, int qp_stride, int8_t *q,
+                            size_t l_stride, hipStream_t st) {
+#define QC_STEP_COND(NIT)                                                                                                               \
+  hipLaunchKernelGGL(step_cond_kernel<NIT>, dim3(D / 16), dim3(256), (size_t)D * sizeof(double), st, h1, w2, b2, table, labels, n_labels, \
+                     null_label, B, D, c, flags, L, qp, qp_stride, q, l_stride)
+  if (D <= 256) QC_STEP_COND(1);
+  else if (D <= 512) QC_STEP_COND(2);
+  else if (D <= 1280) QC_STEP_COND(5);
+  else QC_STEP_COND(8);
+#undef QC_STEP_COND
+  return hipGetLastError();
+}
+
+template <int R, int RF, int NIT, int NI>
+static hipError_t launch_step_mod_as(const float *cond, const float *fw, const float *fb, float *fmod, int B, int D, const GemmArgs &a, int nz,
+                                     hipStream_t st) {
+  const int nb_final = (2 * D + 15) / 16 * ((B + RF - 1) / RF), nb_ada = ((a.sel_D ? 2 * a.sel_D : a.N) + 31) / 32;
+  const dim3 grid(nb_final + nb_ada * nz);
+  const size_t smem = (size_t)RF * D * sizeof(double);           // 64 KB at most
+  if (a.w4) hipLaunchKernelGGL((step_mod_kernel<R, RF, NIT, NI, true>), grid, dim3(256), smem, st, nb_final, cond, fw, fb, fmod, B, D, nb_ada, a);
+  else hipLaunchKernelGGL((step_mod_kernel<R, RF, NIT, NI, false>), grid, dim3(256), smem, st, nb_final, cond, fw, fb, fmod, B, D, nb_ada, a);
+  return hipGetLastError();
+}
+
+template <int R, int RF>
+static hipError_t launch_step_mod_rows(const float *cond, const float *fw, const float *fb, float *fmod, int B, int D, const GemmArgs &a, int nz,
+                                       hipStream_t st) {
+  if (D <= 256) return launch_step_mod_as<R, RF, 1, 2>(cond, fw, fb, fmod, B, D, a, nz, st);
+  if (D <= 512) return launch_step_mod_as<R, RF, 2, 4>(cond, fw, fb, fmod, B, D, a, nz, st);
+  if (D <= 1280) return launch_step_mod_as<R, RF, 5, 10>(cond, fw, fb, fmod, B, D, a, nz, st);
+  return launch_step_mod_as<R, RF, 8, 16>(cond, fw, fb, fmod, B, D, a, nz, st);
+}
+
+hipError_t launch_step_mod(const float *cond, const float *fw, const float *fb, float *fmod, int B, int D, const GemmArgs &a, int nz,
+                           hipStream_t st) {
+  if (B <= 1) return launch_step_mod_rows<1, 1>(cond, fw, fb, fmod, B, D, a, nz, st);
+  if (B <= 2) return launch_step_mod_rows<2, 2>(cond, fw, fb, fmod, B, D, a, nz, st);
+  if (B <= 4) return launch_step_mod_rows<4, 4>(cond, fw, fb, fmod, B, D, a, nz, st);
+  return launch_step_mod_rows<8, 4>(cond, fw, fb, fmod, B, D, a, nz, st);
 }
 
 // ---------------------------------------------------------------- final layer

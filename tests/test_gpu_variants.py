@@ -370,3 +370,29 @@ def test_conditioning_embedding_and_final_layer(model, B):
     want = dit.denoiser(lat.astype(np.float64), np.full(B, 333), lab, model, w, lin, {}, True)
     assert_close(eps.cpu().numpy(), want, "eps")
     ctx.close()
+
+
+@pytest.mark.parametrize("model,wb,B,cfg", [
+    (replace(_net(2048, 32, 2048, 6, 6), depth=2), 8, 4, 1.5),        # widest row, 8 rows of conditioning
+    (replace(_net(272, 4, 544, 6, 10), depth=3), 4, 3, 0.0),          # 272 = 2 * 128 + 16: the last load of a weight row is 16 bytes
+    (replace(_net(16, 1, 32, 4, 4), depth=9), 8, 5, 0.0),             # one group of 16 features; more codes than threads
+    (replace(_net(384, 6, 512, 66, 62), depth=1), 4, 1, 1.5),         # 2046 tokens: two to a workgroup of the embedding
+    (replace(_net(1152, 16, 1152, 10, 14), depth=2), 8, 1, 0.0)])
+def test_single_steps_equal_a_window_of_steps(model, wb, B, cfg):
+    """The conditioning of one step (three launches with several parts each) against that of all steps at once."""
+    import torch
+    import paper_2503_02508_amd as qc
+    from qc_testlib import make_pair, oracle_calibration
+    model = replace(model, weight_bits=wb)
+    w = I.make_weights(model, 41)
+    lat, lab = I.make_latents(B, model, 42), I.make_labels(B, model, 43)
+    qp, _, _ = oracle_calibration(model, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    _, ctx = make_pair(model, w, qp, 2 * B if cfg else B, 2)
+    K = _cuda(I.make_vc_factors(4, model.latent_c, 44))
+    whole, single, labels = _cuda(lat), _cuda(lat), _cuda(lab.astype(np.int32))
+    ctx.sample(whole, labels, 4, cfg, K)
+    for i, (t, at, ap) in enumerate(zip(*qc.qc_ddim_schedule(4))):
+        ctx.sample_step(single, labels, i, t, at, ap, cfg, K[i])
+    assert torch.equal(whole, single)
+    assert float((whole - _cuda(lat)).abs().max()) > 0
+    ctx.close()
