@@ -111,12 +111,13 @@ def _chk(rc):
 
 
 def _p(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()          # argtypes makes it a pointer
 
 
 def _stream():
+    # torch.cuda.current_stream().cuda_stream, without the Stream object around it
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 # ---------------------------------------------------------------- single ops
