@@ -21,6 +21,8 @@ constexpr int NUM_SIDE = 3;
 constexpr int WINDOW_ROWS = 512;
 // token rows of one group of the un-quantised forward
 constexpr size_t CAL_ROWS = 1024;
+// rows of conditioning whose adaLN projections the un-quantised forward makes at once (one group of samples at least)
+constexpr size_t CAL_MOD_ROWS = 8;
 
 // a contiguous range of the (effective) batch handled by one stream; `lane` picks its private scratch
 struct Sub {
@@ -106,8 +108,8 @@ struct qc_ctx {
   bool keep_qkv_f32 = false;
   bool stream_bf16 = false;   // the network-level calls keep the residual stream (tokens) as bfloat16
   // scratch of the un-quantised forward (calibration, VC fit), which runs cal_group samples at a time
-  int cal_group;
-  float *cal_h, *cal_o, *cal_a, *cal_u, *cal_mod, *cal_cond;
+  int cal_group, cal_mod_rows;
+  float *cal_h, *cal_o, *cal_u, *cal_mod, *cal_cond;
   int *cal_slots, *cal_label;
   bool weights_loaded;
   // a denoiser call may run its batch as up to MAX_LANES independent sub-batches on internal streams
@@ -230,8 +232,8 @@ static size_t layout(const qc_model_desc &d, int max_batch, char *base, qc_ctx *
   // The un-quantised forward takes as many samples at once as make CAL_ROWS token rows (at least one): its products then
   // read the float32 weights once per group
   const size_t G = std::max<size_t>(1, std::min<size_t>(B, CAL_ROWS / T)), GT = G * T;
-  float *cal_h = a.take<float>(GT * D), *cal_o = a.take<float>(GT * D), *cal_a = a.take<float>(GT * D);
-  float *cal_u = a.take<float>(GT * R), *cal_mod = a.take<float>(G * 6 * D), *cal_cond = a.take<float>(G * D);
+  float *cal_h = a.take<float>(GT * D), *cal_o = a.take<float>(GT * D);
+  float *cal_u = a.take<float>(GT * R), *cal_mod = a.take<float>(L * std::max(G, CAL_MOD_ROWS) * 6 * D), *cal_cond = a.take<float>(G * D);
   int *cal_slots = a.take<int>(L * QC_NUM_SITES * 2), *cal_label = a.take<int>(G);
   float *eps_ref = a.take<float>(B * C * d.latent_h * d.latent_w);
   double *vcfit_work = a.take<double>(B * C * 2);
@@ -241,8 +243,8 @@ static size_t layout(const qc_model_desc &d, int max_batch, char *base, qc_ctx *
     c->label_table = label_table; c->fada_w = fada_w; c->fada_b = fada_b; c->flin_w = flin_w; c->flin_b = flin_b;
     c->dev_qp = dev_qp; c->cache = cache; c->h1 = h1; c->te = te; c->cond = cond; c->mod = mod; c->fmod = fmod;
     c->tokens = tokens; c->qkv = qkv; c->eps = eps; c->silu_q = silu_q; c->qa_ln = qa_ln; c->qa_attn = qa_attn;
-    c->qa_mlp = qa_mlp; c->cal_h = cal_h; c->cal_o = cal_o; c->cal_a = cal_a; c->cal_u = cal_u; c->cal_mod = cal_mod;
-    c->cal_cond = cal_cond; c->cal_group = (int)G;
+    c->qa_mlp = qa_mlp; c->cal_h = cal_h; c->cal_o = cal_o; c->cal_u = cal_u; c->cal_mod = cal_mod;
+    c->cal_cond = cal_cond; c->cal_group = (int)G; c->cal_mod_rows = (int)std::max(G, CAL_MOD_ROWS);
     c->cal_slots = cal_slots; c->cal_label = cal_label; c->eps_ref = eps_ref; c->vcfit_work = vcfit_work; c->dev_flags = dev_flags;
     c->qkv_hm = qkv_hm; c->qkv_part_stride = (long long)part;
     c->qkv_hm_bytes = (2 * part + vpart) * sizeof(float); c->DP = (int)DP; c->Tp = (int)Tp;
@@ -1172,41 +1174,57 @@ static inline float ord2f(int i) {
 
 }  // extern "C"
 
+// The adaLN projections of every block for `rows` conditioning vectors (cal_mod_rows at most): cal_mod[l, r, :], cal_mod_rows rows a block.
+static int fp32_mods(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int rows, hipStream_t st) {
+  const int D = ctx->D;
+  const size_t stride = (size_t)ctx->cal_mod_rows * 6 * D;
+  for (int l = 0; l < ctx->L; l += BLOCK_LINEARS) {
+    BlockLinears b{};
+    const int n = std::min(BLOCK_LINEARS, ctx->L - l);
+    for (int i = 0; i < n; ++i) {
+      b.W[i] = w->blocks[l + i].ada_w;
+      b.b[i] = w->blocks[l + i].ada_b;
+    }
+    QC_HIP(launch_block_linears(b, n, cond, ctx->cal_mod + l * stride, stride, rows, 6 * D, D, st));
+  }
+  return QC_OK;
+}
+
 // Block l of the un-quantised fp32 forward on g samples, the first of them b0 of the group that the scratch holds (cond, tokens and o
-// point at the group's first).  With slot != null the min / max of the five quantiser sites are folded into slot[site][2].
-static int fp32_block(qc_ctx *ctx, const qc_block_weights_f32 &b, const float *cond, int b0, int g, int *slot, float *tokens, float *o,
-                      hipStream_t st) {
+// point at the group's first, mod at the block's adaLN projections of the group's first).  With slot != null the min / max of the five
+// quantiser sites are folded into slot[site][2].
+static int fp32_block(qc_ctx *ctx, const qc_block_weights_f32 &b, const float *cond, const float *mod, int b0, int g, int *slot, float *tokens,
+                      float *o, hipStream_t st) {
   const int D = ctx->D, R = ctx->R, T = ctx->T, M = g * T;
   const size_t row0 = (size_t)b0 * T;
-  float *mod = ctx->cal_mod + (size_t)b0 * 6 * D, *x = tokens + row0 * D, *h = ctx->cal_h + row0 * D, *a = ctx->cal_a + row0 * D;
+  float *x = tokens + row0 * D, *h = ctx->cal_h + row0 * D;
   float *u = ctx->cal_u + row0 * R, *qkv = ctx->qkv + row0 * 3 * D;
   cond += (size_t)b0 * D;
+  mod += (size_t)b0 * 6 * D;
   o += row0 * D;
   if (slot) QC_HIP(launch_minmax_silu(cond, (size_t)g * D, slot + 2 * QC_SITE_ADA, st));
-  QC_HIP(launch_small_linear(cond, D, 0, 0, b.ada_w, b.ada_b, mod, 6 * D, g, 6 * D, D, 1, 0, st));
   QC_HIP(launch_ln_mod_quant(x, 0, mod, mod + D, 6 * D, M, D, T, nullptr, nullptr, h, st));
   if (slot) QC_HIP(launch_minmax(h, (size_t)M * D, slot + 2 * QC_SITE_QKV, st));
-  QC_HIP(launch_linear_f32(h, b.qkv_w, b.qkv_b, qkv, M, 3 * D, D, 0, st));
+  QC_HIP(launch_linear_f32(h, b.qkv_w, b.qkv_b, qkv, M, 3 * D, D, 0, nullptr, 0, 1, st));
   QC_HIP(launch_attention(qkv, g, T, ctx->H, ctx->hd, nullptr, nullptr, o, st));
   if (slot) QC_HIP(launch_minmax(o, (size_t)M * D, slot + 2 * QC_SITE_PROJ, st));
-  QC_HIP(launch_linear_f32(o, b.proj_w, b.proj_b, a, M, D, D, 0, st));
-  QC_HIP(launch_cache_reuse(x, 0, a, mod + 2 * D, 6 * D, g, T, D, false, st));
+  QC_HIP(launch_linear_f32(o, b.proj_w, b.proj_b, x, M, D, D, 0, mod + 2 * D, 6 * D, T, st));
   QC_HIP(launch_ln_mod_quant(x, 0, mod + 3 * D, mod + 4 * D, 6 * D, M, D, T, nullptr, nullptr, h, st));
   if (slot) QC_HIP(launch_minmax(h, (size_t)M * D, slot + 2 * QC_SITE_FC1, st));
-  QC_HIP(launch_linear_f32(h, b.fc1_w, b.fc1_b, u, M, R, D, 1, st));
+  QC_HIP(launch_linear_f32(h, b.fc1_w, b.fc1_b, u, M, R, D, 1, nullptr, 0, 1, st));
   if (slot) QC_HIP(launch_minmax(u, (size_t)M * R, slot + 2 * QC_SITE_FC2, st));
-  QC_HIP(launch_linear_f32(u, b.fc2_w, b.fc2_b, a, M, D, R, 0, st));
-  QC_HIP(launch_cache_reuse(x, 0, a, mod + 5 * D, 6 * D, g, T, D, false, st));
+  QC_HIP(launch_linear_f32(u, b.fc2_w, b.fc2_b, x, M, D, R, 0, mod + 5 * D, 6 * D, T, st));
   return QC_OK;
 }
 
 // Un-quantised fp32 forward of g samples through all blocks (the network the quantiser parameters are
 // calibrated on and the reference the VC factors are fitted against): tokens must hold the embedded samples,
 // cond their conditioning vectors [g, D].  With slots != null the min / max of the five quantiser sites of
-// every block are folded into slots[l][site][2].  o: where the attention's output goes; cal_h will do (its last reader, the
+// every block are folded into slots[l][site][2].  The adaLN projections of the samples are rows mod_row .. of cal_mod.  o: where the attention's output goes; cal_h will do (its last reader, the
 // QKV product, is then done) unless the tokens lie in cal_o already.  Two halves of the samples run beside each other, for
 // the same reasons as in choose_lanes.
-static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int g, int *slots, float *tokens, float *o, hipStream_t st) {
+static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int mod_row, int g, int *slots, float *tokens, float *o,
+                       hipStream_t st) {
   const int g0 = (g + 1) / 2;
   int rc = QC_OK;
   hipStream_t side[2] = {st, st};
@@ -1219,8 +1237,9 @@ static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, 
   }
   for (int l = 0; l < ctx->L && !rc; ++l) {
     int *slot = slots ? slots + (size_t)l * QC_NUM_SITES * 2 : nullptr;
-    rc = fp32_block(ctx, w->blocks[l], cond, 0, g0, slot, tokens, o, side[0]);
-    if (!rc && g > g0) rc = fp32_block(ctx, w->blocks[l], cond, g0, g - g0, slot, tokens, o, side[1]);
+    const float *mod = ctx->cal_mod + ((size_t)l * ctx->cal_mod_rows + mod_row) * 6 * ctx->D;
+    rc = fp32_block(ctx, w->blocks[l], cond, mod, 0, g0, slot, tokens, o, side[0]);
+    if (!rc && g > g0) rc = fp32_block(ctx, w->blocks[l], cond, mod, g0, g - g0, slot, tokens, o, side[1]);
   }
   for (int i = 0; i < 2 && g > g0; ++i) {           // also after an error
     QC_HIP(hipEventRecord(ctx->ev_f32_join[i], side[i]));
@@ -1230,8 +1249,9 @@ static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, 
 }
 
 // eps[B] of the un-quantised network with the conditioning vectors in rows r0 .. of cond and fmod; x holds n_src latents, batch
-// element b reads latent b % n_src (guidance runs the same latents with the labels and with the null label).
-static int denoise_f32_prepared(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, int n_src, size_t r0, int B, float *eps_out,
+// element b reads latent b % n_src (guidance runs the same latents with the labels and with the null label).  Their adaLN projections
+// are rows mod_row .. of cal_mod, or are made here (mod_row < 0).
+static int denoise_f32_prepared(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, int n_src, size_t r0, int mod_row, int B, float *eps_out,
                                 float *tokens, float *o, hipStream_t st) {
   const int D = ctx->D;
   const size_t lat = (size_t)ctx->C * ctx->d.latent_h * ctx->d.latent_w;
@@ -1239,7 +1259,8 @@ static int denoise_f32_prepared(qc_ctx *ctx, const qc_weights_f32 *w, const floa
     const int g = std::min(ctx->cal_group, B - b);
     QC_HIP(launch_embed(x, ctx->patch_w, ctx->patch_b, ctx->pos, tokens, 0, g, n_src, ctx->C, ctx->d.latent_h, ctx->d.latent_w,
                         ctx->d.patch, D, b, st));
-    const int rc = fp32_blocks(ctx, w, ctx->cond + (r0 + b) * D, g, nullptr, tokens, o, st);
+    int rc = mod_row < 0 ? fp32_mods(ctx, w, ctx->cond + (r0 + b) * D, g, st) : QC_OK;
+    if (!rc) rc = fp32_blocks(ctx, w, ctx->cond + (r0 + b) * D, mod_row < 0 ? 0 : mod_row + b, g, nullptr, tokens, o, st);
     if (rc) return rc;
     QC_HIP(launch_final(tokens, 0, ctx->fmod + (r0 + b) * 2 * D, ctx->flin_w, ctx->flin_b, eps_out + b * lat, g, ctx->C,
                         ctx->d.latent_h, ctx->d.latent_w, ctx->d.patch, D, st));
@@ -1255,7 +1276,7 @@ static int denoise_f32_impl(qc_ctx *ctx, const qc_weights_f32 *w, const float *x
   const int rc = run_cond(ctx, &t32, 1, labels, n_labels, B, false, st);
   if (rc) return rc;
   QC_HIP(launch_small_linear(ctx->cond, D, 0, 0, ctx->fada_w, ctx->fada_b, ctx->fmod, 2 * D, B, 2 * D, D, 1, 0, st));
-  return denoise_f32_prepared(ctx, w, x, n_src, 0, B, eps_out, ctx->tokens, ctx->cal_o, st);
+  return denoise_f32_prepared(ctx, w, x, n_src, 0, -1, B, eps_out, ctx->tokens, ctx->cal_o, st);
 }
 
 extern "C" {
@@ -1294,7 +1315,8 @@ int qc_calibrate_minmax(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, co
     }
     QC_HIP(launch_embed(x + i * lat, ctx->patch_w, ctx->patch_b, ctx->pos, ctx->tokens, 0, g, g, ctx->C, ctx->d.latent_h,
                         ctx->d.latent_w, ctx->d.patch, D, 0, st));
-    rc = fp32_blocks(ctx, w, ctx->cal_cond, g, ctx->cal_slots, ctx->tokens, ctx->cal_o, st);
+    rc = fp32_mods(ctx, w, ctx->cal_cond, g, st);
+    if (!rc) rc = fp32_blocks(ctx, w, ctx->cal_cond, 0, g, ctx->cal_slots, ctx->tokens, ctx->cal_o, st);
     if (rc) return rc;
     QC_HIP(hipStreamSynchronize(st));        // the labels are the caller's host memory
   }
@@ -1406,7 +1428,7 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
   if (rc) return rc;
   if (!ctx->cache_mask.empty() && steps > ctx->mask_steps)
     QC_FAIL(QC_ERR_RANGE, "%d steps requested but the installed cache schedule has %d", steps, ctx->mask_steps);
-  const int HW = ctx->d.latent_h * ctx->d.latent_w, C = ctx->C;
+  const int HW = ctx->d.latent_h * ctx->d.latent_w, C = ctx->C, D = ctx->D;
   // The un-quantised network never reads anything of the quantised one, which is much shorter and a chain of small launches:
   // the first runs in two halves on two internal streams, its tokens in cal_o, the second in one part on a third, and only the
   // update of x_ref waits for the previous fit.  (The optional row-major copy of Q | K | V lies where the un-quantised network
@@ -1424,11 +1446,19 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
     QC_HIP(hipStreamWaitEvent(rs, ctx->ev_ready, 0));
   }
   float *tokens = beside ? ctx->cal_o : ctx->tokens, *o = beside ? ctx->cal_h : ctx->cal_o;
-  const auto step = [&](int i, int w_slot) -> int {
+  // the un-quantised network's adaLN projections of as many steps at once as cal_mod holds
+  const int mod_steps = ctx->cal_mod_rows / Beff;
+  const auto step = [&](int i, int w_slot, int nw) -> int {
     const double cx = std::sqrt(ap[i] / at[i]);
     const double ce = std::sqrt(1.0 - ap[i]) - cx * std::sqrt(1.0 - at[i]);
     // reference: un-quantised network, every step in full, no VC
-    int r = denoise_f32_prepared(ctx, w, x_ref, B, (size_t)w_slot * Beff, Beff, ctx->eps_ref, tokens, o, rs);
+    int r = QC_OK, mod_row = -1;
+    if (mod_steps > 0) {
+      mod_row = w_slot % mod_steps * Beff;
+      if (mod_row == 0) r = fp32_mods(ctx, w, ctx->cond + (size_t)w_slot * Beff * D, std::min(mod_steps, nw - w_slot) * Beff, rs);
+      if (r) return r;
+    }
+    r = denoise_f32_prepared(ctx, w, x_ref, B, (size_t)w_slot * Beff, mod_row, Beff, ctx->eps_ref, tokens, o, rs);
     if (r) return r;
     if (beside && i > 0) QC_HIP(hipStreamWaitEvent(rs, ctx->ev_fit, 0));
     QC_HIP(launch_ddim_vc(x_ref, ctx->eps_ref, B, C, HW, cx, ce, cfg_scale, nullptr, rs));
@@ -1454,7 +1484,7 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
       QC_HIP(hipEventRecord(ctx->ev_ready, qs));
       QC_HIP(hipStreamWaitEvent(rs, ctx->ev_ready, 0));
     }
-    for (int i = i0; i < i0 + nw && !rc; ++i) rc = step(i, i - i0);
+    for (int i = i0; i < i0 + nw && !rc; ++i) rc = step(i, i - i0, nw);
   }
   if (beside) {                           // also after an error: the caller's stream is never past work that still runs
     QC_HIP(hipEventRecord(ctx->ev_ref, rs));

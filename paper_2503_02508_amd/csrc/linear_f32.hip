@@ -1,5 +1,5 @@
 // float32 linear layers of the un-quantised reference network (calibration, variance-compensation fit):
-// y = act(x W^T + b), every output one chain of float32 fused multiply-adds in ascending k.
+// y = act(x W^T + b) or y += gate * (x W^T + b), every output one chain of float32 fused multiply-adds in ascending k.
 //
 // The chain runs on the matrix cores: v_mfma_f32_16x16x4_f32 adds its four products one after the other, each with the
 // rounding of a fused multiply-add, in ascending k (checked bit by bit against fmaf; the same holds for 32x32x2), so the
@@ -32,7 +32,7 @@ __device__ __forceinline__ float gelu_f(float v) {
 template <int TB, int BK>
 __global__ __launch_bounds__(256, 2) void linear_f32_kernel(const float *__restrict__ x, const float *__restrict__ W,
                                                             const float *__restrict__ bias, float *__restrict__ y, int M, int N, int K,
-                                                            int gelu) {
+                                                            int gelu, const float *__restrict__ gate, int ld_gate, int T) {
   constexpr int R = 32 * TB, NQ = BK / 4, NS = 4;            // rows of either operand, steps of a slab, slab buffers
   constexpr int CH = BK / 4, RP = 256 / CH, NL = R / RP;     // 16-byte chunks of a slab row, rows per pass, passes
   __shared__ __align__(16) float slabs[NS][2][R * BK];
@@ -138,21 +138,24 @@ __global__ __launch_bounds__(256, 2) void linear_f32_kernel(const float *__restr
         if (m < M && n < N) {
           float v = acc[i][j][r] + bs;
           if (gelu) v = gelu_f(v);
-          y[(size_t)m * N + n] = v;
+          float *const at = y + (size_t)m * N + n;
+          if (gate) *at = *at + gate[(size_t)(m / T) * ld_gate + n] * v;      // as cache_reuse_kernel adds a stored v
+          else *at = v;
         }
       }
   }
 }
 
-hipError_t launch_linear_f32(const float *x, const float *W, const float *b, float *y, int M, int N, int K, int gelu, hipStream_t st) {
+hipError_t launch_linear_f32(const float *x, const float *W, const float *b, float *y, int M, int N, int K, int gelu, const float *gate,
+                             int ld_gate, int T, hipStream_t st) {
   if (K % 4 || K < 4) return hipErrorInvalidValue;           // chunks of 16 bytes; the widths of a model are multiples of 16
   // Whole tiles per compute unit, in blocks of 16 x 16 per SIMD.  TB = 2 moves half the bytes per product, which is worth 16 % of a
   // block's time (K = 1152: 5.2 against 6.2 us); TB = 1 divides the work among the compute units more evenly.
   const long long t2 = (long long)((M + 63) / 64) * ((N + 63) / 64), t1 = (long long)((M + 31) / 32) * ((N + 31) / 32);
   if (0.84 * 4.0 * (double)((t2 + 255) / 256) <= (double)((t1 + 255) / 256))
-    hipLaunchKernelGGL((linear_f32_kernel<2, 32>), dim3((unsigned)((t2 + 7) / 8 * 8)), dim3(256), 0, st, x, W, b, y, M, N, K, gelu);
+    hipLaunchKernelGGL((linear_f32_kernel<2, 32>), dim3((unsigned)((t2 + 7) / 8 * 8)), dim3(256), 0, st, x, W, b, y, M, N, K, gelu, gate, ld_gate, T);
   else
-    hipLaunchKernelGGL((linear_f32_kernel<1, 64>), dim3((unsigned)((t1 + 7) / 8 * 8)), dim3(256), 0, st, x, W, b, y, M, N, K, gelu);
+    hipLaunchKernelGGL((linear_f32_kernel<1, 64>), dim3((unsigned)((t1 + 7) / 8 * 8)), dim3(256), 0, st, x, W, b, y, M, N, K, gelu, gate, ld_gate, T);
   return hipGetLastError();
 }
 

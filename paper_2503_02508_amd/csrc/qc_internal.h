@@ -218,8 +218,16 @@ hipError_t launch_attention(const float *qkv, int B, int T, int H, int hd, const
 hipError_t launch_attention_f16(const float *q32, const float *k32, const float *vt32, int B, int T, int Tp, int H, int hd,
                                 int DPv, const QParam *qp, int8_t *q_out, int beside, hipStream_t st);
 // calibration helpers
-hipError_t launch_linear_f32(const float *x, const float *W, const float *b, float *y, int M, int N, int K, int gelu,
-                             hipStream_t st);
+// gate != null: y[m, :] += gate[m / T, :] * (x W^T + b)[m, :]
+hipError_t launch_linear_f32(const float *x, const float *W, const float *b, float *y, int M, int N, int K, int gelu, const float *gate,
+                             int ld_gate, int T, hipStream_t st);
+// one few-rows linear layer per block: y[l, b, :] = W_l silu(x[b, :]) + b_l, l < n <= BLOCK_LINEARS
+constexpr int BLOCK_LINEARS = 32;
+struct BlockLinears {
+  const float *W[BLOCK_LINEARS], *b[BLOCK_LINEARS];
+};
+hipError_t launch_block_linears(const BlockLinears &w, int n, const float *x, float *y, size_t block_stride, int B, int N, int K,
+                                hipStream_t st);
 hipError_t launch_minmax(const float *x, size_t n, int *slot, hipStream_t st);
 hipError_t launch_minmax_silu(const float *x, size_t n, int *slot, hipStream_t st);
 hipError_t launch_fill_i32(int *p, size_t n, int v, hipStream_t st);

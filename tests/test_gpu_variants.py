@@ -396,3 +396,28 @@ def test_single_steps_equal_a_window_of_steps(model, wb, B, cfg):
     assert torch.equal(whole, single)
     assert float((whole - _cuda(lat)).abs().max()) > 0
     ctx.close()
+
+
+@pytest.mark.parametrize("model,B,steps,cfg", [
+    (replace(_net(48, 4, 112, 10, 14), depth=34), 3, 5, 0.0),         # more blocks than a launch takes; two steps' projections at once
+    (replace(_net(32, 2, 64, 64, 64), depth=2), 5, 2, 1.5),           # ten rows of conditioning, samples one at a time
+    (replace(_net(2048, 32, 2048, 4, 4), depth=1), 5, 3, 0.0)])       # widest row
+def test_reference_trajectory_of_a_fit_does_not_depend_on_the_batch(model, B, steps, cfg):
+    """The un-quantised trajectory beside the quantised one: adaLN projections of several steps at once against one latent's."""
+    import torch
+    from qc_testlib import make_pair, oracle_calibration
+    w = I.make_weights(model, 51)
+    lat, lab = I.make_latents(B, model, 52), I.make_labels(B, model, 53).astype(np.int32)
+    qp, _, _ = oracle_calibration(model, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    _, ctx = make_pair(model, w, qp, 2 * B if cfg else B, 2)
+    ctx.load_weights(w, keep_fp32=True)
+
+    def fit(b0, b1):
+        x, ref, K = _cuda(lat[b0:b1]), _cuda(lat[b0:b1]), torch.empty(steps, model.latent_c, device="cuda")
+        ctx.vc_fit_sampler(x, ref, _cuda(lab[b0:b1]), steps, cfg, 1e-3, K)
+        return ref
+    whole = fit(0, B)
+    assert float((whole - _cuda(lat)).abs().max()) > 0
+    for b in range(B):
+        assert torch.equal(whole[b:b + 1], fit(b, b + 1))
+    ctx.close()
