@@ -216,112 +216,164 @@ __global__ __launch_bounds__(512) void ln_mod_quant_kernel(const void *__restric
 
 // ---- one wavefront per token row
 // The wavefront-per-row form of the same operation, for launches with thousands of rows: a lane holds NV float4 of
-// the row (float4 index lane + 64 it), the (sum, sum of squares) reduction stays inside the wavefront (DPP moves inside
-// rows of 16 lanes, the four row sums read back as scalars: no LDS, no barrier), a wavefront walks `rows_per_wave`
-// consecutive rows with the next row's loads in flight while it works on the current one, and keeps the modulation
-// vectors of the batch element in registers from row to row.  The value that is quantised is the same float64
-// expression as above, rounded to float32 once.  Eq. 1 takes v * (1 / s) where that is certain to round to the same
-// integer as the IEEE quotient v / s and the quotient itself otherwise (decided for a float4 of the whole wavefront at
-// a time, so the common case is branch-free).
-// What bounds it: vector issue, about 34 instructions an element in the compiled loop (21 of them modulation and quantiser, the others the
-// two sums and the loads; a third float64), against 5 bytes; 32768 rows of 1152 move 3.6 TB/s.
-// So 1 + scale is formed once a batch element and the test of a float4 is one comparison of its largest values: 57 -> 53 us there,
-// 17.1 -> 15.0 at 8192 rows.  (The shifts as float64 as well: a wavefront less on a SIMD, 56; two register sets that change places instead of
-// the copies: 56 - 60.)
-// Eq. 1 for four values at once, packed signed codes.  qf = v * inv_s differs from the correctly rounded quotient by
-// less than 2 units in its last place (inv_s carries half a unit of relative error, the product another half, the
-// quotient's own rounding a third), so when qf is farther than 4e-7 |qf| from a rounding boundary both round to the same
-// integer; otherwise the quotient decides.  zu = zero point + 128 (the paper's unsigned code), clamped to 0 .. 255 and
-// converted exactly; the sign bit of each byte is flipped back at the end.
-__device__ __forceinline__ unsigned quant4_packed(float h0, float h1, float h2, float h3, float s, float inv_s, float zu) {
-  const float h[4] = {h0, h1, h2, h3};
-  float r[4], d[4], q[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    q[e] = h[e] * inv_s;
-    r[e] = __builtin_rintf(q[e]);
-    d[e] = q[e] - r[e];
-  }
-  // the largest distance from an integer and the largest quotient of the four: one comparison
-  const float far = fmaxf(fmaxf(fabsf(d[0]), fabsf(d[1])), fmaxf(fabsf(d[2]), fabsf(d[3])));
-  const float big = fmaxf(fmaxf(fabsf(q[0]), fabsf(q[1])), fmaxf(fabsf(q[2]), fabsf(q[3])));
-  if (__builtin_amdgcn_ballot_w64(!(fmaf(4e-7f, big, far) < 0.5f)) != 0ull) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = __builtin_rintf(h[e] / s);
-  }
+// the row (float4 index lane + 64 it), the sums of values and squares stay inside the wavefront (no LDS, no barrier), a wavefront walks
+// `rows_per_wave` consecutive rows with the next row's loads in flight while it works on the current one, and keeps the modulation
+// vectors of the batch element in registers from row to row.
+//
+// Mean and variance are float64 sums; the code of an element is decided in float32 where that is certain to be the code of the float64
+// value.  With c' = (1 + scale) / s and s' = shift / s + zero point (formed once a batch element),
+//   v = ((x - mean) rstd) c',   q = v + s',   code = q rounded to nearest even, clamped to 0 .. 255 (the paper's unsigned code)
+// is off the value that Eq. 1 rounds by at most, in units of 2^-24: of |v| 1 (x - mean) + 3 (reciprocal square root, its argument) + 2
+// (two products) + 3.5 (c': 1 + scale, 1 / s, their product) + 1 (the sum) + 2 (on the other side, the value's rounding to float32 and
+// the quotient's) = 12.5, and of |shift| / s 1.5 + 1 (s') + 1 (the sum) + 2; the zero point in s' and in the sum, 2^-17 each below 256 (beyond,
+// every value clamps to the same code); and the mean's rounding, |mean| rstd |c'|.  So an element is in doubt when q lies closer than
+// 8e-7 |v| + near to a half, near = 1.6e-5 + 3.4e-7 |shift| / s + 6.2e-8 |mean| rstd |c'| (maxima and sums of the lane's columns): about
+// 8e-5 of the elements; the wavefront's values around them take the float64 expression and the IEEE quotient (ln_codes_exact).  A row
+// or a column whose window is not finite is in doubt throughout.
+//
+// What bounds it: at thousands of rows the memory system (32768 rows of 1152, 189 MB, in 31 us, the input in the memory-side cache in
+// part); else vector issue, some 13 instructions an element and 50 a row for the sums (in pairs: the sum of the values in the lower half
+// of the wavefront, that of the squares in the upper).  With every value in float64 it was 34 an element: 8192 rows 13.6 -> 11.1 us, 32768
+// 38 -> 31, bfloat16 rows, whose conversion also waited for the loads, 46 -> 26; in the sampler, whose large batches run at the chip's power limit,
+// 16 x 1024 tokens 103.2 -> 101.6 ms.
+__device__ __forceinline__ unsigned ln_codes_exact(float4 x, float4 c, float4 sh, double mean, double var, float s, float zu) {
+  const double rstd = 1.0 / sqrt(fmax(var, 0.0) + 1e-6);
+  const float xs[4] = {x.x, x.y, x.z, x.w}, cs[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sh.x, sh.y, sh.z, sh.w};
   unsigned w = 0;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(r[e] + zu, 0.0f, 255.0f), e, w);
-  return w ^ 0x80808080u;
+  for (int e = 0; e < 4; ++e) {
+    const float h = (float)((xs[e] - mean) * rstd * (1.0 + (double)cs[e]) + (double)ss[e]);
+    w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(__builtin_rintf(h / s) + zu, 0.0f, 255.0f), e, w);
+  }
+  return w;
 }
 
-template <int NV>
-__global__ __launch_bounds__(256) void ln_mod_quant_wave_kernel(const void *__restrict__ x, int x_bf16, const float *__restrict__ shift,
+// v_permlane32_swap / v_permlane16_swap: the upper half (the odd rows of 16) of a changes places with the lower half (the even rows) of b
+template <int W>
+__device__ __forceinline__ void swap_rows(double a, double b, double &a2, double &b2) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+  u2 lo, hi;
+  if constexpr (W == 32) {
+    lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  } else {
+    lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+  }
+  a2 = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+  b2 = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+
+template <int NV, bool BF16>
+__global__ __launch_bounds__(256) void ln_mod_quant_wave_kernel(const void *__restrict__ x, const float *__restrict__ shift,
                                                                 const float *__restrict__ scale, int ld_mod, int M, int D, int T,
                                                                 const QParam *qp, int8_t *__restrict__ q, int rows_per_wave) {
+  typedef typename std::conditional<BF16, uint2, float4>::type raw4;      // four elements as they lie in memory
+  const auto value4 = [](const raw4 &r) {
+    if constexpr (BF16)
+      return make_float4(__builtin_bit_cast(float, r.x << 16), __builtin_bit_cast(float, r.x & 0xFFFF0000u),
+                         __builtin_bit_cast(float, r.y << 16), __builtin_bit_cast(float, r.y & 0xFFFF0000u));
+    else
+      return r;
+  };
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   const int m_begin = wv * rows_per_wave;
   if (m_begin >= M) return;                        // whole wavefronts leave; the kernel has no barrier
   const int m_end = min(m_begin + rows_per_wave, M);
-  const int nv4 = D >> 2;
-  bool live[NV];
+  const int nv4 = D >> 2;                          // 64 (NV - 1) < nv4 <= 64 NV: only the last float4 of a lane may lie beyond the row
+  const bool in_last = lane + 64 * (NV - 1) < nv4;
   int kc[NV];
 #pragma unroll
-  for (int it = 0; it < NV; ++it) {
-    live[it] = lane + 64 * it < nv4;
-    kc[it] = live[it] ? lane + 64 * it : 0;
-  }
+  for (int it = 0; it < NV; ++it) kc[it] = it < NV - 1 || in_last ? lane + 64 * it : 0;
   const QParam t = *qp;
-  const float qs = t.s, inv_s = 1.0f / t.s, zu = (float)(t.z + 128);
-  float4 xa[NV], xn[NV], s4[NV];
-  double cd[NV][4];                                // 1 + scale
+  const float qs = t.s, zu = (float)(t.z + 128), inv_s = 1.0f / t.s;
+  const double inv_d = 1.0 / (double)D;
+  float4 xa[NV], cq[NV], sq4[NV];
+  raw4 xn[NV];
 #pragma unroll
-  for (int it = 0; it < NV; ++it) xa[it] = stream_load4(x, (((size_t)m_begin * D) >> 2) + kc[it], x_bf16);
-  int b_cur = -1;
+  for (int it = 0; it < NV; ++it) xa[it] = value4(((const raw4 *)x)[(((size_t)m_begin * D) >> 2) + kc[it]]);
+  float near_s = 0.f, near_c = 0.f;
+  int b = m_begin / T, left = 0;                   // batch element; rows that its vectors in registers still serve
   for (int m = m_begin; m < m_end; ++m) {
     const int mn = min(m + 1, m_end - 1);          // the last row is requested once more (never used)
 #pragma unroll
-    for (int it = 0; it < NV; ++it) xn[it] = stream_load4(x, (((size_t)mn * D) >> 2) + kc[it], x_bf16);
-    const int b = m / T;
-    if (b != b_cur) {
+    for (int it = 0; it < NV; ++it) xn[it] = ((const raw4 *)x)[(((size_t)mn * D) >> 2) + kc[it]];
+    if (left == 0) {
+      if (m > m_begin) ++b;
+      left = (b + 1) * T - m;
+      near_c = near_s = 0.f;
 #pragma unroll
       for (int it = 0; it < NV; ++it) {
-        s4[it] = *(const float4 *)(shift + (size_t)b * ld_mod + 4 * kc[it]);
-        const float4 c4 = *(const float4 *)(scale + (size_t)b * ld_mod + 4 * kc[it]);
-        cd[it][0] = 1.0 + (double)c4.x;
-        cd[it][1] = 1.0 + (double)c4.y;
-        cd[it][2] = 1.0 + (double)c4.z;
-        cd[it][3] = 1.0 + (double)c4.w;
+        const float4 sv = *(const float4 *)(shift + (size_t)b * ld_mod + 4 * kc[it]), cv = *(const float4 *)(scale + (size_t)b * ld_mod + 4 * kc[it]);
+        cq[it] = make_float4((1.f + cv.x) * inv_s, (1.f + cv.y) * inv_s, (1.f + cv.z) * inv_s, (1.f + cv.w) * inv_s);
+        sq4[it] = make_float4(fmaf(sv.x, inv_s, zu), fmaf(sv.y, inv_s, zu), fmaf(sv.z, inv_s, zu), fmaf(sv.w, inv_s, zu));
+        near_c += (fabsf(cq[it].x) + fabsf(cq[it].y)) + (fabsf(cq[it].z) + fabsf(cq[it].w));      // (a NaN stays)
+        near_s = fmaxf(near_s, fmaxf(fmaxf(fabsf(sv.x), fabsf(sv.y)), fmaxf(fabsf(sv.z), fabsf(sv.w))));
       }
-      b_cur = b;
+      near_c *= 6.2e-8f;
+      near_s = fmaf(3.4e-7f * near_s, inv_s, 1.6e-5f);
     }
+    --left;
+    if (!in_last) xa[NV - 1] = make_float4(0.f, 0.f, 0.f, 0.f);
     double sum = 0.0, sq = 0.0;
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
-      if (live[it]) {
-        const double a = xa[it].x, bq = xa[it].y, c = xa[it].z, d = xa[it].w;
-        sum += (a + bq) + (c + d);
-        sq += (a * a + bq * bq) + (c * c + d * d);
-      }
+      const double a0 = xa[it].x, a1 = xa[it].y, a2 = xa[it].z, a3 = xa[it].w;
+      sum += (a0 + a1) + (a2 + a3);
+      sq = fma(a0, a0, fma(a1, a1, fma(a2, a2, fma(a3, a3, sq))));
     }
-    sum = wave_sum_dpp(sum);
-    sq = wave_sum_dpp(sq);
-    const double mean = sum / (double)D;
-    const double var = sq / (double)D - mean * mean;
-    const double rstd = 1.0 / sqrt(fmax(var, 0.0) + 1e-6);
+    // both sums at once: lanes 0 .. 31 take over the values', 32 .. 63 the squares'
+    double v, w2;
+    swap_rows<32>(sum, sq, v, w2);
+    v += w2;
+    v += dpp_move_d<0xB1>(v);     // as in wave_sum_dpp
+    v += dpp_move_d<0x4E>(v);
+    v += dpp_move_d<0x141>(v);
+    v += dpp_move_d<0x140>(v);
+    swap_rows<16>(v, v, v, w2);
+    v += w2;
+    const double est = v * inv_d;                  // v / D: the quotient's estimate with its remainder divided once more
+    v = fabs(est) < 1e300 ? fma(fma(-est, (double)D, v), inv_d, est) : est;
+    double mean, var;
+    swap_rows<32>(v, v, mean, var);
+    var = var - mean * mean;
+    const float mh = (float)mean, vf = (float)fmax(var, 0.0) + 1e-6f;
+    const float rstd = __builtin_amdgcn_rsqf(vf);
+    // a variance beyond float32's range: every element in doubt
+    const float near = vf < 1e37f ? fmaf(near_c * fabsf(mh), rstd, near_s) : INFINITY;
+    unsigned w[NV];
+    float least[NV];
+    bool doubt = false;
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
-      if (live[it]) {
-        const float h0 = (float)((xa[it].x - mean) * rstd * cd[it][0] + (double)s4[it].x);
-        const float h1 = (float)((xa[it].y - mean) * rstd * cd[it][1] + (double)s4[it].y);
-        const float h2 = (float)((xa[it].z - mean) * rstd * cd[it][2] + (double)s4[it].z);
-        const float h3 = (float)((xa[it].w - mean) * rstd * cd[it][3] + (double)s4[it].w);
-        *(unsigned *)(q + (size_t)m * D + 4 * kc[it]) = quant4_packed(h0, h1, h2, h3, qs, inv_s, zu);
+      const float xs[4] = {xa[it].x, xa[it].y, xa[it].z, xa[it].w}, cs[4] = {cq[it].x, cq[it].y, cq[it].z, cq[it].w};
+      const float ss[4] = {sq4[it].x, sq4[it].y, sq4[it].z, sq4[it].w};
+      float clear[4];
+      w[it] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float u = ((xs[e] - mh) * rstd) * cs[e];
+        const float qv = u + ss[e];
+        w[it] = __builtin_amdgcn_cvt_pk_u8_f32(qv, e, w[it]);
+        clear[e] = fmaf(-8e-7f, fabsf(u), fabsf(__builtin_amdgcn_fractf(qv) - 0.5f));
       }
+      least[it] = fminf(fminf(clear[0], clear[1]), fminf(clear[2], clear[3]));
+      doubt = doubt || !(least[it] >= near);
+    }
+    if (__builtin_amdgcn_ballot_w64(doubt) != 0ull) {
+#pragma unroll
+      for (int it = 0; it < NV; ++it)
+        if (__builtin_amdgcn_ballot_w64(!(least[it] >= near)) != 0ull)
+          w[it] = ln_codes_exact(xa[it], *(const float4 *)(scale + (size_t)b * ld_mod + 4 * kc[it]), *(const float4 *)(shift + (size_t)b * ld_mod + 4 * kc[it]),
+                                 mean, var, qs, zu);
     }
 #pragma unroll
-    for (int it = 0; it < NV; ++it) xa[it] = xn[it];
+    for (int it = 0; it < NV; ++it)
+      if (it < NV - 1 || in_last) *(unsigned *)(q + (size_t)m * D + 4 * kc[it]) = w[it] ^ 0x80808080u;
+#pragma unroll
+    for (int it = 0; it < NV; ++it) xa[it] = value4(xn[it]);
   }
 }
 
@@ -331,18 +383,25 @@ hipError_t launch_ln_mod_quant(const void *x, int x_bf16, const float *shift, co
   if (D % 4 || threads > 512) return hipErrorInvalidValue;
   const int nv = (D / 4 + 63) / 64;
   if (q && !f32_out && M >= 1024 && nv <= 5) {
-    // wavefront per row; with thousands of rows four consecutive rows per wavefront (they share the batch element's
-    // modulation vectors; 2 / 4 / 8 / 16 rows measured at M = 32768, before the last changes: 53.3 / 51.8 / 55.3 / 57.7 us)
-    const int rpw = M >= 8192 ? 4 : 1;
+    // wavefront per row; with thousands of rows several consecutive ones (they share the batch element's modulation vectors and its
+    // float32 constants).  1 / 2 / 4 / 8 rows, us (width 1152): 2048 rows 4.5 / 5.1 / 6.6 / 9.5, 4096: 7.0 / 6.1 / 7.0 / 10.7, 8192: 12.3 / 11.9 /
+    // 11.1 / 12.5, 32768: 35.9 / 32.4 / 31.4 / 34.6
+    const int rpw = M >= 8192 ? 4 : M >= 4096 ? 2 : 1;
     const int waves = (M + rpw - 1) / rpw;
     const dim3 grid((waves + 3) / 4);
+#define QC_LN(NV)                                                                                                                             \
+  do {                                                                                                                                        \
+    if (x_bf16) hipLaunchKernelGGL((ln_mod_quant_wave_kernel<NV, true>), grid, dim3(256), 0, st, x, shift, scale, ld_mod, M, D, T, qp, q, rpw); \
+    else hipLaunchKernelGGL((ln_mod_quant_wave_kernel<NV, false>), grid, dim3(256), 0, st, x, shift, scale, ld_mod, M, D, T, qp, q, rpw);       \
+  } while (0)
     switch (nv) {
-      case 1: hipLaunchKernelGGL(ln_mod_quant_wave_kernel<1>, grid, dim3(256), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T, qp, q, rpw); break;
-      case 2: hipLaunchKernelGGL(ln_mod_quant_wave_kernel<2>, grid, dim3(256), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T, qp, q, rpw); break;
-      case 3: hipLaunchKernelGGL(ln_mod_quant_wave_kernel<3>, grid, dim3(256), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T, qp, q, rpw); break;
-      case 4: hipLaunchKernelGGL(ln_mod_quant_wave_kernel<4>, grid, dim3(256), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T, qp, q, rpw); break;
-      default: hipLaunchKernelGGL(ln_mod_quant_wave_kernel<5>, grid, dim3(256), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T, qp, q, rpw); break;
+      case 1: QC_LN(1); break;
+      case 2: QC_LN(2); break;
+      case 3: QC_LN(3); break;
+      case 4: QC_LN(4); break;
+      default: QC_LN(5); break;
     }
+#undef QC_LN
   } else if (M >= 8192)
     hipLaunchKernelGGL(ln_mod_quant_kernel<4>, dim3((M + 3) / 4), dim3(threads), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T,
                        qp, q, f32_out);

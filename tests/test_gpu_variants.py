@@ -421,3 +421,45 @@ def test_reference_trajectory_of_a_fit_does_not_depend_on_the_batch(model, B, st
     for b in range(B):
         assert torch.equal(whole[b:b + 1], fit(b, b + 1))
     ctx.close()
+
+
+@pytest.mark.parametrize("hidden,hw,B", [(64, (14, 10), 32), (272, (14, 10), 60), (576, (18, 14), 17), (1008, (14, 10), 61),
+                                         (1152, (14, 10), 236), (1280, (50, 34), 3), (1152, (6, 6), 456)])
+def test_layer_norm_codes_of_many_rows(hidden, hw, B):
+    """A wavefront a row (1, 2 or 4 rows in turn, batch elements that end between them), which decides most codes in float32,
+    against a workgroup a row, which forms every value in float64: means far off, outliers, constant rows, ranges beyond float32's squares,
+    values that are not finite."""
+    import torch
+    import paper_2503_02508_amd as qc
+    from qc_testlib import make_pair, oracle_calibration
+    model = _net(hidden, hidden // 16, 64, *hw)
+    w = I.make_weights(model, 61)
+    T, D = model.tokens, model.hidden
+    lat, lab = I.make_latents(1, model, 62), I.make_labels(1, model, 63)
+    qp, _, _ = oracle_calibration(model, w, lat=lat, lab=lab, t=np.array([400]))
+    _, ctx = make_pair(model, w, qp, B, 1)
+    rng = np.random.default_rng(64)
+    x = rng.standard_normal((B * T, D)).astype(np.float32)
+    kind = np.arange(B * T) % 64
+    x[kind == 1] += 300.0
+    x[kind == 2] *= 1e-3
+    x[kind == 3, 5] *= 1e3
+    x[kind == 4] = 0.0
+    x[kind == 5] = 1.5
+    x[kind == 6] *= 1e25
+    x[kind == 7, 0] = np.inf
+    x[kind == 8, D - 1] = np.nan
+    x[kind == 9, 1] = -3e38
+    x[kind == 10] *= 1e-25
+    cond = rng.standard_normal((B, D)).astype(np.float32)
+
+    def codes(b0, b1):
+        ctx.dit_block(0, qc.QC_FULL, _cuda(x[b0 * T:b1 * T].reshape(b1 - b0, T, D)), _cuda(cond[b0:b1]))
+        return ctx.workspace("qact_ln", ((b1 - b0) * T, D), torch.int8).clone()
+    whole = codes(0, B)
+    assert B * T >= 1024 and int(whole.unique().numel()) > 100
+    step = 1023 // T
+    for b0 in range(0, B, max(1, step)):
+        b1 = min(B, b0 + max(1, step))
+        assert torch.equal(whole[b0 * T:b1 * T], codes(b0, b1))
+    ctx.close()
