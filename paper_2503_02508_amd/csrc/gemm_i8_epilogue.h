@@ -98,21 +98,63 @@ __device__ __forceinline__ int quant_code(float v, float s, float inv_s, float z
   return (int)r;
 }
 
+// What the epilogue of a tile reads from memory besides the accumulators, for kernels that request it in front of their main loop (the
+// same tile arguments): of one wavefront's TM x TN blocks of 32 x 32, lane l's column l % 32 of every block column.  X: the residual
+// stream's elements too (float32 ones: converting others would wait for them at once).
+template <int EPI, int TM, int TN, bool X>
+struct EpiPre {
+  static_assert(!X || EPI == EPI_RESID, "");
+  QParam qp, oq;
+  float sc[TN], bs[TN], gate[TN];
+  int zw[TN];
+  float x[X ? TN : 1][TM][16];
+};
+template <int BM, int BN, int WM, int WN, int EPI, bool X>
+__device__ __forceinline__ void epilogue_request(const GemmArgs &p, EpiPre<EPI, BM / WM / 32, BN / WN / 32, X> &e, const int wave, const int m0,
+                                                 const int n0) {
+  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+  const int lane = threadIdx.x & 63, wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
+  e.qp = p.a_qp ? *p.a_qp : QParam{p.a_scale, p.a_zp};
+  if constexpr (EPI == EPI_GELU_Q) e.oq = *p.o_qp;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int n = min(n0 + wn0 + j * 32 + (lane & 31), p.N - 1);
+    e.sc[j] = p.w_scale[n];
+    e.zw[j] = p.wsum[n];
+    e.bs[j] = p.bias ? p.bias[n] : 0.0f;
+    if constexpr (EPI == EPI_RESID) e.gate[j] = p.gate[(long long)(m0 / p.rows_per_batch) * p.ld_gate + n];
+    if constexpr (X) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = min(m0 + wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), p.M - 1);
+          e.x[j][i][r] = ((const float *)p.x)[(long long)m * p.N + n];
+        }
+    }
+  }
+}
+
 // Epilogue of a tile: acc[i][j] is the 32 x 32 block (i along the rows m of the activations, j along the output
 // columns n) of wavefront (wave / WN, wave % WN); for EPI_GELU_Q the weights were the first MFMA operand (register
 // index runs along n), otherwise the activations were (register index runs along m).  smem: the workgroup's dynamic
 // LDS, free for reuse (every wavefront is past its last fragment read).
 // RBF: the residual stream or the cache may be bfloat16 (read from the arguments); false: both are known to be float32.
-template <int BM, int BN, int WM, int WN, int EPI, bool RBF = true>
+// pre: what epilogue_request has fetched (z is 0 then), or null.
+template <int BM, int BN, int WM, int WN, int EPI, bool RBF = true, bool PRE = false, bool PREX = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM / WM / 32][BN / WN / 32], unsigned char *smem,
-                                              const int m0, const int n0, const int z) {
+                                              const int m0, const int n0, const int z,
+                                              const EpiPre<EPI, BM / WM / 32, BN / WN / 32, PREX> *pre = nullptr) {
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32, NT = 64 * WM * WN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
   const int ncover = p.sel_D ? 2 * p.sel_D : p.N;
   float a_s = p.a_scale;
   int a_z = p.a_zp;
-  if (p.a_qp) {
+  if constexpr (PRE) {
+    a_s = pre->qp.s;
+    a_z = pre->qp.z;
+  } else if (p.a_qp) {
     QParam q = p.a_qp[(long long)z * p.zs_qp];
     a_s = q.s;
     a_z = q.z;
@@ -132,7 +174,18 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
     int *fix_cnt = (int *)(stage + BM * SROW);
     int *fix_ent = fix_cnt + 4;                        // [GELU_FIX_CAP][4]: accumulator minus zero-point term, column, row
     if (tid == 0) *fix_cnt = 0;
-    if (tid < BN) {
+    if constexpr (PRE) {
+      if (wm0 == 0 && lane < 32) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int nl = wn0 + j * 32 + lane;
+          const bool ok = n0 + nl < p.N;
+          c_sc[nl] = ok ? a_s * pre->sc[j] : 0.0f;
+          c_zw[nl] = ok ? a_z * pre->zw[j] : 0;
+          c_bs[nl] = ok ? pre->bs[j] : 0.0f;
+        }
+      }
+    } else if (tid < BN) {
       const int n = n0 + tid;
       const bool ok = n < p.N;
       c_sc[tid] = ok ? a_s * w_scale[n] : 0.0f;
@@ -140,7 +193,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
       c_bs[tid] = (ok && bias) ? bias[n] : 0.0f;
     }
     __syncthreads();
-    const QParam oq = *p.o_qp;
+    QParam oq;
+    if constexpr (PRE) oq = pre->oq;
+    else oq = *p.o_qp;
     const GeluQuant gq(oq);
     const int g = lane >> 5;
 #pragma unroll
@@ -272,9 +327,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
     for (int j = 0; j < TN; ++j) {
       const int n = n0 + wn0 + j * 32 + (lane & 31);
       if (n >= p.N) continue;
-      const double sc = (double)a_s * (double)w_scale[n];
-      const int zw = a_z * wsum[n];
-      const double bs = bias ? (double)bias[n] : 0.0;
+      const double sc = (double)a_s * (double)(PRE ? pre->sc[j] : w_scale[n]);
+      const int zw = a_z * (PRE ? pre->zw[j] : wsum[n]);
+      const double bs = PRE ? (double)pre->bs[j] : bias ? (double)bias[n] : 0.0;
       const int part = n / D, nn = n - part * D, h = nn / p.hd, e = nn - h * p.hd;
       float *dqk = part == 0 ? p.q32 : p.k32;
 #pragma unroll
@@ -329,12 +384,13 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int m = min(m0 + wm0 + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), p.M - 1);
-          xv[j][i][r] = stream_load(p.x, (long long)m * p.N + n, x_bf16);
+          if constexpr (PREX) xv[j][i][r] = pre->x[j][i][r];
+          else xv[j][i][r] = stream_load(p.x, (long long)m * p.N + n, x_bf16);
         }
-      scv[j] = (double)a_s * (double)w_scale[n];
-      zwv[j] = a_z * wsum[n];
-      bsv[j] = bias ? (double)bias[n] : 0.0;
-      gv[j] = p.gate[(long long)b_uniform * p.ld_gate + n];
+      scv[j] = (double)a_s * (double)(PRE ? pre->sc[j] : w_scale[n]);
+      zwv[j] = a_z * (PRE ? pre->zw[j] : wsum[n]);
+      bsv[j] = PRE ? (double)pre->bs[j] : bias ? (double)bias[n] : 0.0;
+      gv[j] = PRE ? pre->gate[j] : p.gate[(long long)b_uniform * p.ld_gate + n];
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
@@ -377,10 +433,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &p, v16i (&acc)[BM 
   for (int j = 0; j < TN; ++j) {
     const int jl = n0 + wn0 + j * 32 + (lane & 31);
     if (jl >= ncover) continue;
-    const int n = map_col(jl, p.sel_D);
-    const double sc = (double)a_s * (double)w_scale[n];
-    const int zw = a_z * wsum[n];
-    const double bs = bias ? (double)bias[n] : 0.0;
+    const int n = map_col(jl, p.sel_D);                // (PRE: sel_D is 0)
+    const double sc = (double)a_s * (double)(PRE ? pre->sc[j] : w_scale[n]);
+    const int zw = a_z * (PRE ? pre->zw[j] : wsum[n]);
+    const double bs = PRE ? (double)pre->bs[j] : bias ? (double)bias[n] : 0.0;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
 #pragma unroll

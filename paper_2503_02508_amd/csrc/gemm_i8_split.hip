@@ -32,7 +32,8 @@ constexpr int split_en(int tm, int tn, int nw) {
   return best;
 }
 
-template <int TM, int TN, int NW, int EPI, bool W4, bool WROW, bool RBF>
+// FEW: no more tiles than compute units.
+template <int TM, int TN, int NW, int EPI, bool W4, bool WROW, bool RBF, bool FEW>
 __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void gemm_i8_split_kernel(GemmArgs p) {
   constexpr int BM = 32 * TM, BN = 32 * TN, NB = TM * TN, CK = 128;
   constexpr int EM = split_em(TM, TN, NW), EN = split_en(TM, TN, NW);   // wavefront grid of the epilogue
@@ -143,10 +144,22 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
     store_a(c);
     compute(set);
   };
+  // Nothing covers a round trip to memory behind the sums of a lone workgroup: what the epilogue reads comes in behind the first
+  // chunk.  (Not for the larger tiles, which have no registers left for it; the residual stream's elements only where a unit has one
+  // workgroup, and not where they may be bfloat16: converting would wait for them.)  One latent of 256 tokens, 50 steps: 40.5 ->
+  // 39.3 ms; with 64 x 64 tiles and the stream's elements on every launch 39.5, and 8 latents 81.3 -> 83.0.
+  constexpr bool PRE = TM * TN <= 2, PREX = FEW && TM * TN <= 2 && EPI == EPI_RESID && !RBF;
+  EpiPre<EPI, TM / EM, TN / EN, PREX> pre;
+  int c = wave, left = mine;
   if (mine > 0) {
-    int c = wave, left = mine;
     load_a(c);
     load_b(0, c);
+  }
+  if constexpr (PRE) {
+    epilogue_request<BM, BN, EM, EN, EPI, PREX>(p, pre, min(wave, EM * EN - 1), m0, n0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (mine > 0) {
     for (; left > 2; left -= 2, c += 2 * NW) {
       step(0, c);
       step(1, c + NW);
@@ -216,7 +229,7 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
   }
   __syncthreads();                                                 // the sums are read: LDS is free for the epilogue
   if (wave >= EM * EN) return;                                     // (ended wavefronts do not count at its barriers)
-  gemm_epilogue<BM, BN, EM, EN, EPI, RBF>(p, fin, smem, m0, n0, 0);
+  gemm_epilogue<BM, BN, EM, EN, EPI, RBF, PRE, PREX>(p, fin, smem, m0, n0, 0, &pre);
 }
 
 template <int TM, int TN, int NW, int EPI, bool W4, bool WROW, bool RBF = false>
@@ -229,11 +242,12 @@ static hipError_t launch_split(const GemmArgs &a, hipStream_t st) {
   constexpr int s_epi = EPI == EPI_GELU_Q ? BN * 12 + BM * (BN + 16) + 16 + GELU_FIX_CAP * 16 : 0;
   constexpr int smem = s_loop > s_red ? (s_loop > s_epi ? s_loop : s_epi) : (s_red > s_epi ? s_red : s_epi);
   static_assert(smem <= 160 * 1024, "LDS of a compute unit");
-  static std::atomic<unsigned long long> lds{0};
-  auto kern = gemm_i8_split_kernel<TM, TN, NW, EPI, W4, WROW, RBF>;
-  if (const hipError_t e = allow_lds((const void *)kern, smem, lds)) return e;
+  static std::atomic<unsigned long long> lds[2];
   GemmArgs b = a;
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  const bool few = (long long)tiles_m * tiles_n <= 256;
+  auto kern = few ? gemm_i8_split_kernel<TM, TN, NW, EPI, W4, WROW, RBF, true> : gemm_i8_split_kernel<TM, TN, NW, EPI, W4, WROW, RBF, false>;
+  if (const hipError_t e = allow_lds((const void *)kern, smem, lds[few])) return e;
   b.xcd_m = xcd_rows(tiles_m, tiles_n, (double)a.M * a.K, (double)a.N * a.K * (W4 ? 0.5 : 1.0));
   const int cm = (tiles_m + b.xcd_m - 1) / b.xcd_m, xn = NUM_XCD / b.xcd_m, cn = (tiles_n + xn - 1) / xn;
   hipLaunchKernelGGL(kern, dim3(NUM_XCD * cm * cn), dim3(64 * NW), smem, st, b);
