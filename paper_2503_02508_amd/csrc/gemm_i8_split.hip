@@ -9,7 +9,7 @@
 //     16-byte chunks swizzled with the row's low three bits (conflict-free writes and reads).
 //   * weights in fragment order go straight to registers; row-major ones (WROW: the caller's matrix of qc_w8a8_linear) take
 //     the activations' way.
-//   * the loads of the next chunk are in flight while a chunk is multiplied.
+//   * the loads of the next two chunks are in flight while a chunk is multiplied, of three where a compute unit has no second tile.
 // What bounds it: the 60 bytes per clock a compute unit draws from its L2 (32 TM + 32 TN rows of K bytes per tile), and the
 // fixed costs around it (launch, first memory round trip, reduction, epilogue).
 #include "gemm_i8_epilogue.h"
@@ -32,12 +32,21 @@ constexpr int split_en(int tm, int tn, int nw) {
   return best;
 }
 
+// Chunks of a wavefront in flight.  What a launch of few tiles waits for are round trips to weights that lie in HBM, one after the
+// other; K = 1152 is three chunks a wavefront, all requested before the first is multiplied.  32 x 64 tiles of which a compute unit
+// has several keep to two (160 registers, three workgroups a unit: with three chunks fc1 at 256 rows 10.8 -> 12.2 us, proj at 1024 rows
+// 9.5 -> 11.2), 64 x 64 ones have no registers for a third, a 64 x 96 tile's third gained nothing.  Row-major weights go through LDS, one.
+// One chunk | this, in sampling runs of 50 steps: one latent of 256 tokens 39.4 | 38.4 ms (proj and fc2 together 17.0 | 16.4 us), 8 latents 81.5 |
+// 80.2 (fc2).
+constexpr int split_depth(int tm, int tn, bool few, bool wrow) { return wrow ? 1 : few && tm * tn == 2 ? 3 : 2; }
+
 // FEW: no more tiles than compute units.
 template <int TM, int TN, int NW, int EPI, bool W4, bool WROW, bool RBF, bool FEW>
 __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void gemm_i8_split_kernel(GemmArgs p) {
   constexpr int BM = 32 * TM, BN = 32 * TN, NB = TM * TN, CK = 128;
   constexpr int EM = split_em(TM, TN, NW), EN = split_en(TM, TN, NW);   // wavefront grid of the epilogue
   static_assert(EM * EN <= NW && TM % EM == 0 && TN % EN == 0, "every block needs a wavefront that finishes it");
+  constexpr int PF = split_depth(TM, TN, FEW, WROW);
   constexpr int WREG = (BM + (WROW ? BN : 0)) * CK;                // private LDS bytes of a wavefront
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -54,7 +63,7 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
   const int lrow = lane >> 3, lc = lane & 7;                       // row within a pass of 8 rows, 16-byte chunk
   unsigned aoff[TM * 4], boff[WROW ? TN * 4 : 1];
 #pragma unroll
-  for (int i = 0; i < TM * 4; ++i) aoff[i] = (unsigned)(min(m0 + 8 * i + lrow, p.M - 1) - m0) * (unsigned)p.lda;
+  for (int i = 0; i < TM * 4; ++i) aoff[i] = (unsigned)(min(m0 + 8 * i + lrow, p.M - 1) - m0) * (unsigned)p.lda + (WROW ? 0 : lc * 16);
   if constexpr (WROW) {
 #pragma unroll
     for (int i = 0; i < TN * 4; ++i) boff[i] = (unsigned)(min(n0 + 8 * i + lrow, p.N - 1) - n0) * (unsigned)(W4 ? p.K >> 1 : p.K);
@@ -63,42 +72,54 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
   constexpr int FRAG = W4 ? 512 : 1024;                            // bytes per weight fragment
   typedef typename std::conditional<W4, v2i, v4i>::type wload_t;
   const int ng = p.K / 32, nblocks = p.N / 32;
-  const unsigned char *wbase[TN];
+  const int bl0 = n0 / 32;                                         // (n0 < N: the tile's first block of columns exists)
+  const unsigned char *wbase = WROW ? (const unsigned char *)p.W + (size_t)n0 * (W4 ? p.K >> 1 : p.K)
+                                    : (const unsigned char *)p.Wt + (size_t)bl0 * ng * FRAG;
+  // buffer loads: a lane's offset in one register, the chunk's in a scalar one, no 64-bit address a load
+  const auto abuf = __builtin_amdgcn_make_buffer_rsrc((void *)abase, 0, -1, 0x00027000);
+  const auto wbuf = __builtin_amdgcn_make_buffer_rsrc((void *)wbase, 0, -1, 0x00027000);
+  int woff[TN];
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
-    wbase[j] = WROW ? (const unsigned char *)p.W + (size_t)n0 * (W4 ? p.K >> 1 : p.K)
-                    : (const unsigned char *)p.Wt + (size_t)min(n0 / 32 + j, nblocks - 1) * ng * FRAG;
+  for (int j = 0; j < TN; ++j) woff[j] = (min(bl0 + j, nblocks - 1) - bl0) * ng * FRAG;
   unsigned char *sA = smem + wave * WREG, *sB = sA + BM * CK;
-  v4i ra[TM * 4];
-  wload_t rb[2][TN * 4];                                           // WROW: only set 0 is used, until it is in LDS
-  auto load_a = [&](int c) {
-    const unsigned k = (unsigned)min(c * CK + lc * 16, p.K - 16);  // beyond K: re-read the end, zeroed in store_a
+  v4i ra[PF][TM * 4];
+  wload_t rb[PF][TN * 4];                                          // WROW: used until the chunk is in LDS
+  auto load_a = [&](int set, int c) {
+    if constexpr (WROW) {
+      const unsigned k = (unsigned)min(c * CK + lc * 16, p.K - 16);  // beyond K: re-read the end, zeroed in store_a
 #pragma unroll
-    for (int i = 0; i < TM * 4; ++i) ra[i] = *(const v4i *)(abase + aoff[i] + k);
+      for (int i = 0; i < TM * 4; ++i) ra[set][i] = *(const v4i *)(abase + aoff[i] + k);
+    } else {                                                       // K is whole chunks
+#pragma unroll
+      for (int i = 0; i < TM * 4; ++i) ra[set][i] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(abuf, aoff[i], c * CK, 0));
+    }
   };
   auto load_b = [&](int set, int c) {
     if constexpr (WROW) {
       const unsigned k = (unsigned)min(c * CK + lc * 16, p.K - 16);
 #pragma unroll
-      for (int i = 0; i < TN * 4; ++i) rb[0][i] = *(const wload_t *)(wbase[0] + boff[i] + (W4 ? k >> 1 : k));
+      for (int i = 0; i < TN * 4; ++i) rb[set][i] = *(const wload_t *)(wbase + boff[i] + (W4 ? k >> 1 : k));
     } else {
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          rb[set][j * 4 + g] = *(const wload_t *)(wbase[j] + (size_t)(c * 4 + g) * FRAG + (unsigned)lane * (W4 ? 8 : 16));
+        for (int g = 0; g < 4; ++g) {
+          const int so = woff[j] + (c * 4 + g) * FRAG;
+          if constexpr (W4) rb[set][j * 4 + g] = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(wbuf, lane * 8, so, 0));
+          else rb[set][j * 4 + g] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wbuf, lane * 16, so, 0));
+        }
     }
   };
-  auto store_a = [&](int c) {
-    const bool zero = c * CK + lc * 16 >= p.K;
+  auto store_a = [&](int set, int c) {
+    const bool zero = WROW && c * CK + lc * 16 >= p.K;
 #pragma unroll
-    for (int i = 0; i < TM * 4; ++i) *(v4i *)(sA + (8 * i + lrow) * CK + ((lc ^ lrow) * 16)) = zero ? (v4i){0, 0, 0, 0} : ra[i];
+    for (int i = 0; i < TM * 4; ++i) *(v4i *)(sA + (8 * i + lrow) * CK + ((lc ^ lrow) * 16)) = zero ? (v4i){0, 0, 0, 0} : ra[set][i];
     if constexpr (WROW) {
 #pragma unroll
       for (int i = 0; i < TN * 4; ++i) {
         v4i v;
-        if constexpr (W4) v = unpack_w4(rb[0][i]);
-        else v = rb[0][i];
+        if constexpr (W4) v = unpack_w4(rb[set][i]);
+        else v = rb[set][i];
         *(v4i *)(sB + (8 * i + lrow) * CK + ((lc ^ lrow) * 16)) = v;
       }
     }
@@ -132,17 +153,26 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
         }
     }
   };
-  // straight-line steps: chunk c is in registers (set), the next one is requested before c is multiplied
+  // straight-line steps: chunk c is in registers (set); they are requested anew for chunk c + PF NW as they become free, the activations' once they are in LDS, the weights' once they are multiplied (WROW: with the activations')
   auto step = [&](int set, int c) {
-    store_a(c);
-    load_a(c + NW);
-    load_b(set ^ 1, c + NW);
+    const int next = min(c + PF * NW, nc - 1);                     // (beyond the last chunk: not used)
+    store_a(set, c);
+    load_a(set, next);
+    if constexpr (WROW) load_b(set, next);
     __builtin_amdgcn_sched_barrier(0);
     compute(set);
+    if constexpr (!WROW) {
+      __builtin_amdgcn_sched_barrier(0);
+      load_b(set, next);
+    }
   };
   auto last = [&](int set, int c) {
-    store_a(c);
+    store_a(set, c);
     compute(set);
+  };
+  auto request = [&](int d) {
+    load_a(d, wave + d * NW);
+    load_b(d, wave + d * NW);
   };
   // Nothing covers a round trip to memory behind the sums of a lone workgroup: what the epilogue reads comes in behind the first
   // chunk.  (Not for the larger tiles, which have no registers left for it; the residual stream's elements only where a unit has one
@@ -150,26 +180,40 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
   // 39.3 ms; with 64 x 64 tiles and the stream's elements on every launch 39.5, and 8 latents 81.3 -> 83.0.
   constexpr bool PRE = TM * TN <= 2, PREX = FEW && TM * TN <= 2 && EPI == EPI_RESID && !RBF;
   EpiPre<EPI, TM / EM, TN / EN, PREX> pre;
-  int c = wave, left = mine;
-  if (mine > 0) {
-    load_a(c);
-    load_b(0, c);
-  }
+  load_a(0, min(wave, nc - 1));                                    // (a wavefront without a chunk makes no use of it)
+  load_b(0, min(wave, nc - 1));
   if constexpr (PRE) {
+    __builtin_amdgcn_sched_barrier(0);
     epilogue_request<BM, BN, EM, EN, EPI, PREX>(p, pre, min(wave, EM * EN - 1), m0, n0);
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (mine > 0) {
-    for (; left > 2; left -= 2, c += 2 * NW) {
-      step(0, c);
-      step(1, c + NW);
+  // a path of its own for fewer than PF chunks: where paths with different numbers of loads in flight meet, the compiler waits for more
+  // than it has to
+  if (mine >= PF) {
+#pragma unroll
+    for (int d = 1; d < PF; ++d) request(d);
+    __builtin_amdgcn_sched_barrier(0);
+    int c = wave, left = mine;
+    for (; left > PF; left -= PF, c += PF * NW) {
+#pragma unroll
+      for (int d = 0; d < PF; ++d) step(d, c + d * NW);
     }
-    if (left == 2) {
-      step(0, c);
-      last(1, c + NW);
-    } else {
-      last(0, c);
+    last(0, c);
+    if constexpr (PF > 1) {
+      if (left > 1) {
+        last(1, c + NW);
+        if constexpr (PF > 2) {
+          if (left > 2) last(2, c + 2 * NW);
+        }
+      }
     }
+  } else if (PF > 2 && mine == 2) {
+    request(1);
+    __builtin_amdgcn_sched_barrier(0);
+    last(0, wave);
+    last(1, wave + NW);
+  } else if (mine == 1) {
+    last(0, wave);
   }
 
   // ---- the partial sums meet.  A block is 64 lanes x 16 integers, stored as 4 x [64 lanes][4].

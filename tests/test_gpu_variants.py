@@ -67,6 +67,10 @@ def _net(hidden, heads, mlp, h, w, patch=2):
     ("split-K: 32 x 64 tiles in place of 252 of 64 x 64, 425 tokens", _net(1152, 16, 4608, 50, 34), 2, 8),
     ("split-K: 32 x 64 tiles in place of 288 of 64 x 64, 4-bit", _net(1152, 16, 4608, 32, 32), 1, 4),
     ("split-K: 64 x 96 tiles", _net(1152, 16, 4608, 32, 32), 4, 8),
+    # chunks of K a wavefront of the MLP's second product walks, three of them in flight: 4 and 3, 5, 4
+    ("split-K: 13 chunks", _net(512, 8, 1664, 20, 28), 2, 8),
+    ("split-K: 20 chunks", _net(512, 8, 2560, 20, 28), 2, 8),
+    ("split-K: 16 chunks, 4-bit", _net(512, 8, 2048, 20, 28), 2, 4),
 ])
 def test_quantisers_of_small_and_ragged_launches(name, model, B, wb):
     from test_gpu_quantisers import test_each_fused_quantiser_alone as check
