@@ -279,7 +279,8 @@ __device__ __forceinline__ unsigned ln_codes_exact(float4 x, float4 c, float4 sh
   return w;
 }
 
-template <int NV, bool BF16>
+// ONE: a wavefront has one row, no next one to request (1024 rows 5.8 -> 5.5 us beside the other half's kernels).
+template <int NV, bool BF16, bool ONE>
 __global__ __launch_bounds__(256) void ln_mod_quant_wave_kernel(const void *__restrict__ x, const float *__restrict__ shift,
                                                                 const float *__restrict__ scale, int ld_mod, int M, int D, int T,
                                                                 const QParam *qp, int8_t *__restrict__ q, int rows_per_wave) {
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(256) void ln_mod_quant_wave_kernel(const void *__re
   for (int m = m_begin; m < m_end; ++m) {
     const int mn = min(m + 1, m_end - 1);          // the last row is requested once more (never used)
 #pragma unroll
-    for (int it = 0; it < NV; ++it) xn[it] = ((const raw4 *)x)[(((size_t)mn * D) >> 2) + kc[it]];
+    for (int it = 0; it < NV && !ONE; ++it) xn[it] = ((const raw4 *)x)[(((size_t)mn * D) >> 2) + kc[it]];
     if (left == 0) {
       if (m > m_begin) ++b;
       left = (b + 1) * T - m;
@@ -387,7 +388,7 @@ __global__ __launch_bounds__(256) void ln_mod_quant_wave_kernel(const void *__re
     for (int it = 0; it < NV; ++it)
       if (it < NV - 1 || in_last) *(unsigned *)(q + (size_t)m * D + 4 * kc[it]) = w[it] ^ 0x80808080u;
 #pragma unroll
-    for (int it = 0; it < NV; ++it) xa[it] = value4(xn[it]);
+    for (int it = 0; it < NV && !ONE; ++it) xa[it] = value4(xn[it]);
   }
 }
 
@@ -396,17 +397,22 @@ hipError_t launch_ln_mod_quant(const void *x, int x_bf16, const float *shift, co
   const int threads = ((D / 4 + 63) / 64) * 64;
   if (D % 4 || threads > 512) return hipErrorInvalidValue;
   const int nv = (D / 4 + 63) / 64;
-  if (q && !f32_out && M >= 1024 && nv <= 5) {
+  if (q && !f32_out && M >= 640 && nv <= 5) {
     // wavefront per row; with thousands of rows several consecutive ones (they share the batch element's modulation vectors and its
     // float32 constants).  1 / 2 / 4 / 8 rows, us (width 1152): 2048 rows 4.5 / 5.1 / 6.6 / 9.5, 4096: 7.0 / 6.1 / 7.0 / 10.7, 8192: 12.3 / 11.9 /
-    // 11.1 / 12.5, 32768: 35.9 / 32.4 / 31.4 / 34.6
+    // 11.1 / 12.5, 32768: 35.9 / 32.4 / 31.4 / 34.6.  From 640 rows on, a workgroup a row | a wavefront a row, 20 steps of width 1152: 2 latents
+    // (512 rows) 20.10 | 20.19 ms, 3 (768) 21.89 | 21.73, 5 of 240 tokens in bfloat16 (720 and 480) 30.0 | 29.7; at 1024 rows 6.8 | 5.5 us
     const int rpw = M >= 8192 ? 4 : M >= 4096 ? 2 : 1;
     const int waves = (M + rpw - 1) / rpw;
     const dim3 grid((waves + 3) / 4);
-#define QC_LN(NV)                                                                                                                             \
-  do {                                                                                                                                        \
-    if (x_bf16) hipLaunchKernelGGL((ln_mod_quant_wave_kernel<NV, true>), grid, dim3(256), 0, st, x, shift, scale, ld_mod, M, D, T, qp, q, rpw); \
-    else hipLaunchKernelGGL((ln_mod_quant_wave_kernel<NV, false>), grid, dim3(256), 0, st, x, shift, scale, ld_mod, M, D, T, qp, q, rpw);       \
+#define QC_LN_AS(NV, BF16, ONE) \
+  hipLaunchKernelGGL((ln_mod_quant_wave_kernel<NV, BF16, ONE>), grid, dim3(256), 0, st, x, shift, scale, ld_mod, M, D, T, qp, q, rpw)
+#define QC_LN(NV)                                  \
+  do {                                             \
+    if (x_bf16 && rpw == 1) QC_LN_AS(NV, true, true); \
+    else if (x_bf16) QC_LN_AS(NV, true, false);    \
+    else if (rpw == 1) QC_LN_AS(NV, false, true);  \
+    else QC_LN_AS(NV, false, false);               \
   } while (0)
     switch (nv) {
       case 1: QC_LN(1); break;
@@ -416,6 +422,7 @@ hipError_t launch_ln_mod_quant(const void *x, int x_bf16, const float *shift, co
       default: QC_LN(5); break;
     }
 #undef QC_LN
+#undef QC_LN_AS
   } else if (M >= 8192)
     hipLaunchKernelGGL(ln_mod_quant_kernel<4>, dim3((M + 3) / 4), dim3(threads), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T,
                        qp, q, f32_out);

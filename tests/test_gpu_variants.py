@@ -428,7 +428,8 @@ def test_reference_trajectory_of_a_fit_does_not_depend_on_the_batch(model, B, st
 
 
 @pytest.mark.parametrize("hidden,hw,B", [(64, (14, 10), 32), (272, (14, 10), 60), (576, (18, 14), 17), (1008, (14, 10), 61),
-                                         (1152, (14, 10), 236), (1280, (50, 34), 3), (1152, (6, 6), 456)])
+                                         (1152, (14, 10), 236), (1280, (50, 34), 3), (1152, (6, 6), 456),
+                                         (768, (6, 6), 73)])
 def test_layer_norm_codes_of_many_rows(hidden, hw, B):
     """A wavefront a row (1, 2 or 4 rows in turn, batch elements that end between them), which decides most codes in float32,
     against a workgroup a row, which forms every value in float64: means far off, outliers, constant rows, ranges beyond float32's squares,
@@ -461,8 +462,8 @@ def test_layer_norm_codes_of_many_rows(hidden, hw, B):
         ctx.dit_block(0, qc.QC_FULL, _cuda(x[b0 * T:b1 * T].reshape(b1 - b0, T, D)), _cuda(cond[b0:b1]))
         return ctx.workspace("qact_ln", ((b1 - b0) * T, D), torch.int8).clone()
     whole = codes(0, B)
-    assert B * T >= 1024 and int(whole.unique().numel()) > 100
-    step = 1023 // T
+    assert B * T >= 640 and int(whole.unique().numel()) > 100
+    step = 639 // T
     for b0 in range(0, B, max(1, step)):
         b1 = min(B, b0 + max(1, step))
         assert torch.equal(whole[b0 * T:b1 * T], codes(b0, b1))
