@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <math.h>
 #include <algorithm>
+#include <type_traits>
 #include <utility>
 #include <vector>
 #include "qc_tap.h"
@@ -1185,6 +1186,10 @@ constexpr int KM_DONE = 2, KM_PASSES = 3, KM_COUNT = 4;
 // subsample took 48 for an assignment on the vector units and 32 for sums by LDS atomics.  The products are what is left:
 // 392 instructions of 32 cycles a wavefront, on 384 workgroups, so half the compute units have two.
 constexpr int KM_ROWS = 256;
+// Up to 16 KM_STAGE_NC dimensions, the rows of a range of one batch stay in LDS for the sums, whose chains of eight rows a round trip were
+// the longest part of a pass (1536 samples, 8 clusters 9.7 -> 8.6 us), and are requested before the centres are formed.  Clusterings of
+// 1200 to 30000 samples, up to 16 clusters: 0.5 - 2.6 % faster; with 17 to 32 dimensions too nothing gained, with 33 to 48 1 % slower.
+constexpr int KM_STAGE_NC = 1;
 typedef float kmv4 __attribute__((ext_vector_type(4)));
 
 // `own` (it > 0, no kmeans_finish_kernel in between): every workgroup starts from the sums of the pass before and forms the centres
@@ -1222,6 +1227,8 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
   extern __shared__ float sm[];
   const int k16 = (k + 15) & ~15;
   float *const cs = sm, *const cn = sm + k16 * S;
+  float *const us = cn + k16;                     // STAGE: the rows of a range of one batch, as the centres
+  constexpr bool STAGE = NC <= KM_STAGE_NC;
   __shared__ int lab_s[KM_ROWS], queue[KM_ROWS], queued, changed, touched[KB_MAX];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ql = lane & 15, g = lane >> 4;
   const float kappa = (float)(5 * d + 16) * 5.9604645e-8f;
@@ -1231,6 +1238,30 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
     changed = 0;
   }
   if (tid < KB_MAX) touched[tid] = it == 0;       // the first pass writes every count
+  const int r0 = blockIdx.x * rows_per, r1 = min(N, r0 + rows_per);
+  const bool staged = STAGE && r1 - r0 <= KM_ROWS;
+  kmv4 uf[2][NC];
+  auto load_rows = [&](int b0) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float *u = U + (long long)min(b0 + wave * 32 + 16 * j + ql, N - 1) * d;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int f = 16 * c + 4 * g;
+        if (V4) {
+          const kmv4 v = *(const kmv4 *)(u + min(f, d - 4));
+          uf[j][c] = f < d ? v : (kmv4){0.f, 0.f, 0.f, 0.f};
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v = u[min(f + e, d - 1)];
+            uf[j][c][e] = f + e < d ? v : 0.f;
+          }
+        }
+      }
+    }
+  };
+  if constexpr (STAGE) load_rows(r0);             // beside the loads of the sums
   // The sums and counts of before go to this pass's copy at once; the clusters that turn out to be touched are written again below, barriers
   // later (so that their loads lie beside the others: at the end, for the kept ones alone, a clustering of 1536 samples is 2 % slower).
   double *const ps = psum + (long long)blockIdx.x * k * d;
@@ -1290,29 +1321,15 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
   }
   __syncthreads();
 
-  const int r0 = blockIdx.x * rows_per, r1 = min(N, r0 + rows_per);
   for (int b0 = r0; b0 < r1; b0 += KM_ROWS) {
-    kmv4 uf[2][NC];
     float un[2], v1[2], v2[2];
     int i1[2];
+    if (!STAGE || b0 > r0) load_rows(b0);
+    if (staged)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const float *u = U + (long long)min(b0 + wave * 32 + 16 * j + ql, N - 1) * d;
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int f = 16 * c + 4 * g;
-        if (V4) {
-          const kmv4 v = *(const kmv4 *)(u + min(f, d - 4));
-          uf[j][c] = f < d ? v : (kmv4){0.f, 0.f, 0.f, 0.f};
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float v = u[min(f + e, d - 1)];
-            uf[j][c][e] = f + e < d ? v : 0.f;
-          }
-        }
-      }
-    }
+        for (int c = 0; c < NC; ++c) *(kmv4 *)(us + (wave * 32 + 16 * j + ql) * S + 16 * c + 4 * g) = uf[j][c];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       float s = 0.f;
@@ -1410,8 +1427,7 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
   }
   if (!changed) return;                           // the same value in every thread
 
-  for (int c = wave; c < k; c += NW) {
-    if (!touched[c]) continue;
+  auto sums_of = [&](const int c, auto from_lds) {
     double s0 = 0.0, s1 = 0.0;
     int count = 0;
     const int ja = min(lane, d - 1), jb = min(lane + 64, d - 1);
@@ -1429,8 +1445,12 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             const int r = (int)__builtin_ctzll(rows);
-            a[i] = base[(long long)r * d + ja];
-            b[i] = base[(long long)r * d + jb];
+            if constexpr (from_lds()) {
+              a[i] = us[(64 * q + r) * S + ja];
+            } else {
+              a[i] = base[(long long)r * d + ja];
+              b[i] = base[(long long)r * d + jb];
+            }
             have = i + 1;
             const unsigned long long rest = rows & (rows - 1);
             if (!rest) { rows = 0; break; }
@@ -1440,7 +1460,7 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
           for (int i = 0; i < 8; ++i)
             if (i < have) {
               s0 += (double)a[i];
-              s1 += (double)b[i];
+              if constexpr (!from_lds()) s1 += (double)b[i];
             }
         }
       }
@@ -1453,6 +1473,16 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
       pcnt[blockIdx.x * k + c] = count;
       dirty[c] = 1;
     }
+  };
+  for (int c = wave; c < k; c += NW) {
+    if (!touched[c]) continue;
+    if constexpr (STAGE) {
+      if (staged) {
+        sums_of(c, std::integral_constant<bool, true>());
+        continue;
+      }
+    }
+    sums_of(c, std::integral_constant<bool, false>());
   }
 }
 
@@ -2004,7 +2034,7 @@ int embed_impl(const float *L, int N, int n, int n0, int k, int kb, int iters, c
 hipError_t launch_kmeans_pass(const float *U, int N, int d, float *centres, int k, int *labels, const SmallWork &w, int *ctl, int it, bool own,
                               long long zu, long long zlab, Group gr, hipStream_t st) {
   const int nc = (d + 15) / 16, k16 = (k + 15) / 16 * 16;
-  const size_t lds = (size_t)k16 * (16 * nc + 4 + 1) * sizeof(float);
+  const size_t lds = ((size_t)k16 * (16 * nc + 4 + 1) + (nc <= KM_STAGE_NC ? (size_t)KM_ROWS * (16 * nc + 4) : 0)) * sizeof(float);
   const bool v4 = d % 4 == 0 && aligned16(U);
   const size_t out = kmeans_own(N, d, k) ? it & 1 : 0, in = kmeans_own(N, d, k) ? out ^ 1 : 0;
 #define KM_CASE(NC)                                                                                                          \
