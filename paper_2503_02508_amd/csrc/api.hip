@@ -1220,9 +1220,9 @@ static int fp32_block(qc_ctx *ctx, const qc_block_weights_f32 &b, const float *c
 // Un-quantised fp32 forward of g samples through all blocks (the network the quantiser parameters are
 // calibrated on and the reference the VC factors are fitted against): tokens must hold the embedded samples,
 // cond their conditioning vectors [g, D].  With slots != null the min / max of the five quantiser sites of
-// every block are folded into slots[l][site][2].  The adaLN projections of the samples are rows mod_row .. of cal_mod.  o: where the attention's output goes; cal_h will do (its last reader, the
-// QKV product, is then done) unless the tokens lie in cal_o already.  Two halves of the samples run beside each other, for
-// the same reasons as in choose_lanes.
+// every block are folded into slots[l][site][2].  The adaLN projections of the samples are rows mod_row .. of cal_mod.
+// o: where the attention's output goes; cal_h will do (its last reader, the QKV product, is then done) unless the tokens lie in cal_o
+// already.  Two halves of the samples run beside each other, for the same reasons as in choose_lanes.
 static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int mod_row, int g, int *slots, float *tokens, float *o,
                        hipStream_t st) {
   const int g0 = (g + 1) / 2;

@@ -153,7 +153,8 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
         }
     }
   };
-  // straight-line steps: chunk c is in registers (set); they are requested anew for chunk c + PF NW as they become free, the activations' once they are in LDS, the weights' once they are multiplied (WROW: with the activations')
+  // straight-line steps: chunk c is in registers (set); they are requested anew for chunk c + PF NW as they become free, the activations'
+  // once they are in LDS, the weights' once they are multiplied (WROW: with the activations')
   auto step = [&](int set, int c) {
     const int next = min(c + PF * NW, nc - 1);                     // (beyond the last chunk: not used)
     store_a(set, c);

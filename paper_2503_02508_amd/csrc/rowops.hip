@@ -579,7 +579,6 @@ __global__ __launch_bounds__(256) void small_linear_kernel(const float *__restri
                             [&](int b, int n, float v) { y[(size_t)b * ldy + n] = v; });
 }
 
-
 template <int R, int NIT>
 static hipError_t launch_small_linear_as(const float *x, int ldx, int t_first, int t_step, const float *W, const float *b, float *y, int ldy,
                                          int B, int N, int K, int act_in, int act_out, hipStream_t st) {
