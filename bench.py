@@ -34,11 +34,11 @@ TAP_ITERS, TAP_MAX_PASSES = 8, 100   # power-iteration rounds and k-means pass l
 # under profiles/, keyed by (workload, kernel class).  None where no counter run covers the pair.
 TRAFFIC = {
     # profiles/sampler_cfg1_dit_xl2_b8_hbm_traffic.txt: (FETCH_SIZE * 2.0 + WRITE_SIZE * 1.0) KiB per dispatch
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc2"): (16870.0 * 2.0 + 9216.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_qkv"): (9093.3 * 2.0 + 15182.6) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc1"): (16082.6 * 2.0 + 4608.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_proj"): (6150.0 * 2.0 + 9216.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "attention"): (7048.0 * 2.0 + 1536.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc2"): (16850.1 * 2.0 + 9216.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_qkv"): (9093.3 * 2.0 + 15164.1) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc1"): (16085.6 * 2.0 + 4608.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_proj"): (6146.5 * 2.0 + 9216.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "attention"): (7048.5 * 2.0 + 1536.0) * 1024,
     # profiles/sampler_cfg2_dit_xl2_b64_cfg_hbm_traffic.txt
     ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc2"): (145813.8 * 2.0 + 147461.4) * 1024,
     ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_qkv"): (65825.1 * 2.0 + 243508.2) * 1024,
