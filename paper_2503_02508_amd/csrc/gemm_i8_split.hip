@@ -156,7 +156,7 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
   // straight-line steps: chunk c is in registers (set); they are requested anew for chunk c + PF NW as they become free, the activations'
   // once they are in LDS, the weights' once they are multiplied (WROW: with the activations')
   auto step = [&](int set, int c) {
-    const int next = min(c + PF * NW, nc - 1);                     // (beyond the last chunk: not used)
+    const int next = WROW ? c + NW : min(c + PF * NW, nc - 1);     // (beyond the last chunk: not used; WROW: there is one)
     store_a(set, c);
     load_a(set, next);
     if constexpr (WROW) load_b(set, next);
@@ -179,42 +179,60 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
   // chunk.  (Not for the larger tiles, which have no registers left for it; the residual stream's elements only where a unit has one
   // workgroup, and not where they may be bfloat16: converting would wait for them.)  One latent of 256 tokens, 50 steps: 40.5 ->
   // 39.3 ms; with 64 x 64 tiles and the stream's elements on every launch 39.5, and 8 latents 81.3 -> 83.0.
-  constexpr bool PRE = TM * TN <= 2, PREX = FEW && TM * TN <= 2 && EPI == EPI_RESID && !RBF;
+  constexpr bool PRE = !WROW && TM * TN <= 2, PREX = PRE && FEW && EPI == EPI_RESID && !RBF;
   EpiPre<EPI, TM / EM, TN / EN, PREX> pre;
-  load_a(0, min(wave, nc - 1));                                    // (a wavefront without a chunk makes no use of it)
-  load_b(0, min(wave, nc - 1));
-  if constexpr (PRE) {
-    __builtin_amdgcn_sched_barrier(0);
-    epilogue_request<BM, BN, EM, EN, EPI, PREX>(p, pre, min(wave, EM * EN - 1), m0, n0);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  // a path of its own for fewer than PF chunks: where paths with different numbers of loads in flight meet, the compiler waits for more
-  // than it has to
-  if (mine >= PF) {
-#pragma unroll
-    for (int d = 1; d < PF; ++d) request(d);
-    __builtin_amdgcn_sched_barrier(0);
-    int c = wave, left = mine;
-    for (; left > PF; left -= PF, c += PF * NW) {
-#pragma unroll
-      for (int d = 0; d < PF; ++d) step(d, c + d * NW);
+  if constexpr (WROW) {
+    // one chunk in flight, two steps a turn of the loop.  As the others (below; one step a turn, the epilogue's loads in front), float32 linears
+    // of 1 to 2048 rows took 3 % longer on average, 4-bit ones up to 11 %: 500 x 1152 x 4608 13.1 -> 14.6 us
+    if (mine > 0) {
+      load_a(0, wave);
+      load_b(0, wave);
+      int c = wave, left = mine;
+      for (; left > 2; left -= 2, c += 2 * NW) {
+        step(0, c);
+        step(0, c + NW);
+      }
+      if (left == 2) {
+        step(0, c);
+        last(0, c + NW);
+      } else {
+        last(0, c);
+      }
     }
-    last(0, c);
-    if constexpr (PF > 1) {
+  } else {
+    load_a(0, min(wave, nc - 1));                                    // (a wavefront without a chunk makes no use of it)
+    load_b(0, min(wave, nc - 1));
+    if constexpr (PRE) {
+      __builtin_amdgcn_sched_barrier(0);
+      epilogue_request<BM, BN, EM, EN, EPI, PREX>(p, pre, min(wave, EM * EN - 1), m0, n0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // a path of its own for fewer than PF chunks: where paths with different numbers of loads in flight meet, the compiler waits for more
+    // than it has to
+    if (mine >= PF) {
+#pragma unroll
+      for (int d = 1; d < PF; ++d) request(d);
+      __builtin_amdgcn_sched_barrier(0);
+      int c = wave, left = mine;
+      for (; left > PF; left -= PF, c += PF * NW) {
+#pragma unroll
+        for (int d = 0; d < PF; ++d) step(d, c + d * NW);
+      }
+      last(0, c);
       if (left > 1) {
         last(1, c + NW);
         if constexpr (PF > 2) {
           if (left > 2) last(2, c + 2 * NW);
         }
       }
+    } else if (PF > 2 && mine == 2) {
+      request(1);
+      __builtin_amdgcn_sched_barrier(0);
+      last(0, wave);
+      last(1, wave + NW);
+    } else if (mine == 1) {
+      last(0, wave);
     }
-  } else if (PF > 2 && mine == 2) {
-    request(1);
-    __builtin_amdgcn_sched_barrier(0);
-    last(0, wave);
-    last(1, wave + NW);
-  } else if (mine == 1) {
-    last(0, wave);
   }
 
   // ---- the partial sums meet.  A block is 64 lanes x 16 integers, stored as 4 x [64 lanes][4].
