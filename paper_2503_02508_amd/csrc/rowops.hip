@@ -169,9 +169,10 @@ __device__ __forceinline__ void wave_sum_pair(double &a, double &b) {
 // at once, one memory round trip.  R = 1 gives the most workgroups (small M); R = 4 puts four times the bytes in
 // flight per compute unit, which is what the memory system needs to run near its peak at large M.  The arithmetic of a
 // row, and with it every code, is the same for both.  What bounds a small launch is its chain of round trips: the parameters come with the
-// rows, the sums of a wavefront meet in lane moves and every thread finishes the statistics, behind one barrier (256 rows of
-// 1152 3.10 -> 2.86 us, 425 3.53 -> 3.08).
-template <int R>
+// rows, the sums of a wavefront meet in lane moves and, ALL, every thread finishes the statistics, behind one barrier (256 rows of
+// 1152 3.10 -> 2.86 us, 425 3.53 -> 3.08).  A large launch has the double-precision division and square root of all its wavefronts to issue
+// instead (8192 rows of 2048 25 -> 32 us): there one thread a row finishes them and a second barrier hands them on.
+template <int R, bool ALL>
 __global__ __launch_bounds__(512) void ln_mod_quant_kernel(const void *__restrict__ x, int x_bf16, const float *__restrict__ shift,
                                                            const float *__restrict__ scale, int ld_mod, int M, int D, int T,
                                                            const QParam *qp, int8_t *__restrict__ q,
@@ -215,18 +216,29 @@ __global__ __launch_bounds__(512) void ln_mod_quant_kernel(const void *__restric
     }
   }
   __syncthreads();
-  double stat[R][2];                              // every thread finishes them itself: no second exchange
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
+  const auto finish = [&](int r, double &mean, double &rstd) {
     double tot = 0.0, tot2 = 0.0;
     for (int w = 0; w < nw; ++w) {
       tot += red[r][w];
       tot2 += red[r][8 + w];
     }
-    const double mean = tot / (double)D;
+    mean = tot / (double)D;
     const double var = tot2 / (double)D - mean * mean;
-    stat[r][0] = mean;
-    stat[r][1] = 1.0 / sqrt(fmax(var, 0.0) + 1e-6);
+    rstd = 1.0 / sqrt(fmax(var, 0.0) + 1e-6);
+  };
+  double stat[R][2];
+  if constexpr (ALL) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) finish(r, stat[r][0], stat[r][1]);
+  } else {
+    __shared__ double stat_s[R][2];
+    if (threadIdx.x < R) finish(threadIdx.x, stat_s[threadIdx.x][0], stat_s[threadIdx.x][1]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      stat[r][0] = stat_s[r][0];
+      stat[r][1] = stat_s[r][1];
+    }
   }
   if (!live) return;
 #pragma unroll
@@ -424,10 +436,16 @@ hipError_t launch_ln_mod_quant(const void *x, int x_bf16, const float *shift, co
 #undef QC_LN
 #undef QC_LN_AS
   } else if (M >= 8192)
-    hipLaunchKernelGGL(ln_mod_quant_kernel<4>, dim3((M + 3) / 4), dim3(threads), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T,
+    hipLaunchKernelGGL((ln_mod_quant_kernel<4, false>), dim3((M + 3) / 4), dim3(threads), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T,
                        qp, q, f32_out);
+  else if (M * nv <= 2400 && nv < 8)
+    // every thread finishes the statistics while the launch has fewer wavefronts than the chip finishes side by side.  Every thread | one,
+    // us: 256 rows of 384 2.36 | 2.48, 512 of 768 2.75 | 2.78, 512 of 1152 3.12 | 3.09, 800 of 768 3.20 | 3.13, 800 of 1152 4.28 | 3.46; 16 rows
+    // of 1536 2.73 | 2.76, of 2048 2.63 | 2.53
+    hipLaunchKernelGGL((ln_mod_quant_kernel<1, true>), dim3(M), dim3(threads), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T, qp, q,
+                       f32_out);
   else
-    hipLaunchKernelGGL(ln_mod_quant_kernel<1>, dim3(M), dim3(threads), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T, qp, q,
+    hipLaunchKernelGGL((ln_mod_quant_kernel<1, false>), dim3(M), dim3(threads), 0, st, x, x_bf16, shift, scale, ld_mod, M, D, T, qp, q,
                        f32_out);
   return hipGetLastError();
 }

@@ -429,11 +429,11 @@ def test_reference_trajectory_of_a_fit_does_not_depend_on_the_batch(model, B, st
 
 @pytest.mark.parametrize("hidden,hw,B", [(64, (14, 10), 32), (272, (14, 10), 60), (576, (18, 14), 17), (1008, (14, 10), 61),
                                          (1152, (14, 10), 236), (1280, (50, 34), 3), (1152, (6, 6), 456),
-                                         (768, (6, 6), 73)])
+                                         (768, (6, 6), 73), (1536, (14, 10), 235), (2048, (14, 10), 20)])
 def test_layer_norm_codes_of_many_rows(hidden, hw, B):
     """A wavefront a row (1, 2 or 4 rows in turn, batch elements that end between them), which decides most codes in float32,
-    against a workgroup a row, which forms every value in float64: means far off, outliers, constant rows, ranges beyond float32's squares,
-    values that are not finite."""
+    against a workgroup a row, which forms every value in float64, each thread the statistics or one for all (wider rows: a workgroup for
+    4 rows or for one): means far off, outliers, constant rows, ranges beyond float32's squares, values that are not finite."""
     import torch
     import paper_2503_02508_amd as qc
     from qc_testlib import make_pair, oracle_calibration
@@ -463,8 +463,8 @@ def test_layer_norm_codes_of_many_rows(hidden, hw, B):
         return ctx.workspace("qact_ln", ((b1 - b0) * T, D), torch.int8).clone()
     whole = codes(0, B)
     assert B * T >= 640 and int(whole.unique().numel()) > 100
-    step = 639 // T
-    for b0 in range(0, B, max(1, step)):
-        b1 = min(B, b0 + max(1, step))
-        assert torch.equal(whole[b0 * T:b1 * T], codes(b0, b1))
+    for step in (639 // T, 2400 // -(-D // 256) // T):
+        for b0 in range(0, B, max(1, step)):
+            b1 = min(B, b0 + max(1, step))
+            assert torch.equal(whole[b0 * T:b1 * T], codes(b0, b1))
     ctx.close()
