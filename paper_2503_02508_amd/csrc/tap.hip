@@ -5,7 +5,6 @@
 #include <stdint.h>
 #include <math.h>
 #include <algorithm>
-#include <type_traits>
 #include <utility>
 #include <vector>
 #include "qc_tap.h"
@@ -1187,8 +1186,9 @@ constexpr int KM_DONE = 2, KM_PASSES = 3, KM_COUNT = 4;
 // 392 instructions of 32 cycles a wavefront, on 384 workgroups, so half the compute units have two.
 constexpr int KM_ROWS = 256;
 // Up to 16 KM_STAGE_NC dimensions, the rows of a range of one batch stay in LDS for the sums, whose chains of eight rows a round trip were
-// the longest part of a pass (1536 samples, 8 clusters 9.7 -> 8.6 us), and are requested before the centres are formed.  Clusterings of
-// 1200 to 30000 samples, up to 16 clusters: 0.5 - 2.6 % faster; with 17 to 32 dimensions too nothing gained, with 33 to 48 1 % slower.
+// the longest part of a pass.  k-means of 500 to 65536 samples, 2 to 16 dimensions, 2 to 128 clusters, 16 passes: 2 - 10 % faster (1536
+// samples, 8 of each 290 -> 270 us; 32768 446 -> 436).  With 17 to 32 dimensions too nothing gained, with 33 to 48 1 % slower; with the rows
+// requested in front of the centres, beside the loads of the sums, 32768 samples took 5 % longer.
 constexpr int KM_STAGE_NC = 1;
 typedef float kmv4 __attribute__((ext_vector_type(4)));
 
@@ -1202,7 +1202,7 @@ typedef float kmv4 __attribute__((ext_vector_type(4)));
 // either read by all (its cluster is empty) or written by workgroup 0 (it is not), and which of the two follows from the counts
 // of the pass before; labels are each range's own; the control words are read as said above, `dirty` is only set.  Without `own` the
 // two copies are one (psum_in == psum), which a workgroup reads and writes in its own range alone.
-template <int NC, bool V4>
+template <int NC, bool V4, bool STAGE>
 __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N, int d, float *centres, int k, int rows_per,
                                                           int *labels, const double *psum_in, const int *pcnt_in, double *psum, int *pcnt,
                                                           int *dirty, int *ctl, int it, int own,
@@ -1227,8 +1227,7 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
   extern __shared__ float sm[];
   const int k16 = (k + 15) & ~15;
   float *const cs = sm, *const cn = sm + k16 * S;
-  float *const us = cn + k16;                     // STAGE: the rows of a range of one batch, as the centres
-  constexpr bool STAGE = NC <= KM_STAGE_NC;
+  float *const us = cn + k16;                     // STAGE: the rows of the range, laid out as the centres
   __shared__ int lab_s[KM_ROWS], queue[KM_ROWS], queued, changed, touched[KB_MAX];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ql = lane & 15, g = lane >> 4;
   const float kappa = (float)(5 * d + 16) * 5.9604645e-8f;
@@ -1238,30 +1237,6 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
     changed = 0;
   }
   if (tid < KB_MAX) touched[tid] = it == 0;       // the first pass writes every count
-  const int r0 = blockIdx.x * rows_per, r1 = min(N, r0 + rows_per);
-  const bool staged = STAGE && r1 - r0 <= KM_ROWS;
-  kmv4 uf[2][NC];
-  auto load_rows = [&](int b0) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const float *u = U + (long long)min(b0 + wave * 32 + 16 * j + ql, N - 1) * d;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int f = 16 * c + 4 * g;
-        if (V4) {
-          const kmv4 v = *(const kmv4 *)(u + min(f, d - 4));
-          uf[j][c] = f < d ? v : (kmv4){0.f, 0.f, 0.f, 0.f};
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float v = u[min(f + e, d - 1)];
-            uf[j][c][e] = f + e < d ? v : 0.f;
-          }
-        }
-      }
-    }
-  };
-  if constexpr (STAGE) load_rows(r0);             // beside the loads of the sums
   // The sums and counts of before go to this pass's copy at once; the clusters that turn out to be touched are written again below, barriers
   // later (so that their loads lie beside the others: at the end, for the kept ones alone, a clustering of 1536 samples is 2 % slower).
   double *const ps = psum + (long long)blockIdx.x * k * d;
@@ -1285,12 +1260,26 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
           q[i] = pcnt_in[bb * k + c];
           t[i] = psum_in[((long long)bb * k + c) * d + j];
         }
+        // (a count of 0: sums of an earlier pass, or none)  Up to 16 dimensions, the additions are selects behind all loads.  The compiler may make
+        // a branch of each otherwise, or of the first sum's load, which then is a round trip of its own (a pass of 128 ranges 23 -> 25 us, of 256
+        // 51 -> 56).  With more dimensions the selects' masks spill scalar registers, which passes that are not `own` pay for too: 300000 samples
+        // of 24 1.5 % slower.
+        if constexpr (NC == 1) {
+          asm volatile("" ::: "memory");
 #pragma unroll
-        for (int i = 0; i < AHEAD; ++i)
-          if (b + i < (int)gridDim.x && q[i] > 0) {         // a count of 0: sums of an earlier pass, or none
-            tot += t[i];
-            m += q[i];
+          for (int i = 0; i < AHEAD; ++i) {
+            const bool have = b + i < (int)gridDim.x && q[i] > 0;
+            tot += have ? t[i] : 0.0;
+            m += have ? q[i] : 0;
           }
+        } else {
+#pragma unroll
+          for (int i = 0; i < AHEAD; ++i)
+            if (b + i < (int)gridDim.x && q[i] > 0) {
+              tot += t[i];
+              m += q[i];
+            }
+        }
       }
       stored = m <= 0;
       if (!stored) {
@@ -1321,15 +1310,30 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
   }
   __syncthreads();
 
+  const int r0 = blockIdx.x * rows_per, r1 = min(N, r0 + rows_per);
   for (int b0 = r0; b0 < r1; b0 += KM_ROWS) {
+    kmv4 uf[2][NC];
     float un[2], v1[2], v2[2];
     int i1[2];
-    if (!STAGE || b0 > r0) load_rows(b0);
-    if (staged)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j) {
+      const float *u = U + (long long)min(b0 + wave * 32 + 16 * j + ql, N - 1) * d;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) *(kmv4 *)(us + (wave * 32 + 16 * j + ql) * S + 16 * c + 4 * g) = uf[j][c];
+      for (int c = 0; c < NC; ++c) {
+        const int f = 16 * c + 4 * g;
+        if (V4) {
+          const kmv4 v = *(const kmv4 *)(u + min(f, d - 4));
+          uf[j][c] = f < d ? v : (kmv4){0.f, 0.f, 0.f, 0.f};
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v = u[min(f + e, d - 1)];
+            uf[j][c][e] = f + e < d ? v : 0.f;
+          }
+        }
+        if constexpr (STAGE) *(kmv4 *)(us + (wave * 32 + 16 * j + ql) * S + f) = uf[j][c];
+      }
+    }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       float s = 0.f;
@@ -1427,7 +1431,8 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
   }
   if (!changed) return;                           // the same value in every thread
 
-  auto sums_of = [&](const int c, auto from_lds) {
+  for (int c = wave; c < k; c += NW) {
+    if (!touched[c]) continue;
     double s0 = 0.0, s1 = 0.0;
     int count = 0;
     const int ja = min(lane, d - 1), jb = min(lane + 64, d - 1);
@@ -1445,7 +1450,7 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             const int r = (int)__builtin_ctzll(rows);
-            if constexpr (from_lds()) {
+            if constexpr (STAGE) {
               a[i] = us[(64 * q + r) * S + ja];
             } else {
               a[i] = base[(long long)r * d + ja];
@@ -1460,7 +1465,7 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
           for (int i = 0; i < 8; ++i)
             if (i < have) {
               s0 += (double)a[i];
-              if constexpr (!from_lds()) s1 += (double)b[i];
+              if constexpr (!STAGE) s1 += (double)b[i];
             }
         }
       }
@@ -1473,16 +1478,6 @@ __global__ __launch_bounds__(512) void kmeans_pass_kernel(const float *U, int N,
       pcnt[blockIdx.x * k + c] = count;
       dirty[c] = 1;
     }
-  };
-  for (int c = wave; c < k; c += NW) {
-    if (!touched[c]) continue;
-    if constexpr (STAGE) {
-      if (staged) {
-        sums_of(c, std::integral_constant<bool, true>());
-        continue;
-      }
-    }
-    sums_of(c, std::integral_constant<bool, false>());
   }
 }
 
@@ -2031,15 +2026,23 @@ int embed_impl(const float *L, int N, int n, int n0, int k, int kb, int iters, c
   return QC_OK;
 }
 
+template <int NC>
+auto kmeans_kernel(bool v4, bool stage) {
+  if constexpr (NC <= KM_STAGE_NC)
+    if (stage) return v4 ? kmeans_pass_kernel<NC, true, true> : kmeans_pass_kernel<NC, false, true>;
+  return v4 ? kmeans_pass_kernel<NC, true, false> : kmeans_pass_kernel<NC, false, false>;
+}
+
 hipError_t launch_kmeans_pass(const float *U, int N, int d, float *centres, int k, int *labels, const SmallWork &w, int *ctl, int it, bool own,
                               long long zu, long long zlab, Group gr, hipStream_t st) {
   const int nc = (d + 15) / 16, k16 = (k + 15) / 16 * 16;
-  const size_t lds = ((size_t)k16 * (16 * nc + 4 + 1) + (nc <= KM_STAGE_NC ? (size_t)KM_ROWS * (16 * nc + 4) : 0)) * sizeof(float);
+  const bool stage = nc <= KM_STAGE_NC && kmeans_rows_per(N) <= KM_ROWS;
+  const size_t lds = ((size_t)k16 * (16 * nc + 4 + 1) + (stage ? (size_t)KM_ROWS * (16 * nc + 4) : 0)) * sizeof(float);
   const bool v4 = d % 4 == 0 && aligned16(U);
   const size_t out = kmeans_own(N, d, k) ? it & 1 : 0, in = kmeans_own(N, d, k) ? out ^ 1 : 0;
 #define KM_CASE(NC)                                                                                                          \
   case NC: {                                                                                                                 \
-    const auto kern = v4 ? kmeans_pass_kernel<NC, true> : kmeans_pass_kernel<NC, false>;                                     \
+    const auto kern = kmeans_kernel<NC>(v4, stage);                                                                          \
     const hipError_t e = it == 0 ? set_lds((const void *)kern, lds) : hipSuccess;                                            \
     if (e != hipSuccess) return e;                                                                                           \
     hipLaunchKernelGGL(kern, dim3(kmeans_blocks(N), 1, (unsigned)gr.nz), dim3(512), lds, st, U, N, d, centres, k, kmeans_rows_per(N), \

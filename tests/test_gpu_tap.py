@@ -472,6 +472,8 @@ def test_edge_shapes(qc):
 @pytest.mark.parametrize("N,d,k", [
     (70000, 8, 4),            # ranges of 274 rows, two batches each; centres formed by the passes themselves (256 x 32 sums)
     (70000, 7, 6),            # the same ranges, element loads, centres by a kernel of their own
+    (65536, 4, 10),           # the largest ranges of one batch, whose rows stay in LDS
+    (5000, 13, 39),           # the same, element loads, more centres than a turn of the threads forms
     (2600, 31, 10),           # element loads, two chunks of 16 dimensions
     (1537, 24, 40),           # 6720 sums
     (1537, 24, 72),           # 12096: beyond the rule
