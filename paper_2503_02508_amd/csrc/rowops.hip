@@ -629,9 +629,10 @@ hipError_t launch_small_linear(const float *x, int ldx, int t_first, int t_step,
   return launch_small_linear_rows<8>(x, ldx, t_first, t_step, W, b, y, ldy, B, N, K, act_in, act_out, st);
 }
 
-// The same for one linear layer per block in one launch (grid z): the weights of all blocks stream from memory once for all rows,
+// The same for one linear layer per block in one launch (grid z): the weights of all blocks stream from memory once for up to eight rows,
 // where a launch per block and half of the samples stood in the chain of the un-quantised network (18 us each, DiT-XL/2, two samples).
-// A workgroup takes 4 x 16 outputs, which share the activated inputs.  With the gated additions in the products' epilogues (4.6 us
+// Four rows at a time | eight, us, 28 blocks of width 1152: 4 rows 274 | 292, 8 rows 524 | 328, 64 rows 3654 | 2175 (a launch a block 4671); 12
+// of 384: 64 rows 343 | 127 (239).  A workgroup takes 4 x 16 outputs, which share the activated inputs.  With the gated additions in the products' epilogues (4.6 us
 // each), a factor fit of 3 steps and 2 latents takes 19.3 -> 18.4 ms.
 constexpr int BL_TILES = 4;
 template <int R, int NIT>
@@ -655,7 +656,11 @@ __global__ __launch_bounds__(256) void block_linears_kernel(BlockLinears w, cons
 template <int R, int NIT>
 static hipError_t launch_block_linears_as(const BlockLinears &w, int n, const float *x, float *y, size_t block_stride, int B, int N, int K,
                                           hipStream_t st) {
-  const size_t smem = (size_t)R * K * sizeof(double);            // 64 KB at most
+  const size_t smem = (size_t)R * K * sizeof(double);
+  if (smem > 64 * 1024) {                         // as for one linear
+    static std::atomic<unsigned long long> lds{0};
+    if (const hipError_t e = allow_lds((const void *)block_linears_kernel<R, NIT>, R * 256 * NIT * (int)sizeof(double), lds)) return e;
+  }
   hipLaunchKernelGGL((block_linears_kernel<R, NIT>), dim3((N + 16 * BL_TILES - 1) / (16 * BL_TILES), (B + R - 1) / R, n), dim3(256), smem, st, w, x,
                      y, block_stride, B, N, K);
   return hipGetLastError();
@@ -675,7 +680,8 @@ hipError_t launch_block_linears(const BlockLinears &w, int n, const float *x, fl
   if (K % 4 || K > 2048 || n > BLOCK_LINEARS) return hipErrorInvalidValue;
   if (B <= 1) return launch_block_linears_rows<1>(w, n, x, y, block_stride, B, N, K, st);
   if (B <= 2) return launch_block_linears_rows<2>(w, n, x, y, block_stride, B, N, K, st);
-  return launch_block_linears_rows<4>(w, n, x, y, block_stride, B, N, K, st);
+  if (B <= 4) return launch_block_linears_rows<4>(w, n, x, y, block_stride, B, N, K, st);
+  return launch_block_linears_rows<8>(w, n, x, y, block_stride, B, N, K, st);
 }
 
 // ----------------------------------------------------------- conditioning
