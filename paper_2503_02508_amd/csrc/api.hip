@@ -21,7 +21,7 @@ constexpr int NUM_SIDE = 3;
 constexpr int WINDOW_ROWS = 512;
 // token rows of one group of the un-quantised forward
 constexpr size_t CAL_ROWS = 1024;
-// rows of conditioning whose adaLN projections the un-quantised forward makes at once (one group of samples at least)
+// rows of conditioning whose adaLN projections the un-quantised forward makes for all blocks at once
 constexpr size_t CAL_MOD_ROWS = 8;
 
 // a contiguous range of the (effective) batch handled by one stream; `lane` picks its private scratch
@@ -108,7 +108,7 @@ struct qc_ctx {
   bool keep_qkv_f32 = false;
   bool stream_bf16 = false;   // the network-level calls keep the residual stream (tokens) as bfloat16
   // scratch of the un-quantised forward (calibration, VC fit), which runs cal_group samples at a time
-  int cal_group, cal_mod_rows;
+  int cal_group, cal_mod_rows;                    // cal_mod_rows: rows of cal_mod, CAL_MOD_ROWS a block and a group's at least
   float *cal_h, *cal_o, *cal_u, *cal_mod, *cal_cond;
   int *cal_slots, *cal_label;
   bool weights_loaded;
@@ -233,7 +233,7 @@ static size_t layout(const qc_model_desc &d, int max_batch, char *base, qc_ctx *
   // read the float32 weights once per group
   const size_t G = std::max<size_t>(1, std::min<size_t>(B, CAL_ROWS / T)), GT = G * T;
   float *cal_h = a.take<float>(GT * D), *cal_o = a.take<float>(GT * D);
-  float *cal_u = a.take<float>(GT * R), *cal_mod = a.take<float>(L * std::max(G, CAL_MOD_ROWS) * 6 * D), *cal_cond = a.take<float>(G * D);
+  float *cal_u = a.take<float>(GT * R), *cal_mod = a.take<float>(std::max(G, L * CAL_MOD_ROWS) * 6 * D), *cal_cond = a.take<float>(G * D);
   int *cal_slots = a.take<int>(L * QC_NUM_SITES * 2), *cal_label = a.take<int>(G);
   float *eps_ref = a.take<float>(B * C * d.latent_h * d.latent_w);
   double *vcfit_work = a.take<double>(B * C * 2);
@@ -244,7 +244,7 @@ static size_t layout(const qc_model_desc &d, int max_batch, char *base, qc_ctx *
     c->dev_qp = dev_qp; c->cache = cache; c->h1 = h1; c->te = te; c->cond = cond; c->mod = mod; c->fmod = fmod;
     c->tokens = tokens; c->qkv = qkv; c->eps = eps; c->silu_q = silu_q; c->qa_ln = qa_ln; c->qa_attn = qa_attn;
     c->qa_mlp = qa_mlp; c->cal_h = cal_h; c->cal_o = cal_o; c->cal_u = cal_u; c->cal_mod = cal_mod;
-    c->cal_cond = cal_cond; c->cal_group = (int)G; c->cal_mod_rows = (int)std::max(G, CAL_MOD_ROWS);
+    c->cal_cond = cal_cond; c->cal_group = (int)G; c->cal_mod_rows = (int)std::max(G, L * CAL_MOD_ROWS);
     c->cal_slots = cal_slots; c->cal_label = cal_label; c->eps_ref = eps_ref; c->vcfit_work = vcfit_work; c->dev_flags = dev_flags;
     c->qkv_hm = qkv_hm; c->qkv_part_stride = (long long)part;
     c->qkv_hm_bytes = (2 * part + vpart) * sizeof(float); c->DP = (int)DP; c->Tp = (int)Tp;
@@ -1174,18 +1174,18 @@ static inline float ord2f(int i) {
 
 }  // extern "C"
 
-// The adaLN projections of every block for `rows` conditioning vectors (cal_mod_rows at most): cal_mod[l, r, :], cal_mod_rows rows a block.
-static int fp32_mods(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int rows, hipStream_t st) {
+// The adaLN projections of blocks l0 .. l0 + nl for `rows` conditioning vectors: mod[l - l0, r, :], `block_rows` rows a block.
+static int fp32_mods(qc_ctx *ctx, const qc_weights_f32 *w, int l0, int nl, const float *cond, int rows, float *mod, int block_rows, hipStream_t st) {
   const int D = ctx->D;
-  const size_t stride = (size_t)ctx->cal_mod_rows * 6 * D;
-  for (int l = 0; l < ctx->L; l += BLOCK_LINEARS) {
+  const size_t stride = (size_t)block_rows * 6 * D;
+  for (int l = 0; l < nl; l += BLOCK_LINEARS) {
     BlockLinears b{};
-    const int n = std::min(BLOCK_LINEARS, ctx->L - l);
+    const int n = std::min(BLOCK_LINEARS, nl - l);
     for (int i = 0; i < n; ++i) {
-      b.W[i] = w->blocks[l + i].ada_w;
-      b.b[i] = w->blocks[l + i].ada_b;
+      b.W[i] = w->blocks[l0 + l + i].ada_w;
+      b.b[i] = w->blocks[l0 + l + i].ada_b;
     }
-    QC_HIP(launch_block_linears(b, n, cond, ctx->cal_mod + l * stride, stride, rows, 6 * D, D, st));
+    QC_HIP(launch_block_linears(b, n, cond, mod + l * stride, stride, rows, 6 * D, D, st));
   }
   return QC_OK;
 }
@@ -1220,13 +1220,21 @@ static int fp32_block(qc_ctx *ctx, const qc_block_weights_f32 &b, const float *c
 // Un-quantised fp32 forward of g samples through all blocks (the network the quantiser parameters are
 // calibrated on and the reference the VC factors are fitted against): tokens must hold the embedded samples,
 // cond their conditioning vectors [g, D].  With slots != null the min / max of the five quantiser sites of
-// every block are folded into slots[l][site][2].  The adaLN projections of the samples are rows mod_row .. of cal_mod.
-// o: where the attention's output goes; cal_h will do (its last reader, the QKV product, is then done) unless the tokens lie in cal_o
+// every block are folded into slots[l][site][2].  The adaLN projections of the samples are rows mod_row .. of each block's CAL_MOD_ROWS in
+// cal_mod, or are made here (mod_row < 0): for all blocks at once if they fit there, else for as many blocks at a time as cal_mod holds, by each
+// half for itself.  o: where the attention's output goes; cal_h will do (its last reader, the QKV product, is then done) unless the tokens lie in cal_o
 // already.  Two halves of the samples run beside each other, for the same reasons as in choose_lanes.
 static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, int mod_row, int g, int *slots, float *tokens, float *o,
                        hipStream_t st) {
   const int g0 = (g + 1) / 2;
+  const size_t mod_row_len = (size_t)6 * ctx->D;
+  const int at_once = g <= (int)CAL_MOD_ROWS ? 0 : std::min(ctx->L, ctx->cal_mod_rows / g);      // blocks whose projections a half makes at a time
   int rc = QC_OK;
+  if (mod_row < 0 && at_once == 0) {
+    rc = fp32_mods(ctx, w, 0, ctx->L, cond, g, ctx->cal_mod, (int)CAL_MOD_ROWS, st);
+    if (rc) return rc;
+    mod_row = 0;
+  }
   hipStream_t side[2] = {st, st};
   if (g > g0) {
     rc = make_events({&ctx->ev_f32_fork, &ctx->ev_f32_join[0], &ctx->ev_f32_join[1]});
@@ -1237,7 +1245,16 @@ static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, 
   }
   for (int l = 0; l < ctx->L && !rc; ++l) {
     int *slot = slots ? slots + (size_t)l * QC_NUM_SITES * 2 : nullptr;
-    const float *mod = ctx->cal_mod + ((size_t)l * ctx->cal_mod_rows + mod_row) * 6 * ctx->D;
+    float *mod = ctx->cal_mod + ((size_t)l * CAL_MOD_ROWS + mod_row) * mod_row_len;
+    if (mod_row < 0) {
+      mod = ctx->cal_mod + (size_t)(l % at_once) * g * mod_row_len;
+      if (l % at_once == 0) {                       // (behind the half's last block that read the former ones)
+        const int nl = std::min(at_once, ctx->L - l);
+        rc = fp32_mods(ctx, w, l, nl, cond, g0, mod, g, side[0]);
+        if (!rc && g > g0) rc = fp32_mods(ctx, w, l, nl, cond + (size_t)g0 * ctx->D, g - g0, mod + g0 * mod_row_len, g, side[1]);
+        if (rc) break;
+      }
+    }
     rc = fp32_block(ctx, w->blocks[l], cond, mod, 0, g0, slot, tokens, o, side[0]);
     if (!rc && g > g0) rc = fp32_block(ctx, w->blocks[l], cond, mod, g0, g - g0, slot, tokens, o, side[1]);
   }
@@ -1250,7 +1267,7 @@ static int fp32_blocks(qc_ctx *ctx, const qc_weights_f32 *w, const float *cond, 
 
 // eps[B] of the un-quantised network with the conditioning vectors in rows r0 .. of cond and fmod; x holds n_src latents, batch
 // element b reads latent b % n_src (guidance runs the same latents with the labels and with the null label).  Their adaLN projections
-// are rows mod_row .. of cal_mod, or are made here (mod_row < 0).
+// are rows mod_row .. of each block's in cal_mod, or are made on the way (mod_row < 0).
 static int denoise_f32_prepared(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, int n_src, size_t r0, int mod_row, int B, float *eps_out,
                                 float *tokens, float *o, hipStream_t st) {
   const int D = ctx->D;
@@ -1259,8 +1276,7 @@ static int denoise_f32_prepared(qc_ctx *ctx, const qc_weights_f32 *w, const floa
     const int g = std::min(ctx->cal_group, B - b);
     QC_HIP(launch_embed(x, ctx->patch_w, ctx->patch_b, ctx->pos, tokens, 0, g, n_src, ctx->C, ctx->d.latent_h, ctx->d.latent_w,
                         ctx->d.patch, D, b, st));
-    int rc = mod_row < 0 ? fp32_mods(ctx, w, ctx->cond + (r0 + b) * D, g, st) : QC_OK;
-    if (!rc) rc = fp32_blocks(ctx, w, ctx->cond + (r0 + b) * D, mod_row < 0 ? 0 : mod_row + b, g, nullptr, tokens, o, st);
+    const int rc = fp32_blocks(ctx, w, ctx->cond + (r0 + b) * D, mod_row < 0 ? -1 : mod_row + b, g, nullptr, tokens, o, st);
     if (rc) return rc;
     QC_HIP(launch_final(tokens, 0, ctx->fmod + (r0 + b) * 2 * D, ctx->flin_w, ctx->flin_b, eps_out + b * lat, g, ctx->C,
                         ctx->d.latent_h, ctx->d.latent_w, ctx->d.patch, D, st));
@@ -1315,8 +1331,7 @@ int qc_calibrate_minmax(qc_ctx *ctx, const qc_weights_f32 *w, const float *x, co
     }
     QC_HIP(launch_embed(x + i * lat, ctx->patch_w, ctx->patch_b, ctx->pos, ctx->tokens, 0, g, g, ctx->C, ctx->d.latent_h,
                         ctx->d.latent_w, ctx->d.patch, D, 0, st));
-    rc = fp32_mods(ctx, w, ctx->cal_cond, g, st);
-    if (!rc) rc = fp32_blocks(ctx, w, ctx->cal_cond, 0, g, ctx->cal_slots, ctx->tokens, ctx->cal_o, st);
+    rc = fp32_blocks(ctx, w, ctx->cal_cond, -1, g, ctx->cal_slots, ctx->tokens, ctx->cal_o, st);
     if (rc) return rc;
     QC_HIP(hipStreamSynchronize(st));        // the labels are the caller's host memory
   }
@@ -1446,8 +1461,8 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
     QC_HIP(hipStreamWaitEvent(rs, ctx->ev_ready, 0));
   }
   float *tokens = beside ? ctx->cal_o : ctx->tokens, *o = beside ? ctx->cal_h : ctx->cal_o;
-  // the un-quantised network's adaLN projections of as many steps at once as cal_mod holds
-  const int mod_steps = ctx->cal_mod_rows / Beff;
+  // the un-quantised network's adaLN projections of as many steps at once as cal_mod holds for all blocks
+  const int mod_steps = (int)CAL_MOD_ROWS / Beff;
   const auto step = [&](int i, int w_slot, int nw) -> int {
     const double cx = std::sqrt(ap[i] / at[i]);
     const double ce = std::sqrt(1.0 - ap[i]) - cx * std::sqrt(1.0 - at[i]);
@@ -1455,7 +1470,9 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
     int r = QC_OK, mod_row = -1;
     if (mod_steps > 0) {
       mod_row = w_slot % mod_steps * Beff;
-      if (mod_row == 0) r = fp32_mods(ctx, w, ctx->cond + (size_t)w_slot * Beff * D, std::min(mod_steps, nw - w_slot) * Beff, rs);
+      if (mod_row == 0)
+        r = fp32_mods(ctx, w, 0, ctx->L, ctx->cond + (size_t)w_slot * Beff * D, std::min(mod_steps, nw - w_slot) * Beff, ctx->cal_mod,
+                      (int)CAL_MOD_ROWS, rs);
       if (r) return r;
     }
     r = denoise_f32_prepared(ctx, w, x_ref, B, (size_t)w_slot * Beff, mod_row, Beff, ctx->eps_ref, tokens, o, rs);

@@ -59,6 +59,17 @@ def test_arena_bytes_and_bad_descriptions(qc):
     assert qc.lib.qc_arena_bytes(C.byref(_desc(qc)), 4, None) == -1
 
 
+def test_arena_of_large_batches_of_small_latents(qc):
+    """What a block adds to the arena grows with the batch by its two cached outputs; the un-quantised forward's projections do not grow with both."""
+    def size(depth, batch):
+        n = C.c_size_t()
+        assert qc.lib.qc_arena_bytes(C.byref(_desc(qc, depth=depth, latent_h=4, latent_w=4, patch=2)), batch, C.byref(n)) == 0
+        return n.value
+    D = _desc(qc).hidden
+    grown = (size(28, 256) - size(20, 256)) - (size(28, 8) - size(20, 8))
+    assert grown <= 8 * 2 * (256 - 8) * 4 * D * 4 + 64 * 256, grown              # 4 tokens a sample; 256-byte steps
+
+
 def test_create_rejects_bad_arenas_without_a_device(qc):
     h = C.c_void_p()
     d = _desc(qc)

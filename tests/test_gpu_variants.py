@@ -405,6 +405,8 @@ def test_single_steps_equal_a_window_of_steps(model, wb, B, cfg):
 @pytest.mark.parametrize("model,B,steps,cfg", [
     (replace(_net(48, 4, 112, 10, 14), depth=34), 3, 5, 0.0),         # more blocks than a launch takes; two steps' projections at once
     (replace(_net(32, 2, 64, 64, 64), depth=2), 5, 2, 1.5),           # ten rows of conditioning, samples one at a time
+    (replace(_net(64, 4, 128, 4, 4), depth=34), 21, 2, 1.5),          # 42 rows together: the projections of six blocks at a time
+    (replace(_net(32, 2, 64, 4, 4), depth=2), 19, 2, 0.0),            # 19 rows, more than eight a block: one block at a time
     (replace(_net(2048, 32, 2048, 4, 4), depth=1), 5, 3, 0.0)])       # widest row
 def test_reference_trajectory_of_a_fit_does_not_depend_on_the_batch(model, B, steps, cfg):
     """The un-quantised trajectory beside the quantised one: adaLN projections of several steps at once against one latent's."""
