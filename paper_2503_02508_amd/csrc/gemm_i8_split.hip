@@ -40,7 +40,10 @@ constexpr int split_en(int tm, int tn, int nw) {
 // 80.2 (fc2).
 constexpr int split_depth(int tm, int tn, bool few, bool wrow) { return wrow ? 1 : few && tm * tn == 2 ? 3 : 2; }
 
-// FEW: no more tiles than compute units.
+// whether a kernel differs with FEW
+constexpr bool split_few(int tm, int tn, bool wrow) { return !wrow && tm * tn <= 2; }
+
+// FEW: no more tiles than compute units (32 x 32 tiles are never more than 126; false for the kernels that are the same either way).
 template <int TM, int TN, int NW, int EPI, bool W4, bool WROW, bool RBF, bool FEW>
 __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void gemm_i8_split_kernel(GemmArgs p) {
   constexpr int BM = 32 * TM, BN = 32 * TN, NB = TM * TN, CK = 128;
@@ -308,8 +311,10 @@ static hipError_t launch_split(const GemmArgs &a, hipStream_t st) {
   static std::atomic<unsigned long long> lds[2];
   GemmArgs b = a;
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
-  const bool few = (long long)tiles_m * tiles_n <= 256;
-  auto kern = few ? gemm_i8_split_kernel<TM, TN, NW, EPI, W4, WROW, RBF, true> : gemm_i8_split_kernel<TM, TN, NW, EPI, W4, WROW, RBF, false>;
+  const bool few = split_few(TM, TN, WROW) && (TM * TN == 1 || (long long)tiles_m * tiles_n <= 256);
+  auto kern = gemm_i8_split_kernel<TM, TN, NW, EPI, W4, WROW, RBF, split_few(TM, TN, WROW)>;
+  if constexpr (split_few(TM, TN, WROW) && TM * TN > 1)
+    if (!few) kern = gemm_i8_split_kernel<TM, TN, NW, EPI, W4, WROW, RBF, false>;
   if (const hipError_t e = allow_lds((const void *)kern, smem, lds[few])) return e;
   b.xcd_m = xcd_rows(tiles_m, tiles_n, (double)a.M * a.K, (double)a.N * a.K * (W4 ? 0.5 : 1.0));
   const int cm = (tiles_m + b.xcd_m - 1) / b.xcd_m, xn = NUM_XCD / b.xcd_m, cn = (tiles_n + xn - 1) / xn;
