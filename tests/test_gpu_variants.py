@@ -393,12 +393,15 @@ def test_single_steps_equal_a_window_of_steps(model, wb, B, cfg):
     qp, _, _ = oracle_calibration(model, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
     _, ctx = make_pair(model, w, qp, 2 * B if cfg else B, 2)
     K = _cuda(I.make_vc_factors(4, model.latent_c, 44))
-    whole, single, labels = _cuda(lat), _cuda(lat), _cuda(lab.astype(np.int32))
-    ctx.sample(whole, labels, 4, cfg, K)
-    for i, (t, at, ap) in enumerate(zip(*qc.qc_ddim_schedule(4))):
-        ctx.sample_step(single, labels, i, t, at, ap, cfg, K[i])
-    assert torch.equal(whole, single)
-    assert float((whole - _cuda(lat)).abs().max()) > 0
+    labels = _cuda(lab.astype(np.int32))
+    for stream in ("fp32", "bf16"):
+        ctx.set_stream_format(stream)
+        whole, single = _cuda(lat), _cuda(lat)
+        ctx.sample(whole, labels, 4, cfg, K)
+        for i, (t, at, ap) in enumerate(zip(*qc.qc_ddim_schedule(4))):
+            ctx.sample_step(single, labels, i, t, at, ap, cfg, K[i])
+        assert torch.equal(whole, single), stream
+        assert float((whole - _cuda(lat)).abs().max()) > 0
     ctx.close()
 
 
@@ -469,4 +472,42 @@ def test_layer_norm_codes_of_many_rows(hidden, hw, B):
         for b0 in range(0, B, max(1, step)):
             b1 = min(B, b0 + max(1, step))
             assert torch.equal(whole[b0 * T:b1 * T], codes(b0, b1))
+    ctx.close()
+
+
+@pytest.mark.parametrize("hidden,B", [(64, 480), (272, 40), (272, 240), (576, 480), (1008, 40), (1152, 240)])
+def test_layer_norm_of_many_bfloat16_rows(hidden, B):
+    """The same with a bfloat16 stream (launches of 700 to 16800 rows, 1, 2 or 4 to a wavefront, against 630): every module output of a block
+    and the noise estimate, for tokens of all sizes, equal ones, and ones that are not finite."""
+    import torch
+    import paper_2503_02508_amd as qc
+    from qc_testlib import make_pair, oracle_calibration
+    model = _net(hidden, hidden // 16, 64, 14, 10)
+    w = I.make_weights(model, 71)
+    lat, lab = I.make_latents(B, model, 72), I.make_labels(B, model, 73).astype(np.int32)
+    qp, _, _ = oracle_calibration(model, w, lat=lat[:1], lab=lab[:1], t=np.array([400]))
+    _, ctx = make_pair(model, w, qp, B, 2)
+    ctx.set_stream_format("bf16")
+    kind = np.arange(B) % 16
+    lat[kind == 1] *= 1e4
+    lat[kind == 2] = 0.0
+    lat[kind == 3] += 300.0
+    lat[kind == 4] *= 1e25
+    lat[kind == 5, 0, 3, 3] = np.inf
+    lat[kind == 6, 1, 0, 9] = np.nan
+    lat[kind == 7, 2, 5, 5] = 3e4
+    lat[kind == 8] *= 1e-25
+    x, y = _cuda(lat), _cuda(lab)
+
+    def run(b0, b1):
+        eps = torch.empty_like(x[b0:b1])
+        ctx.denoise(x[b0:b1], 500, y[b0:b1], b1 - b0, qc.QC_FULL, eps)
+        return eps, *(ctx.cache_tensor(0, m, b1 - b0).clone() for m in (qc.QC_CACHE_ATTN, qc.QC_CACHE_MLP))
+    whole = run(0, B)
+    fine = torch.from_numpy((kind < 4) | (kind > 6)).cuda()
+    assert bool(whole[0][fine].isfinite().all()) and float(whole[0][fine].abs().max()) > 0
+    for b0 in range(0, B, 18):
+        b1 = min(B, b0 + 18)
+        for name, a, b in zip(("eps", "attention", "mlp"), whole, run(b0, b1)):
+            assert torch.allclose(a[b0:b1], b, rtol=0, atol=0, equal_nan=True), (name, b0)
     ctx.close()
