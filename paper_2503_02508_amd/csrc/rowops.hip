@@ -147,8 +147,8 @@ __device__ __forceinline__ void swap_rows(double a, double b, double &a2, double
   b2 = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
 }
 
-// Both sums of a wavefront at once, in every lane: lanes 0 .. 31 take over the first, 32 .. 63 the second.
-__device__ __forceinline__ void wave_sum_pair(double &a, double &b) {
+// Both sums of a wavefront at once: the first in lanes 0 .. 31, the second in 32 .. 63 ...
+__device__ __forceinline__ double wave_sum_halves(double a, double b) {
   double v, w;
   swap_rows<32>(a, b, v, w);
   v += w;
@@ -157,7 +157,11 @@ __device__ __forceinline__ void wave_sum_pair(double &a, double &b) {
   v += dpp_move_d<0x141>(v);
   v += dpp_move_d<0x140>(v);
   swap_rows<16>(v, v, v, w);
-  v += w;
+  return v + w;
+}
+// ... and both in every lane.
+__device__ __forceinline__ void wave_sum_pair(double &a, double &b) {
+  const double v = wave_sum_halves(a, b);
   swap_rows<32>(v, v, a, b);
 }
 
@@ -351,16 +355,7 @@ __global__ __launch_bounds__(256) void ln_mod_quant_wave_kernel(const void *__re
       sum += (a0 + a1) + (a2 + a3);
       sq = fma(a0, a0, fma(a1, a1, fma(a2, a2, fma(a3, a3, sq))));
     }
-    // both sums at once: lanes 0 .. 31 take over the values', 32 .. 63 the squares'
-    double v, w2;
-    swap_rows<32>(sum, sq, v, w2);
-    v += w2;
-    v += dpp_move_d<0xB1>(v);     // as in wave_sum_dpp
-    v += dpp_move_d<0x4E>(v);
-    v += dpp_move_d<0x141>(v);
-    v += dpp_move_d<0x140>(v);
-    swap_rows<16>(v, v, v, w2);
-    v += w2;
+    double v = wave_sum_halves(sum, sq);
     const double est = v * inv_d;                  // v / D: the quotient's estimate with its remainder divided once more
     v = fabs(est) < 1e300 ? fma(fma(-est, (double)D, v), inv_d, est) : est;
     double mean, var;
