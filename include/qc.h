@@ -317,7 +317,10 @@ int qc_vc_fit_sampler(qc_ctx *ctx, const qc_weights_f32 *w, float *x_hat, float 
 
 /* Kernel classes of the per-launch timing below. */
 enum {
-  QC_K_ADALN = 0,          /* batched adaLN projection GEMM (all blocks, M = batch)      */
+  QC_K_ADALN = 0,          /* batched adaLN projection GEMM (all blocks, M = batch); in a
+                              qc_denoise / qc_sample_step of at most 8 rows and 2048 tokens
+                              in one part the same launch also makes the final layer's
+                              modulation (2D x D, float32)                                */
   QC_K_LN_QUANT = 1,       /* LayerNorm + modulate + quantise (two per block)            */
   QC_K_GEMM_QKV = 2,       /* QKV GEMM + dequantise                                       */
   QC_K_ATTENTION = 3,      /* softmax(QK^T)V + quantise                                   */

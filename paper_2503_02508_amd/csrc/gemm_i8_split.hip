@@ -9,7 +9,8 @@
 //     16-byte chunks swizzled with the row's low three bits (conflict-free writes and reads).
 //   * weights in fragment order go straight to registers; row-major ones (WROW: the caller's matrix of qc_w8a8_linear) take
 //     the activations' way.
-//   * the loads of the next two chunks are in flight while a chunk is multiplied, of three where a compute unit has no second tile.
+//   * the first two chunks are requested at once (three where a compute unit has no second tile); from then on the activations of that many
+//     chunks are ahead of the one that is multiplied, the weights of one less: their registers are free only behind the products.
 // What bounds it: the 60 bytes per clock a compute unit draws from its L2 (32 TM + 32 TN rows of K bytes per tile), and the
 // fixed costs around it (launch, first memory round trip, reduction, epilogue).
 #include "gemm_i8_epilogue.h"
@@ -32,11 +33,11 @@ constexpr int split_en(int tm, int tn, int nw) {
   return best;
 }
 
-// Chunks of a wavefront in flight.  What a launch of few tiles waits for are round trips to weights that lie in HBM, one after the
-// other; K = 1152 is three chunks a wavefront, all requested before the first is multiplied.  32 x 64 tiles of which a compute unit
-// has several keep to two (160 registers, three workgroups a unit: with three chunks fc1 at 256 rows 10.8 -> 12.2 us, proj at 1024 rows
+// Chunks of a wavefront that are requested before it multiplies the first, and register sets.  What a launch of few tiles waits for are round
+// trips to weights that lie in HBM, one after the other; K = 1152 is three chunks a wavefront.  32 x 64 tiles of which a compute unit has
+// several, and 32 x 32 ones (one or two chunks a wavefront up to K = 2048), keep to two (160 registers, three workgroups a unit: with three chunks fc1 at 256 rows 10.8 -> 12.2 us, proj at 1024 rows
 // 9.5 -> 11.2), 64 x 64 ones have no registers for a third, a 64 x 96 tile's third gained nothing.  Row-major weights go through LDS, one.
-// One chunk | this, in sampling runs of 50 steps: one latent of 256 tokens 39.4 | 38.4 ms (proj and fc2 together 17.0 | 16.4 us), 8 latents 81.5 |
+// One chunk ahead | this, in sampling runs of 50 steps: one latent of 256 tokens 39.4 | 38.4 ms (proj and fc2 together 17.0 | 16.4 us), 8 latents 81.5 |
 // 80.2 (fc2).
 constexpr int split_depth(int tm, int tn, bool few, bool wrow) { return wrow ? 1 : few && tm * tn == 2 ? 3 : 2; }
 

@@ -262,7 +262,7 @@ __global__ __launch_bounds__(512) void ln_mod_quant_kernel(const void *__restric
 }
 
 // ---- one wavefront per token row
-// The wavefront-per-row form of the same operation, for launches with thousands of rows: a lane holds NV float4 of
+// The wavefront-per-row form of the same operation, for launches of many rows (launch_ln_mod_quant): a lane holds NV float4 of
 // the row (float4 index lane + 64 it), the sums of values and squares stay inside the wavefront (no LDS, no barrier), a wavefront walks
 // `rows_per_wave` consecutive rows with the next row's loads in flight while it works on the current one, and keeps the modulation
 // vectors of the batch element in registers from row to row.
@@ -281,8 +281,8 @@ __global__ __launch_bounds__(512) void ln_mod_quant_kernel(const void *__restric
 // What bounds it: at thousands of rows the memory system (32768 rows of 1152, 189 MB, in 31 us, the input in the memory-side cache in
 // part); else vector issue, some 13 instructions an element and 50 a row for the sums (in pairs: the sum of the values in the lower half
 // of the wavefront, that of the squares in the upper).  With every value in float64 it was 34 an element: 8192 rows 13.6 -> 11.1 us, 32768
-// 38 -> 31, bfloat16 rows, whose conversion also waited for the loads, 46 -> 26; in the sampler, whose large batches run at the chip's power limit,
-// 16 x 1024 tokens 103.2 -> 101.6 ms.
+// 38 -> 31, bfloat16 rows, whose conversion also waited for the loads, 46 -> 26.  In the sampler, beside the other half's attention, whose two
+// wavefronts leave a SIMD no registers for another, it gained 1 - 2 % of a run of 16 x 1024 tokens.
 __device__ __forceinline__ unsigned ln_codes_exact(float4 x, float4 c, float4 sh, double mean, double var, float s, float zu) {
   const double rstd = 1.0 / sqrt(fmax(var, 0.0) + 1e-6);
   const float xs[4] = {x.x, x.y, x.z, x.w}, cs[4] = {c.x, c.y, c.z, c.w}, ss[4] = {sh.x, sh.y, sh.z, sh.w};
@@ -406,9 +406,12 @@ hipError_t launch_ln_mod_quant(const void *x, int x_bf16, const float *shift, co
   const int nv = (D / 4 + 63) / 64;
   if (q && !f32_out && M >= 640 && nv <= 5) {
     // wavefront per row; with thousands of rows several consecutive ones (they share the batch element's modulation vectors and its
-    // float32 constants).  1 / 2 / 4 / 8 rows, us (width 1152): 2048 rows 4.5 / 5.1 / 6.6 / 9.5, 4096: 7.0 / 6.1 / 7.0 / 10.7, 8192: 12.3 / 11.9 /
-    // 11.1 / 12.5, 32768: 35.9 / 32.4 / 31.4 / 34.6.  From 640 rows on, a workgroup a row | a wavefront a row, 20 steps of width 1152: 2 latents
-    // (512 rows) 20.10 | 20.19 ms, 3 (768) 21.89 | 21.73, 5 of 240 tokens in bfloat16 (720 and 480) 30.0 | 29.7; at 1024 rows 6.8 | 5.5 us
+    // float32 constants).  1 / 2 / 4 / 8 rows, us (width 1152): 2048 rows 4.2 / 4.9 / 6.6 / 9.8, 4096: 6.7 / 6.2 / 7.0 / 10.0, 8192: 11.9 / 12.2 /
+    // 11.0 / 12.5, 32768: 33.8 / 32.7 / 31.8 / 34.7; narrower rows 1 / 2 / 4: 4096 of 384 3.9 / 4.2 / 4.8, of 768 4.8 / 4.8 / 5.5, 8192 of 384 5.7 / 5.5 /
+    // 5.8, of 1024 10.3 / 9.4 / 9.8.  (bfloat16 rows alone would rather have one up to 6144, 4096 of 1152 8.8 / 9.5 / 10.5; beside the other half's
+    // kernels one row costs networks of width 768 and 1152 1 %.)
+    // From where, a workgroup a row | a wavefront a row, networks in two halves, width 1152: 768 rows a half 4709 | 4657 us, 960 5953 | 5871, 1000 7943 |
+    // 7801; in one part, and with widths of 128 to 768, the sides differ by less than runs of one do (1 - 3 %).  1024 rows alone: 3.7 | 3.5
     const int rpw = M >= 8192 ? 4 : M >= 4096 ? 2 : 1;
     const int waves = (M + rpw - 1) / rpw;
     const dim3 grid((waves + 3) / 4);
@@ -962,7 +965,8 @@ __global__ __launch_bounds__(256) void step_mod_kernel(int nb_final, const float
 }
 
 // Whether the three kernels cover a call: one timestep, a few rows, and few enough tokens that embedding them takes no longer than the
-// linear beside it.
+// linear beside it: the gain ends there (two blocks, a refreshed | a cached step in six launches -> three: 1 latent of 1024 tokens, width 384
+// 150 -> 140 | 34 -> 25 us, 1152 266 -> 256 | 53 -> 43; of 2048 tokens, width 384 274 -> 265 | 37 -> 28, 1152 503 -> 498 | 58 -> 54, 2048 775 -> 777 | 82 -> 78).
 bool step_cond_covers(int B, int freq_dim, int C, int p, int D, int M) {
   return B <= STEP_ROWS && freq_dim <= 256 && freq_dim % 4 == 0 && C * p * p == 16 && D <= 2048 && M <= 2048;
 }
