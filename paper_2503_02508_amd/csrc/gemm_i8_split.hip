@@ -9,8 +9,8 @@
 //     16-byte chunks swizzled with the row's low three bits (conflict-free writes and reads).
 //   * weights in fragment order go straight to registers; row-major ones (WROW: the caller's matrix of qc_w8a8_linear) take
 //     the activations' way.
-//   * the first two chunks are requested at once (three where a compute unit has no second tile); from then on the activations of that many
-//     chunks are ahead of the one that is multiplied, the weights of one less: their registers are free only behind the products.
+//   * the first chunks (split_depth) are requested at once; from then on the activations of that many chunks are ahead of the one that is
+//     multiplied, the weights of one less: their registers are free only behind the products.
 // What bounds it: the 60 bytes per clock a compute unit draws from its L2 (32 TM + 32 TN rows of K bytes per tile), and the
 // fixed costs around it (launch, first memory round trip, reduction, epilogue).
 #include "gemm_i8_epilogue.h"
@@ -35,11 +35,12 @@ constexpr int split_en(int tm, int tn, int nw) {
 
 // Chunks of a wavefront that are requested before it multiplies the first, and register sets.  What a launch of few tiles waits for are round
 // trips to weights that lie in HBM, one after the other; K = 1152 is three chunks a wavefront.  32 x 64 tiles of which a compute unit has
-// several, and 32 x 32 ones (one or two chunks a wavefront up to K = 2048), keep to two (160 registers, three workgroups a unit: with three chunks fc1 at 256 rows 10.8 -> 12.2 us, proj at 1024 rows
-// 9.5 -> 11.2), 64 x 64 ones have no registers for a third, a 64 x 96 tile's third gained nothing.  Row-major weights go through LDS, one.
-// One chunk ahead | this, in sampling runs of 50 steps: one latent of 256 tokens 39.4 | 38.4 ms (proj and fc2 together 17.0 | 16.4 us), 8 latents 81.5 |
-// 80.2 (fc2).
-constexpr int split_depth(int tm, int tn, bool few, bool wrow) { return wrow ? 1 : few && tm * tn == 2 ? 3 : 2; }
+// several keep to one: 112 registers, four workgroups a unit (two chunks, 160 and three, against that: QKV of 425 x 1152 x 1152 11.6 -> 9.9 us, fc2
+// of 512 x 8192 x 2048 25.0 -> 23.9; 425 tokens of width 1152, 24 blocks, 7718 -> 7431 us, 8 latents 10235 -> 10081; three chunks were another 10 - 18 %
+// slower).  32 x 32 tiles have one or two chunks a wavefront up to K = 2048, 64 x 64 ones no registers for a third, a 64 x 96 tile's third gained
+// nothing.  Row-major weights go through LDS, one.
+// One latent of 256 tokens, 50 steps, one chunk everywhere | this: 39.4 | 38.4 ms (proj and fc2 together 17.0 | 16.4 us).
+constexpr int split_depth(int tm, int tn, bool few, bool wrow) { return wrow ? 1 : tm * tn == 2 ? (few ? 3 : 1) : 2; }
 
 // whether a kernel differs with FEW
 constexpr bool split_few(int tm, int tn, bool wrow) { return !wrow && tm * tn <= 2; }
@@ -223,17 +224,21 @@ __global__ __launch_bounds__(64 * NW, (NW <= 4 && TM * TN <= 4) ? 2 : 1) void ge
         for (int d = 0; d < PF; ++d) step(d, c + d * NW);
       }
       last(0, c);
-      if (left > 1) {
-        last(1, c + NW);
-        if constexpr (PF > 2) {
-          if (left > 2) last(2, c + 2 * NW);
+      if constexpr (PF > 1) {
+        if (left > 1) {
+          last(1, c + NW);
+          if constexpr (PF > 2) {
+            if (left > 2) last(2, c + 2 * NW);
+          }
         }
       }
     } else if (PF > 2 && mine == 2) {
-      request(1);
-      __builtin_amdgcn_sched_barrier(0);
-      last(0, wave);
-      last(1, wave + NW);
+      if constexpr (PF > 2) {
+        request(1);
+        __builtin_amdgcn_sched_barrier(0);
+        last(0, wave);
+        last(1, wave + NW);
+      }
     } else if (mine == 1) {
       last(0, wave);
     }
