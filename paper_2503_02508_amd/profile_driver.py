@@ -14,7 +14,7 @@ byte is fetched from and written to HBM once).
     rocprofv3 --pmc WRITE_SIZE --kernel-trace -d <out> -- python3 paper_2503_02508_amd/profile_driver.py
 
 With `--workload tap1` the run is the calibration-set clustering instead, with one subsample at the benchmark's sizes and
-settings, followed by the same copies.
+settings, followed by the same copies; with `--workload linear` twenty 8-bit linears of 16384 x 4608 x 1152 with their quantiser.
 """
 from __future__ import annotations
 
@@ -39,8 +39,8 @@ def main():
     import torch
     import paper_2503_02508_amd as qc
 
-    if args.workload.startswith("tap"):
-        run_tap(args, qc, np, torch)
+    if args.workload == "linear" or args.workload.startswith("tap"):
+        (run_linear if args.workload == "linear" else run_tap)(args, qc, np, torch)
         copies(args, torch)
         return
     from synthetic import dit_inputs as I
@@ -83,6 +83,21 @@ def run_tap(args, qc, np, torch):
     lab, per = torch.empty(wl.N, dtype=torch.int32, device="cuda"), torch.empty((1, wl.N), dtype=torch.int32, device="cuda")
     print("profile_driver: %s, one subsample" % wl.name, flush=True)
     qc.qc_tap_cluster(Xd, td, subs, wl.alpha, wl.k, 8, q0, init, 100, lab, per, work)
+    torch.cuda.synchronize()
+
+
+def run_linear(args, qc, np, torch):
+    M, N, K = 16384, 4608, 1152
+    torch.cuda.set_device(0)
+    x, w, bias = torch.randn(M, K, device="cuda"), torch.randn(N, K, device="cuda") * 0.02, torch.randn(N, device="cuda") * 0.02
+    q, y = torch.empty((M, K), dtype=torch.int8, device="cuda"), torch.empty((M, N), device="cuda")
+    qw, ws = torch.empty((N, K), dtype=torch.int8, device="cuda"), torch.empty(N, device="cuda")
+    wsum = torch.empty(N, dtype=torch.int32, device="cuda")
+    qc.qc_quantize_weight(w, 8, qw, ws, wsum)
+    print("profile_driver: linear %d x %d x %d" % (M, N, K), flush=True)
+    for _ in range(20):
+        qc.qc_quantize_act(x, q, 0.04, 121)
+        qc.qc_w8a8_linear(q, qw, wsum, ws, bias, 0.04, 121, 8, y)
     torch.cuda.synchronize()
 
 

@@ -434,7 +434,7 @@ def test_reference_trajectory_of_a_fit_does_not_depend_on_the_batch(model, B, st
 
 @pytest.mark.parametrize("hidden,hw,B", [(64, (14, 10), 32), (272, (14, 10), 60), (576, (18, 14), 17), (1008, (14, 10), 61),
                                          (1152, (14, 10), 236), (1280, (50, 34), 3), (1152, (6, 6), 456),
-                                         (768, (6, 6), 73), (1536, (14, 10), 235), (2048, (14, 10), 20)])
+                                         (1152, (6, 6), 73), (768, (6, 6), 73), (1536, (14, 10), 235), (2048, (14, 10), 20)])
 def test_layer_norm_codes_of_many_rows(hidden, hw, B):
     """A wavefront a row (1, 2 or 4 rows in turn, batch elements that end between them), which decides most codes in float32,
     against a workgroup a row, which forms every value in float64, each thread the statistics or one for all (wider rows: a workgroup for
