@@ -34,23 +34,23 @@ TAP_ITERS, TAP_MAX_PASSES = 8, 100   # power-iteration rounds and k-means pass l
 # under profiles/, keyed by (workload, kernel class).  None where no counter run covers the pair.
 TRAFFIC = {
     # profiles/sampler_cfg1_dit_xl2_b8_hbm_traffic.txt: (FETCH_SIZE * 2.0 + WRITE_SIZE * 1.0) KiB per dispatch
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc2"): (16850.1 * 2.0 + 9216.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_qkv"): (9093.3 * 2.0 + 15164.1) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc1"): (16085.6 * 2.0 + 4608.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_proj"): (6146.5 * 2.0 + 9216.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc2"): (16857.1 * 2.0 + 9216.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_qkv"): (9093.3 * 2.0 + 15291.6) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc1"): (16082.6 * 2.0 + 4608.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_proj"): (6139.1 * 2.0 + 9216.0) * 1024,
     ("dit_xl2_256_w8a8_b8_ddim50_n2", "attention"): (7048.5 * 2.0 + 1536.0) * 1024,
     # profiles/sampler_cfg2_dit_xl2_b64_cfg_hbm_traffic.txt
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc2"): (145813.8 * 2.0 + 147461.4) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_qkv"): (65825.1 * 2.0 + 243508.2) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc1"): (110695.8 * 2.0 + 73728.8) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_proj"): (60129.9 * 2.0 + 147467.1) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "attention"): (124324.0 * 2.0 + 24576.0) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc2"): (145938.9 * 2.0 + 147460.6) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_qkv"): (65605.7 * 2.0 + 243560.8) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc1"): (110598.6 * 2.0 + 73746.2) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_proj"): (60326.5 * 2.0 + 147464.5) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "attention"): (124366.7 * 2.0 + 24576.0) * 1024,
     # profiles/sampler_cfg3_dit_xl2_512_b16_hbm_traffic.txt
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc2"): (67727.1 * 2.0 + 73751.1) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_qkv"): (32505.2 * 2.0 + 123222.5) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc1"): (56542.4 * 2.0 + 36864.9) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_proj"): (29814.2 * 2.0 + 73735.9) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "attention"): (64642.1 * 2.0 + 12288.0) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc2"): (68366.6 * 2.0 + 73750.4) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_qkv"): (32556.4 * 2.0 + 124416.1) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc1"): (56564.2 * 2.0 + 36898.2) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_proj"): (29923.7 * 2.0 + 73735.6) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "attention"): (64576.6 * 2.0 + 12288.0) * 1024,
     # profiles/clustering_tap1_counters.txt
     ("tap1", "similarity"): (1724819.0 * 2.0 + 210910.1) * 1024,
 }
