@@ -398,11 +398,15 @@ __device__ __forceinline__ void decide_again_and_store(unsigned char *stage, con
 // products instead of three (the lo x lo terms come with them), and one addition across lanes at the end.
 // (16 heads of 72, 16 x 1024 tokens: 301.6 -> 298 us, and 0.1 - 1 % closer to float64 in the mean.)
 //
-// What bounds it: issue slots of the vector pipe, which an MFMA shares for about half of its 16 cycles.  Per tile of 64 keys
-// a wavefront issues 112 MFMAs (QB = 2, d = 72) and about 6 vector instructions per probability (exponential, subtraction,
-// half a maximum, one and a half for the split, the sum), so the vector work is what was cut: the running max is only raised
-// when a tile exceeds it by more than MAX_SLACK (a probability may reach 2^MAX_SLACK; hi + lo keep their relative precision),
-// which leaves one test per tile instead of two shuffles, an exponential and the rescaling of every output register.
+// What bounds it: no unit alone.  Per tile of 64 keys a wavefront (QB = 2, d = 72) issues 582 vector instructions in the mean,
+// prologue and epilogue included, 112 of them MFMAs: about 15 others for each of a lane's 32 probabilities.  Counters at
+// 8 x 1024 tokens, 16 heads (190 us): matrix pipes busy in 28 % of the cycles (64 x 256 tokens: 23 %), a vector instruction
+// issuing in 43 %, 1.43 wavefronts a SIMD in the mean of the two that fit.  A wavefront spends 30 % of its time issuing vector
+// instructions, 5 % on LDS, 39 % waiting to issue and 21 % at waits and barriers.  What it waits to issue for is not shown; the
+// staging of a tile between two barriers, when nothing is multiplied, is one candidate.  Vector work is what was cut so far: the
+// running max is only raised when a tile exceeds it by more than MAX_SLACK (a probability may reach 2^MAX_SLACK; hi + lo keep
+// their relative precision), which leaves one test per tile instead of two shuffles, an exponential and the rescaling of every
+// output register.
 // The sum of the probabilities stays a float32 addition each: a row of ones in V^T gives it for free (2 - 4 % of a launch), but
 // from the 22 bits of the halves and with the matrix cores' accumulation, 1.2 (256 keys) to 1.6 (4096) times as far from
 // float64, and the outputs of a sharp softmax over 4096 keys 1.5 times.

@@ -11,8 +11,9 @@
 //     the activations' way.
 //   * the first chunks (split_depth) are requested at once; from then on the activations of that many chunks are ahead of the one that is
 //     multiplied, the weights of one less: their registers are free only behind the products.
-// What bounds it: the 60 bytes per clock a compute unit draws from its L2 (32 TM + 32 TN rows of K bytes per tile), and the
-// fixed costs around it (launch, first memory round trip, reduction, epilogue).
+// What bounds it: with few rows the round trips to weights that lie in HBM and the fixed costs around them (launch, reduction,
+// epilogue).  With 1024 rows no unit: fc2 of 1024 x 1152 x 4608 (64 x 96 tiles, 18.3 us) has 192 of 256 compute units at work, each
+// drawing 737 KB, 17 bytes a clock of the 60 its L2 gives, with 9 % of the matrix pipes busy; what it waits for there is not shown.
 #include "gemm_i8_epilogue.h"
 
 namespace qc {
