@@ -189,23 +189,33 @@ __device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc<TM> &acc, unsi
     const auto buf = __builtin_amdgcn_make_buffer_rsrc((part == 0 ? p.q32 : p.k32) + (size_t)b * T * D, 0, -1, 0x00027000);
     const int col = row * 4, nn = nn0 + col, h = head_of(nn), e = nn - h * p.hd;
     const int off = ((h * T + tb + g) * p.hd + e) * 4;
+    const auto rows_out = [&](auto nt) {
 #pragma unroll
-    for (int ip = 0; ip < TM; ip += 2) {
-      big_stage_rows<TM>(acc, stage, cst, wn0, a_s, ip);
+      for (int ip = 0; ip < TM; ip += 2) {
+        big_stage_rows<TM>(acc, stage, cst, wn0, a_s, ip);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const v4u v = *(const v4u *)(stage + (q * 4 + g) * BIG_SR + col);
-        const int m = ip * 16 + q * 4;
-        if (!RAG) {
-          big_store16(v, buf, off + m * p.hd * 4, true);
-        } else {
-          // row beyond the first batch element: its token 0 lies (heads - 1) * T tokens further than the next row would
-          const int o = off + (m + (m + g >= bnd ? (p.heads - 1) * T : 0)) * p.hd * 4;
-          if (m + g < rows) big_store16(v, buf, o, true);
+        for (int q = 0; q < 8; ++q) {
+          const v4u v = *(const v4u *)(stage + (q * 4 + g) * BIG_SR + col);
+          const int m = ip * 16 + q * 4;
+          if (!RAG) {
+            big_store16(v, buf, off + m * p.hd * 4, decltype(nt)::value);
+          } else {
+            // row beyond the first batch element: its token 0 lies (heads - 1) * T tokens further than the next row would
+            const int o = off + (m + (m + g >= bnd ? (p.heads - 1) * T : 0)) * p.hd * 4;
+            if (m + g < rows) big_store16(v, buf, o, decltype(nt)::value);
+          }
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
+    };
+    // A wavefront's 64 columns cut the rows of heads of 72 features into pieces of 128-byte lines, which streaming stores send to memory one
+    // by one and others let meet in the L2.  Streaming | not, us, heads of 72: 16384 rows of 256 tokens 88 | 76, 8192 53.8 | 42.7,
+    // 2048 (64-row tiles) 16.4 | 14.6; of 64: 16384 56.4 | 54.3.  Ragged tiles, of 72: 4240 rows 25.9 | 23.7, 6000 38.2 | 35.3, 16000 84.8 | 82.6,
+    // 18000 93.9 | 95.8; but 64-row tiles 15.3 | 16.1 (2120), and heads of 64, whole lines, 49.4 | 52.3 (18000), 12.5 | 13.5 (2120).
+    if constexpr (!RAG) rows_out(std::false_type{});
+    else if constexpr (TM == 4) rows_out(std::true_type{});
+    else if ((p.hd & 31) == 0) rows_out(std::true_type{});
+    else rows_out(std::false_type{});
     return;
   }
   // V^T: 64 tokens of the wavefront's 64 features at a time
@@ -329,9 +339,9 @@ __device__ __forceinline__ void big_resid(const GemmArgs &p, BigAcc<TM> &acc, un
   }
 }
 
-// float32 rows [M, ldy], any N and M
-template <int TM>
-__device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+// float32 rows [M, ldy], any N and M.  NT: streaming stores (below)
+template <int TM, bool NT>
+__device__ __forceinline__ void big_f32_rows(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
   const int left = p.N - n0 - wn0, rows = min(16 * TM, p.M - m0);
   if (left <= 0) return;
@@ -342,24 +352,35 @@ __device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc<TM> &acc, unsi
   for (int ip = 0; ip < TM; ip += 2) {
     QC_SB;
     big_stage_rows<TM>(acc, stage, cst, wn0, a_s, ip);
-    if ((p.N & 3) == 0) {                                     // whole groups of four columns
+    if (NT || (p.N & 3) == 0) {                               // whole groups of four columns
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const int m = ip * 16 + q * 4;
         const v4u v = *(const v4u *)(stage + (q * 4 + g) * BIG_SR + col);
-        if (col < left && m + g < rows) big_store16(v, buf, ((m + g) * p.ldy + col) * 4, true);
+        if (col < left && m + g < rows) big_store16(v, buf, ((m + g) * p.ldy + col) * 4, NT);
       }
     } else {                                                  // a row of 64 columns at a time
 #pragma unroll 8
       for (int r = 0; r < 32; ++r) {
         const int m = ip * 16 + r;
         const unsigned v = *(const unsigned *)(stage + r * BIG_SR + lane);
-        if (lane < left && m < rows) __builtin_amdgcn_raw_buffer_store_b32(v, buf, lane * 4, m * p.ldy * 4, 2);
+        if (lane < left && m < rows) __builtin_amdgcn_raw_buffer_store_b32(v, buf, lane * 4, m * p.ldy * 4, 0);
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     QC_SB;
   }
+}
+// Streaming stores of parts of a 128-byte line reach memory one by one, others meet in the L2 first: rows that are no whole lines
+// go without, unless the result is larger than the memory-side cache and its rows whole groups of 16 bytes.  16384 rows, K = 1152, us,
+// streaming | not: N = 3460 106 | 93, 2308 78 | 68, 1160 47 | 43.5, 3333 119 | 103; 4600 124 | 128, 4100 118 | 118, 4603 140 | 132;
+// rows of whole lines: 4608 115.5 | 121, 1152 41.4 | 42.9, 2304 68 | 68.5.
+template <int TM>
+__device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
+  if ((p.ldy & 31) == 0 || ((p.N & 3) == 0 && (size_t)p.M * p.ldy * sizeof(float) > ((size_t)256 << 20)))
+    big_f32_rows<TM, true>(p, acc, smem, cst, m0, n0, a_s);
+  else
+    big_f32_rows<TM, false>(p, acc, smem, cst, m0, n0, a_s);
 }
 
 template <int TM, int EPI, int TAG, bool W4, bool RBF, bool RAG>
