@@ -62,6 +62,11 @@ def _net(hidden, heads, mlp, h, w, patch=2):
     ("64-row tiles, 100 tokens", _net(384, 6, 1536, 20, 20), 21, 8),
     ("64-row tiles, 77 tokens, 4-bit", _net(384, 6, 1536, 14, 22), 27, 4),
     ("64-row tiles, 64 tokens", _net(384, 6, 1536, 16, 16), 40, 8),
+    # V^T of tiles whose tokens start anywhere in a unit of four: 2, 3, 1 tokens more than whole units; the last two in tiles of 128 rows
+    ("64-row tiles, 78 tokens", _net(384, 6, 1536, 12, 26), 27, 8),
+    ("64-row tiles, 91 tokens", _net(384, 6, 1536, 14, 26), 23, 8),
+    ("large-M, 255 tokens, 64 features a head", _net(384, 6, 1536, 30, 34), 16, 8),
+    ("large-M, 133 tokens, 64 features a head", _net(384, 6, 1536, 14, 38), 31, 8),
     ("64-row tiles, residuals, 425 tokens", _net(1152, 16, 4608, 50, 34), 5, 8),
     ("64-row tiles, residuals, 256 tokens, 4-bit", _net(1152, 16, 4608, 32, 32), 9, 4),
     ("split-K: 32 x 64 tiles in place of 252 of 64 x 64, 425 tokens", _net(1152, 16, 4608, 50, 34), 2, 8),
