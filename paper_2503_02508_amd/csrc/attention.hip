@@ -23,6 +23,8 @@
 // are read from LDS a step ahead.  Us (16 heads of 72): 1 x 256 tokens 26.5 -> 18.1, 4 x 256 29.2 -> 22.1, 2 x 425 45.2 -> 31.8, 1 x 1024
 // 98.6 -> 66.0, 1 x 4096 992 -> 874.  (Workgroups of 32 queries, twice as many: 1 x 256 21.2, 4 x 256 27.7, 1 x 4096 1200, against 20.1, 23.9
 // and 926 without the fragments read ahead.)
+#include <type_traits>
+
 #include "qc_internal.h"
 
 namespace qc {
@@ -229,8 +231,9 @@ hipError_t launch_attention(const float *qkv, int B, int T, int H, int hd, const
 //
 // One workgroup = 128 queries of one (batch, head); each of the 4 wavefronts
 // owns two blocks of 16 queries, so every K / V^T fragment read from LDS feeds
-// two MFMAs.  The next key tile is loaded into registers while the current one
-// is being used.
+// two MFMAs.  Two key tiles lie in LDS: while one is multiplied, the next one is
+// split from registers into the other behind the products of the scores, and the
+// one after that comes into the registers from then on.
 namespace qc {
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
@@ -392,18 +395,25 @@ __device__ __forceinline__ void decide_again_and_store(unsigned char *stage, con
 // arithmetic per query is the same in both.
 //
 // TAIL: the last feature chunk holds at most 8 real features (d = 72: 64 + 8).  Its three products then share ONE
-// instruction: of the 32 k positions of the K operand, 0..7 are the features' hi halves, 8..15 their lo halves, 16..23 the
-// hi halves again, and the query operand has hi, hi, lo there (7 instructions per key block instead of 9 at d = 72).
+// instruction: of the 32 k positions of the K operand, 0..7 are the features' hi halves, 8..15 their lo halves, 16..23 (and 24..31)
+// the hi halves again, and the query operand has hi, hi, lo (and zeros) there (7 instructions per key block instead of 9 at d = 72).
 // The last block of V^T then has at most 8 real features as well, and its other 8 rows hold their lo halves: one fragment, two
 // products instead of three (the lo x lo terms come with them), and one addition across lanes at the end.
 // (16 heads of 72, 16 x 1024 tokens: 301.6 -> 298 us, and 0.1 - 1 % closer to float64 in the mean.)
 //
-// What bounds it: no unit alone.  Per tile of 64 keys a wavefront (QB = 2, d = 72) issues 582 vector instructions in the mean,
-// prologue and epilogue included, 112 of them MFMAs: about 15 others for each of a lane's 32 probabilities.  Counters at
-// 8 x 1024 tokens, 16 heads (190 us): matrix pipes busy in 28 % of the cycles (64 x 256 tokens: 23 %), a vector instruction
-// issuing in 43 %, 1.43 wavefronts a SIMD in the mean of the two that fit.  A wavefront spends 30 % of its time issuing vector
-// instructions, 5 % on LDS, 39 % waiting to issue and 21 % at waits and barriers.  What it waits to issue for is not shown; the
-// staging of a tile between two barriers, when nothing is multiplied, is one candidate.  Vector work is what was cut so far: the
+// What bounds it: vector issue.  Per tile of 64 keys a wavefront (QB = 2, d = 72) issues 112 MFMAs and about 300 other vector
+// instructions, 32 of them exponentials.  On this chip an MFMA 16x16x32 takes 18 clocks of the matrix pipe and keeps the SIMD, for
+// whichever of its wavefronts, from issuing for 10 of them (two FMAs behind each cost nothing, every further one 4 clocks), so the
+// two kinds add up to 5000 of the 6150 clocks that a tile of both resident wavefronts takes.  Cycle counters, 64 x 256 tokens, 16
+// heads of 72, clocks a wavefront: first loads and first tile 8400; a tile 6150 at 1024 keys, 5510 here: scores and staging 2540, softmax
+// 1240, V^T products 1060, barrier and loads 670; codes 3500; decisions and rows out 4200.  With one tile in LDS, staged between two
+// barriers, a tile took 6830: 64 x 256 tokens 92.8 -> 90.3 us, 8 x 1024 158 -> 154, 10 x 425 59.5 -> 56.2, 4 x 256 15.3 -> 14.4, 8 x 256
+// 20.2 -> 19.3 (LDS active in 33 % of the cycles -> 28 %, conflicts in 13 % -> 8 %).  Units of K and V^T are dealt to threads such that their
+// places are constants away from a few registers: the tables of places that stood here would not fit beside a tile in flight, and a
+// single register in scratch memory costs more than the second tile gains.
+// Not better: 32x32x16 products (half the issue slots, the same clocks a tile, and the chip, at its power limit, runs them 4 % slower),
+// eight wavefronts on one tile (half the staging, 3 - 10 % slower), one branch for all outputs of a query.
+// Vector work is what was cut before: the
 // running max is only raised when a tile exceeds it by more than MAX_SLACK (a probability may reach 2^MAX_SLACK; hi + lo keep
 // their relative precision), which leaves one test per tile instead of two shuffles, an exponential and the rescaling of every
 // output register.
@@ -416,19 +426,21 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
                                                             float q_mul, const QParam *qp, int8_t *__restrict__ q_out) {
   constexpr int NM = TAIL ? NCH - 1 : NCH;        // feature chunks multiplied in three instructions
   constexpr int NI = NM + (TAIL ? 1 : 0);         // fragment steps per key block
-  constexpr int KROW = 32 * NM + 8;               // halves per K row in LDS (16 bytes of padding)
-  constexpr int TROW = 32 + 8;                    // halves per row of the tail operand
-  constexpr int VROW = 64 + 8;                    // halves per V^T row in LDS
-  constexpr int NW = 4, NT = 64 * NW;            // wavefronts, threads
-  constexpr int KCH = (64 * 4 * NEB + NT - 1) / NT;       // 16-byte chunks of K per thread per tile (d <= 16 NEB)
-  constexpr int VCH = (NEB * 16 * 8 + NT - 1) / NT;       // 32-byte chunks of V^T
+  constexpr int NW = 4, NT = 64 * NW;             // wavefronts, threads
+  constexpr int KCH = NEB;                        // 16-byte units of K per thread per tile: units p, p + 4, ... of row r (below)
+  constexpr int VCH = (NEB + 1) / 2;              // 32-byte units of V^T: unit c of rows f, f + 32, ...
   constexpr int NQ = 16 * QB * NW;                // queries of this workgroup
   constexpr float MAX_SLACK = 8.0f;
-  __shared__ __align__(16) _Float16 Ksh[2 * 64 * KROW + (TAIL ? 64 * TROW : 0)];
-  __shared__ __align__(16) _Float16 Vsh[2][NEB * 16 * VROW];
+  // A tile in LDS, in units of 16 bytes without padding, whose places are swapped so that 16 rows of one unit lie in 16 different
+  // places of 256 bytes (free of conflicts when they are read).  K: one plane of 64 rows x 32 features per feature chunk, hi then
+  // lo; the packed tail has 8 hi and 8 lo halves a row.  V^T: rows of 64 keys, hi then lo; the last block of TAIL holds both.
+  constexpr int KPL = 64 * 32, KTL = TAIL ? 64 * 16 : 0;  // halves of a plane and of the tail
+  constexpr int KSZ = 2 * NM * KPL + KTL, VSZ = 64 * (16 * NEB + 16 * (TAIL ? NEB - 1 : NEB));
+  // two tiles where two workgroups a compute unit have room for them (160 KB): not for 76 and 80 features, whose tiles take 45 KB
+  constexpr int NBUF = 4 * (KSZ + VSZ) <= 78 * 1024 ? 2 : 1;
+  __shared__ __align__(16) _Float16 kv_s[NBUF][KSZ + VSZ];
   __shared__ int fix_cnt_s;                       // outputs queued for the exact decision (epilogue)
   __shared__ float m_s[NQ];                       // running max of every query (reference point of the exact decision)
-  _Float16 *const Khi = Ksh, *const Klo = Ksh + 64 * KROW, *const Kt = Ksh + 2 * 64 * KROW;
 
   const int D = H * hd;
   if (threadIdx.x == 0) fix_cnt_s = 0;            // published by the barriers of the key loop
@@ -445,98 +457,78 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   const int ql = lane & 15, g = lane >> 4;
   const long long tok_base = (long long)bh * T * hd;
   const long long vt_base = (long long)bh * DPv * Tp;
-  const int kchunks = 64 * (hd / 4);            // 16-byte chunks of one K tile
-
-  // what no tile writes: the feature padding of the K rows and the V^T rows beyond d (zeros)
-  for (int i = tid; i < (int)(sizeof(Ksh) / 16); i += NT) ((v8h *)Ksh)[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
-  for (int i = tid; i < (16 * NEB - hd) * VROW / 8; i += NT) {
-    ((v8h *)(Vsh[0] + hd * VROW))[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
-    ((v8h *)(Vsh[1] + hd * VROW))[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
+  // what no tile writes, where a head has padding: the padded features of the K rows and the V^T rows beyond d (zeros)
+  if (hd != 32 * NM + (TAIL ? 8 : 0) || hd != 16 * NEB - (TAIL ? 8 : 0)) {
+    for (int i = tid; i < (int)(sizeof(kv_s) / 16); i += NT) ((v8h *)kv_s)[i] = (v8h){0, 0, 0, 0, 0, 0, 0, 0};
+    __syncthreads();
   }
 
-  v4f o[QB][NEB];
-#pragma unroll
-  for (int j = 0; j < QB; ++j)
-#pragma unroll
-    for (int e = 0; e < NEB; ++e) o[j][e] = (v4f){0.f, 0.f, 0.f, 0.f};
-  float m_run[QB], l_run[QB];
-#pragma unroll
-  for (int j = 0; j < QB; ++j) {
-    m_run[j] = -INFINITY;
-    l_run[j] = 0.0f;
-  }
-
-  v4f kreg[KCH];
-  v4f vreg[2][VCH];
-  // Offsets of this thread's K and V^T chunks in memory and in LDS (the same for every tile: no address arithmetic in the
-  // loop).  Loads never branch: a chunk index beyond the tile is clamped to the last chunk, a key beyond T to key T - 1
-  // (finite values that the ragged-tile mask or the store predicate discards), so that all loads of a tile are issued back
-  // to back and nothing waits in between.
-  const int hd4 = hd >> 2;
-  unsigned koff[KCH], voff[VCH];
-  int k_hi[KCH], k_lo[KCH], v_at[VCH], v_lo[VCH]; // positions in Ksh / Vsh[0], in halves; negative: no such chunk
-#pragma unroll
-  for (int u = 0; u < KCH; ++u) {
-    const int i = tid + NT * u, ic = min(i, kchunks - 1);
-    const int r = ic / hd4, c = (ic - r * hd4) * 4;
-    const bool tail = TAIL && c >= 32 * NM;
-    koff[u] = (unsigned)(min(r, T - 1) * hd + c);
-    k_hi[u] = i >= kchunks ? -1 : tail ? 2 * 64 * KROW + r * TROW + c - 32 * NM : r * KROW + c;
-    k_lo[u] = tail ? k_hi[u] + 8 : k_hi[u] + 64 * KROW;
-  }
-#pragma unroll
-  for (int u = 0; u < VCH; ++u) {
-    const int i = tid + NT * u, ic = min(i, hd * 8 - 1);
-    voff[u] = (unsigned)((ic >> 3) * Tp + (ic & 7) * 8);
-    v_at[u] = i < hd * 8 ? (i >> 3) * VROW + (i & 7) * 8 : -1;
-    v_lo[u] = v_at[u] + (TAIL && (i >> 3) >= 16 * (NEB - 1) ? 8 : 16 * NEB) * VROW;
-  }
+  // This thread's part of a tile: of K, the 16-byte units kp, kp + 4, ... of row kr; of V^T, the 32-byte unit vc of rows vf, vf + 32, ...
+  // Its places in memory and in LDS are then constants away from a few registers.  Loads never branch: a unit or row beyond the
+  // head's last reads the last one, a key beyond T key T - 1 (finite values that the ragged-tile mask or the store predicate
+  // discards), so that all loads of a tile are issued back to back and nothing waits in between.
+  const int hd4 = hd >> 2, kr = tid >> 2, kp = tid & 3, vf = tid >> 3, vc = tid & 7;
   const float *const kbase = Kp + tok_base, *const vbase = Vt + vt_base;
-  auto load_tile = [&](int k0) {
-    const float *kb = kbase + (size_t)k0 * hd, *vb = vbase + k0;
-    if (k0 + 64 <= T || k0 == 0) {                // the first tile's offsets are clamped already
+  const int klast = min(kp + 4 * (KCH - 1), hd4 - 1) * 4 - kp * 4;             // from a thread's first unit to its last, in floats
+  const unsigned voff = (unsigned)(vf * Tp + vc * 8), vlast = (unsigned)(min(vf + 32 * (VCH - 1), hd - 1) * Tp + vc * 8);
+  const bool k_has = kp + 4 * (KCH - 1) < hd4, v_has = vf + 32 * (VCH - 1) < hd;
+  // places in LDS, in halves: K's even and odd units, the tail's hi and lo half, V^T's rows, the lo row of the shared block
+  const int ksw = (kr >> 2) & 3, kat0 = kr * 32 + (((kp >> 1) ^ ksw) << 3) + (kp & 1) * 4, kat1 = kat0 ^ 16;
+  const int ktl0 = 2 * NM * KPL + kr * 16 + (((kr >> 3) & 1) << 3) + (kp & 1) * 4, ktl1 = ktl0 ^ 8;
+  const int vat0 = KSZ + vf * 64 + ((vc ^ ((vf >> 1) & 7)) << 3), vat1 = (vat0 ^ 32) + 8 * 64;
+  auto load_tile = [&](int k0, v4f (&kreg)[KCH], v4f (&vreg)[2][VCH]) {
+    const float *const kb = kbase + (size_t)k0 * hd, *vb = vbase + k0;
+    const unsigned off = (unsigned)(min(kr, T - 1 - k0) * hd + kp * 4);
 #pragma unroll
-      for (int u = 0; u < KCH; ++u) kreg[u] = *(const v4f *)(kb + koff[u]);
-    } else {
-#pragma unroll
-      for (int u = 0; u < KCH; ++u) {
-        const int ic = min(tid + NT * u, kchunks - 1), r = ic / hd4;
-        kreg[u] = *(const v4f *)(kb + (min(r, T - 1 - k0) * hd + (ic - r * hd4) * 4));
-      }
-    }
+    for (int u = 0; u < KCH - 1; ++u) kreg[u] = *(const v4f *)(kb + off + 16 * u);
+    kreg[KCH - 1] = *(const v4f *)(kb + (unsigned)(off + klast));
 #pragma unroll
     for (int u = 0; u < VCH; ++u) {
-      vreg[0][u] = *(const v4f *)(vb + voff[u]);
-      vreg[1][u] = *(const v4f *)(vb + voff[u] + 4);
+      const float *const src = u < VCH - 1 ? vb + (size_t)(32 * u) * Tp + voff : vb + vlast;
+      vreg[0][u] = *(const v4f *)src;
+      vreg[1][u] = *(const v4f *)(src + 4);
     }
   };
-  auto store_tile = [&]() {
-#pragma unroll
-    for (int u = 0; u < KCH; ++u) {
-      if (k_hi[u] >= 0) {
+  // unit u of a tile (K's, then V^T's) from registers to LDS
+  auto store_unit = [&](int u, _Float16 *dst, const v4f (&kreg)[KCH], const v4f (&vreg)[2][VCH]) {
+    if (u < KCH) {
+      if (u < KCH - 1 || k_has) {
         v2u hi, lo;
         split_pairs(kreg[u], hi, lo);
-        *(v2u *)(Ksh + k_hi[u]) = hi;
-        *(v2u *)(Ksh + k_lo[u]) = lo;
-        if (TAIL && k_lo[u] - k_hi[u] == 8) *(v2u *)(Ksh + k_hi[u] + 16) = hi;
+        if (TAIL && u == KCH - 1) {
+          *(v2u *)(dst + ktl0) = hi;
+          *(v2u *)(dst + ktl1) = lo;
+        } else {
+          _Float16 *const at = dst + (u & 1 ? kat1 : kat0) + (u >> 1) * KPL;
+          *(v2u *)at = hi;
+          *(v2u *)(at + NM * KPL) = lo;
+        }
       }
-    }
-#pragma unroll
-    for (int u = 0; u < VCH; ++u) {
-      if (v_at[u] >= 0) {
+    } else {
+      const int w = u - KCH;
+      if (w < VCH - 1 || v_has) {
         v2u h0, l0, h1, l1;
-        split_pairs(vreg[0][u], h0, l0);
-        split_pairs(vreg[1][u], h1, l1);
-        *(v4u *)(Vsh[0] + v_at[u]) = (v4u){h0.x, h0.y, h1.x, h1.y};
-        *(v4u *)(Vsh[0] + v_lo[u]) = (v4u){l0.x, l0.y, l1.x, l1.y};
+        split_pairs(vreg[0][w], h0, l0);
+        split_pairs(vreg[1][w], h1, l1);
+        _Float16 *const at = dst + vat0 + w * 32 * 64;
+        *(v4u *)at = (v4u){h0.x, h0.y, h1.x, h1.y};
+        *(v4u *)(TAIL && w == VCH - 1 ? dst + vat1 + w * 32 * 64 : at + NEB * 16 * 64) = (v4u){l0.x, l0.y, l1.x, l1.y};
       }
     }
   };
+  const auto lds_barrier = [] {                   // (loads from memory stay in flight)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
 
-  load_tile(0);                            // first key tile and the queries are in flight together
+  v4f kreg[KCH], vreg[2][VCH];
   int q_row[QB];
   v8h qh[QB][NI], qlo[QB][NM > 0 ? NM : 1];       // with TAIL, qh[.][NM] is the packed tail operand
   {
+    // the first two key tiles and the queries are in flight together
+    v4f kfirst[KCH], vfirst[2][VCH];
+    load_tile(0, kfirst, vfirst);
     // all query loads are issued before any is used; rows beyond T read row T-1 (their results are never
     // stored), features beyond d read the last chunk and are zeroed below
     v4f qraw[QB][NCH][2];
@@ -551,6 +543,9 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
         qraw[j][c][1] = *(const v4f *)(src + min(f + 4, hd - 4));
       }
     }
+    if (64 < T) load_tile(64, kreg, vreg);
+#pragma unroll
+    for (int u = 0; u < KCH + VCH; ++u) store_unit(u, kv_s[0], kfirst, vfirst);
 #pragma unroll
     for (int j = 0; j < QB; ++j)
 #pragma unroll
@@ -572,61 +567,86 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
         }
       }
   }
+  v4f o[QB][NEB];
+#pragma unroll
+  for (int j = 0; j < QB; ++j)
+#pragma unroll
+    for (int e = 0; e < NEB; ++e) o[j][e] = (v4f){0.f, 0.f, 0.f, 0.f};
+  float m_run[QB], l_run[QB];
+#pragma unroll
+  for (int j = 0; j < QB; ++j) {
+    m_run[j] = -INFINITY;
+    l_run[j] = 0.0f;
+  }
+  // this lane's fragments: row ql of a block, unit g of a K plane, units g and 4 + g of a V^T row; of the tail, the lane groups take
+  // hi, lo, hi (and hi again, against zeros)
+  const int kat = ql * 32 + ((g ^ (ql >> 2)) << 3), tat = ql * 16 + (((g == 1 ? 1 : 0) ^ (ql >> 3)) << 3);
+  const int vat[2] = {ql * 64 + ((g ^ (ql >> 1)) << 3), ql * 64 + (((4 + g) ^ (ql >> 1)) << 3)};
+  lds_barrier();
+
   for (int k0 = 0; k0 < T; k0 += 64) {
-    __syncthreads();                       // everyone is done with the previous tile
-    store_tile();
-    __syncthreads();
-    if (k0 + 64 < T) load_tile(k0 + 64);   // in flight during the MFMAs below
+    const bool more = k0 + 64 < T;
+    const _Float16 *const cur = kv_s[NBUF == 2 ? (k0 >> 6) & 1 : 0], *const curv = cur + KSZ;
+    _Float16 *const nxt = kv_s[NBUF == 2 ? ((k0 >> 6) & 1) ^ 1 : 0];
 
     // S^T = K Q^T: the K fragments run two iterations ahead of the MFMAs that use them (LDS latency is
-    // several MFMA groups long and a wavefront is alone on its SIMD)
+    // several MFMA groups long and a wavefront is alone on its SIMD).  The next tile goes to the other buffer behind the products
     v4f s[QB][4];
-    constexpr int NS = 4 * NI;
-    v8h kfh[3], kfl[3];
-    auto load_k = [&](int it, int slot) {
-      const int kt = it / NI, c = it % NI;
-      if (c < NM) {
-        kfh[slot] = *(const v8h *)(Khi + (kt * 16 + ql) * KROW + 32 * c + 8 * g);
-        kfl[slot] = *(const v8h *)(Klo + (kt * 16 + ql) * KROW + 32 * c + 8 * g);
-      } else {
-        kfh[slot] = *(const v8h *)(Kt + (kt * 16 + ql) * TROW + 8 * g);
+    auto scores = [&](auto stage_next) {
+      constexpr int NS = 4 * NI, NU = KCH + VCH;
+      v8h kfh[3], kfl[3];
+      auto load_k = [&](int it, int slot) {
+        const int kt = it / NI, c = it % NI;
+        if (c < NM) {
+          kfh[slot] = *(const v8h *)(cur + c * KPL + kt * 16 * 32 + kat);
+          kfl[slot] = *(const v8h *)(cur + (NM + c) * KPL + kt * 16 * 32 + kat);
+        } else {
+          kfh[slot] = *(const v8h *)(cur + 2 * NM * KPL + kt * 16 * 16 + tat);
+        }
+      };
+      load_k(0, 0);
+      load_k(1, 1);
+      v4f acc[QB];
+#pragma unroll
+      for (int it = 0; it < NS; ++it) {
+        const int kt = it / NI, c = it % NI, slot = it % 3;
+        if (it + 2 < NS) load_k(it + 2, (it + 2) % 3);
+        __builtin_amdgcn_sched_barrier(0);
+        const v8h kh = kfh[slot], kl = kfl[slot];
+        if (c == 0) {
+#pragma unroll
+          for (int j = 0; j < QB; ++j) acc[j] = (v4f){0.f, 0.f, 0.f, 0.f};
+        }
+        // the query blocks alternate so that consecutive MFMAs do not wait on each other's result
+        if (c < NM) {
+#pragma unroll
+          for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, qh[j][c], acc[j], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qlo[j][c < NM ? c : 0], acc[j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qh[j][c], acc[j], 0, 0, 0);
+        if constexpr (decltype(stage_next)::value) {
+#pragma unroll
+          for (int u = NU * it / NS; u < NU * (it + 1) / NS; ++u) store_unit(u, nxt, kreg, vreg);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (c == NI - 1) {
+#pragma unroll
+          for (int j = 0; j < QB; ++j) s[j][kt] = acc[j];
+        }
       }
     };
-    load_k(0, 0);
-    load_k(1, 1);
-    v4f acc[QB];
-#pragma unroll
-    for (int it = 0; it < NS; ++it) {
-      const int kt = it / NI, c = it % NI, slot = it % 3;
-      if (it + 2 < NS) load_k(it + 2, (it + 2) % 3);
-      __builtin_amdgcn_sched_barrier(0);
-      const v8h kh = kfh[slot], kl = kfl[slot];
-      if (c == 0) {
-#pragma unroll
-        for (int j = 0; j < QB; ++j) acc[j] = (v4f){0.f, 0.f, 0.f, 0.f};
-      }
-      // the query blocks alternate so that consecutive MFMAs do not wait on each other's result
-      if (c < NM) {
-#pragma unroll
-        for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kl, qh[j][c], acc[j], 0, 0, 0);
-#pragma unroll
-        for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qlo[j][c < NM ? c : 0], acc[j], 0, 0, 0);
-      }
-#pragma unroll
-      for (int j = 0; j < QB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kh, qh[j][c], acc[j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (c == NI - 1) {
-#pragma unroll
-        for (int j = 0; j < QB; ++j) s[j][kt] = acc[j];
-      }
-    }
+    if (NBUF == 2 && more) scores(std::true_type{});
+    else scores(std::false_type{});
+    if (NBUF == 2 && k0 + 128 < T) load_tile(k0 + 128, kreg, vreg);       // in flight until the next tile's products
     // the first V^T fragments are requested before the softmax arithmetic, which hides their latency
     constexpr int NP = 2 * NEB;
     v8h vfh[3], vfl[3];
     auto load_v = [&](int it, int slot) {
       const int a = it / NEB, e = it % NEB;
-      vfh[slot] = *(const v8h *)(Vsh[0] + (e * 16 + ql) * VROW + 32 * a + 8 * g);
-      if (!TAIL || e < NEB - 1) vfl[slot] = *(const v8h *)(Vsh[1] + (e * 16 + ql) * VROW + 32 * a + 8 * g);
+      vfh[slot] = *(const v8h *)(curv + e * 16 * 64 + vat[a]);
+      if (!TAIL || e < NEB - 1) vfl[slot] = *(const v8h *)(curv + (NEB + e) * 16 * 64 + vat[a]);
     };
     load_v(0, 0);
     load_v(1, 1);
@@ -702,6 +722,15 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
       for (int j = 0; j < QB; ++j) o[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh, ph[j][a], o[j][e], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (more) {
+      if constexpr (NBUF == 1) {
+        lds_barrier();                            // everyone is done with this tile
+#pragma unroll
+        for (int u = 0; u < KCH + VCH; ++u) store_unit(u, nxt, kreg, vreg);
+        if (k0 + 128 < T) load_tile(k0 + 128, kreg, vreg);
+      }
+      lds_barrier();
+    }
   }
   if constexpr (TAIL) {                           // the lo halves' rows to those of their features: 8 rows = 2 lane groups further
 #pragma unroll
@@ -716,8 +745,8 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   const QParam t = *qp;
   const float qs = t.s, qz = (float)t.z;
   constexpr int SRB = 16 * NEB;                   // staged row: the head's features, padded
-  static_assert(NQ * SRB + FIX_CAP * 8 <= (int)sizeof(Ksh), "the epilogue's staging area must fit in the K tile buffers");
-  unsigned char *stage = (unsigned char *)Ksh;
+  static_assert(NQ * SRB + FIX_CAP * 8 <= 2 * KSZ, "the epilogue's staging area must fit in the K tile");
+  unsigned char *stage = (unsigned char *)kv_s;
   int *fix_cnt = &fix_cnt_s;
   int *fix_ent = (int *)(stage + NQ * SRB);       // [FIX_CAP][2]: query within the workgroup, feature
   __syncthreads();                                // every wavefront is past its last K / V^T fragment
@@ -768,8 +797,8 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
     }
   }
   __syncthreads();
-  constexpr int FB = (int)sizeof(Vsh) / (NW * 16) < 64 ? (int)sizeof(Vsh) / (NW * 16) : 64;   // outputs per batch of parts in LDS
-  decide_again_and_store<NEB, NQ, NW, FB>(stage, &fix_cnt_s, fix_ent, (double *)&Vsh[0][0], m_s, Qp + tok_base, kbase, vbase, qblk * NQ, T,
+  constexpr int FB = 2 * VSZ / (NW * 16) < 64 ? 2 * VSZ / (NW * 16) : 64;       // outputs per batch of parts in LDS
+  decide_again_and_store<NEB, NQ, NW, FB>(stage, &fix_cnt_s, fix_ent, (double *)(kv_s[0] + KSZ), m_s, Qp + tok_base, kbase, vbase, qblk * NQ, T,
                                           Tp, hd, D, qs, qz, q_out + (size_t)b * T * D + (size_t)h * hd);
 }
 

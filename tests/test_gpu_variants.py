@@ -44,6 +44,18 @@ def _net(hidden, heads, mlp, h, w, patch=2):
     ("attention: 72 features a head, 1 key past a tile", _net(288, 4, 512, 10, 26), 2, 8),
     ("attention: two query blocks a wavefront, 575 tokens", _net(256, 4, 512, 46, 50), 33, 8),
     ("attention: 16 features a head", _net(64, 4, 128, 16, 22), 2, 8),
+    # keys in LDS: two tiles there, or one (76 and 80 features); one, two, three and more tiles of keys, the last one full, ragged or with a
+    # single key; a packed tail of four features, padded feature chunks
+    ("attention, one query block: 72 features, 64 tokens", _net(1152, 16, 1152, 16, 16), 9, 8),
+    ("attention, one query block: 72 features, 128 tokens", _net(1152, 16, 1152, 16, 32), 5, 8),
+    ("attention, one query block: 64 features, 192 tokens", _net(384, 6, 512, 24, 32), 9, 8),
+    ("attention, one query block: 80 features, 260 tokens", _net(320, 4, 512, 20, 52), 9, 8),
+    ("attention, one query block: 76 features, 35 tokens", _net(304, 4, 512, 10, 14), 36, 8),
+    ("attention, two query blocks: 68 features, 193 tokens", _net(272, 4, 512, 2, 386), 34, 8),
+    ("attention, two query blocks: 44 features, 256 tokens", _net(176, 4, 512, 32, 32), 33, 8),
+    ("attention, two query blocks: 20 features, 129 tokens", _net(80, 4, 512, 6, 86), 34, 8),
+    ("attention, two query blocks: 80 features, 200 tokens", _net(320, 4, 512, 20, 40), 33, 8),
+    ("attention, two query blocks: 12 features, 320 tokens", _net(48, 4, 512, 32, 40), 22, 8),
     # keys shared by the wavefronts: two rounds of tiles, the second of three wavefronts (the last one's ragged); one tile for three
     # wavefronts and a half of queries; fewer keys than a tile, padded feature chunk; 80 features a head
     ("attention, shared keys: 425 tokens, 32 queries a workgroup", _net(1152, 16, 1152, 50, 34), 1, 8),
