@@ -289,8 +289,12 @@ __device__ __forceinline__ void split_operand(v4f a, v4f b, v8h &hi, v8h &lo) {
 // the rows go out.  qbase, kbase, vbase: float32 Q, K and V^T of the (batch, head); m_s: reference point of the exponentials
 // per query; parts: FB * NW * 16 bytes of LDS, [output][wavefront][2]; q_out: the head's first byte in the batch element's
 // first output row.
+// ONE: at most 64 NW keys, so that a wavefront has one group of them, the same for all outputs: its rows are loaded once and no next group is
+// requested.  A kernel of its own for each: with both ways in one, registers went to scratch memory, and a launch that has any, even if
+// only this part uses it, is 10 - 20 % slower.  16 heads of 72, us, the general way | ONE: 64 x 256 tokens 88.6 | 87.1, 4 x 256 14.2 | 13.6,
+// 8 x 256 19.1 | 18.6; with the rows that go out below: 64 x 256 90.8 -> 87.1, 4 x 256 14.4 -> 13.6, 10 x 425 55.6 -> 54.8.
 constexpr int FIX_CAP = 192;
-template <int NEB, int NQ, int NW, int FB>
+template <int NEB, int NQ, int NW, int FB, bool ONE>
 __device__ __forceinline__ void decide_again_and_store(unsigned char *stage, const int *fix_cnt, const int *fix_ent, double *parts,
                                                        const float *m_s, const float *qbase, const float *kbase, const float *vbase,
                                                        int q_first, int T, int Tp, int hd, int D, float qs, float qz,
@@ -308,60 +312,128 @@ __device__ __forceinline__ void decide_again_and_store(unsigned char *stage, con
   const int h4 = lane & 3, kl = lane >> 2;
   for (int base = 0; base < nfix; base += FB) {
     const int nb = min(nfix - base, FB);
-    for (int fi = 0; fi < nb; ++fi) {
-      const int qloc = fix_ent[2 * (base + fi)], feat = fix_ent[2 * (base + fi) + 1];
-      const float *qr = qbase + (size_t)(q_first + qloc) * hd;
-      const float *vrow = vbase + (size_t)feat * Tp;            // V^T row of the feature, keys in vt_pos order
+    if constexpr (ONE) {
       v4f kv[4][NEB];
-      float va;
-      auto load_row = [&](int key, v4f (&dst)[NEB]) {
-        const float *r = kbase + (size_t)min(key, T - 1) * hd;
+      // this lane's chunks of a key row: h4, h4 + 4, ...; the last one is clamped into the row (its query operand is zero then)
+      const auto load_row = [&](int key0, v4f (&dst)[NEB]) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));              // (the places are formed when they are needed, not kept)
+        const int h4 = ln & 3, kl = ln >> 2;
+        const unsigned r = (unsigned)(min(key0 + kl, T - 1) * hd), clast = (unsigned)min(16 * (NEB - 1) + 4 * h4, hd - 4);
 #pragma unroll
-        for (int c = 0; c < NEB; ++c) dst[c] = *(const v4f *)(r + min(16 * c + 4 * h4, hd - 4));
+        for (int c = 0; c < NEB - 1; ++c) dst[c] = *(const v4f *)(kbase + (r + 4 * h4) + 16 * c);
+        dst[NEB - 1] = *(const v4f *)(kbase + (r + clast));
       };
-      int k0 = 64 * wave;
+      const auto load_group = [&]() {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) load_row(k0 + 16 * u + kl, kv[u]);
-      va = vrow[vt_pos(min(k0 + 16 * h4 + kl, Tp - 1))];
-      double qd[NEB][4];
+        for (int u = 0; u < 4; ++u) load_row(64 * wave + 16 * u, kv[u]);
+      };
+      load_group();
+#pragma unroll 1
+      for (int fi = 0; fi < nb; ++fi) {
+        const int qloc = __builtin_amdgcn_readfirstlane(fix_ent[2 * (base + fi)]);
+        const int feat = __builtin_amdgcn_readfirstlane(fix_ent[2 * (base + fi) + 1]);
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int h4 = ln & 3, kl = ln >> 2;
+        const float *qr = qbase + (size_t)(q_first + qloc) * hd;
+        const float *vrow = vbase + (size_t)feat * Tp;          // V^T row of the feature, keys in vt_pos order
+        const float v = vrow[(unsigned)vt_pos(min(64 * wave + 16 * h4 + kl, Tp - 1))];
+        double qd[NEB][4];
 #pragma unroll
-      for (int c = 0; c < NEB; ++c) {
-        const int f = 16 * c + 4 * h4;
-        const v4f t4 = *(const v4f *)(qr + min(f, hd - 4));
+        for (int c = 0; c < NEB; ++c) {
+          const int f = 16 * c + 4 * h4;
+          const v4f t4 = *(const v4f *)(qr + (unsigned)min(f, hd - 4));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) qd[c][e] = f < hd ? (double)t4[e] : 0.0;
-      }
-      const double mref = (double)m_s[qloc] * 0.6931471805599453;       // base 2 -> natural
-      double den = 0.0, num = 0.0;
-      for (; k0 < T; k0 += 64 * NW) {
-        const float v = va;
-        double sc = 0.0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-          for (int c = 0; c < NEB; ++c) {
-            a0 = fma(qd[c][0], (double)kv[u][c][0], a0);
-            a1 = fma(qd[c][1], (double)kv[u][c][1], a1);
-            a0 = fma(qd[c][2], (double)kv[u][c][2], a0);
-            a1 = fma(qd[c][3], (double)kv[u][c][3], a1);
-          }
-          load_row(k0 + 64 * NW + 16 * u + kl, kv[u]);          // beyond T: the last row again, never used
-          a0 += a1;
-          a0 += dpp_move_d<0xB1>(a0);                           // quad_perm [1, 0, 3, 2], then [2, 3, 0, 1]: the four lanes
-          a0 += dpp_move_d<0x4E>(a0);                           // hold the whole dot product
-          sc = h4 == u ? a0 : sc;
+          for (int e = 0; e < 4; ++e) qd[c][e] = f < hd ? (double)t4[e] : 0.0;
         }
-        va = vrow[vt_pos(min(k0 + 64 * NW + 16 * h4 + kl, Tp - 1))];
-        const double pj = k0 + 16 * h4 + kl < T ? exp(sc * rs - mref) : 0.0;
-        den += pj;
-        num = fma(pj, (double)v, num);
+        const double mref = (double)m_s[qloc] * 0.6931471805599453;     // base 2 -> natural
+        double den = 0.0, num = 0.0;
+        if (64 * wave < T) {
+          double sc = 0.0;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+            for (int c = 0; c < NEB; ++c) {
+              a0 = fma(qd[c][0], (double)kv[u][c][0], a0);
+              a1 = fma(qd[c][1], (double)kv[u][c][1], a1);
+              a0 = fma(qd[c][2], (double)kv[u][c][2], a0);
+              a1 = fma(qd[c][3], (double)kv[u][c][3], a1);
+            }
+            a0 += a1;
+            a0 += dpp_move_d<0xB1>(a0);                         // quad_perm [1, 0, 3, 2], then [2, 3, 0, 1]: the four lanes
+            a0 += dpp_move_d<0x4E>(a0);                         // hold the whole dot product
+            sc = h4 == u ? a0 : sc;
+            __builtin_amdgcn_sched_barrier(0);                  // (the conversions of one row at a time: all of them would not fit)
+          }
+          const double pj = 64 * wave + 16 * h4 + kl < T ? exp(sc * rs - mref) : 0.0;
+          den += pj;
+          num = fma(pj, (double)v, num);
+        }
+        den = wave_sum_dpp(den);
+        num = wave_sum_dpp(num);
+        if (lane == 0) {
+          parts[(fi * NW + wave) * 2] = den;
+          parts[(fi * NW + wave) * 2 + 1] = num;
+        }
       }
-      den = wave_sum_dpp(den);
-      num = wave_sum_dpp(num);
-      if (lane == 0) {
-        parts[(fi * NW + wave) * 2] = den;
-        parts[(fi * NW + wave) * 2 + 1] = num;
+    } else {
+      for (int fi = 0; fi < nb; ++fi) {
+        const int qloc = fix_ent[2 * (base + fi)], feat = fix_ent[2 * (base + fi) + 1];
+        const float *qr = qbase + (size_t)(q_first + qloc) * hd;
+        const float *vrow = vbase + (size_t)feat * Tp;            // V^T row of the feature, keys in vt_pos order
+        v4f kv[4][NEB];
+        float va;
+        auto load_row = [&](int key, v4f (&dst)[NEB]) {
+          const float *r = kbase + (size_t)min(key, T - 1) * hd;
+#pragma unroll
+          for (int c = 0; c < NEB; ++c) dst[c] = *(const v4f *)(r + min(16 * c + 4 * h4, hd - 4));
+        };
+        int k0 = 64 * wave;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load_row(k0 + 16 * u + kl, kv[u]);
+        va = vrow[vt_pos(min(k0 + 16 * h4 + kl, Tp - 1))];
+        double qd[NEB][4];
+#pragma unroll
+        for (int c = 0; c < NEB; ++c) {
+          const int f = 16 * c + 4 * h4;
+          const v4f t4 = *(const v4f *)(qr + min(f, hd - 4));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) qd[c][e] = f < hd ? (double)t4[e] : 0.0;
+        }
+        const double mref = (double)m_s[qloc] * 0.6931471805599453;       // base 2 -> natural
+        double den = 0.0, num = 0.0;
+        for (; k0 < T; k0 += 64 * NW) {
+          const float v = va;
+          double sc = 0.0;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+            for (int c = 0; c < NEB; ++c) {
+              a0 = fma(qd[c][0], (double)kv[u][c][0], a0);
+              a1 = fma(qd[c][1], (double)kv[u][c][1], a1);
+              a0 = fma(qd[c][2], (double)kv[u][c][2], a0);
+              a1 = fma(qd[c][3], (double)kv[u][c][3], a1);
+            }
+            load_row(k0 + 64 * NW + 16 * u + kl, kv[u]);          // beyond T: the last row again, never used
+            a0 += a1;
+            a0 += dpp_move_d<0xB1>(a0);                           // quad_perm [1, 0, 3, 2], then [2, 3, 0, 1]: the four lanes
+            a0 += dpp_move_d<0x4E>(a0);                           // hold the whole dot product
+            sc = h4 == u ? a0 : sc;
+          }
+          va = vrow[vt_pos(min(k0 + 64 * NW + 16 * h4 + kl, Tp - 1))];
+          const double pj = k0 + 16 * h4 + kl < T ? exp(sc * rs - mref) : 0.0;
+          den += pj;
+          num = fma(pj, (double)v, num);
+        }
+        den = wave_sum_dpp(den);
+        num = wave_sum_dpp(num);
+        if (lane == 0) {
+          parts[(fi * NW + wave) * 2] = den;
+          parts[(fi * NW + wave) * 2 + 1] = num;
+        }
       }
     }
     __syncthreads();
@@ -378,15 +450,23 @@ __device__ __forceinline__ void decide_again_and_store(unsigned char *stage, con
     }
     __syncthreads();
   }
-  // rows out: hd bytes per query (a multiple of 4), contiguous in the output row of the token
-  const int wpr = hd >> 2;                        // 32-bit words per row (<= 20): 32 lanes per row, 2 NW rows per pass
-  const int wd = tid & 31;
+  // rows out: hd bytes per query (a multiple of 4), contiguous in the output row of the token.  The lanes go by the 32-bit words of all
+  // rows, and every word is read before the first is stored (one after the other, each waited for LDS: 2400 clocks a workgroup)
+  const int wpr = hd >> 2;                        // words per row (at most 4 NEB)
+  const float inv_wpr = __builtin_amdgcn_rcpf((float)wpr);
+  constexpr int NO = (NQ * 4 * NEB + 64 * NW - 1) / (64 * NW);
+  unsigned word[NO];
+  unsigned at[NO];
+  const int n_out = min(NQ, T - q_first) * wpr;
 #pragma unroll
-  for (int r0 = 0; r0 < NQ; r0 += 2 * NW) {
-    const int qloc = r0 + (tid >> 5), qg = q_first + qloc;
-    if (wd < wpr && qg < T)
-      *(unsigned *)(q_out + (size_t)qg * D + 4 * wd) = *(const unsigned *)(stage + qloc * SRB + 4 * wd);
+  for (int k = 0; k < NO; ++k) {
+    const int i = min(tid + 64 * NW * k, NQ * wpr - 1), r = (int)(((float)i + 0.5f) * inv_wpr), wd = i - r * wpr;      // i / wpr, exactly
+    word[k] = *(const unsigned *)(stage + r * SRB + 4 * wd);
+    at[k] = (unsigned)((q_first + r) * D + 4 * wd);
   }
+#pragma unroll
+  for (int k = 0; k < NO; ++k)
+    if (tid + 64 * NW * k < n_out) *(unsigned *)(q_out + at[k]) = word[k];
 }
 
 // NCH feature chunks of 32 (operand width), NEB feature blocks of 16 that hold real features, QB query blocks of 16 per
@@ -420,7 +500,7 @@ __device__ __forceinline__ void decide_again_and_store(unsigned char *stage, con
 // The sum of the probabilities stays a float32 addition each: a row of ones in V^T gives it for free (2 - 4 % of a launch), but
 // from the 22 bits of the halves and with the matrix cores' accumulation, 1.2 (256 keys) to 1.6 (4096) times as far from
 // float64, and the outputs of a sharp softmax over 4096 keys 1.5 times.
-template <int NCH, int NEB, int QB, bool TAIL>
+template <int NCH, int NEB, int QB, bool TAIL, bool ONE>
 __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__restrict__ Qp, const float *__restrict__ Kp,
                                                             const float *__restrict__ Vt, int BH, int T, int Tp, int H, int hd, int DPv,
                                                             float q_mul, const QParam *qp, int8_t *__restrict__ q_out) {
@@ -798,7 +878,7 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   }
   __syncthreads();
   constexpr int FB = 2 * VSZ / (NW * 16) < 64 ? 2 * VSZ / (NW * 16) : 64;       // outputs per batch of parts in LDS
-  decide_again_and_store<NEB, NQ, NW, FB>(stage, &fix_cnt_s, fix_ent, (double *)(kv_s[0] + KSZ), m_s, Qp + tok_base, kbase, vbase, qblk * NQ, T,
+  decide_again_and_store<NEB, NQ, NW, FB, ONE>(stage, &fix_cnt_s, fix_ent, (double *)(kv_s[0] + KSZ), m_s, Qp + tok_base, kbase, vbase, qblk * NQ, T,
                                           Tp, hd, D, qs, qz, q_out + (size_t)b * T * D + (size_t)h * hd);
 }
 
@@ -811,7 +891,7 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
 // kernel is for launches that fit the chip at once; what is left is memory latency, about 1100 vector instructions a wavefront
 // and the exact decisions (2 us).  The running sums meet in LDS at the end: with M the largest running max of a query, each wavefront's sums are scaled by
 // 2^(m - M) in float32, the arithmetic of the rescaling in the key loop.
-template <int NCH, int NEB, int QB, bool TAIL>
+template <int NCH, int NEB, int QB, bool TAIL, bool ONE>
 __global__ __launch_bounds__(256, 1) void attention_f16_keys_kernel(const float *__restrict__ Qp, const float *__restrict__ Kp,
                                                                     const float *__restrict__ Vt, int BH, int T, int Tp, int H, int hd,
                                                                     int DPv, float q_mul, const QParam *qp, int8_t *__restrict__ q_out) {
@@ -1077,7 +1157,7 @@ __global__ __launch_bounds__(256, 1) void attention_f16_keys_kernel(const float 
     *(unsigned *)(stage + qloc * SRB + f) = w4 ^ 0x80808080u;
   }
   __syncthreads();
-  decide_again_and_store<NEB, NQ, NW, FB>(stage, &fix_cnt_s, fix_ent, (double *)osum, m_s, qbase, kbase, vbase, qblk * NQ, T, Tp, hd, D,
+  decide_again_and_store<NEB, NQ, NW, FB, ONE>(stage, &fix_cnt_s, fix_ent, (double *)osum, m_s, qbase, kbase, vbase, qblk * NQ, T, Tp, hd, D,
                                           qs, qz, q_out + (size_t)b * T * D + (size_t)h * hd);
 }
 
@@ -1102,12 +1182,17 @@ hipError_t launch_attention_f16(const float *q32, const float *k32, const float 
   dim3 grid((B * H + 7) / 8 * 8, (T + per_wg - 1) / per_wg);
 #define QC_ATT_LAUNCH(...) \
   hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(256), 0, st, q32, k32, vt32, B * H, T, Tp, H, hd, DPv, q_mul, qp, q_out)
-#define QC_ATT(NCH, NEB, TAIL)                                                \
-  do {                                                                        \
-    if (kq == 1) QC_ATT_LAUNCH(attention_f16_keys_kernel<NCH, NEB, 1, TAIL>); \
-    else if (kq == 2) QC_ATT_LAUNCH(attention_f16_keys_kernel<NCH, NEB, 2, TAIL>); \
-    else if (qb == 1) QC_ATT_LAUNCH(attention_f16_kernel<NCH, NEB, 1, TAIL>); \
-    else QC_ATT_LAUNCH(attention_f16_kernel<NCH, NEB, 2, TAIL>);              \
+#define QC_ATT_ONE(NCH, NEB, TAIL, ONE)                                            \
+  do {                                                                             \
+    if (kq == 1) QC_ATT_LAUNCH(attention_f16_keys_kernel<NCH, NEB, 1, TAIL, ONE>); \
+    else if (kq == 2) QC_ATT_LAUNCH(attention_f16_keys_kernel<NCH, NEB, 2, TAIL, ONE>); \
+    else if (qb == 1) QC_ATT_LAUNCH(attention_f16_kernel<NCH, NEB, 1, TAIL, ONE>); \
+    else QC_ATT_LAUNCH(attention_f16_kernel<NCH, NEB, 2, TAIL, ONE>);              \
+  } while (0)
+#define QC_ATT(NCH, NEB, TAIL)                      \
+  do {  /* 256: 64 keys a wavefront (decide_again_and_store) */ \
+    if (T <= 256) QC_ATT_ONE(NCH, NEB, TAIL, true); \
+    else QC_ATT_ONE(NCH, NEB, TAIL, false);         \
   } while (0)
   const bool tail = nch > 1 && hd - 32 * (nch - 1) <= 8;      // at most 8 features in the last chunk
   if (nch == 1 && neb == 1) QC_ATT(1, 1, false);
@@ -1119,6 +1204,7 @@ hipError_t launch_attention_f16(const float *q32, const float *k32, const float 
   else if (nch == 3 && neb == 5) QC_ATT(3, 5, false);
   else return hipErrorInvalidValue;
 #undef QC_ATT
+#undef QC_ATT_ONE
 #undef QC_ATT_LAUNCH
   return hipGetLastError();
 }
