@@ -310,15 +310,19 @@ __global__ __launch_bounds__(256, 2) void sgemm_kernel(SgemmArgs p) {
 
 // The same product for operands that are both contiguous along k, K a multiple of 4 (split K: whole slabs), or both along their own
 // index, and take 16-byte loads, on tiles of 64 WT x 64 WT whose slabs go straight to LDS (gemm_f32_tile.h).  Same chains, same bits.  What bounds it: the matrix
-// rate at the clock the chip holds (2.1 - 2.3 GHz): of a launch's cycles the matrix cores are busy 85 % (similarity, epilogue included).  32768 x 1638 x 4096: 4.2 ms on sgemm_kernel
-// (105 TFLOP/s, slabs through registers, two workgroups a compute unit), 3.2 here (138; four buffers 3.3, eight 3.2, ten 3.25, slabs of
-// 32 k 3.3, wavefronts of 128 x 64 3.5, tiles of 128 x 256 3.25); the library's product takes 2.96.  The order of the tiles made
-// no difference.  L^T L of 32768 x 1640 (three): 3.0 ms there, 2.6 here.
+// rate at the clock the chip holds (2.1 - 2.3 GHz).  32768 x 1638 x 4096: 4.2 ms on sgemm_kernel (105 TFLOP/s, slabs through
+// registers, two workgroups a compute unit), 3.2 here with one workgroup of 128 x 128 and six buffers a compute unit (138; four buffers 3.3,
+// eight 3.2, ten 3.25, slabs of 32 k 3.3, wavefronts of 128 x 64 3.5, tiles of 128 x 256 3.25); the library's product takes 2.96.  The order of
+// the tiles made no difference.  Four buffers leave room for two such workgroups (64 KB of LDS each), so that one multiplies while
+// the other starts or stores, which a lone one does with the matrix cores idle: similarity of three subsamples with its epilogue 11.08 ->
+// 10.78 ms (119 -> 122 TFLOP/s), L^T L of 32768 x 1640 (three; 3.0 ms on sgemm_kernel) 2.60 -> 2.51, block products 76 -> 67 us.  Tiles of
+// 64 x 64 have room for three with six buffers; four buffers made no difference there.
 constexpr int NT_BK = 16;
 template <int WT, int EPI, bool TN>      // TN: both operands contiguous along their own index (plain products)
-__global__ __launch_bounds__(256, WT == 2 ? 1 : 2) void sgemm_slab_kernel(SgemmArgs p) {
-  using Tile = qc::F32Tile<2, 2, WT, WT, NT_BK, 6>;
-  __shared__ __align__(16) float slabs[6 * Tile::SLAB];
+__global__ __launch_bounds__(256, 2) void sgemm_slab_kernel(SgemmArgs p) {
+  constexpr int NS = WT == 2 ? 4 : 6;      // slab buffers
+  using Tile = qc::F32Tile<2, 2, WT, WT, NT_BK, NS>;
+  __shared__ __align__(16) float slabs[NS * Tile::SLAB];
   const int tiles_m = (p.M + Tile::RM - 1) / Tile::RM, tiles_n = (p.N + Tile::RN - 1) / Tile::RN;
   const int total = TN && p.sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n, per_xcd = (total + NUM_XCD - 1) / NUM_XCD;
   const int t = (blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
