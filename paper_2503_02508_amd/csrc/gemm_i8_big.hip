@@ -753,9 +753,13 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   if (const hipError_t e = allow_lds((const void *)kern, smem, lds)) return e;
   const int tiles_n = (a.N + BIG_BN - 1) / BIG_BN, tiles = ((a.M + BM - 1) / BM) * tiles_n;
   GemmArgs b = a;
-  // tile rows per group: every column tile of a group resident on its XCD at once (64 workgroup slots), at most 4
-  // rows of 128 (measured on M = 32768: 4 rows beat 16 by 2 - 9 % on the four linears of DiT-XL/2, 1 - 2 rows lose again)
-  b.group_m = std::min(std::max(64 / tiles_n, 1), 32 / TM);
+  // Tile rows per group.  Few columns: every column tile of a group resident on its XCD at once (64 workgroup slots), at most 4 rows of
+  // 128 (5 column tiles, M = 16384: proj 48.3 us, with 8 rows 49.3, 16 51.7; fc2 95.4, 96.8, 98.0).  From 12 column tiles of 128 rows on, 8
+  // rows: the 64 resident tiles are then 8 x 8, which pulls the least into the L2 (3 rows of fc1 stream all its weights, more than
+  // the L2 holds, once for every 384 rows).  K = 1152, us, 3 - 4 rows | 8 | 12: 3456 columns, M = 32768 174 | 162 | 162, 16384 82 | 82 | 82, 8192 39.8 |
+  // 38.8 | 39.9, 4096 22.6 | 22.0 | 22.7, 4250 25.0 | 25.6 | 25.5; 4608 columns, 32768 186 | 187 | 183, 16384 95.4 | 92.4 | 91.9 (16), 8192 53.3 | 51.8, 4096 34.7
+  // | 33.0 | 34.0, 2048 22.1 | 21.6 | 22.1; K = 768, 3072 columns equal.  64-row tiles gain and lose 2 % by shape and stay.
+  b.group_m = TM == 8 && tiles_n >= 12 ? 8 : std::min(std::max(64 / tiles_n, 1), 32 / TM);
   hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), smem, st, b);
   return hipGetLastError();
 }
