@@ -758,8 +758,13 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   // rows: the 64 resident tiles are then 8 x 8, which pulls the least into the L2 (3 rows of fc1 stream all its weights, more than
   // the L2 holds, once for every 384 rows).  K = 1152, us, 3 - 4 rows | 8 | 12: 3456 columns, M = 32768 174 | 162 | 162, 16384 82 | 82 | 82, 8192 39.8 |
   // 38.8 | 39.9, 4096 22.6 | 22.0 | 22.7, 4250 25.0 | 25.6 | 25.5; 4608 columns, 32768 186 | 187 | 183, 16384 95.4 | 92.4 | 91.9 (16), 8192 53.3 | 51.8, 4096 34.7
-  // | 33.0 | 34.0, 2048 22.1 | 21.6 | 22.1; K = 768, 3072 columns equal.  64-row tiles gain and lose 2 % by shape and stay.
-  b.group_m = TM == 8 && tiles_n >= 12 ? 8 : std::min(std::max(64 / tiles_n, 1), 32 / TM);
+  // | 33.0 | 34.0, 2048 22.1 | 21.6 | 22.1; K = 768, 3072 columns equal.  Not where the last group is a good part of the rows (the 4250 above),
+  // nor for float32 results whose rows are no whole lines, whose pieces then meet later (16300 x 4600 x 1008 127 | 131, 32000 x 3300 x 400 151 | 159), or
+  // of fewer than some 1500 tiles (9000 x 4000 x 1152 69.9 | 70.8; 16384 x 4608 x 1152 115 | 112, 16000 x 3456 x 1152 88.5 | 87.8).  64-row tiles gain and lose
+  // 2 % by shape and stay.
+  const int tiles_m = tiles / tiles_n;
+  const bool eight = TM == 8 && tiles_n >= 12 && (tiles_m % 8 == 0 || tiles_m >= 64) && (EPI != EPI_F32 || ((a.ldy & 31) == 0 && tiles >= 1500));
+  b.group_m = eight ? 8 : std::min(std::max(64 / tiles_n, 1), 32 / TM);
   hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), smem, st, b);
   return hipGetLastError();
 }
