@@ -1172,9 +1172,9 @@ hipError_t launch_attention_f16(const float *q32, const float *k32, const float 
   // 1 x 425 21.8 / 17.1 / 22.5, 3 x 256 23.5 / 17.8 / 15.3, 2 x 425 38.6 / 26.5 / 23.6, 1 x 1024 78 / 52.5 / 44.9, 1 x 64 6.8 / 8.7 /
   // 7.6; 6 heads of 64: 1 x 256 8.4 / 10.1 / 11.0, 4 x 256 12.9 / 10.5 / 11.7.
   // Otherwise two query blocks per wavefront (128 queries per workgroup) when that makes more workgroups than compute units, else
-  // one.  Measured, one / two (16 heads of 72; us): 128 x 256 tokens 240 / 185, 16 x 1024: 361 / 287, 2 x 4096: 854 / 731, 16 x 256:
-  // 34.5 / 27.5, 10 x 425: 57.8 / 55.7, 8 x 256: 18.8 / 19.0, 3 x 425: 28.5 / 32.0; workgroups of eight wavefronts came out
-  // within 2 % at 1024 tokens and behind elsewhere.
+  // one.  Measured, one / two (16 heads of 72; us): 4 x 256 tokens 13.6 / 17.0, 6 x 256 18.0 / 18.0, 8 x 256 18.8 / 19.1, 10 x 256 25.0 / 24.4,
+  // 16 x 256 34.0 / 28.7, 3 x 425 26.1 / 27.6, 4 x 425 27.3 / 30.1, 5 x 425 36.1 / 35.8, 8 x 425 47.2 / 42.2, 1 x 1024 43.3 / 56.9, 2 x 1024 56.5 / 55.3,
+  // 4 x 1024 102 / 84; 6 heads of 64: 32 x 256 24.1 / 23.3, 24 x 256 21.3 / 21.4.
   const long long share = 256 / (beside > 1 ? beside : 1), heads = (long long)B * H;
   const int kq = heads * ((T + 15) / 16) <= share ? 1 : heads * ((T + 31) / 32) <= share ? 2 : 0;
   const int qb = B * H * ((T + 127) / 128) <= 256 ? 1 : 2;
