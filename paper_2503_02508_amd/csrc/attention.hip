@@ -233,7 +233,8 @@ hipError_t launch_attention(const float *qkv, int B, int T, int H, int hd, const
 // owns two blocks of 16 queries, so every K / V^T fragment read from LDS feeds
 // two MFMAs.  Two key tiles lie in LDS: while one is multiplied, the next one is
 // split from registers into the other behind the products of the scores, and the
-// one after that comes into the registers from then on.
+// one after that comes into the registers from then on.  (One query block a
+// wavefront, or no room for two: one tile, written between two barriers.)
 namespace qc {
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
@@ -516,8 +517,12 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   // lo; the packed tail has 8 hi and 8 lo halves a row.  V^T: rows of 64 keys, hi then lo; the last block of TAIL holds both.
   constexpr int KPL = 64 * 32, KTL = TAIL ? 64 * 16 : 0;  // halves of a plane and of the tail
   constexpr int KSZ = 2 * NM * KPL + KTL, VSZ = 64 * (16 * NEB + 16 * (TAIL ? NEB - 1 : NEB));
-  // two tiles where two workgroups a compute unit have room for them (160 KB): not for 76 and 80 features, whose tiles take 45 KB
-  constexpr int NBUF = 4 * (KSZ + VSZ) <= 78 * 1024 ? 2 : 1;
+  // Two tiles where two workgroups a compute unit have room for them (160 KB): not for 76 and 80 features, whose tiles take 45 KB.
+  // Nor with one query block a wavefront: such a launch is small and in a run lies beside the other half's kernels.  By itself it gains
+  // from the second tile (4 x 256 tokens 15.3 -> 14.4 us), a run loses: 28 blocks of width 1152, 50 steps of 8 x 256 tokens (two halves of
+  // 4) 78.6 ms with two tiles, 76.7 with one; 12 blocks, 4 steps: width 384, 40 x 256 tokens 2.90 | 2.80, width 768, 20 x 256 3.44 |
+  // 3.37, width 1152, 4 x 1024 5.82 | 5.74, 6 x 425 3.78 | 3.75, 16 x 256 4.20 | 4.18; 6 x 256 equal.
+  constexpr int NBUF = QB == 2 && 4 * (KSZ + VSZ) <= 78 * 1024 ? 2 : 1;
   __shared__ __align__(16) _Float16 kv_s[NBUF][KSZ + VSZ];
   __shared__ int fix_cnt_s;                       // outputs queued for the exact decision (epilogue)
   __shared__ float m_s[NQ];                       // running max of every query (reference point of the exact decision)
@@ -606,9 +611,10 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   int q_row[QB];
   v8h qh[QB][NI], qlo[QB][NM > 0 ? NM : 1];       // with TAIL, qh[.][NM] is the packed tail operand
   {
-    // the first two key tiles and the queries are in flight together
+    // the queries are in flight together with the first two key tiles, or the first one where LDS holds one
     v4f kfirst[KCH], vfirst[2][VCH];
-    load_tile(0, kfirst, vfirst);
+    if constexpr (NBUF == 2) load_tile(0, kfirst, vfirst);
+    else load_tile(0, kreg, vreg);
     // all query loads are issued before any is used; rows beyond T read row T-1 (their results are never
     // stored), features beyond d read the last chunk and are zeroed below
     v4f qraw[QB][NCH][2];
@@ -623,9 +629,11 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
         qraw[j][c][1] = *(const v4f *)(src + min(f + 4, hd - 4));
       }
     }
-    if (64 < T) load_tile(64, kreg, vreg);
+    if constexpr (NBUF == 2) {
+      if (64 < T) load_tile(64, kreg, vreg);
 #pragma unroll
-    for (int u = 0; u < KCH + VCH; ++u) store_unit(u, kv_s[0], kfirst, vfirst);
+      for (int u = 0; u < KCH + VCH; ++u) store_unit(u, kv_s[0], kfirst, vfirst);
+    }
 #pragma unroll
     for (int j = 0; j < QB; ++j)
 #pragma unroll
@@ -662,12 +670,21 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   // hi, lo, hi (and hi again, against zeros)
   const int kat = ql * 32 + ((g ^ (ql >> 2)) << 3), tat = ql * 16 + (((g == 1 ? 1 : 0) ^ (ql >> 3)) << 3);
   const int vat[2] = {ql * 64 + ((g ^ (ql >> 1)) << 3), ql * 64 + (((4 + g) ^ (ql >> 1)) << 3)};
-  lds_barrier();
+  lds_barrier();          // (one tile: nothing to publish yet, but a run of 8 x 256 tokens takes 76.7 ms with it, 76.9 without)
 
   for (int k0 = 0; k0 < T; k0 += 64) {
     const bool more = k0 + 64 < T;
+    if constexpr (NBUF == 1) {
+      // at the head of the loop, not behind the V^T products (runs of width 768, 20 x 256 tokens, 3.40 ms there, 3.37 here; width 384, 40 x 256
+      // 2.84 | 2.80)
+      if (k0) lds_barrier();                      // everyone is done with the tile before
+#pragma unroll
+      for (int u = 0; u < KCH + VCH; ++u) store_unit(u, kv_s[0], kreg, vreg);
+      if (more) load_tile(k0 + 64, kreg, vreg);
+      lds_barrier();
+    }
     const _Float16 *const cur = kv_s[NBUF == 2 ? (k0 >> 6) & 1 : 0], *const curv = cur + KSZ;
-    _Float16 *const nxt = kv_s[NBUF == 2 ? ((k0 >> 6) & 1) ^ 1 : 0];
+    _Float16 *const nxt = kv_s[NBUF == 2 ? ((k0 >> 6) & 1) ^ 1 : 0];        // (two tiles)
 
     // S^T = K Q^T: the K fragments run two iterations ahead of the MFMAs that use them (LDS latency is
     // several MFMA groups long and a wavefront is alone on its SIMD).  The next tile goes to the other buffer behind the products
@@ -802,15 +819,7 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
       for (int j = 0; j < QB; ++j) o[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh, ph[j][a], o[j][e], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (more) {
-      if constexpr (NBUF == 1) {
-        lds_barrier();                            // everyone is done with this tile
-#pragma unroll
-        for (int u = 0; u < KCH + VCH; ++u) store_unit(u, nxt, kreg, vreg);
-        if (k0 + 128 < T) load_tile(k0 + 128, kreg, vreg);
-      }
-      lds_barrier();
-    }
+    if (NBUF == 2 && more) lds_barrier();
   }
   if constexpr (TAIL) {                           // the lo halves' rows to those of their features: 8 rows = 2 lane groups further
 #pragma unroll

@@ -146,3 +146,33 @@ def test_the_library_imports_no_allocator():
     names = subprocess.run(["nm", "-D", "--undefined-only", os.path.join(PKG, "libqc.so")], check=True, stdout=subprocess.PIPE, text=True).stdout
     assert "hipLaunchKernel" in names
     assert not re.findall(r"\bhip\w*(?:Malloc|MemPool|MemCreate|MemAlloc)\w*", names)
+
+
+def _resources(obj):
+    """{kernel: (vector registers, LDS bytes, scratch bytes)} of a code object's metadata."""
+    text = subprocess.run([LLVM + "llvm-readobj", "--notes", obj], check=True, stdout=subprocess.PIPE, text=True).stdout
+    out = {}
+    for part in re.split(r"^\s*- \.agpr_count:", text, flags=re.M)[1:]:
+        at = lambda key: re.search(r"\.%s:\s*(\S+)" % key, part).group(1)  # noqa: E731
+        out[at("symbol")] = tuple(int(at(k)) for k in ("vgpr_count", "group_segment_fixed_size", "private_segment_fixed_size"))
+    return out
+
+
+def test_attention_leaves_the_compute_unit_room(tmp_path):
+    """Attention of small launches runs beside the other half's kernels: with two key tiles in LDS (74 KB at 72 features a head) 50
+    steps of 8 x 256 tokens took 78.6 ms, with one 76.7.  And a register in scratch memory costs every launch 10 - 20 %."""
+    if not os.path.exists(LLVM + "llvm-readobj"):
+        pytest.skip("no llvm-readobj")
+    seen = 0
+    for obj in _code_objects(os.path.join(PKG, "libqc.so"), str(tmp_path)):
+        for name, (_, lds, scratch) in _resources(obj).items():
+            m = re.match(r"_ZN2qc20attention_f16_kernelILi(\d)ELi(\d)ELi(\d)E", name)       # 32- and 16-feature blocks, query blocks
+            if not m:
+                continue
+            seen += 1
+            neb, qb = int(m.group(2)), int(m.group(3))
+            assert scratch == 0, (name, scratch)
+            # a tile of K and V^T, hi and lo halves: 64 keys of up to 96 + 80 features
+            if qb == 1:
+                assert lds <= 4 * 64 * (32 * ((neb + 1) // 2) + 16 * neb) + 1024, (name, lds)
+    assert seen >= 14
