@@ -522,7 +522,11 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   // from the second tile (4 x 256 tokens 15.3 -> 14.4 us), a run loses: 28 blocks of width 1152, 50 steps of 8 x 256 tokens (two halves of
   // 4) 78.6 ms with two tiles, 76.7 with one; 12 blocks, 4 steps: width 384, 40 x 256 tokens 2.90 | 2.80, width 768, 20 x 256 3.44 |
   // 3.37, width 1152, 4 x 1024 5.82 | 5.74, 6 x 425 3.78 | 3.75, 16 x 256 4.20 | 4.18; 6 x 256 equal.
-  constexpr int NBUF = QB == 2 && 4 * (KSZ + VSZ) <= 78 * 1024 ? 2 : 1;
+  // Nor for heads of up to 32 features: their kernels fit three or four wavefronts a SIMD, with a tile in flight beside the loop one less.
+  // A block's attention, two | one, us: 24 heads of 16, 32 x 1024 tokens 277 | 266, 64 x 256 50.2 | 46.0, 12 of 32, 32 x 1024 204 | 189,
+  // 8 x 1024 69 | 62, 36 of 32, 16 x 1024 307 | 280, 24 of 20, 8 x 1024 91 | 86.  (A tile, of one buffer, stored behind the V^T products takes as
+  // many registers: the compiler moves the conversions among them.)
+  constexpr int NBUF = NCH > 1 && QB == 2 && 4 * (KSZ + VSZ) <= 78 * 1024 ? 2 : 1;
   __shared__ __align__(16) _Float16 kv_s[NBUF][KSZ + VSZ];
   __shared__ int fix_cnt_s;                       // outputs queued for the exact decision (epilogue)
   __shared__ float m_s[NQ];                       // running max of every query (reference point of the exact decision)
