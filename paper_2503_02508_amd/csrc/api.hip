@@ -647,7 +647,7 @@ static int run_block_full(qc_ctx *ctx, int l, void *x, int xb, const Sub &sb, hi
   {
     GemmArgs a = base(bq.lin[QC_SITE_QKV], qa_ln, D, QC_SITE_QKV);
     a.q32 = q32; a.k32 = k32; a.vt32 = vt32;
-    a.heads = ctx->H; a.hd = ctx->hd; a.DP = ctx->DP; a.Tp = ctx->Tp; a.rows_per_batch = T;
+    a.heads = ctx->H; a.hd = ctx->hd; a.DP = ctx->DP; a.Tp = ctx->Tp; a.rows_per_batch = T; a.beside = sb.lanes;
     if (ctx->keep_qkv_f32) { a.y = ctx->qkv + row0 * 3 * D; a.ldy = 3 * D; }      // row-major copy for inspection
     QC_PROF(QC_K_GEMM_QKV);
     QC_HIP(launch_gemm(a, EPI_QKV, 1, st, QC_SITE_QKV));

@@ -208,13 +208,7 @@ __device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc<TM> &acc, unsi
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
     };
-    // A wavefront's 64 columns cut the rows of heads of 72 features into pieces of 128-byte lines, which streaming stores send to memory one
-    // by one and others let meet in the L2.  Streaming | not, us, heads of 72: 16384 rows of 256 tokens 88 | 76, 8192 53.8 | 42.7,
-    // 2048 (64-row tiles) 16.4 | 14.6; of 64: 16384 56.4 | 54.3.  Ragged tiles, of 72: 4240 rows 25.9 | 23.7, 6000 38.2 | 35.3, 16000 84.8 | 82.6,
-    // 18000 93.9 | 95.8; but 64-row tiles 15.3 | 16.1 (2120), and heads of 64, whole lines, 49.4 | 52.3 (18000), 12.5 | 13.5 (2120).
-    if constexpr (!RAG) rows_out(std::false_type{});
-    else if constexpr (TM == 4) rows_out(std::true_type{});
-    else if ((p.hd & 31) == 0) rows_out(std::true_type{});
+    if (p.stream_qk) rows_out(std::true_type{});
     else rows_out(std::false_type{});
     return;
   }
@@ -765,6 +759,15 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   const int tiles_m = tiles / tiles_n;
   const bool eight = TM == 8 && tiles_n >= 12 && (tiles_m % 8 == 0 || tiles_m >= 64) && (EPI != EPI_F32 || ((a.ldy & 31) == 0 && tiles >= 1500));
   b.group_m = eight ? 8 : std::min(std::max(64 / tiles_n, 1), 32 / TM);
+  // Streaming stores for Q and K.  A wavefront's 64 columns cut the rows of heads of 72 features into pieces of 128-byte lines, which streaming
+  // stores send to memory one by one and others let meet in the L2.  Heads of whole lines are cut into whole lines; those stream where the results of
+  // all launches that run together are more than half of the memory-side cache, from which attention would read what fits.  Whole runs, 12 blocks,
+  // 4 steps, 256 tokens, two halves, ms, streaming | not (MB of all results): heads of 72, width 1152: 64 latents (226) 13.00 | 12.69, 128 (453)
+  // 24.42 | 24.36, 256 (906) 48.7 | 49.0; heads of 64, width 768: 32 (75) 4.48 | 4.47, 64 (151) 7.58 | 7.75, 96 10.86 | 11.00, 256 (604) 27.7 | 28.1,
+  // width 384: 64 (75) 3.76 | 3.73, 128 (151) 6.45 | 6.50, 512 (604) 24.0 | 24.7, width 1152: 64 (226) 12.72 | 12.76, 128 24.2 | 24.4.  Ragged tiles, 425
+  // tokens: 72, 10 and 16 latents 5.07 | 5.05, 7.31 | 7.27, 76 27.9 | 28.0; 64, width 768, 16 latents 4.62 | 4.58, 76 equal.
+  if constexpr (EPI == EPI_QKV)
+    b.stream_qk = (a.hd & 31) == 0 && (size_t)std::max(a.beside, 1) * a.M * a.N * sizeof(float) > ((size_t)128 << 20);
   hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), smem, st, b);
   return hipGetLastError();
 }
