@@ -188,6 +188,8 @@ def test_64_row_tiles_equal_the_small_launches(hw, B, cache, stream):
 
 @pytest.mark.parametrize("model,B", [(_net(1152, 16, 4608, 32, 32), 2 * 16 + 1),        # halves of 17 and 16 latents
                                      (_net(384, 6, 1536, 64, 64), 5), (_net(384, 6, 1536, 50, 34), 41),
+                                     # groups of eight tile rows, the last one of six and of three
+                                     (_net(1152, 16, 4608, 50, 34), 41),
                                      # Q | K | V of both halves above 128 MiB: streaming stores, whole tiles and ragged ones
                                      (_net(384, 6, 1536, 32, 32), 115), (_net(384, 12, 1536, 50, 34), 69)])
 def test_halves_of_a_large_batch(model, B):
