@@ -357,7 +357,7 @@ __device__ __forceinline__ void big_resid(const GemmArgs &p, BigAcc<TM> &acc, un
   }
 }
 
-// float32 rows [M, ldy], any N and M.  NT: streaming stores (below)
+// float32 rows [M, ldy], any N and M.  NT: streaming stores (below), N a multiple of 4
 template <int TM, bool NT>
 __device__ __forceinline__ void big_f32_rows(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
@@ -395,7 +395,7 @@ __device__ __forceinline__ void big_f32_rows(const GemmArgs &p, BigAcc<TM> &acc,
 // rows of whole lines: 4608 115.5 | 121, 1152 41.4 | 42.9, 2304 68 | 68.5.
 template <int TM>
 __device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
-  if ((p.ldy & 31) == 0 || ((p.N & 3) == 0 && (size_t)p.M * p.ldy * sizeof(float) > ((size_t)256 << 20)))
+  if ((p.N & 3) == 0 && ((p.ldy & 31) == 0 || (size_t)p.M * p.ldy * sizeof(float) > ((size_t)256 << 20)))
     big_f32_rows<TM, true>(p, acc, smem, cst, m0, n0, a_s);
   else
     big_f32_rows<TM, false>(p, acc, smem, cst, m0, n0, a_s);
