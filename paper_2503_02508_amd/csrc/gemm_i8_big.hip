@@ -208,7 +208,7 @@ __device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc<TM> &acc, unsi
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
     };
-    if (p.stream_qk) rows_out(std::true_type{});
+    if (TM == 8 && p.stream_qk) rows_out(std::true_type{});    // (launches of 64-row tiles write at most 300 of them, 20 MB)
     else rows_out(std::false_type{});
     return;
   }
@@ -753,9 +753,10 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   // than the L2 holds, once for every 384 rows).  Fewer bytes of K a tile do not pay for the wider order: 16384 rows of qc_w8a8_linear, us, 4 | 8 rows:
   // 4608 columns, K = 512 92.2 | 95.9, 640 99.2 | 102.2, 768 106.7 | 108.2, 896 115.1 | 113.1, 1008 125.8 | 123.9, 1152 130.5 | 126.8, 1408 148.7 | 143.0;
   // 3456, K = 768 85.6 | 87.1, 896 91.6 | 92.0, 1008 102.1 | 101.8, 1152 105.1 | 104.4; packed weights, 4608, K = 768 105.4 | 106.1, 1152 136.8 |
-  // 136.0, 2304 220.0 | 218.5.  In a block fc1 of width 768, 32768 rows, 99.6 | 102.3, and packed, half the bytes, of width 1152, 16384 rows, 100.5 | 104.1.
+  // 136.0, 2304 220.0 | 218.5.  In a block fc1 of width 768, 32768 rows, 99.6 | 102.3.
   // Networks of width 1152, one block by itself, us: QKV of 65536 rows 333 | 321, 32768 164 | 159, 16384 75.7 | 80.2 (without attention beside or
-  // behind it 82 | 82), 8192 42.2 | 41.8; fc1 367 | 365, 185.8 | 185.4, 96.6 | 99.3, 55.9 | 54.6.  What decides is the run, whose halves share the caches: 128 guided
+  // behind it 82 | 82), 8192 42.2 | 41.8; fc1 367 | 365, 185.8 | 185.4, 96.6 | 99.3, 55.9 | 54.6;
+  // packed weights, 16384 rows 100.5 | 104.1, 4096 34.7 | 33.0.  What decides is the run, whose halves share the caches: 128 guided
   // latents of 256 tokens (9 steps, 28 blocks) 88.9 ms with 4 rows, 88.7 with 8; 12 blocks, 4 steps: 32 latents 6.85 | 6.81, 64 12.38 | 12.42, 96 18.28 | 18.18,
   // 128 24.29 | 24.21, 256 equal, 76 of 425 tokens 27.82 | 27.77.
   // Not where the last group is a good part of the rows (M = 4250 25.0 | 25.6), nor for float32 results whose rows are no whole lines, whose pieces
@@ -763,7 +764,7 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   // 80.9 | 81.3, 13000 106.9 | 107.9, 14336 117.7 | 117.2, 24576 186.8 | 182.9; 3456, 12288 90.2 | 91.2, 14336 94.7 | 94.5, 17000 113.7 | 111.8; 4096 columns
   // lose up to 1 % below 3000 tiles: 16384 118.0 | 119.0, 24576 164.7 | 163.8).  64-row tiles gain and lose 2 % by shape and stay.
   const int tiles_m = tiles / tiles_n;
-  const bool eight = TM == 8 && tiles_n >= 12 && a.K >= (W4 && EPI != EPI_F32 ? 1920 : 960) && (tiles_m % 8 == 0 || tiles_m >= 64) &&
+  const bool eight = TM == 8 && tiles_n >= 12 && a.K >= 960 && (tiles_m % 8 == 0 || tiles_m >= 64) &&
                      (EPI != EPI_F32 || ((a.ldy & 31) == 0 && tiles >= 1500));
   b.group_m = eight ? 8 : std::min(std::max(64 / tiles_n, 1), 32 / TM);
   // Streaming stores for Q and K.  A wavefront's 64 columns cut the rows of heads of 72 features into pieces of 128-byte lines, which streaming
