@@ -292,8 +292,12 @@ __device__ __forceinline__ void split_operand(v4f a, v4f b, v8h &hi, v8h &lo) {
 // first output row.
 // ONE: at most 64 NW keys, so that a wavefront has one group of them, the same for all outputs: its rows are loaded once and no next group is
 // requested.  A kernel of its own for each: with both ways in one, registers went to scratch memory, and a launch that has any, even if
-// only this part uses it, is 10 - 20 % slower.  16 heads of 72, us, the general way | ONE: 64 x 256 tokens 88.6 | 87.1, 4 x 256 14.2 | 13.6,
-// 8 x 256 19.1 | 18.6; with the rows that go out below: 64 x 256 90.8 -> 87.1, 4 x 256 14.4 -> 13.6, 10 x 425 55.6 -> 54.8.
+// only this part uses it, is 10 - 20 % slower.  16 heads of 72, us, the general way | ONE: 128 x 256 tokens 179 | 177, 64 x 256 87 | 87, 16 x 256
+// 29.3 | 28.8, 8 x 256 18.4 | 18.1, 4 x 256 13.8 | 13.3; runs of 8 latents of 256 tokens 0.4 % faster.
+// What it costs: a decision takes about 4300 clocks at 256 keys and 10 500 at 1024.  The mean
+// is 0.28 decisions a workgroup of 128 queries at 256 keys, 1.0 at 1024, 4.1 at 4096; but a launch of few rounds of workgroups ends with those that
+// have several.  Us with decisions | with the queue left empty | with this part compiled out: 8 x 1024 tokens 150.5 | 120.2 | 120.1, 64 x 256
+// 87 | 82 | 82, 2 x 4096 724 | 433 | 433, 4 x 256 13.3 | 11.0 | 10.5: all of it is the decisions themselves, nothing registers or code size.
 constexpr int FIX_CAP = 192;
 template <int NEB, int NQ, int NW, int FB, bool ONE>
 __device__ __forceinline__ void decide_again_and_store(unsigned char *stage, const int *fix_cnt, const int *fix_ent, double *parts,
@@ -482,16 +486,17 @@ __device__ __forceinline__ void decide_again_and_store(unsigned char *stage, con
 // products instead of three (the lo x lo terms come with them), and one addition across lanes at the end.
 // (16 heads of 72, 16 x 1024 tokens: 301.6 -> 298 us, and 0.1 - 1 % closer to float64 in the mean.)
 //
-// What bounds it: vector issue.  Per tile of 64 keys a wavefront (QB = 2, d = 72) issues 112 MFMAs and about 300 other vector
+// What bounds the key loop: vector issue.  Per tile of 64 keys a wavefront (QB = 2, d = 72) issues 112 MFMAs and about 300 other vector
 // instructions, 32 of them exponentials.  On this chip an MFMA 16x16x32 takes 18 clocks of the matrix pipe and keeps the SIMD, for
 // whichever of its wavefronts, from issuing for 10 of them (two FMAs behind each cost nothing, every further one 4 clocks), so the
-// two kinds add up to 5000 of the 6150 clocks that a tile of both resident wavefronts takes.  Cycle counters, 64 x 256 tokens, 16
-// heads of 72, clocks a wavefront: first loads and first tile 8400; a tile 6150 at 1024 keys, 5510 here: scores and staging 2540, softmax
-// 1240, V^T products 1060, barrier and loads 670; codes 3500; decisions and rows out 4200.  With one tile in LDS, staged between two
-// barriers, a tile took 6830: 64 x 256 tokens 92.8 -> 90.3 us, 8 x 1024 158 -> 154, 10 x 425 59.5 -> 56.2, 4 x 256 15.3 -> 14.4, 8 x 256
-// 20.2 -> 19.3 (LDS active in 33 % of the cycles -> 28 %, conflicts in 13 % -> 8 %).  Units of K and V^T are dealt to threads such that their
-// places are constants away from a few registers: the tables of places that stood here would not fit beside a tile in flight, and a
-// single register in scratch memory costs more than the second tile gains.
+// two kinds add up to 5000 of the 6170 clocks that a tile of both resident wavefronts takes.  Cycle counters, 8 x 1024 tokens, 16
+// heads of 72, clocks a wavefront: first loads and first tile 9900; 16 tiles of 6170 (scores and staging 2690, softmax 1300, V^T products 1130,
+// barrier and loads 1050); codes 4000; decisions and rows out 12 600: 125 000, twice a slot, of the launch's 290 000 - 340 000, in
+// which 1.5 of a SIMD's two slots are taken in the mean: the rest is the last round, which waits for the workgroups with most decisions.  64 x 256
+// tokens: 8300; 4 tiles of 5580; 3500; 3200.  With one tile in LDS, staged between two barriers, a tile took 6830: 64 x 256 tokens 92.8 -> 90.3 us,
+// 8 x 1024 158 -> 154, 10 x 425 59.5 -> 56.2 (LDS active in 33 % of the cycles -> 28 %, conflicts in 13 % -> 8 %).  Units of K and V^T are dealt to
+// threads such that their places are constants away from a few registers: the tables of places that stood here would not fit beside a tile in flight,
+// and a single register in scratch memory costs more than the second tile gains.
 // Not better: 32x32x16 products (half the issue slots, the same clocks a tile, and the chip, at its power limit, runs them 4 % slower),
 // eight wavefronts on one tile (half the staging, 3 - 10 % slower), one branch for all outputs of a query.
 // Vector work is what was cut before: the
@@ -518,9 +523,9 @@ __global__ __launch_bounds__(256, 2) void attention_f16_kernel(const float *__re
   constexpr int KPL = 64 * 32, KTL = TAIL ? 64 * 16 : 0;  // halves of a plane and of the tail
   constexpr int KSZ = 2 * NM * KPL + KTL, VSZ = 64 * (16 * NEB + 16 * (TAIL ? NEB - 1 : NEB));
   // Two tiles where two workgroups a compute unit have room for them (160 KB): not for 76 and 80 features, whose tiles take 45 KB.
-  // Nor with one query block a wavefront: such a launch is small and in a run lies beside the other half's kernels.  By itself it gains
-  // from the second tile (4 x 256 tokens 15.3 -> 14.4 us), a run loses: 28 blocks of width 1152, 50 steps of 8 x 256 tokens (two halves of
-  // 4) 78.6 ms with two tiles, 76.7 with one; 12 blocks, 4 steps: width 384, 40 x 256 tokens 2.90 | 2.80, width 768, 20 x 256 3.44 |
+  // Nor with one query block a wavefront, whose tile is multiplied in half the time: by itself 4 x 256 tokens 13.0 us with two tiles, 12.5 with one,
+  // 8 x 256 17.5 | 16.9, 1 x 1024 42.1 | 40.9, and beside the other half's kernels, which need LDS too, more: 28 blocks of width 1152, 50 steps
+  // of 8 x 256 tokens (two halves of 4) 78.6 ms | 76.7; 12 blocks, 4 steps: width 384, 40 x 256 tokens 2.90 | 2.80, width 768, 20 x 256 3.43 |
   // 3.37, width 1152, 4 x 1024 5.82 | 5.74, 6 x 425 3.78 | 3.75, 16 x 256 4.20 | 4.18; 6 x 256 equal.
   // Nor for heads of up to 32 features: their kernels fit three or four wavefronts a SIMD, with a tile in flight beside the loop one less.
   // A block's attention, two | one, us: 24 heads of 16, 32 x 1024 tokens 277 | 266, 64 x 256 50.2 | 46.0, 12 of 32, 32 x 1024 204 | 189,
@@ -1181,13 +1186,17 @@ hipError_t launch_attention_f16(const float *q32, const float *k32, const float 
   const float q_mul = 1.4426950408889634f / std::sqrt((float)hd);     // log2(e) / sqrt(d)
   // Keys shared by the wavefronts, 16 (else 32) queries a workgroup, while that makes no more workgroups than this launch's share of
   // the compute units (`beside` launches of its kind run at the same time).  Measured, keys shared with 16 / with 32 queries / not
-  // shared (16 heads of 72; us back to back, 4.5 of them the launch): 1 x 256 tokens 9.3 / 10.7 / 14.5, 2 x 256 18.3 / 11.9 / 15.0,
-  // 1 x 425 21.8 / 17.1 / 22.5, 3 x 256 23.5 / 17.8 / 15.3, 2 x 425 38.6 / 26.5 / 23.6, 1 x 1024 78 / 52.5 / 44.9, 1 x 64 6.8 / 8.7 /
-  // 7.6; 6 heads of 64: 1 x 256 8.4 / 10.1 / 11.0, 4 x 256 12.9 / 10.5 / 11.7.
+  // shared, one query block (16 heads of 72; us back to back, 4.5 of them the launch): 1 x 64 tokens 7.1 / 8.9 / 7.2, 1 x 256 9.9 / 12.2 / 12.4, 2 x 256
+  // 16.7 / 11.7 / 11.8, 1 x 425 22.1 / 17.2 / 18.4, 3 x 256 22.5 / 19.5 / 12.0, 2 x 425 38.9 / 28.1 / 19.1, 1 x 1024 84 / 58.4 / 40.9; 6 heads of 64:
+  // 1 x 256 8.6 / 9.8 / 11.0, 4 x 256 12.7 / 10.2 / 10.6, 5 x 256 12.7 / 10.2 / 11.3, 6 x 256 16.9 / 16.5 / 11.2, 1 x 1024 38.6 / 26.3 / 30.1.  Runs of 12 blocks with
+  // 192 | 256 | 384 for the compute units: 1 x 256 tokens 1.43 | 1.36 | 1.36 ms, 1 x 425 2.05 | 1.99 | 2.00, 3 x 256 1.93 | 1.93 | 2.11; 6 heads: 5 x 256
+  // 1.32 | 1.29 | 1.29, 1 x 1024 1.64 | 1.64 | 1.92.
   // Otherwise two query blocks per wavefront (128 queries per workgroup) when that makes more workgroups than compute units, else
-  // one.  Measured, one / two (16 heads of 72; us): 4 x 256 tokens 13.6 / 17.0, 6 x 256 18.0 / 18.0, 8 x 256 18.8 / 19.1, 10 x 256 25.0 / 24.4,
-  // 16 x 256 34.0 / 28.7, 3 x 425 26.1 / 27.6, 4 x 425 27.3 / 30.1, 5 x 425 36.1 / 35.8, 8 x 425 47.2 / 42.2, 1 x 1024 43.3 / 56.9, 2 x 1024 56.5 / 55.3,
-  // 4 x 1024 102 / 84; 6 heads of 64: 32 x 256 24.1 / 23.3, 24 x 256 21.3 / 21.4.
+  // one.  Measured, one / two (16 heads of 72; us): 4 x 256 tokens 12.5 / 16.5, 6 x 256 16.3 / 17.3, 8 x 256 16.9 / 18.0, 9 x 256 23.4 / 23.6, 10 x 256
+  // 24.0 / 23.6, 12 x 256 27.2 / 25.0, 16 x 256 31.4 / 27.3, 3 x 425 24.5 / 26.6, 4 x 425 25.1 / 29.3, 5 x 425 34.1 / 34.5, 6 x 425 37.5 / 36.8, 8 x 425 43.3 / 39.8,
+  // 1 x 1024 40.9 / 56.2, 2 x 1024 52.2 / 53.0, 3 x 1024 81.9 / 74.2; 6 heads of 64: 20 x 256 14.4 / 15.7, 24 x 256 20.0 / 20.4, 32 x 256 23.9 / 22.0.  Runs with
+  // 192 | 256 | 384 there, two halves: 16 x 256 4.25 | 4.31 | 4.32 ms, 14 x 256 4.05 | 4.00 | 4.00, 8 x 425 4.41 | 4.29 | 4.29, 10 x 425 5.09 | 5.07 | 4.99; width 384,
+  // 40 x 256 2.83 | 2.87 | 2.87, 56 x 256 3.58 | 3.59 | 3.64.
   const long long share = 256 / (beside > 1 ? beside : 1), heads = (long long)B * H;
   const int kq = heads * ((T + 15) / 16) <= share ? 1 : heads * ((T + 31) / 32) <= share ? 2 : 0;
   const int qb = B * H * ((T + 127) / 128) <= 256 ? 1 : 2;
