@@ -36,21 +36,21 @@ TRAFFIC = {
     # profiles/sampler_cfg1_dit_xl2_b8_hbm_traffic.txt: (FETCH_SIZE * 2.0 + WRITE_SIZE * 1.0) KiB per dispatch
     ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc2"): (16857.1 * 2.0 + 9216.0) * 1024,
     ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_qkv"): (9091.8 * 2.0 + 13824.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc1"): (16083.0 * 2.0 + 4608.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_fc1"): (16084.7 * 2.0 + 4608.0) * 1024,
     ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_proj"): (6139.1 * 2.0 + 9216.0) * 1024,
-    ("dit_xl2_256_w8a8_b8_ddim50_n2", "attention"): (7041.6 * 2.0 + 1536.0) * 1024,
+    ("dit_xl2_256_w8a8_b8_ddim50_n2", "attention"): (7025.5 * 2.0 + 1536.0) * 1024,
     # profiles/sampler_cfg2_dit_xl2_b64_cfg_hbm_traffic.txt
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc2"): (145318.4 * 2.0 + 147461.5) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_qkv"): (54015.1 * 2.0 + 223446.1) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc1"): (52168.7 * 2.0 + 73728.1) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_proj"): (59871.5 * 2.0 + 147466.1) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "attention"): (128468.0 * 2.0 + 24576.0) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc2"): (145852.7 * 2.0 + 147460.5) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_qkv"): (54077.2 * 2.0 + 223664.9) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc1"): (52103.4 * 2.0 + 73737.8) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_proj"): (60238.4 * 2.0 + 147464.9) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "attention"): (128674.8 * 2.0 + 24576.0) * 1024,
     # profiles/sampler_cfg3_dit_xl2_512_b16_hbm_traffic.txt
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc2"): (67308.2 * 2.0 + 73750.2) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_qkv"): (25595.1 * 2.0 + 111346.3) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc1"): (26196.8 * 2.0 + 36864.1) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_proj"): (29807.0 * 2.0 + 73734.2) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "attention"): (65423.1 * 2.0 + 12288.0) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc2"): (67547.2 * 2.0 + 73743.5) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_qkv"): (25168.5 * 2.0 + 111494.0) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc1"): (26208.7 * 2.0 + 36914.4) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_proj"): (29750.4 * 2.0 + 73736.2) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "attention"): (65417.4 * 2.0 + 12288.0) * 1024,
     # profiles/clustering_tap1_counters.txt
     ("tap1", "similarity"): (1600218.9 * 2.0 + 231013.5) * 1024,
 }
