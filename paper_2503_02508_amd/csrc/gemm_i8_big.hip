@@ -767,15 +767,19 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   const bool eight = TM == 8 && tiles_n >= 12 && a.K >= 960 && (tiles_m % 8 == 0 || tiles_m >= 64) &&
                      (EPI != EPI_F32 || ((a.ldy & 31) == 0 && tiles >= 1500));
   b.group_m = eight ? 8 : std::min(std::max(64 / tiles_n, 1), 32 / TM);
-  // Streaming stores for Q and K.  A wavefront's 64 columns cut the rows of heads of 72 features into pieces of 128-byte lines, which streaming
-  // stores send to memory one by one and others let meet in the L2.  Heads of whole lines are cut into whole lines; those stream where the results of
-  // all launches that run together are more than half of the memory-side cache, from which attention would read what fits.  Whole runs, 12 blocks,
-  // 4 steps, 256 tokens, two halves, ms, streaming | not (MB of all results): heads of 72, width 1152: 64 latents (226) 13.00 | 12.69, 128 (453)
-  // 24.42 | 24.36, 256 (906) 48.7 | 49.0; heads of 64, width 768: 32 (75) 4.48 | 4.47, 64 (151) 7.58 | 7.75, 96 10.86 | 11.00, 256 (604) 27.7 | 28.1,
-  // width 384: 64 (75) 3.76 | 3.73, 128 (151) 6.45 | 6.50, 512 (604) 24.0 | 24.7, width 1152: 64 (226) 12.72 | 12.76, 128 24.2 | 24.4.  Ragged tiles, 425
-  // tokens: 72, 10 and 16 latents 5.07 | 5.05, 7.31 | 7.27, 76 27.9 | 28.0; 64, width 768, 16 latents 4.62 | 4.58, 76 equal.
+  // Streaming stores for Q and K, by the results of all launches that run together.  Heads of whole 128-byte lines (a wavefront's 64 columns cut their
+  // rows into whole lines): above half of the memory-side cache, from which attention would read what fits.  Other heads (72 features: pieces of lines,
+  // which streaming stores send to memory one by one and others let meet in the L2): not before the results are nearly twice that cache.
+  // Whole runs, 12 blocks, 4 steps, 256 tokens, two halves, ms, streaming | not (MB of all results): heads of 64, width 768: 32 latents (75) 4.48 | 4.47,
+  // 64 (151) 7.58 | 7.75, 96 10.86 | 11.00, 256 (604) 27.7 | 28.1, width 384: 64 (75) 3.76 | 3.73, 128 (151) 6.45 | 6.50, 512 (604) 24.0 | 24.7, width
+  // 1152: 64 (226) 12.72 | 12.76, 128 24.2 | 24.4; heads of 72, width 1152: 64 (226) 13.00 | 12.69, 96 (340) 18.48 | 18.40, 128 (453) 24.45 | 24.46,
+  // 192 (679) 36.75 | 36.81, 256 (906) 48.9 | 49.3, 64 of 1024 tokens (906) 67.8 | 68.1, 76 of 425 (447) 28.0 | 28.2; heads of 80, width 640, 256
+  // (503) 22.9 | 23.1.  Ragged tiles, 425 tokens: 72, 10 and 16 latents 5.07 | 5.05, 7.31 | 7.27; 64, width 768, 16 latents 4.62 | 4.58, 76 equal.
+  // One block alone, QKV and attention: 72, 65536 rows 340 + 358 | 327 + 369 us, 32768 178 + 187 | 163 + 189, 24576 141 + 144 | 124 + 142; 80, width 640, 65536 rows
+  // 134 + 201 | 155 + 202.  (With activations that fill the codes' range, which lowers the clock rate, 72, 32768 rows 186 + 239 | 182 + 239, and 177 + 238 with
+  // four tile rows a group and streaming: there this launch is 3 % slower than it could be.)
   if constexpr (EPI == EPI_QKV)
-    b.stream_qk = (a.hd & 31) == 0 && (size_t)std::max(a.beside, 1) * a.M * a.N * sizeof(float) > ((size_t)128 << 20);
+    b.stream_qk = (size_t)std::max(a.beside, 1) * a.M * a.N * sizeof(float) > ((size_t)((a.hd & 31) == 0 ? 128 : 448) << 20);
   hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), smem, st, b);
   return hipGetLastError();
 }
