@@ -208,7 +208,7 @@ __device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc<TM> &acc, unsi
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
     };
-    if (TM == 8 && p.stream_qk) rows_out(std::true_type{});    // (launches of 64-row tiles write at most 300 of them, 20 MB)
+    if (TM == 8 && p.stream_out) rows_out(std::true_type{});    // (launches of 64-row tiles write at most 300 of them, 20 MB)
     else rows_out(std::false_type{});
     return;
   }
@@ -357,7 +357,7 @@ __device__ __forceinline__ void big_resid(const GemmArgs &p, BigAcc<TM> &acc, un
   }
 }
 
-// float32 rows [M, ldy], any N and M.  NT: streaming stores (below), N a multiple of 4
+// float32 rows [M, ldy], any N and M.  NT: streaming stores
 template <int TM, bool NT>
 __device__ __forceinline__ void big_f32_rows(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
@@ -370,7 +370,7 @@ __device__ __forceinline__ void big_f32_rows(const GemmArgs &p, BigAcc<TM> &acc,
   for (int ip = 0; ip < TM; ip += 2) {
     QC_SB;
     big_stage_rows<TM>(acc, stage, cst, wn0, a_s, ip);
-    if (NT || (p.N & 3) == 0) {                               // whole groups of four columns
+    if ((p.N & 3) == 0) {                                     // whole groups of four columns
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const int m = ip * 16 + q * 4;
@@ -382,23 +382,17 @@ __device__ __forceinline__ void big_f32_rows(const GemmArgs &p, BigAcc<TM> &acc,
       for (int r = 0; r < 32; ++r) {
         const int m = ip * 16 + r;
         const unsigned v = *(const unsigned *)(stage + r * BIG_SR + lane);
-        if (lane < left && m < rows) __builtin_amdgcn_raw_buffer_store_b32(v, buf, lane * 4, m * p.ldy * 4, 0);
+        if (lane < left && m < rows) __builtin_amdgcn_raw_buffer_store_b32(v, buf, lane * 4, m * p.ldy * 4, NT ? 2 : 0);
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     QC_SB;
   }
 }
-// Streaming stores of parts of a 128-byte line reach memory one by one, others meet in the L2 first: rows that are no whole lines
-// go without, unless the result is larger than the memory-side cache and its rows whole groups of 16 bytes.  16384 rows, K = 1152, us,
-// streaming | not: N = 3460 106 | 93, 2308 78 | 68, 1160 47 | 43.5, 3333 119 | 103; 4600 124 | 128, 4100 118 | 118, 4603 140 | 132;
-// rows of whole lines: 4608 115.5 | 121, 1152 41.4 | 42.9, 2304 68 | 68.5.
 template <int TM>
 __device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
-  if ((p.N & 3) == 0 && ((p.ldy & 31) == 0 || (size_t)p.M * p.ldy * sizeof(float) > ((size_t)256 << 20)))
-    big_f32_rows<TM, true>(p, acc, smem, cst, m0, n0, a_s);
-  else
-    big_f32_rows<TM, false>(p, acc, smem, cst, m0, n0, a_s);
+  if (p.stream_out) big_f32_rows<TM, true>(p, acc, smem, cst, m0, n0, a_s);
+  else big_f32_rows<TM, false>(p, acc, smem, cst, m0, n0, a_s);
 }
 
 template <int TM, int EPI, int TAG, bool W4, bool RBF, bool RAG>
@@ -779,7 +773,21 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   // 134 + 201 | 155 + 202.  (With activations that fill the codes' range, which lowers the clock rate, 72, 32768 rows 186 + 239 | 182 + 239, and 177 + 238 with
   // four tile rows a group and streaming: there this launch is 3 % slower than it could be.)
   if constexpr (EPI == EPI_QKV)
-    b.stream_qk = (size_t)std::max(a.beside, 1) * a.M * a.N * sizeof(float) > ((size_t)((a.hd & 31) == 0 ? 128 : 448) << 20);
+    b.stream_out = (size_t)std::max(a.beside, 1) * a.M * a.N * sizeof(float) > ((size_t)((a.hd & 31) == 0 ? 128 : 448) << 20);
+  // Float32 rows of whole lines stream.  Others, cut into pieces, where the result, the codes and the float32 values that these were made from outgrow the
+  // memory-side cache, the sooner the longer a tile multiplies and the pieces' writes hide behind it (one float a lane, N no multiple of 4, hides
+  // them later).  16384 - 49152 rows, us with the quantiser, streaming | not (MB of all three, x K / 1000): N = 1160, 16384 rows, K = 1152 64.3 | 59.7 (170,
+  // 196), 24576 81.6 | 76.3 (255, 294), 32768 99.8 | 104.3 (341, 393), K = 768 86.3 | 79.4 (278, 213), 1408 107.6 | 117.3 (383, 539); N = 2308, 16384, K = 1152
+  // 92.9 | 84.5 (245, 282), 20480 111.4 | 110.3 (307, 354), 24576 127.4 | 131.0 (369, 425), 32768 158 | 172 (491, 566), 576 135.8 | 122.5 (397, 229), 12288, K =
+  // 2304 114.1 | 109.2 (255, 588); N = 3460, 16384, 1152 121.5 | 118.5 (321, 370), 1408 129.7 | 134.3 (342, 482), 32768 211 | 241 (643, 741); N = 4100, 16384 133.4 |
+  // 141.0 (363, 418), 24576, K = 704 165.2 | 163.0 (490, 345), 768 164.0 | 166.3 (497, 382); N = 4600, 16384, 896 133.9 | 131.7 (375, 336), 1152 138.5 | 149.1 (396, 456);
+  // N = 2309, 16384, 1152 104.8 | 93.3 (245, 282), 32768 179.5 | 179.4 (491, 566), 49152 256 | 288 (737, 849); N = 3333, 16384, 1152 134 | 127 (313, 360), 2304 179 |
+  // 187 (407, 937), 32768, 768 204 | 200 (563, 432), 1152 237 | 247 (626, 721).  Rows of whole lines, 16384: 4608 115.5 | 121, 1152 41.4 | 42.9, 2304 68 | 68.5.
+  if constexpr (EPI == EPI_F32) {
+    const double all = (double)a.M * (4.0 * a.N + 5.0 * a.K);
+    const int Kp = (a.K + BIG_BK - 1) / BIG_BK * BIG_BK;      // what a tile multiplies
+    b.stream_out = (a.ldy & 31) == 0 || (all > 3.0e8 && all * Kp > ((a.N & 3) == 0 ? 3.8e11 : 5.6e11));
+  }
   hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), smem, st, b);
   return hipGetLastError();
 }

@@ -102,7 +102,8 @@ def test_w8a8_linear_accumulators_bit_exact(qc, bits, M, N, K):
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K", [(16385, 1155, 848), (4001, 3460, 1168), (8192, 2048, 1024),
                                    (16384, 4608, 1920),         # groups of eight tile rows, the last one of five or six
-                                   (16384, 4600, 1152)])        # a result above 256 MiB, rows of whole groups of 16 bytes but not of whole lines
+                                   # rows that are no whole lines: streamed in groups of 16 bytes and in single values, and in groups not streamed
+                                   (16384, 4600, 1152), (49152, 1155, 1168), (16384, 1160, 1152)])
 def test_w8a8_linear_large(qc, bits, M, N, K):
     """Large products, with the large-M kernel where its rule takes them (the first and the last, when no accumulators are asked
     for): partial tiles in every direction, and whole ones, equal to the tile kernel bit for bit and to exact sums of sampled rows."""
