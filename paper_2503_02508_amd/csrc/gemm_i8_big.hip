@@ -748,32 +748,36 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   // 4608 columns, K = 512 92.2 | 95.9, 640 99.2 | 102.2, 768 106.7 | 108.2, 896 115.1 | 113.1, 1008 125.8 | 123.9, 1152 130.5 | 126.8, 1408 148.7 | 143.0;
   // 3456, K = 768 85.6 | 87.1, 896 91.6 | 92.0, 1008 102.1 | 101.8, 1152 105.1 | 104.4; packed weights, 4608, K = 768 105.4 | 106.1, 1152 136.8 |
   // 136.0, 2304 220.0 | 218.5.  In a block fc1 of width 768, 32768 rows, 99.6 | 102.3.
-  // Networks of width 1152, one block by itself, us: QKV of 65536 rows 333 | 321, 32768 164 | 159, 16384 75.7 | 80.2 (without attention beside or
-  // behind it 82 | 82), 8192 42.2 | 41.8; fc1 367 | 365, 185.8 | 185.4, 96.6 | 99.3, 55.9 | 54.6;
-  // packed weights, 16384 rows 100.5 | 104.1, 4096 34.7 | 33.0.  What decides is the run, whose halves share the caches: 128 guided
-  // latents of 256 tokens (9 steps, 28 blocks) 88.9 ms with 4 rows, 88.7 with 8; 12 blocks, 4 steps: 32 latents 6.85 | 6.81, 64 12.38 | 12.42, 96 18.28 | 18.18,
-  // 128 24.29 | 24.21, 256 equal, 76 of 425 tokens 27.82 | 27.77.
+  // fc1 of networks of width 1152, one block by itself, us: 65536 rows 367 | 365, 32768 185.8 | 185.4, 16384 96.6 | 99.3, 8192 55.9 | 54.6; packed weights, 16384
+  // rows 100.5 | 104.1, 4096 34.7 | 33.0.  What decides is the run, whose halves share the caches: 128 guided latents of 256 tokens (9 steps, 28
+  // blocks, QKV too) 88.9 ms with 4 rows, 88.7 with 8; 12 blocks, 4 steps: 32 latents 6.85 | 6.81, 64 12.38 | 12.42, 96 18.28 | 18.18, 128 24.29 | 24.21.
+  // QKV takes 4 there, which 8 do not beat in a run and are slower than where Q and K stream.  A block's launch, width 1152, us, 4 rows | 8, without
+  // streaming: 8192 rows 43.8 | 43.2, 16384 79.4 | 81.4, 24576 142 | 145, 28672 166 | 163, 32768 184 | 186 (166 | 164 on a chip that holds its clocks), 65536
+  // 339 | 329; streaming: 16384 90 | 98, 32768 181 | 190 (166 | 174), 65536 equal.  Runs of 12 blocks, 4 steps, fc1 with 8: 24 latents 5.71 | 5.71 ms, 32 6.94 | 6.96,
+  // 64 12.73 | 12.82, 96 18.63 | 18.60, 128 24.72 | 24.79, 256 49.4 | 49.4, 32 of 1024 tokens 35.07 | 35.00, 76 of 425 28.64 | 28.59; wider networks, 3 (2) | 4 | 8: width 1536,
+  // 6 blocks, 32 latents 5.32 | 5.25 | 5.25, 64 10.39 | 10.34 | 10.40, 128 20.44 | 20.39 | 20.37; 2048, 4 blocks, 32 5.79 | 5.71 | 5.73, 64 11.48 | 11.37 | 11.36, 128 22.20 |
+  // 21.96 | 22.21.
   // Not where the last group is a good part of the rows (M = 4250 25.0 | 25.6), nor for float32 results whose rows are no whole lines, whose pieces
   // then meet later (16300 x 4600 x 1008 127 | 131, 32000 x 3300 x 400 151 | 159), or of fewer than some 1500 tiles (K = 1152, 4608 columns, 8192 rows
   // 80.9 | 81.3, 13000 106.9 | 107.9, 14336 117.7 | 117.2, 24576 186.8 | 182.9; 3456, 12288 90.2 | 91.2, 14336 94.7 | 94.5, 17000 113.7 | 111.8; 4096 columns
   // lose up to 1 % below 3000 tiles: 16384 118.0 | 119.0, 24576 164.7 | 163.8).  64-row tiles gain and lose 2 % by shape and stay.
   const int tiles_m = tiles / tiles_n;
-  const bool eight = TM == 8 && tiles_n >= 12 && a.K >= 960 && (tiles_m % 8 == 0 || tiles_m >= 64) &&
-                     (EPI != EPI_F32 || ((a.ldy & 31) == 0 && tiles >= 1500));
-  b.group_m = eight ? 8 : std::min(std::max(64 / tiles_n, 1), 32 / TM);
+  const bool wide = TM == 8 && tiles_n >= 12 && a.K >= 960 && (tiles_m % 8 == 0 || tiles_m >= 64) &&
+                    (EPI != EPI_F32 || ((a.ldy & 31) == 0 && tiles >= 1500));
+  b.group_m = wide ? (EPI == EPI_QKV ? 4 : 8) : std::min(std::max(64 / tiles_n, 1), 32 / TM);
   // Streaming stores for Q and K, by the results of all launches that run together.  Heads of whole 128-byte lines (a wavefront's 64 columns cut their
   // rows into whole lines): above half of the memory-side cache, from which attention would read what fits.  Other heads (72 features: pieces of lines,
-  // which streaming stores send to memory one by one and others let meet in the L2): not before the results are nearly twice that cache.
+  // which streaming stores send to memory one by one and others let meet in the L2): not before the results are 1.4 times that cache.
   // Whole runs, 12 blocks, 4 steps, 256 tokens, two halves, ms, streaming | not (MB of all results): heads of 64, width 768: 32 latents (75) 4.48 | 4.47,
   // 64 (151) 7.58 | 7.75, 96 10.86 | 11.00, 256 (604) 27.7 | 28.1, width 384: 64 (75) 3.76 | 3.73, 128 (151) 6.45 | 6.50, 512 (604) 24.0 | 24.7, width
-  // 1152: 64 (226) 12.72 | 12.76, 128 24.2 | 24.4; heads of 72, width 1152: 64 (226) 13.00 | 12.69, 96 (340) 18.48 | 18.40, 128 (453) 24.45 | 24.46,
-  // 192 (679) 36.75 | 36.81, 256 (906) 48.9 | 49.3, 64 of 1024 tokens (906) 67.8 | 68.1, 76 of 425 (447) 28.0 | 28.2; heads of 80, width 640, 256
-  // (503) 22.9 | 23.1.  Ragged tiles, 425 tokens: 72, 10 and 16 latents 5.07 | 5.05, 7.31 | 7.27; 64, width 768, 16 latents 4.62 | 4.58, 76 equal.
-  // One block alone, QKV and attention: 72, 65536 rows 340 + 358 | 327 + 369 us, 32768 178 + 187 | 163 + 189, 24576 141 + 144 | 124 + 142; 80, width 640, 65536 rows
-  // 134 + 201 | 155 + 202.  (With activations that fill the codes' range, which lowers the clock rate, 72, 32768 rows 186 + 239 | 182 + 239, and 177 + 238 with
-  // four tile rows a group and streaming: there this launch is 3 % slower than it could be.)
+  // 1152: 64 (226) 12.72 | 12.76, 128 24.2 | 24.4; heads of 72, width 1152: 64 (226) 12.93 | 12.71, 96 (340) 18.79 | 18.65, 104 (368) 20.44 | 20.48,
+  // 120 (425) 23.49 | 23.59, 128 (453) 24.83 | 24.87, 136 (481) 26.75 | 26.92, 192 (679) 37.40 | 37.47, 60 of 425 tokens (353) 22.51 | 22.55, 68 (400) 25.76 | 25.88, 76 (447)
+  // 28.56 | 28.65; heads of 80, width 640, 192 (377) 17.68 | 17.76, 224 (440) 20.55 | 20.69, 256 (503) 23.22 | 23.44.
+  // Ragged tiles, 425 tokens: 72, 10 and 16 latents 5.07 | 5.05, 7.31 | 7.27; 64, width 768, 16 latents 4.62 | 4.58, 76 equal.
+  // One block alone, QKV and attention, us: 72, 16384 rows 90 + 114 | 79 + 114, 24576 145 + 189 | 142 + 191, 28672 166 + 216 | 166 + 216, 32768 181 + 241 | 184 + 242
+  // (on a chip that holds its clocks 166 + 229 | 166 + 230), 40960 226 + 291 | 224 + 292, 65536 338 + 440 | 339 + 449.
   if constexpr (EPI == EPI_QKV)
-    b.stream_out = (size_t)std::max(a.beside, 1) * a.M * a.N * sizeof(float) > ((size_t)((a.hd & 31) == 0 ? 128 : 448) << 20);
+    b.stream_out = (size_t)std::max(a.beside, 1) * a.M * a.N * sizeof(float) > ((size_t)((a.hd & 31) == 0 ? 128 : 352) << 20);
   // Float32 rows of whole lines stream.  Others, cut into pieces, where the result, the codes and the float32 values that these were made from outgrow the
   // memory-side cache, the sooner the longer a tile multiplies and the pieces' writes hide behind it (one float a lane, N no multiple of 4, hides
   // them later).  16384 - 49152 rows, us with the quantiser, streaming | not (MB of all three, x K / 1000): N = 1160, 16384 rows, K = 1152 64.3 | 59.7 (170,
