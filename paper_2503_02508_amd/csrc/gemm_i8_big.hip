@@ -171,7 +171,9 @@ __device__ __forceinline__ void big_gelu(const GemmArgs &p, BigAcc<TM> &acc, uns
   }
 }
 
-template <int TM, bool RAG>
+// NT: streaming stores for Q and K.  A kernel of its own: with both ways in one, chosen by an argument (3890 instructions instead of 3044), 16 latents of
+// 1024 tokens (28 blocks, 10 steps) took 0.1 - 0.4 % more than with a kernel that knew one way; now 99.6 | 99.7 ms.
+template <int TM, bool RAG, bool NT>
 __device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc<TM> &acc, unsigned char *smem, const float *cst, int m0, int n0, float a_s) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn0 = wave * 64, row = lane & 15, g = lane >> 4;
   if (n0 + wn0 >= p.N) return;
@@ -189,27 +191,23 @@ __device__ __forceinline__ void big_qkv(const GemmArgs &p, BigAcc<TM> &acc, unsi
     const auto buf = __builtin_amdgcn_make_buffer_rsrc((part == 0 ? p.q32 : p.k32) + (size_t)b * T * D, 0, -1, 0x00027000);
     const int col = row * 4, nn = nn0 + col, h = head_of(nn), e = nn - h * p.hd;
     const int off = ((h * T + tb + g) * p.hd + e) * 4;
-    const auto rows_out = [&](auto nt) {
 #pragma unroll
-      for (int ip = 0; ip < TM; ip += 2) {
-        big_stage_rows<TM>(acc, stage, cst, wn0, a_s, ip);
+    for (int ip = 0; ip < TM; ip += 2) {
+      big_stage_rows<TM>(acc, stage, cst, wn0, a_s, ip);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const v4u v = *(const v4u *)(stage + (q * 4 + g) * BIG_SR + col);
-          const int m = ip * 16 + q * 4;
-          if (!RAG) {
-            big_store16(v, buf, off + m * p.hd * 4, decltype(nt)::value);
-          } else {
-            // row beyond the first batch element: its token 0 lies (heads - 1) * T tokens further than the next row would
-            const int o = off + (m + (m + g >= bnd ? (p.heads - 1) * T : 0)) * p.hd * 4;
-            if (m + g < rows) big_store16(v, buf, o, decltype(nt)::value);
-          }
+      for (int q = 0; q < 8; ++q) {
+        const v4u v = *(const v4u *)(stage + (q * 4 + g) * BIG_SR + col);
+        const int m = ip * 16 + q * 4;
+        if (!RAG) {
+          big_store16(v, buf, off + m * p.hd * 4, NT);
+        } else {
+          // row beyond the first batch element: its token 0 lies (heads - 1) * T tokens further than the next row would
+          const int o = off + (m + (m + g >= bnd ? (p.heads - 1) * T : 0)) * p.hd * 4;
+          if (m + g < rows) big_store16(v, buf, o, NT);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       }
-    };
-    if (TM == 8 && p.stream_out) rows_out(std::true_type{});    // (launches of 64-row tiles write at most 300 of them, 20 MB)
-    else rows_out(std::false_type{});
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
     return;
   }
   // V^T: 64 tokens of the wavefront's 64 features at a time
@@ -395,6 +393,7 @@ __device__ __forceinline__ void big_f32(const GemmArgs &p, BigAcc<TM> &acc, unsi
   else big_f32_rows<TM, false>(p, acc, smem, cst, m0, n0, a_s);
 }
 
+// RBF: the residual epilogue's bfloat16 tensors; for Q | K | V streaming stores
 template <int TM, int EPI, int TAG, bool W4, bool RBF, bool RAG>
 __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   static_assert(TM == 8 || TM == 4, "");
@@ -721,7 +720,7 @@ __global__ __launch_bounds__(256, 2) void gemm_i8_big_kernel(GemmArgs p) {
   QC_SB;
   __syncthreads();
   if constexpr (EPI == EPI_GELU_Q) big_gelu<TM>(p, acc, smem, cst, m0, n0, a_s);
-  else if constexpr (EPI == EPI_QKV) big_qkv<TM, RAG>(p, acc, smem, cst, m0, n0, a_s);
+  else if constexpr (EPI == EPI_QKV) big_qkv<TM, RAG, RBF>(p, acc, smem, cst, m0, n0, a_s);
   else if constexpr (EPI == EPI_F32) big_f32<TM>(p, acc, smem, cst, m0, n0, a_s);
   else big_resid<TM, RBF, RAG>(p, acc, smem, cst, m0, n0, a_s);
 }
@@ -765,19 +764,6 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   const bool wide = TM == 8 && tiles_n >= 12 && a.K >= 960 && (tiles_m % 8 == 0 || tiles_m >= 64) &&
                     (EPI != EPI_F32 || ((a.ldy & 31) == 0 && tiles >= 1500));
   b.group_m = wide ? (EPI == EPI_QKV ? 4 : 8) : std::min(std::max(64 / tiles_n, 1), 32 / TM);
-  // Streaming stores for Q and K, by the results of all launches that run together.  Heads of whole 128-byte lines (a wavefront's 64 columns cut their
-  // rows into whole lines): above half of the memory-side cache, from which attention would read what fits.  Other heads (72 features: pieces of lines,
-  // which streaming stores send to memory one by one and others let meet in the L2): not before the results are 1.4 times that cache.
-  // Whole runs, 12 blocks, 4 steps, 256 tokens, two halves, ms, streaming | not (MB of all results): heads of 64, width 768: 32 latents (75) 4.48 | 4.47,
-  // 64 (151) 7.58 | 7.75, 96 10.86 | 11.00, 256 (604) 27.7 | 28.1, width 384: 64 (75) 3.76 | 3.73, 128 (151) 6.45 | 6.50, 512 (604) 24.0 | 24.7, width
-  // 1152: 64 (226) 12.72 | 12.76, 128 24.2 | 24.4; heads of 72, width 1152: 64 (226) 12.93 | 12.71, 96 (340) 18.79 | 18.65, 104 (368) 20.44 | 20.48,
-  // 120 (425) 23.49 | 23.59, 128 (453) 24.83 | 24.87, 136 (481) 26.75 | 26.92, 192 (679) 37.40 | 37.47, 60 of 425 tokens (353) 22.51 | 22.55, 68 (400) 25.76 | 25.88, 76 (447)
-  // 28.56 | 28.65; heads of 80, width 640, 192 (377) 17.68 | 17.76, 224 (440) 20.55 | 20.69, 256 (503) 23.22 | 23.44.
-  // Ragged tiles, 425 tokens: 72, 10 and 16 latents 5.07 | 5.05, 7.31 | 7.27; 64, width 768, 16 latents 4.62 | 4.58, 76 equal.
-  // One block alone, QKV and attention, us: 72, 16384 rows 90 + 114 | 79 + 114, 24576 145 + 189 | 142 + 191, 28672 166 + 216 | 166 + 216, 32768 181 + 241 | 184 + 242
-  // (on a chip that holds its clocks 166 + 229 | 166 + 230), 40960 226 + 291 | 224 + 292, 65536 338 + 440 | 339 + 449.
-  if constexpr (EPI == EPI_QKV)
-    b.stream_out = (size_t)std::max(a.beside, 1) * a.M * a.N * sizeof(float) > ((size_t)((a.hd & 31) == 0 ? 128 : 352) << 20);
   // Float32 rows of whole lines stream.  Others, cut into pieces, where the result, the codes and the float32 values that these were made from outgrow the
   // memory-side cache, the sooner the longer a tile multiplies and the pieces' writes hide behind it (one float a lane, N no multiple of 4, hides
   // them later).  16384 - 49152 rows, us with the quantiser, streaming | not (MB of all three, x K / 1000): N = 1160, 16384 rows, K = 1152 64.3 | 59.7 (170,
@@ -833,10 +819,30 @@ static hipError_t launch_big_w(const GemmArgs &a, hipStream_t st) {
   return a.w4 ? launch_big_as<8, EPI, TAG, true, RBF>(a, st) : launch_big_as<8, EPI, TAG, false, RBF>(a, st);
 }
 
+// Streaming stores for Q and K, by the results of all launches that run together.  Heads of whole 128-byte lines (a wavefront's 64 columns cut their
+// rows into whole lines): above half of the memory-side cache, from which attention would read what fits.  Other heads (72 features: pieces of lines,
+// which streaming stores send to memory one by one and others let meet in the L2): not before the results are 1.5 times that cache,
+// and 1.75 times where halves run beside each other, which at less gain nothing by it or lose a little.
+// Whole runs, 12 blocks, 4 steps, 256 tokens, two halves, ms, streaming | not (MB of all results): heads of 64, width 768: 32 latents (75) 4.48 | 4.47,
+// 64 (151) 7.58 | 7.75, 96 10.86 | 11.00, 256 (604) 27.7 | 28.1, width 384: 64 (75) 3.76 | 3.73, 128 (151) 6.45 | 6.50, 512 (604) 24.0 | 24.7, width
+// 1152: 64 (226) 12.72 | 12.76, 128 24.2 | 24.4; heads of 72, width 1152: 64 (226) 12.93 | 12.71, 96 (340) 18.79 | 18.65, 112 (396) 21.92 | 21.96,
+// 128 (453) 24.83 | 24.87, 136 (481) 26.75 | 26.92, 192 (679) 37.40 | 37.47, 76 of 425 tokens (447) 28.56 | 28.65, 30 and 32 of 1024 (425, 453) 32.82 | 32.76, 34.80 | 34.67;
+// 28 blocks, 6 steps, guided: 56 (396) 53.53 | 53.47, 60 (425) 57.54 | 57.59, 64 (453, 9 steps) 90.79 | 90.74, 72 (510) 68.69 | 68.91; heads of 80, width 640, 192 (377) 17.68 |
+// 17.76, 256 (503) 23.22 | 23.44.
+// Ragged tiles, 425 tokens: 72, 10 and 16 latents 5.07 | 5.05, 7.31 | 7.27; 64, width 768, 16 latents 4.62 | 4.58, 76 equal.
+// One block alone, QKV and attention, us: 72, 16384 rows 90 + 114 | 79 + 114, 24576 145 + 189 | 142 + 191, 28672 166 + 216 | 166 + 216, 32768 181 + 241 | 184 + 242
+// (on a chip that holds its clocks 166 + 229 | 166 + 230), 40960 226 + 291 | 224 + 292, 65536 338 + 440 | 339 + 449.
+static bool qkv_streams(const GemmArgs &a) {
+  const size_t limit = (a.hd & 31) == 0 ? 128 : a.beside > 1 ? 448 : 384;          // MiB
+  return big_rows(a) == 128 && (size_t)std::max(a.beside, 1) * a.M * a.N * sizeof(float) > limit << 20;      // (64-row tiles: at most 300 of them, 20 MB)
+}
+
 // `site` only names the instantiation (so that profiles tell the linears apart); the residual epilogue is compiled twice,
 // for float32 stream and cache and for the bfloat16 variants of either
 hipError_t launch_gemm_big(const GemmArgs &a, int epi, hipStream_t st, int site) {
   if (epi == EPI_GELU_Q) return launch_big_w<EPI_GELU_Q, QC_SITE_FC1, false>(a, st);
+  if (epi == EPI_QKV && qkv_streams(a))
+    return a.w4 ? launch_big_as<8, EPI_QKV, QC_SITE_QKV, true, true>(a, st) : launch_big_as<8, EPI_QKV, QC_SITE_QKV, false, true>(a, st);
   if (epi == EPI_QKV) return launch_big_w<EPI_QKV, QC_SITE_QKV, false>(a, st);
   if (a.x_bf16 || a.cache_bf16)
     return site == QC_SITE_FC2 ? launch_big_w<EPI_RESID, QC_SITE_FC2, true>(a, st) : launch_big_w<EPI_RESID, QC_SITE_PROJ, true>(a, st);

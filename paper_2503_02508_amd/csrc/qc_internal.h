@@ -67,7 +67,7 @@ struct GemmArgs {
   int xcd_m;                 // XCD grid rows (set by the launcher)
   int group_m;               // large-M kernel: tile rows per group of its tile order (set by the launcher)
   int beside;                // launches of this kind that run at the same time, this one included (0: this one)
-  int stream_out;            // large-M kernel: streaming stores for Q and K, or for float32 rows (set by the launcher)
+  int stream_out;            // large-M kernel: streaming stores for float32 rows (set by the launcher)
   // EPI_F32
   float *y;
   int ldy;

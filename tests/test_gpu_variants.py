@@ -192,7 +192,7 @@ def test_64_row_tiles_equal_the_small_launches(hw, B, cache, stream):
                                      (_net(1152, 16, 4608, 50, 34), 41),
                                      # Q | K | V of both halves above 128 MiB: streaming stores, whole tiles and ragged ones
                                      (_net(384, 6, 1536, 32, 32), 115), (_net(384, 12, 1536, 50, 34), 69),
-                                     # above 352 MiB, heads that are no whole lines
+                                     # above 448 MiB, heads that are no whole lines
                                      (_net(1152, 16, 4608, 32, 32), 133), (_net(1152, 16, 4608, 50, 34), 81)])
 def test_halves_of_a_large_batch(model, B):
     """More than 4096 rows in two concurrent halves: each latent as it comes out alone, eager and in a replayed graph."""
