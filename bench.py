@@ -40,17 +40,17 @@ TRAFFIC = {
     ("dit_xl2_256_w8a8_b8_ddim50_n2", "gemm_proj"): (6139.1 * 2.0 + 9216.0) * 1024,
     ("dit_xl2_256_w8a8_b8_ddim50_n2", "attention"): (7025.5 * 2.0 + 1536.0) * 1024,
     # profiles/sampler_cfg2_dit_xl2_b64_cfg_hbm_traffic.txt
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc2"): (145852.7 * 2.0 + 147460.5) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_qkv"): (54077.2 * 2.0 + 223664.9) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc1"): (52103.4 * 2.0 + 73737.8) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_proj"): (60238.4 * 2.0 + 147464.9) * 1024,
-    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "attention"): (128674.8 * 2.0 + 24576.0) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc2"): (145866.2 * 2.0 + 147461.2) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_qkv"): (74442.8 * 2.0 + 223683.1) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_fc1"): (52164.6 * 2.0 + 73731.2) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "gemm_proj"): (60166.9 * 2.0 + 147464.5) * 1024,
+    ("dit_xl2_256_w8a8_b64_cfg_ddim100_n3", "attention"): (128711.6 * 2.0 + 24576.0) * 1024,
     # profiles/sampler_cfg3_dit_xl2_512_b16_hbm_traffic.txt
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc2"): (67547.2 * 2.0 + 73743.5) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_qkv"): (25168.5 * 2.0 + 111494.0) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc1"): (26208.7 * 2.0 + 36914.4) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_proj"): (29750.4 * 2.0 + 73736.2) * 1024,
-    ("dit_xl2_512_w8a8_b16_ddim50_n2", "attention"): (65417.4 * 2.0 + 12288.0) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc2"): (67959.2 * 2.0 + 73750.8) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_qkv"): (36390.5 * 2.0 + 111304.8) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_fc1"): (26245.0 * 2.0 + 36886.7) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "gemm_proj"): (29830.8 * 2.0 + 73734.3) * 1024,
+    ("dit_xl2_512_w8a8_b16_ddim50_n2", "attention"): (65413.8 * 2.0 + 12288.0) * 1024,
     # profiles/clustering_tap1_counters.txt
     ("tap1", "similarity"): (1600218.9 * 2.0 + 231013.5) * 1024,
 }
