@@ -769,14 +769,14 @@ static hipError_t launch_big_as(const GemmArgs &a, hipStream_t st) {
   // them later).  16384 - 49152 rows, us with the quantiser, streaming | not (MB of all three, x K / 1000): N = 1160, 16384 rows, K = 1152 64.3 | 59.7 (170,
   // 196), 24576 81.6 | 76.3 (255, 294), 32768 99.8 | 104.3 (341, 393), K = 768 86.3 | 79.4 (278, 213), 1408 107.6 | 117.3 (383, 539); N = 2308, 16384, K = 1152
   // 92.9 | 84.5 (245, 282), 20480 111.4 | 110.3 (307, 354), 24576 127.4 | 131.0 (369, 425), 32768 158 | 172 (491, 566), 576 135.8 | 122.5 (397, 229), 12288, K =
-  // 2304 114.1 | 109.2 (255, 588); N = 3460, 16384, 1152 121.5 | 118.5 (321, 370), 1408 129.7 | 134.3 (342, 482), 32768 211 | 241 (643, 741); N = 4100, 16384 133.4 |
-  // 141.0 (363, 418), 24576, K = 704 165.2 | 163.0 (490, 345), 768 164.0 | 166.3 (497, 382); N = 4600, 16384, 896 133.9 | 131.7 (375, 336), 1152 138.5 | 149.1 (396, 456);
+  // 2304 114.1 | 109.2 (255, 588); N = 3460, 16384, 1152 126.0 | 127.4 (321, 370; other inputs each pass), 1408 129.7 | 134.3 (342, 482), 32768 211 | 241 (643, 741); N = 4100, 16384 133.4 |
+  // 141.0 (363, 418), 24576, K = 704 168.3 | 169.7 (490, 376; the same), 768 164.0 | 166.3 (497, 382); N = 4600, 16384, 896 133.9 | 131.7 (375, 336), 1152 138.5 | 149.1 (396, 456);
   // N = 2309, 16384, 1152 104.8 | 93.3 (245, 282), 32768 179.5 | 179.4 (491, 566), 49152 256 | 288 (737, 849); N = 3333, 16384, 1152 134 | 127 (313, 360), 2304 179 |
   // 187 (407, 937), 32768, 768 204 | 200 (563, 432), 1152 237 | 247 (626, 721).  Rows of whole lines, 16384: 4608 115.5 | 121, 1152 41.4 | 42.9, 2304 68 | 68.5.
   if constexpr (EPI == EPI_F32) {
     const double all = (double)a.M * (4.0 * a.N + 5.0 * a.K);
     const int Kp = (a.K + BIG_BK - 1) / BIG_BK * BIG_BK;      // what a tile multiplies
-    b.stream_out = (a.ldy & 31) == 0 || (all > 3.0e8 && all * Kp > ((a.N & 3) == 0 ? 3.8e11 : 5.6e11));
+    b.stream_out = (a.ldy & 31) == 0 || (all > 3.0e8 && all * Kp > ((a.N & 3) == 0 ? 3.65e11 : 5.6e11));
   }
   hipLaunchKernelGGL(kern, dim3(((tiles + 7) / 8) * 8), dim3(256), smem, st, b);
   return hipGetLastError();
